@@ -22,7 +22,9 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 PEAK_MFMA_F16_TFLOPS = 2500.0      # MI355X dense fp16 matrix peak
+PEAK_MFMA_I8_TOPS = 5000.0         # MI355X dense int8 matrix peak
 PEAK_HBM_GBS = 8000.0
+SKETCH_DIMS = 64                    # bytes of a token's sketch: multiply-adds per pair of tokens of the scan
 PEAK_VALU_F64_TFLOPS = 78.6         # 256 CUs x 64 lanes x 2 flop x 2.4 GHz
 
 
@@ -149,12 +151,12 @@ def config5_layer(torch, sb, wl, cap=4096, steps=8, warmup=3):
     deep_ms = time_deep_call(torch, deep, K, V, Q, reps=10)
     units = L.batch * L.n_kv_heads
     nbytes = deep_bytes(units, L.seq_len, L.head_dim, 2, min(L.budget, L.seq_len))
-    gram_flop = 2 * units * (L.seq_len ** 2 / 2) * L.head_dim * 2
+    scan_ops = 2 * units * (L.seq_len ** 2 / 2) * SKETCH_DIMS * 2
     assert min(shallow.out["n_codes_k"].min().item(), shallow.out["n_codes_v"].min().item()) >= 1
     out = {"workload": f"configs[4], one layer: batch 4 x {L.seq_len}, bf16, pool 15, budget = cap = {cap}; one stream",
            "steps": steps, "ms_per_step": ms, "tokens_per_s": L.batch * L.seq_len / (ms * 1e-3), "kernel_ms": per,
            "deep_call_ms": deep_ms, "deep_frac_of_hbm": nbytes / (deep_ms * 1e-3) / 1e9 / PEAK_HBM_GBS,
-           "shallow_gram_frac_of_mfma": gram_flop / (per["shallow_gram"] * 1e-3) / 1e12 / PEAK_MFMA_F16_TFLOPS}
+           "shallow_scan_frac_of_mfma_i8": scan_ops / (per["shallow_scan"] * 1e-3) / 1e12 / PEAK_MFMA_I8_TOPS}
     del deep, shallow, K, V, Q
     torch.cuda.empty_cache()
     return out
@@ -265,7 +267,6 @@ def main():
                     help="run the library's matrix-core and similarity-loop calibrations even with --no-extras")
     ap.add_argument("--no-extras", action="store_true",
                     help="skip the secondary measurements (folded eviction call, config-5 layer, reconstruction, decode)")
-    ap.add_argument("--traffic-json", default=os.path.join(ROOT, "profiles", "shallow_gram_config4_traffic.json"))
     args = ap.parse_args()
     if args.gpus != 1:
         sys.exit("bench.py measures one GPU: this build has no multi-GPU path (run with --gpus 1)")
@@ -324,9 +325,9 @@ def main():
         step()
     drain()
     wall = time.perf_counter() - t0
-    gram_recs = [ms for name, ms in sb.spindle_profile_read() if name == "shallow_gram"]
-    assert len(gram_recs) == args.steps
-    gram_ms = float(np.mean(gram_recs))
+    scan_recs = [ms for name, ms in sb.spindle_profile_read() if name == "shallow_scan"]
+    assert len(scan_recs) == args.steps
+    scan_ms = float(np.mean(scan_recs))
     ms_step = wall * 1e3 / args.steps
 
     # for reference (not the reported throughput): the same steps one at a time, two streams within a step
@@ -371,21 +372,12 @@ def main():
 
     tokens = L.batch * L.seq_len
     units = L.batch * L.n_kv_heads
-    # dominant kernel: the similarity tiles.  Algorithmic work = each unordered token pair
-    # once: n^2/2 pairs x 128 multiply-adds x 2 flop, per (unit, K|V).
+    # the kernel that goes over all pairs of tokens: each unordered pair once, one product of
+    # two 64-byte sketches: n^2/2 pairs x 64 multiply-adds x 2, per (unit, K|V).
+    scan_ops = 2 * units * (L.seq_len ** 2 / 2) * SKETCH_DIMS * 2
+    achieved = scan_ops / (scan_ms * 1e-3) / 1e12
+    # what computing every cosine in fp16 would take (the calibration loop below does)
     gram_flop = 2 * units * (L.seq_len ** 2 / 2) * L.head_dim * 2
-    achieved = gram_flop / (gram_ms * 1e-3) / 1e12
-    # HBM bytes per launch of the dominant kernel: not measurable inside this process (it takes two
-    # rocprofv3 counter runs); read from the committed summary, with the source commit it names
-    traffic, traffic_source = None, None
-    if args.workload == "config4" and args.seq_len == 32768 and os.path.exists(args.traffic_json):
-        try:
-            tj = json.load(open(args.traffic_json))
-            traffic = tj.get("hbm_bytes_per_launch")
-            traffic_source = {"file": os.path.relpath(args.traffic_json, ROOT), "kernel": tj.get("kernel"),
-                              "measured_on_commit": tj.get("measured_on_commit")}
-        except Exception:
-            traffic = None
     out = {
         "metric": "KV tokens compressed/sec per layer (deep & shallow) at 32k ctx",
         "value": tokens / (ms_step * 1e-3),
@@ -419,12 +411,11 @@ def main():
         "codebook_entries_found": n_codes,
         "merge_rounds": st[:, 0].tolist(), "pairs_decided_in_f64": int(st[:, 2].sum()),
         "merge_phase_us_unit0": st[0, 4:14].tolist(),
-        "roofline": {"kernel": "shallow_gram", "bound": "mfma", "kernel_ms": gram_ms, "achieved": achieved,
-                     "peak": PEAK_MFMA_F16_TFLOPS, "unit": "TFLOP/s", "frac": achieved / PEAK_MFMA_F16_TFLOPS,
-                     "traffic": traffic, "traffic_source": traffic_source},
+        "roofline": {"kernel": "shallow_scan", "bound": "mfma int8", "kernel_ms": scan_ms, "achieved": achieved,
+                     "peak": PEAK_MFMA_I8_TOPS, "unit": "TOP/s", "frac": achieved / PEAK_MFMA_I8_TOPS},
     }
     # what the part sustains (measurement aids of the library): a register-resident fp16 MFMA loop, and
-    # the similarity kernel's own loop with the packing of the results left out
+    # a loop over all pairs that does nothing with the results
     if copy_gbs is not None:
         out["hbm_copy_measured"] = {"gb_per_s_read_plus_write": copy_gbs, "frac_of_peak": copy_gbs / PEAK_HBM_GBS,
                                     "bytes": 2 << 30}
@@ -438,15 +429,13 @@ def main():
             "mfma_f16_register_loop_tflops": mfma, "mfma_f16_register_loop_frac_of_peak": mfma / PEAK_MFMA_F16_TFLOPS,
             "mfma_f16_register_loop_workload_like_operands_tflops": mfma_data,
             "mfma_f16_register_loop_workload_like_operands_frac_of_peak": mfma_data / PEAK_MFMA_F16_TFLOPS,
-            "similarity_loop_without_packing_ms": float(np.mean(bare)),
-            "similarity_loop_without_packing_frac_of_peak": gram_flop / (float(np.mean(bare)) * 1e-3) / 1e12 / PEAK_MFMA_F16_TFLOPS,
-            "similarity_loop_without_packing_and_streaming_loads_ms": bare_nostream,
-            "similarity_loop_matrix_instructions_only_ms": bare_mfma,
-            "similarity_loop_matrix_instructions_only_frac_of_peak": gram_flop / (bare_mfma * 1e-3) / 1e12 / PEAK_MFMA_F16_TFLOPS,
-            "note": "without packing: the kernel's matrix instructions, staging and barriers alone; what is left "
-                    "between this and roofline.frac is the vector work on the results.  The next two leave out the "
-                    "loads that stream tokens into LDS, then also the fragment reads: the part is power-limited, "
-                    "and each of these draws from the same budget as the matrix instructions"}
+            "all_pairs_fp16_ms": float(np.mean(bare)),
+            "all_pairs_fp16_frac_of_peak": gram_flop / (float(np.mean(bare)) * 1e-3) / 1e12 / PEAK_MFMA_F16_TFLOPS,
+            "all_pairs_fp16_without_streaming_loads_ms": bare_nostream,
+            "all_pairs_fp16_matrix_instructions_only_ms": bare_mfma,
+            "all_pairs_fp16_matrix_instructions_only_frac_of_peak": gram_flop / (bare_mfma * 1e-3) / 1e12 / PEAK_MFMA_F16_TFLOPS,
+            "note": "all_pairs_fp16: every cosine of the layer by fp16 matrix instructions, results thrown away; the "
+                    "graph is built without it"}
     # secondary: the eviction call against the HBM roofline, timed on its own without events between
     # its kernels (deep_ms above is the breakdown pass, where every kernel is followed by an event gap)
     esz = K.element_size()

@@ -133,8 +133,8 @@ spindle_status spindle_compress_deep(const spindle_kv_desc *desc, const void *K,
 
 /*
  * Bytes of workspace spindle_compress_shallow needs when `n_tensors` (1 or 2) of
- * K, V are processed in one call.  Dominated by the bit-packed adjacency matrix:
- * seq_len^2 / 8 bytes per unit and tensor.
+ * K, V are processed in one call.  Dominated by the room for the neighbour lists of the densest
+ * graph: seq_len^2 / 8 bytes per unit and tensor.
  */
 spindle_status spindle_shallow_workspace_bytes(const spindle_kv_desc *desc, int32_t n_tensors,
                                                size_t *bytes);
@@ -180,7 +180,7 @@ spindle_status spindle_compress_shallow(const spindle_kv_desc *desc, const void 
  * spindle_compress_shallow in two halves, for a caller that overlaps other work with the
  * second one (e.g. the eviction call of another layer on a second stream that waits for an
  * event recorded between the two):
- *   spindle_shallow_graph     magnitudes, similarities, G, degrees and neighbour lists
+ *   spindle_shallow_graph     magnitudes, similarities, degrees and neighbour lists
  *                             (Eq. 4, 8-10): the phase that fills the chip.  Writes mag_*,
  *                             adj_* and deg_* if given, clears C* and sets n_codes_* to -1;
  *                             everything else goes to the workspace
@@ -241,8 +241,8 @@ spindle_status spindle_compress_shallow_layer(const spindle_kv_desc *desc, const
  * Diagnostics of the last spindle_compress_shallow call that used `workspace` with this
  * shape: for each of the batch * n_kv_heads * n_tensors problems i (all K units first,
  * then all V units), with s = stats + 16*i: s[0] = rounds of the parallel codebook
- * construction, s[1] = codebook entries found, s[2] = token pairs whose adjacency was
- * decided in double precision, s[4..13] = microseconds the workgroup that runs the later
+ * construction, s[1] = codebook entries found, s[2] = adjacency decisions taken in double
+ * precision (a pair of tokens is decided from each of its ends), s[4..13] = microseconds the workgroup that runs the later
  * rounds of the problem spent in their phases (s[4] loading keys and compacting the list of
  * remaining tokens, s[6] one-hop maxima, s[8] two-hop maxima and picks, s[10] degree updates,
  * s[12], s[13] bookkeeping; the odd slots in between are unused), others 0.  `stats` is a HOST
@@ -370,8 +370,9 @@ spindle_status spindle_reserve_ratio(int64_t kept_tokens, int64_t total_tokens, 
 
 /*
  * enable = 1: every kernel the library launches from now on is bracketed by a pair of HIP
- * events recorded on the stream it is launched on; enable = 2: only the similarity kernel of
- * spindle_compress_shallow ("shallow_gram") is; enable = 0 stops recording.  An event between
+ * events recorded on the stream it is launched on; enable = 2: only the kernel of
+ * spindle_compress_shallow that goes over all pairs of tokens ("shallow_scan") is; enable = 0 stops
+ * recording.  An event between
  * two kernels of a stream costs about 10 us of idle time on the GPU, so mode 1 lengthens a
  * step by some 5 % and is meant for breakdowns, mode 2 (two events per call) for measuring the
  * dominant kernel inside a timed run.  Every call discards the records collected so far.
@@ -395,20 +396,18 @@ int32_t spindle_profile_read(char *names, float *ms, int32_t max);
  *                                 rate of the matrix cores with no memory traffic and no other
  *                                 work, in TFLOP/s.  `pattern` 0: small non-negative operand
  *                                 values (few bits switch between instructions); 1: pseudo-random
- *                                 values with the signs and magnitudes of the similarity kernel's
- *                                 operands, which draw more power per instruction and so show the
+ *                                 values with the signs and magnitudes of fp16 unit vectors
+ *                                 (x 2^10), which draw more power per instruction and so show the
  *                                 clock the part sustains on such data.
- *   spindle_calibrate_similarity  the similarity kernel of spindle_compress_shallow run again on
- *                                 the unit vectors an earlier call with the same desc and n_tensors
- *                                 left in `workspace`, with the same staging, barriers and matrix
- *                                 instructions but without the packing of the results, and
- *                                 nothing written: its duration in milliseconds.  `mode` 0: as
- *                                 just said; 1: also without the loads that stream a chunk's
- *                                 tokens into LDS after its first two stages (the matrix
- *                                 instructions keep reading the same staged tokens); 2: matrix
- *                                 instructions only, both operands from registers.  The three
- *                                 show what the vector work, the streaming and the fragment
- *                                 reads each cost beside the matrix instructions.
+ *   spindle_calibrate_similarity  all cosine similarities by fp16 matrix instructions on the unit
+ *                                 vectors an earlier spindle_compress_shallow call with the same desc
+ *                                 and n_tensors left in `workspace`, each pair of 256-token panels once,
+ *                                 nothing done with the results and nothing written: its duration in
+ *                                 milliseconds, the time a kernel that computes every pair cannot go
+ *                                 below.  `mode` 0: as just said; 1: without the loads that stream the
+ *                                 tokens into LDS after the first two stages (the matrix instructions
+ *                                 keep reading the same staged tokens); 2: matrix instructions only,
+ *                                 both operands from registers.
  */
 spindle_status spindle_calibrate_mfma(int32_t iters, int32_t pattern, void *stream, double *tflops);
 /*   spindle_calibrate_copy        a plain copy of `bytes` from src to dst (device buffers, 16-byte

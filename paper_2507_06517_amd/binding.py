@@ -257,7 +257,7 @@ def decode_merge(X_new, dtype, theta, Cb, n_codes):
 
 
 def spindle_profile(mode) -> None:
-    """0/False: off; 1/True: HIP events around every kernel; 2: around the similarity kernel only."""
+    """0/False: off; 1/True: HIP events around every kernel; 2: around shallow_scan only."""
     _check(lib().spindle_profile(int(mode)))
 
 
@@ -503,7 +503,7 @@ def compress_shallow_layer(K, V, dtype, theta_k, theta_v, max_codes):
 
 def spindle_calibrate_mfma(iters: int = 4096, pattern: int = 0, stream=None) -> float:
     """TFLOP/s of a register-resident fp16 MFMA loop on the whole chip (measurement aid); pattern 1 =
-    operands with the signs and magnitudes of the similarity kernel's."""
+    operands with the signs and magnitudes of fp16 unit vectors."""
     out = C.c_double(0.0)
     _check(lib().spindle_calibrate_mfma(int(iters), int(pattern), stream or _stream(), C.byref(out)))
     return out.value
@@ -518,9 +518,9 @@ def spindle_calibrate_copy(src, dst, stream=None) -> float:
 
 
 def spindle_calibrate_similarity(plan: "ShallowPlan", mode: int = 0, stream=None) -> float:
-    """Milliseconds of the similarity kernel's loop without its packing, on the unit vectors the
-    plan's last run left in its workspace (measurement aid); mode 1 also without the streaming
-    loads, mode 2 matrix instructions only."""
+    """Milliseconds of all cosine similarities by fp16 matrix instructions, nothing done with the
+    results, on the unit vectors the plan's last run left in its workspace (measurement aid); mode 1
+    without the streaming loads, mode 2 matrix instructions only."""
     out = C.c_double(0.0)
     n_t = sum(1 for k in plan.out if k.startswith("ref_"))
     _check(lib().spindle_calibrate_similarity(C.byref(plan.desc), n_t, _ptr(plan.ws), int(plan.ws_bytes),

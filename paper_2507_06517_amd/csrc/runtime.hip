@@ -63,7 +63,7 @@ struct ProfRec {
 };
 static std::mutex g_prof_mu;
 static std::vector<ProfRec> g_prof;
-static int g_prof_mode = 0;             // 0 off, 1 every kernel, 2 only the similarity kernel
+static int g_prof_mode = 0;             // 0 off, 1 every kernel, 2 only shallow_scan
 
 static void prof_clear() {
   for (ProfRec &r : g_prof) {
@@ -75,7 +75,7 @@ static void prof_clear() {
 
 ProfScope::ProfScope(const char *name, hipStream_t s) : idx(-1), st(s) {
   if (g_prof_mode == 0) return;
-  if (g_prof_mode == 2 && strcmp(name, "shallow_gram") != 0) return;
+  if (g_prof_mode == 2 && strcmp(name, "shallow_scan") != 0) return;
   std::lock_guard<std::mutex> lk(g_prof_mu);
   ProfRec r;
   strncpy(r.name, name, sizeof(r.name) - 1);
@@ -180,7 +180,7 @@ namespace {
 // a matrix instruction draws, and with it the clock the part sustains, depends on how many operand
 // bits change from one instruction to the next: pattern 0 = small non-negative values (few bits set,
 // little switching), pattern 1 = pseudo-random values with the sign mix and magnitude of the
-// similarity kernel's operands (unit vectors of 128 dimensions scaled by 2^10), different for
+// fp16 unit vectors (unit vectors of 128 dimensions scaled by 2^10), different for
 // every chain on both sides.
 __global__ __launch_bounds__(256) void cal_mfma_f16(int iters, int pattern) {
   h8 a[4], b[4];

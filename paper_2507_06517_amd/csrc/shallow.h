@@ -2,16 +2,14 @@
 // kernels share.  ut = tensor * units + unit indexes one independent (batch, kv-head, K|V)
 // problem of n tokens.  The kernels, in the order spindle_compress_shallow enqueues them:
 //   shallow_init    counters, flags and outputs that must start from a known value
-//   shallow_prep    magnitudes (Eq. 8) in double precision, unit vectors rounded to fp16
-//   shallow_gram    cosine similarity tiles by fp16 MFMA, thresholded and bit-packed
-//                   into the adjacency matrix G (Eq. 4, 9), upper triangle only; pairs whose
-//                   fp16 similarity lies within kGuard of theta are deferred to shallow_fixup
-//                   (shallow_gram<true>: in-place fallback when a pair list overflows)
-//   shallow_fixup   exact double-precision decision for the deferred pairs;
-//                   every set bit is also left as a (row, column) record
-//   shallow_edge_lists  degrees (Eq. 10) and neighbour lists from those records
-//   shallow_mirror  lower triangle of G by bit transposition     } only when the caller wants G,
-//   shallow_lists   degrees and neighbour lists from the rows of G } or the records do not suffice
+//   shallow_prep    magnitudes (Eq. 8) in double precision, unit vectors rounded to fp16, and a
+//                   64-byte sketch of every token whose products bound the cosines from above
+//   shallow_pivots, shallow_order, shallow_window
+//                   the tokens of a problem sorted so that similar ones stand together
+//   shallow_scan    sketch products of all pairs of 32-token tiles on the int8 matrix cores:
+//                   which tiles can hold a pair above theta at all
+//   shallow_rows    for those tiles the cosines themselves (Eq. 4, 9), decided exactly; degrees
+//                   (Eq. 10) and neighbour lists
 //   merge_onehop, merge_twohop, merge_update
 //                   the first rounds of the greedy highest-degree codebook construction
 //                   (Eq. 11-13) in its exact parallel form, one launch per phase
@@ -22,7 +20,8 @@
 //                   tokens whose entry fell beyond the codebook cap go to the nearest
 //                   stored entry
 //
-// shallow_graph.hip holds the kernels up to the neighbour lists, shallow_merge.hip the greedy
+// shallow_prep.hip holds shallow_prep, shallow_tiles.hip the kernels from the order of the tokens to
+// their lists, shallow_merge.hip the greedy
 // merge, shallow_codebook.hip the codebook order, the outputs and the cap; shallow.hip the
 // workspace layout and the entry points.
 #pragma once
@@ -41,70 +40,73 @@ namespace spindle {
 // adds < 1e-6 and the fp32 accumulation of 128 exact products < 1e-5.
 constexpr float kUnitScale = 1024.f;
 constexpr float kGuard = 1.05e-3f;
-// shallow_gram uses the measured rounding error of the two vectors instead of that worst case:
-// |fp16 MFMA cosine - exact cosine| <= err_a (1 + err_b) + err_b + kGuardSlack, where the
-// slack covers the fp32 accumulation (< 1.6e-5 even with truncation) and fp16 subnormal
-// components should the matrix cores flush them (< 8e-6).
-constexpr float kGuardSlack = 3e-5f;
 
-constexpr int kPanelRows = 256;   // rows of G's column range held in registers per block
-constexpr int kChunkCols = 1024;  // tokens per chunk: one 128-byte line of each row of G
-constexpr int kItemChunks = 4;    // chunks a block handles with the same rows in registers
 constexpr int kStageCols = 64;
-constexpr int kGramThreads = 256;
 constexpr int kLdsRow = 272;      // fp16 row of 128 + 16 B pad (shallow_prep)
 constexpr int kStageBytes = kStageCols * 256;   // staged tokens: unpadded rows, 16-byte pieces swizzled
 
-// Edges a wave may record per chunk (64 rows x 1024 columns): what 32 MiB per problem allow,
-// between 512 (n = 32768: 16384 segments) and 4096 (short sequences, where a cluster of similar
-// tokens fills a larger share of every chunk).
-inline int seg_cap_for(int n) {
-  const long segs = 4L * ((n + 255) / 256) * ((n + 1023) / 1024);
-  long cap = (32L << 20) / (segs * 4);
-  cap = cap < 512 ? 512 : (cap > 4096 ? 4096 : cap);
-  return (int)(cap & ~63L);
-}
-constexpr int kFixBucket = 2048;  // pairs decided in double precision that one row panel can take
+// Sketch of a token: 64 bytes, integers scaled by kSketchScale.  60 coordinates of the unit vector
+// after a Walsh-Hadamard rotation, and the norm of the other 68 spread evenly over the last byte of
+// each 16-byte piece, so that the product of two sketches is at least the cosine, up to rounding
+// (the coordinates left out contribute at most the product of their norms).
+constexpr float kSketchScale = 300.f;
+constexpr int kSketchBytes = 64;
+constexpr int kTile = 32;                        // tokens per tile of the sorted order
+constexpr int kTileBytes = kTile * kSketchBytes;   // sketches of a tile, in matrix-core fragment order
+constexpr int kScanPanel = 16;                   // row tiles of a block of shallow_scan
+constexpr int kScanStage = 8;                    // column tiles it stages at a time
+constexpr uint32_t kSketchUnknown = 1u << 20;    // error of a token whose sketch says nothing
+constexpr int kPivots = 1024;                    // at most, and one per 16 tokens
+constexpr int kOrderTokens = 512;                // tokens per block of shallow_pivots and shallow_order
+// Shorter problems, and thresholds so low that sketches exclude few pairs, skip the order and the
+// scan: shallow_rows then takes every tile.  (Order and scan are four launches, 50 us at 16 problems of
+// 4096 tokens; every tile of 2048 tokens is about 35 us of matrix instructions there.  A sketch product
+// of unrelated tokens is about 0.53 with a spread of 0.06.)
+constexpr int kScanMinTokens = 2048;
+constexpr float kScanMinTheta = 0.7f;
+
 constexpr int kCounters = 32;     // ints per ut
-// Grid round r reads the list length C_ALIVE0 + r and builds C_ALIVE0 + r + 1, and has its own
-// candidate and dying counters, so that nothing has to be cleared between the rounds; the
-// slots 6..15 hold the phase timings of the tail kernel.
-enum { C_ALIVE0 = 0, C_ALIVE1 = 1, C_CAND = 2, C_DYING = 3, C_PICKS = 4, C_ROUNDS = 5,
-       C_ALIVE2 = 16, C_CAND1 = 17, C_DYING1 = 18 };
-__host__ __device__ constexpr int alive_slot(int round) { return round < 2 ? C_ALIVE0 + round : C_ALIVE2; }
+// (slots 6..15 hold the phase timings of shallow_merge)
+enum { C_PICKS = 4, C_ROUNDS = 5, C_DONE = 16 };
 
 struct ShallowParams {
   const char *X[2];        // input tensors [U][n][128] in `dtype` (index = tensor slot)
   float theta[2];
-  int dtype, U, UT, n, Wp;  // Wp = words per adjacency row (multiple of 4)
+  int dtype, U, UT, n;
   KvLayout lay;            // rows of the input tensors
   int cap;
   // workspace
   _Float16 *Xh;            // [UT][n][128] unit vectors
   double *m64;             // [UT][n]
-  float *err;              // [UT][n] distance of the stored fp16 unit vector from the exact one (units of the norm)
-  unsigned *echunk;        // [UT][ceil(n/1024)] largest err of each 1024-token chunk (float bits)
-  uint32_t *G;             // [UT][n][Wp]
-  int *deg0, *slot, *alive, *alive2, *cand, *dying, *pick_vert, *rank, *rank_vert;   // [UT][n]
-  uint16_t *nbr;           // [UT][n][kListCap] neighbour lists of the sparse rows
-  uint8_t *gone8;          // [UT][n16] 1 once a token has been given a slot (grid rounds of the merge); n16 = n rounded up to 16
-  int n16;
-  uint32_t *key, *gone, *m1, *pick_key;                                      // [UT][n]
+  int *slot, *alive, *cand, *dying, *rank, *rank_vert;   // [UT][n] (cand: candidate bits in the grid rounds)
+  // Lists, keys and everything after them count tokens by position: place in the sorted order.
+  uint16_t *perm, *iperm;  // [UT][n] token at a position, position of a token
+  float *inv, *invp;       // [UT][n] factor of a token's row in the cosine (see shallow_rows), by token and by position
+  uint8_t *sk0;            // [UT][n][64] sketches by token
+  uint32_t *serr;          // [UT][n] distance of the sketch from what it stands for, sketch units squared
+  uint16_t *bucket;        // [UT][n] pivot of a token
+  int *first;              // [UT][kPivots] tokens of lower pivots
+  uint16_t *hist;          // [UT][order blocks][kPivots] tokens per bucket in each block of tokens
+  int8_t *sk;              // [UT][Tp][kTileBytes] sketches by position
+  uint32_t *etile;         // [UT][Tp] largest serr of a tile
+  uint32_t *tpairs;        // [UT][T][TW] bit t of row r: tiles r and t may hold a pair above theta
+  int T, Tp, TW;           // tiles, rounded up to whole panels; words per row of tpairs
+  int scan;                // 1: tokens are sorted and tpairs says which tiles count; 0: all tiles, positions = tokens
+  int scan_thr[2];         // theta in sketch units squared
+  _Float16 *Xl;            // [UT][n][128] fp32 inputs: what fp16 rounding took off the unit vectors, x 2^11
+  // Neighbours of a position, 16 positions at a time: words (half tile << 16 | one bit per position of
+  // it), only those with a bit set; or, where a tile's rows would need more than list_row words each on
+  // average, the bits of all half tiles in order (list_row words hold them).
+  uint2 *rows;             // [UT][n] first word and number of words of a row; dense rows: kDenseRow | half tiles
+  uint32_t *lists;         // [UT][n][list_row]
+  int list_row;            // words per row on average
+  int n16;                 // n rounded up to whole half tiles: pitch of key and m1
+  uint32_t *key, *m1;      // [UT][n16] (remaining degree << 16) | (0xFFFF - token), 0 once removed; largest in the neighbourhood
+  uint32_t *live[3];       // [UT][T] bit per position: still there at the start of round 0, 1, 2
+  uint32_t *picked;        // [UT][T] bit per position: became a codebook entry
+  uint32_t *pick_key;      // [UT][n] key of a picked position at pick time; slot = position of a token's entry
   int *counters;           // [UT][kCounters]
-  uint32_t *fix;           // [UT][fix_cap] deferred pairs, b << 16 | a
-  unsigned *fix_count;     // [UT]
-  unsigned *fix_overflow;  // [1] some list was full
-  // set bits of the computed part of G as (row << 16 | column), one segment per (problem, chunk,
-  // row panel, wave): segment ((ut * nJc + J) * nI + I) * 4 + w, seg_cap entries
-  int seg_cap;             // entries per segment
-  uint32_t *edges;
-  unsigned *ecount;        // entries of each segment
-  uint32_t *fedges;        // [UT][panels][kFixBucket] pairs shallow_fixup found adjacent, row << 16 | column,
-                           //     filed under the 256-row panel of each end whose list they extend
-  unsigned *fecount;       // [UT][panels]
-  unsigned *need_full;     // [1] an edge segment ran full or a row has more neighbours than a list holds:
-                           //     degrees and lists are then taken from the complete bitmap
-  unsigned fix_cap;        // per ut
+  unsigned *pairs_exact;   // [UT] pairs decided in double precision
   uint32_t *ovf;           // [UT][n] tokens whose codebook entry was cut, per problem
   unsigned *ovf_cnt;       // [UT] their number
   float2 *cstat;           // [UT][n][2] per cut token and lane group: largest approximate cosine seen, entries collected
@@ -124,12 +126,11 @@ __device__ __forceinline__ const char *x_row(const ShallowParams &p, int ut, int
 }
 
 // x_a . x_b in double precision, summed in dimension order (products are exact).
-template <int DT>
+template <int DT, int kBatch = 8>                      // kBatch: 16-byte pieces of each row in flight
 __device__ double dot64(const char *ra, const char *rb) {
   typedef typename Elem<DT>::type T;
   constexpr int per = 16 / sizeof(T);
   double acc = 0.0;
-  constexpr int kBatch = 8;                          // pieces of each row in flight
   for (int c0 = 0; c0 < kHeadDim / per; c0 += kBatch) {
     u4 va[kBatch], vb[kBatch];
 #pragma unroll
@@ -163,21 +164,23 @@ __device__ inline double cos64(const ShallowParams &p, int ut, int a, int b) {
   return dot64_any(p.dtype, x_row(p, ut, a), x_row(p, ut, b)) / den;
 }
 
-// Entries of a token's neighbour list (uint16 indices); rows with more neighbours are read from
-// the bitmap G instead.
-constexpr int kListCap = 256;
-// Where the p-th neighbour of a row is stored: lane sl of the 8-lane segment that later walks
-// the row reads the 16 entries from sl * 16 on (of each half of 128), so the neighbours are dealt
-// out to the lanes in turn and a short row occupies all eight lanes instead of the first one.
-__host__ __device__ constexpr int list_slot(int p) { return (p & ~127) | ((p & 7) << 4) | ((p & 127) >> 3); }
+constexpr uint32_t kDenseRow = 1u << 31;
+
+template <int DT, int kBatch>
+__device__ inline double cos64(const ShallowParams &p, int ut, int a, int b) {   // the type known at compile time
+  const double den = p.m64[(size_t)ut * p.n + a] * p.m64[(size_t)ut * p.n + b];
+  if (!(den > 0.0)) return 0.0;
+  return dot64<DT, kBatch>(x_row(p, ut, a), x_row(p, ut, b)) / den;
+}
 
 // Entries per cut token and lane group that shallow_assign hands to the exact comparison.
 constexpr int kCandCap = 8;
 
 // ---------------------------------------------------------------- launches, one per source file
 // Each enqueues its kernels on `st` in order and returns SPINDLE_OK or the failed HIP call.
-// force: the caller wants the adjacency matrix, so the full bitmap is completed as well.
-spindle_status launch_graph(const ShallowParams &p, hipStream_t st, int force);
+spindle_status launch_prep(const ShallowParams &p, hipStream_t st);
+spindle_status launch_tiles(const ShallowParams &p, hipStream_t st);      // order, scan and lists
+spindle_status launch_adjacency(const ShallowParams &p, uint32_t *const out[2], hipStream_t st);   // exports G
 spindle_status launch_bare_similarity(const ShallowParams &p, hipStream_t st, int mode);   // measurement aid
 spindle_status launch_merge(const ShallowParams &p, hipStream_t st);
 spindle_status launch_codebook(const ShallowParams &p, hipStream_t st);

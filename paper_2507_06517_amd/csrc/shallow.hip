@@ -20,69 +20,66 @@ __global__ __launch_bounds__(256) void shallow_init(ShallowParams p, size_t nzer
   }
 }
 
-// Copies the rows of G without their padding words.
-__global__ void export_adj(const uint32_t *G, uint32_t *out, size_t rows, int Wp, int W) {
-  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < rows * W; i += (size_t)gridDim.x * blockDim.x)
-    out[i] = G[(i / W) * Wp + (i % W)];
-}
-
 // ---------------------------------------------------------------- workspace
-// 32-bit words at the end of the workspace that every call clears before use.
-size_t zero_words(int UT, int n) {
-  const size_t nchunk = (size_t)((n + kChunkCols - 1) / kChunkCols), nI = (size_t)((n + kPanelRows - 1) / kPanelRows);
-  return (size_t)UT * kCounters + 4 + 2 * (size_t)UT + (size_t)UT * nchunk + (size_t)UT * nI;
+int tiles_of(int n) { return (n + kTile - 1) / kTile; }
+int padded_tiles_of(int n) { return (int)align_up((size_t)tiles_of(n), kScanPanel); }
+
+// 32-bit words at the end of the workspace that every call clears before use (`scan`: also what
+// only the scan writes).
+size_t zero_words(int UT, int n, int scan) {
+  size_t w = (size_t)UT * kCounters + 4 + 2 * (size_t)UT;
+  if (scan) w += (size_t)UT * padded_tiles_of(n) + (size_t)UT * tiles_of(n) * ((tiles_of(n) + 31) / 32);
+  return w;
 }
 
 size_t carve(ShallowParams &p, void *ws, int UT, int n) {
   Carver cv(ws);
   const size_t N = (size_t)UT * n;
-  p.Wp = ((n + 127) / 128) * 4;   // whole 16-byte pieces: shallow_gram writes every word of a row
-  p.Xh = cv.take<_Float16>((N + 512) * kHeadDim);   // shallow_gram stages up to 5 tiles past the last token
+  p.T = tiles_of(n);
+  p.Tp = padded_tiles_of(n);
+  p.TW = (p.T + 31) / 32;
+  p.Xh = cv.take<_Float16>((N + 512) * kHeadDim);   // the similarity loop stages up to 5 tiles past the last token
+  p.Xl = p.dtype == SPINDLE_F32 ? cv.take<_Float16>(N * kHeadDim) : nullptr;
   p.m64 = cv.take<double>(N);
-  p.err = cv.take<float>(N);
-  p.G = cv.take<uint32_t>(N * p.Wp);
-  p.deg0 = cv.take<int>(N);
+  p.list_row = p.T;
+  p.lists = cv.take<uint32_t>(N * p.list_row);
+  p.rows = cv.take<uint2>(N);
+  p.perm = cv.take<uint16_t>(N);
+  p.iperm = cv.take<uint16_t>(N);
+  p.inv = cv.take<float>(N);
+  p.invp = cv.take<float>(N);
+  p.sk0 = cv.take<uint8_t>(N * kSketchBytes);
+  p.serr = cv.take<uint32_t>(N);
+  p.bucket = cv.take<uint16_t>(N);
+  p.first = cv.take<int>((size_t)UT * kPivots);
+  p.hist = cv.take<uint16_t>((size_t)UT * ((n + kOrderTokens - 1) / kOrderTokens) * kPivots);
+  p.sk = cv.take<int8_t>((size_t)UT * p.Tp * kTileBytes);
   p.alive = cv.take<int>(N);
-  p.alive2 = cv.take<int>(N);
-  p.gone = cv.take<uint32_t>(N);
   p.n16 = (n + 15) & ~15;
-  p.gone8 = cv.take<uint8_t>((size_t)UT * p.n16);
-  p.nbr = cv.take<uint16_t>(N * kListCap);
+  for (int r = 0; r < 3; ++r) p.live[r] = cv.take<uint32_t>((size_t)UT * p.T);
   p.slot = cv.take<int>(N);
   p.cand = cv.take<int>(N);
   p.dying = cv.take<int>(N);
-  p.pick_vert = cv.take<int>(N);
+  p.picked = cv.take<uint32_t>((size_t)UT * p.T);
   p.rank = cv.take<int>(N);
   p.rank_vert = cv.take<int>(N);
-  p.key = cv.take<uint32_t>(N);
-  p.m1 = cv.take<uint32_t>(N);
+  p.key = cv.take<uint32_t>((size_t)UT * p.n16);
+  p.m1 = cv.take<uint32_t>((size_t)UT * p.n16);
   p.pick_key = cv.take<uint32_t>(N);
   p.ovf = cv.take<uint32_t>(N);
   p.ovf_left = cv.take<uint32_t>(N);
   p.cstat = cv.take<float2>(N * 2);
   p.ccand = cv.take<uint2>(N * 2 * kCandCap);
-  p.fix_cap = (unsigned)(32 * (size_t)n > 4096 ? 32 * (size_t)n : 4096);
-  p.fix = cv.take<uint32_t>((size_t)UT * p.fix_cap);
-  p.fedges = cv.take<uint32_t>((size_t)UT * ((n + kPanelRows - 1) / kPanelRows) * kFixBucket);
-  {
-    const size_t nI = (size_t)((n + kPanelRows - 1) / kPanelRows), nJc = (size_t)((n + kChunkCols - 1) / kChunkCols);
-    p.seg_cap = seg_cap_for(n);
-    p.edges = cv.take<uint32_t>((size_t)UT * nJc * nI * 4 * p.seg_cap);
-    p.ecount = cv.take<unsigned>((size_t)UT * nJc * nI * 4);
-  }
   // everything that must start at zero sits together at the end:
-  // counters [UT][kCounters], ovf_count, fix_overflow, need_full + 1 spare, fix_count [UT], ovf_cnt [UT],
-  // echunk [UT][chunks], fecount [UT][panels]
-  const size_t nchunk = (size_t)((n + kChunkCols - 1) / kChunkCols);
-  p.counters = cv.take<int>(zero_words(UT, n));
+  // counters [UT][kCounters], ovf_count + 3 spare, pairs_exact [UT], ovf_cnt [UT], then (scan) etile [UT][Tp],
+  // tpairs [UT][T][TW]
+  p.counters = cv.take<int>(zero_words(UT, n, 1));
   int *tail = p.counters ? p.counters + (size_t)UT * kCounters : nullptr;
   p.ovf_count = reinterpret_cast<unsigned *>(tail);
-  p.fix_overflow = reinterpret_cast<unsigned *>(tail ? tail + 1 : nullptr);
-  p.fix_count = reinterpret_cast<unsigned *>(tail ? tail + 4 : nullptr);
+  p.pairs_exact = reinterpret_cast<unsigned *>(tail ? tail + 4 : nullptr);
   p.ovf_cnt = reinterpret_cast<unsigned *>(tail ? tail + 4 + UT : nullptr);
-  p.echunk = reinterpret_cast<unsigned *>(tail ? tail + 4 + 2 * (size_t)UT : nullptr);
-  p.fecount = reinterpret_cast<unsigned *>(tail ? tail + 4 + 2 * (size_t)UT + (size_t)UT * nchunk : nullptr);
-  p.need_full = reinterpret_cast<unsigned *>(tail ? tail + 2 : nullptr);
+  p.etile = reinterpret_cast<uint32_t *>(tail ? tail + 4 + 2 * (size_t)UT : nullptr);
+  p.tpairs = p.etile ? p.etile + (size_t)UT * p.Tp : nullptr;
   return cv.total();
 }
 
@@ -99,6 +96,7 @@ extern "C" spindle_status spindle_shallow_workspace_bytes(const spindle_kv_desc 
   if (n_tensors < 1 || n_tensors > 2) SPINDLE_FAIL(SPINDLE_ERR_INVALID_ARG, "n_tensors must be 1 or 2");
   if (desc->seq_len > 65535) SPINDLE_FAIL(SPINDLE_ERR_UNSUPPORTED, "seq_len must be <= 65535 for the codebook path");
   ShallowParams p;
+  p.dtype = desc->dtype;
   *bytes = carve(p, nullptr, desc->batch * desc->n_kv_heads * n_tensors, desc->seq_len);
   return SPINDLE_OK;
 }
@@ -112,13 +110,14 @@ extern "C" spindle_status spindle_shallow_stats(const spindle_kv_desc *desc, int
   const int UT = desc->batch * desc->n_kv_heads * n_tensors;
   ShallowParams p;
   memset(&p, 0, sizeof(p));
+  p.dtype = desc->dtype;
   carve(p, const_cast<void *>(workspace), UT, desc->seq_len);
   hipStream_t st = static_cast<hipStream_t>(stream);
   std::vector<int> cnt((size_t)UT * kCounters);
   std::vector<unsigned> fixc(UT);
   SPINDLE_HIP(hipStreamSynchronize(st));
   SPINDLE_HIP(hipMemcpy(cnt.data(), p.counters, cnt.size() * sizeof(int), hipMemcpyDeviceToHost));
-  SPINDLE_HIP(hipMemcpy(fixc.data(), p.fix_count, fixc.size() * sizeof(unsigned), hipMemcpyDeviceToHost));
+  SPINDLE_HIP(hipMemcpy(fixc.data(), p.pairs_exact, fixc.size() * sizeof(unsigned), hipMemcpyDeviceToHost));
   for (int i = 0; i < UT; ++i) {
     stats[16 * i + 0] = cnt[(size_t)i * kCounters + C_ROUNDS];
     stats[16 * i + 1] = cnt[(size_t)i * kCounters + C_PICKS];
@@ -176,18 +175,23 @@ spindle_status run_shallow(int phases,
     p.n_codes[t] = n_codes_v; p.n_found[t] = n_found_v; p.ref[t] = ref_v; p.mag[t] = mag_v;
     adj[t] = adj_v; p.deg_out[t] = deg_v; ++t;
   }
+  // (a sketch product is never below the cosine minus its error, so a pair above theta is never lost;
+  // the slack covers the fp32 arithmetic that makes the sketches)
+  p.scan = n >= kScanMinTokens;
+  for (int i = 0; i < T; ++i)
+    if (p.theta[i] < kScanMinTheta) p.scan = 0;
+  for (int i = 0; p.scan && i < T; ++i) {
+    const double thr = ((double)p.theta[i] - 1e-4) * kSketchScale * kSketchScale;
+    p.scan_thr[i] = thr < (double)(1 << 28) ? (int)floor(thr) : 1 << 28;
+  }
   if (phases & kPhaseGraph) {
     // zero: counters, list counts, error flag, barriers; codebooks
-    const size_t nzero = zero_words(p.UT, n);
+    const size_t nzero = zero_words(p.UT, n, p.scan);
     const size_t cwords = (size_t)U * max_codes * kHeadDim * dtype_bytes(p.dtype) / 4;
     hipLaunchKernelGGL(shallow_init, dim3(1024), dim3(256), 0, st, p, nzero, cwords, T);
-    if ((s = launch_graph(p, st, adj[0] || adj[1])) != SPINDLE_OK) return s;
-    const int W = (n + 31) / 32;                      // nothing after this point changes G
-    for (int i = 0; i < T; ++i) {
-      if (adj[i])
-        hipLaunchKernelGGL(export_adj, dim3(1024), dim3(256), 0, st, p.G + (size_t)i * U * n * p.Wp, adj[i],
-                           (size_t)U * n, p.Wp, W);
-    }
+    if ((s = launch_prep(p, st)) != SPINDLE_OK) return s;
+    if ((s = launch_tiles(p, st)) != SPINDLE_OK) return s;
+    if ((s = launch_adjacency(p, adj, st)) != SPINDLE_OK) return s;
   }
   if (phases & kPhaseCodebook) {
     if ((s = launch_merge(p, st)) != SPINDLE_OK) return s;

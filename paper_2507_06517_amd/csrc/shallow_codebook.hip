@@ -20,11 +20,11 @@ __device__ __forceinline__ void emit_code(const ShallowParams &p, int ut, int ve
 }
 
 // Codebook order: the picks of a problem sorted by decreasing key at pick time (keys are
-// distinct: they carry the token index).  One workgroup per problem: least-significant-digit
-// radix sort, four stable passes of 8 bits over (key, pick number) pairs that ping-pong
-// between two pairs of arrays left free by the merge.  A pass counts the digits, then walks
-// the items in order, 1024 at a time: lanes with the same digit find each other with eight
-// ballots, waves exchange their digit counts through LDS.
+// distinct: they carry the token index).  One workgroup per problem: the picked positions are listed
+// from their bits, then a least-significant-digit radix sort, four stable passes of 8 bits over
+// (key, position) pairs that ping-pong between two pairs of arrays left free by the merge.  A pass
+// counts the digits, then walks the items in order, 1024 at a time: lanes with the same digit find
+// each other with eight ballots, waves exchange their digit counts through LDS.
 constexpr int kRankThreads = 1024;
 
 __global__ __launch_bounds__(kRankThreads) void shallow_rank(ShallowParams p) {
@@ -34,12 +34,40 @@ __global__ __launch_bounds__(kRankThreads) void shallow_rank(ShallowParams p) {
   __shared__ int scan_tmp[256];
   const int ut = blockIdx.x, tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
   const size_t base = (size_t)ut * p.n;
-  if (p.n_codes[ut / p.U][ut % p.U] < 0) return;     // construction did not finish
-  const int P = p.counters[(size_t)ut * kCounters + C_PICKS];
-  uint32_t *keyA = p.pick_key + base, *keyB = p.m1 + base;
+  int *cnt = p.counters + (size_t)ut * kCounters;
+  if (cnt[C_DONE] == 0) return;                      // construction did not finish: n_codes stays -1
+  uint32_t *keyA = p.m1 + (size_t)ut * p.n16, *keyB = p.key + (size_t)ut * p.n16;
   uint32_t *valA = reinterpret_cast<uint32_t *>(p.cand + base), *valB = reinterpret_cast<uint32_t *>(p.dying + base);
-  for (int s = tid; s < P; s += kRankThreads) valA[s] = (uint32_t)s;
-  __syncthreads();
+  int P = 0;
+  for (int w0 = 0; w0 < p.T; w0 += kRankThreads) {
+    const int i = w0 + tid;
+    uint32_t bits = i < p.T ? p.picked[(size_t)ut * p.T + i] : 0u;
+    int incl = __popc(bits);
+    const int mine = incl;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+      const int x = __shfl_up(incl, o);
+      if (lane >= o) incl += x;
+    }
+    if (lane == kWave - 1) scan_tmp[wave] = incl;
+    __syncthreads();
+    int at = P + incl - mine;
+    for (int q = 0; q < kWaves; ++q) {
+      if (q < wave) at += scan_tmp[q];
+      P += scan_tmp[q];
+    }
+    for (; bits; bits &= bits - 1, ++at) {
+      const int v = i * 32 + __builtin_ctz(bits);
+      valA[at] = (uint32_t)v;
+      keyA[at] = p.pick_key[base + v];
+    }
+    __syncthreads();
+  }
+  if (tid == 0) {
+    cnt[C_PICKS] = P;
+    p.n_codes[ut / p.U][ut % p.U] = P < p.cap ? P : p.cap;
+    if (p.n_found[ut / p.U]) p.n_found[ut / p.U][ut % p.U] = P;
+  }
   for (int pass = 0; pass < 4; ++pass) {
     const int shift = 8 * pass;
     const uint32_t *kin = pass & 1 ? keyB : keyA, *vin = pass & 1 ? valB : valA;
@@ -96,9 +124,9 @@ __global__ __launch_bounds__(kRankThreads) void shallow_rank(ShallowParams p) {
   }
   // four passes: the sorted pairs are back in the first pair of arrays
   for (int r = tid; r < P; r += kRankThreads) {
-    const int s = (int)valA[r];
-    p.rank[base + s] = r;
-    p.rank_vert[base + r] = p.pick_vert[base + s];
+    const int v = (int)valA[r];
+    p.rank[base + v] = r;
+    p.rank_vert[base + r] = (int)p.perm[base + v];   // from here on tokens again
   }
 }
 
@@ -110,10 +138,11 @@ __global__ __launch_bounds__(256) void shallow_emit(ShallowParams p) {
   const int stored = p.n_codes[t][u];
   if (stored < 0) return;                        // the merge did not finish
   const int *rank = p.rank + base, *slot = p.slot + base, *rank_vert = p.rank_vert + base;
+  const uint16_t *iperm = p.iperm + base;
   const int lane = lane_id();
   for (int v0 = blockIdx.x * 256 + threadIdx.x - lane; v0 < n; v0 += gridDim.x * 256) {
     const int v = v0 + lane;
-    const int r = v < n ? rank[slot[v]] : 0;
+    const int r = v < n ? rank[slot[iperm[v]]] : 0;
     if (v < n) p.ref[t][(size_t)u * n + v] = r;
     const bool cut = v < n && r >= p.cap;
     const unsigned long long mk = __ballot(cut);         // one counter update per wave

@@ -14,81 +14,61 @@ namespace {
 // maximum at once; sorting all picks by their key at pick time (which strictly decreases
 // along the sequential loop) restores the codebook order.
 //
-// A round has four phases, each a loop over a list of tokens:
+// A round has three phases:
 //   one-hop   m1[v] = largest key in v's closed neighbourhood; v is a candidate if it is its own
 //   two-hop   a candidate whose neighbours' m1 never exceed its key is picked: its remaining
-//             neighbours get its slot, are queued as `dying` and marked in the `dead` bitmap
-//   degree    neighbours of dying tokens that stay lose one degree (Eq. 13)
-//   compact   keys of dying tokens become 0, the list of remaining tokens is rebuilt
-// The first kGridRounds rounds, where most tokens are still there, run as grid-wide kernels
-// (one launch per phase, state in global memory); the remaining rounds run in one
-// 1024-thread workgroup per problem with keys and the dead bitmap in LDS, separated by
-// workgroup barriers only.  Rows are handled by 8-lane segments, four rows in flight.
+//             neighbours get its position as their slot and leave the next round's live bits
+//   update    keys of tokens that left become 0, those that stay count the neighbours still
+//             there (Eq. 13): one population count per word of their list
+// The first kGridRounds rounds, where most tokens are still there, run as grid-wide kernels (one launch
+// per phase): a wave takes 32 consecutive positions, eight lanes per row, and what it finds goes out
+// as the 32 bits of its positions (live, candidate, picked), so that no list has to be built and no
+// counter is shared: same-address atomics cost about 40 ns each here.  Neighbours stand close to each
+// other in the sorted order, so the 64-byte reads of 16 keys at a time mostly hit the caches.
+// The remaining rounds run in one 1024-thread workgroup per problem with keys and live bits in LDS,
+// separated by workgroup barriers only.  Bound by the latency of a row's words and what they point at:
+// two grid rounds of 16 problems of 32768 tokens take 0.09 ms (0.165 ms with single neighbours, lists of
+// remaining tokens and counters), of 64 such problems with half of the tokens isolated 0.24 (0.55) ms.
 constexpr int kMergeThreads = 1024;
 constexpr int kSegW = 8;                 // lanes that share one row
-constexpr int kGridRounds = 2;
-static_assert(kGridRounds <= 2, "alive_slot and the per-round counters cover two grid rounds");
+constexpr int kGridRounds = 2;           // live[] holds the bits of one round more
 constexpr int kPhaseThreads = 256;
-constexpr int kKeysInLds = 36 * 1024;   // tokens whose keys fit in LDS next to the other buffers
+constexpr int kKeysInLds = 36 * 1024;   // tokens whose keys fit in LDS next to the live bits
 
-// The part of a row's neighbourhood one lane of a segment looks at: up to 16 entries of
-// each half of the list, or (dense rows) every eighth 16-byte piece of the bitmap row.
-struct Nbrs {
-  u4 q[4];        // entries sl*16 .. +15 and 128 + sl*16 .. +15 of the list
-  int cnt0, cnt1; // entries of this lane in each half; cnt0 = -1: dense row, walk the bitmap
-  const u4 *row;
+struct Row {
+  const uint32_t *w;
+  int n;            // words
+  bool dense;       // the bits of all half tiles in order instead of words
 };
 
-__device__ __forceinline__ Nbrs load_nbrs(const ShallowParams &p, size_t base, int v, int sl) {
-  Nbrs r;
-  const int d0 = p.deg0[base + v];
-  const u4 *src = reinterpret_cast<const u4 *>(p.nbr + (base + v) * kListCap + sl * 16);
-  r.q[0] = src[0];    // unconditional: the slot exists for every row, and the loads
-  r.q[1] = src[1];    // then do not wait for the degree
-  r.row = reinterpret_cast<const u4 *>(p.G + (base + v) * p.Wp);
-  // entries sl, sl + 8, ... of each half belong to this lane (list_slot)
-  const int h0 = d0 < 128 ? d0 : 128, h1 = d0 - 128;
-  const int c0 = (h0 - sl + 7) >> 3, c1 = (h1 - sl + 7) >> 3;
-  r.cnt0 = d0 <= kListCap ? (c0 < 0 ? 0 : c0) : -1;
-  r.cnt1 = d0 <= kListCap && h1 > 0 ? (c1 < 0 ? 0 : c1) : 0;
-  if (r.cnt1 > 0) {
-    r.q[2] = src[16];
-    r.q[3] = src[17];
-  }
-  return r;
+__device__ __forceinline__ Row row_at(const ShallowParams &p, size_t base, const uint32_t *lists, int v) {
+  const uint2 info = p.rows[base + v];
+  return Row{lists + info.x, (int)(info.y & ~kDenseRow), (info.y & kDenseRow) != 0};
 }
 
-// Calls f(b) for every neighbour b in this lane's part of the row.
-template <typename F>
-__device__ __forceinline__ void for_nbrs(const ShallowParams &p, const Nbrs &r, int sl, F f) {
-  if (r.cnt0 >= 0) {
-    // most rows are short: every fourth entry the wave checks whether any lane has more
+// Word i of a row: half tile << 16 | bits.
+__device__ __forceinline__ uint32_t word_at(const Row &r, int i) {
+  return r.dense ? ((uint32_t)i << 16) | reinterpret_cast<const uint16_t *>(r.w)[i] : r.w[i];
+}
+
+// Largest of the 16 values of the half tile that the bits select (and m).
+__device__ __forceinline__ uint32_t masked_max(const uint32_t *a, uint32_t word, uint32_t m) {
+  const u4 *q = reinterpret_cast<const u4 *>(a + (word >> 16) * 16);
 #pragma unroll
-    for (int j = 0; j < 16; ++j) {
-      if (j > 0 && (j & 3) == 0 && __ballot(j < r.cnt0) == 0) break;
-      if (j < r.cnt0) f((int)((r.q[j >> 3][(j >> 1) & 3] >> (16 * (j & 1))) & 0xFFFFu));
-    }
-    if (r.cnt1 > 0) {
+  for (int i = 0; i < 4; ++i) {
+    const u4 x = q[i];
 #pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        if (j > 0 && (j & 3) == 0 && __ballot(j < r.cnt1) == 0) break;
-        if (j < r.cnt1) f((int)((r.q[2 + (j >> 3)][(j >> 1) & 3] >> (16 * (j & 1))) & 0xFFFFu));
-      }
-    }
-  } else {
-    for (int w4 = sl; w4 < p.Wp / 4; w4 += kSegW) {
-      const u4 q = r.row[w4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        uint32_t bits = q[j];
-        while (bits) {
-          const int t = __builtin_ctz(bits);
-          bits &= bits - 1;
-          f((w4 * 4 + j) * 32 + t);
-        }
-      }
+    for (int j = 0; j < 4; ++j) {
+      const uint32_t y = x[j] & (uint32_t)__builtin_amdgcn_sbfe((int)word, 4 * i + j, 1);
+      m = y > m ? y : m;
     }
   }
+  return m;
+}
+
+// The bits of `word` that are set in the bit array `live` (one bit per position).
+__device__ __forceinline__ uint32_t still(const uint32_t *live, uint32_t word) {
+  return word & 0xFFFFu & (live[word >> 17] >> ((word >> 12) & 16));
 }
 
 // Lane exchanges inside an 8-lane segment by DPP (no LDS round trip): the two quad
@@ -114,515 +94,214 @@ __device__ __forceinline__ int seg_sum(int v) {             // over a segment, r
   return v;
 }
 
-// The same walk four entries at a time: f4(b, ok) gets four neighbour slots of this lane
-// (ok[t] false: slot t is past the end of the lane's part and b[t] is not a token) and can issue
-// its look-ups together, so that a row costs a few memory round trips instead of one per
-// entry; the wave stops as soon as no lane has entries left.  f1(b) handles one neighbour of
-// a dense row (bitmap walk).
-template <typename F4, typename F1>
-__device__ __forceinline__ void for_nbrs4(const ShallowParams &p, const Nbrs &r, int sl, F4 f4, F1 f1) {
-  if (r.cnt0 >= 0) {
-#pragma unroll
-    for (int half = 0; half < 2; ++half) {
-      const int cnt = half ? r.cnt1 : r.cnt0;
-      if (__ballot(cnt > 0) == 0) break;               // wave-uniform
-#pragma unroll
-      for (int j0 = 0; j0 < 16; j0 += 4) {
-        if (__ballot(j0 < cnt) == 0) break;            // wave-uniform
-        int b[4];
-        bool ok[4];
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          const int j = j0 + t;
-          ok[t] = j < cnt;
-          b[t] = (int)((r.q[2 * half + (j >> 3)][(j >> 1) & 3] >> (16 * (j & 1))) & 0xFFFFu);
-        }
-        f4(b, ok);
-      }
-    }
-  } else {
-    for (int w4 = sl; w4 < p.Wp / 4; w4 += kSegW) {
-      const u4 q = r.row[w4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        uint32_t bits = q[j];
-        while (bits) {
-          const int t = __builtin_ctz(bits);
-          bits &= bits - 1;
-          f1((w4 * 4 + j) * 32 + t);
-        }
-      }
-    }
-  }
+// Bit s of the result: `on` of segment s (0..7), given in the segment's first lane.
+__device__ __forceinline__ uint32_t seg_bits(bool on) {
+  const unsigned long long m = __ballot(on && (lane_id() & (kSegW - 1)) == 0);
+  // bits 0, 8, 16, ... gathered by a multiplication (each half of 32 bits has four of them)
+  const uint32_t lo = (uint32_t)m & 0x01010101u, hi = (uint32_t)(m >> 32) & 0x01010101u;
+  return ((lo * 0x10204080u) >> 28 & 0xFu) | (((hi * 0x10204080u) >> 28 & 0xFu) << 4);
 }
 
-// Where the state of one problem lives for the running kernel (LDS or global memory), and
-// which segments of the launch work on it: segment `seg` of `nsegs`, a wave's segments
-// being consecutive.
-struct MergeView {
-  uint32_t *key;        // (remaining degree << 16) | (0xFFFF - index); 0 once removed
-  uint32_t *dead;       // bit v set once token v has been given a slot
-  int *n_alive, *n_cand, *n_dying, *n_picks;
-  int seg, nsegs, sl;
-};
-
-__device__ __forceinline__ void phase_onehop(const ShallowParams &p, size_t base, const MergeView &w,
-                                             const int *alive, int nalive) {
-  constexpr int kPer = kWave / kSegW;
-  uint32_t *m1 = p.m1 + base;
-  int *cand = p.cand + base;
-  const int lane = lane_id();
-  for (int i0 = w.seg - w.seg % kPer; i0 < nalive; i0 += 4 * w.nsegs) {
-    int vv[4];
-    bool on[4];
-    Nbrs r[4];
-    uint32_t m[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int i = i0 + w.seg % kPer + k * w.nsegs;
-      on[k] = i < nalive;
-      vv[k] = on[k] ? alive[i] : 0;
-    }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) r[k] = load_nbrs(p, base, vv[k], w.sl);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      uint32_t mk = on[k] ? w.key[vv[k]] : 0;          // a token is its own neighbour
-      if (on[k]) {
-        const int self = vv[k];
-        for_nbrs4(p, r[k], w.sl,
-                  [&](const int *b, const bool *ok) {
-                    uint32_t kk[4];
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) kk[t] = w.key[ok[t] ? b[t] : self];   // own key again: harmless
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) mk = kk[t] > mk ? kk[t] : mk;
-                  },
-                  [&](int b) { const uint32_t kk = w.key[b]; mk = kk > mk ? kk : mk; });
-      }
-      m[k] = seg_max(mk);
-    }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const bool lead = w.sl == 0 && on[k];
-      if (lead) m1[vv[k]] = m[k];
-      const bool is_cand = lead && m[k] == w.key[vv[k]];
-      const unsigned long long mk = __ballot(is_cand);     // one counter update per wave
-      if (mk) {
-        int at = 0;
-        if (lane == __builtin_ctzll(mk)) at = atomicAdd(w.n_cand, __popcll(mk));
-        at = __shfl(at, __builtin_ctzll(mk));
-        if (is_cand) cand[at + __popcll(mk & ((1ull << lane) - 1ull))] = vv[k];
-      }
-    }
-  }
-}
-
-// kBytes: `dead` is the byte array of the grid rounds (plain stores); else the bitmap of the tail
-// kFlight: candidates a segment works on at once
-template <bool kBytes, int kFlight>
-__device__ __forceinline__ void phase_twohop(const ShallowParams &p, size_t base, const MergeView &w, int ncand) {
-  constexpr int kPer = kWave / kSegW;
-  const uint32_t *m1 = p.m1 + base;
-  const int *cand = p.cand + base;
-  int *slot = p.slot + base, *dying = p.dying + base, *pick_vert = p.pick_vert + base;
-  uint32_t *pick_key = p.pick_key + base;
-  const int lane = lane_id();
-  for (int i0 = w.seg - w.seg % kPer; i0 < ncand; i0 += kFlight * w.nsegs) {
-    int uv[kFlight], rem[kFlight];
-    bool on[kFlight];
-    uint32_t ku[kFlight], m[kFlight];
-    Nbrs r[kFlight];
-#pragma unroll
-    for (int k = 0; k < kFlight; ++k) {
-      const int i = i0 + w.seg % kPer + k * w.nsegs;
-      on[k] = i < ncand;
-      uv[k] = on[k] ? cand[i] : 0;
-    }
-#pragma unroll
-    for (int k = 0; k < kFlight; ++k) {
-      ku[k] = on[k] ? w.key[uv[k]] : 0xFFFFFFFFu;
-      r[k] = load_nbrs(p, base, uv[k], w.sl);
-    }
-#pragma unroll
-    for (int k = 0; k < kFlight; ++k) {
-      uint32_t mk = 0;
-      int rk = 0;                                    // remaining neighbours in this lane's part
-      // remaining = key != 0 (keys only change in the later phases of the round)
-      if (on[k]) {
-        const int self = uv[k];
-        for_nbrs4(p, r[k], w.sl,
-                  [&](const int *b, const bool *ok) {
-                    uint32_t kk[4], q[4];
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) kk[t] = w.key[ok[t] ? b[t] : self];
-                    bool there[4];
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) {
-                      there[t] = ok[t] && kk[t] != 0;
-                      q[t] = m1[there[t] ? b[t] : self];
-                    }
-#pragma unroll
-                    for (int t = 0; t < 4; ++t)
-                      if (there[t]) { mk = q[t] > mk ? q[t] : mk; ++rk; }
-                  },
-                  [&](int b) {
-                    if (w.key[b] != 0) { const uint32_t q = m1[b]; mk = q > mk ? q : mk; ++rk; }
-                  });
-      }
-      m[k] = seg_max(mk);
-      rem[k] = rk;
-    }
-#pragma unroll
-    for (int k = 0; k < kFlight; ++k) {
-      const bool picked = on[k] && m[k] == ku[k];
-      // one update of each counter per wave: picks by the segment leaders, dying tokens by all lanes
-      const unsigned long long pk = __ballot(picked && w.sl == 0);
-      if (pk != 0) {                                 // wave-uniform
-        int s = 0;
-        {
-          int at = 0;
-          if (lane == __builtin_ctzll(pk)) at = atomicAdd(w.n_picks, __popcll(pk));
-          at = __shfl(at, __builtin_ctzll(pk));
-          if (picked && w.sl == 0) {
-            s = at + __popcll(pk & ((1ull << lane) - 1ull));
-            pick_key[s] = ku[k];
-            pick_vert[s] = uv[k];
-          }
-        }
-        s = __shfl(s, lane & ~(kSegW - 1));
-        const int mine = picked ? rem[k] : 0;
-        int incl = mine;
-#pragma unroll
-        for (int o = 1; o < kWave; o <<= 1) {
-          const int x = __shfl_up(incl, o);
-          if (lane >= o) incl += x;
-        }
-        int at = 0;
-        if (lane == kWave - 1) at = atomicAdd(w.n_dying, incl);
-        at = __shfl(at, kWave - 1) + incl - mine;
-        auto take = [&](int b) {
-          slot[b] = s;
-          if (kBytes) reinterpret_cast<uint8_t *>(w.dead)[b] = 1;
-          else atomicOr(&w.dead[b >> 5], 1u << (b & 31));
-          dying[at++] = b;
-        };
-        if (picked) {
-          const int self = uv[k];
-          for_nbrs4(p, r[k], w.sl,
-                    [&](const int *b, const bool *ok) {
-                      uint32_t kk[4];
-#pragma unroll
-                      for (int t = 0; t < 4; ++t) kk[t] = w.key[ok[t] ? b[t] : self];
-#pragma unroll
-                      for (int t = 0; t < 4; ++t)
-                        if (ok[t] && kk[t] != 0) take(b[t]);
-                    },
-                    [&](int b) { if (w.key[b] != 0) take(b); });
-        }
-      }
-    }
-  }
-}
-
-__device__ __forceinline__ void phase_degree(const ShallowParams &p, size_t base, const MergeView &w, int ndying) {
-  constexpr int kPer = kWave / kSegW;
-  const int *dying = p.dying + base;
-  for (int i0 = w.seg - w.seg % kPer; i0 < ndying; i0 += 4 * w.nsegs) {
-    Nbrs r[4];
-    bool on[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int i = i0 + w.seg % kPer + k * w.nsegs;
-      on[k] = i < ndying;
-      r[k] = load_nbrs(p, base, on[k] ? dying[i] : 0, w.sl);
-    }
-    auto drop = [&](int b) {   // tokens that stay: not marked dead (the bitmap also covers earlier rounds)
-      if (!((w.dead[b >> 5] >> (b & 31)) & 1u)) atomicSub(&w.key[b], 1u << 16);
-    };
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-      if (on[k])
-        for_nbrs4(p, r[k], w.sl,
-                  [&](const int *b, const bool *ok) {
-                    uint32_t word[4];
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) word[t] = w.dead[(ok[t] ? b[t] : 0) >> 5];
-#pragma unroll
-                    for (int t = 0; t < 4; ++t)
-                      if (ok[t] && !((word[t] >> (b[t] & 31)) & 1u)) atomicSub(&w.key[b[t]], 1u << 16);
-                  },
-                  drop);
-  }
-}
-
-// Eq. 13 the other way round: every token of the list counts its neighbours that are still
-// there (dead bitmap).  Cheaper than phase_degree when more tokens left than stayed.
-__device__ __forceinline__ void phase_recount(const ShallowParams &p, size_t base, const MergeView &w,
-                                              const int *alive, int nalive) {
-  constexpr int kPer = kWave / kSegW;
-  for (int i0 = w.seg - w.seg % kPer; i0 < nalive; i0 += 4 * w.nsegs) {
-    int vv[4];
-    bool on[4];
-    Nbrs r[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int i = i0 + w.seg % kPer + k * w.nsegs;
-      on[k] = i < nalive;
-      vv[k] = on[k] ? alive[i] : 0;
-    }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) r[k] = load_nbrs(p, base, vv[k], w.sl);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      int c = 0;
-      if (on[k])
-        for_nbrs4(p, r[k], w.sl,
-                  [&](const int *b, const bool *ok) {
-                    uint32_t word[4];
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) word[t] = w.dead[(ok[t] ? b[t] : 0) >> 5];
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) c += ok[t] && !((word[t] >> (b[t] & 31)) & 1u);
-                  },
-                  [&](int b) { c += !((w.dead[b >> 5] >> (b & 31)) & 1u); });
-      c = seg_sum(c);
-      if (on[k] && w.sl == 0) w.key[vv[k]] = ((uint32_t)c << 16) | (uint32_t)(0xFFFF - vv[k]);
-    }
-  }
-}
-
-__device__ __forceinline__ MergeView global_view(const ShallowParams &p, int ut, int round) {
-  MergeView w;
-  const size_t base = (size_t)ut * p.n;
-  int *cnt = p.counters + (size_t)ut * kCounters;
-  w.key = p.key + base;
-  w.dead = reinterpret_cast<uint32_t *>(p.gone8 + (size_t)ut * p.n16);
-  w.n_alive = cnt + alive_slot(round);
-  w.n_cand = cnt + (round ? C_CAND1 : C_CAND);
-  w.n_dying = cnt + (round ? C_DYING1 : C_DYING);
-  w.n_picks = cnt + C_PICKS;
-  w.seg = (blockIdx.x * blockDim.x + threadIdx.x) / kSegW;
-  w.nsegs = gridDim.x * blockDim.x / kSegW;
-  w.sl = threadIdx.x & (kSegW - 1);
-  return w;
-}
-
-// Grid-wide phases of round `round` (blockIdx.y = problem).  The list of remaining tokens
-// alternates between the `alive` and `alive2` rows, its length between counters 0 and 1.
-// With dynamic LDS for n keys the block first copies the keys of its problem there: the
-// phase is bound by the random key look-ups, which LDS serves several times faster than L2.
-__global__ __launch_bounds__(kMergeThreads) void merge_onehop(ShallowParams p, int round, int keys_in_lds) {
-  extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
-  const int ut = blockIdx.y;
-  const size_t base = (size_t)ut * p.n;
-  MergeView w = global_view(p, ut, round);
-  const int nalive = *w.n_alive;
-  if ((int)(blockIdx.x * blockDim.x / kSegW) >= nalive) return;      // block-uniform: no work for this block
-  if (keys_in_lds) {
-    if ((p.n & 3) == 0) {                             // rows of the key array are then 16-byte aligned
-      const u4 *src = reinterpret_cast<const u4 *>(p.key + base);
-      for (int i = threadIdx.x; i < p.n / 4; i += blockDim.x) reinterpret_cast<u4 *>(lds)[i] = src[i];
-    } else {
-      for (int i = threadIdx.x; i < p.n; i += blockDim.x) lds[i] = p.key[base + i];
-    }
-    __syncthreads();
-    w.key = lds;
-  }
-  phase_onehop(p, base, w, (round & 1 ? p.alive2 : p.alive) + base, nalive);
-}
-// Two-hop phase of a grid round.  When candidates are few (hundreds per problem: they then
-// have the longest lists, and every look-up here is a trip to L2) a wave takes one candidate:
-// with four slots per lane its whole list is one look-up step for the keys and one for their
-// one-hop maxima, whatever its length.
-__global__ __launch_bounds__(kPhaseThreads) void merge_twohop(ShallowParams p, int round) {
-  const int ut = blockIdx.y, lane = lane_id();
-  const size_t base = (size_t)ut * p.n;
-  int *cnt = p.counters + (size_t)ut * kCounters;
-  const int ncand = cnt[round ? C_CAND1 : C_CAND];
-  int *n_dying = cnt + (round ? C_DYING1 : C_DYING), *n_picks = cnt + C_PICKS;
-  const uint32_t *key = p.key + base, *m1 = p.m1 + base;
-  const int *cand = p.cand + base;
-  int *slot = p.slot + base, *dying = p.dying + base, *pick_vert = p.pick_vert + base;
-  uint32_t *pick_key = p.pick_key + base;
-  uint8_t *gone = p.gone8 + (size_t)ut * p.n16;
-  const int wave0 = (blockIdx.x * blockDim.x + threadIdx.x) / kWave, nwaves = gridDim.x * blockDim.x / kWave;
-  if (ncand > 2 * nwaves) {
-    // many candidates (isolated tokens are all candidates): short lists, eight lanes per row
-    const MergeView w = global_view(p, ut, round);
-    phase_twohop<true, 4>(p, base, w, ncand);
+// ---------------------------------------------------------------- grid rounds
+// Wave index within a problem = word of the bit arrays = 32 positions; pass k of 4 takes positions
+// 8 k .. 8 k + 7 of it, one per segment.
+__global__ __launch_bounds__(kPhaseThreads) void merge_onehop(ShallowParams p, int round) {
+  const int ut = blockIdx.y, W = (int)blockIdx.x * (kPhaseThreads / kWave) + (int)(threadIdx.x >> 6);
+  if (W >= p.T) return;
+  const int lane = lane_id(), seg = lane / kSegW, sl = lane & (kSegW - 1);
+  const uint32_t live = __builtin_amdgcn_readfirstlane(p.live[round][(size_t)ut * p.T + W]);
+  uint32_t *cand = reinterpret_cast<uint32_t *>(p.cand + (size_t)ut * p.n);
+  if (live == 0) {
+    if (lane == 0) cand[W] = 0;
     return;
   }
-  for (int i = wave0; i < ncand; i += nwaves) {      // wave-uniform
-    const int u = cand[i];
+  const size_t base = (size_t)ut * p.n;
+  const uint32_t *key = p.key + (size_t)ut * p.n16, *lists = p.lists + base * p.list_row;
+  uint32_t *m1 = p.m1 + (size_t)ut * p.n16;
+  Row r[4];
+  uint32_t w0[4], own[4];
+  bool on[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    on[k] = (live >> (8 * k + seg)) & 1;
+    const int v = on[k] ? W * kTile + 8 * k + seg : W * kTile;
+    r[k] = row_at(p, base, lists, v);
+    own[k] = key[v];
+  }
+#pragma unroll
+  for (int k = 0; k < 4; ++k) w0[k] = on[k] && sl < r[k].n ? word_at(r[k], sl) : 0;
+  uint32_t bits = 0;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    uint32_t m = own[k];                              // a token is its own neighbour
+    if (w0[k] & 0xFFFFu) m = masked_max(key, w0[k], m);
+    for (int i = sl + kSegW; on[k] && i < r[k].n; i += kSegW) {
+      const uint32_t w = word_at(r[k], i);
+      if (w & 0xFFFFu) m = masked_max(key, w, m);
+    }
+    m = seg_max(m);
+    if (on[k] && sl == 0) m1[W * kTile + 8 * k + seg] = m;
+    bits |= seg_bits(on[k] && m == own[k]) << (8 * k);
+  }
+  if (lane == 0) cand[W] = bits;
+}
+
+__global__ __launch_bounds__(kPhaseThreads) void merge_twohop(ShallowParams p, int round) {
+  const int ut = blockIdx.y, W = (int)blockIdx.x * (kPhaseThreads / kWave) + (int)(threadIdx.x >> 6);
+  if (W >= p.T) return;
+  const int lane = lane_id(), seg = lane / kSegW, sl = lane & (kSegW - 1);
+  const size_t base = (size_t)ut * p.n;
+  const uint32_t cand = __builtin_amdgcn_readfirstlane(reinterpret_cast<const uint32_t *>(p.cand + base)[W]);
+  uint32_t *picked = p.picked + (size_t)ut * p.T + W;
+  if (cand == 0) {
+    if (round == 0 && lane == 0) *picked = 0;
+    return;
+  }
+  const uint32_t *key = p.key + (size_t)ut * p.n16, *m1 = p.m1 + (size_t)ut * p.n16;
+  const uint32_t *lists = p.lists + base * p.list_row, *live = p.live[round] + (size_t)ut * p.T;
+  uint32_t *next[2] = {p.live[1] + (size_t)ut * p.T, p.live[2] + (size_t)ut * p.T};
+  int *slot = p.slot + base;
+  uint32_t bits = 0;
+  for (int k = 0; k < 4; ++k) {
+    if (((cand >> (8 * k)) & 0xFFu) == 0) continue;   // wave-uniform
+    const bool on = (cand >> (8 * k + seg)) & 1;
+    const int u = on ? W * kTile + 8 * k + seg : W * kTile;
+    const Row r = row_at(p, base, lists, u);
     const uint32_t ku = key[u];
-    const int d0 = p.deg0[base + u];
-    int b[4];
-    bool there[4] = {false, false, false, false};
-    uint32_t mk = 0;
-    int rk = 0;                                       // remaining neighbours in this lane's slots
-    const u4 *row = reinterpret_cast<const u4 *>(p.G + (base + u) * p.Wp);
-    if (d0 <= kListCap) {
-      const uint2 raw = *reinterpret_cast<const uint2 *>(p.nbr + (base + u) * kListCap + 4 * lane);
-      uint32_t kk[4], q[4];
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const int s = 4 * lane + t;                  // slot -> position in the list (inverse of list_slot)
-        const int at = (s & ~127) | ((s & 15) << 3) | ((s & 127) >> 4);
-        b[t] = (int)(((t < 2 ? raw.x : raw.y) >> (16 * (t & 1))) & 0xFFFFu);
-        there[t] = at < d0;
-        kk[t] = key[there[t] ? b[t] : u];
-      }
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        there[t] = there[t] && kk[t] != 0;           // remaining = key != 0 (keys change later in the round)
-        q[t] = m1[there[t] ? b[t] : u];
-      }
-#pragma unroll
-      for (int t = 0; t < 4; ++t)
-        if (there[t]) { mk = q[t] > mk ? q[t] : mk; ++rk; }
-    } else {
-      for (int w4 = lane; w4 < p.Wp / 4; w4 += kWave) {
-        const u4 qw = row[w4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          uint32_t bits = qw[j];
-          while (bits) {
-            const int t = __builtin_ctz(bits);
-            bits &= bits - 1;
-            const int v = (w4 * 4 + j) * 32 + t;
-            if (key[v] != 0) { const uint32_t q = m1[v]; mk = q > mk ? q : mk; ++rk; }
-          }
-        }
+    uint32_t m = 0;
+    for (int i = sl; on && i < r.n; i += kSegW) {
+      const uint32_t w = word_at(r, i);
+      const uint32_t rem = still(live, w);            // neighbours still there at the start of the round
+      if (rem) m = masked_max(m1, (w & 0xFFFF0000u) | rem, m);
+    }
+    const bool pick = on && seg_max(m) == ku;
+    bits |= seg_bits(pick) << (8 * k);
+    if (pick) {
+      if (sl == 0) p.pick_key[base + u] = ku;
+      for (int i = sl; i < r.n; i += kSegW) {
+        const uint32_t w = word_at(r, i);
+        uint32_t rem = still(live, w);
+        if (rem == 0) continue;
+        const uint32_t clear = ~(rem << ((w >> 12) & 16));
+        if (round == 0) atomicAnd(next[0] + (w >> 17), clear);
+        atomicAnd(next[1] + (w >> 17), clear);
+        do {
+          slot[(w >> 16) * 16 + __builtin_ctz(rem)] = u;
+          rem &= rem - 1;
+        } while (rem);
       }
     }
+  }
+  if (lane == 0) *picked = (round == 0 ? 0u : *picked) | bits;
+}
+
+__global__ __launch_bounds__(kPhaseThreads) void merge_update(ShallowParams p, int round) {
+  const int ut = blockIdx.y, W = (int)blockIdx.x * (kPhaseThreads / kWave) + (int)(threadIdx.x >> 6);
+  if (W >= p.T) return;
+  const int lane = lane_id(), seg = lane / kSegW, sl = lane & (kSegW - 1);
+  const uint32_t *next = p.live[round + 1] + (size_t)ut * p.T;
+  const uint32_t was = __builtin_amdgcn_readfirstlane(p.live[round][(size_t)ut * p.T + W]);
+  const uint32_t now = __builtin_amdgcn_readfirstlane(next[W]);
+  if (was == 0) return;
+  const size_t base = (size_t)ut * p.n;
+  uint32_t *key = p.key + (size_t)ut * p.n16 + W * kTile;
+  const uint32_t *lists = p.lists + base * p.list_row;
+  if (lane < kTile && ((was & ~now) >> lane & 1)) key[lane] = 0;
+  if (now == 0) return;
+  Row r[4];
+  uint32_t w0[4], own[4];
+  bool on[4];
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      const uint32_t x = __shfl_xor(mk, o);
-      mk = x > mk ? x : mk;
+  for (int k = 0; k < 4; ++k) {
+    on[k] = (now >> (8 * k + seg)) & 1;
+    r[k] = row_at(p, base, lists, on[k] ? W * kTile + 8 * k + seg : W * kTile);
+    own[k] = on[k] ? key[8 * k + seg] : 0;
+  }
+#pragma unroll
+  for (int k = 0; k < 4; ++k) w0[k] = on[k] && sl < r[k].n ? word_at(r[k], sl) : 0;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    int c = __popc(still(next, w0[k]));
+    for (int i = sl + kSegW; on[k] && i < r[k].n; i += kSegW) c += __popc(still(next, word_at(r[k], i)));
+    c = seg_sum(c);
+    if (on[k] && sl == 0) key[8 * k + seg] = ((uint32_t)c << 16) | (own[k] & 0xFFFFu);
+  }
+}
+
+// ---------------------------------------------------------------- remaining rounds
+// State of one problem in the workgroup: keys in LDS (or global memory), bits in LDS.
+struct Tail {
+  const uint32_t *lists;
+  uint32_t *key, *live, *next;
+  int *n_cand, *n_dying;
+  int seg, sl;
+};
+constexpr int kTailSegs = kMergeThreads / kSegW;
+
+__device__ __forceinline__ void tail_onehop(const ShallowParams &p, size_t base, const Tail &w, uint32_t *m1,
+                                            const int *alive, int nalive) {
+  int *cand = p.cand + base;
+  for (int i0 = 0; i0 < nalive; i0 += 4 * kTailSegs) {
+    Row r[4];
+    int vv[4];
+    bool on[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int i = i0 + k * kTailSegs + w.seg;
+      on[k] = i < nalive;
+      vv[k] = on[k] ? alive[i] : 0;
     }
-    if (mk != ku) continue;                           // wave-uniform: not the largest key within two hops
-    int s = 0;
-    if (lane == 0) {
-      s = atomicAdd(n_picks, 1);
-      pick_key[s] = ku;
-      pick_vert[s] = u;
-    }
-    s = __shfl(s, 0);
-    int incl = rk;
 #pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-      const int x = __shfl_up(incl, o);
-      if (lane >= o) incl += x;
-    }
-    int at = 0;
-    if (lane == kWave - 1) at = atomicAdd(n_dying, incl);
-    at = __shfl(at, kWave - 1) + incl - rk;
-    auto take = [&](int v) {
-      slot[v] = s;
-      gone[v] = 1;
-      dying[at++] = v;
-    };
-    if (d0 <= kListCap) {
+    for (int k = 0; k < 4; ++k) r[k] = row_at(p, base, w.lists, vv[k]);
 #pragma unroll
-      for (int t = 0; t < 4; ++t)
-        if (there[t]) take(b[t]);
-    } else {
-      for (int w4 = lane; w4 < p.Wp / 4; w4 += kWave) {
-        const u4 qw = row[w4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          uint32_t bits = qw[j];
-          while (bits) {
-            const int t = __builtin_ctz(bits);
-            bits &= bits - 1;
-            const int v = (w4 * 4 + j) * 32 + t;
-            if (key[v] != 0) take(v);
-          }
-        }
+    for (int k = 0; k < 4; ++k) {
+      const uint32_t own = on[k] ? w.key[vv[k]] : 0;
+      uint32_t m = own;
+      for (int i = w.sl; on[k] && i < r[k].n; i += kSegW) {
+        const uint32_t x = word_at(r[k], i);
+        if (x & 0xFFFFu) m = masked_max(w.key, x, m);
+      }
+      m = seg_max(m);
+      if (on[k] && w.sl == 0) {
+        m1[vv[k]] = m;
+        if (m == own) cand[atomicAdd(w.n_cand, 1)] = vv[k];
       }
     }
   }
 }
-// End of a grid round.  Tokens marked dead get key 0; every other token of the list counts
-// its neighbours that are not dead (its new degree, Eq. 13: with most tokens leaving in the
-// first rounds, recounting the few that stay is cheaper than subtracting at every
-// neighbour of every leaving token), gets its new key and moves to the other list.
-__global__ __launch_bounds__(kMergeThreads) void merge_update(ShallowParams p, int round) {
-  extern __shared__ __attribute__((aligned(16))) uint32_t lds[];     // dead flags of the problem, one byte per token
-  constexpr int kPer = kWave / kSegW;
-  const int ut = blockIdx.y, lane = lane_id(), n = p.n;
-  const size_t base = (size_t)ut * n;
-  int *cnt = p.counters + (size_t)ut * kCounters;
-  const int nalive = cnt[alive_slot(round)];
-  const int seg = (blockIdx.x * blockDim.x + threadIdx.x) / kSegW, nsegs = gridDim.x * blockDim.x / kSegW;
-  const int sl = threadIdx.x & (kSegW - 1);
-  if ((int)(blockIdx.x * blockDim.x / kSegW) >= nalive) return;
-  {
-    const u4 *src8 = reinterpret_cast<const u4 *>(p.gone8 + (size_t)ut * p.n16);
-    for (int i = threadIdx.x; i < p.n16 / 16; i += blockDim.x) reinterpret_cast<u4 *>(lds)[i] = src8[i];
-  }
-  __syncthreads();
-  const uint8_t *dead = reinterpret_cast<const uint8_t *>(lds);
-  const int *src = (round & 1 ? p.alive2 : p.alive) + base;
-  int *dst = (round & 1 ? p.alive : p.alive2) + base;
-  uint32_t *key = p.key + base;
-  __shared__ int wave_total[kMergeThreads / kWave], block_at;
-  const int wave = threadIdx.x / kWave;
-  // block-uniform trip count (the appends below synchronise the block): waves past the end
-  // of the list run with all lanes idle
-  for (int b0 = blockIdx.x * blockDim.x / kSegW; b0 < nalive; b0 += 4 * nsegs) {
-    const int i0 = b0 + wave * kPer;
-    int vv[4];
-    bool live[4];
-    Nbrs r[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int i = i0 + seg % kPer + k * nsegs;
-      vv[k] = i < nalive ? src[i] : -1;
-      live[k] = vv[k] >= 0 && !dead[vv[k]];
-      if (vv[k] >= 0 && !live[k] && sl == 0) key[vv[k]] = 0;
+
+__device__ __forceinline__ void tail_twohop(const ShallowParams &p, int ut, size_t base, const Tail &w,
+                                            const uint32_t *m1, int ncand) {
+  const int *cand = p.cand + base;
+  int *slot = p.slot + base, *dying = p.dying + base;
+  for (int i0 = w.seg; i0 < ncand; i0 += kTailSegs) {
+    const int u = cand[i0];
+    const Row r = row_at(p, base, w.lists, u);
+    const uint32_t ku = w.key[u];
+    uint32_t m = 0;
+    for (int i = w.sl; i < r.n; i += kSegW) {
+      const uint32_t x = word_at(r, i);
+      const uint32_t rem = still(w.live, x);
+      if (rem) m = masked_max(m1, (x & 0xFFFF0000u) | rem, m);
     }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) r[k] = load_nbrs(p, base, live[k] ? vv[k] : 0, sl);
-    unsigned long long mk[4];
-    int mine = 0;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      int c = 0;
-      if (live[k])
-        for_nbrs4(p, r[k], sl,
-                  [&](const int *b, const bool *ok) {
-                    uint8_t gone[4];
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) gone[t] = dead[ok[t] ? b[t] : 0];
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) c += ok[t] && !gone[t];
-                  },
-                  [&](int b) { c += !dead[b]; });
-      c = seg_sum(c);
-      const bool lead = live[k] && sl == 0;
-      if (lead) key[vv[k]] = ((uint32_t)c << 16) | (uint32_t)(0xFFFF - vv[k]);
-      mk[k] = __ballot(lead);
-      mine += __popcll(mk[k]);
+    if (seg_max(m) != ku) continue;
+    if (w.sl == 0) {
+      p.pick_key[base + u] = ku;
+      atomicOr(p.picked + (size_t)ut * p.T + (u >> 5), 1u << (u & 31));
     }
-    // one counter update per block and trip: same-address atomics are served one at a time
-    if (lane == 0) wave_total[wave] = mine;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      int t = 0;
-      for (int q = 0; q < kMergeThreads / kWave; ++q) t += wave_total[q];
-      block_at = t ? atomicAdd(&cnt[alive_slot(round + 1)], t) : 0;
+    for (int i = w.sl; i < r.n; i += kSegW) {
+      const uint32_t x = word_at(r, i);
+      uint32_t rem = still(w.live, x);
+      if (rem == 0) continue;
+      atomicAnd(&w.next[x >> 17], ~(rem << ((x >> 12) & 16)));
+      int at = atomicAdd(w.n_dying, __popc(rem));
+      do {
+        const int v = (int)(x >> 16) * 16 + __builtin_ctz(rem);
+        rem &= rem - 1;
+        slot[v] = u;
+        dying[at++] = v;
+      } while (rem);
     }
-    __syncthreads();
-    int at = block_at;
-    for (int q = 0; q < wave; ++q) at += wave_total[q];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      if (live[k] && sl == 0) dst[at + __popcll(mk[k] & ((1ull << lane) - 1ull))] = vv[k];
-      at += __popcll(mk[k]);
-    }
-    __syncthreads();                                 // wave_total is rewritten by the next trip
   }
 }
 
@@ -633,70 +312,75 @@ __global__ __launch_bounds__(kMergeThreads) void merge_update(ShallowParams p, i
     tick_ = now_;                              \
   }
 
-// Remaining rounds and the outputs, one workgroup per problem.
 __global__ __launch_bounds__(kMergeThreads) void shallow_merge(ShallowParams p) {
   extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
-  __shared__ int sh_n[4];                     // alive, candidates, dying, picks
-  const int ut = blockIdx.x, n = p.n, tid = threadIdx.x;
+  __shared__ int sh_n[3];                     // alive, candidates, dying
+  __shared__ int wsum[kMergeThreads / kWave];
+  const int ut = blockIdx.x, n = p.n, T = p.T, tid = threadIdx.x;
   const int lane = lane_id(), wave = tid >> 6;
   const size_t base = (size_t)ut * n;
   const bool keys_in_lds = n <= kKeysInLds;
-  const int dead_words = (n + 31) / 32;
   int *cnt = p.counters + (size_t)ut * kCounters;
-  MergeView w;
-  w.key = keys_in_lds ? lds : p.key + base;
-  w.dead = keys_in_lds ? lds + ((n + 3) & ~3) : p.gone + base;
-  w.n_alive = &sh_n[0]; w.n_cand = &sh_n[1]; w.n_dying = &sh_n[2]; w.n_picks = &sh_n[3];
-  w.seg = tid / kSegW; w.nsegs = kMergeThreads / kSegW; w.sl = tid & (kSegW - 1);
-  int *slot = p.slot + base, *dying = p.dying + base;
-  // the list the last grid round left behind; this kernel compacts it in place
-  int *alive = (kGridRounds & 1 ? p.alive2 : p.alive) + base;
+  uint32_t *gkey = p.key + (size_t)ut * p.n16, *m1 = p.m1 + (size_t)ut * p.n16;
+  Tail w;
+  w.lists = p.lists + base * p.list_row;
+  w.live = lds;
+  w.next = lds + ((T + 3) & ~3);
+  w.key = keys_in_lds ? w.next + ((T + 3) & ~3) : gkey;
+  w.n_cand = &sh_n[1]; w.n_dying = &sh_n[2];
+  w.seg = tid / kSegW; w.sl = tid & (kSegW - 1);
+  int *alive = p.alive + base;
+  const int *dying = p.dying + base;
   long long tick_ = 0;
   if (tid == 0) tick_ = wall_clock64();
 
-  if (keys_in_lds) {
-    if ((n & 3) == 0) {                               // rows of the key array are then 16-byte aligned
-      const u4 *src = reinterpret_cast<const u4 *>(p.key + base);
-      for (int i = tid; i < n / 4; i += kMergeThreads) reinterpret_cast<u4 *>(w.key)[i] = src[i];
-    } else {
-      for (int v = tid; v < n; v += kMergeThreads) w.key[v] = p.key[base + v];
-    }
-  }
-  {
-    // the grid rounds keep one byte (0 or 1) per token; this kernel works on a bitmap
-    const u4 *g8 = reinterpret_cast<const u4 *>(p.gone8 + (size_t)ut * p.n16);   // 16-byte aligned rows of n16 bytes
-    for (int i = tid; i < dead_words; i += kMergeThreads) {
-      uint32_t word = 0;
+  // tokens left after the grid rounds, as a list
+  const uint32_t *glive = p.live[kGridRounds] + (size_t)ut * T;
+  if (tid < 3) sh_n[tid] = 0;
+  for (int w0 = 0; w0 < T; w0 += kMergeThreads) {
+    const int i = w0 + tid;
+    uint32_t bits = i < T ? glive[i] : 0;
+    if (i < T) w.live[i] = w.next[i] = bits;
+    int incl = __popc(bits);
+    const int mine = incl;
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const u4 q = 2 * i + h < p.n16 / 16 ? g8[2 * i + h] : u4{0, 0, 0, 0};
-#pragma unroll
-        for (int j = 0; j < 4; ++j)                    // four 0/1 bytes -> four bits
-          word |= (((q[j] & 0x01010101u) * 0x01020408u) >> 24 & 0xFu) << (16 * h + 4 * j);
-      }
-      w.dead[i] = word;
+    for (int o = 1; o < kWave; o <<= 1) {
+      const int x = __shfl_up(incl, o);
+      if (lane >= o) incl += x;
     }
+    __syncthreads();                                  // wsum of the trip before has been read
+    if (lane == kWave - 1) wsum[wave] = incl;
+    __syncthreads();
+    int at = sh_n[0] + incl - mine;
+    for (int q = 0; q < wave; ++q) at += wsum[q];
+    for (; bits; bits &= bits - 1) alive[at++] = i * 32 + __builtin_ctz(bits);
+    __syncthreads();
+    if (tid == kMergeThreads - 1) sh_n[0] = at;
   }
-  if (tid == 0) { sh_n[0] = cnt[alive_slot(kGridRounds)]; sh_n[1] = 0; sh_n[2] = 0; sh_n[3] = cnt[C_PICKS]; }
+  __syncthreads();
+  if (sh_n[0] > 0 && keys_in_lds) {
+    const u4 *src = reinterpret_cast<const u4 *>(gkey);
+    for (int i = tid; i < p.n16 / 4; i += kMergeThreads) reinterpret_cast<u4 *>(w.key)[i] = src[i];
+  }
   __syncthreads();
   MERGE_TICK(0)
 
   // every round removes at least the token of largest key, so n rounds always suffice;
-  // the bound only guards against a corrupted adjacency matrix
+  // the bound only guards against a workspace overwritten under the running call
   int round = kGridRounds;
   for (; round <= n + kGridRounds; ++round) {
     const int nalive = sh_n[0];
     if (nalive == 0) break;
-    phase_onehop(p, base, w, alive, nalive);
+    tail_onehop(p, base, w, m1, alive, nalive);
     __syncthreads();
     MERGE_TICK(2)
-    phase_twohop<false, 2>(p, base, w, sh_n[1]);
+    tail_twohop(p, ut, base, w, m1, sh_n[1]);
     __syncthreads();
     MERGE_TICK(4)
     const int ndying = sh_n[2];
     for (int i = tid; i < ndying; i += kMergeThreads) w.key[dying[i]] = 0;
-    if (tid == 0) { sh_n[0] = 0; sh_n[1] = 0; sh_n[2] = 0; }
     __syncthreads();
+    if (tid < 3) sh_n[tid] = 0;
     // survivors, compacted in place (each wave appends its survivors with one LDS atomic;
     // the write index never passes the read index of a later chunk because chunks are
     // consumed by all waves in lock step)
@@ -715,53 +399,52 @@ __global__ __launch_bounds__(kMergeThreads) void shallow_merge(ShallowParams p) 
     MERGE_TICK(0)
     // degrees of the survivors (Eq. 13): subtract at the neighbours of the tokens that left,
     // or recount at the tokens that stayed, whichever list is shorter
-    if (ndying <= nalive - ndying) phase_degree(p, base, w, ndying);
-    else phase_recount(p, base, w, alive, nalive - ndying);
+    const int nleft = nalive - ndying;
+    if (ndying <= nleft) {
+      for (int i0 = w.seg; i0 < ndying; i0 += kTailSegs) {
+        const Row r = row_at(p, base, w.lists, dying[i0]);
+        for (int i = w.sl; i < r.n; i += kSegW) {
+          const uint32_t x = word_at(r, i);
+          for (uint32_t rem = still(w.next, x); rem; rem &= rem - 1)
+            atomicSub(&w.key[(x >> 16) * 16 + __builtin_ctz(rem)], 1u << 16);
+        }
+      }
+    } else {
+      for (int i0 = w.seg; i0 < nleft; i0 += kTailSegs) {
+        const int v = alive[i0];
+        const Row r = row_at(p, base, w.lists, v);
+        int c = 0;
+        for (int i = w.sl; i < r.n; i += kSegW) c += __popc(still(w.next, word_at(r, i)));
+        c = seg_sum(c);
+        if (w.sl == 0) w.key[v] = ((uint32_t)c << 16) | (w.key[v] & 0xFFFFu);
+      }
+    }
+    for (int i = tid; i < T; i += kMergeThreads) w.live[i] = w.next[i];
     __syncthreads();
     MERGE_TICK(6)
   }
-  if (tid == 0) cnt[C_ROUNDS] = round;
-  if (sh_n[0] != 0) return;                      // did not converge: n_codes stays -1
-
-  const int P = sh_n[3];
-  if (tid == 0) cnt[C_PICKS] = P;
-  MERGE_TICK(8)
-
-  const int t = ut / p.U, u = ut % p.U;
   if (tid == 0) {
-    p.n_codes[t][u] = P < p.cap ? P : p.cap;
-    if (p.n_found[t]) p.n_found[t][u] = P;
+    cnt[C_ROUNDS] = round;
+    cnt[C_DONE] = sh_n[0] == 0;                      // (else n_codes stays -1)
   }
-  MERGE_TICK(9)
+  MERGE_TICK(8)
 }
 
 }  // namespace
 
 spindle_status launch_merge(const ShallowParams &p, hipStream_t st) {
   const int n = p.n;
-  int gx = (n + 4 * (kPhaseThreads / kSegW) - 1) / (4 * (kPhaseThreads / kSegW));
-  if (gx > 256) gx = 256;
-  // candidates are a small part of the tokens: an eighth of the blocks that would give every
-  // 8-lane segment four rows (a grid of mostly idle blocks costs more than a second trip)
-  const dim3 tg(gx / 8 > 0 ? gx / 8 : 1, p.UT);
-  // one-hop phase: 1024-thread blocks with the keys of the problem in LDS when they fit
-  const int keys_in_lds = n <= kKeysInLds;
-  const size_t key_lds = keys_in_lds ? (size_t)((n + 3) & ~3) * sizeof(uint32_t) : 0;
-  int ox = (n + 4 * (kMergeThreads / kSegW) - 1) / (4 * (kMergeThreads / kSegW));
-  if (ox > 16) ox = 16;
-  static LdsLimit lim_onehop, lim_update, lim_merge;      // raised once per device to the largest size in use
-  if (spindle_status e = allow_lds(lim_onehop, reinterpret_cast<const void *>(&merge_onehop), kKeysInLds * sizeof(uint32_t))) return e;
-  const size_t dead_lds = (size_t)p.n16;
-  if (spindle_status e = allow_lds(lim_update, reinterpret_cast<const void *>(&merge_update), 65536)) return e;
-  if (spindle_status e = allow_lds(lim_merge, reinterpret_cast<const void *>(&shallow_merge),
-                                   (kKeysInLds + kKeysInLds / 32) * sizeof(uint32_t))) return e;
+  const dim3 pg((unsigned)((p.T + kPhaseThreads / kWave - 1) / (kPhaseThreads / kWave)), p.UT);
   for (int round = 0; round < kGridRounds; ++round) {
     ProfScope ps("shallow_merge_grid", st);
-    hipLaunchKernelGGL(merge_onehop, dim3(ox, p.UT), dim3(kMergeThreads), key_lds, st, p, round, keys_in_lds);
-    hipLaunchKernelGGL(merge_twohop, tg, dim3(kPhaseThreads), 0, st, p, round);
-    hipLaunchKernelGGL(merge_update, dim3(ox, p.UT), dim3(kMergeThreads), dead_lds, st, p, round);   // 1024 threads: fewer copies of the flags
+    hipLaunchKernelGGL(merge_onehop, pg, dim3(kPhaseThreads), 0, st, p, round);
+    hipLaunchKernelGGL(merge_twohop, pg, dim3(kPhaseThreads), 0, st, p, round);
+    hipLaunchKernelGGL(merge_update, pg, dim3(kPhaseThreads), 0, st, p, round);
   }
-  const size_t merge_lds = n <= kKeysInLds ? ((size_t)((n + 3) & ~3) + (n + 31) / 32) * sizeof(uint32_t) : 0;
+  static LdsLimit lim_merge;                              // raised once per device to the largest size in use
+  if (spindle_status e = allow_lds(lim_merge, reinterpret_cast<const void *>(&shallow_merge),
+                                   (kKeysInLds + 2 * (kKeysInLds / 32 + 4)) * sizeof(uint32_t))) return e;
+  const size_t merge_lds = ((n <= kKeysInLds ? (size_t)p.n16 : 0) + 2 * (size_t)((p.T + 3) & ~3)) * sizeof(uint32_t);
   { ProfScope ps("shallow_merge", st);
   hipLaunchKernelGGL(shallow_merge, dim3(p.UT), dim3(kMergeThreads), merge_lds, st, p); }
   SPINDLE_HIP(hipGetLastError());

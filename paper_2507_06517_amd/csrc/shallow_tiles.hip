@@ -1,0 +1,694 @@
+// Similarity graph of the codebook path as neighbour lists (Eq. 4, 9, 10): the tokens sorted so that
+// similar ones stand together, the pairs of 32-token tiles that can hold a pair above theta found
+// from short sketches, and the cosines themselves only for those.
+#include "mma.h"
+#include "shallow.h"
+
+namespace spindle {
+namespace {
+
+typedef int i4v __attribute__((ext_vector_type(4)));
+typedef int i16v __attribute__((ext_vector_type(16)));
+
+// Blocks are dealt round-robin to the 8 XCDs; this numbering gives each XCD a run of consecutive
+// items (a problem's blocks share its L2).  The launch has a multiple of 8 blocks.
+__device__ __forceinline__ int xcd_item() { return (int)(blockIdx.x & 7) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3); }
+inline unsigned xcd_grid(size_t items) { return (unsigned)align_up(items, 8); }
+
+// ---------------------------------------------------------------- order
+// Every token goes to a pivot (up to 1024 tokens taken at equal distances): the lowest one whose sketch
+// product lies in the same step of 16384 (0.18 of a cosine) as the largest.  The lowest instead of
+// the nearest, so that the tokens of one cluster stay together when several pivots belong to it, and
+// mostly also when none does and the products are all small.  The steps end at 0.51, 0.70, 0.88: near
+// 0.53, where the products of unrelated tokens lie, a step would gather every second pivot's tokens at
+// the lowest pivots (kStepOffset moves them away from there).
+constexpr int kStepOffset = 3000;
+constexpr int kPivotThreads = 256;
+
+__global__ __launch_bounds__(kPivotThreads) void shallow_pivots(ShallowParams p, int npiv, int nblk) {
+  __shared__ __attribute__((aligned(16))) char piv[kPivots * kSketchBytes];    // fragment order: tile, half, lane
+  __shared__ uint32_t cnt[kPivots];
+  const int item = xcd_item();
+  if (item >= p.UT * nblk) return;
+  const int ut = item / nblk, blk = item % nblk, n = p.n;
+  const uint8_t *sk = p.sk0 + (size_t)ut * n * kSketchBytes;
+  const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6, g = lane >> 5, c = lane & 31;
+  for (int i = tid; i < npiv * 4; i += kPivotThreads) {
+    const int j = i >> 2, piece = i & 3;               // piece = 2 * half + lane group
+    const int tok = (int)((long)j * n / npiv);
+    *reinterpret_cast<u4 *>(piv + (j >> 5) * kTileBytes + (piece >> 1) * 1024 + ((piece & 1) * 32 + (j & 31)) * 16) =
+        *reinterpret_cast<const u4 *>(sk + (size_t)tok * kSketchBytes + piece * 16);
+  }
+  for (int i = tid; i < kPivots; i += kPivotThreads) cnt[i] = 0;
+  // the wave's 128 tokens: matrix columns = lanes
+  i4v bf[4][2];
+  int tok[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    tok[r] = blk * kOrderTokens + wave * 128 + r * 32 + c;
+    const uint8_t *s = sk + (size_t)(tok[r] < n ? tok[r] : n - 1) * kSketchBytes + g * 16;
+    bf[r][0] = *reinterpret_cast<const i4v *>(s);
+    bf[r][1] = *reinterpret_cast<const i4v *>(s + 32);
+  }
+  __syncthreads();
+  int best[4] = {INT32_MIN, INT32_MIN, INT32_MIN, INT32_MIN};
+  for (int pt = 0; pt < npiv / 32; ++pt) {
+    const i4v a0 = *reinterpret_cast<const i4v *>(piv + pt * kTileBytes + lane * 16);
+    const i4v a1 = *reinterpret_cast<const i4v *>(piv + pt * kTileBytes + 1024 + lane * 16);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      i16v acc;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[v] = kStepOffset;
+      acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(a0, bf[r][0], acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(a1, bf[r][1], acc, 0, 0, 0);
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int x = (acc[v] & ~16383) | (kPivots - 1 - (pt * 32 + mma_row(v, g)));
+        best[r] = x > best[r] ? x : best[r];
+      }
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int o = __shfl_xor(best[r], 32);
+    const int b = kPivots - 1 - ((o > best[r] ? o : best[r]) & 16383);
+    if (g == 0 && tok[r] < n) {
+      p.bucket[(size_t)ut * n + tok[r]] = (uint16_t)b;
+      atomicAdd(&cnt[b], 1u);
+    }
+  }
+  __syncthreads();
+  uint16_t *h = p.hist + ((size_t)ut * nblk + blk) * kPivots;
+  for (int i = tid; i < kPivots; i += kPivotThreads) h[i] = (uint16_t)cnt[i];
+}
+
+// Tokens in the order of their pivots: a counting sort whose counts shallow_pivots left per block of
+// tokens (every block adds up the ones it needs, so no launch in between).
+__global__ __launch_bounds__(kPivots) void shallow_order(ShallowParams p, int nblk) {
+  __shared__ int cursor[kPivots];
+  __shared__ int wsum[kPivots / kWave];
+  const int item = xcd_item();
+  if (item >= p.UT * nblk) return;
+  const int ut = item / nblk, blk = item % nblk, n = p.n;
+  const size_t base = (size_t)ut * n;
+  const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
+  const uint16_t *h = p.hist + (size_t)ut * nblk * kPivots + tid;
+  int total = 0, before = 0;
+#pragma unroll 8
+  for (int k = 0; k < nblk; ++k) {
+    const int x = h[(size_t)k * kPivots];
+    total += x;
+    before += k < blk ? x : 0;
+  }
+  int incl = total;
+#pragma unroll
+  for (int o = 1; o < kWave; o <<= 1) {
+    const int x = __shfl_up(incl, o);
+    if (lane >= o) incl += x;
+  }
+  if (lane == kWave - 1) wsum[wave] = incl;
+  __syncthreads();
+  for (int w = 0; w < wave; ++w) incl += wsum[w];
+  cursor[tid] = incl - total + before;
+  if (blk == 0) p.first[(size_t)ut * kPivots + tid] = incl - total;
+  __syncthreads();
+  const int tok = blk * kOrderTokens + tid;
+  if (tid < kOrderTokens && tok < n) p.perm[base + atomicAdd(&cursor[p.bucket[base + tok]], 1)] = (uint16_t)tok;
+}
+
+// A window of 2048 places in that order: the tokens of each pivot sorted by eight signs of their
+// sketches (a token counts the ones of its pivot that go before it), which keeps together what has no
+// pivot of its own.  Then everything later kernels read by position.  Sketches go to fragment order:
+// tile, half of the 64 bytes, lane.
+constexpr int kWindow = 2048;
+constexpr int kWindowThreads = 1024;
+
+__global__ __launch_bounds__(kWindowThreads) void shallow_window(ShallowParams p, int nwin) {
+  __shared__ __attribute__((aligned(16))) uint32_t order_by[kWindow];   // signs << 16 | place in the window
+  __shared__ uint16_t at_place[kWindow];
+  const int item = xcd_item();
+  if (item >= p.UT * nwin) return;
+  const int ut = item / nwin, n = p.n, w0 = (item % nwin) * kWindow, w1 = min(n, w0 + kWindow);
+  const size_t base = (size_t)ut * n;
+  const int tid = threadIdx.x;
+  int tok[2], lo[2], hi[2];
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const int i = tid + k * kWindowThreads;
+    tok[k] = -1;
+    if (w0 + i < w1) {
+      tok[k] = (int)p.perm[base + w0 + i];
+      const int b = (int)p.bucket[base + tok[k]];
+      const int *first = p.first + (size_t)ut * kPivots + b;
+      lo[k] = max(first[0], w0) - w0;
+      hi[k] = min(b + 1 < kPivots ? first[1] : n, w1) - w0;
+      const uint2 s = *reinterpret_cast<const uint2 *>(p.sk0 + (base + tok[k]) * kSketchBytes);
+      const uint32_t signs = ((s.x >> 7 & 0x01010101u) * 0x10204080u >> 28) | ((s.y >> 7 & 0x01010101u) * 0x10204080u >> 28 << 4);
+      order_by[i] = signs << 16 | (uint32_t)i;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    if (tok[k] < 0) continue;
+    const uint32_t own = order_by[tid + k * kWindowThreads];
+    int r = lo[k];
+#pragma unroll 8
+    for (int j = lo[k]; j < hi[k]; ++j) r += order_by[j] < own;
+    at_place[r] = (uint16_t)tok[k];
+  }
+  __syncthreads();
+  int8_t *sk = p.sk + (size_t)ut * p.Tp * kTileBytes;
+  const int end = w1 < n ? w1 : p.Tp * kTile;         // the last window also fills the places past the last token
+  for (int pos = w0 + tid; pos < end; pos += kWindowThreads) {
+    u4 *d = reinterpret_cast<u4 *>(sk + (size_t)(pos >> 5) * kTileBytes);
+    uint32_t e = 0;
+    if (pos < n) {
+      const int t = (int)at_place[pos - w0];
+      p.perm[base + pos] = (uint16_t)t;
+      p.iperm[base + t] = (uint16_t)pos;
+      p.invp[base + pos] = p.inv[base + t];
+      const u4 *s = reinterpret_cast<const u4 *>(p.sk0 + (base + t) * kSketchBytes);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) d[(k >> 1) * 64 + (k & 1) * 32 + (pos & 31)] = s[k];
+      e = p.serr[base + t];
+    } else {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) d[(k >> 1) * 64 + (k & 1) * 32 + (pos & 31)] = u4{0, 0, 0, 0};
+    }
+#pragma unroll
+    for (int o = 16; o > 0; o >>= 1) e = max(e, (uint32_t)__shfl_xor((int)e, o));
+    if ((pos & 31) == 0) p.etile[(size_t)ut * p.Tp + (pos >> 5)] = e;
+  }
+}
+
+// ---------------------------------------------------------------- scan
+// A block takes a panel of 16 row tiles (four per wave, their sketches in registers as the matrix
+// columns) against a run of column tiles from its own first tile onwards, staged through LDS eight at
+// a time (fragment order: loads and reads are both linear, no bank conflicts).  Per 32 x 32 pairs two
+// 32x32x32 int8 matrix instructions; all the results are needed for is their maximum, eight
+// v_max3 per lane, and one comparison for the wave's four tiles.  Tiles that pass are marked in both
+// directions.  16 problems of 32768 tokens: 0.38 ms = 2.9 POP/s, bound by the matrix cores (3.2 POP/s
+// from registers); all cosines in fp16, with the bits packed and records written, took 1.80 ms.
+constexpr int kScanThreads = 256;
+
+__global__ __launch_bounds__(kScanThreads, 2) void shallow_scan(ShallowParams p, int stages_per_item, int njg) {
+  __shared__ __attribute__((aligned(1024))) char stage[2][kScanStage * kTileBytes];
+  const int nI = p.Tp / kScanPanel, nS = p.Tp / kScanStage;
+  // blocks are dealt round-robin to the 8 XCDs: an XCD sweeps the panels of one (problem, column group) at a time, the groups
+  // rotated by problem so that every XCD sees long and short ones
+  const int xcd = blockIdx.x & 7, s_ = blockIdx.x >> 3;
+  const int I = s_ % nI, pj = (s_ / nI) * 8 + xcd;
+  if (pj >= p.UT * njg) return;
+  const int ut = pj / njg, Jg = (pj % njg + ut) % njg;
+  int s0 = Jg * stages_per_item, s1 = s0 + stages_per_item;
+  if (s0 < I * (kScanPanel / kScanStage)) s0 = I * (kScanPanel / kScanStage);
+  if (s1 > nS) s1 = nS;
+  if (s0 >= s1) return;
+  const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const char *sk = reinterpret_cast<const char *>(p.sk) + (size_t)ut * p.Tp * kTileBytes;
+  const uint32_t *et = p.etile + (size_t)ut * p.Tp;
+  const int r0 = I * kScanPanel + wave * 4;
+  const int thr0 = p.scan_thr[ut / p.U];
+  i4v bf[4][2];
+  int ethr[4];                                         // theta less the row tile's error
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    bf[r][0] = *reinterpret_cast<const i4v *>(sk + (size_t)(r0 + r) * kTileBytes + lane * 16);
+    bf[r][1] = *reinterpret_cast<const i4v *>(sk + (size_t)(r0 + r) * kTileBytes + 1024 + lane * 16);
+    ethr[r] = thr0 - (int)et[r0 + r];
+  }
+  const int emin = min(min(ethr[0], ethr[1]), min(ethr[2], ethr[3]));
+  const uint32_t stage_lds = (uint32_t)(size_t)(__attribute__((address_space(3))) char *)stage;
+  auto dma = [&](int s) {
+    const char *src = sk + (size_t)s * (kScanStage * kTileBytes) + wave * 4096;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      lds_dma16_at(src, (uint32_t)(q * 1024 + lane * 16),
+                   stage_lds + (s & 1) * (kScanStage * kTileBytes) + wave * 4096 + q * 1024);
+  };
+  dma(s0);
+  for (int s = s0; s < s1; ++s) {
+    const int ecol = (int)et[s * kScanStage + (lane & 7)];
+    __builtin_amdgcn_s_waitcnt(0x0F70);                // vmcnt(0): this wave's part of stage s has landed
+    __syncthreads();                                   // ... and every wave's; the other buffer is free
+    if (s + 1 < s1) dma(s + 1);
+    const char *st = stage[s & 1];
+#pragma unroll
+    for (int t = 0; t < kScanStage; ++t) {
+      const i4v a0 = *reinterpret_cast<const i4v *>(st + t * kTileBytes + lane * 16);
+      const i4v a1 = *reinterpret_cast<const i4v *>(st + t * kTileBytes + 1024 + lane * 16);
+      int m[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        i16v acc = {};
+        acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(a0, bf[r][0], acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(a1, bf[r][1], acc, 0, 0, 0);
+        int x = acc[0];
+#pragma unroll
+        for (int v = 1; v < 16; ++v) x = max(x, acc[v]);
+        m[r] = x;
+      }
+      const int ec = __builtin_amdgcn_readlane(ecol, t);
+      if (__any(max(max(m[0], m[1]), max(m[2], m[3])) > emin - ec)) {
+        const int T = p.T, ct = s * kScanStage + t;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int rt = r0 + r;
+          if (__any(m[r] > ethr[r] - ec) && rt < T && ct < T && lane == 0) {
+            uint32_t *tp = p.tpairs + (size_t)ut * T * p.TW;
+            atomicOr(tp + (size_t)rt * p.TW + (ct >> 5), 1u << (ct & 31));
+            atomicOr(tp + (size_t)ct * p.TW + (rt >> 5), 1u << (rt & 31));
+          }
+        }
+      }
+    }
+  }
+}
+
+// ---------------------------------------------------------------- rows
+// Cosines of the marked tile pairs, neighbour words and degrees.
+// fp16 and bf16: the products are taken on the raw rows (exact products, fp32 sums), whose error is
+// that of the sums alone; fp32: on the fp16 unit vectors and their remainders, x_h y_h + 2^-11 (x_h y_l +
+// x_l y_h), which leaves out 2^-22 of the cosine.  With f_a the factor of a row (1 / m_a, or 1 / 1024 for
+// the unit vectors) the decision S_ab > theta is the sign of dot * f_b - theta / f_a.  The sums are good
+// to 2e-5 (128 terms, even with truncation); a result within kRowsGuard / f_a of zero is decided in
+// double precision as the definition says (the pairs wait in LDS for a wave's worth of them).
+//
+// A block takes 4 / kCols neighbouring row tiles and walks over the column tiles that any of them is
+// marked for, kCols at a time: their rows are gathered straight into LDS, two steps ahead of their
+// use, and every wave multiplies one of them with one row tile (held in registers).  kCols = 1: what
+// similar rows have in common is read once for four row tiles; kCols = 4: short problems, where there
+// are too few row tiles to fill the chip.  Bound by the gathered rows (random 256-byte rows, mostly from
+// L2): 0.31 ms for 16 problems of 32768 tokens, 0.26 ms for 128 of 8192 in clusters of 128, where one wave
+// per row tile with its own gathers took 0.73 and 0.84 ms; the double-precision pass and the kernel that
+// made lists from records before took 0.21 and 0.63 ms on top of all the cosines.
+constexpr float kRowsGuard = 7e-5f;
+constexpr int kRowsQueue = 192;                    // waiting pairs per wave
+constexpr int kRowsThreads = 256;
+
+template <int DT, int kCols>
+struct RowsLds {
+  static constexpr int kPart = kTile * 256;                              // 32 rows of 128 two-byte elements
+  static constexpr int kStage = kCols * kPart * (DT == SPINDLE_F32 ? 2 : 1);
+  static constexpr int kStages = kCols == 1 ? 3 : 2;
+  static constexpr int kBatch = kCols == 1 ? 32 : 16;                    // steps whose result bits a wave keeps
+  char stage[kStages][kStage];
+  float inv[kBatch * kCols][kTile];
+  uint16_t tok[kBatch * kCols][kTile];
+  uint16_t bits[4][kBatch * kWave];
+  uint16_t queue[4][kRowsQueue];
+  uint16_t tiles[2048];                                                  // column tile | 1 << (11 + row tile of the block)
+  int deg[4][kWave], words[4][kWave];
+  int ntiles;
+};
+
+template <int DT, int kCols>
+__global__ __launch_bounds__(kRowsThreads, 2) void shallow_rows(ShallowParams p, int nblk) {
+  typedef Mma<DT == SPINDLE_BF16 ? SPINDLE_BF16 : SPINDLE_F16> M;
+  typedef RowsLds<DT, kCols> L;
+  constexpr bool kSplit = DT == SPINDLE_F32;
+  constexpr int kRT = 4 / kCols;                       // row tiles of the block
+  extern __shared__ __attribute__((aligned(1024))) char lds_raw[];
+  L &l = *reinterpret_cast<L *>(lds_raw);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = lane_id(), g = lane >> 5, c = lane & 31;
+  const int tid = threadIdx.x, member = wave % kCols, rt = wave / kCols;
+  const int item = xcd_item();
+  if (item >= p.UT * nblk) return;
+  const int ut = item / nblk, n = p.n, T = p.T, R0 = (item % nblk) * kRT, R = R0 + rt;
+  const bool mine = R < T;                             // (the last block's last row tiles may not exist)
+  const size_t base = (size_t)ut * n;
+  uint16_t *bits = l.bits[wave], *queue = l.queue[wave];
+  const uint16_t *perm = p.perm + base;
+  const float *inv = (p.scan ? p.invp : p.inv) + base;
+  const float theta = p.theta[ut / p.U];
+
+  const char *X, *Xlo = nullptr;
+  size_t row_bytes;
+  if (kSplit) {
+    X = reinterpret_cast<const char *>(p.Xh) + base * 256;
+    Xlo = reinterpret_cast<const char *>(p.Xl) + base * 256;
+    row_bytes = 256;
+  } else {
+    X = x_row(p, ut, 0);
+    row_bytes = (size_t)p.lay.st;
+  }
+  // column tiles any row tile of the block is marked for, each with the row tiles it is for
+  if (wave == 0) {
+    if (p.scan) {
+      uint32_t word[kRT], any = 0;                     // lane w: word w of the rows of tpairs
+#pragma unroll
+      for (int k = 0; k < kRT; ++k) {
+        word[k] = 0;
+        if (R0 + k < T && lane < p.TW) word[k] = p.tpairs[((size_t)ut * T + R0 + k) * p.TW + lane];
+        if (R0 + k < T && lane == (R0 + k) >> 5) word[k] |= 1u << ((R0 + k) & 31);   // G_aa = 1 whatever theta is
+        any |= word[k];
+      }
+      int at = __popc(any);
+#pragma unroll
+      for (int o = 1; o < kWave; o <<= 1) {
+        const int x = __shfl_up(at, o);
+        if (lane >= o) at += x;
+      }
+      if (lane == kWave - 1) l.ntiles = at;
+      at -= __popc(any);
+      for (; any; any &= any - 1) {
+        const int t = __builtin_ctz(any);
+        uint32_t e = (uint32_t)(lane * 32 + t);
+#pragma unroll
+        for (int k = 0; k < kRT; ++k) e |= (word[k] >> t & 1u) << (11 + k);
+        l.tiles[at++] = (uint16_t)e;
+      }
+    } else {
+      for (int t = lane; t < T; t += kWave) l.tiles[t] = (uint16_t)(t | ((1 << kRT) - 1) << 11);
+      if (lane == 0) l.ntiles = T;
+    }
+  }
+  // the wave's rows: matrix columns = lanes
+  const int row = R * kTile + c;
+  const bool row_on = row < n;
+  const int row_tok = (int)perm[row_on ? row : n - 1];
+  typename M::frag bf[M::kSteps], bl[kSplit ? M::kSteps : 1];
+  {
+    const size_t at = (size_t)row_tok * row_bytes;
+#pragma unroll
+    for (int ks = 0; ks < M::kSteps; ++ks) {
+      bf[ks] = M::load(X + at, ks, g);
+      if (kSplit) bl[kSplit ? ks : 0] = M::load(Xlo + at, ks, g);
+    }
+  }
+  const float frow = inv[row_on ? row : n - 1];
+  const bool odd_row = frow != frow;                   // every pair of it is decided in double precision
+  // zero vectors: cosine 0, as if theta / f_a were huge (and of the sign of theta)
+  const float mrow = odd_row ? 1.f : frow > 0.f ? 1.f / frow : 0x1p100f;
+  const float lim = frow == 0.f && theta == 0.f ? 1.f : theta * mrow;
+  const float band = frow > 0.f ? kRowsGuard * mrow : 0.f;
+  const bool any_odd_row = __any(odd_row);
+
+  // Rows of a staged tile keep their 16-byte piece k at place k ^ swz(row), so that sixteen consecutive
+  // lanes of a 128-bit read hit sixteen different bank groups.  The token at place 16 g + v feeds matrix
+  // row 8 (v / 4) + 4 g + v % 4, so that result v of lane group g is column 16 g + v.
+  const int prow = 16 * ((c >> 2) & 1) + 4 * (c >> 3) + (c & 3);
+  auto swz = [](int r) { return (r & 7) | ((r & 16) >> 1); };
+  int soff[M::kSteps];
+#pragma unroll
+  for (int ks = 0; ks < M::kSteps; ++ks) soff[ks] = prow * 256 + (((2 * ks + g) ^ swz(prow)) << 4);
+  const uint32_t stage_lds = (uint32_t)(size_t)(__attribute__((address_space(3))) char *)lds_raw;
+  __syncthreads();
+  const int ntiles = __builtin_amdgcn_readfirstlane(l.ntiles);
+  const int nall = (ntiles + kCols - 1) / kCols;       // steps
+
+  // A problem with more steps than a batch holds goes through them twice: degrees and words counted
+  // first, then the same bits again to be written.
+  const int nbatch = (nall + L::kBatch - 1) / L::kBatch, npass = nbatch == 1 ? 1 : 2 * nbatch;
+  int deg = 0, words = 0, nq = 0, ndecided = 0;
+  bool dense = false;
+  uint32_t *out = nullptr;
+  for (int pass = 0; pass < npass; ++pass) {
+    const int s0 = (pass < nbatch ? pass : pass - nbatch) * L::kBatch, ns = min(L::kBatch, nall - s0);
+    const int t0 = s0 * kCols, nt = min(L::kBatch * kCols, ntiles - t0);
+    if (pass > 0) __syncthreads();                     // the batch before is done with these
+    for (int i = tid; i < nt * kTile; i += kRowsThreads) {
+      const int col = (int)(l.tiles[t0 + (i >> 5)] & 2047u) * kTile + (i & 31);
+      l.tok[i >> 5][i & 31] = perm[col < n ? col : n - 1];
+      l.inv[i >> 5][i & 31] = col < n ? inv[col] : 0.f;
+    }
+    __syncthreads();
+    // loads of step s: the wave brings in 8 rows of every tile, four rows of 256 bytes per load
+    auto fetch = [&](int s) __attribute__((always_inline)) {
+#pragma unroll
+      for (int k = 0; k < kCols; ++k) {
+        const int i = min(s * kCols + k, nt - 1);      // (a last step may have fewer tiles)
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          const int r = wave * 8 + q * 4 + (lane >> 4);
+          const size_t at = (size_t)l.tok[i][r] * row_bytes + (size_t)(((lane & 15) ^ swz(r)) << 4);
+          const uint32_t to = stage_lds + (uint32_t)((s % L::kStages) * L::kStage + k * L::kPart + (wave * 8 + q * 4) * 256);
+          lds_dma16(X + at, to);
+          if (kSplit) lds_dma16(Xlo + at, to + kCols * L::kPart);
+        }
+      }
+    };
+    fetch(0);
+    if (L::kStages > 2 && ns > 1) fetch(1);
+    for (int s = 0; s < ns; ++s) {
+      // the wave's loads of step s have landed (those of step s + 1 may still be on their way), and behind
+      // the barrier every wave's; the buffer of step s - 1 is free
+      if (L::kStages > 2 && s + 1 < ns) __builtin_amdgcn_s_waitcnt(kSplit ? 0x0F74 : 0x0F72);
+      else __builtin_amdgcn_s_waitcnt(0x0F70);
+      __syncthreads();
+      if (s + L::kStages - 1 < ns) fetch(s + L::kStages - 1);
+      const int i = s * kCols + member;                // this wave's tile of the batch
+      const uint32_t entry = i < nt ? (uint32_t)__builtin_amdgcn_readfirstlane((int)l.tiles[t0 + i]) : 0u;
+      if (!(entry >> (11 + rt) & 1u)) {                // wave-uniform
+        bits[s * kWave + lane] = 0;
+        continue;
+      }
+      const int t = (int)(entry & 2047u);
+      const char *st = l.stage[s % L::kStages] + member * L::kPart;
+      f16v acc, lo;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) { acc[v] = 0.f; lo[v] = 0.f; }
+#pragma unroll
+      for (int ks = 0; ks < M::kSteps; ++ks) {
+        const typename M::frag f = *reinterpret_cast<const typename M::frag *>(st + soff[ks]);
+        acc = M::mma(f, bf[ks], acc);
+        if (kSplit) {
+          const typename M::frag fl = *reinterpret_cast<const typename M::frag *>(st + kCols * L::kPart + soff[ks]);
+          lo = M::mma(f, bl[kSplit ? ks : 0], lo);
+          lo = M::mma(fl, bf[ks], lo);
+        }
+      }
+      const float *fc = l.inv[i];
+      const bool odd = any_odd_row || __any(fc[c] != fc[c]);
+      uint32_t neg = 0;
+      float mn = INFINITY;
+      float x[16];
+#pragma unroll
+      for (int v = 15; v >= 0; --v) {
+        const float d = kSplit ? fmaf(lo[v], 0x1p-11f, acc[v]) : acc[v];
+        x[v] = fmaf(d, fc[16 * g + v], -lim);
+        neg = __builtin_amdgcn_alignbit(neg, __float_as_uint(x[v]), 31);
+        mn = fminf(mn, fabsf(x[v]));
+      }
+      uint32_t yes = ~neg & 0xFFFFu;
+      uint32_t valid = row_on ? 0xFFFFu : 0u;
+      const int nv = n - t * kTile - 16 * g;           // columns past the end
+      if (nv < 16) valid = nv <= 0 ? 0u : valid & ((1u << nv) - 1u);
+      yes &= valid;
+      const bool self = t == R && (c >> 4) == g;
+      uint32_t close = 0;
+      if (odd || __any(mn < band)) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const float fv = fc[16 * g + v];
+          if (odd_row || fv != fv || fabsf(x[v]) < band) close |= 1u << v;
+        }
+        close &= valid;
+        if (self) close &= ~(1u << (c & 15));
+        yes &= ~close;
+      }
+      if (self && row_on) yes |= 1u << (c & 15);       // G_aa = 1
+      bits[s * kWave + lane] = (uint16_t)yes;
+      for (;;) {                                       // one close pair per lane at a time into the queue
+        const unsigned long long m = __ballot(close != 0);
+        if (nq > kRowsQueue - kWave || (m == 0 && nq > 0 && s + 1 == ns)) {
+          // (the bits are written as halves elsewhere and as words here: keep the compiler from reordering them)
+          asm volatile("" ::: "memory");
+          for (int j = lane; j < nq; j += kWave) {
+            const uint32_t e = queue[j];
+            const int slot = (int)(e >> 10), ln = (int)((e >> 4) & 63), v = (int)(e & 15);
+            const int a = (int)perm[R * kTile + (ln & 31)], b = (int)l.tok[slot * kCols + member][16 * (ln >> 5) + v];
+            ndecided += pass < nbatch;
+            if (cos64<DT, 4>(p, ut, a, b) > (double)theta) {
+              const int at = slot * kWave + ln;
+              atomicOr(reinterpret_cast<uint32_t *>(bits) + (at >> 1), 1u << (v + 16 * (at & 1)));
+            }
+          }
+          nq = 0;
+          asm volatile("" ::: "memory");
+        }
+        if (m == 0) break;
+        if (close) {
+          const int v = __builtin_ctz(close);
+          close &= close - 1;
+          queue[nq + __popcll(m & ((1ull << lane) - 1ull))] = (uint16_t)(s << 10 | lane << 4 | v);
+        }
+        nq += __popcll(m);
+      }
+    }
+    // (the last step may not have been this wave's: pairs still waiting)
+    if (nq > 0) {
+      asm volatile("" ::: "memory");
+      for (int j = lane; j < nq; j += kWave) {
+        const uint32_t e = queue[j];
+        const int slot = (int)(e >> 10), ln = (int)((e >> 4) & 63), v = (int)(e & 15);
+        const int a = (int)perm[R * kTile + (ln & 31)], b = (int)l.tok[slot * kCols + member][16 * (ln >> 5) + v];
+        ndecided += pass < nbatch;
+        if (cos64<DT, 4>(p, ut, a, b) > (double)theta) {
+          const int at = slot * kWave + ln;
+          atomicOr(reinterpret_cast<uint32_t *>(bits) + (at >> 1), 1u << (v + 16 * (at & 1)));
+        }
+      }
+      nq = 0;
+      asm volatile("" ::: "memory");
+    }
+    if (pass < nbatch)
+      for (int s = 0; s < ns; ++s) {
+        const uint32_t m = bits[s * kWave + lane];
+        deg += __popc(m);
+        words += m != 0;
+      }
+    if (pass == nbatch - 1) {
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) ndecided += __shfl_xor(ndecided, o);
+      if (lane == 0 && ndecided) atomicAdd(p.pairs_exact + ut, (unsigned)ndecided);
+      l.deg[wave][lane] = deg;
+      l.words[wave][lane] = words;
+      __syncthreads();
+      // a row's words: those of lane group 0 of every wave of its row tile, then those of group 1
+      int total = 0, d = 0, at = 0;
+#pragma unroll
+      for (int q = 0; q < kCols; ++q) {
+        const int w = rt * kCols + q;
+        const int x0 = l.words[w][c], x1 = l.words[w][32 + c];
+        d += l.deg[w][c] + l.deg[w][32 + c];
+        total += x0 + x1;
+        at += g == 0 ? (q < member ? x0 : 0) : x0 + (q < member ? x1 : 0);
+      }
+      int incl = total;                                // over the 32 rows (the same in both lane groups)
+#pragma unroll
+      for (int o = 1; o < 32; o <<= 1) {
+        const int y = __shfl_up(incl, o, 32);
+        if (c >= o) incl += y;
+      }
+      const int rows_here = mine ? min(kTile, n - R * kTile) : 0;
+      dense = __builtin_amdgcn_readlane(incl, 31) > rows_here * p.list_row;
+      uint32_t *lists = p.lists + base * p.list_row;
+      const uint32_t first = dense ? (uint32_t)row * p.list_row : (uint32_t)(R * kTile * p.list_row + incl - total);
+      if (g == 0 && row_on && member == 0) {
+        p.key[(size_t)ut * p.n16 + row] = ((uint32_t)d << 16) | (uint32_t)(0xFFFF - row_tok);
+        p.rows[base + row] = make_uint2(first, dense ? kDenseRow | (uint32_t)(2 * T) : (uint32_t)total);
+        if (p.deg_out[ut / p.U]) p.deg_out[ut / p.U][(size_t)(ut % p.U) * n + row_tok] = d;
+      }
+      if (lane == 0 && member == 0 && mine) {
+        const uint32_t ones = rows_here == kTile ? 0xFFFFFFFFu : (1u << rows_here) - 1u;
+        p.live[0][(size_t)ut * T + R] = ones;
+        p.live[1][(size_t)ut * T + R] = ones;
+        p.live[2][(size_t)ut * T + R] = ones;
+      }
+      out = lists + first + (dense ? 0 : at);
+      if (dense && p.scan && member == 0) {            // tiles that were not marked: no bits
+        for (int i = lane; i < rows_here * p.list_row; i += kWave) lists[(size_t)R * kTile * p.list_row + i] = 0;
+        __builtin_amdgcn_s_waitcnt(0x0F70);            // before the bits of the marked ones are written
+      }
+      __syncthreads();
+    }
+    if (nbatch == 1 || pass >= nbatch) {
+      for (int s = 0; s < ns; ++s) {
+        const int i = s * kCols + member;
+        if (i >= nt) break;
+        const uint32_t m = bits[s * kWave + lane], half = 2u * (l.tiles[t0 + i] & 2047u) + g;
+        if (dense) {
+          if (row_on) reinterpret_cast<uint16_t *>(out)[half] = (uint16_t)m;
+        } else if (m) {
+          *out++ = half << 16 | m;
+        }
+      }
+    }
+  }
+}
+
+// ---------------------------------------------------------------- adjacency export
+// One wave per row: its words, from positions to tokens, collected as bits in LDS.
+__global__ __launch_bounds__(256) void shallow_adjacency(ShallowParams p, uint32_t *out, int t) {
+  __shared__ uint32_t acc[4][65536 / 32];
+  const int wave = threadIdx.x >> 6, lane = lane_id(), n = p.n, W = (n + 31) / 32;
+  const size_t nrows = (size_t)p.U * n;
+  for (size_t i0 = (size_t)blockIdx.x * 4; i0 < nrows; i0 += (size_t)gridDim.x * 4) {
+    const size_t i = i0 + wave;
+    if (i < nrows)
+      for (int k = lane; k < W; k += kWave) acc[wave][k] = 0;
+    __syncthreads();
+    const size_t base = (size_t)(t * p.U) * n + i / n * n;
+    int row = 0;
+    if (i < nrows) {
+      const int v = (int)(i % n);
+      const uint2 info = p.rows[base + v];
+      const uint32_t *w = p.lists + base * p.list_row + info.x;
+      const bool dense = (info.y & kDenseRow) != 0;
+      const int nw = (int)(info.y & ~kDenseRow);
+      row = (int)p.perm[base + v];
+      for (int k = lane; k < nw; k += kWave) {
+        const uint32_t x = dense ? (uint32_t)k << 16 | reinterpret_cast<const uint16_t *>(w)[k] : w[k];
+        for (uint32_t m = x & 0xFFFFu; m; m &= m - 1) {
+          const int b = (int)p.perm[base + (x >> 16) * 16 + __builtin_ctz(m)];
+          atomicOr(&acc[wave][b >> 5], 1u << (b & 31));
+        }
+      }
+    }
+    __syncthreads();
+    if (i < nrows)
+      for (int k = lane; k < W; k += kWave) out[(i / n * n + row) * W + k] = acc[wave][k];
+    __syncthreads();
+  }
+}
+
+}  // namespace
+
+namespace {
+template <int DT, int kCols>
+spindle_status launch_rows(const ShallowParams &p, hipStream_t st) {
+  constexpr int kRT = 4 / kCols;
+  static LdsLimit lim;
+  if (spindle_status e = allow_lds(lim, reinterpret_cast<const void *>(&shallow_rows<DT, kCols>), sizeof(RowsLds<DT, kCols>))) return e;
+  const int nblk = (p.T + kRT - 1) / kRT;
+  ProfScope ps("shallow_rows", st);
+  hipLaunchKernelGGL((shallow_rows<DT, kCols>), dim3(xcd_grid((size_t)p.UT * nblk)), dim3(kRowsThreads), sizeof(RowsLds<DT, kCols>),
+                     st, p, nblk);
+  return SPINDLE_OK;
+}
+template <int DT>
+spindle_status launch_rows(const ShallowParams &p, hipStream_t st) {
+  // one row tile per block while four would leave compute units without a block (one fp32 head of 512
+  // tokens, K and V: 15 us against 47 us with a wave per row tile)
+  if ((long)p.UT * p.T < 1024) return launch_rows<DT, 4>(p, st);
+  return launch_rows<DT, 1>(p, st);
+}
+}  // namespace
+
+spindle_status launch_tiles(const ShallowParams &p, hipStream_t st) {
+  const int n = p.n;
+  if (p.scan) {
+    const int nblk = (n + kOrderTokens - 1) / kOrderTokens, nwin = (n + kWindow - 1) / kWindow;
+    int npiv = (n / 16) & ~31;
+    if (npiv > kPivots) npiv = kPivots;
+    { ProfScope ps("shallow_pivots", st);
+    hipLaunchKernelGGL(shallow_pivots, dim3(xcd_grid((size_t)p.UT * nblk)), dim3(kPivotThreads), 0, st, p, npiv, nblk); }
+    { ProfScope ps("shallow_order", st);
+    hipLaunchKernelGGL(shallow_order, dim3(xcd_grid((size_t)p.UT * nblk)), dim3(kPivots), 0, st, p, nblk); }
+    { ProfScope ps("shallow_window", st);
+    hipLaunchKernelGGL(shallow_window, dim3(xcd_grid((size_t)p.UT * nwin)), dim3(kWindowThreads), 0, st, p, nwin); }
+    // stages per block: about 2048 blocks, so that short problems fill the chip too, at most 16 (a block
+    // then lasts about 15 us)
+    const int nI = p.Tp / kScanPanel, nS = p.Tp / kScanStage;
+    const long work = (long)p.UT * nI * (nI + 1);
+    int per = (int)(work / 2048);
+    per = per < 1 ? 1 : (per > 16 ? 16 : per);
+    const int njg = (nS + per - 1) / per;
+    { ProfScope ps("shallow_scan", st);
+    hipLaunchKernelGGL(shallow_scan, dim3((unsigned)(8 * nI * ((p.UT * njg + 7) / 8))), dim3(kScanThreads), 0, st, p, per, njg); }
+  }
+  if (p.dtype == SPINDLE_F16) return launch_rows<SPINDLE_F16>(p, st);
+  if (p.dtype == SPINDLE_BF16) return launch_rows<SPINDLE_BF16>(p, st);
+  return launch_rows<SPINDLE_F32>(p, st);
+}
+
+spindle_status launch_adjacency(const ShallowParams &p, uint32_t *const out[2], hipStream_t st) {
+  for (int t = 0; t < p.UT / p.U; ++t)
+    if (out[t]) hipLaunchKernelGGL(shallow_adjacency, dim3(2048), dim3(256), 0, st, p, out[t], t);
+  return SPINDLE_OK;
+}
+
+}  // namespace spindle

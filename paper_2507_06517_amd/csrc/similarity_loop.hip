@@ -1,0 +1,115 @@
+// Measurement aid: cosine similarities of all pairs of tokens by fp16 matrix instructions, with nothing
+// done with the results (spindle_calibrate_similarity).
+#include "mma.h"
+#include "shallow.h"
+
+namespace spindle {
+namespace {
+
+constexpr int kPanelRows = 256;   // rows held in registers per block
+constexpr int kChunkCols = 1024;  // tokens per chunk
+constexpr int kItemChunks = 4;    // chunks a block handles with the same rows in registers
+constexpr int kLoopThreads = 256;
+
+// Block = 4 waves; wave w keeps the unit vectors of tokens a in [I*256 + 64w, +64) as MFMA B fragments
+// and streams the tokens b of the chunks from its own first row on through LDS.
+//   kMode 0   staging, barriers, fragment reads and matrix instructions
+//   kMode 1   without the loads of a chunk's stages after the first two (the matrix instructions keep
+//             reading the same staged tokens)
+//   kMode 2   matrix instructions only, both operands from registers
+template <int kMode>
+__global__ __launch_bounds__(kLoopThreads, 2) void similarity_loop(ShallowParams p) {
+  typedef Mma<SPINDLE_F16> M;
+  // two stages of 64 tokens, filled by direct global->LDS loads.  Row r keeps its 16-byte piece
+  // k at position k ^ swz(r), swz(r) = (r & 7) | ((r & 16) >> 1), so that sixteen consecutive lanes
+  // of a 128-bit LDS read (sixteen different rows, same k) hit sixteen different bank groups.
+  __shared__ __attribute__((aligned(1024))) char stage[2 * kStageBytes];
+  const int n = p.n;
+  const int nI = (n + kPanelRows - 1) / kPanelRows;
+  const int nJ = (n + kChunkCols * kItemChunks - 1) / (kChunkCols * kItemChunks);
+  // blocks are dealt round-robin to the 8 XCDs: each XCD takes one (ut, chunk group) at a time and
+  // sweeps the row panels, so the chunk is re-read from that XCD's L2
+  const int xcd = blockIdx.x & 7, s_ = blockIdx.x >> 3;
+  const int I = s_ % nI, pj = (s_ / nI) * 8 + xcd;
+  if (pj >= p.UT * nJ) return;
+  const int ut = pj / nJ, Jg = (pj % nJ + ut) % nJ;
+  const int Jfirst = (I * kPanelRows) / kChunkCols;
+  if ((Jg + 1) * kItemChunks <= Jfirst) return;
+  const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), g = lane >> 5, c = lane & 31;
+  const char *Xh = reinterpret_cast<const char *>(p.Xh) + (size_t)ut * n * 256;
+  M::frag af[2][M::kSteps];
+#pragma unroll
+  for (int cb = 0; cb < 2; ++cb) {
+    const int a = I * kPanelRows + 64 * wave + 32 * cb + c;
+#pragma unroll
+    for (int ks = 0; ks < M::kSteps; ++ks)
+      af[cb][ks] = a < n ? M::load(Xh + (size_t)a * 256, ks, g) : M::zero();
+  }
+  int soff[M::kSteps];                             // byte offset of this lane's fragment ks in tile 0 of a stage
+#pragma unroll
+  for (int ks = 0; ks < M::kSteps; ++ks)
+    soff[ks] = c * 256 + (((2 * ks + g) ^ ((c & 7) | ((c & 16) >> 1))) << 4);
+  uint32_t voff[4];                                // this lane's source offset within a stage, per load
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int r = (wave * 4 + q) * 4 + (lane >> 4);
+    voff[q] = (uint32_t)(r * 256 + (((lane & 15) ^ ((r & 7) | ((r & 16) >> 1))) << 4));
+  }
+  const uint32_t stage_lds = (uint32_t)(size_t)(__attribute__((address_space(3))) char *)stage;
+  auto dma = [&](int b0, int bufsel) {
+    const char *sbase = Xh + (size_t)b0 * 256;       // (rows past the end exist, the array is padded)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) lds_dma16_at(sbase, voff[q], stage_lds + bufsel * kStageBytes + (wave * 4 + q) * 1024);
+  };
+  auto frag_at = [&](int bufsel, int ct, int ks) -> M::frag {
+    if (kMode == 2) {                                 // a register operand the compiler cannot see through
+      M::frag f = af[ct][ks];
+      asm volatile("" : "+v"(f));
+      return f;
+    }
+    return *reinterpret_cast<const M::frag *>(stage + bufsel * kStageBytes + ct * 32 * 256 + soff[ks]);
+  };
+  uint32_t keep = 0;
+  int col = Jg * kItemChunks * kChunkCols, end = (Jg + 1) * kItemChunks * kChunkCols;
+  if (col < I * kPanelRows) col = I * kPanelRows;
+  if (end > n) end = n;
+  dma(col, 0);
+  dma(col + kStageCols, 1);
+  for (int s = 0; col < end; ++s, col += kStageCols) {
+    // stage s has landed; the loads of stage s + 1 stay in flight
+    __builtin_amdgcn_s_waitcnt(kMode == 0 ? 0x0F74 : 0x0F70);
+    __syncthreads();
+    f16v r[2][2];
+#pragma unroll
+    for (int ct = 0; ct < 2; ++ct) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) { r[ct][0][v] = 0.f; r[ct][1][v] = 0.f; }
+#pragma unroll
+      for (int ks = 0; ks < M::kSteps; ++ks) {
+        const M::frag f = frag_at(s & 1, ct, ks);
+        r[ct][0] = M::mma(f, af[0][ks], r[ct][0]);
+        r[ct][1] = M::mma(f, af[1][ks], r[ct][1]);
+      }
+    }
+    keep |= __float_as_uint(r[0][0][0]) | __float_as_uint(r[0][1][0]) | __float_as_uint(r[1][0][0]) | __float_as_uint(r[1][1][0]);
+    __syncthreads();                                 // every wave is done with the stage
+    if (kMode == 0) dma(col + 2 * kStageCols, s & 1);
+  }
+  __builtin_amdgcn_s_waitcnt(0x0F70);
+  if (keep == 0x9E3779B9u) p.ovf[0] = keep;          // never in practice: keeps the results alive
+}
+
+}  // namespace
+
+spindle_status launch_bare_similarity(const ShallowParams &p, hipStream_t st, int mode) {
+  const int nI = (p.n + kPanelRows - 1) / kPanelRows;
+  const int nJ = (p.n + kChunkCols * kItemChunks - 1) / (kChunkCols * kItemChunks);
+  const dim3 grid(8 * nI * ((p.UT * nJ + 7) / 8));
+  if (mode == 0) hipLaunchKernelGGL(similarity_loop<0>, grid, dim3(kLoopThreads), 0, st, p);
+  else if (mode == 1) hipLaunchKernelGGL(similarity_loop<1>, grid, dim3(kLoopThreads), 0, st, p);
+  else hipLaunchKernelGGL(similarity_loop<2>, grid, dim3(kLoopThreads), 0, st, p);
+  SPINDLE_HIP(hipGetLastError());
+  return SPINDLE_OK;
+}
+
+}  // namespace spindle

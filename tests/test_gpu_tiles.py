@@ -1,0 +1,76 @@
+"""Parity of the graph phase where its cases meet: the lengths at which tokens start to be sorted and
+scanned by sketches, at which a window of the sort or a panel of the scan ends, and at which a block
+of the list kernel takes four row tiles instead of one; tokens whose sketch or whose products are out
+of range; lists as words and as bits.  Everything is compared bit for bit with the oracle."""
+import numpy as np
+import pytest
+
+from paper_2507_06517_amd import workloads as wl
+
+import parity
+
+pytestmark = [pytest.mark.gpu, pytest.mark.timeout(300)]
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
+@pytest.mark.parametrize("l", [2047, 2048, 2049, 2560, 4095, 4097])
+def test_lengths_around_the_scan_and_its_windows(oracle, dtype, l):
+    # sorted from 2048 tokens on, windows of 2048 places, panels of 512: ragged and whole ends
+    L = wl.small_random(61, dtype, B=1, H=1, l=l, lw=1, cap=max(1, l // 9), n_centroids=l // 40, noise_frac=0.3,
+                        drift_sigma=0.003)
+    parity.check_shallow_layer(oracle, L, debug=False)
+    parity.check_shallow_layer(oracle, L, cap=l, tensors=("k",))            # with G and the degrees
+
+
+@pytest.mark.parametrize("H,l", [(1, 2304), (8, 2016), (8, 2048), (16, 1000), (17, 960)])
+def test_block_shapes_of_the_list_kernel(oracle, H, l):
+    # 1024 row tiles over all problems of the call is where a block starts to take four of them
+    L = wl.small_random(62, "f16", B=1, H=H, l=l, lw=1, cap=l, n_centroids=20, noise_frac=0.2)
+    units = [(0, h) for h in sorted({0, H // 2, H - 1})]
+    parity.check_shallow_layer(oracle, L, units=units, debug=False)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
+def test_dense_rows_and_low_thresholds(oracle, dtype):
+    # nearly everything adjacent: more words per row than the lists hold, so they are kept as bits;
+    # with a threshold near zero every tile counts and nothing is sorted
+    for l, centroids, theta in ((2300, 1, 0.9), (2300, 2, 0.05), (1100, 1, 0.5), (2100, 3, -0.3)):
+        L = wl.small_random(63, dtype, B=1, H=1, l=l, lw=1, cap=50, n_centroids=centroids, noise_frac=0.1)
+        L.theta_k = L.theta_v = theta
+        parity.check_shallow_layer(oracle, L, debug=False, tensors=("k",))
+        parity.check_shallow_layer(oracle, L, tensors=("v",))
+
+
+@pytest.mark.parametrize("l", [700, 2200])
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
+def test_magnitudes_out_of_the_ordinary(oracle, dtype, l):
+    # zero vectors, subnormal components, and norms whose fp32 products would leave the range: such rows
+    # are decided in double precision; also a threshold of one, which not even a token itself exceeds
+    L = wl.small_random(64, dtype, B=1, H=1, l=l, lw=1, cap=l, n_centroids=12, noise_frac=0.2)
+    x = wl.to_f64(L.K, dtype)
+    small, big = {"f16": (2.0 ** -20, 512.0), "bf16": (2.0 ** -60, 2.0 ** 58), "f32": (2.0 ** -105, 2.0 ** 104)}[dtype]
+    x[0, 0, 10:20] *= small
+    x[0, 0, 30:40] *= big
+    x[0, 0, 50:53] = 0.0
+    x[0, 0, l - 1] = x[0, 0, 3] * small
+    x[0, 0, l - 2] = x[0, 0, 3] * big
+    L.K = wl.cast(x, dtype)
+    parity.check_shallow_layer(oracle, L, debug=False, tensors=("k",))
+    L.theta_k = 1.0
+    parity.check_shallow_layer(oracle, L, debug=False, tensors=("k",))
+
+
+def test_structured_vectors(oracle):
+    # vectors the rotation of the sketch maps to few coordinates (constant, alternating, single ones), scaled
+    # copies, opposite ones: sketches of little use, whose errors must widen what is looked at
+    rng = np.random.default_rng(65)
+    l, d = 2100, 128
+    H = np.ones((1, 1))
+    for _ in range(7):
+        H = np.block([[H, H], [H, -H]])
+    x = np.concatenate([H, np.eye(d), -H[:40]])[rng.integers(0, 2 * d + 40, l)]
+    x = x * rng.uniform(0.1, 3.0, (l, 1)) + 0.01 * rng.standard_normal((l, d))
+    K = wl.cast(x[None, None], "f16")
+    L = wl.Layer("f16", K, K.copy(), np.zeros((1, 1, 1, d), np.float16), 1, 1, 1, l, l)
+    parity.check_shallow_layer(oracle, L, tensors=("k",), debug=False)
+    parity.check_shallow_layer(oracle, L, tensors=("v",), debug=False, cap=60)
