@@ -120,6 +120,11 @@ struct ShallowParams {
   int32_t *deg_out[2];     // optional initial degrees
 };
 
+// Blocks are dealt round-robin to the 8 XCDs; this numbering gives each XCD a run of consecutive
+// items (a problem's blocks share its L2).  The launch has a multiple of 8 blocks.
+__device__ __forceinline__ int xcd_item() { return (int)(blockIdx.x & 7) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3); }
+inline unsigned xcd_grid(size_t items) { return (unsigned)align_up(items, 8); }
+
 __device__ __forceinline__ const char *x_row(const ShallowParams &p, int ut, int a) {
   const int t = ut / p.U, u = ut % p.U;
   return p.X[t] + kv_unit_offset(p.lay, u) + (size_t)a * (size_t)p.lay.st;

@@ -5,159 +5,272 @@
 namespace spindle {
 namespace {
 
-// One codebook vector: the unit vector of a picked token, in the input type.
-template <int DT>
-__device__ __forceinline__ void emit_code(const ShallowParams &p, int ut, int vert, int r) {
-  typedef typename Elem<DT>::type T;
-  const int t = ut / p.U, u = ut % p.U;
-  const T *src = reinterpret_cast<const T *>(x_row(p, ut, vert));
-  T *dst = reinterpret_cast<T *>(p.C[t]) + ((size_t)u * p.cap + r) * kHeadDim;
-  const double m = p.m64[(size_t)ut * p.n + vert];
-  for (int d = lane_id(); d < kHeadDim; d += kWave) {
-    const double x = (double)Elem<DT>::to_float(src[d]);
-    dst[d] = Elem<DT>::from_float(m > 0.0 ? (float)(x / m) : 0.f);
-  }
-}
-
-// Codebook order: the picks of a problem sorted by decreasing key at pick time (keys are
-// distinct: they carry the token index).  One workgroup per problem: the picked positions are listed
-// from their bits, then a least-significant-digit radix sort, four stable passes of 8 bits over
-// (key, position) pairs that ping-pong between two pairs of arrays left free by the merge.  A pass
-// counts the digits, then walks the items in order, 1024 at a time: lanes with the same digit find
-// each other with eight ballots, waves exchange their digit counts through LDS.
+// Codebook order: the picks of a problem sorted by decreasing key at pick time, i.e. by decreasing
+// degree and among equal degrees by increasing token.  One workgroup per problem lists the picks in token
+// order as degree << 16 | position, then a least-significant-digit radix sort of the degrees: at most two
+// stable passes of 8 bits that ping-pong between two arrays left free by the merge; a pass whose digit all
+// picks share is left out (degrees below 256: one pass).  In a pass every wave owns a run of the items:
+// it counts their digits, and after one sum over waves and digits places them, 64 at a time, lanes with the
+// same digit finding each other with eight ballots.
+// Bound by latency, one workgroup per problem: 2 problems of 32768 rows 50 -> 43 us, one layer of 16 x 32768
+// beside two others 128 -> 88 us, 64 x 32768 with half of the tokens isolated 275 -> 219 us, one of 512
+// tokens 19 -> 12 us against four passes over (key, position) pairs, 1024 items and five barriers at a time.
 constexpr int kRankThreads = 1024;
 
+__device__ __forceinline__ unsigned long long same_digit(int d, bool on) {
+  unsigned long long peers = __ballot(on);
+#pragma unroll
+  for (int bit = 0; bit < 8; ++bit) {
+    const unsigned long long m = __ballot((d >> bit) & 1);
+    peers &= ((d >> bit) & 1) ? m : ~m;
+  }
+  return peers;
+}
+
 __global__ __launch_bounds__(kRankThreads) void shallow_rank(ShallowParams p) {
-  constexpr int kWaves = kRankThreads / 64;
-  __shared__ int base_of[256];                       // next output position of each digit
-  __shared__ int wave_cnt[kWaves][256];              // items of each digit per wave in the current tile
-  __shared__ int scan_tmp[256];
-  const int ut = blockIdx.x, tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
-  const size_t base = (size_t)ut * p.n;
+  constexpr int kWaves = kRankThreads / 64, kAtOnce = 4;
+  __shared__ uint32_t picked[2048];                  // bit per position (n <= 65535)
+  __shared__ int before[1024];                       // picked tokens in front of 64 consecutive ones
+  __shared__ int place[kWaves][256];                 // next output position of a digit of a wave's items
+  __shared__ int wsum[kWaves];
+  __shared__ int sh_alike;
+  const int ut = blockIdx.x, tid = threadIdx.x, lane = lane_id(), wave = tid >> 6, n = p.n;
+  const size_t base = (size_t)ut * n;
   int *cnt = p.counters + (size_t)ut * kCounters;
   if (cnt[C_DONE] == 0) return;                      // construction did not finish: n_codes stays -1
-  uint32_t *keyA = p.m1 + (size_t)ut * p.n16, *keyB = p.key + (size_t)ut * p.n16;
-  uint32_t *valA = reinterpret_cast<uint32_t *>(p.cand + base), *valB = reinterpret_cast<uint32_t *>(p.dying + base);
+  for (int i = tid; i < p.T; i += kRankThreads) picked[i] = p.picked[(size_t)ut * p.T + i];
+  before[tid] = 0;
+  __syncthreads();
+  // thread t takes tokens t, t + 1024, ..., eight loads in flight (loops kept short: with all trips unrolled the
+  // instruction fetches of a cold kernel cost more than the loads)
+  constexpr int kLoads = 8;
+  auto is_picked = [&](int tok, int v) { return tok < n && (picked[v >> 5] >> (v & 31) & 1u); };
+#pragma unroll 1
+  for (int t0 = tid; t0 - tid < n; t0 += kLoads * kRankThreads) {
+    int v[kLoads];
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i) v[i] = t0 + i * kRankThreads < n ? (int)p.iperm[base + t0 + i * kRankThreads] : 0;
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i) {
+      const unsigned long long mk = __ballot(is_picked(t0 + i * kRankThreads, v[i]));
+      if (lane == 0) before[min(1023, (t0 + i * kRankThreads) >> 6)] = __popcll(mk);
+    }
+  }
+  __syncthreads();
   int P = 0;
-  for (int w0 = 0; w0 < p.T; w0 += kRankThreads) {
-    const int i = w0 + tid;
-    uint32_t bits = i < p.T ? p.picked[(size_t)ut * p.T + i] : 0u;
-    int incl = __popc(bits);
-    const int mine = incl;
+  {
+    const int own = before[tid];
+    int incl = own;
 #pragma unroll
     for (int o = 1; o < kWave; o <<= 1) {
       const int x = __shfl_up(incl, o);
       if (lane >= o) incl += x;
     }
-    if (lane == kWave - 1) scan_tmp[wave] = incl;
+    if (lane == kWave - 1) wsum[wave] = incl;
     __syncthreads();
-    int at = P + incl - mine;
     for (int q = 0; q < kWaves; ++q) {
-      if (q < wave) at += scan_tmp[q];
-      P += scan_tmp[q];
+      if (q < wave) incl += wsum[q];
+      P += wsum[q];
     }
-    for (; bits; bits &= bits - 1, ++at) {
-      const int v = i * 32 + __builtin_ctz(bits);
-      valA[at] = (uint32_t)v;
-      keyA[at] = p.pick_key[base + v];
-    }
-    __syncthreads();
+    before[tid] = incl - own;
   }
   if (tid == 0) {
     cnt[C_PICKS] = P;
     p.n_codes[ut / p.U][ut % p.U] = P < p.cap ? P : p.cap;
     if (p.n_found[ut / p.U]) p.n_found[ut / p.U][ut % p.U] = P;
   }
-  for (int pass = 0; pass < 4; ++pass) {
-    const int shift = 8 * pass;
-    const uint32_t *kin = pass & 1 ? keyB : keyA, *vin = pass & 1 ? valB : valA;
-    uint32_t *kout = pass & 1 ? keyA : keyB, *vout = pass & 1 ? valA : valB;
-    // digit 255 - byte: larger keys first
-    if (tid < 256) base_of[tid] = 0;
-    __syncthreads();
-    for (int s = tid; s < P; s += kRankThreads) atomicAdd(&base_of[255 - ((kin[s] >> shift) & 255u)], 1);
-    __syncthreads();
-    // exclusive prefix sum over the 256 counters
-    if (tid < 256) scan_tmp[tid] = base_of[tid];
-    __syncthreads();
-    for (int o = 1; o < 256; o <<= 1) {
-      int x = 0;
-      if (tid < 256 && tid >= o) x = scan_tmp[tid - o];
-      __syncthreads();
-      if (tid < 256) scan_tmp[tid] += x;
-      __syncthreads();
-    }
-    if (tid < 256) base_of[tid] = scan_tmp[tid] - base_of[tid];
-    __syncthreads();
-    for (int s0 = 0; s0 < P; s0 += kRankThreads) {
-      const int s = s0 + tid;
-      const bool on = s < P;
-      const uint32_t k = on ? kin[s] : 0u, v = on ? vin[s] : 0u;
-      const int d = on ? 255 - (int)((k >> shift) & 255u) : 256;      // 256: no item
-      for (int j = tid; j < kWaves * 256; j += kRankThreads) (&wave_cnt[0][0])[j] = 0;
-      // lanes of the wave with the same digit
-      unsigned long long peers = __ballot(on);
+  __syncthreads();
+  uint32_t *src = p.m1 + (size_t)ut * p.n16, *dst = p.key + (size_t)ut * p.n16;
+#pragma unroll 1
+  for (int t0 = tid; t0 - tid < n; t0 += kLoads * kRankThreads) {
+    int v[kLoads];
+    uint32_t k[kLoads];
 #pragma unroll
-      for (int bit = 0; bit < 8; ++bit) {
-        const unsigned long long m = __ballot((d >> bit) & 1);
-        peers &= ((d >> bit) & 1) ? m : ~m;
-      }
-      const int before = __popcll(peers & ((1ull << lane) - 1ull));
-      __syncthreads();                                // counters cleared
-      if (on && before == 0) wave_cnt[wave][d] = __popcll(peers);
-      __syncthreads();
-      if (on) {
-        int at = base_of[d] + before;
-        for (int w = 0; w < wave; ++w) at += wave_cnt[w][d];
-        kout[at] = k;
-        vout[at] = v;
-      }
-      __syncthreads();
-      if (tid < 256) {
-        int t = 0;
+    for (int i = 0; i < kLoads; ++i) v[i] = t0 + i * kRankThreads < n ? (int)p.iperm[base + t0 + i * kRankThreads] : 0;
 #pragma unroll
-        for (int w = 0; w < kWaves; ++w) t += wave_cnt[w][tid];
-        base_of[tid] += t;
-      }
-      __syncthreads();
+    for (int i = 0; i < kLoads; ++i) k[i] = p.pick_key[base + v[i]];
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i) {
+      const int tok = t0 + i * kRankThreads;
+      const bool on = is_picked(tok, v[i]);
+      const unsigned long long mk = __ballot(on);
+      if (on) src[before[tok >> 6] + __popcll(mk & ((1ull << lane) - 1ull))] = (k[i] & 0xFFFF0000u) | (uint32_t)v[i];
     }
   }
-  // four passes: the sorted pairs are back in the first pair of arrays
-  for (int r = tid; r < P; r += kRankThreads) {
-    const int v = (int)valA[r];
-    p.rank[base + v] = r;
-    p.rank_vert[base + r] = (int)p.perm[base + v];   // from here on tokens again
+  const int run = (((P + kWaves - 1) / kWaves) + 63) & ~63;      // items per wave
+  const int s_begin = min(P, wave * run), s_end = min(P, s_begin + run);
+  volatile int *mine = place[wave];
+#pragma unroll 1
+  for (int shift = 16; shift < 32; shift += 8) {
+    for (int i = tid; i < kWaves * 256; i += kRankThreads) (&place[0][0])[i] = 0;
+    if (tid == 0) sh_alike = 0;
+    __syncthreads();
+#pragma unroll 1
+    for (int s0 = s_begin; s0 < s_end; s0 += 64 * kAtOnce) {
+      uint32_t k[kAtOnce];
+#pragma unroll
+      for (int q = 0; q < kAtOnce; ++q) {
+        const int s = s0 + 64 * q + lane;
+        k[q] = s < s_end ? src[s] : 0u;
+      }
+#pragma unroll
+      for (int q = 0; q < kAtOnce; ++q) {
+        const bool on = s0 + 64 * q + lane < s_end;
+        const int d = 255 - (int)((k[q] >> shift) & 255u);        // larger degrees first
+        const unsigned long long peers = same_digit(d, on);
+        if (on && lane == __builtin_ctzll(peers)) mine[d] = mine[d] + __popcll(peers);
+        __builtin_amdgcn_wave_barrier();
+      }
+    }
+    __syncthreads();
+    int total = 0, incl = 0;
+    if (tid < 256) {
+#pragma unroll
+      for (int w = 0; w < kWaves; ++w) total += place[w][tid];
+      incl = total;
+#pragma unroll
+      for (int o = 1; o < kWave; o <<= 1) {
+        const int x = __shfl_up(incl, o);
+        if (lane >= o) incl += x;
+      }
+      if (lane == kWave - 1) wsum[wave] = incl;
+      if (total == P) sh_alike = 1;
+    }
+    __syncthreads();
+    if (sh_alike) {                                  // this digit orders nothing (no picks: likewise)
+      __syncthreads();
+      continue;
+    }
+    if (tid < 256) {
+      int at = incl - total;
+      for (int w = 0; w < wave; ++w) at += wsum[w];
+#pragma unroll
+      for (int w = 0; w < kWaves; ++w) {
+        const int c = place[w][tid];
+        place[w][tid] = at;
+        at += c;
+      }
+    }
+    __syncthreads();
+#pragma unroll 1
+    for (int s0 = s_begin; s0 < s_end; s0 += 64 * kAtOnce) {
+      uint32_t k[kAtOnce];
+#pragma unroll
+      for (int q = 0; q < kAtOnce; ++q) {
+        const int s = s0 + 64 * q + lane;
+        k[q] = s < s_end ? src[s] : 0u;
+      }
+#pragma unroll
+      for (int q = 0; q < kAtOnce; ++q) {
+        const bool on = s0 + 64 * q + lane < s_end;
+        const int d = 255 - (int)((k[q] >> shift) & 255u);
+        const unsigned long long peers = same_digit(d, on);
+        const int at = mine[d];
+        __builtin_amdgcn_wave_barrier();
+        if (on) {
+          dst[at + __popcll(peers & ((1ull << lane) - 1ull))] = k[q];
+          if (lane == __builtin_ctzll(peers)) mine[d] = at + __popcll(peers);
+        }
+        __builtin_amdgcn_wave_barrier();
+      }
+    }
+    __syncthreads();
+    uint32_t *x = src;
+    src = dst;
+    dst = x;
+  }
+#pragma unroll 1
+  for (int r0 = 0; r0 < P; r0 += kAtOnce * kRankThreads) {
+    int v[kAtOnce], tok[kAtOnce];
+#pragma unroll
+    for (int q = 0; q < kAtOnce; ++q) v[q] = r0 + q * kRankThreads + tid < P ? (int)(src[r0 + q * kRankThreads + tid] & 0xFFFFu) : 0;
+#pragma unroll
+    for (int q = 0; q < kAtOnce; ++q) tok[q] = (int)p.perm[base + v[q]];
+#pragma unroll
+    for (int q = 0; q < kAtOnce; ++q) {
+      const int r = r0 + q * kRankThreads + tid;
+      if (r < P) {
+        p.rank[base + v[q]] = r;
+        p.rank_vert[base + r] = tok[q];              // from here on tokens again
+      }
+    }
   }
 }
 
-// References (Eq. 12, renumbered in codebook order) and codebook entries (Eq. 11), grid-wide.
-__global__ __launch_bounds__(256) void shallow_emit(ShallowParams p) {
-  const int ut = blockIdx.y, n = p.n;
+// References (Eq. 12, renumbered in codebook order) and codebook entries (Eq. 11), grid-wide.  A
+// thread takes a token's reference, a group of lanes with 16 bytes each (16 lanes; 32 for fp32) an entry
+// row.  Bound by latency, three dependent loads per reference and two per entry, so a block takes 32
+// entries in a few trips and four references per thread at once; a problem's blocks share an XCD's L2.  Where a
+// block for every 1024 tokens walked its entries one row per wave at a time and every wave updated the counter
+// of cut tokens: 64 problems of 32768 tokens with 4096 entries 225 -> 59 us, 2 of 32768 37 -> 9 us, one of 512
+// tokens with 128 entries 27 -> 7 us.
+constexpr int kEmitThreads = 256;
+
+constexpr int kEmitTokens = 4 * kEmitThreads;        // per block
+
+template <int DT>
+__global__ __launch_bounds__(kEmitThreads) void shallow_emit(ShallowParams p, int nblk) {
+  typedef typename Elem<DT>::type T;
+  constexpr int kPer = 16 / (int)sizeof(T), kLanes = kHeadDim / kPer;   // elements per lane, lanes per row
+  __shared__ int wsum[kEmitThreads / kWave];
+  __shared__ unsigned sh_at;
+  const int item = xcd_item();
+  if (item >= p.UT * nblk) return;
+  const int ut = item / nblk, blk = item % nblk, n = p.n;
   const size_t base = (size_t)ut * n;
   const int t = ut / p.U, u = ut % p.U;
   const int stored = p.n_codes[t][u];
   if (stored < 0) return;                        // the merge did not finish
   const int *rank = p.rank + base, *slot = p.slot + base, *rank_vert = p.rank_vert + base;
-  const uint16_t *iperm = p.iperm + base;
-  const int lane = lane_id();
-  for (int v0 = blockIdx.x * 256 + threadIdx.x - lane; v0 < n; v0 += gridDim.x * 256) {
-    const int v = v0 + lane;
-    const int r = v < n ? rank[slot[iperm[v]]] : 0;
-    if (v < n) p.ref[t][(size_t)u * n + v] = r;
-    const bool cut = v < n && r >= p.cap;
-    const unsigned long long mk = __ballot(cut);         // one counter update per wave
-    if (mk) {
-      unsigned at = 0;
-      if (lane == __builtin_ctzll(mk)) at = atomicAdd(p.ovf_cnt + ut, (unsigned)__popcll(mk));
-      at = __shfl(at, __builtin_ctzll(mk));
-      if (cut) p.ovf[base + at + __popcll(mk & ((1ull << lane) - 1ull))] = (uint32_t)v;
+  const int lane = lane_id(), tid = threadIdx.x, wave = tid >> 6;
+  const int v0 = blk * kEmitTokens + tid;
+  if (blk * kEmitTokens < n) {
+    int r[4], ncut = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) r[k] = v0 + k * kEmitThreads < n ? (int)p.iperm[base + v0 + k * kEmitThreads] : 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) r[k] = slot[r[k]];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) r[k] = rank[r[k]];
+    unsigned long long mk[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int v = v0 + k * kEmitThreads;
+      if (v < n) p.ref[t][(size_t)u * n + v] = r[k];
+      mk[k] = __ballot(v < n && r[k] >= p.cap);
+      ncut += __popcll(mk[k]);
+    }
+    if (lane == 0) wsum[wave] = ncut;
+    __syncthreads();
+    int at = 0, total = 0;
+#pragma unroll
+    for (int w = 0; w < kEmitThreads / kWave; ++w) {
+      at += w < wave ? wsum[w] : 0;
+      total += wsum[w];
+    }
+    if (total) {                                 // one counter update per block
+      if (tid == 0) sh_at = atomicAdd(p.ovf_cnt + ut, (unsigned)total);
+      __syncthreads();
+      at += (int)sh_at;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        if (mk[k] >> lane & 1ull) p.ovf[base + at + __popcll(mk[k] & ((1ull << lane) - 1ull))] = (uint32_t)(v0 + k * kEmitThreads);
+        at += __popcll(mk[k]);
+      }
     }
   }
-  for (int r = blockIdx.x * 4 + (threadIdx.x >> 6); r < stored; r += gridDim.x * 4) {
-    const int vert = rank_vert[r];
-    if (p.dtype == SPINDLE_F16) emit_code<SPINDLE_F16>(p, ut, vert, r);
-    else if (p.dtype == SPINDLE_BF16) emit_code<SPINDLE_BF16>(p, ut, vert, r);
-    else emit_code<SPINDLE_F32>(p, ut, vert, r);
+  const int piece = tid % kLanes;
+  for (int e = (blk * kEmitThreads + tid) / kLanes; e < stored; e += nblk * (kEmitThreads / kLanes)) {
+    const int vert = rank_vert[e];
+    const double m = p.m64[base + vert];
+    const u4 in = reinterpret_cast<const u4 *>(x_row(p, ut, vert))[piece];
+    const T *x = reinterpret_cast<const T *>(&in);
+    u4 out;
+    T *y = reinterpret_cast<T *>(&out);
+#pragma unroll
+    for (int k = 0; k < kPer; ++k)
+      y[k] = Elem<DT>::from_float(m > 0.0 ? (float)((double)Elem<DT>::to_float(x[k]) / m) : 0.f);
+    reinterpret_cast<u4 *>(reinterpret_cast<T *>(p.C[t]) + ((size_t)u * p.cap + e) * kHeadDim)[piece] = out;
   }
 }
 
@@ -376,8 +489,13 @@ spindle_status launch_codebook(const ShallowParams &p, hipStream_t st) {
   { ProfScope ps("shallow_rank", st);
   hipLaunchKernelGGL(shallow_rank, dim3(p.UT), dim3(kRankThreads), 0, st, p); }
   { ProfScope ps("shallow_emit", st);
-  int ex = (n + 1023) / 1024;
-  hipLaunchKernelGGL(shallow_emit, dim3(ex < 64 ? ex : 64, p.UT), dim3(256), 0, st, p); }
+  // as many blocks as the references or the entries ask for, whichever is more
+  const int kept = p.cap < n ? p.cap : n;
+  const int nref = (n + kEmitTokens - 1) / kEmitTokens, ncode = (kept + 31) / 32, nblk = nref > ncode ? nref : ncode;
+  const dim3 eg(xcd_grid((size_t)p.UT * nblk));
+  if (p.dtype == SPINDLE_F16) hipLaunchKernelGGL(shallow_emit<SPINDLE_F16>, eg, dim3(kEmitThreads), 0, st, p, nblk);
+  else if (p.dtype == SPINDLE_BF16) hipLaunchKernelGGL(shallow_emit<SPINDLE_BF16>, eg, dim3(kEmitThreads), 0, st, p, nblk);
+  else hipLaunchKernelGGL(shallow_emit<SPINDLE_F32>, eg, dim3(kEmitThreads), 0, st, p, nblk); }
   { ProfScope ps("shallow_assign", st);
   hipLaunchKernelGGL(shallow_assign, dim3((n + kAssignThreads - 1) / kAssignThreads, p.UT), dim3(kAssignThreads), 0, st, p);
   int ax = (n + 255) / 256;

@@ -10,11 +10,6 @@ namespace {
 typedef int i4v __attribute__((ext_vector_type(4)));
 typedef int i16v __attribute__((ext_vector_type(16)));
 
-// Blocks are dealt round-robin to the 8 XCDs; this numbering gives each XCD a run of consecutive
-// items (a problem's blocks share its L2).  The launch has a multiple of 8 blocks.
-__device__ __forceinline__ int xcd_item() { return (int)(blockIdx.x & 7) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3); }
-inline unsigned xcd_grid(size_t items) { return (unsigned)align_up(items, 8); }
-
 // ---------------------------------------------------------------- order
 // Every token goes to a pivot (up to 1024 tokens taken at equal distances): the lowest one whose sketch
 // product lies in the same step of 16384 (0.18 of a cosine) as the largest.  The lowest instead of

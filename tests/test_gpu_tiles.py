@@ -74,3 +74,19 @@ def test_structured_vectors(oracle):
     L = wl.Layer("f16", K, K.copy(), np.zeros((1, 1, 1, d), np.float16), 1, 1, 1, l, l)
     parity.check_shallow_layer(oracle, L, tensors=("k",), debug=False)
     parity.check_shallow_layer(oracle, L, tensors=("v",), debug=False, cap=60)
+
+
+@pytest.mark.parametrize("sizes", [(1,), (1,) * 70, (300, 255, 256, 257, 2) + (1,) * 40, (600, 600, 3, 3) + (1,) * 1030])
+@pytest.mark.parametrize("dtype", ["f16", "f32"])
+def test_codebook_order(oracle, dtype, sizes):
+    # the codebook is ordered by degree, then token: one degree only, degrees that differ in the low or the high
+    # byte, more picks than a block sorts at a time, tokens of equal degree in any order of similarity
+    rng = np.random.default_rng(66)
+    which = rng.permutation(np.repeat(np.arange(len(sizes)), sizes))
+    centres = rng.standard_normal((len(sizes), 128))
+    x = centres[which] * rng.uniform(0.5, 2.0, (len(which), 1)) + 0.01 * rng.standard_normal((len(which), 128))
+    K = wl.cast(x[None, None], dtype)
+    l = len(which)
+    L = wl.Layer(dtype, K, K.copy(), np.zeros_like(K[:, :, :1]), 1, 1, 1, l, l)
+    parity.check_shallow_layer(oracle, L, tensors=("k",), debug=False)
+    parity.check_shallow_layer(oracle, L, tensors=("v",), debug=False, cap=max(1, len(sizes) // 3))
