@@ -377,12 +377,29 @@ __global__ __launch_bounds__(kBuildThreads) void decode_build(DecodeParams p) {
 // as doubles in LDS, every thread a few stored entries (same sums, same decision as
 // decode_match), a reduction over the workgroup, and Alg. 1 on the at most MT unmatched
 // tokens by the first wave (adjacency in one word per token, the loop as stated).
+// A sum runs over the dimensions in order, so a lane has a stored row to itself; but rows read by
+// their lanes 16 bytes at a time are 64 cache lines per load, which a compute unit's cache loses
+// again before the next piece of them is read.  So a wave reads its 64 rows one cache line of each at a
+// time, eight lanes per line, a line ahead in registers, and turns them round in LDS.
+// The sums in double precision bound it now (a token slot costs a multiply-add per element, so the tokens
+// are counted in the kernel's type).  8 heads, one fp16 token each against 1650 entries: 22 -> 14 us a call.
 constexpr int kSmallThreads = 1024;
+constexpr int kSmallLine = 128;                      // bytes of a row at a time
+constexpr int kSmallLds = kSmallThreads * kSmallLine;
+
+// Four slots of 2-byte tokens: the reads of the tokens' values keep LDS busy, and rows that go through it
+// as well gain only once there are several turns of 1024 entries; their lanes read them directly (8 heads,
+// 3 tokens, 1000 entries: 17 us, through LDS 18).  fp32 rows are twice as long: through LDS 20 us, directly 23.
+template <int DT, int MT>
+constexpr bool small_in_lines() { return MT < 4 || DT == SPINDLE_F32; }
 
 template <int DT, int MT>
 __global__ __launch_bounds__(kSmallThreads) void decode_small(DecodeParams p) {
   typedef typename Elem<DT>::type T;
-  constexpr int per = 16 / sizeof(T), pieces = kHeadDim / per, kWaves = kSmallThreads / kWave;
+  constexpr int per = 16 / sizeof(T), kWaves = kSmallThreads / kWave;
+  constexpr int row_bytes = kHeadDim * sizeof(T), kLines = row_bytes / kSmallLine, kPieces = kSmallLine / 16;
+  constexpr bool direct = !small_in_lines<DT, MT>();
+  extern __shared__ __attribute__((aligned(16))) char lines[];
   __shared__ __attribute__((aligned(16))) double xs[kHeadDim][MT];
   __shared__ double ms[MT];
   __shared__ double red_v[kWaves][MT];
@@ -392,6 +409,20 @@ __global__ __launch_bounds__(kSmallThreads) void decode_small(DecodeParams p) {
   const int u = blockIdx.x, tid = threadIdx.x, lane = lane_id(), wave = tid >> 6, m = p.m;
   int nc = p.n_codes[u];
   nc = nc < 0 ? 0 : (nc > p.cap ? p.cap : nc);
+  // the wave's entries: 64 of every 1024
+  const int ngroups = nc > wave * kWave ? (nc - wave * kWave + kSmallThreads - 1) / kSmallThreads : 0;
+  const char *Cb = p.C + (size_t)u * p.cap * row_bytes;
+  u4 ahead[kPieces];
+  auto load = [&](int step) __attribute__((always_inline)) {   // line step % kLines of group step / kLines
+    const int c0 = (step / kLines) * kSmallThreads + wave * kWave;
+#pragma unroll
+    for (int q = 0; q < kPieces; ++q) {
+      const int c = min(c0 + q * (kWave / kPieces) + lane / kPieces, nc - 1);
+      ahead[q] = *reinterpret_cast<const u4 *>(Cb + (size_t)c * row_bytes + (step % kLines) * kSmallLine +
+                                               (lane % kPieces) * 16);
+    }
+  };
+  if (ngroups > 0 && !direct) load(0);
   for (int i = tid; i < MT * kHeadDim; i += kSmallThreads) {
     const int tok = i / kHeadDim, dim = i % kHeadDim;
     xs[dim][tok] = tok < m ? (double)Elem<DT>::to_float(reinterpret_cast<const T *>(token_row<DT>(p, u, tok))[dim]) : 0.0;
@@ -399,6 +430,7 @@ __global__ __launch_bounds__(kSmallThreads) void decode_small(DecodeParams p) {
   __syncthreads();
   if (tid < MT) {
     double ss = 0.0;
+#pragma unroll 16
     for (int dim = 0; dim < kHeadDim; ++dim) ss += xs[dim][tid] * xs[dim][tid];
     const double mg = sqrt(ss);
     ms[tid] = mg;
@@ -414,21 +446,47 @@ __global__ __launch_bounds__(kSmallThreads) void decode_small(DecodeParams p) {
     bidx[t] = -1;
   }
   const double low = p.theta >= 0.0 ? p.theta * (1.0 - 1e-12) : -INFINITY;   // see decode_match
-  for (int c = tid; c < nc; c += kSmallThreads) {   // ascending: the first of equal values stays
-    const u4 *row = reinterpret_cast<const u4 *>(p.C + ((size_t)u * p.cap + c) * (kHeadDim * sizeof(T)));
+  // piece k of row r at place k ^ (r / 2) % 8: sixteen consecutive lanes of either access hit all 64 banks
+  char *own = lines + wave * (kWave * kSmallLine);
+  for (int grp = 0; grp < ngroups; ++grp) {          // ascending: the first of equal values stays
+    const int c = grp * kSmallThreads + tid;
     double acc[MT], css = 0.0;
 #pragma unroll
     for (int t = 0; t < MT; ++t) acc[t] = 0.0;
-    for (int pc = 0; pc < pieces; ++pc) {
-      const u4 v = row[pc];
+    auto add = [&](const u4 &v, int dim) __attribute__((always_inline)) {   // 16 bytes from dimension `dim` on
 #pragma unroll
       for (int j = 0; j < per; ++j) {
         const double y = (double)Elem<DT>::to_float(reinterpret_cast<const T *>(&v)[j]);
         css += y * y;
 #pragma unroll
-        for (int t = 0; t < MT; ++t) acc[t] += xs[pc * per + j][t] * y;
+        for (int t = 0; t < MT; ++t) acc[t] += xs[dim + j][t] * y;
+      }
+    };
+    if (direct) {
+      if (c >= nc) continue;
+      const u4 *row = reinterpret_cast<const u4 *>(Cb + (size_t)c * row_bytes);
+      for (int pc = 0; pc < row_bytes / 16; ++pc) add(row[pc], pc * per);
+    } else {
+#pragma unroll 1
+      for (int line = 0; line < kLines; ++line) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // the line before has been read
+#pragma unroll
+        for (int q = 0; q < kPieces; ++q) {
+          const int r = q * (kWave / kPieces) + lane / kPieces;
+          *reinterpret_cast<u4 *>(own + r * kSmallLine + (((lane % kPieces) ^ ((r >> 1) & 7)) << 4)) = ahead[q];
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // LDS keeps the order of one wave's accesses
+        const int step = grp * kLines + line;
+        if (step + 1 < ngroups * kLines) load(step + 1);
+#pragma unroll
+        for (int pc = 0; pc < kPieces; ++pc) {
+          add(*reinterpret_cast<const u4 *>(own + lane * kSmallLine + ((pc ^ ((lane >> 1) & 7)) << 4)),
+              (line * kPieces + pc) * per);
+          if (pc & 1) __builtin_amdgcn_sched_barrier(0);   // (all tokens' values at once would not fit the registers)
+        }
       }
     }
+    if (c >= nc) continue;                           // (lanes past the end summed the last row)
     const double cn = sqrt(css);
 #pragma unroll
     for (int t = 0; t < MT; ++t) {
@@ -624,6 +682,23 @@ spindle_status decode_check_args(const spindle_kv_desc *desc, const void *X_new,
   return SPINDLE_OK;
 }
 
+template <int DT, int MT>
+spindle_status launch_small(const DecodeParams &p, hipStream_t st) {
+  constexpr int lds = small_in_lines<DT, MT>() ? kSmallLds : 0;
+  static LdsLimit lim;
+  if (lds > 0)
+    if (spindle_status e = allow_lds(lim, reinterpret_cast<const void *>(&decode_small<DT, MT>), lds)) return e;
+  hipLaunchKernelGGL((decode_small<DT, MT>), dim3(p.U), dim3(kSmallThreads), lds, st, p);
+  return SPINDLE_OK;
+}
+// By the number of tokens: every token slot costs a multiply-add per element of the codebook, used or not.
+template <int DT>
+spindle_status launch_small(const DecodeParams &p, hipStream_t st) {
+  if (p.m == 1) return launch_small<DT, 1>(p, st);
+  if (p.m == 2) return launch_small<DT, 2>(p, st);
+  return launch_small<DT, 4>(p, st);
+}
+
 // Enqueues the kernels of one merge; `scratch_mem` holds decode_carve's arrays and needs no
 // initial content: every element a kernel reads was written by an earlier kernel of the same call.
 spindle_status decode_enqueue(const spindle_kv_desc *desc, const void *X_new, float theta, int32_t max_codes,
@@ -645,11 +720,11 @@ spindle_status decode_enqueue(const spindle_kv_desc *desc, const void *X_new, fl
   p.theta = (double)theta;
   if (p.m <= 4) {
     ProfScope ps("decode_small", st);
-#define SPINDLE_DECODE_SMALL(DT) hipLaunchKernelGGL((decode_small<DT, 4>), dim3(p.U), dim3(kSmallThreads), 0, st, p)
-    if (p.dtype == SPINDLE_F16) SPINDLE_DECODE_SMALL(SPINDLE_F16);
-    else if (p.dtype == SPINDLE_BF16) SPINDLE_DECODE_SMALL(SPINDLE_BF16);
-    else SPINDLE_DECODE_SMALL(SPINDLE_F32);
-#undef SPINDLE_DECODE_SMALL
+    spindle_status e;
+    if (p.dtype == SPINDLE_F16) e = launch_small<SPINDLE_F16>(p, st);
+    else if (p.dtype == SPINDLE_BF16) e = launch_small<SPINDLE_BF16>(p, st);
+    else e = launch_small<SPINDLE_F32>(p, st);
+    if (e != SPINDLE_OK) return e;
     SPINDLE_HIP(hipGetLastError());
     return SPINDLE_OK;
   }

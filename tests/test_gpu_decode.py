@@ -115,6 +115,27 @@ def test_few_tokens_per_call(oracle, dtype, m):
             run_and_check(oracle, np.ascontiguousarray(new[:, :1]), small, nc[:, :1], dtype, theta)
 
 
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
+@pytest.mark.parametrize("m", [1, 2, 3])
+def test_few_tokens_against_any_number_of_entries(oracle, dtype, m):
+    # one launch reads 64 entries per wave and 1024 per turn: around both, with the entries of one token at the ends
+    sizes = [1, 63, 64, 65, 1023, 1024, 1025, 2050]
+    rng = np.random.default_rng(71)
+    cap = 2060
+    Cb = np.zeros((1, len(sizes), cap, 128))
+    new = rng.standard_normal((1, len(sizes), m, 128))
+    for h, k in enumerate(sizes):
+        Cb[0, h, :k] = rng.standard_normal((k, 128))
+        new[0, h, 0] = 3.0 * Cb[0, h, k - 1]             # the last entry
+        if m > 1:
+            new[0, h, 1] = Cb[0, h, k // 2]
+    nc = np.array([sizes], dtype=np.int32)
+    res, _, _ = run_and_check(oracle, wl.cast(new, dtype), wl.cast(Cb, dtype), nc, dtype, 0.95)
+    assert [int(o["ref"][0]) for o in res] == [k - 1 for k in sizes]
+    if m > 1:
+        assert [int(o["ref"][1]) for o in res] == [k // 2 for k in sizes]
+
+
 def test_empty_partial_and_full_codebooks(oracle):
     # unit 0: no stored entries (plain Alg. 1 on the new tokens); unit 1: half of the prefill's
     # entries; units 2, 3: all of them; then tables with two free rows and with none
