@@ -1,4 +1,4 @@
-// Codebook path: workspace layout and the C entry points (kernels: shallow_graph.hip,
+// Codebook path: workspace layout and the C entry points (kernels: shallow_prep.hip, shallow_tiles.hip,
 // shallow_merge.hip, shallow_codebook.hip; what they share: shallow.h).
 #include <vector>
 

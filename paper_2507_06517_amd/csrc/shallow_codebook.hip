@@ -316,7 +316,7 @@ __global__ __launch_bounds__(kAssignThreads, 2) void shallow_assign(ShallowParam
 #pragma unroll
     for (int ks = 0; ks < M::kSteps; ++ks) af[cb][ks] = valid[cb] ? M::load(Xh + (size_t)tok * 256, ks, g) : M::zero();
   }
-  // staged entry 16*g + v of a tile is fed to matrix row 8*(v/4) + 4*g + v%4 (as in shallow_gram)
+  // staged entry 16*g + v of a tile is fed to matrix row 8*(v/4) + 4*g + v%4 (as in shallow_rows)
   const int prow = 16 * ((c >> 2) & 1) + 4 * (c >> 3) + (c & 3);
   int soff[M::kSteps];
 #pragma unroll
