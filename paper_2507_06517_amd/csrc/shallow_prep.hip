@@ -45,11 +45,15 @@ __global__ __launch_bounds__(256) void shallow_prep(ShallowParams p) {
     p.m64[idx] = m;
     p.mag[t][(size_t)(ut % p.U) * p.n + row0 + r] = (float)m;
     row_inv[r] = m > 0.0 ? (double)kUnitScale / m : 0.0;
-    // (NaN: the products of the row may leave the range of fp32, shallow_rows decides its pairs in
-    // double precision)
-    float inv = m > 0.0 ? (float)(1.0 / m) : 0.f;
-    if (DT == SPINDLE_F32) inv = m > 0.0 ? (m > 0x1p-100 && m < 0x1p100 ? 1.f / kUnitScale : NAN) : 0.f;
-    else if (m > 0.0 && !(m > 0x1p-40 && m < 0x1p55)) inv = NAN;
+    // NaN: the products of the row may leave the range of fp32, shallow_rows decides its pairs in
+    // double precision.  Rows that hold a NaN or an infinity go the same way: their products are NaN with
+    // a sign that depends on the order of the operands, so the two ends of a pair could decide
+    // differently, and the merge needs a symmetric relation.
+    float inv = 0.f;
+    if (m != 0.0) {
+      const bool usual = DT == SPINDLE_F32 ? m > 0x1p-100 && m < 0x1p100 : m > 0x1p-40 && m < 0x1p55;
+      inv = !usual ? NAN : DT == SPINDLE_F32 ? 1.f / kUnitScale : (float)(1.0 / m);
+    }
     p.inv[idx] = inv;
     p.perm[idx] = (uint16_t)(row0 + r);
     p.iperm[idx] = (uint16_t)(row0 + r);
@@ -132,7 +136,7 @@ __global__ __launch_bounds__(256) void shallow_prep(ShallowParams p) {
         // most half of the two squares.  In sketch units squared, rounded up.
         const float e = sqrtf(q2) * (1.f / kSketchScale);
         if (part == 0)
-          p.serr[idx] = fine ? (uint32_t)((e + 0.5f * e * e) * (kSketchScale * kSketchScale * (1.f + 1e-5f))) + 2u : kSketchUnknown;
+          p.serr[idx] = fine && e < 4.f ? (uint32_t)((e + 0.5f * e * e) * (kSketchScale * kSketchScale * (1.f + 1e-5f))) + 2u : kSketchUnknown;
       }
     }
   }

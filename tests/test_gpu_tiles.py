@@ -60,6 +60,27 @@ def test_magnitudes_out_of_the_ordinary(oracle, dtype, l):
     parity.check_shallow_layer(oracle, L, debug=False, tensors=("k",))
 
 
+@pytest.mark.parametrize("l", [700, 2200])
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
+def test_rows_that_are_not_finite_have_no_neighbours(oracle, dtype, l):
+    # a cosine with such a row is no number or 0 / NaN, never above a threshold: G stays symmetric whatever the
+    # signs of the NaNs are, these tokens get entries of their own and nobody else's reference changes
+    L = wl.small_random(67, dtype, B=1, H=1, l=l, lw=1, cap=l, n_centroids=12, noise_frac=0.2)
+    x = wl.to_f64(L.K, dtype)
+    odd = np.array([0, 1, 2, 3, 40, 41, 333, l - 2, l - 1])
+    for i, t in enumerate(odd):
+        x[0, 0, t, i::17] = (np.nan, -np.nan, np.inf, -np.inf)[i % 4]
+    with np.errstate(over="ignore", invalid="ignore"):
+        L.K = wl.cast(x, dtype)
+    g = parity.gpu_shallow(L, tensors=("k",))
+    adj = np.unpackbits(g["adj_k"][0, 0].view(np.uint8), axis=1, bitorder="little")[:, :l]
+    assert np.array_equal(adj, adj.T)
+    assert np.array_equal(adj[odd], np.eye(l, dtype=np.uint8)[odd])
+    o = oracle.shallow_unit(wl.to_f64(L.K[0, 0], dtype), float(np.float32(L.theta_k)), l)
+    assert np.array_equal(g["deg_k"][0, 0], o["deg"]) and np.array_equal(g["ref_k"][0, 0], o["ref"])
+    assert g["n_codes_k"][0, 0] == o["n_codes"]
+
+
 def test_structured_vectors(oracle):
     # vectors the rotation of the sketch maps to few coordinates (constant, alternating, single ones), scaled
     # copies, opposite ones: sketches of little use, whose errors must widen what is looked at
