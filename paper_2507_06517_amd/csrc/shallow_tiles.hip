@@ -282,6 +282,7 @@ __global__ __launch_bounds__(kScanThreads, 2) void shallow_scan(ShallowParams p,
 constexpr float kRowsGuard = 7e-5f;
 constexpr int kRowsQueue = 192;                    // waiting pairs per wave
 constexpr int kRowsThreads = 256;
+constexpr int kRowsPitch = kWave + 2;              // result bits of a step, and a word so that one lane's bits of 32 steps are 32 banks
 
 template <int DT, int kCols>
 struct RowsLds {
@@ -292,12 +293,91 @@ struct RowsLds {
   char stage[kStages][kStage];
   float inv[kBatch * kCols][kTile];
   uint16_t tok[kBatch * kCols][kTile];
-  uint16_t bits[4][kBatch * kWave];
+  uint16_t bits[4][kBatch * kRowsPitch];
   uint16_t queue[4][kRowsQueue];
   uint16_t tiles[2048];                                                  // column tile | 1 << (11 + row tile of the block)
   int deg[4][kWave], words[4][kWave];
   int ntiles;
 };
+
+// A wave's rows r0 .. r0 + nr - 1 of row tile R from the bits in memory (word t of a row's room: column tile t, written for the
+// tiles of the list): counted, and turned into words in place.  A row is in registers before any of
+// it is overwritten, kRows rows at a time for the latency of the reads.  16 problems of 32768 similar tokens: 9.9 ms for
+// the kernel, 19.6 where cosines were taken again to write words whose number was known by then.
+template <int kRows, int kWords>
+__device__ __forceinline__ void rows_from_memory(const ShallowParams &p, int ut, int R, int r0, int nr, int rows_here,
+                                                 const uint16_t *tiles, int ntiles) {
+  const int lane = lane_id(), n = p.n, T = p.T, pitch = p.list_row;
+  const size_t base = (size_t)ut * n;
+  uint32_t *lists = p.lists + base * pitch + (size_t)R * kTile * pitch;
+  const unsigned long long below = (1ull << lane) - 1ull;
+  int deg = 0;                                         // lane i: those of row r0 + i
+  uint32_t words = 0;
+  const int r1 = min(r0 + nr, rows_here);
+  for (int r = r0; r < r1; r += kRows) {
+    uint32_t w[kRows][kWords];
+#pragma unroll
+    for (int k = 0; k < kWords; ++k) {
+      const int i = k * kWave + lane;
+      if (k * kWave < ntiles) {                        // wave-uniform, as below
+        const int t = (int)(tiles[min(i, ntiles - 1)] & 2047u);
+#pragma unroll
+        for (int j = 0; j < kRows; ++j) w[j][k] = i < ntiles && r + j < r1 ? lists[(size_t)(r + j) * pitch + t] : 0u;
+      } else {
+#pragma unroll
+        for (int j = 0; j < kRows; ++j) w[j][k] = 0u;
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < kRows; ++j) {
+      if (r + j >= r1) continue;
+      int d = 0, total = 0;
+#pragma unroll
+      for (int k = 0; k < kWords; ++k)
+        if (k * kWave < ntiles) {
+          d += __popc(w[j][k]);
+          total += __popcll(__ballot((w[j][k] & 0xFFFFu) != 0)) + __popcll(__ballot(w[j][k] >> 16 != 0));
+        }
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) d += __shfl_xor(d, o);
+      const bool dense = total > pitch;
+      if (lane == r + j - r0) {
+        deg = d;
+        words = dense ? kDenseRow | (uint32_t)(2 * T) : (uint32_t)total;
+      }
+      uint32_t *out = lists + (size_t)(r + j) * pitch;
+      if (dense) {
+        if (ntiles == T) continue;                     // every tile has its word already
+        for (int t = lane; t < T; t += kWave) out[t] = 0;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");   // before the bits of the marked ones are written
+#pragma unroll
+        for (int k = 0; k < kWords; ++k)
+          if (k * kWave + lane < ntiles) out[tiles[k * kWave + lane] & 2047u] = w[j][k];
+        continue;
+      }
+      int at = 0;
+#pragma unroll
+      for (int k = 0; k < kWords; ++k)
+        if (k * kWave < ntiles) {
+          const uint32_t lo = w[j][k] & 0xFFFFu, hi = w[j][k] >> 16;
+          const unsigned long long mlo = __ballot(lo != 0), mhi = __ballot(hi != 0);
+          if (w[j][k]) {
+            const uint32_t half = 2u * (tiles[k * kWave + lane] & 2047u);
+            uint32_t *o = out + at + __popcll(mlo & below) + __popcll(mhi & below);
+            if (lo) *o++ = half << 16 | lo;
+            if (hi) *o = (half + 1) << 16 | hi;
+          }
+          at += __popcll(mlo) + __popcll(mhi);
+        }
+    }
+  }
+  if (lane < r1 - r0) {
+    const int row = R * kTile + r0 + lane, tok = (int)p.perm[base + row];
+    p.key[(size_t)ut * p.n16 + row] = ((uint32_t)deg << 16) | (uint32_t)(0xFFFF - tok);
+    p.rows[base + row] = make_uint2((uint32_t)row * pitch, words);
+    if (p.deg_out[ut / p.U]) p.deg_out[ut / p.U][(size_t)(ut % p.U) * n + tok] = deg;
+  }
+}
 
 template <int DT, int kCols>
 __global__ __launch_bounds__(kRowsThreads, 2) void shallow_rows(ShallowParams p, int nblk) {
@@ -394,16 +474,16 @@ __global__ __launch_bounds__(kRowsThreads, 2) void shallow_rows(ShallowParams p,
   const int ntiles = __builtin_amdgcn_readfirstlane(l.ntiles);
   const int nall = (ntiles + kCols - 1) / kCols;       // steps
 
-  // A problem with more steps than a batch holds goes through them twice: degrees and words counted
-  // first, then the same bits again to be written.
-  const int nbatch = (nall + L::kBatch - 1) / L::kBatch, npass = nbatch == 1 ? 1 : 2 * nbatch;
-  int deg = 0, words = 0, nq = 0, ndecided = 0;
-  bool dense = false;
-  uint32_t *out = nullptr;
-  for (int pass = 0; pass < npass; ++pass) {
-    const int s0 = (pass < nbatch ? pass : pass - nbatch) * L::kBatch, ns = min(L::kBatch, nall - s0);
+  // Bits of more steps than a batch holds go to the rows' room in the lists, word t for column tile t, and
+  // from there into words at the end.
+  const int nbatch = (nall + L::kBatch - 1) / L::kBatch;
+  const int rows_here = mine ? min(kTile, n - R * kTile) : 0;
+  uint32_t *lists = p.lists + base * p.list_row;
+  int nq = 0, ndecided = 0;
+  for (int batch = 0; batch < nbatch; ++batch) {
+    const int s0 = batch * L::kBatch, ns = min(L::kBatch, nall - s0);
     const int t0 = s0 * kCols, nt = min(L::kBatch * kCols, ntiles - t0);
-    if (pass > 0) __syncthreads();                     // the batch before is done with these
+    if (batch > 0) __syncthreads();                    // the batch before is done with these
     for (int i = tid; i < nt * kTile; i += kRowsThreads) {
       const int col = (int)(l.tiles[t0 + (i >> 5)] & 2047u) * kTile + (i & 31);
       l.tok[i >> 5][i & 31] = perm[col < n ? col : n - 1];
@@ -437,7 +517,7 @@ __global__ __launch_bounds__(kRowsThreads, 2) void shallow_rows(ShallowParams p,
       const int i = s * kCols + member;                // this wave's tile of the batch
       const uint32_t entry = i < nt ? (uint32_t)__builtin_amdgcn_readfirstlane((int)l.tiles[t0 + i]) : 0u;
       if (!(entry >> (11 + rt) & 1u)) {                // wave-uniform
-        bits[s * kWave + lane] = 0;
+        bits[s * kRowsPitch + lane] = 0;
         continue;
       }
       const int t = (int)(entry & 2047u);
@@ -485,7 +565,7 @@ __global__ __launch_bounds__(kRowsThreads, 2) void shallow_rows(ShallowParams p,
         yes &= ~close;
       }
       if (self && row_on) yes |= 1u << (c & 15);       // G_aa = 1
-      bits[s * kWave + lane] = (uint16_t)yes;
+      bits[s * kRowsPitch + lane] = (uint16_t)yes;
       for (;;) {                                       // one close pair per lane at a time into the queue
         const unsigned long long m = __ballot(close != 0);
         if (nq > kRowsQueue - kWave || (m == 0 && nq > 0 && s + 1 == ns)) {
@@ -495,9 +575,9 @@ __global__ __launch_bounds__(kRowsThreads, 2) void shallow_rows(ShallowParams p,
             const uint32_t e = queue[j];
             const int slot = (int)(e >> 10), ln = (int)((e >> 4) & 63), v = (int)(e & 15);
             const int a = (int)perm[R * kTile + (ln & 31)], b = (int)l.tok[slot * kCols + member][16 * (ln >> 5) + v];
-            ndecided += pass < nbatch;
+            ++ndecided;
             if (cos64<DT, 4>(p, ut, a, b) > (double)theta) {
-              const int at = slot * kWave + ln;
+              const int at = slot * kRowsPitch + ln;
               atomicOr(reinterpret_cast<uint32_t *>(bits) + (at >> 1), 1u << (v + 16 * (at & 1)));
             }
           }
@@ -520,77 +600,86 @@ __global__ __launch_bounds__(kRowsThreads, 2) void shallow_rows(ShallowParams p,
         const uint32_t e = queue[j];
         const int slot = (int)(e >> 10), ln = (int)((e >> 4) & 63), v = (int)(e & 15);
         const int a = (int)perm[R * kTile + (ln & 31)], b = (int)l.tok[slot * kCols + member][16 * (ln >> 5) + v];
-        ndecided += pass < nbatch;
+        ++ndecided;
         if (cos64<DT, 4>(p, ut, a, b) > (double)theta) {
-          const int at = slot * kWave + ln;
+          const int at = slot * kRowsPitch + ln;
           atomicOr(reinterpret_cast<uint32_t *>(bits) + (at >> 1), 1u << (v + 16 * (at & 1)));
         }
       }
       nq = 0;
       asm volatile("" ::: "memory");
     }
-    if (pass < nbatch)
-      for (int s = 0; s < ns; ++s) {
-        const uint32_t m = bits[s * kWave + lane];
-        deg += __popc(m);
-        words += m != 0;
-      }
-    if (pass == nbatch - 1) {
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) ndecided += __shfl_xor(ndecided, o);
-      if (lane == 0 && ndecided) atomicAdd(p.pairs_exact + ut, (unsigned)ndecided);
-      l.deg[wave][lane] = deg;
-      l.words[wave][lane] = words;
-      __syncthreads();
-      // a row's words: those of lane group 0 of every wave of its row tile, then those of group 1
-      int total = 0, d = 0, at = 0;
-#pragma unroll
-      for (int q = 0; q < kCols; ++q) {
-        const int w = rt * kCols + q;
-        const int x0 = l.words[w][c], x1 = l.words[w][32 + c];
-        d += l.deg[w][c] + l.deg[w][32 + c];
-        total += x0 + x1;
-        at += g == 0 ? (q < member ? x0 : 0) : x0 + (q < member ? x1 : 0);
-      }
-      int incl = total;                                // over the 32 rows (the same in both lane groups)
-#pragma unroll
-      for (int o = 1; o < 32; o <<= 1) {
-        const int y = __shfl_up(incl, o, 32);
-        if (c >= o) incl += y;
-      }
-      const int rows_here = mine ? min(kTile, n - R * kTile) : 0;
-      dense = __builtin_amdgcn_readlane(incl, 31) > rows_here * p.list_row;
-      uint32_t *lists = p.lists + base * p.list_row;
-      const uint32_t first = dense ? (uint32_t)row * p.list_row : (uint32_t)(R * kTile * p.list_row + incl - total);
-      if (g == 0 && row_on && member == 0) {
-        p.key[(size_t)ut * p.n16 + row] = ((uint32_t)d << 16) | (uint32_t)(0xFFFF - row_tok);
-        p.rows[base + row] = make_uint2(first, dense ? kDenseRow | (uint32_t)(2 * T) : (uint32_t)total);
-        if (p.deg_out[ut / p.U]) p.deg_out[ut / p.U][(size_t)(ut % p.U) * n + row_tok] = d;
-      }
-      if (lane == 0 && member == 0 && mine) {
-        const uint32_t ones = rows_here == kTile ? 0xFFFFFFFFu : (1u << rows_here) - 1u;
-        p.live[0][(size_t)ut * T + R] = ones;
-        p.live[1][(size_t)ut * T + R] = ones;
-        p.live[2][(size_t)ut * T + R] = ones;
-      }
-      out = lists + first + (dense ? 0 : at);
-      if (dense && p.scan && member == 0) {            // tiles that were not marked: no bits
-        for (int i = lane; i < rows_here * p.list_row; i += kWave) lists[(size_t)R * kTile * p.list_row + i] = 0;
-        __builtin_amdgcn_s_waitcnt(0x0F70);            // before the bits of the marked ones are written
-      }
-      __syncthreads();
+    if (nbatch == 1) break;
+    constexpr int kRowsAtOnce = kWave / L::kBatch;     // lanes along the steps: runs of neighbouring tiles are runs of memory
+    const int ls = lane % L::kBatch, li = ls * kCols + member;
+    if (ls < ns && li < nt) {
+      const int t = (int)(l.tiles[t0 + li] & 2047u);
+      for (int r = lane / L::kBatch; r < rows_here; r += kRowsAtOnce)
+        lists[(size_t)(R * kTile + r) * p.list_row + t] =
+            (uint32_t)bits[ls * kRowsPitch + r] | (uint32_t)bits[ls * kRowsPitch + 32 + r] << 16;
     }
-    if (nbatch == 1 || pass >= nbatch) {
-      for (int s = 0; s < ns; ++s) {
-        const int i = s * kCols + member;
-        if (i >= nt) break;
-        const uint32_t m = bits[s * kWave + lane], half = 2u * (l.tiles[t0 + i] & 2047u) + g;
-        if (dense) {
-          if (row_on) reinterpret_cast<uint16_t *>(out)[half] = (uint16_t)m;
-        } else if (m) {
-          *out++ = half << 16 | m;
-        }
-      }
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) ndecided += __shfl_xor(ndecided, o);
+  if (lane == 0 && ndecided) atomicAdd(p.pairs_exact + ut, (unsigned)ndecided);
+  if (lane == 0 && member == 0 && mine) {
+    const uint32_t ones = rows_here == kTile ? 0xFFFFFFFFu : (1u << rows_here) - 1u;
+    p.live[0][(size_t)ut * T + R] = ones;
+    p.live[1][(size_t)ut * T + R] = ones;
+    p.live[2][(size_t)ut * T + R] = ones;
+  }
+  if (nbatch > 1) {
+    __syncthreads();                                   // (and the words in memory are every wave's to read)
+    if (ntiles <= 8 * kWave) rows_from_memory<4, 8>(p, ut, R, member * (kTile / kCols), kTile / kCols, rows_here, l.tiles, ntiles);
+    else rows_from_memory<1, 32>(p, ut, R, member * (kTile / kCols), kTile / kCols, rows_here, l.tiles, ntiles);
+    return;
+  }
+  int deg = 0, words = 0;
+  for (int s = 0; s < nall; ++s) {
+    const uint32_t m = bits[s * kRowsPitch + lane];
+    deg += __popc(m);
+    words += m != 0;
+  }
+  l.deg[wave][lane] = deg;
+  l.words[wave][lane] = words;
+  __syncthreads();
+  // a row's words: those of lane group 0 of every wave of its row tile, then those of group 1
+  int total = 0, d = 0, at = 0;
+#pragma unroll
+  for (int q = 0; q < kCols; ++q) {
+    const int w = rt * kCols + q;
+    const int x0 = l.words[w][c], x1 = l.words[w][32 + c];
+    d += l.deg[w][c] + l.deg[w][32 + c];
+    total += x0 + x1;
+    at += g == 0 ? (q < member ? x0 : 0) : x0 + (q < member ? x1 : 0);
+  }
+  int incl = total;                                    // over the 32 rows (the same in both lane groups)
+#pragma unroll
+  for (int o = 1; o < 32; o <<= 1) {
+    const int y = __shfl_up(incl, o, 32);
+    if (c >= o) incl += y;
+  }
+  const bool dense = __builtin_amdgcn_readlane(incl, 31) > rows_here * p.list_row;
+  const uint32_t first = dense ? (uint32_t)row * p.list_row : (uint32_t)(R * kTile * p.list_row + incl - total);
+  if (g == 0 && row_on && member == 0) {
+    p.key[(size_t)ut * p.n16 + row] = ((uint32_t)d << 16) | (uint32_t)(0xFFFF - row_tok);
+    p.rows[base + row] = make_uint2(first, dense ? kDenseRow | (uint32_t)(2 * T) : (uint32_t)total);
+    if (p.deg_out[ut / p.U]) p.deg_out[ut / p.U][(size_t)(ut % p.U) * n + row_tok] = d;
+  }
+  uint32_t *out = lists + first + (dense ? 0 : at);
+  if (dense && p.scan && member == 0) {                // tiles that were not marked: no bits
+    for (int i = lane; i < rows_here * p.list_row; i += kWave) lists[(size_t)R * kTile * p.list_row + i] = 0;
+    __builtin_amdgcn_s_waitcnt(0x0F70);                // before the bits of the marked ones are written
+  }
+  __syncthreads();
+  for (int s = 0; s < nall; ++s) {
+    const int i = s * kCols + member;
+    if (i >= ntiles) break;
+    const uint32_t m = bits[s * kRowsPitch + lane], half = 2u * (l.tiles[i] & 2047u) + g;
+    if (dense) {
+      if (row_on) reinterpret_cast<uint16_t *>(out)[half] = (uint16_t)m;
+    } else if (m) {
+      *out++ = half << 16 | m;
     }
   }
 }

@@ -31,6 +31,50 @@ def test_block_shapes_of_the_list_kernel(oracle, H, l):
 
 
 @pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
+@pytest.mark.parametrize("H,l,centroids,theta", [(8, 2081, 3, 0.9), (8, 2081, 1, 0.9), (8, 2050, 2, 0.05),
+                                                 (8, 2047, 30, 0.6), (9, 1900, 3, -0.3), (3, 2500, 4, 0.8)])
+def test_more_column_tiles_than_a_batch_holds(oracle, dtype, H, l, centroids, theta):
+    # bits of more than 32 column tiles (64 where a block has one row tile) wait in memory: as words where few half
+    # tiles hold neighbours, as bits where nearly all do, next to row tiles that do not exist; from 1024 row
+    # tiles on a block has four of them
+    L = wl.small_random(68, dtype, B=1, H=H, l=l, lw=1, cap=l, n_centroids=centroids, noise_frac=0.2)
+    L.theta_k = L.theta_v = theta
+    parity.check_shallow_layer(oracle, L, units=[(0, 0), (0, H - 1)])
+    parity.check_shallow_layer(oracle, L, units=[(0, H // 2)], debug=False, cap=37)
+
+
+@pytest.mark.parametrize("dtype,theta,sizes", [("f16", 0.9, (9000, 7000, 600)), ("f32", 0.45, (8,) * 2110), ("bf16", 0.5, (16900,)),
+                                               ("f16", 0.5, (6000,) + (7,) * 1600)])
+def test_rows_of_more_than_512_column_tiles(dtype, theta, sizes):
+    # clusters far from each other: every token's neighbours are its cluster, so degrees, entries (by size, then by
+    # first token) and references are known without computing a cosine
+    rng = np.random.default_rng(69)
+    which = rng.permutation(np.repeat(np.arange(len(sizes)), sizes))
+    centres = rng.standard_normal((len(sizes), 128))
+    x = centres[which] * rng.uniform(0.5, 2.0, (len(which), 1)) + 0.02 * rng.standard_normal((len(which), 128))
+    unit = centres / np.linalg.norm(centres, axis=1, keepdims=True)
+    apart = unit @ unit.T - 2.0 * np.eye(len(sizes))
+    for i, j in np.argwhere(apart > theta - 0.08):            # (1600 random centres: a few pairs may be too close)
+        if i < j:
+            x[which == j] = np.nan
+    lost = np.isnan(x[:, 0])
+    x, which = x[~lost], which[~lost]
+    l = len(which)
+    K = wl.cast(x[None, None], dtype)
+    L = wl.Layer(dtype, K, K.copy(), np.zeros_like(K[:, :, :1]), 1, 1, 1, l, l)
+    L.theta_k = L.theta_v = theta
+    g = parity.gpu_shallow(L, tensors=("k",))
+    names, first, inverse, count = np.unique(which, return_index=True, return_inverse=True, return_counts=True)
+    assert l > 16384 and np.array_equal(g["deg_k"][0, 0], count[inverse])
+    order = np.lexsort((first, -count))
+    rank = np.empty(len(names), np.int64)
+    rank[order] = np.arange(len(names))
+    assert g["n_found_k"][0, 0] == len(names) and np.array_equal(g["ref_k"][0, 0], rank[inverse])
+    adj = np.unpackbits(g["adj_k"][0, 0, :64].view(np.uint8), axis=1, bitorder="little")[:, :l]
+    assert np.array_equal(adj, (which[:64, None] == which[None]).astype(np.uint8))
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
 def test_dense_rows_and_low_thresholds(oracle, dtype):
     # nearly everything adjacent: more words per row than the lists hold, so they are kept as bits;
     # with a threshold near zero every tile counts and nothing is sorted
