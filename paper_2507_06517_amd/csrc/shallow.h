@@ -8,6 +8,7 @@
 //                   the tokens of a problem sorted so that similar ones stand together
 //   shallow_scan    sketch products of all pairs of 32-token tiles on the int8 matrix cores:
 //                   which tiles can hold a pair above theta at all
+//   shallow_refine  where the sketches exclude little, the same from the fp16 unit vectors
 //   shallow_rows    for those tiles the cosines themselves (Eq. 4, 9), decided exactly; degrees
 //                   (Eq. 10) and neighbour lists
 //   merge_onehop, merge_twohop, merge_update
@@ -55,15 +56,28 @@ constexpr int kTile = 32;                        // tokens per tile of the sorte
 constexpr int kTileBytes = kTile * kSketchBytes;   // sketches of a tile, in matrix-core fragment order
 constexpr int kScanPanel = 16;                   // row tiles of a block of shallow_scan
 constexpr int kScanStage = 8;                    // column tiles it stages at a time
+constexpr int kScanRun = 16;                     // stages of a block at most
 constexpr uint32_t kSketchUnknown = 1u << 20;    // error of a token whose sketch says nothing
 constexpr int kPivots = 1024;                    // at most, and one per 16 tokens
 constexpr int kOrderTokens = 512;                // tokens per block of shallow_pivots and shallow_order
-// Shorter problems, and thresholds so low that sketches exclude few pairs, skip the order and the
-// scan: shallow_rows then takes every tile.  (Order and scan are four launches, 50 us at 16 problems of
-// 4096 tokens; every tile of 2048 tokens is about 35 us of matrix instructions there.  A sketch product
-// of unrelated tokens is about 0.53 with a spread of 0.06.)
-constexpr int kScanMinTokens = 2048;
-constexpr float kScanMinTheta = 0.7f;
+// Problems of 2048 tokens and more are sorted and scanned, shorter ones only where there are many: what the launches
+// take, about 45 us, has to come back from shallow_rows, which then needn't take every tile.  Clusters and
+// isolated tokens, without and with: 16 problems of 1280 124, 142 and 107, 151 us, of 1536 135, 152 and 111, 152; 64 of
+// 1024 119, 136 and 120, 150, of 1280 203, 231 and 143, 185; 256 of 1024 294, 332 and 225, 296.
+inline int scan_pays(int UT, int n) {
+  const long T = (n + 31) / 32;
+  return n >= 2048 || (n >= 1024 && UT * T * (T - 24) >= 18000);
+}
+// Below kSketchMinTheta the sketches are not asked: a sketch product of unrelated tokens is about 0.53 with a
+// spread of 0.06, so the largest of a pair of tiles is above 0.7 nearly always.  Below kVectorMinTheta the unit
+// vectors are not asked either: at 0.3 a third of the pairs of tiles of unrelated tokens hold a cosine above it, three
+// quarters for four row tiles together, and what is left out of shallow_rows is what finding it takes.
+constexpr float kSketchMinTheta = 0.7f, kVectorMinTheta = 0.3f;
+enum { kByNone, kByVector, kBySketch };
+// Column tiles a scan block may mark before the unit vectors decide instead, counted once for the four row tiles
+// that shallow_rows takes together: all pairs from the unit vectors cost a fifth of what shallow_rows takes
+// for all of them (16 problems of 32768 tokens: 1.8 and 9.9 ms).
+constexpr float kRefineShare = 0.22f;
 
 constexpr int kCounters = 32;     // ints per ut
 // (slots 6..15 hold the phase timings of shallow_merge)
@@ -92,6 +106,9 @@ struct ShallowParams {
   uint32_t *tpairs;        // [UT][T][TW] bit t of row r: tiles r and t may hold a pair above theta
   int T, Tp, TW;           // tiles, rounded up to whole panels; words per row of tpairs
   int scan;                // 1: tokens are sorted and tpairs says which tiles count; 0: all tiles, positions = tokens
+  int stages_per_item, njg;   // column stages of a block of the scan, runs of them in a problem
+  uint32_t *todo;          // [scan_blocks] 1: left to shallow_refine
+  int by[2];               // which tile pairs count: kBySketch, kByVector or, all of them, kByNone
   int scan_thr[2];         // theta in sketch units squared
   _Float16 *Xl;            // [UT][n][128] fp32 inputs: what fp16 rounding took off the unit vectors, x 2^11
   // Neighbours of a position, 16 positions at a time: words (half tile << 16 | one bit per position of
@@ -177,6 +194,9 @@ __device__ inline double cos64(const ShallowParams &p, int ut, int a, int b) {  
   if (!(den > 0.0)) return 0.0;
   return dot64<DT, kBatch>(x_row(p, ut, a), x_row(p, ut, b)) / den;
 }
+
+// Blocks of shallow_scan, a multiple of 8.
+inline int scan_blocks(const ShallowParams &p) { return 8 * (p.Tp / kScanPanel) * ((p.UT * p.njg + 7) / 8); }
 
 // Entries per cut token and lane group that shallow_assign hands to the exact comparison.
 constexpr int kCandCap = 8;

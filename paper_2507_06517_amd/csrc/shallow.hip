@@ -38,6 +38,13 @@ size_t carve(ShallowParams &p, void *ws, int UT, int n) {
   p.T = tiles_of(n);
   p.Tp = padded_tiles_of(n);
   p.TW = (p.T + 31) / 32;
+  p.UT = UT;
+  // stages per block of the scan: about 2048 blocks, so that short problems fill the chip too (the longest last
+  // about 15 us)
+  const int nI = p.Tp / kScanPanel, nS = p.Tp / kScanStage;
+  const long work = (long)UT * nI * (nI + 1) / 2048;
+  p.stages_per_item = work < 1 ? 1 : (work > kScanRun ? kScanRun : (int)work);
+  p.njg = (nS + p.stages_per_item - 1) / p.stages_per_item;
   p.Xh = cv.take<_Float16>((N + 512) * kHeadDim);   // the similarity loop stages up to 5 tiles past the last token
   p.Xl = p.dtype == SPINDLE_F32 ? cv.take<_Float16>(N * kHeadDim) : nullptr;
   p.m64 = cv.take<double>(N);
@@ -54,6 +61,7 @@ size_t carve(ShallowParams &p, void *ws, int UT, int n) {
   p.first = cv.take<int>((size_t)UT * kPivots);
   p.hist = cv.take<uint16_t>((size_t)UT * ((n + kOrderTokens - 1) / kOrderTokens) * kPivots);
   p.sk = cv.take<int8_t>((size_t)UT * p.Tp * kTileBytes);
+  p.todo = cv.take<uint32_t>(scan_blocks(p));
   p.alive = cv.take<int>(N);
   p.n16 = (n + 15) & ~15;
   for (int r = 0; r < 3; ++r) p.live[r] = cv.take<uint32_t>((size_t)UT * p.T);
@@ -177,11 +185,10 @@ spindle_status run_shallow(int phases,
   }
   // (a sketch product is never below the cosine minus its error, so a pair above theta is never lost;
   // the slack covers the fp32 arithmetic that makes the sketches)
-  p.scan = n >= kScanMinTokens;
-  for (int i = 0; i < T; ++i)
-    if (p.theta[i] < kScanMinTheta) p.scan = 0;
-  for (int i = 0; p.scan && i < T; ++i) {
-    const double thr = ((double)p.theta[i] - 1e-4) * kSketchScale * kSketchScale;
+  p.scan = scan_pays(p.UT, n);
+  for (int i = 0; i < T; ++i) {
+    p.by[i] = !p.scan || p.theta[i] < kVectorMinTheta ? kByNone : p.theta[i] < kSketchMinTheta ? kByVector : kBySketch;
+    const double thr = p.by[i] == kBySketch ? ((double)p.theta[i] - 1e-4) * kSketchScale * kSketchScale : 0.0;
     p.scan_thr[i] = thr < (double)(1 << 28) ? (int)floor(thr) : 1 << 28;
   }
   if (phases & kPhaseGraph) {

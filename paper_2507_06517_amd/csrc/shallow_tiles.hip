@@ -179,33 +179,77 @@ __global__ __launch_bounds__(kWindowThreads) void shallow_window(ShallowParams p
 }
 
 // ---------------------------------------------------------------- scan
-// A block takes a panel of 16 row tiles (four per wave, their sketches in registers as the matrix
-// columns) against a run of column tiles from its own first tile onwards, staged through LDS eight at
-// a time (fragment order: loads and reads are both linear, no bank conflicts).  Per 32 x 32 pairs two
-// 32x32x32 int8 matrix instructions; all the results are needed for is their maximum, eight
+// Work of shallow_scan and shallow_refine: a panel of 16 row tiles against a run of column tiles from its own
+// first tile onwards.  Blocks are dealt round-robin to the 8 XCDs: an XCD sweeps the panels of one (problem,
+// column group) at a time, the groups rotated by problem so that every XCD sees long and short ones.
+struct ScanItem {
+  int ut, I, s0, s1;                                   // stages of kScanStage column tiles
+};
+
+__device__ __forceinline__ ScanItem scan_item(const ShallowParams &p, int item, int xcd) {
+  const int nI = p.Tp / kScanPanel, nS = p.Tp / kScanStage, pj = item / nI * 8 + xcd, Jg = pj % p.njg;
+  ScanItem w;
+  w.I = item % nI;
+  w.ut = pj / p.njg;
+  w.s0 = (Jg + w.ut) % p.njg * p.stages_per_item;
+  w.s1 = pj < p.UT * p.njg ? min(nS, w.s0 + p.stages_per_item) : 0;
+  w.s0 = max(w.s0, w.I * (kScanPanel / kScanStage));
+  return w;
+}
+
+// A wave's marks, one byte per row tile and stage, into both directions of tpairs.
+template <int kRowTiles>
+__device__ __forceinline__ void put_marks(const ShallowParams &p, int ut, int r0, int s0, int s1, const uint8_t (*marks)[kScanRun]) {
+  static_assert(kScanRun == 16, "a lane per row tile and stage");
+  uint32_t *tp = p.tpairs + (size_t)ut * p.T * p.TW;
+  const int lane = lane_id(), T = p.T;
+  {
+    const int r = lane / kScanRun, s = s0 + lane % kScanRun;
+    if (r < kRowTiles && s < s1 && r0 + r < T) {
+      uint32_t b = marks[r][lane % kScanRun];
+      const int left = T - s * kScanStage;             // tiles that exist
+      if (left < kScanStage) b &= left <= 0 ? 0u : (1u << left) - 1u;
+      if (b) atomicOr(tp + (size_t)(r0 + r) * p.TW + (s >> 2), b << (8 * (s & 3)));
+    }
+  }
+  for (int i = lane; i < (s1 - s0) * kScanStage; i += kWave) {
+    const int ct = s0 * kScanStage + i;
+    uint32_t m = 0;
+#pragma unroll
+    for (int r = 0; r < kRowTiles; ++r)
+      if (r0 + r < T) m |= (uint32_t)(marks[r][i / kScanStage] >> (i % kScanStage) & 1) << r;
+    if (m && ct < T) atomicOr(tp + (size_t)ct * p.TW + (r0 >> 5), m << (r0 & 31));
+  }
+}
+
+// The row tiles' sketches stay in registers as the matrix columns, four tiles per wave; the column tiles are
+// staged through LDS eight at a time (fragment order: loads and reads are both linear, no bank conflicts).  Per
+// 32 x 32 pairs two 32x32x32 int8 matrix instructions; all the results are needed for is their maximum, eight
 // v_max3 per lane, and one comparison for the wave's four tiles.  Tiles that pass are marked in both
-// directions.  16 problems of 32768 tokens: 0.38 ms = 2.9 POP/s, bound by the matrix cores (3.2 POP/s
-// from registers); all cosines in fp16, with the bits packed and records written, took 1.80 ms.
+// directions.  16 problems of 32768 tokens: 0.38 ms = 2.9 POP/s; all cosines in fp16, with the bits packed
+// and records written, took 1.80 ms.
+// A block that finds more than kRefineShare of its column tiles marked (keys with a common component, low
+// thresholds) stops and leaves all of its pairs to shallow_refine.  The panel's own columns don't count, and a
+// run of similar tokens behind them is allowed for: those are true neighbours.
 constexpr int kScanThreads = 256;
 
-__global__ __launch_bounds__(kScanThreads, 2) void shallow_scan(ShallowParams p, int stages_per_item, int njg) {
+__global__ __launch_bounds__(kScanThreads, 2) void shallow_scan(ShallowParams p) {
   __shared__ __attribute__((aligned(1024))) char stage[2][kScanStage * kTileBytes];
-  const int nI = p.Tp / kScanPanel, nS = p.Tp / kScanStage;
-  // blocks are dealt round-robin to the 8 XCDs: an XCD sweeps the panels of one (problem, column group) at a time, the groups
-  // rotated by problem so that every XCD sees long and short ones
-  const int xcd = blockIdx.x & 7, s_ = blockIdx.x >> 3;
-  const int I = s_ % nI, pj = (s_ / nI) * 8 + xcd;
-  if (pj >= p.UT * njg) return;
-  const int ut = pj / njg, Jg = (pj % njg + ut) % njg;
-  int s0 = Jg * stages_per_item, s1 = s0 + stages_per_item;
-  if (s0 < I * (kScanPanel / kScanStage)) s0 = I * (kScanPanel / kScanStage);
-  if (s1 > nS) s1 = nS;
-  if (s0 >= s1) return;
+  __shared__ uint8_t marks[kScanPanel][kScanRun];
+  __shared__ int found[kScanRun];                      // marks of a stage, once for the four row tiles of a wave
+  const int xcd = blockIdx.x & 7;
+  const ScanItem w = scan_item(p, blockIdx.x >> 3, xcd);
+  if (w.s0 >= w.s1 || p.by[w.ut / p.U] != kBySketch) {
+    if (threadIdx.x == 0) p.todo[blockIdx.x] = w.s0 < w.s1 && p.by[w.ut / p.U] == kByVector;
+    return;
+  }
   const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const char *sk = reinterpret_cast<const char *>(p.sk) + (size_t)ut * p.Tp * kTileBytes;
-  const uint32_t *et = p.etile + (size_t)ut * p.Tp;
-  const int r0 = I * kScanPanel + wave * 4;
-  const int thr0 = p.scan_thr[ut / p.U];
+  const char *sk = reinterpret_cast<const char *>(p.sk) + (size_t)w.ut * p.Tp * kTileBytes;
+  const uint32_t *et = p.etile + (size_t)w.ut * p.Tp;
+  const int r0 = w.I * kScanPanel + wave * 4;
+  const int thr0 = p.scan_thr[w.ut / p.U];
+  reinterpret_cast<uint8_t *>(marks)[threadIdx.x] = 0;
+  if (threadIdx.x < kScanRun) found[threadIdx.x] = 0;
   i4v bf[4][2];
   int ethr[4];                                         // theta less the row tile's error
 #pragma unroll
@@ -223,13 +267,24 @@ __global__ __launch_bounds__(kScanThreads, 2) void shallow_scan(ShallowParams p,
       lds_dma16_at(src, (uint32_t)(q * 1024 + lane * 16),
                    stage_lds + (s & 1) * (kScanStage * kTileBytes) + wave * 4096 + q * 1024);
   };
-  dma(s0);
-  for (int s = s0; s < s1; ++s) {
-    const int ecol = (int)et[s * kScanStage + (lane & 7)];
+  constexpr int kPerStage = kScanPanel / 4 * kScanStage;   // column tiles, once per wave
+  const int own = (w.I + 1) * (kScanPanel / kScanStage);   // first stage behind the panel's own columns
+  int all = 0;                                         // marks of the stages from there on
+  bool refine = false;
+  dma(w.s0);
+  for (int s = w.s0;; ++s) {
+    const int ecol = s < w.s1 ? (int)et[s * kScanStage + (lane & 7)] : 0;
     __builtin_amdgcn_s_waitcnt(0x0F70);                // vmcnt(0): this wave's part of stage s has landed
     __syncthreads();                                   // ... and every wave's; the other buffer is free
-    if (s + 1 < s1) dma(s + 1);
+    if (s > w.s0 && s > own) {
+      all += found[s - 1 - w.s0];
+      refine = all > (s - max(own, w.s0)) * (int)(kRefineShare * kPerStage) + 3 * kPerStage / 4;
+      if (refine) break;
+    }
+    if (s == w.s1) break;
+    if (s + 1 < w.s1) dma(s + 1);
     const char *st = stage[s & 1];
+    uint32_t hit[4] = {0, 0, 0, 0};
 #pragma unroll
     for (int t = 0; t < kScanStage; ++t) {
       const i4v a0 = *reinterpret_cast<const i4v *>(st + t * kTileBytes + lane * 16);
@@ -247,17 +302,149 @@ __global__ __launch_bounds__(kScanThreads, 2) void shallow_scan(ShallowParams p,
       }
       const int ec = __builtin_amdgcn_readlane(ecol, t);
       if (__any(max(max(m[0], m[1]), max(m[2], m[3])) > emin - ec)) {
-        const int T = p.T, ct = s * kScanStage + t;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int rt = r0 + r;
-          if (__any(m[r] > ethr[r] - ec) && rt < T && ct < T && lane == 0) {
-            uint32_t *tp = p.tpairs + (size_t)ut * T * p.TW;
-            atomicOr(tp + (size_t)rt * p.TW + (ct >> 5), 1u << (ct & 31));
-            atomicOr(tp + (size_t)ct * p.TW + (rt >> 5), 1u << (rt & 31));
+        for (int r = 0; r < 4; ++r)
+          if (__any(m[r] > ethr[r] - ec)) hit[r] |= 1u << t;
+      }
+    }
+    if (hit[0] | hit[1] | hit[2] | hit[3]) {
+      if (lane == 0) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) marks[wave * 4 + r][s - w.s0] = (uint8_t)hit[r];
+        atomicAdd(&found[s - w.s0], __popc(hit[0] | hit[1] | hit[2] | hit[3]));
+      }
+    }
+  }
+  if (threadIdx.x == 0) p.todo[blockIdx.x] = refine;
+  if (!refine) put_marks<4>(p, w.ut, r0, w.s0, w.s1, marks + wave * 4);
+}
+
+// What shallow_scan left over, from the fp16 unit vectors: a tile pair is marked if one of its cosines can be
+// above theta, kGuard allowed for.  Half of a scan block's panel at a time: two row tiles per wave in
+// registers, the columns gathered into LDS in their order, 64 at a time, two steps ahead of their use; the
+// maxima of a tile are taken while the matrix cores work on the next one.  The blocks stay and deal the work
+// out among them in the scan's order, so that an XCD's blocks share their columns in its L2.
+// 16 problems of 32768 tokens, all pairs: 1.8 ms = 1.2 PFLOP/s; three blocks per compute unit without the overlap 2.05 ms.
+constexpr int kRefineThreads = 256;
+constexpr int kRefineBlocks = 512;                     // two per compute unit
+constexpr int kRefineStages = 3;
+constexpr int kRefineList = 2048;                      // items looked at in one go
+
+__global__ __launch_bounds__(kRefineThreads, 2) void shallow_refine(ShallowParams p, int nitems) {
+  typedef Mma<SPINDLE_F16> M;
+  __shared__ __attribute__((aligned(1024))) char stage[kRefineStages][kStageBytes];
+  __shared__ uint16_t cols[kScanRun * kScanStage * kTile];
+  __shared__ uint8_t marks[kScanPanel / 2][kScanRun];
+  __shared__ uint16_t list[kRefineList];
+  __shared__ int wave_n[kRefineList / kWave];
+  const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), g = lane >> 5, c = lane & 31;
+  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, nslots = gridDim.x >> 3, n = p.n;
+  int soff[M::kSteps];                                 // byte offset of this lane's fragment ks in tile 0 of a stage
+#pragma unroll
+  for (int ks = 0; ks < M::kSteps; ++ks) soff[ks] = c * 256 + (((2 * ks + g) ^ ((c & 7) | ((c & 16) >> 1))) << 4);
+  const uint32_t stage_lds = (uint32_t)(size_t)(__attribute__((address_space(3))) char *)stage;
+  for (int i0 = 0; i0 < nitems; i0 += kRefineList) {
+    // the items left over, every block the same list: so many per run of 64, then their places
+    constexpr int kRuns = kRefineList / kWave / (kRefineThreads / kWave);
+    unsigned long long on[kRuns];
+    if (i0 > 0) __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kRuns; ++k) {
+      const int i = i0 + (k * (kRefineThreads / kWave) + wave) * kWave + lane;
+      on[k] = __ballot(i < nitems && p.todo[(size_t)min(i, nitems - 1) * 8 + xcd] != 0);
+      if (lane == 0) wave_n[k * (kRefineThreads / kWave) + wave] = __popcll(on[k]);
+    }
+    __syncthreads();
+    int total = 0;
+    for (int q = 0; q < kRefineList / kWave; ++q) {
+      const int x = wave_n[q];
+      if (q % (kRefineThreads / kWave) == wave) {
+        const int k = q / (kRefineThreads / kWave);
+        unsigned long long m = 0;
+#pragma unroll
+        for (int j = 0; j < kRuns; ++j) m = j == k ? on[j] : m;
+        if (m >> lane & 1) list[total + __popcll(m & ((1ull << lane) - 1ull))] = (uint16_t)(q * kWave + lane);
+      }
+      total += x;
+    }
+    __syncthreads();
+    for (int at = slot; at < 2 * total; at += nslots) {
+      const ScanItem w = scan_item(p, i0 + list[at >> 1], xcd);
+      const size_t base = (size_t)w.ut * n;
+      const char *Xh = reinterpret_cast<const char *>(p.Xh) + base * 256;
+      const uint16_t *perm = p.perm + base;
+      const uint32_t *et = p.etile + (size_t)w.ut * p.Tp;
+      const int r0 = w.I * kScanPanel + (at & 1) * (kScanPanel / 2) + 2 * wave;
+      const int tile0 = w.s0 * kScanStage, ntiles = (w.s1 - w.s0) * kScanStage, nsteps = ntiles * kTile / kStageCols;
+      const int thr = __float_as_int((p.theta[w.ut / p.U] - kGuard) * (kUnitScale * kUnitScale));
+      __syncthreads();                                 // the item before is done with these
+      for (int i = threadIdx.x; i < ntiles * kTile; i += kRefineThreads) cols[i] = perm[min(tile0 * kTile + i, n - 1)];
+      if (threadIdx.x < sizeof(marks)) reinterpret_cast<uint8_t *>(marks)[threadIdx.x] = 0;
+      M::frag af[2][M::kSteps];
+      bool odd[2];                                     // rows whose unit vectors say nothing,
+#pragma unroll
+      for (int cb = 0; cb < 2; ++cb) {
+        const char *row = Xh + (size_t)perm[min((r0 + cb) * kTile + c, n - 1)] * 256;
+#pragma unroll
+        for (int ks = 0; ks < M::kSteps; ++ks) af[cb][ks] = M::load(row, ks, g);
+        odd[cb] = et[r0 + cb] >= kSketchUnknown;
+      }
+      unsigned long long odd_cols[2];                  // ... and columns, a bit per tile
+#pragma unroll
+      for (int k = 0; k < 2; ++k)
+        odd_cols[k] = __ballot(k * kWave + lane < ntiles && et[tile0 + min(k * kWave + lane, ntiles - 1)] >= kSketchUnknown);
+      __syncthreads();
+      auto dma = [&](int s) __attribute__((always_inline)) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int r = (wave * 4 + q) * 4 + (lane >> 4);
+          lds_dma16_at(Xh, (uint32_t)cols[s * kStageCols + r] * 256u + (((lane & 15) ^ ((r & 7) | ((r & 16) >> 1))) << 4),
+                       stage_lds + (s % kRefineStages) * kStageBytes + (wave * 4 + q) * 1024);
+        }
+      };
+      // results of column tile t; thr is positive: floats order as integers as far as it matters
+      auto look = [&](int t, const f16v &x0, const f16v &x1) __attribute__((always_inline)) {
+        int m0 = __float_as_int(x0[0]), m1 = __float_as_int(x1[0]);
+#pragma unroll
+        for (int v = 1; v < 16; ++v) { m0 = max(m0, __float_as_int(x0[v])); m1 = max(m1, __float_as_int(x1[v])); }
+        const bool oddc = odd_cols[t >> 6] >> (t & 63) & 1;
+        const bool hit0 = oddc | odd[0] | (__any(m0 > thr) != 0), hit1 = oddc | odd[1] | (__any(m1 > thr) != 0);
+        if ((hit0 | hit1) && lane < 2 && (lane ? hit1 : hit0)) marks[2 * wave + lane][t >> 3] |= (uint8_t)(1u << (t & 7));
+      };
+      f16v y0, y1;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) { y0[v] = 0.f; y1[v] = 0.f; }   // (below thr)
+      dma(0);
+      dma(1);                                          // (a stage of the scan is four steps)
+      for (int s = 0; s < nsteps; ++s) {
+        // the wave's loads of step s have landed (those of step s + 1 may be on their way), and behind the barrier
+        // every wave's; the buffer of step s - 1 is free
+        if (s + 1 < nsteps) __builtin_amdgcn_s_waitcnt(0x0F74);
+        else __builtin_amdgcn_s_waitcnt(0x0F70);
+        __syncthreads();
+        if (s + 2 < nsteps) dma(s + 2);
+        const char *st = stage[s % kRefineStages];
+#pragma unroll
+        for (int ct = 0; ct < 2; ++ct) {
+          f16v x0, x1;
+#pragma unroll
+          for (int v = 0; v < 16; ++v) { x0[v] = 0.f; x1[v] = 0.f; }
+          M::frag f[M::kSteps];
+#pragma unroll
+          for (int ks = 0; ks < M::kSteps; ++ks) f[ks] = *reinterpret_cast<const M::frag *>(st + ct * kTile * 256 + soff[ks]);
+          __builtin_amdgcn_sched_barrier(0);           // all reads on their way before the first instruction waits
+#pragma unroll
+          for (int ks = 0; ks < M::kSteps; ++ks) {
+            x0 = M::mma(f[ks], af[0][ks], x0);
+            x1 = M::mma(f[ks], af[1][ks], x1);
           }
+          if (ct > 0 || s > 0) look(2 * s + ct - 1, y0, y1);
+          y0 = x0;
+          y1 = x1;
         }
       }
+      look(2 * nsteps - 1, y0, y1);
+      put_marks<2>(p, w.ut, r0, w.s0, w.s1, marks + 2 * wave);
     }
   }
 }
@@ -411,7 +598,7 @@ __global__ __launch_bounds__(kRowsThreads, 2) void shallow_rows(ShallowParams p,
   }
   // column tiles any row tile of the block is marked for, each with the row tiles it is for
   if (wave == 0) {
-    if (p.scan) {
+    if (p.by[ut / p.U] != kByNone) {
       uint32_t word[kRT], any = 0;                     // lane w: word w of the rows of tpairs
 #pragma unroll
       for (int k = 0; k < kRT; ++k) {
@@ -754,15 +941,11 @@ spindle_status launch_tiles(const ShallowParams &p, hipStream_t st) {
     hipLaunchKernelGGL(shallow_order, dim3(xcd_grid((size_t)p.UT * nblk)), dim3(kPivots), 0, st, p, nblk); }
     { ProfScope ps("shallow_window", st);
     hipLaunchKernelGGL(shallow_window, dim3(xcd_grid((size_t)p.UT * nwin)), dim3(kWindowThreads), 0, st, p, nwin); }
-    // stages per block: about 2048 blocks, so that short problems fill the chip too, at most 16 (a block
-    // then lasts about 15 us)
-    const int nI = p.Tp / kScanPanel, nS = p.Tp / kScanStage;
-    const long work = (long)p.UT * nI * (nI + 1);
-    int per = (int)(work / 2048);
-    per = per < 1 ? 1 : (per > 16 ? 16 : per);
-    const int njg = (nS + per - 1) / per;
+    const int nitems = scan_blocks(p) / 8;
     { ProfScope ps("shallow_scan", st);
-    hipLaunchKernelGGL(shallow_scan, dim3((unsigned)(8 * nI * ((p.UT * njg + 7) / 8))), dim3(kScanThreads), 0, st, p, per, njg); }
+    hipLaunchKernelGGL(shallow_scan, dim3((unsigned)(8 * nitems)), dim3(kScanThreads), 0, st, p); }
+    { ProfScope ps("shallow_refine", st);
+    hipLaunchKernelGGL(shallow_refine, dim3(kRefineBlocks), dim3(kRefineThreads), 0, st, p, nitems); }
   }
   if (p.dtype == SPINDLE_F16) return launch_rows<SPINDLE_F16>(p, st);
   if (p.dtype == SPINDLE_BF16) return launch_rows<SPINDLE_BF16>(p, st);

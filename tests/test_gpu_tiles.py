@@ -125,6 +125,31 @@ def test_rows_that_are_not_finite_have_no_neighbours(oracle, dtype, l):
     assert g["n_codes_k"][0, 0] == o["n_codes"]
 
 
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
+@pytest.mark.parametrize("H,l,common,theta_k,theta_v", [(1, 4600, 0.0, 0.5, 0.97), (1, 4111, 0.5, 0.8, 0.29), (1, 4700, 0.8, 0.95, 0.72),
+                                                        (1, 3600, 0.9, 0.97, 0.9), (1, 4200, 0.3, 0.31, 0.3), (24, 1111, 0.6, 0.6, 0.9),
+                                                        (16, 1300, 0.0, 0.95, 0.2), (6, 1283, 0.8, 0.9, 0.98)])
+def test_tile_pairs_by_sketch_by_vector_and_all(oracle, dtype, H, l, common, theta_k, theta_v):
+    # keys that share a direction (cosines of unrelated ones around `common`) and thresholds on both sides of what
+    # sketches and unit vectors can exclude, another one for K than for V; problems of 1024 tokens and more that are
+    # sorted because there are many; rows whose unit vectors say nothing among them
+    rng = np.random.default_rng(70)
+    which = rng.integers(0, l // 40, (1, H, l))
+    out = []
+    for _ in range(2):
+        centres = np.sqrt(common) * rng.standard_normal(128) + np.sqrt(1 - common) * rng.standard_normal((l // 40, 128))
+        x = centres[which] + 0.1 * rng.standard_normal((1, H, l, 128))
+        x[..., rng.random(l) < 0.2, :] += 0.5 * rng.standard_normal(128)
+        x[:, :, 5] = 0.0
+        x[:, :, [7, l - 3]] *= {"f16": 2.0 ** -18, "bf16": 2.0 ** -70, "f32": 2.0 ** -110}[dtype]
+        x[:, :, [9, l // 2]] *= {"f16": 512.0, "bf16": 2.0 ** 60, "f32": 2.0 ** 108}[dtype]
+        out.append(wl.cast(x, dtype))
+    L = wl.Layer(dtype, out[0], out[1], np.zeros_like(out[0][:, :, :1]), 1, 1, 1, l, l)
+    L.theta_k, L.theta_v = theta_k, theta_v
+    parity.check_shallow_layer(oracle, L, units=[(0, 0), (0, H - 1)])
+    parity.check_shallow_layer(oracle, L, units=[(0, H // 2)], debug=False, cap=l // 50)
+
+
 def test_structured_vectors(oracle):
     # vectors the rotation of the sketch maps to few coordinates (constant, alternating, single ones), scaled
     # copies, opposite ones: sketches of little use, whose errors must widen what is looked at
