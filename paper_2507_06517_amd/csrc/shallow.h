@@ -99,6 +99,7 @@ struct ShallowParams {
   uint8_t *sk0;            // [UT][n][64] sketches by token
   uint32_t *serr;          // [UT][n] distance of the sketch from what it stands for, sketch units squared
   uint16_t *bucket;        // [UT][n] pivot of a token
+  uint32_t *mean;          // [UT][2] first eight coordinates of the pivots' mean
   int *first;              // [UT][kPivots] tokens of lower pivots
   uint16_t *hist;          // [UT][order blocks][kPivots] tokens per bucket in each block of tokens
   int8_t *sk;              // [UT][Tp][kTileBytes] sketches by position

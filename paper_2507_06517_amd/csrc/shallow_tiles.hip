@@ -17,24 +17,37 @@ typedef int i16v __attribute__((ext_vector_type(16)));
 // mostly also when none does and the products are all small.  The steps end at 0.51, 0.70, 0.88: near
 // 0.53, where the products of unrelated tokens lie, a step would gather every second pivot's tokens at
 // the lowest pivots (kStepOffset moves them away from there).
+// Keys that share a direction differ in the rest only, so where the mean of a sample of the pivots is more than
+// kMeanSome of the mean squared length left without it, it is taken off the pivots' coordinates.  Products of unrelated tokens
+// then lie around that of the norms the sketches leave out, with a spread of 0.129 of the length left; the steps
+// are about three times that wide, and one ends 2.7 times it above.  Where the mean is most of the length, more than
+// kMeanMost, the norms vary more than what is left: their four bytes then carry the token's own product with
+// the mean instead.
 constexpr int kStepOffset = 3000;
+constexpr float kStepEnd = 0.345f, kStep = 0.388f, kMeanSome = 0.15f, kMeanMost = 1.9f;
+constexpr int kMeanOf = 128;
 constexpr int kPivotThreads = 256;
 
 __global__ __launch_bounds__(kPivotThreads) void shallow_pivots(ShallowParams p, int npiv, int nblk) {
   __shared__ __attribute__((aligned(16))) char piv[kPivots * kSketchBytes];    // fragment order: tile, half, lane
   __shared__ uint32_t cnt[kPivots];
+  __shared__ __attribute__((aligned(16))) int init[kPivots];                   // what is taken off a pivot's products
+  __shared__ __attribute__((aligned(16))) int sum[kSketchBytes], mean4[kSketchBytes / 4];
+  __shared__ int sum_sq;
   const int item = xcd_item();
   if (item >= p.UT * nblk) return;
   const int ut = item / nblk, blk = item % nblk, n = p.n;
   const uint8_t *sk = p.sk0 + (size_t)ut * n * kSketchBytes;
   const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6, g = lane >> 5, c = lane & 31;
+  auto piv_at = [](int j, int piece) { return (j >> 5) * kTileBytes + (piece >> 1) * 1024 + ((piece & 1) * 32 + (j & 31)) * 16; };
   for (int i = tid; i < npiv * 4; i += kPivotThreads) {
     const int j = i >> 2, piece = i & 3;               // piece = 2 * half + lane group
     const int tok = (int)((long)j * n / npiv);
-    *reinterpret_cast<u4 *>(piv + (j >> 5) * kTileBytes + (piece >> 1) * 1024 + ((piece & 1) * 32 + (j & 31)) * 16) =
-        *reinterpret_cast<const u4 *>(sk + (size_t)tok * kSketchBytes + piece * 16);
+    *reinterpret_cast<u4 *>(piv + piv_at(j, piece)) = *reinterpret_cast<const u4 *>(sk + (size_t)tok * kSketchBytes + piece * 16);
   }
   for (int i = tid; i < kPivots; i += kPivotThreads) cnt[i] = 0;
+  if (tid < kSketchBytes) sum[tid] = 0;
+  if (tid == 0) sum_sq = 0;
   // the wave's 128 tokens: matrix columns = lanes
   i4v bf[4][2];
   int tok[4];
@@ -45,21 +58,103 @@ __global__ __launch_bounds__(kPivotThreads) void shallow_pivots(ShallowParams p,
     bf[r][0] = *reinterpret_cast<const i4v *>(s);
     bf[r][1] = *reinterpret_cast<const i4v *>(s + 32);
   }
+  const int every = max(1, npiv / kMeanOf), nmean = (npiv + every - 1) / every;
+  __syncthreads();
+  {
+    // a thread sums four bytes of every 16th of the sample
+    const int d = tid & 15;
+    int a[4] = {0, 0, 0, 0}, sq = 0;
+#pragma unroll 8
+    for (int j = (tid >> 4) * every; j < npiv; j += 16 * every) {
+      const int x = *reinterpret_cast<const int *>(piv + piv_at(j, d >> 2) + (d & 3) * 4);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) a[k] += __builtin_amdgcn_sbfe(x, 8 * k, 8);
+      const int y = (d & 3) == 3 ? x & 0x00FFFFFF : x;   // (the last bytes are norms)
+      sq = __builtin_amdgcn_sdot4(y, y, sq, false);
+    }
+#pragma unroll
+    for (int o = 32; o >= 16; o >>= 1) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) a[k] += __shfl_xor(a[k], o);
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) sq += __shfl_xor(sq, o);
+    if (lane < 16)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) atomicAdd(&sum[4 * d + k], a[k]);
+    if (lane == 0) atomicAdd(&sum_sq, sq);
+  }
+  __syncthreads();
+  if (tid < kSketchBytes / 4) {
+    uint32_t m = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if ((tid & 3) < 3 || k < 3) m |= ((uint32_t)(int)rintf((float)sum[4 * tid + k] / (float)nmean) & 0xFFu) << (8 * k);
+    mean4[tid] = (int)m;
+  }
+  __syncthreads();
+  int mm = 0;                                          // squared length of the mean
+#pragma unroll
+  for (int d = 0; d < kSketchBytes / 4; ++d) mm = __builtin_amdgcn_sdot4(mean4[d], mean4[d], mm, false);
+  float norms = 0.f;                                   // mean product of the norms
+#pragma unroll
+  for (int d = 15; d < kSketchBytes; d += 16) norms += (float)sum[d] * (float)sum[d] / ((float)nmean * (float)nmean);
+  // (every block of a problem comes to the same figures)
+  const float left = fmaxf((float)sum_sq / (float)nmean - (float)mm, 1.f);
+  const bool some = (float)mm > kMeanSome * left, most = (float)mm > kMeanMost * left;
+  const int bits = some ? min(14, max(10, (int)rintf(log2f(kStep * left)))) : 14, mask = -(1 << bits);
+  const int off = some ? -(int)((most ? 0.f : norms) + kStepEnd * left) : kStepOffset;
+  for (int j = tid; j < npiv; j += kPivotThreads) {
+    int x = off;
+#pragma unroll
+    for (int piece = 0; some && piece < 4; ++piece) {
+      const i4v v = *reinterpret_cast<const i4v *>(piv + piv_at(j, piece));
+      const i4v m = *reinterpret_cast<const i4v *>(mean4 + 4 * piece);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) x -= __builtin_amdgcn_sdot4(v[k], m[k], 0, false);
+    }
+    init[j] = x;
+    if (most)
+#pragma unroll
+      for (int piece = 0; piece < 4; ++piece) piv[piv_at(j, piece) + 15] = 127;
+  }
+  if (blk == 0 && tid < 2) p.mean[2 * ut + tid] = some ? (uint32_t)mean4[tid] : 0u;
+  if (most) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      int x = 0;                                       // (a lane has pieces g and g + 2 of the four)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const i4v m = *reinterpret_cast<const i4v *>(mean4 + 4 * (2 * h + g));
+#pragma unroll
+        for (int k = 0; k < 4; ++k) x = __builtin_amdgcn_sdot4(bf[r][h][k], m[k], x, false);
+      }
+      x += __shfl_xor(x, 32);
+      const int q = min(508, max(-508, (int)rintf((float)(mm - x) * (1.f / 127.f))));   // dealt out to the four
+      bf[r][0][3] = (bf[r][0][3] & 0x00FFFFFF) | ((q + g) >> 2) << 24;
+      bf[r][1][3] = (bf[r][1][3] & 0x00FFFFFF) | ((q + 2 + g) >> 2) << 24;
+    }
+  }
   __syncthreads();
   int best[4] = {INT32_MIN, INT32_MIN, INT32_MIN, INT32_MIN};
   for (int pt = 0; pt < npiv / 32; ++pt) {
     const i4v a0 = *reinterpret_cast<const i4v *>(piv + pt * kTileBytes + lane * 16);
     const i4v a1 = *reinterpret_cast<const i4v *>(piv + pt * kTileBytes + 1024 + lane * 16);
+    i16v off4;
+#pragma unroll
+    for (int v = 0; v < 16; v += 4) {
+      const i4v x = *reinterpret_cast<const i4v *>(init + pt * 32 + mma_row(v, g));
+#pragma unroll
+      for (int k = 0; k < 4; ++k) off4[v + k] = x[k];
+    }
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      i16v acc;
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[v] = kStepOffset;
+      i16v acc = off4;
       acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(a0, bf[r][0], acc, 0, 0, 0);
       acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(a1, bf[r][1], acc, 0, 0, 0);
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
-        const int x = (acc[v] & ~16383) | (kPivots - 1 - (pt * 32 + mma_row(v, g)));
+        const int x = (acc[v] & mask) | (kPivots - 1 - (pt * 32 + mma_row(v, g)));
         best[r] = x > best[r] ? x : best[r];
       }
     }
@@ -67,7 +162,7 @@ __global__ __launch_bounds__(kPivotThreads) void shallow_pivots(ShallowParams p,
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     const int o = __shfl_xor(best[r], 32);
-    const int b = kPivots - 1 - ((o > best[r] ? o : best[r]) & 16383);
+    const int b = kPivots - 1 - ((o > best[r] ? o : best[r]) & (kPivots - 1));
     if (g == 0 && tok[r] < n) {
       p.bucket[(size_t)ut * n + tok[r]] = (uint16_t)b;
       atomicAdd(&cnt[b], 1u);
@@ -113,7 +208,7 @@ __global__ __launch_bounds__(kPivots) void shallow_order(ShallowParams p, int nb
 }
 
 // A window of 2048 places in that order: the tokens of each pivot sorted by eight signs of their
-// sketches (a token counts the ones of its pivot that go before it), which keeps together what has no
+// sketches less the mean (a token counts the ones of its pivot that go before it), which keeps together what has no
 // pivot of its own.  Then everything later kernels read by position.  Sketches go to fragment order:
 // tile, half of the 64 bytes, lane.
 constexpr int kWindow = 2048;
@@ -127,6 +222,7 @@ __global__ __launch_bounds__(kWindowThreads) void shallow_window(ShallowParams p
   const int ut = item / nwin, n = p.n, w0 = (item % nwin) * kWindow, w1 = min(n, w0 + kWindow);
   const size_t base = (size_t)ut * n;
   const int tid = threadIdx.x;
+  const uint2 mean = reinterpret_cast<const uint2 *>(p.mean)[ut];
   int tok[2], lo[2], hi[2];
 #pragma unroll
   for (int k = 0; k < 2; ++k) {
@@ -139,7 +235,10 @@ __global__ __launch_bounds__(kWindowThreads) void shallow_window(ShallowParams p
       lo[k] = max(first[0], w0) - w0;
       hi[k] = min(b + 1 < kPivots ? first[1] : n, w1) - w0;
       const uint2 s = *reinterpret_cast<const uint2 *>(p.sk0 + (base + tok[k]) * kSketchBytes);
-      const uint32_t signs = ((s.x >> 7 & 0x01010101u) * 0x10204080u >> 28) | ((s.y >> 7 & 0x01010101u) * 0x10204080u >> 28 << 4);
+      uint32_t signs = 0;
+#pragma unroll
+      for (int d = 0; d < 8; ++d)
+        signs |= (uint32_t)((int8_t)((d < 4 ? s.x : s.y) >> 8 * (d & 3)) < (int8_t)((d < 4 ? mean.x : mean.y) >> 8 * (d & 3))) << d;
       order_by[i] = signs << 16 | (uint32_t)i;
     }
   }
