@@ -51,6 +51,22 @@ __device__ __forceinline__ uint32_t word_at(const Row &r, int i) {
   return r.dense ? ((uint32_t)i << 16) | reinterpret_cast<const uint16_t *>(r.w)[i] : r.w[i];
 }
 
+// f(word) for words i, i + 8, ... of a row that have bits, four loads in flight.
+template <typename F>
+__device__ __forceinline__ void for_words(const Row &r, int i, F f) {
+  for (; i < r.n; i += 4 * kSegW) {
+    uint32_t x[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int k = i + j * kSegW;
+      x[j] = k >= r.n ? 0u : r.dense ? reinterpret_cast<const uint16_t *>(r.w)[k] : r.w[k];
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (x[j] & 0xFFFFu) f(r.dense ? (uint32_t)(i + j * kSegW) << 16 | x[j] : x[j]);
+  }
+}
+
 // Largest of the 16 values of the half tile that the bits select (and m).
 __device__ __forceinline__ uint32_t masked_max(const uint32_t *a, uint32_t word, uint32_t m) {
   const u4 *q = reinterpret_cast<const u4 *>(a + (word >> 16) * 16);
@@ -69,6 +85,19 @@ __device__ __forceinline__ uint32_t masked_max(const uint32_t *a, uint32_t word,
 // The bits of `word` that are set in the bit array `live` (one bit per position).
 __device__ __forceinline__ uint32_t still(const uint32_t *live, uint32_t word) {
   return word & 0xFFFFu & (live[word >> 17] >> ((word >> 12) & 16));
+}
+
+// Largest of the values in LDS that the bits `rem` of the word select (and m).  One at a time where no lane of the wave
+// has more than a few: a late round of a dense graph, or neighbours all over the sequence (16 problems of 8192
+// tokens with a tenth of all pairs adjacent: the remaining rounds 13.7 -> 10.7 ms together with four loads in flight per row).
+__device__ __forceinline__ uint32_t selected_max(const uint32_t *a, uint32_t word, uint32_t rem, uint32_t m) {
+  if (__any(__popc(rem) > 4)) return masked_max(a, (word & 0xFFFF0000u) | rem, m);
+  const uint32_t *q = a + (word >> 16) * 16;
+  for (; rem; rem &= rem - 1) {
+    const uint32_t y = q[__builtin_ctz(rem)];
+    m = y > m ? y : m;
+  }
+  return m;
 }
 
 // Lane exchanges inside an 8-lane segment by DPP (no LDS round trip): the two quad
@@ -135,10 +164,7 @@ __global__ __launch_bounds__(kPhaseThreads) void merge_onehop(ShallowParams p, i
   for (int k = 0; k < 4; ++k) {
     uint32_t m = own[k];                              // a token is its own neighbour
     if (w0[k] & 0xFFFFu) m = masked_max(key, w0[k], m);
-    for (int i = sl + kSegW; on[k] && i < r[k].n; i += kSegW) {
-      const uint32_t w = word_at(r[k], i);
-      if (w & 0xFFFFu) m = masked_max(key, w, m);
-    }
+    if (on[k]) for_words(r[k], sl + kSegW, [&](uint32_t w) { m = masked_max(key, w, m); });
     m = seg_max(m);
     if (on[k] && sl == 0) m1[W * kTile + 8 * k + seg] = m;
     bits |= seg_bits(on[k] && m == own[k]) << (8 * k);
@@ -169,11 +195,11 @@ __global__ __launch_bounds__(kPhaseThreads) void merge_twohop(ShallowParams p, i
     const Row r = row_at(p, base, lists, u);
     const uint32_t ku = key[u];
     uint32_t m = 0;
-    for (int i = sl; on && i < r.n; i += kSegW) {
-      const uint32_t w = word_at(r, i);
-      const uint32_t rem = still(live, w);            // neighbours still there at the start of the round
-      if (rem) m = masked_max(m1, (w & 0xFFFF0000u) | rem, m);
-    }
+    if (on)
+      for_words(r, sl, [&](uint32_t w) {
+        const uint32_t rem = still(live, w);          // neighbours still there at the start of the round
+        if (rem) m = masked_max(m1, (w & 0xFFFF0000u) | rem, m);
+      });
     const bool pick = on && seg_max(m) == ku;
     bits |= seg_bits(pick) << (8 * k);
     if (pick) {
@@ -222,7 +248,7 @@ __global__ __launch_bounds__(kPhaseThreads) void merge_update(ShallowParams p, i
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
     int c = __popc(still(next, w0[k]));
-    for (int i = sl + kSegW; on[k] && i < r[k].n; i += kSegW) c += __popc(still(next, word_at(r[k], i)));
+    if (on[k]) for_words(r[k], sl + kSegW, [&](uint32_t w) { c += __popc(still(next, w)); });
     c = seg_sum(c);
     if (on[k] && sl == 0) key[8 * k + seg] = ((uint32_t)c << 16) | (own[k] & 0xFFFFu);
   }
@@ -257,10 +283,11 @@ __device__ __forceinline__ void tail_onehop(const ShallowParams &p, size_t base,
     for (int k = 0; k < 4; ++k) {
       const uint32_t own = on[k] ? w.key[vv[k]] : 0;
       uint32_t m = own;
-      for (int i = w.sl; on[k] && i < r[k].n; i += kSegW) {
-        const uint32_t x = word_at(r[k], i);
-        if (x & 0xFFFFu) m = masked_max(w.key, x, m);
-      }
+      if (on[k])
+        for_words(r[k], w.sl, [&](uint32_t x) {
+          const uint32_t rem = still(w.live, x);
+          if (rem) m = selected_max(w.key, x, rem, m);
+        });
       m = seg_max(m);
       if (on[k] && w.sl == 0) {
         m1[vv[k]] = m;
@@ -279,11 +306,10 @@ __device__ __forceinline__ void tail_twohop(const ShallowParams &p, int ut, size
     const Row r = row_at(p, base, w.lists, u);
     const uint32_t ku = w.key[u];
     uint32_t m = 0;
-    for (int i = w.sl; i < r.n; i += kSegW) {
-      const uint32_t x = word_at(r, i);
+    for_words(r, w.sl, [&](uint32_t x) {
       const uint32_t rem = still(w.live, x);
-      if (rem) m = masked_max(m1, (x & 0xFFFF0000u) | rem, m);
-    }
+      if (rem) m = selected_max(m1, x, rem, m);
+    });
     if (seg_max(m) != ku) continue;
     if (w.sl == 0) {
       p.pick_key[base + u] = ku;
@@ -403,18 +429,17 @@ __global__ __launch_bounds__(kMergeThreads) void shallow_merge(ShallowParams p) 
     if (ndying <= nleft) {
       for (int i0 = w.seg; i0 < ndying; i0 += kTailSegs) {
         const Row r = row_at(p, base, w.lists, dying[i0]);
-        for (int i = w.sl; i < r.n; i += kSegW) {
-          const uint32_t x = word_at(r, i);
+        for_words(r, w.sl, [&](uint32_t x) {
           for (uint32_t rem = still(w.next, x); rem; rem &= rem - 1)
             atomicSub(&w.key[(x >> 16) * 16 + __builtin_ctz(rem)], 1u << 16);
-        }
+        });
       }
     } else {
       for (int i0 = w.seg; i0 < nleft; i0 += kTailSegs) {
         const int v = alive[i0];
         const Row r = row_at(p, base, w.lists, v);
         int c = 0;
-        for (int i = w.sl; i < r.n; i += kSegW) c += __popc(still(w.next, word_at(r, i)));
+        for_words(r, w.sl, [&](uint32_t x) { c += __popc(still(w.next, x)); });
         c = seg_sum(c);
         if (w.sl == 0) w.key[v] = ((uint32_t)c << 16) | (w.key[v] & 0xFFFFu);
       }
