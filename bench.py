@@ -325,9 +325,9 @@ def main():
         step()
     drain()
     wall = time.perf_counter() - t0
-    scan_recs = [ms for name, ms in sb.spindle_profile_read() if name == "shallow_scan"]
-    assert len(scan_recs) == args.steps
-    scan_ms = float(np.mean(scan_recs))
+    pair_recs = sb.spindle_profile_read()            # one per step; short prompts are not scanned, their kernel takes all pairs
+    assert len(pair_recs) == args.steps and len({name for name, _ in pair_recs}) == 1
+    pair_kernel, pair_ms = pair_recs[0][0], float(np.mean([ms for _, ms in pair_recs]))
     ms_step = wall * 1e3 / args.steps
 
     # for reference (not the reported throughput): the same steps one at a time, two streams within a step
@@ -373,9 +373,11 @@ def main():
     tokens = L.batch * L.seq_len
     units = L.batch * L.n_kv_heads
     # the kernel that goes over all pairs of tokens: each unordered pair once, one product of
-    # two 64-byte sketches: n^2/2 pairs x 64 multiply-adds x 2, per (unit, K|V).
-    scan_ops = 2 * units * (L.seq_len ** 2 / 2) * SKETCH_DIMS * 2
-    achieved = scan_ops / (scan_ms * 1e-3) / 1e12
+    # two 64-byte sketches (short prompts: of two tokens): n^2/2 pairs x 64 (128) multiply-adds x 2, per (unit, K|V).
+    scanned = pair_kernel == "shallow_scan"
+    pair_ops = 2 * units * (L.seq_len ** 2 / 2) * (SKETCH_DIMS if scanned else L.head_dim) * 2
+    achieved = pair_ops / (pair_ms * 1e-3) / 1e12
+    pair_peak = PEAK_MFMA_I8_TOPS if scanned else PEAK_MFMA_F16_TFLOPS
     # what computing every cosine in fp16 would take (the calibration loop below does)
     gram_flop = 2 * units * (L.seq_len ** 2 / 2) * L.head_dim * 2
     out = {
@@ -411,8 +413,9 @@ def main():
         "codebook_entries_found": n_codes,
         "merge_rounds": st[:, 0].tolist(), "pairs_decided_in_f64": int(st[:, 2].sum()),
         "merge_phase_us_unit0": st[0, 4:14].tolist(),
-        "roofline": {"kernel": "shallow_scan", "bound": "mfma int8", "kernel_ms": scan_ms, "achieved": achieved,
-                     "peak": PEAK_MFMA_I8_TOPS, "unit": "TOP/s", "frac": achieved / PEAK_MFMA_I8_TOPS},
+        "roofline": {"kernel": pair_kernel, "bound": "mfma int8" if scanned else "mfma fp16", "kernel_ms": pair_ms,
+                     "achieved": achieved, "peak": pair_peak, "unit": "TOP/s" if scanned else "TFLOP/s",
+                     "frac": achieved / pair_peak},
     }
     # what the part sustains (measurement aids of the library): a register-resident fp16 MFMA loop, and
     # a loop over all pairs that does nothing with the results

@@ -257,7 +257,7 @@ def decode_merge(X_new, dtype, theta, Cb, n_codes):
 
 
 def spindle_profile(mode) -> None:
-    """0/False: off; 1/True: HIP events around every kernel; 2: around shallow_scan only."""
+    """0/False: off; 1/True: HIP events around every kernel; 2: around the kernel of a codebook call that goes over all pairs."""
     _check(lib().spindle_profile(int(mode)))
 
 

@@ -49,7 +49,7 @@ __host__ __device__ inline size_t kv_unit_offset(const KvLayout &L, int unit) {
 struct ProfScope {
   int idx;
   hipStream_t st;
-  ProfScope(const char *name, hipStream_t s);
+  ProfScope(const char *name, hipStream_t s, bool pairs = false);   // pairs: the one kernel of a call that mode 2 records
   ~ProfScope();
 };
 

@@ -63,7 +63,7 @@ struct ProfRec {
 };
 static std::mutex g_prof_mu;
 static std::vector<ProfRec> g_prof;
-static int g_prof_mode = 0;             // 0 off, 1 every kernel, 2 only shallow_scan
+static int g_prof_mode = 0;             // 0 off, 1 every kernel, 2 only the one that goes over all pairs of tokens
 
 static void prof_clear() {
   for (ProfRec &r : g_prof) {
@@ -73,9 +73,9 @@ static void prof_clear() {
   g_prof.clear();
 }
 
-ProfScope::ProfScope(const char *name, hipStream_t s) : idx(-1), st(s) {
+ProfScope::ProfScope(const char *name, hipStream_t s, bool pairs) : idx(-1), st(s) {
   if (g_prof_mode == 0) return;
-  if (g_prof_mode == 2 && strcmp(name, "shallow_scan") != 0) return;
+  if (g_prof_mode == 2 && !pairs) return;
   std::lock_guard<std::mutex> lk(g_prof_mu);
   ProfRec r;
   strncpy(r.name, name, sizeof(r.name) - 1);

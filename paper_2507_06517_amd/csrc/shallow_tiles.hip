@@ -1008,13 +1008,16 @@ __global__ __launch_bounds__(256) void shallow_adjacency(ShallowParams p, uint32
 }  // namespace
 
 namespace {
+// How the tile pairs that count are found; of K and V the one that is looked at first.
+int most_by(const ShallowParams &p) { return p.UT > p.U && p.by[1] > p.by[0] ? p.by[1] : p.by[0]; }
+
 template <int DT, int kCols>
 spindle_status launch_rows(const ShallowParams &p, hipStream_t st) {
   constexpr int kRT = 4 / kCols;
   static LdsLimit lim;
   if (spindle_status e = allow_lds(lim, reinterpret_cast<const void *>(&shallow_rows<DT, kCols>), sizeof(RowsLds<DT, kCols>))) return e;
   const int nblk = (p.T + kRT - 1) / kRT;
-  ProfScope ps("shallow_rows", st);
+  ProfScope ps("shallow_rows", st, most_by(p) == kByNone);
   hipLaunchKernelGGL((shallow_rows<DT, kCols>), dim3(xcd_grid((size_t)p.UT * nblk)), dim3(kRowsThreads), sizeof(RowsLds<DT, kCols>),
                      st, p, nblk);
   return SPINDLE_OK;
@@ -1041,9 +1044,9 @@ spindle_status launch_tiles(const ShallowParams &p, hipStream_t st) {
     { ProfScope ps("shallow_window", st);
     hipLaunchKernelGGL(shallow_window, dim3(xcd_grid((size_t)p.UT * nwin)), dim3(kWindowThreads), 0, st, p, nwin); }
     const int nitems = scan_blocks(p) / 8;
-    { ProfScope ps("shallow_scan", st);
+    { ProfScope ps("shallow_scan", st, most_by(p) == kBySketch);
     hipLaunchKernelGGL(shallow_scan, dim3((unsigned)(8 * nitems)), dim3(kScanThreads), 0, st, p); }
-    { ProfScope ps("shallow_refine", st);
+    { ProfScope ps("shallow_refine", st, most_by(p) == kByVector);
     hipLaunchKernelGGL(shallow_refine, dim3(kRefineBlocks), dim3(kRefineThreads), 0, st, p, nitems); }
   }
   if (p.dtype == SPINDLE_F16) return launch_rows<SPINDLE_F16>(p, st);

@@ -150,6 +150,23 @@ def test_tile_pairs_by_sketch_by_vector_and_all(oracle, dtype, H, l, common, the
     parity.check_shallow_layer(oracle, L, units=[(0, H // 2)], debug=False, cap=l // 50)
 
 
+@pytest.mark.parametrize("H,l,theta_k,theta_v,kernel", [(1, 700, 0.98, 0.95, "shallow_rows"), (1, 2100, 0.2, 0.98, "shallow_scan"),
+                                                        (1, 2100, 0.6, 0.2, "shallow_refine"), (1, 2100, 0.2, 0.1, "shallow_rows"),
+                                                        (64, 1500, 0.98, 0.95, "shallow_scan")])
+def test_one_record_per_call_of_the_kernel_over_all_pairs(H, l, theta_k, theta_v, kernel):
+    import torch
+    from paper_2507_06517_amd import binding as sb
+    K = torch.randn(1, H, l, 128, device="cuda", dtype=torch.float16)
+    plan = sb.plan_shallow(K, "f16", theta_k, theta_v, 32)
+    sb.spindle_profile(2)
+    try:
+        plan.run(K, K)
+        plan.run(K, K)
+        assert [name for name, _ in sb.spindle_profile_read()] == [kernel] * 2
+    finally:
+        sb.spindle_profile(0)
+
+
 def test_structured_vectors(oracle):
     # vectors the rotation of the sketch maps to few coordinates (constant, alternating, single ones), scaled
     # copies, opposite ones: sketches of little use, whose errors must widen what is looked at
