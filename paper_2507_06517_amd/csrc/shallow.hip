@@ -7,7 +7,7 @@
 namespace spindle {
 namespace {
 
-// What must hold before the first kernel of a call: counters, list counts and flags zero,
+// What must hold before the first kernel of a call: counters, errors and marks zero,
 // n_codes = -1 ("not finished"), codebooks zero.  One launch for all of it.
 __global__ __launch_bounds__(256) void shallow_init(ShallowParams p, size_t nzero, size_t cwords, int T) {
   const size_t stride = (size_t)gridDim.x * blockDim.x, i0 = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -193,7 +193,7 @@ spindle_status run_shallow(int phases,
     p.scan_thr[i] = thr < (double)(1 << 28) ? (int)floor(thr) : 1 << 28;
   }
   if (phases & kPhaseGraph) {
-    // zero: counters, list counts, error flag, barriers; codebooks
+    // zero: counters, and where there is a scan its errors and marks; codebooks
     const size_t nzero = zero_words(p.UT, n, p.scan);
     const size_t cwords = (size_t)U * max_codes * kHeadDim * dtype_bytes(p.dtype) / 4;
     hipLaunchKernelGGL(shallow_init, dim3(1024), dim3(256), 0, st, p, nzero, cwords, T);

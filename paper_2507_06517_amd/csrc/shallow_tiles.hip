@@ -104,10 +104,10 @@ __global__ __launch_bounds__(kPivotThreads) void shallow_pivots(ShallowParams p,
   const bool some = (float)mm > kMeanSome * left, most = (float)mm > kMeanMost * left;
   const int bits = some ? min(14, max(10, (int)rintf(log2f(kStep * left)))) : 14, mask = -(1 << bits);
   const int off = some ? -(int)((most ? 0.f : norms) + kStepEnd * left) : kStepOffset;
-  for (int j = tid; j < npiv; j += kPivotThreads) {
+  for (int j = tid; some && j < npiv; j += kPivotThreads) {
     int x = off;
 #pragma unroll
-    for (int piece = 0; some && piece < 4; ++piece) {
+    for (int piece = 0; piece < 4; ++piece) {
       const i4v v = *reinterpret_cast<const i4v *>(piv + piv_at(j, piece));
       const i4v m = *reinterpret_cast<const i4v *>(mean4 + 4 * piece);
 #pragma unroll
@@ -137,27 +137,40 @@ __global__ __launch_bounds__(kPivotThreads) void shallow_pivots(ShallowParams p,
   }
   __syncthreads();
   int best[4] = {INT32_MIN, INT32_MIN, INT32_MIN, INT32_MIN};
-  for (int pt = 0; pt < npiv / 32; ++pt) {
-    const i4v a0 = *reinterpret_cast<const i4v *>(piv + pt * kTileBytes + lane * 16);
-    const i4v a1 = *reinterpret_cast<const i4v *>(piv + pt * kTileBytes + 1024 + lane * 16);
-    i16v off4;
+  auto compare = [&](auto first) __attribute__((always_inline)) {   // first(pt): what the products of a pivot tile start at
+    for (int pt = 0; pt < npiv / 32; ++pt) {
+      const i4v a0 = *reinterpret_cast<const i4v *>(piv + pt * kTileBytes + lane * 16);
+      const i4v a1 = *reinterpret_cast<const i4v *>(piv + pt * kTileBytes + 1024 + lane * 16);
+      const i16v off4 = first(pt);
 #pragma unroll
-    for (int v = 0; v < 16; v += 4) {
-      const i4v x = *reinterpret_cast<const i4v *>(init + pt * 32 + mma_row(v, g));
+      for (int r = 0; r < 4; ++r) {
+        i16v acc = off4;
+        acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(a0, bf[r][0], acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(a1, bf[r][1], acc, 0, 0, 0);
 #pragma unroll
-      for (int k = 0; k < 4; ++k) off4[v + k] = x[k];
-    }
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      i16v acc = off4;
-      acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(a0, bf[r][0], acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(a1, bf[r][1], acc, 0, 0, 0);
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int x = (acc[v] & mask) | (kPivots - 1 - (pt * 32 + mma_row(v, g)));
-        best[r] = x > best[r] ? x : best[r];
+        for (int v = 0; v < 16; ++v) {
+          const int x = (acc[v] & mask) | (kPivots - 1 - (pt * 32 + mma_row(v, g)));
+          best[r] = x > best[r] ? x : best[r];
+        }
       }
     }
+  };
+  if (some) {
+    compare([&](int pt) {
+      i16v x16;
+#pragma unroll
+      for (int v = 0; v < 16; v += 4) {
+        const i4v x = *reinterpret_cast<const i4v *>(init + pt * 32 + mma_row(v, g));
+#pragma unroll
+        for (int k = 0; k < 4; ++k) x16[v + k] = x[k];
+      }
+      return x16;
+    });
+  } else {
+    i16v x16;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) x16[v] = off;
+    compare([&](int) { return x16; });
   }
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
@@ -445,15 +458,16 @@ __global__ __launch_bounds__(kRefineThreads, 2) void shallow_refine(ShallowParam
   for (int i0 = 0; i0 < nitems; i0 += kRefineList) {
     // the items left over, every block the same list: so many per run of 64, then their places
     constexpr int kRuns = kRefineList / kWave / (kRefineThreads / kWave);
-    unsigned long long on[kRuns];
+    unsigned long long on[kRuns], any = 0;
     if (i0 > 0) __syncthreads();
 #pragma unroll
     for (int k = 0; k < kRuns; ++k) {
       const int i = i0 + (k * (kRefineThreads / kWave) + wave) * kWave + lane;
       on[k] = __ballot(i < nitems && p.todo[(size_t)min(i, nitems - 1) * 8 + xcd] != 0);
       if (lane == 0) wave_n[k * (kRefineThreads / kWave) + wave] = __popcll(on[k]);
+      any |= on[k];
     }
-    __syncthreads();
+    if (!__syncthreads_or(any != 0)) continue;         // the ordinary case
     int total = 0;
     for (int q = 0; q < kRefineList / kWave; ++q) {
       const int x = wave_n[q];
@@ -580,9 +594,8 @@ struct RowsLds {
   float inv[kBatch * kCols][kTile];
   uint16_t tok[kBatch * kCols][kTile];
   uint16_t bits[4][kBatch * kRowsPitch];
-  uint16_t queue[4][kRowsQueue];
+  __attribute__((aligned(4))) uint16_t queue[4][kRowsQueue];                                         // at the end: degree << 16 | words of every lane
   uint16_t tiles[2048];                                                  // column tile | 1 << (11 + row tile of the block)
-  int deg[4][kWave], words[4][kWave];
   int ntiles;
 };
 
@@ -926,16 +939,19 @@ __global__ __launch_bounds__(kRowsThreads, 2) void shallow_rows(ShallowParams p,
     deg += __popc(m);
     words += m != 0;
   }
-  l.deg[wave][lane] = deg;
-  l.words[wave][lane] = words;
+  static_assert(kRowsQueue * sizeof(uint16_t) >= kWave * sizeof(uint32_t), "the counts take the queue's place");
+  auto counts = [&](int w) { return reinterpret_cast<uint32_t *>(l.queue[w]); };
+  asm volatile("" ::: "memory");                       // (read as halves before)
+  counts(wave)[lane] = (uint32_t)deg << 16 | (uint32_t)words;
   __syncthreads();
   // a row's words: those of lane group 0 of every wave of its row tile, then those of group 1
   int total = 0, d = 0, at = 0;
 #pragma unroll
   for (int q = 0; q < kCols; ++q) {
     const int w = rt * kCols + q;
-    const int x0 = l.words[w][c], x1 = l.words[w][32 + c];
-    d += l.deg[w][c] + l.deg[w][32 + c];
+    const uint32_t n0 = counts(w)[c], n1 = counts(w)[32 + c];
+    const int x0 = (int)(n0 & 0xFFFFu), x1 = (int)(n1 & 0xFFFFu);
+    d += (int)(n0 >> 16) + (int)(n1 >> 16);
     total += x0 + x1;
     at += g == 0 ? (q < member ? x0 : 0) : x0 + (q < member ? x1 : 0);
   }
