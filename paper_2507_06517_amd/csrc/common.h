@@ -137,9 +137,4 @@ __device__ __forceinline__ void lds_dma16_at(const void *wave_base, uint32_t lan
                : "memory", "m0");
 }
 
-// Spread the four nibbles of a 16-bit value to bits [8k, 8k+4) of a 32-bit word.
-__device__ __forceinline__ uint32_t spread_nibbles(uint32_t p) {
-  return (p & 0xFu) | ((p & 0xF0u) << 4) | ((p & 0xF00u) << 8) | ((p & 0xF000u) << 12);
-}
-
 }  // namespace spindle

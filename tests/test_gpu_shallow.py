@@ -26,18 +26,16 @@ def test_small_ragged(oracle, dtype, l):
 
 @pytest.mark.parametrize("l,n_centroids", [(1100, 6), (2500, 6), (2500, 40), (3300, 64)])
 def test_without_adjacency_export(oracle, l, n_centroids):
-    # no adjacency output requested: the lower triangle of G is only written when some row has
-    # more neighbours than a list holds (few centroids), else the lists are built from the
-    # transposed tiles alone (many centroids)
+    # no adjacency output requested, graphs whose rows are kept as bits (few centroids) and as words
+    # (many centroids)
     L = wl.small_random(12, "f16", B=1, H=2, l=l, lw=1, cap=l, n_centroids=n_centroids, noise_frac=0.3)
     parity.check_shallow_layer(oracle, L, debug=False)
 
 
 @pytest.mark.parametrize("l", [255, 256, 257, 511, 513, 769, 1023, 1024, 1025, 1281, 2049])
 def test_panel_boundaries_without_adjacency_export(oracle, l):
-    # the similarity kernel starts a 256-row panel's own 1024-token chunk at the panel's first row
-    # and records a pair of two panels once, from the earlier one: lengths around the panel and
-    # chunk boundaries, graphs sparse enough for the lists to come from the records
+    # lengths around multiples of the 32-token tiles, of the 1024 tokens that fill a batch of the list kernel's
+    # steps, and where a second batch begins
     L = wl.small_random(31, "f16", B=1, H=2, l=l, lw=1, cap=l, n_centroids=max(4, l // 24), noise_frac=0.2,
                         drift_sigma=0.002)
     parity.check_shallow_layer(oracle, L, debug=False)
@@ -83,9 +81,9 @@ def test_knife_edge_pairs_are_decided_exactly(oracle):
 
 
 def test_more_close_pairs_than_the_pair_list_holds(oracle):
-    # every pair of tokens has a cosine within a few 1e-3 of theta: far more pairs fall inside the
-    # fp16 guard band than the list of deferred pairs holds (32 n), so the library has to fall back
-    # to deciding the close pairs in place, tile by tile, and to lists built from the bitmap
+    # every pair of tokens has a cosine within a few 1e-3 of theta: a step of the list kernel finds more pairs
+    # too close to decide in fp32 than a wave's list of waiting pairs holds (192), so the list is emptied in
+    # the middle of steps as well as at the end of a batch
     rng = np.random.default_rng(77)
     n, d, theta = 1200, 128, 0.98
     c = rng.standard_normal(d)
@@ -99,11 +97,11 @@ def test_more_close_pairs_than_the_pair_list_holds(oracle):
     S = wl.to_f64(K[0, 0], "f16")
     S /= np.linalg.norm(S, axis=1, keepdims=True)
     close = (np.abs(S @ S.T - theta) < 2e-4).sum() // 2
-    assert close > 32 * n, "the input must overflow the pair list"
+    assert close > 32 * n, "the input must hold many close pairs"
     L = wl.Layer("f16", K, K.copy(), np.zeros((1, 1, 1, d), np.float16), 1, 1, 1, n, n, theta_k=theta, theta_v=theta)
     parity.check_shallow_layer(oracle, L, tensors=("k",))
     parity.check_shallow_layer(oracle, L, tensors=("k",), cap=100, debug=False)
-    # the library's own count of deferred pairs confirms that the list ran full
+    # the library's own count of decisions in double precision: more than 30 per row and step
     import torch
     from paper_2507_06517_amd import binding as sb
     Kd = sb.to_device(L.K, "f16")

@@ -43,6 +43,22 @@ def test_more_column_tiles_than_a_batch_holds(oracle, dtype, H, l, centroids, th
     parity.check_shallow_layer(oracle, L, units=[(0, H // 2)], debug=False, cap=37)
 
 
+@pytest.mark.parametrize("dtype", ["f16", "f32"])
+def test_close_pairs_in_every_batch(oracle, dtype):
+    # cosines theta + (1 - theta) u_a.u_b, a few percent of them decided in double precision, in blocks of four row
+    # tiles with three batches of column tiles, some of which are the last of one wave and not of the others
+    rng = np.random.default_rng(71)
+    H, l, theta = 8, 2081, 0.98
+    c = np.zeros(128)
+    c[::2] = 1.0 / 8.0
+    u = rng.standard_normal((1, H, l, 128))
+    u -= (u @ c)[..., None] * c
+    u /= np.linalg.norm(u, axis=-1, keepdims=True)
+    K = wl.cast((np.sqrt(theta) * c + np.sqrt(1 - theta) * u) * rng.uniform(0.5, 2.0, (1, H, l, 1)), dtype)
+    L = wl.Layer(dtype, K, K.copy(), np.zeros_like(K[:, :, :1]), 1, 1, 1, l, l, theta_k=theta, theta_v=theta)
+    parity.check_shallow_layer(oracle, L, units=[(0, 0), (0, H - 1)])
+
+
 @pytest.mark.parametrize("dtype,theta,sizes", [("f16", 0.9, (9000, 7000, 600)), ("f32", 0.45, (8,) * 2110), ("bf16", 0.5, (16900,)),
                                                ("f16", 0.5, (6000,) + (7,) * 1600)])
 def test_rows_of_more_than_512_column_tiles(dtype, theta, sizes):
