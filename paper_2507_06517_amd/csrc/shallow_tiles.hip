@@ -390,7 +390,7 @@ __global__ __launch_bounds__(kScanThreads, 2) void shallow_scan(ShallowParams p)
     __syncthreads();                                   // ... and every wave's; the other buffer is free
     if (s > w.s0 && s > own) {
       all += found[s - 1 - w.s0];
-      refine = all > (s - max(own, w.s0)) * (int)(kRefineShare * kPerStage) + 3 * kPerStage / 4;
+      refine = all > (s - max(own, w.s0)) * (int)(kRefineShare * kPerStage) + kPerStage / 3;
       if (refine) break;
     }
     if (s == w.s1) break;
