@@ -444,7 +444,8 @@ __global__ __launch_bounds__(256) void shallow_assign_exact(ShallowParams p) {
         }
       }
     }
-    p.ref[ut / p.U][(size_t)(ut % p.U) * n + a] = bj;
+    // no cosine is a number (the token holds a NaN or an infinity): the first entry, as among equal ones
+    p.ref[ut / p.U][(size_t)(ut % p.U) * n + a] = bj == 0x7FFFFFFF ? 0 : bj;
   }
 }
 
@@ -477,7 +478,7 @@ __global__ __launch_bounds__(256) void shallow_overflow(ShallowParams p) {
       }
       __syncthreads();
     }
-    if (threadIdx.x == 0) p.ref[ut / p.U][(size_t)(ut % p.U) * p.n + a] = sh_j[0];
+    if (threadIdx.x == 0) p.ref[ut / p.U][(size_t)(ut % p.U) * p.n + a] = sh_j[0] == 0x7FFFFFFF ? 0 : sh_j[0];
     __syncthreads();
   }
 }

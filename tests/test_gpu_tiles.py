@@ -183,6 +183,22 @@ def test_one_record_per_call_of_the_kernel_over_all_pairs(H, l, theta_k, theta_v
         sb.spindle_profile(0)
 
 
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
+def test_cut_tokens_that_are_not_finite_refer_to_a_stored_entry(oracle, dtype):
+    # their cosines are no numbers, so no entry is the nearest: the first one, never a reference out of range
+    l, cap = 700, 20
+    L = wl.small_random(72, dtype, B=1, H=1, l=l, lw=1, cap=cap, n_centroids=12, noise_frac=0.3)
+    x = wl.to_f64(L.K, dtype)
+    for i, t in enumerate((3, 77, 333, 500, 501, 502, 600, l - 1)):
+        x[0, 0, t, i::17] = (np.nan, -np.nan, np.inf, -np.inf)[i % 4]
+    with np.errstate(over="ignore", invalid="ignore"):
+        L.K = wl.cast(x, dtype)
+    g = parity.gpu_shallow(L, tensors=("k",))
+    o = oracle.shallow_unit(wl.to_f64(L.K[0, 0], dtype), float(np.float32(L.theta_k)), cap)
+    assert o["n_codes_uncapped"] > cap + 8 and g["n_codes_k"][0, 0] == cap
+    assert np.array_equal(g["ref_k"][0, 0], o["ref"])
+
+
 def test_structured_vectors(oracle):
     # vectors the rotation of the sketch maps to few coordinates (constant, alternating, single ones), scaled
     # copies, opposite ones: sketches of little use, whose errors must widen what is looked at
