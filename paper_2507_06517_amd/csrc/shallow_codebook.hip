@@ -444,8 +444,11 @@ __global__ __launch_bounds__(256) void shallow_assign_exact(ShallowParams p) {
         }
       }
     }
-    // no cosine is a number (the token holds a NaN or an infinity): the first entry, as among equal ones
-    p.ref[ut / p.U][(size_t)(ut % p.U) * n + a] = bj == 0x7FFFFFFF ? 0 : bj;
+    if (bj == 0x7FFFFFFF) {                            // no approximate cosine is a number: a NaN or an infinity in the token
+      p.ovf_left[atomicAdd(p.ovf_count, 1u)] = ((uint32_t)ut << 16) | (uint32_t)a;
+      continue;
+    }
+    p.ref[ut / p.U][(size_t)(ut % p.U) * n + a] = bj;
   }
 }
 
