@@ -576,9 +576,8 @@ __global__ __launch_bounds__(kRefineThreads, 2) void shallow_refine(ShallowParam
 // use, and every wave multiplies one of them with one row tile (held in registers).  kCols = 1: what
 // similar rows have in common is read once for four row tiles; kCols = 4: short problems, where there
 // are too few row tiles to fill the chip.  Bound by the gathered rows (random 256-byte rows, mostly from
-// L2): 0.31 ms for 16 problems of 32768 tokens, 0.26 ms for 128 of 8192 in clusters of 128, where one wave
-// per row tile with its own gathers took 0.73 and 0.84 ms; the double-precision pass and the kernel that
-// made lists from records before took 0.21 and 0.63 ms on top of all the cosines.
+// L2): 0.22 ms for 16 problems of 32768 tokens, 0.20 ms for 128 of 8192 in clusters of 128, three blocks per compute unit
+// (0.31 and 0.25 with two); one wave per row tile with its own gathers took 0.73 and 0.84 ms.
 constexpr float kRowsGuard = 7e-5f;
 constexpr int kRowsQueue = 192;                    // waiting pairs per wave
 constexpr int kRowsThreads = 256;
@@ -1040,8 +1039,9 @@ spindle_status launch_rows(const ShallowParams &p, hipStream_t st) {
 }
 template <int DT>
 spindle_status launch_rows(const ShallowParams &p, hipStream_t st) {
-  // one row tile per block while four would leave compute units without a block (one fp32 head of 512
-  // tokens, K and V: 15 us against 47 us with a wave per row tile)
+  // one row tile per block while four would leave compute units without a block: fp16 and fp32 heads of 512 tokens,
+  // 256 row tiles in all 12 and 15 us (four per block 21 and 27), 512 row tiles 21 and 30 (21 and 28), 1024 38 and 47 (22 and
+  // 28); of 1000 tokens, 512 row tiles 31 and 38 (35 and 52), 1024 60 and 72 (36 and 47)
   if ((long)p.UT * p.T < 1024) return launch_rows<DT, 4>(p, st);
   return launch_rows<DT, 1>(p, st);
 }
