@@ -1,9 +1,9 @@
 // Similarity codebook replacement (Sec. "Similarity Based Token Replacement", Alg. 1): what its
 // kernels share.  ut = tensor * units + unit indexes one independent (batch, kv-head, K|V)
 // problem of n tokens.  The kernels, in the order spindle_compress_shallow enqueues them:
-//   shallow_init    counters, flags and outputs that must start from a known value
-//   shallow_prep    magnitudes (Eq. 8) in double precision, unit vectors rounded to fp16, and a
-//                   64-byte sketch of every token whose products bound the cosines from above
+//   shallow_prep    what must start from a known value; magnitudes (Eq. 8) in double precision, unit
+//                   vectors rounded to fp16, and a 64-byte sketch of every token whose products bound
+//                   the cosines from above
 //   shallow_pivots, shallow_order, shallow_window
 //                   the tokens of a problem sorted so that similar ones stand together
 //   shallow_scan    sketch products of all pairs of 32-token tiles on the int8 matrix cores:
@@ -14,8 +14,8 @@
 //   merge_onehop, merge_twohop, merge_update
 //                   the first rounds of the greedy highest-degree codebook construction
 //                   (Eq. 11-13) in its exact parallel form, one launch per phase
-//   shallow_merge   the remaining rounds, one workgroup per problem
-//   shallow_rank    codebook order of the picked tokens
+//   shallow_merge   the remaining rounds (all of them for short problems) and the codebook order of
+//                   the picked tokens, one workgroup per problem
 //   shallow_emit    references in codebook order and the codebook vectors
 //   shallow_assign, shallow_assign_exact, shallow_overflow
 //                   tokens whose entry fell beyond the codebook cap go to the nearest
@@ -81,7 +81,7 @@ constexpr float kRefineShare = 0.22f;
 
 constexpr int kCounters = 32;     // ints per ut
 // (slots 6..15 hold the phase timings of shallow_merge)
-enum { C_PICKS = 4, C_ROUNDS = 5, C_DONE = 16 };
+enum { C_PICKS = 4, C_ROUNDS = 5 };
 
 struct ShallowParams {
   const char *X[2];        // input tensors [U][n][128] in `dtype` (index = tensor slot)
@@ -204,7 +204,7 @@ constexpr int kCandCap = 8;
 
 // ---------------------------------------------------------------- launches, one per source file
 // Each enqueues its kernels on `st` in order and returns SPINDLE_OK or the failed HIP call.
-spindle_status launch_prep(const ShallowParams &p, hipStream_t st);
+spindle_status launch_prep(const ShallowParams &p, size_t nzero, size_t cpieces, hipStream_t st);   // words to clear, 16-byte pieces of a tensor's codebooks
 spindle_status launch_tiles(const ShallowParams &p, hipStream_t st);      // order, scan and lists
 spindle_status launch_adjacency(const ShallowParams &p, uint32_t *const out[2], hipStream_t st);   // exports G
 spindle_status launch_bare_similarity(const ShallowParams &p, hipStream_t st, int mode);   // measurement aid

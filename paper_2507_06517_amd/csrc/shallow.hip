@@ -7,19 +7,6 @@
 namespace spindle {
 namespace {
 
-// What must hold before the first kernel of a call: counters, errors and marks zero,
-// n_codes = -1 ("not finished"), codebooks zero.  One launch for all of it.
-__global__ __launch_bounds__(256) void shallow_init(ShallowParams p, size_t nzero, size_t cwords, int T) {
-  const size_t stride = (size_t)gridDim.x * blockDim.x, i0 = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  uint32_t *z = reinterpret_cast<uint32_t *>(p.counters);
-  for (size_t i = i0; i < nzero; i += stride) z[i] = 0u;
-  for (int t = 0; t < T; ++t) {
-    for (size_t i = i0; i < (size_t)p.U; i += stride) p.n_codes[t][i] = -1;
-    u4 *c = reinterpret_cast<u4 *>(p.C[t]);               // 16-byte aligned, a multiple of 16 bytes per row
-    for (size_t i = i0; i < cwords / 4; i += stride) c[i] = u4{0, 0, 0, 0};
-  }
-}
-
 // ---------------------------------------------------------------- workspace
 int tiles_of(int n) { return (n + kTile - 1) / kTile; }
 int padded_tiles_of(int n) { return (int)align_up((size_t)tiles_of(n), kScanPanel); }
@@ -195,9 +182,8 @@ spindle_status run_shallow(int phases,
   if (phases & kPhaseGraph) {
     // zero: counters, and where there is a scan its errors and marks; codebooks
     const size_t nzero = zero_words(p.UT, n, p.scan);
-    const size_t cwords = (size_t)U * max_codes * kHeadDim * dtype_bytes(p.dtype) / 4;
-    hipLaunchKernelGGL(shallow_init, dim3(1024), dim3(256), 0, st, p, nzero, cwords, T);
-    if ((s = launch_prep(p, st)) != SPINDLE_OK) return s;
+    const size_t cpieces = (size_t)U * max_codes * kHeadDim * dtype_bytes(p.dtype) / 16;
+    if ((s = launch_prep(p, nzero, cpieces, st)) != SPINDLE_OK) return s;
     if ((s = launch_tiles(p, st)) != SPINDLE_OK) return s;
     if ((s = launch_adjacency(p, adj, st)) != SPINDLE_OK) return s;
   }

@@ -1,201 +1,9 @@
-// Codebook order, outputs and the codebook cap (Alg. 1; Eq. 4 for the re-pointed tokens).
+// Outputs and the codebook cap (Alg. 1; Eq. 4 for the re-pointed tokens).
 #include "mma.h"
 #include "shallow.h"
 
 namespace spindle {
 namespace {
-
-// Codebook order: the picks of a problem sorted by decreasing key at pick time, i.e. by decreasing
-// degree and among equal degrees by increasing token.  One workgroup per problem lists the picks in token
-// order as degree << 16 | position, then a least-significant-digit radix sort of the degrees: at most two
-// stable passes of 8 bits that ping-pong between two arrays left free by the merge; a pass whose digit all
-// picks share is left out (degrees below 256: one pass).  In a pass every wave owns a run of the items:
-// it counts their digits, and after one sum over waves and digits places them, 64 at a time, lanes with the
-// same digit finding each other with eight ballots.
-// Bound by latency, one workgroup per problem: 2 problems of 32768 rows 50 -> 43 us, one layer of 16 x 32768
-// beside two others 128 -> 88 us, 64 x 32768 with half of the tokens isolated 275 -> 219 us, one of 512
-// tokens 19 -> 12 us against four passes over (key, position) pairs, 1024 items and five barriers at a time.
-constexpr int kRankThreads = 1024;
-
-__device__ __forceinline__ unsigned long long same_digit(int d, bool on) {
-  unsigned long long peers = __ballot(on);
-#pragma unroll
-  for (int bit = 0; bit < 8; ++bit) {
-    const unsigned long long m = __ballot((d >> bit) & 1);
-    peers &= ((d >> bit) & 1) ? m : ~m;
-  }
-  return peers;
-}
-
-__global__ __launch_bounds__(kRankThreads) void shallow_rank(ShallowParams p) {
-  constexpr int kWaves = kRankThreads / 64, kAtOnce = 4;
-  __shared__ uint32_t picked[2048];                  // bit per position (n <= 65535)
-  __shared__ int before[1024];                       // picked tokens in front of 64 consecutive ones
-  __shared__ int place[kWaves][256];                 // next output position of a digit of a wave's items
-  __shared__ int wsum[kWaves];
-  __shared__ int sh_alike;
-  const int ut = blockIdx.x, tid = threadIdx.x, lane = lane_id(), wave = tid >> 6, n = p.n;
-  const size_t base = (size_t)ut * n;
-  int *cnt = p.counters + (size_t)ut * kCounters;
-  if (cnt[C_DONE] == 0) return;                      // construction did not finish: n_codes stays -1
-  for (int i = tid; i < p.T; i += kRankThreads) picked[i] = p.picked[(size_t)ut * p.T + i];
-  before[tid] = 0;
-  __syncthreads();
-  // thread t takes tokens t, t + 1024, ..., eight loads in flight (loops kept short: with all trips unrolled the
-  // instruction fetches of a cold kernel cost more than the loads)
-  constexpr int kLoads = 8;
-  auto is_picked = [&](int tok, int v) { return tok < n && (picked[v >> 5] >> (v & 31) & 1u); };
-#pragma unroll 1
-  for (int t0 = tid; t0 - tid < n; t0 += kLoads * kRankThreads) {
-    int v[kLoads];
-#pragma unroll
-    for (int i = 0; i < kLoads; ++i) v[i] = t0 + i * kRankThreads < n ? (int)p.iperm[base + t0 + i * kRankThreads] : 0;
-#pragma unroll
-    for (int i = 0; i < kLoads; ++i) {
-      const unsigned long long mk = __ballot(is_picked(t0 + i * kRankThreads, v[i]));
-      if (lane == 0) before[min(1023, (t0 + i * kRankThreads) >> 6)] = __popcll(mk);
-    }
-  }
-  __syncthreads();
-  int P = 0;
-  {
-    const int own = before[tid];
-    int incl = own;
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-      const int x = __shfl_up(incl, o);
-      if (lane >= o) incl += x;
-    }
-    if (lane == kWave - 1) wsum[wave] = incl;
-    __syncthreads();
-    for (int q = 0; q < kWaves; ++q) {
-      if (q < wave) incl += wsum[q];
-      P += wsum[q];
-    }
-    before[tid] = incl - own;
-  }
-  if (tid == 0) {
-    cnt[C_PICKS] = P;
-    p.n_codes[ut / p.U][ut % p.U] = P < p.cap ? P : p.cap;
-    if (p.n_found[ut / p.U]) p.n_found[ut / p.U][ut % p.U] = P;
-  }
-  __syncthreads();
-  uint32_t *src = p.m1 + (size_t)ut * p.n16, *dst = p.key + (size_t)ut * p.n16;
-#pragma unroll 1
-  for (int t0 = tid; t0 - tid < n; t0 += kLoads * kRankThreads) {
-    int v[kLoads];
-    uint32_t k[kLoads];
-#pragma unroll
-    for (int i = 0; i < kLoads; ++i) v[i] = t0 + i * kRankThreads < n ? (int)p.iperm[base + t0 + i * kRankThreads] : 0;
-#pragma unroll
-    for (int i = 0; i < kLoads; ++i) k[i] = p.pick_key[base + v[i]];
-#pragma unroll
-    for (int i = 0; i < kLoads; ++i) {
-      const int tok = t0 + i * kRankThreads;
-      const bool on = is_picked(tok, v[i]);
-      const unsigned long long mk = __ballot(on);
-      if (on) src[before[tok >> 6] + __popcll(mk & ((1ull << lane) - 1ull))] = (k[i] & 0xFFFF0000u) | (uint32_t)v[i];
-    }
-  }
-  const int run = (((P + kWaves - 1) / kWaves) + 63) & ~63;      // items per wave
-  const int s_begin = min(P, wave * run), s_end = min(P, s_begin + run);
-  volatile int *mine = place[wave];
-#pragma unroll 1
-  for (int shift = 16; shift < 32; shift += 8) {
-    for (int i = tid; i < kWaves * 256; i += kRankThreads) (&place[0][0])[i] = 0;
-    if (tid == 0) sh_alike = 0;
-    __syncthreads();
-#pragma unroll 1
-    for (int s0 = s_begin; s0 < s_end; s0 += 64 * kAtOnce) {
-      uint32_t k[kAtOnce];
-#pragma unroll
-      for (int q = 0; q < kAtOnce; ++q) {
-        const int s = s0 + 64 * q + lane;
-        k[q] = s < s_end ? src[s] : 0u;
-      }
-#pragma unroll
-      for (int q = 0; q < kAtOnce; ++q) {
-        const bool on = s0 + 64 * q + lane < s_end;
-        const int d = 255 - (int)((k[q] >> shift) & 255u);        // larger degrees first
-        const unsigned long long peers = same_digit(d, on);
-        if (on && lane == __builtin_ctzll(peers)) mine[d] = mine[d] + __popcll(peers);
-        __builtin_amdgcn_wave_barrier();
-      }
-    }
-    __syncthreads();
-    int total = 0, incl = 0;
-    if (tid < 256) {
-#pragma unroll
-      for (int w = 0; w < kWaves; ++w) total += place[w][tid];
-      incl = total;
-#pragma unroll
-      for (int o = 1; o < kWave; o <<= 1) {
-        const int x = __shfl_up(incl, o);
-        if (lane >= o) incl += x;
-      }
-      if (lane == kWave - 1) wsum[wave] = incl;
-      if (total == P) sh_alike = 1;
-    }
-    __syncthreads();
-    if (sh_alike) {                                  // this digit orders nothing (no picks: likewise)
-      __syncthreads();
-      continue;
-    }
-    if (tid < 256) {
-      int at = incl - total;
-      for (int w = 0; w < wave; ++w) at += wsum[w];
-#pragma unroll
-      for (int w = 0; w < kWaves; ++w) {
-        const int c = place[w][tid];
-        place[w][tid] = at;
-        at += c;
-      }
-    }
-    __syncthreads();
-#pragma unroll 1
-    for (int s0 = s_begin; s0 < s_end; s0 += 64 * kAtOnce) {
-      uint32_t k[kAtOnce];
-#pragma unroll
-      for (int q = 0; q < kAtOnce; ++q) {
-        const int s = s0 + 64 * q + lane;
-        k[q] = s < s_end ? src[s] : 0u;
-      }
-#pragma unroll
-      for (int q = 0; q < kAtOnce; ++q) {
-        const bool on = s0 + 64 * q + lane < s_end;
-        const int d = 255 - (int)((k[q] >> shift) & 255u);
-        const unsigned long long peers = same_digit(d, on);
-        const int at = mine[d];
-        __builtin_amdgcn_wave_barrier();
-        if (on) {
-          dst[at + __popcll(peers & ((1ull << lane) - 1ull))] = k[q];
-          if (lane == __builtin_ctzll(peers)) mine[d] = at + __popcll(peers);
-        }
-        __builtin_amdgcn_wave_barrier();
-      }
-    }
-    __syncthreads();
-    uint32_t *x = src;
-    src = dst;
-    dst = x;
-  }
-#pragma unroll 1
-  for (int r0 = 0; r0 < P; r0 += kAtOnce * kRankThreads) {
-    int v[kAtOnce], tok[kAtOnce];
-#pragma unroll
-    for (int q = 0; q < kAtOnce; ++q) v[q] = r0 + q * kRankThreads + tid < P ? (int)(src[r0 + q * kRankThreads + tid] & 0xFFFFu) : 0;
-#pragma unroll
-    for (int q = 0; q < kAtOnce; ++q) tok[q] = (int)p.perm[base + v[q]];
-#pragma unroll
-    for (int q = 0; q < kAtOnce; ++q) {
-      const int r = r0 + q * kRankThreads + tid;
-      if (r < P) {
-        p.rank[base + v[q]] = r;
-        p.rank_vert[base + r] = tok[q];              // from here on tokens again
-      }
-    }
-  }
-}
 
 // References (Eq. 12, renumbered in codebook order) and codebook entries (Eq. 11), grid-wide.  A
 // thread takes a token's reference, a group of lanes with 16 bytes each (16 lanes; 32 for fp32) an entry
@@ -490,8 +298,6 @@ __global__ __launch_bounds__(256) void shallow_overflow(ShallowParams p) {
 
 spindle_status launch_codebook(const ShallowParams &p, hipStream_t st) {
   const int n = p.n;
-  { ProfScope ps("shallow_rank", st);
-  hipLaunchKernelGGL(shallow_rank, dim3(p.UT), dim3(kRankThreads), 0, st, p); }
   { ProfScope ps("shallow_emit", st);
   // as many blocks as the references or the entries ask for, whichever is more
   const int kept = p.cap < n ? p.cap : n;

@@ -32,6 +32,10 @@ namespace {
 constexpr int kMergeThreads = 1024;
 constexpr int kSegW = 8;                 // lanes that share one row
 constexpr int kGridRounds = 2;           // live[] holds the bits of one round more
+// Up to here the workgroup per problem runs all rounds: six launches less, and no more than eight rows per lane segment
+// and phase.  f16, us per call with and without the grid rounds, clusters and half isolated: one head of 512
+// tokens 68, 88 and 55, 73; 8 of 1024 95, 125 and 81, 115; 8 of 1536 114, 163 and 111, 170; 8 of 2048 129, 178 and 132, 196.
+constexpr int kTailOnly = 1024;
 constexpr int kPhaseThreads = 256;
 constexpr int kKeysInLds = 36 * 1024;   // tokens whose keys fit in LDS next to the live bits
 
@@ -258,7 +262,7 @@ __global__ __launch_bounds__(kPhaseThreads) void merge_update(ShallowParams p, i
 // State of one problem in the workgroup: keys in LDS (or global memory), bits in LDS.
 struct Tail {
   const uint32_t *lists;
-  uint32_t *key, *live, *next;
+  uint32_t *key, *live, *next, *picked;
   int *n_cand, *n_dying;
   int seg, sl;
 };
@@ -297,7 +301,7 @@ __device__ __forceinline__ void tail_onehop(const ShallowParams &p, size_t base,
   }
 }
 
-__device__ __forceinline__ void tail_twohop(const ShallowParams &p, int ut, size_t base, const Tail &w,
+__device__ __forceinline__ void tail_twohop(const ShallowParams &p, size_t base, const Tail &w,
                                             const uint32_t *m1, int ncand) {
   const int *cand = p.cand + base;
   int *slot = p.slot + base, *dying = p.dying + base;
@@ -313,7 +317,7 @@ __device__ __forceinline__ void tail_twohop(const ShallowParams &p, int ut, size
     if (seg_max(m) != ku) continue;
     if (w.sl == 0) {
       p.pick_key[base + u] = ku;
-      atomicOr(p.picked + (size_t)ut * p.T + (u >> 5), 1u << (u & 31));
+      atomicOr(&w.picked[u >> 5], 1u << (u & 31));
     }
     for (int i = w.sl; i < r.n; i += kSegW) {
       const uint32_t x = word_at(r, i);
@@ -331,6 +335,203 @@ __device__ __forceinline__ void tail_twohop(const ShallowParams &p, int ut, size
   }
 }
 
+// ---------------------------------------------------------------- codebook order
+// Codebook order: the picks of a problem sorted by decreasing key at pick time, i.e. by decreasing
+// degree and among equal degrees by increasing token.  One workgroup per problem lists the picks in token
+// order as degree << 16 | position, then a least-significant-digit radix sort of the degrees: at most two
+// stable passes of 8 bits that ping-pong between two arrays left free by the merge; a pass whose digit all
+// picks share is left out (degrees below 256: one pass).  In a pass every wave owns a run of the items:
+// it counts their digits, and after one sum over waves and digits places them, 64 at a time, lanes with the
+// same digit finding each other with eight ballots.
+// Bound by latency, one workgroup per problem: as a kernel of its own on arrays in memory 43 us for 2 problems of
+// 32768 rows, 88 for one layer of 16 x 32768 beside two others, 12 for 512 tokens.  It is the end of
+// shallow_merge, whose LDS is free by then: with the launch before it gone and the picks in LDS a call of 512 to
+// 4096 tokens takes 5 us less.
+__device__ __forceinline__ unsigned long long same_digit(int d, bool on) {
+  unsigned long long peers = __ballot(on);
+#pragma unroll
+  for (int bit = 0; bit < 8; ++bit) {
+    const unsigned long long m = __ballot((d >> bit) & 1);
+    peers &= ((d >> bit) & 1) ? m : ~m;
+  }
+  return peers;
+}
+
+struct RankLds {
+  int before[1024];                                  // picked tokens in front of 64 consecutive ones
+  int place[kMergeThreads / kWave][256];             // next output position of a digit of a wave's items
+  int wsum[kMergeThreads / kWave];
+  int alike;
+};
+
+// `room` words behind `l` are free: picks that fit there twice are sorted in LDS.
+__device__ __forceinline__ void rank_picks(const ShallowParams &p, int ut, const uint32_t *picked, RankLds &l, int room) {
+  constexpr int kWaves = kMergeThreads / kWave, kAtOnce = 4;
+  int *before = l.before, *wsum = l.wsum;
+  auto &place = l.place;
+  const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6, n = p.n;
+  const size_t base = (size_t)ut * n;
+  int *cnt = p.counters + (size_t)ut * kCounters;
+  before[tid] = 0;
+  __syncthreads();
+  // thread t takes tokens t, t + 1024, ..., eight loads in flight (loops kept short: with all trips unrolled the
+  // instruction fetches of a cold kernel cost more than the loads)
+  constexpr int kLoads = 8;
+  auto is_picked = [&](int tok, int v) { return tok < n && (picked[v >> 5] >> (v & 31) & 1u); };
+#pragma unroll 1
+  for (int t0 = tid; t0 - tid < n; t0 += kLoads * kMergeThreads) {
+    int v[kLoads];
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i) v[i] = t0 + i * kMergeThreads < n ? (int)p.iperm[base + t0 + i * kMergeThreads] : 0;
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i) {
+      const unsigned long long mk = __ballot(is_picked(t0 + i * kMergeThreads, v[i]));
+      if (lane == 0) before[min(1023, (t0 + i * kMergeThreads) >> 6)] = __popcll(mk);
+    }
+  }
+  __syncthreads();
+  int P = 0;
+  {
+    const int own = before[tid];
+    int incl = own;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+      const int x = __shfl_up(incl, o);
+      if (lane >= o) incl += x;
+    }
+    if (lane == kWave - 1) wsum[wave] = incl;
+    __syncthreads();
+    for (int q = 0; q < kWaves; ++q) {
+      if (q < wave) incl += wsum[q];
+      P += wsum[q];
+    }
+    before[tid] = incl - own;
+  }
+  if (tid == 0) {
+    cnt[C_PICKS] = P;
+    p.n_codes[ut / p.U][ut % p.U] = P < p.cap ? P : p.cap;
+    if (p.n_found[ut / p.U]) p.n_found[ut / p.U][ut % p.U] = P;
+  }
+  __syncthreads();
+  const bool in_lds = 2 * P <= room;
+  uint32_t *src = in_lds ? reinterpret_cast<uint32_t *>(&l + 1) : p.m1 + (size_t)ut * p.n16;
+  uint32_t *dst = in_lds ? src + P : p.key + (size_t)ut * p.n16;
+#pragma unroll 1
+  for (int t0 = tid; t0 - tid < n; t0 += kLoads * kMergeThreads) {
+    int v[kLoads];
+    uint32_t k[kLoads];
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i) v[i] = t0 + i * kMergeThreads < n ? (int)p.iperm[base + t0 + i * kMergeThreads] : 0;
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i) k[i] = is_picked(t0 + i * kMergeThreads, v[i]) ? p.pick_key[base + v[i]] : 0u;
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i) {
+      const int tok = t0 + i * kMergeThreads;
+      const bool on = k[i] != 0;                     // (a token's key at pick time counts itself)
+      const unsigned long long mk = __ballot(on);
+      if (on) src[before[tok >> 6] + __popcll(mk & ((1ull << lane) - 1ull))] = (k[i] & 0xFFFF0000u) | (uint32_t)v[i];
+    }
+  }
+  const int run = (((P + kWaves - 1) / kWaves) + 63) & ~63;      // items per wave
+  const int s_begin = min(P, wave * run), s_end = min(P, s_begin + run);
+  volatile int *mine = place[wave];
+#pragma unroll 1
+  for (int shift = 16; shift < 32; shift += 8) {
+    for (int i = tid; i < kWaves * 256; i += kMergeThreads) (&place[0][0])[i] = 0;
+    if (tid == 0) l.alike = 0;
+    __syncthreads();
+#pragma unroll 1
+    for (int s0 = s_begin; s0 < s_end; s0 += 64 * kAtOnce) {
+      uint32_t k[kAtOnce];
+#pragma unroll
+      for (int q = 0; q < kAtOnce; ++q) {
+        const int s = s0 + 64 * q + lane;
+        k[q] = s < s_end ? src[s] : 0u;
+      }
+#pragma unroll
+      for (int q = 0; q < kAtOnce; ++q) {
+        const bool on = s0 + 64 * q + lane < s_end;
+        const int d = 255 - (int)((k[q] >> shift) & 255u);        // larger degrees first
+        const unsigned long long peers = same_digit(d, on);
+        if (on && lane == __builtin_ctzll(peers)) mine[d] = mine[d] + __popcll(peers);
+        __builtin_amdgcn_wave_barrier();
+      }
+    }
+    __syncthreads();
+    int total = 0, incl = 0;
+    if (tid < 256) {
+#pragma unroll
+      for (int w = 0; w < kWaves; ++w) total += place[w][tid];
+      incl = total;
+#pragma unroll
+      for (int o = 1; o < kWave; o <<= 1) {
+        const int x = __shfl_up(incl, o);
+        if (lane >= o) incl += x;
+      }
+      if (lane == kWave - 1) wsum[wave] = incl;
+      if (total == P) l.alike = 1;
+    }
+    __syncthreads();
+    if (l.alike) {                                  // this digit orders nothing (no picks: likewise)
+      __syncthreads();
+      continue;
+    }
+    if (tid < 256) {
+      int at = incl - total;
+      for (int w = 0; w < wave; ++w) at += wsum[w];
+#pragma unroll
+      for (int w = 0; w < kWaves; ++w) {
+        const int c = place[w][tid];
+        place[w][tid] = at;
+        at += c;
+      }
+    }
+    __syncthreads();
+#pragma unroll 1
+    for (int s0 = s_begin; s0 < s_end; s0 += 64 * kAtOnce) {
+      uint32_t k[kAtOnce];
+#pragma unroll
+      for (int q = 0; q < kAtOnce; ++q) {
+        const int s = s0 + 64 * q + lane;
+        k[q] = s < s_end ? src[s] : 0u;
+      }
+#pragma unroll
+      for (int q = 0; q < kAtOnce; ++q) {
+        const bool on = s0 + 64 * q + lane < s_end;
+        const int d = 255 - (int)((k[q] >> shift) & 255u);
+        const unsigned long long peers = same_digit(d, on);
+        const int at = mine[d];
+        __builtin_amdgcn_wave_barrier();
+        if (on) {
+          dst[at + __popcll(peers & ((1ull << lane) - 1ull))] = k[q];
+          if (lane == __builtin_ctzll(peers)) mine[d] = at + __popcll(peers);
+        }
+        __builtin_amdgcn_wave_barrier();
+      }
+    }
+    __syncthreads();
+    uint32_t *x = src;
+    src = dst;
+    dst = x;
+  }
+#pragma unroll 1
+  for (int r0 = 0; r0 < P; r0 += kAtOnce * kMergeThreads) {
+    int v[kAtOnce], tok[kAtOnce];
+#pragma unroll
+    for (int q = 0; q < kAtOnce; ++q) v[q] = r0 + q * kMergeThreads + tid < P ? (int)(src[r0 + q * kMergeThreads + tid] & 0xFFFFu) : 0;
+#pragma unroll
+    for (int q = 0; q < kAtOnce; ++q) tok[q] = (int)p.perm[base + v[q]];
+#pragma unroll
+    for (int q = 0; q < kAtOnce; ++q) {
+      const int r = r0 + q * kMergeThreads + tid;
+      if (r < P) {
+        p.rank[base + v[q]] = r;
+        p.rank_vert[base + r] = tok[q];              // from here on tokens again
+      }
+    }
+  }
+}
+
 #define MERGE_TICK(k)                          \
   if (tid == 0) {                              \
     const long long now_ = wall_clock64();     \
@@ -338,7 +539,7 @@ __device__ __forceinline__ void tail_twohop(const ShallowParams &p, int ut, size
     tick_ = now_;                              \
   }
 
-__global__ __launch_bounds__(kMergeThreads) void shallow_merge(ShallowParams p) {
+__global__ __launch_bounds__(kMergeThreads) void shallow_merge(ShallowParams p, int first_round, int lds_words) {
   extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
   __shared__ int sh_n[3];                     // alive, candidates, dying
   __shared__ int wsum[kMergeThreads / kWave];
@@ -348,11 +549,13 @@ __global__ __launch_bounds__(kMergeThreads) void shallow_merge(ShallowParams p) 
   const bool keys_in_lds = n <= kKeysInLds;
   int *cnt = p.counters + (size_t)ut * kCounters;
   uint32_t *gkey = p.key + (size_t)ut * p.n16, *m1 = p.m1 + (size_t)ut * p.n16;
+  const int T4 = (T + 3) & ~3;
   Tail w;
   w.lists = p.lists + base * p.list_row;
-  w.live = lds;
-  w.next = lds + ((T + 3) & ~3);
-  w.key = keys_in_lds ? w.next + ((T + 3) & ~3) : gkey;
+  w.picked = lds;
+  w.live = lds + T4;
+  w.next = w.live + T4;
+  w.key = keys_in_lds ? w.next + T4 : gkey;
   w.n_cand = &sh_n[1]; w.n_dying = &sh_n[2];
   w.seg = tid / kSegW; w.sl = tid & (kSegW - 1);
   int *alive = p.alive + base;
@@ -361,8 +564,9 @@ __global__ __launch_bounds__(kMergeThreads) void shallow_merge(ShallowParams p) 
   if (tid == 0) tick_ = wall_clock64();
 
   // tokens left after the grid rounds, as a list
-  const uint32_t *glive = p.live[kGridRounds] + (size_t)ut * T;
+  const uint32_t *glive = p.live[first_round] + (size_t)ut * T;
   if (tid < 3) sh_n[tid] = 0;
+  for (int i = tid; i < T; i += kMergeThreads) w.picked[i] = first_round > 0 ? p.picked[(size_t)ut * T + i] : 0u;
   for (int w0 = 0; w0 < T; w0 += kMergeThreads) {
     const int i = w0 + tid;
     uint32_t bits = i < T ? glive[i] : 0;
@@ -393,14 +597,14 @@ __global__ __launch_bounds__(kMergeThreads) void shallow_merge(ShallowParams p) 
 
   // every round removes at least the token of largest key, so n rounds always suffice;
   // the bound only guards against a workspace overwritten under the running call
-  int round = kGridRounds;
+  int round = first_round;
   for (; round <= n + kGridRounds; ++round) {
     const int nalive = sh_n[0];
     if (nalive == 0) break;
     tail_onehop(p, base, w, m1, alive, nalive);
     __syncthreads();
     MERGE_TICK(2)
-    tail_twohop(p, ut, base, w, m1, sh_n[1]);
+    tail_twohop(p, base, w, m1, sh_n[1]);
     __syncthreads();
     MERGE_TICK(4)
     const int ndying = sh_n[2];
@@ -448,11 +652,11 @@ __global__ __launch_bounds__(kMergeThreads) void shallow_merge(ShallowParams p) 
     __syncthreads();
     MERGE_TICK(6)
   }
-  if (tid == 0) {
-    cnt[C_ROUNDS] = round;
-    cnt[C_DONE] = sh_n[0] == 0;                      // (else n_codes stays -1)
-  }
+  if (tid == 0) cnt[C_ROUNDS] = round;
   MERGE_TICK(8)
+  if (sh_n[0] != 0) return;                          // construction did not finish: n_codes stays -1
+  RankLds &l = *reinterpret_cast<RankLds *>(w.live);
+  rank_picks(p, ut, w.picked, l, lds_words - T4 - (int)(sizeof(RankLds) / sizeof(uint32_t)));
 }
 
 }  // namespace
@@ -460,18 +664,24 @@ __global__ __launch_bounds__(kMergeThreads) void shallow_merge(ShallowParams p) 
 spindle_status launch_merge(const ShallowParams &p, hipStream_t st) {
   const int n = p.n;
   const dim3 pg((unsigned)((p.T + kPhaseThreads / kWave - 1) / (kPhaseThreads / kWave)), p.UT);
-  for (int round = 0; round < kGridRounds; ++round) {
+  const int first_round = n <= kTailOnly ? 0 : kGridRounds;
+  for (int round = 0; round < first_round; ++round) {
     ProfScope ps("shallow_merge_grid", st);
     hipLaunchKernelGGL(merge_onehop, pg, dim3(kPhaseThreads), 0, st, p, round);
     hipLaunchKernelGGL(merge_twohop, pg, dim3(kPhaseThreads), 0, st, p, round);
     hipLaunchKernelGGL(merge_update, pg, dim3(kPhaseThreads), 0, st, p, round);
   }
+  // LDS: bits picked, live and next, keys; afterwards, in the place of all but the first, the codebook order's arrays
+  // and the picks twice, as far as two blocks per compute unit allow or the keys took that much anyway
+  const size_t T4 = (size_t)((p.T + 3) & ~3), rank = T4 + sizeof(RankLds) / sizeof(uint32_t);
+  size_t words = 3 * T4 + (n <= kKeysInLds ? (size_t)p.n16 : 0);
+  const size_t want = rank + 2 * (size_t)n, half = 78 * 1024 / sizeof(uint32_t);
+  if (words < want) words = want <= half ? want : (words < half ? half : words);
   static LdsLimit lim_merge;                              // raised once per device to the largest size in use
   if (spindle_status e = allow_lds(lim_merge, reinterpret_cast<const void *>(&shallow_merge),
-                                   (kKeysInLds + 2 * (kKeysInLds / 32 + 4)) * sizeof(uint32_t))) return e;
-  const size_t merge_lds = ((n <= kKeysInLds ? (size_t)p.n16 : 0) + 2 * (size_t)((p.T + 3) & ~3)) * sizeof(uint32_t);
+                                   (kKeysInLds + 3 * (kKeysInLds / 32 + 4)) * sizeof(uint32_t))) return e;
   { ProfScope ps("shallow_merge", st);
-  hipLaunchKernelGGL(shallow_merge, dim3(p.UT), dim3(kMergeThreads), merge_lds, st, p); }
+  hipLaunchKernelGGL(shallow_merge, dim3(p.UT), dim3(kMergeThreads), words * sizeof(uint32_t), st, p, first_round, (int)words); }
   SPINDLE_HIP(hipGetLastError());
   return SPINDLE_OK;
 }

@@ -4,12 +4,27 @@
 namespace spindle {
 namespace {
 
+// Counters, errors and marks zero, n_codes = -1 ("not finished"), codebooks zero: every thread of the launch writes
+// its share.  (As a launch of its own it took 3 to 6 us of every call, most of it the launch.)
+__device__ __forceinline__ void begin_call(const ShallowParams &p, size_t nzero, size_t cpieces) {
+  const size_t stride = (size_t)gridDim.x * gridDim.y * 256;
+  const size_t i0 = ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * 256 + threadIdx.x;
+  uint32_t *z = reinterpret_cast<uint32_t *>(p.counters);
+  for (size_t i = i0; i < nzero; i += stride) z[i] = 0u;
+  for (int t = 0; t < p.UT / p.U; ++t) {
+    for (size_t i = i0; i < (size_t)p.U; i += stride) p.n_codes[t][i] = -1;
+    u4 *c = reinterpret_cast<u4 *>(p.C[t]);               // 16-byte aligned, a multiple of 16 bytes per row
+    for (size_t i = i0; i < cpieces; i += stride) c[i] = u4{0, 0, 0, 0};
+  }
+}
+
 // 64 tokens per block.  kSketch: also the tokens' sketches (shallow.h).  The rotation is a 128-point
 // Walsh-Hadamard transform, 32 coordinates per thread: five stages in registers, two across the
 // four threads of a token by quad permutations.  It spreads what a vector has in a few coordinates
 // over all of them, so that the 60 kept ones carry their share of every vector's norm.
+// It is the first kernel of a call and also writes what must hold before the others (begin_call).
 template <int DT, bool kSketch>
-__global__ __launch_bounds__(256) void shallow_prep(ShallowParams p) {
+__global__ __launch_bounds__(256) void shallow_prep(ShallowParams p, size_t nzero, size_t cpieces) {
   typedef typename Elem<DT>::type T;
   constexpr int kRows = 64;
   constexpr int row_bytes = kHeadDim * sizeof(T);
@@ -20,6 +35,7 @@ __global__ __launch_bounds__(256) void shallow_prep(ShallowParams p) {
   __shared__ double row_inv[kRows];
   const int ut = blockIdx.y, t = ut / p.U;
   const int row0 = blockIdx.x * kRows;
+  begin_call(p, nzero, cpieces);
   for (int i = threadIdx.x; i < kRows * tpr; i += 256) {
     const int r = i / tpr, ch = i % tpr;
     u4 v = {0, 0, 0, 0};
@@ -151,12 +167,12 @@ __global__ __launch_bounds__(256) void shallow_prep(ShallowParams p) {
 
 }  // namespace
 
-spindle_status launch_prep(const ShallowParams &p, hipStream_t st) {
+spindle_status launch_prep(const ShallowParams &p, size_t nzero, size_t cpieces, hipStream_t st) {
   const dim3 pgrid((p.n + 63) / 64, p.UT);
 #define SPINDLE_PREP(DT)                                                                                          \
   do {                                                                                                            \
-    if (p.scan) hipLaunchKernelGGL((shallow_prep<DT, true>), pgrid, dim3(256), 0, st, p);                         \
-    else hipLaunchKernelGGL((shallow_prep<DT, false>), pgrid, dim3(256), 0, st, p);                               \
+    if (p.scan) hipLaunchKernelGGL((shallow_prep<DT, true>), pgrid, dim3(256), 0, st, p, nzero, cpieces);         \
+    else hipLaunchKernelGGL((shallow_prep<DT, false>), pgrid, dim3(256), 0, st, p, nzero, cpieces);               \
   } while (0)
   ProfScope ps("shallow_prep", st);
   if (p.dtype == SPINDLE_F16) SPINDLE_PREP(SPINDLE_F16);

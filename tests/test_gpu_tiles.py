@@ -90,6 +90,26 @@ def test_rows_of_more_than_512_column_tiles(dtype, theta, sizes):
     assert np.array_equal(adj, (which[:64, None] == which[None]).astype(np.uint8))
 
 
+@pytest.mark.parametrize("sizes", [(300,) + (2,) * 400 + (1,) * 7600, (300,) + (2,) * 400 + (1,) * 3000, (257,) + (3,) * 100 + (1,) * 467,
+                                   (1,) * 1025, (512, 512), (513, 512)])
+def test_codebook_order_in_lds_and_in_memory(sizes):
+    # picks that fit twice into the free LDS of the merge kernel (7000 of them at 8000 tokens) and more than that,
+    # degrees of one and of two digits, with and without the grid rounds (from 1025 tokens on); the order is that of
+    # the clusters' sizes, then of their first tokens
+    rng = np.random.default_rng(73)
+    which = rng.permutation(np.repeat(np.arange(len(sizes)), sizes))
+    centres = rng.standard_normal((len(sizes), 128))
+    x = centres[which] * rng.uniform(0.5, 2.0, (len(which), 1)) + 0.01 * rng.standard_normal((len(which), 128))
+    l = len(which)
+    K = wl.cast(x[None, None], "f16")
+    L = wl.Layer("f16", K, K.copy(), np.zeros_like(K[:, :, :1]), 1, 1, 1, l, l, theta_k=0.95, theta_v=0.95)
+    g = parity.gpu_shallow(L, tensors=("k",), debug=False)
+    names, first, inverse, count = np.unique(which, return_index=True, return_inverse=True, return_counts=True)
+    rank = np.empty(len(names), np.int64)
+    rank[np.lexsort((first, -count))] = np.arange(len(names))
+    assert g["n_found_k"][0, 0] == len(names) and np.array_equal(g["ref_k"][0, 0], rank[inverse])
+
+
 @pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
 def test_dense_rows_and_low_thresholds(oracle, dtype):
     # nearly everything adjacent: more words per row than the lists hold, so they are kept as bits;
