@@ -109,6 +109,31 @@ struct Elem<SPINDLE_BF16> {
   }
 };
 
+// x_a . x_b in double precision, summed in dimension order (products are exact).
+template <int DT, int kBatch = 8>                      // kBatch: 16-byte pieces of each row in flight
+__device__ double dot64(const char *ra, const char *rb) {
+  typedef typename Elem<DT>::type T;
+  constexpr int per = 16 / sizeof(T);
+  double acc = 0.0;
+  for (int c0 = 0; c0 < kHeadDim / per; c0 += kBatch) {
+    u4 va[kBatch], vb[kBatch];
+#pragma unroll
+    for (int i = 0; i < kBatch; ++i) {
+      va[i] = reinterpret_cast<const u4 *>(ra)[c0 + i];
+      vb[i] = reinterpret_cast<const u4 *>(rb)[c0 + i];
+    }
+#pragma unroll
+    for (int i = 0; i < kBatch; ++i) {
+      const T *ea = reinterpret_cast<const T *>(&va[i]);
+      const T *eb = reinterpret_cast<const T *>(&vb[i]);
+#pragma unroll
+      for (int j = 0; j < per; ++j)
+        acc += (double)Elem<DT>::to_float(ea[j]) * (double)Elem<DT>::to_float(eb[j]);
+    }
+  }
+  return acc;
+}
+
 __device__ __forceinline__ int lane_id() { return threadIdx.x & 63; }
 
 // 16 bytes per lane from global memory straight into LDS: lane i's piece lands at

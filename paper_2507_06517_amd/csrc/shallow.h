@@ -148,31 +148,6 @@ __device__ __forceinline__ const char *x_row(const ShallowParams &p, int ut, int
   return p.X[t] + kv_unit_offset(p.lay, u) + (size_t)a * (size_t)p.lay.st;
 }
 
-// x_a . x_b in double precision, summed in dimension order (products are exact).
-template <int DT, int kBatch = 8>                      // kBatch: 16-byte pieces of each row in flight
-__device__ double dot64(const char *ra, const char *rb) {
-  typedef typename Elem<DT>::type T;
-  constexpr int per = 16 / sizeof(T);
-  double acc = 0.0;
-  for (int c0 = 0; c0 < kHeadDim / per; c0 += kBatch) {
-    u4 va[kBatch], vb[kBatch];
-#pragma unroll
-    for (int i = 0; i < kBatch; ++i) {
-      va[i] = reinterpret_cast<const u4 *>(ra)[c0 + i];
-      vb[i] = reinterpret_cast<const u4 *>(rb)[c0 + i];
-    }
-#pragma unroll
-    for (int i = 0; i < kBatch; ++i) {
-      const T *ea = reinterpret_cast<const T *>(&va[i]);
-      const T *eb = reinterpret_cast<const T *>(&vb[i]);
-#pragma unroll
-      for (int j = 0; j < per; ++j)
-        acc += (double)Elem<DT>::to_float(ea[j]) * (double)Elem<DT>::to_float(eb[j]);
-    }
-  }
-  return acc;
-}
-
 __device__ inline double dot64_any(int dtype, const char *ra, const char *rb) {
   if (dtype == SPINDLE_F16) return dot64<SPINDLE_F16>(ra, rb);
   if (dtype == SPINDLE_BF16) return dot64<SPINDLE_BF16>(ra, rb);

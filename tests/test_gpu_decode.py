@@ -237,6 +237,43 @@ def test_two_steps_in_a_row(oracle):
     run_and_check(oracle, second, Cb1, nc1, dtype, theta)
 
 
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
+@pytest.mark.parametrize("m", [5, 31, 33, 64, 65, 128, 129, 256, 257])
+def test_unmatched_tokens_around_the_tiles(oracle, dtype, m):
+    # nothing stored: all tokens are unmatched, around the 32 x 32 tiles of their pairs and the 64, 128 and 256 tokens
+    # that one wave builds from; clusters of a size each, some of them with cosines close to the threshold
+    rng = np.random.default_rng(m)
+    c = rng.standard_normal((1, 2, 9, 128))
+    which = rng.integers(0, 9, (2, m)) * (rng.random((2, m)) < 0.8)
+    new = np.stack([c[0, h, which[h]] for h in range(2)])[None] + rng.choice([0.1, 0.225], (1, 2, m, 1)) * rng.standard_normal((1, 2, m, 128))
+    lone = rng.random((1, 2, m, 1)) < 0.2
+    new = wl.cast(np.where(lone, rng.standard_normal(new.shape), new), dtype)
+    run_and_check(oracle, new, wl.cast(np.zeros((1, 2, m + 3, 128)), dtype), np.zeros((1, 2), np.int32), dtype, 0.95)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
+@pytest.mark.parametrize("m", [1, 4, 40])
+def test_equal_entries_and_rows_out_of_range(oracle, dtype, m):
+    # 1100 stored rows: 700 equal ones (more candidates than a list of the decode step holds: the lowest wins), zero
+    # rows, rows whose products leave fp32; tokens equal to them, zero, tiny and huge; around slices of 512
+    rng = np.random.default_rng(5)
+    small, big = {"f16": (2.0 ** -14, 256.0), "bf16": (2.0 ** -60, 2.0 ** 58), "f32": (2.0 ** -60, 2.0 ** 62)}[dtype]
+    ent = rng.standard_normal((1100, 128))
+    ent[300:1000] = ent[300]
+    ent[[7, 511, 512, 1099]] = 0.0
+    ent[20] *= small
+    ent[21] *= big
+    new = np.concatenate([ent[[300, 20, 21, 5]], rng.standard_normal((36, 128))])
+    new[4], new[5], new[6], new[7], new[8] = ent[20] * 3.0, 0.0, ent[5] * small, ent[5] * big, ent[1000]
+    Cb = wl.cast(np.concatenate([ent, np.zeros((60, 128))])[None, None], dtype)
+    for theta in (0.95, -0.5):
+        for first in range(0, 9, m):
+            n = wl.cast(new[first:first + m][None, None], dtype)
+            res, _, _ = run_and_check(oracle, n, Cb, np.array([[1100]], np.int32), dtype, theta)
+            if first == 0:
+                assert res[0]["ref"][0] == 300
+
+
 def test_rejects_bad_arguments():
     import torch
     from paper_2507_06517_amd import binding as sb
