@@ -72,13 +72,47 @@ struct Geo {
 #pragma unroll
     for (int j = 0; j < kLoadsPerWave; ++j) lds_dma16_at(base, off[j], lds + (wave * kLoadsPerWave + j) * 1024);
   }
-  // MFMA operand fragment ks of staged key `row` for lane group g
-  static __device__ __forceinline__ typename M::frag frag(const char *buf, int row, int ks, int g) {
+  static constexpr int kFrags = DT == SPINDLE_F32 ? 16 : 8;        // 16-byte pieces of a row per lane group
+  // MFMA operand pieces j of staged row `row` for lane group g: piece 2 j + g (one step of a 16-bit type; four of
+  // fp32, whose lane groups may hold any dimensions as long as both operands agree)
+  static __device__ __forceinline__ u4 piece(const char *buf, int row, int j, int g) {
+    return *reinterpret_cast<const u4 *>(buf + row * kRowBytes + (((2 * j + g) ^ (row & (kPieces - 1))) << 4));
+  }
+  static __device__ __forceinline__ f16v mma(u4 a, u4 b, f16v c) {
     if constexpr (DT == SPINDLE_F32) {
-      const int e = 2 * ks + g;
-      return *reinterpret_cast<const float *>(buf + row * kRowBytes + ((((e >> 2) ^ (row & 31)) << 4) | ((e & 3) << 2)));
+#pragma unroll
+      for (int i = 0; i < 4; ++i) c = M::mma(__uint_as_float(a[i]), __uint_as_float(b[i]), c);
+      return c;
     } else {
-      return *reinterpret_cast<const typename M::frag *>(buf + row * kRowBytes + (((2 * ks + g) ^ (row & 15)) << 4));
+      return M::mma(__builtin_bit_cast(typename M::frag, a), __builtin_bit_cast(typename M::frag, b), c);
+    }
+  }
+  // The wave's 64 query rows (row group wr of WR) into registers, through a stage buffer.  Everything loaded to LDS
+  // before has landed for every wave when this returns, and the buffer is free again.
+  template <int WR>
+  static __device__ __forceinline__ void queries(u4 (&qf)[2][kFrags], const char *Qunit, int R, const char *buf, uint32_t lds, int wr,
+                                                 int wave, int lane) {
+    constexpr int kAtOnce = 64 * WR < kStageKeys ? 64 * WR : kStageKeys;
+#pragma unroll
+    for (int q0 = 0; q0 < 64 * WR; q0 += kAtOnce) {
+      load_queries(Qunit, q0, kAtOnce, R, lds, wave, lane);
+      __builtin_amdgcn_s_waitcnt(0x0F70);              // vmcnt(0): this wave's part has landed
+      __syncthreads();
+      if (64 * wr >= q0 && 64 * wr < q0 + kAtOnce)     // wave-uniform
+#pragma unroll
+        for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+          for (int j = 0; j < kFrags; ++j) qf[rb][j] = piece(buf, 64 * wr - q0 + 32 * rb + (lane & 31), j, lane >> 5);
+      __builtin_amdgcn_s_waitcnt(0xC07F);              // lgkmcnt(0): read
+      __syncthreads();
+    }
+  }
+  // Query rows q0 .. q0 + n - 1 of a unit of R (the last one again past them) into `lds` as a stage is.
+  static __device__ __forceinline__ void load_queries(const char *Qunit, int q0, int n, int R, uint32_t lds, int wave, int lane) {
+    for (int q = wave; q < n / kRowsPerLoad; q += kWaves) {
+      const int r = q * kRowsPerLoad + lane / kPieces;
+      const int piece = (lane % kPieces) ^ (r & (kPieces - 1));
+      lds_dma16(Qunit + (size_t)min(q0 + r, R - 1) * kRowBytes + piece * 16, lds + q * 1024);
     }
   }
 };
@@ -159,20 +193,18 @@ __global__ __launch_bounds__(Geo<DT>::kThreads) void deep_stats(DeepParams p) {
   };
   stage_load(key_begin, lds0);
 
-  // query fragments stay in registers for the whole block
-  typename M::frag qf[2][M::kSteps];
+  // Query fragments stay in registers for the whole block.  They come through the second stage buffer (fp32: 128
+  // rows at a time): read in fragment order, where lanes next to each other have different rows, the 64 KiB of 256
+  // rows take a compute unit 4 us.
+  u4 qf[2][S::kFrags];
+  S::template queries<WR>(qf, Qunit, p.R, smem + S::kStageBytes, lds0 + S::kStageBytes, wr, wave, lane);
   int klim[2];                                         // last key this lane's query row may attend to
 #pragma unroll
   for (int rb = 0; rb < 2; ++rb) {
     const int row = 64 * wr + 32 * rb + c;
-#pragma unroll
-    for (int ks = 0; ks < M::kSteps; ++ks)
-      qf[rb][ks] = row < p.R ? M::load(Qunit + (size_t)row * M::kRowBytes, ks, g) : M::zero();
     klim[rb] = row < p.R ? p.lc + row % p.lw : -1;    // causal mask: query b of the window sits at l_c + b
   }
   float m[2] = {-INFINITY, -INFINITY}, z[2] = {0.f, 0.f};
-  __builtin_amdgcn_s_waitcnt(0x0F70);                  // vmcnt(0): this wave's part of the stage has landed
-  __syncthreads();
 
   for (int s = 0; s < nst; ++s) {
     const int k0 = key_begin + s * S::kStageKeys;
@@ -182,10 +214,10 @@ __global__ __launch_bounds__(Geo<DT>::kThreads) void deep_stats(DeepParams p) {
     // The fragments of a tile are fetched from LDS together, those of the wave's next tile right
     // after the matrix instructions of the current one are issued, so that the LDS latency falls
     // into the vector work on the results (the other wave of the SIMD multiplies meanwhile).
-    typename M::frag kf[kPrefetch ? M::kSteps : 1];
+    u4 kf[kPrefetch ? S::kFrags : 1];
     if (kPrefetch && k0 + wk * 32 < p.l) {
 #pragma unroll
-      for (int ks = 0; ks < M::kSteps; ++ks) kf[kPrefetch ? ks : 0] = S::frag(buf, wk * 32 + c, ks, g);
+      for (int j = 0; j < S::kFrags; ++j) kf[kPrefetch ? j : 0] = S::piece(buf, wk * 32 + c, j, g);
     }
 #pragma unroll
     for (int t = 0; t < kTilesPerWave; ++t) {
@@ -199,22 +231,22 @@ __global__ __launch_bounds__(Geo<DT>::kThreads) void deep_stats(DeepParams p) {
         for (int v = 0; v < 16; ++v) acc[rb][v] = 0.f;
       if (kPrefetch) {
 #pragma unroll
-        for (int ks = 0; ks < M::kSteps; ++ks) {
-          acc[0] = M::mma(kf[kPrefetch ? ks : 0], qf[0][ks], acc[0]);
-          acc[1] = M::mma(kf[kPrefetch ? ks : 0], qf[1][ks], acc[1]);
+        for (int j = 0; j < S::kFrags; ++j) {
+          acc[0] = S::mma(kf[kPrefetch ? j : 0], qf[0][j], acc[0]);
+          acc[1] = S::mma(kf[kPrefetch ? j : 0], qf[1][j], acc[1]);
         }
         __builtin_amdgcn_sched_barrier(0);
         if (t + 1 < kTilesPerWave && tk0 + WK * 32 < p.l) {
 #pragma unroll
-          for (int ks = 0; ks < M::kSteps; ++ks) kf[kPrefetch ? ks : 0] = S::frag(buf, (ct + WK) * 32 + c, ks, g);
+          for (int j = 0; j < S::kFrags; ++j) kf[kPrefetch ? j : 0] = S::piece(buf, (ct + WK) * 32 + c, j, g);
         }
         __builtin_amdgcn_sched_barrier(0);
       } else {
 #pragma unroll
-        for (int ks = 0; ks < M::kSteps; ++ks) {
-          const typename M::frag f = S::frag(buf, ct * 32 + c, ks, g);
-          acc[0] = M::mma(f, qf[0][ks], acc[0]);
-          acc[1] = M::mma(f, qf[1][ks], acc[1]);
+        for (int j = 0; j < S::kFrags; ++j) {
+          const u4 f = S::piece(buf, ct * 32 + c, j, g);
+          acc[0] = S::mma(f, qf[0][j], acc[0]);
+          acc[1] = S::mma(f, qf[1][j], acc[1]);
         }
       }
 #pragma unroll
@@ -334,16 +366,8 @@ __global__ __launch_bounds__(Geo<DT>::kThreads) void deep_accumulate(DeepParams 
     row_const[row] = row < p.R && zz > 0.f ? mm + log2f(zz) : INFINITY;        // rows of the padding weigh nothing
   }
 
-  typename M::frag qf[2][M::kSteps];
-#pragma unroll
-  for (int rb = 0; rb < 2; ++rb) {
-    const int row = 64 * wr + 32 * rb + c;
-#pragma unroll
-    for (int ks = 0; ks < M::kSteps; ++ks)
-      qf[rb][ks] = row < p.R ? M::load(Qunit + (size_t)row * M::kRowBytes, ks, g) : M::zero();
-  }
-  __builtin_amdgcn_s_waitcnt(0x0F70);
-  __syncthreads();
+  u4 qf[2][S::kFrags];
+  S::template queries<WR>(qf, Qunit, p.R, smem + S::kStageBytes, lds0 + S::kStageBytes, wr, wave, lane);   // as in deep_stats
   float cst[2][16];
 #pragma unroll
   for (int rb = 0; rb < 2; ++rb)
@@ -355,10 +379,10 @@ __global__ __launch_bounds__(Geo<DT>::kThreads) void deep_accumulate(DeepParams 
     if (s + 1 < nst) stage_load(k0 + S::kStageKeys, lds0 + ((s + 1) & 1) * S::kStageBytes);
     const char *buf = smem + (s & 1) * S::kStageBytes;
     float *cp = colpart + (s & 1) * (WR * S::kStageKeys);
-    typename M::frag kf[kPrefetch ? M::kSteps : 1];    // as in deep_stats
+    u4 kf[kPrefetch ? S::kFrags : 1];    // as in deep_stats
     if (kPrefetch && k0 + wk * 32 < p.lc) {
 #pragma unroll
-      for (int ks = 0; ks < M::kSteps; ++ks) kf[kPrefetch ? ks : 0] = S::frag(buf, wk * 32 + c, ks, g);
+      for (int j = 0; j < S::kFrags; ++j) kf[kPrefetch ? j : 0] = S::piece(buf, wk * 32 + c, j, g);
     }
 #pragma unroll
     for (int t = 0; t < kTilesPerWave; ++t) {
@@ -371,22 +395,22 @@ __global__ __launch_bounds__(Geo<DT>::kThreads) void deep_accumulate(DeepParams 
         for (int v = 0; v < 16; ++v) acc[rb][v] = 0.f;
       if (kPrefetch) {
 #pragma unroll
-        for (int ks = 0; ks < M::kSteps; ++ks) {
-          acc[0] = M::mma(qf[0][ks], kf[kPrefetch ? ks : 0], acc[0]);
-          acc[1] = M::mma(qf[1][ks], kf[kPrefetch ? ks : 0], acc[1]);
+        for (int j = 0; j < S::kFrags; ++j) {
+          acc[0] = S::mma(qf[0][j], kf[kPrefetch ? j : 0], acc[0]);
+          acc[1] = S::mma(qf[1][j], kf[kPrefetch ? j : 0], acc[1]);
         }
         __builtin_amdgcn_sched_barrier(0);
         if (t + 1 < kTilesPerWave && k0 + (ct + WK) * 32 < p.lc) {
 #pragma unroll
-          for (int ks = 0; ks < M::kSteps; ++ks) kf[kPrefetch ? ks : 0] = S::frag(buf, (ct + WK) * 32 + c, ks, g);
+          for (int j = 0; j < S::kFrags; ++j) kf[kPrefetch ? j : 0] = S::piece(buf, (ct + WK) * 32 + c, j, g);
         }
         __builtin_amdgcn_sched_barrier(0);
       } else {
 #pragma unroll
-        for (int ks = 0; ks < M::kSteps; ++ks) {
-          const typename M::frag f = S::frag(buf, ct * 32 + c, ks, g);
-          acc[0] = M::mma(qf[0][ks], f, acc[0]);
-          acc[1] = M::mma(qf[1][ks], f, acc[1]);
+        for (int j = 0; j < S::kFrags; ++j) {
+          const u4 f = S::piece(buf, ct * 32 + c, j, g);
+          acc[0] = S::mma(qf[0][j], f, acc[0]);
+          acc[1] = S::mma(qf[1][j], f, acc[1]);
         }
       }
       float cs0 = 0.f, cs1 = 0.f;
