@@ -24,18 +24,21 @@ namespace spindle {
 namespace {
 
 constexpr float kLog2e = 1.4426950408889634f;
-constexpr int kMaxStagesPerBlock = 4;
+constexpr int kMaxStagesPerBlock = 16;
 constexpr int kBins = 4096;          // histogram over the top 12 bits of the order-preserving score keys
 
-// Staging geometry of one element type: a stage is 64 KiB of keys.
-template <int DT>
+// Staging geometry: KEYS keys per stage, WR waves split the (padded) query rows in groups of 32, the others the 32-key
+// tiles of a stage.  Sixteen waves where there are tiles for them: with 32 rows a wave fits 128 registers, and four
+// waves per SIMD find each other in different phases, so that the matrix instructions of some run beside the
+// exponentials of others (two waves of 64 rows mostly waited in the same one).
+template <int DT, int WR, int KEYS>
 struct Geo {
   typedef Mma<DT> M;
   static constexpr int kRowBytes = M::kRowBytes;
   static constexpr int kPieces = kRowBytes / 16;                   // 16-byte pieces per key
-  static constexpr int kStageKeys = DT == SPINDLE_F32 ? 128 : 256;
+  static constexpr int kStageKeys = KEYS;
   static constexpr int kStageBytes = kStageKeys * kRowBytes;
-  static constexpr int kWaves = DT == SPINDLE_F32 ? 4 : 8;
+  static constexpr int kWaves = WR * (KEYS / 32) < 16 ? WR * (KEYS / 32) : 16;
   static constexpr int kThreads = 64 * kWaves;
   static constexpr int kTiles = kStageKeys / 32;                   // 32-key MFMA tiles per stage
   static constexpr int kRowsPerLoad = 1024 / kRowBytes;            // keys one wave-wide load brings
@@ -87,22 +90,19 @@ struct Geo {
       return M::mma(__builtin_bit_cast(typename M::frag, a), __builtin_bit_cast(typename M::frag, b), c);
     }
   }
-  // The wave's 64 query rows (row group wr of WR) into registers, through a stage buffer.  Everything loaded to LDS
+  // The wave's 32 query rows (row group wr) into registers, through the second stage buffer.  Everything loaded to LDS
   // before has landed for every wave when this returns, and the buffer is free again.
-  template <int WR>
-  static __device__ __forceinline__ void queries(u4 (&qf)[2][kFrags], const char *Qunit, int R, const char *buf, uint32_t lds, int wr,
+  static __device__ __forceinline__ void queries(u4 (&qf)[kFrags], const char *Qunit, int R, const char *buf, uint32_t lds, int wr,
                                                  int wave, int lane) {
-    constexpr int kAtOnce = 64 * WR < kStageKeys ? 64 * WR : kStageKeys;
+    constexpr int kAtOnce = 32 * WR < kStageKeys ? 32 * WR : kStageKeys;
 #pragma unroll
-    for (int q0 = 0; q0 < 64 * WR; q0 += kAtOnce) {
+    for (int q0 = 0; q0 < 32 * WR; q0 += kAtOnce) {
       load_queries(Qunit, q0, kAtOnce, R, lds, wave, lane);
       __builtin_amdgcn_s_waitcnt(0x0F70);              // vmcnt(0): this wave's part has landed
       __syncthreads();
-      if (64 * wr >= q0 && 64 * wr < q0 + kAtOnce)     // wave-uniform
+      if (32 * wr >= q0 && 32 * wr < q0 + kAtOnce)     // wave-uniform
 #pragma unroll
-        for (int rb = 0; rb < 2; ++rb)
-#pragma unroll
-          for (int j = 0; j < kFrags; ++j) qf[rb][j] = piece(buf, 64 * wr - q0 + 32 * rb + (lane & 31), j, lane >> 5);
+        for (int j = 0; j < kFrags; ++j) qf[j] = piece(buf, 32 * wr - q0 + (lane & 31), j, lane >> 5);
       __builtin_amdgcn_s_waitcnt(0xC07F);              // lgkmcnt(0): read
       __syncthreads();
     }
@@ -116,15 +116,6 @@ struct Geo {
     }
   }
 };
-
-// Stages a block takes: as many as leave about one block per compute unit.  The fixed cost of
-// a block (query fragments, the merge of the chunk statistics) outweighs idle units only while
-// the grid still covers the chip.
-inline int stages_per_block(int U, int l, int stage_keys) {
-  const long total = (long)U * ((l + stage_keys - 1) / stage_keys);
-  const long s = total / 256;
-  return s < 1 ? 1 : (s > kMaxStagesPerBlock ? kMaxStagesPerBlock : (int)s);
-}
 
 struct DeepParams {
   const char *K;       // [U][l][128] elements
@@ -153,14 +144,13 @@ __device__ __forceinline__ uint32_t lds_address(const void *ptr) {
   return (uint32_t)(size_t)(__attribute__((address_space(3))) const char *)ptr;
 }
 
-// Pass 1.  Grid (chunks, units).  WR waves split the (padded) query rows in groups of 64, the
-// other kWaves / WR split the 32-key tiles of a stage.  The matrix product is taken as keys x
+// Pass 1.  Grid (chunks, units).  The matrix product is taken as keys x
 // query rows, so a lane owns one query row (its column of the result) and the sixteen results
 // in its registers are sixteen keys: the running (max, sum) of a row is two registers per lane
 // and needs no exchange until the end of the block.
-template <int DT, int WR>
-__global__ __launch_bounds__(Geo<DT>::kThreads) void deep_stats(DeepParams p) {
-  typedef Geo<DT> S;
+template <int DT, int WR, int KEYS>
+__global__ __launch_bounds__((Geo<DT, WR, KEYS>::kThreads)) void deep_stats(DeepParams p) {
+  typedef Geo<DT, WR, KEYS> S;
   typedef Mma<DT> M;
   constexpr int WK = S::kWaves / WR;
   constexpr int kTilesPerWave = S::kTiles / WK;
@@ -196,15 +186,11 @@ __global__ __launch_bounds__(Geo<DT>::kThreads) void deep_stats(DeepParams p) {
   // Query fragments stay in registers for the whole block.  They come through the second stage buffer (fp32: 128
   // rows at a time): read in fragment order, where lanes next to each other have different rows, the 64 KiB of 256
   // rows take a compute unit 4 us.
-  u4 qf[2][S::kFrags];
-  S::template queries<WR>(qf, Qunit, p.R, smem + S::kStageBytes, lds0 + S::kStageBytes, wr, wave, lane);
-  int klim[2];                                         // last key this lane's query row may attend to
-#pragma unroll
-  for (int rb = 0; rb < 2; ++rb) {
-    const int row = 64 * wr + 32 * rb + c;
-    klim[rb] = row < p.R ? p.lc + row % p.lw : -1;    // causal mask: query b of the window sits at l_c + b
-  }
-  float m[2] = {-INFINITY, -INFINITY}, z[2] = {0.f, 0.f};
+  u4 qf[S::kFrags];
+  S::queries(qf, Qunit, p.R, smem + S::kStageBytes, lds0 + S::kStageBytes, wr, wave, lane);
+  const int qrow = 32 * wr + c;
+  const int klim = qrow < p.R ? p.lc + qrow % p.lw : -1;   // last key this lane's query row may attend to: query b of the window sits at l_c + b
+  float m = -INFINITY, z = 0.f;
 
   for (int s = 0; s < nst; ++s) {
     const int k0 = key_begin + s * S::kStageKeys;
@@ -224,17 +210,12 @@ __global__ __launch_bounds__(Geo<DT>::kThreads) void deep_stats(DeepParams p) {
       const int ct = wk + t * WK;
       const int tk0 = k0 + ct * 32;
       if (tk0 >= p.l) continue;                        // wave-uniform
-      f16v acc[2];
+      f16v acc;
 #pragma unroll
-      for (int rb = 0; rb < 2; ++rb)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[rb][v] = 0.f;
+      for (int v = 0; v < 16; ++v) acc[v] = 0.f;
       if (kPrefetch) {
 #pragma unroll
-        for (int j = 0; j < S::kFrags; ++j) {
-          acc[0] = S::mma(kf[kPrefetch ? j : 0], qf[0][j], acc[0]);
-          acc[1] = S::mma(kf[kPrefetch ? j : 0], qf[1][j], acc[1]);
-        }
+        for (int j = 0; j < S::kFrags; ++j) acc = S::mma(kf[kPrefetch ? j : 0], qf[j], acc);
         __builtin_amdgcn_sched_barrier(0);
         if (t + 1 < kTilesPerWave && tk0 + WK * 32 < p.l) {
 #pragma unroll
@@ -243,46 +224,39 @@ __global__ __launch_bounds__(Geo<DT>::kThreads) void deep_stats(DeepParams p) {
         __builtin_amdgcn_sched_barrier(0);
       } else {
 #pragma unroll
-        for (int j = 0; j < S::kFrags; ++j) {
-          const u4 f = S::piece(buf, ct * 32 + c, j, g);
-          acc[0] = S::mma(f, qf[0][j], acc[0]);
-          acc[1] = S::mma(f, qf[1][j], acc[1]);
-        }
+        for (int j = 0; j < S::kFrags; ++j) acc = S::mma(S::piece(buf, ct * 32 + c, j, g), qf[j], acc);
       }
+      if (!tail) {
+        float hi = acc[0], lo = acc[0];
 #pragma unroll
-      for (int rb = 0; rb < 2; ++rb) {
-        if (!tail) {
-          float hi = acc[rb][0], lo = acc[rb][0];
+        for (int v = 1; v < 16; ++v) hi = fmaxf(hi, acc[v]);
+        if (p.sc2 < 0.f) {                             // uniform; a negative scale turns the order round
 #pragma unroll
-          for (int v = 1; v < 16; ++v) hi = fmaxf(hi, acc[rb][v]);
-          if (p.sc2 < 0.f) {                           // uniform; a negative scale turns the order round
+          for (int v = 1; v < 16; ++v) lo = fminf(lo, acc[v]);
+          hi = lo;
+        }
+        const float mn = fmaxf(m, hi * p.sc2);
+        float sum = 0.f;
 #pragma unroll
-            for (int v = 1; v < 16; ++v) lo = fminf(lo, acc[rb][v]);
-            hi = lo;
-          }
-          const float mn = fmaxf(m[rb], hi * p.sc2);
+        for (int v = 0; v < 16; ++v) sum += __builtin_amdgcn_exp2f(fmaf(acc[v], p.sc2, -mn));
+        z = z * __builtin_amdgcn_exp2f(m - mn) + sum;
+        m = mn;
+      } else {
+        float tv[16];
+        float hi = -INFINITY;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const int key = tk0 + mma_row(v, g);
+          tv[v] = key <= klim && key < p.l ? acc[v] * p.sc2 : -INFINITY;
+          hi = fmaxf(hi, tv[v]);
+        }
+        const float mn = fmaxf(m, hi);
+        if (mn > -INFINITY) {
           float sum = 0.f;
 #pragma unroll
-          for (int v = 0; v < 16; ++v) sum += __builtin_amdgcn_exp2f(fmaf(acc[rb][v], p.sc2, -mn));
-          z[rb] = z[rb] * __builtin_amdgcn_exp2f(m[rb] - mn) + sum;
-          m[rb] = mn;
-        } else {
-          float tv[16];
-          float hi = -INFINITY;
-#pragma unroll
-          for (int v = 0; v < 16; ++v) {
-            const int key = tk0 + mma_row(v, g);
-            tv[v] = key <= klim[rb] && key < p.l ? acc[rb][v] * p.sc2 : -INFINITY;
-            hi = fmaxf(hi, tv[v]);
-          }
-          const float mn = fmaxf(m[rb], hi);
-          if (mn > -INFINITY) {
-            float sum = 0.f;
-#pragma unroll
-            for (int v = 0; v < 16; ++v) sum += __builtin_amdgcn_exp2f(tv[v] - mn);
-            z[rb] = z[rb] * __builtin_amdgcn_exp2f(m[rb] - mn) + sum;
-            m[rb] = mn;
-          }
+          for (int v = 0; v < 16; ++v) sum += __builtin_amdgcn_exp2f(tv[v] - mn);
+          z = z * __builtin_amdgcn_exp2f(m - mn) + sum;
+          m = mn;
         }
       }
     }
@@ -292,21 +266,20 @@ __global__ __launch_bounds__(Geo<DT>::kThreads) void deep_stats(DeepParams p) {
 
   // the two lane groups of a wave hold different keys of the same rows; then the WK waves of a
   // row group through LDS, in wave order
-  float2 *red = reinterpret_cast<float2 *>(smem);      // [WK][64 * WR]
-#pragma unroll
-  for (int rb = 0; rb < 2; ++rb) {
-    const float m2 = __shfl_xor(m[rb], 32), z2 = __shfl_xor(z[rb], 32);
-    float mm = g ? m2 : m[rb], zz = g ? z2 : z[rb];    // same operand order in both lane groups
-    merge_stats(mm, zz, g ? m[rb] : m2, g ? z[rb] : z2);
-    if (g == 0) red[wk * (64 * WR) + 64 * wr + 32 * rb + c] = make_float2(mm, zz);
+  float2 *red = reinterpret_cast<float2 *>(smem);      // [WK][32 * WR]
+  {
+    const float m2 = __shfl_xor(m, 32), z2 = __shfl_xor(z, 32);
+    float mm = g ? m2 : m, zz = g ? z2 : z;            // same operand order in both lane groups
+    merge_stats(mm, zz, g ? m : m2, g ? z : z2);
+    if (g == 0) red[wk * (32 * WR) + qrow] = make_float2(mm, zz);
   }
   __syncthreads();
   const int row = threadIdx.x;
-  if (row < 64 * WR) {
+  if (row < 32 * WR) {
     float2 e = red[row];
 #pragma unroll
     for (int j = 1; j < WK; ++j) {
-      const float2 o = red[j * (64 * WR) + row];
+      const float2 o = red[j * (32 * WR) + row];
       merge_stats(e.x, e.y, o.x, o.y);
     }
     p.partial[((size_t)u * p.nchunks + chunk) * p.Rpad + row] = e;
@@ -317,9 +290,9 @@ __global__ __launch_bounds__(Geo<DT>::kThreads) void deep_stats(DeepParams p) {
 // keys: a lane owns one key and its registers hold sixteen query rows, so the sum over the
 // window queries and the heads of the group is a sum over the lane's own registers.  The
 // weight of (row, key) is exp2(logit - c_row) with c_row = max + log2(sum) of the row.
-template <int DT, int WR>
-__global__ __launch_bounds__(Geo<DT>::kThreads) void deep_accumulate(DeepParams p) {
-  typedef Geo<DT> S;
+template <int DT, int WR, int KEYS>
+__global__ __launch_bounds__((Geo<DT, WR, KEYS>::kThreads)) void deep_accumulate(DeepParams p) {
+  typedef Geo<DT, WR, KEYS> S;
   typedef Mma<DT> M;
   constexpr int WK = S::kWaves / WR;
   constexpr int kTilesPerWave = S::kTiles / WK;
@@ -328,7 +301,12 @@ __global__ __launch_bounds__(Geo<DT>::kThreads) void deep_accumulate(DeepParams 
   float *colpart = reinterpret_cast<float *>(smem + 2 * S::kStageBytes);      // [2][WR][kStageKeys]
   float *row_const = colpart + 2 * WR * S::kStageKeys;                          // [256]
 
-  const int u = blockIdx.y, chunk = blockIdx.x;
+  // The blocks go over the keys from the end, each compute-die's blocks over the ones it had in deep_stats (blocks are
+  // dealt round-robin to the 8 dies): what the caches still hold of the last keys read is read first.  24 layers of
+  // 8192 tokens, 402 MB of keys: 107 -> 97 us.
+  const int nx = gridDim.x, total = nx * gridDim.y, id = blockIdx.y * nx + blockIdx.x;
+  const int item = (id & 7) + 8 * ((total - (id & 7) + 7) / 8 - 1 - id / 8);
+  const int u = item / nx, chunk = item % nx;
   const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int g = lane >> 5, c = lane & 31;
   const int wr = wave % WR, wk = wave / WR;
@@ -352,8 +330,7 @@ __global__ __launch_bounds__(Geo<DT>::kThreads) void deep_accumulate(DeepParams 
   // max + log2(sum) of every query row from the per-chunk statistics of the first pass, merged
   // in chunk order by one thread per row (every block of the unit does the same sum in the same
   // order)
-  if ((int)threadIdx.x < p.Rpad) {
-    const int row = threadIdx.x;
+  for (int row = threadIdx.x; row < p.Rpad; row += S::kThreads) {
     const float2 *part = p.partial + (size_t)u * p.nchunks * p.Rpad + row;
     float mm = -INFINITY, zz = 0.f;
     for (int ch0 = 0; ch0 < p.nchunks; ch0 += 32) {   // 32 records in flight: one trip for 32 k keys
@@ -366,13 +343,11 @@ __global__ __launch_bounds__(Geo<DT>::kThreads) void deep_accumulate(DeepParams 
     row_const[row] = row < p.R && zz > 0.f ? mm + log2f(zz) : INFINITY;        // rows of the padding weigh nothing
   }
 
-  u4 qf[2][S::kFrags];
-  S::template queries<WR>(qf, Qunit, p.R, smem + S::kStageBytes, lds0 + S::kStageBytes, wr, wave, lane);   // as in deep_stats
-  float cst[2][16];
+  u4 qf[S::kFrags];
+  S::queries(qf, Qunit, p.R, smem + S::kStageBytes, lds0 + S::kStageBytes, wr, wave, lane);   // as in deep_stats
+  float cst[16];
 #pragma unroll
-  for (int rb = 0; rb < 2; ++rb)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) cst[rb][v] = row_const[64 * wr + 32 * rb + mma_row(v, g)];
+  for (int v = 0; v < 16; ++v) cst[v] = row_const[32 * wr + mma_row(v, g)];
 
   for (int s = 0; s < nst; ++s) {
     const int k0 = key_begin + s * S::kStageKeys;
@@ -388,17 +363,12 @@ __global__ __launch_bounds__(Geo<DT>::kThreads) void deep_accumulate(DeepParams 
     for (int t = 0; t < kTilesPerWave; ++t) {
       const int ct = wk + t * WK;
       if (k0 + ct * 32 >= p.lc) continue;              // wave-uniform
-      f16v acc[2];
+      f16v acc;
 #pragma unroll
-      for (int rb = 0; rb < 2; ++rb)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[rb][v] = 0.f;
+      for (int v = 0; v < 16; ++v) acc[v] = 0.f;
       if (kPrefetch) {
 #pragma unroll
-        for (int j = 0; j < S::kFrags; ++j) {
-          acc[0] = S::mma(qf[0][j], kf[kPrefetch ? j : 0], acc[0]);
-          acc[1] = S::mma(qf[1][j], kf[kPrefetch ? j : 0], acc[1]);
-        }
+        for (int j = 0; j < S::kFrags; ++j) acc = S::mma(qf[j], kf[kPrefetch ? j : 0], acc);
         __builtin_amdgcn_sched_barrier(0);
         if (t + 1 < kTilesPerWave && k0 + (ct + WK) * 32 < p.lc) {
 #pragma unroll
@@ -407,17 +377,13 @@ __global__ __launch_bounds__(Geo<DT>::kThreads) void deep_accumulate(DeepParams 
         __builtin_amdgcn_sched_barrier(0);
       } else {
 #pragma unroll
-        for (int j = 0; j < S::kFrags; ++j) {
-          const u4 f = S::piece(buf, ct * 32 + c, j, g);
-          acc[0] = S::mma(qf[0][j], f, acc[0]);
-          acc[1] = S::mma(qf[1][j], f, acc[1]);
-        }
+        for (int j = 0; j < S::kFrags; ++j) acc = S::mma(qf[j], S::piece(buf, ct * 32 + c, j, g), acc);
       }
       float cs0 = 0.f, cs1 = 0.f;
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        cs0 += __builtin_amdgcn_exp2f(fmaf(acc[0][v], p.sc2, -cst[0][v]));
-        cs1 += __builtin_amdgcn_exp2f(fmaf(acc[1][v], p.sc2, -cst[1][v]));
+      for (int v = 0; v < 16; v += 2) {
+        cs0 += __builtin_amdgcn_exp2f(fmaf(acc[v], p.sc2, -cst[v]));
+        cs1 += __builtin_amdgcn_exp2f(fmaf(acc[v + 1], p.sc2, -cst[v + 1]));
       }
       // the other sixteen rows of each block of 32 sit in the other lane group
       const uint32_t csb = __float_as_uint(cs0 + cs1);
@@ -426,12 +392,12 @@ __global__ __launch_bounds__(Geo<DT>::kThreads) void deep_accumulate(DeepParams 
     }
     __builtin_amdgcn_s_waitcnt(0x0F70);
     __syncthreads();
-    if ((int)threadIdx.x < S::kStageKeys) {            // fixed-order sum over the row groups
-      const int a = k0 + threadIdx.x;
+    for (int i = threadIdx.x; i < S::kStageKeys; i += S::kThreads) {   // fixed-order sum over the row groups
+      const int a = k0 + i;
       if (a < p.lc) {
         float sum = 0.f;
 #pragma unroll
-        for (int j = 0; j < WR; ++j) sum += cp[j * S::kStageKeys + threadIdx.x];
+        for (int j = 0; j < WR; ++j) sum += cp[j * S::kStageKeys + i];
         float v = sum * p.inv_hn;
         if (p.norm == SPINDLE_NORM_PAPER) v = v / (float)(p.l - a);
         p.scores[(size_t)u * p.lc + a] = v;
@@ -746,19 +712,39 @@ struct DeepLayout {
   float *scores;
   uint32_t *pooled;
   int *hist, *done;
-  int stages, nchunks;
+  int keys, stages, nchunks;   // keys per stage, stages per block
   size_t bytes;
 };
 
-int stage_keys_of(int dtype) { return dtype == SPINDLE_F32 ? Geo<SPINDLE_F32>::kStageKeys : Geo<SPINDLE_F16>::kStageKeys; }
-static_assert(Geo<SPINDLE_F16>::kStageKeys == Geo<SPINDLE_BF16>::kStageKeys, "one stage size for the 16-bit types");
+// Keys per stage and stages per block: whatever ends first if 256 blocks run at a time.  A stage of 64 KiB takes about
+// 3.4 us, whatever its size some 0.1 of that more (the barrier), a block 1.2 of it (launch, query fragments, first stage,
+// merges): many blocks are as bad as a last round of few.  Statistics, weights and the rest of the call on fp16
+// keys, us: 24 layers of 8192 tokens with 4 stages per block 282, with 6 276, with 8 (three whole rounds) 253; 32 heads of 32768
+// tokens 251, 236 and 227.
+constexpr int kBlocksAtOnce = 256;
+
+void choose_stages(int U, int l, int dtype, int *keys, int *stages) {
+  const int full = dtype == SPINDLE_F32 ? 128 : 256;
+  double best = INFINITY;
+  for (int k = full; k >= 32; k /= 2) {
+    const int n = (l + k - 1) / k;
+    for (int s = 1; s <= kMaxStagesPerBlock; ++s) {
+      const long blocks = (long)U * ((n + s - 1) / s), rounds = (blocks + kBlocksAtOnce - 1) / kBlocksAtOnce;
+      const double t = (double)rounds * (s * ((double)k / full + 0.1) + 1.2);
+      if (t < best) {
+        best = t;
+        *keys = k;
+        *stages = s;
+      }
+    }
+  }
+}
 
 DeepLayout deep_layout(void *ws, int U, int l, int lw, int Rpad, int dtype) {
   Carver cv(ws);
   DeepLayout L;
-  const int sk = stage_keys_of(dtype);
-  L.stages = stages_per_block(U, l, sk);
-  L.nchunks = (l + L.stages * sk - 1) / (L.stages * sk);
+  choose_stages(U, l, dtype, &L.keys, &L.stages);
+  L.nchunks = (l + L.stages * L.keys - 1) / (L.stages * L.keys);
   const int lc = l - lw;
   L.partial = cv.take<float2>((size_t)U * L.nchunks * Rpad);
   L.scores = cv.take<float>((size_t)U * (lc > 0 ? lc : 1));
@@ -771,30 +757,41 @@ DeepLayout deep_layout(void *ws, int U, int l, int lw, int Rpad, int dtype) {
 
 int padded_rows(int R) { return R <= 64 ? 64 : (R <= 128 ? 128 : 256); }
 
-template <int DT, int WR>
+template <int DT, int WR, int KEYS>
 spindle_status launch_passes(const DeepParams &p, int U, hipStream_t st) {
-  typedef Geo<DT> S;
-  const size_t smem_stats = 2 * (size_t)S::kStageBytes;
+  typedef Geo<DT, WR, KEYS> S;
+  // two stages; the statistics of the waves, or the sums of the row groups over two stages and a constant per row
+  size_t smem_stats = 2 * (size_t)S::kStageBytes;
+  if (smem_stats < (size_t)S::kThreads * sizeof(float2)) smem_stats = (size_t)S::kThreads * sizeof(float2);
   const size_t smem_acc = 2 * (size_t)S::kStageBytes + (2 * WR * S::kStageKeys + 256) * sizeof(float);
   static LdsLimit lim_stats, lim_acc;                  // one pair per instantiation; the sizes are constants of it
-  if (spindle_status e = allow_lds(lim_stats, reinterpret_cast<const void *>(&deep_stats<DT, WR>), smem_stats)) return e;
-  if (spindle_status e = allow_lds(lim_acc, reinterpret_cast<const void *>(&deep_accumulate<DT, WR>), smem_acc)) return e;
+  if (spindle_status e = allow_lds(lim_stats, reinterpret_cast<const void *>(&deep_stats<DT, WR, KEYS>), smem_stats)) return e;
+  if (spindle_status e = allow_lds(lim_acc, reinterpret_cast<const void *>(&deep_accumulate<DT, WR, KEYS>), smem_acc)) return e;
   { ProfScope ps("deep_stats", st);
-  hipLaunchKernelGGL((deep_stats<DT, WR>), dim3(p.nchunks, U), dim3(S::kThreads), smem_stats, st, p); }
+  hipLaunchKernelGGL((deep_stats<DT, WR, KEYS>), dim3(p.nchunks, U), dim3(S::kThreads), smem_stats, st, p); }
   if (p.lc > 0) {
     const int per = p.stages * S::kStageKeys;
     ProfScope ps("deep_accumulate", st);
-    hipLaunchKernelGGL((deep_accumulate<DT, WR>), dim3((p.lc + per - 1) / per, U), dim3(S::kThreads), smem_acc, st, p);
+    hipLaunchKernelGGL((deep_accumulate<DT, WR, KEYS>), dim3((p.lc + per - 1) / per, U), dim3(S::kThreads), smem_acc, st, p);
   }
   SPINDLE_HIP(hipGetLastError());
   return SPINDLE_OK;
 }
 
+template <int DT, int WR>
+spindle_status launch_rows(const DeepParams &p, int keys, int U, hipStream_t st) {
+  if (keys == 32) return launch_passes<DT, WR, 32>(p, U, st);
+  if (keys == 64) return launch_passes<DT, WR, 64>(p, U, st);
+  if (keys == 128) return launch_passes<DT, WR, 128>(p, U, st);
+  if constexpr (DT != SPINDLE_F32) return launch_passes<DT, WR, 256>(p, U, st);
+  SPINDLE_FAIL(SPINDLE_ERR_UNSUPPORTED, "%d keys per stage", keys);
+}
+
 template <int DT>
-spindle_status launch_dtype(const DeepParams &p, int U, hipStream_t st) {
-  if (p.Rpad == 64) return launch_passes<DT, 1>(p, U, st);
-  if (p.Rpad == 128) return launch_passes<DT, 2>(p, U, st);
-  return launch_passes<DT, 4>(p, U, st);
+spindle_status launch_dtype(const DeepParams &p, int keys, int U, hipStream_t st) {
+  if (p.Rpad == 64) return launch_rows<DT, 2>(p, keys, U, st);
+  if (p.Rpad == 128) return launch_rows<DT, 4>(p, keys, U, st);
+  return launch_rows<DT, 8>(p, keys, U, st);
 }
 
 }  // namespace
@@ -863,9 +860,9 @@ extern "C" spindle_status spindle_compress_deep(const spindle_kv_desc *desc, con
   p.sc2 = scale * kLog2e;
   p.inv_hn = 1.0f / (float)desc->group_size;
   p.norm = norm;
-  if (desc->dtype == SPINDLE_F16) s = launch_dtype<SPINDLE_F16>(p, U, st);
-  else if (desc->dtype == SPINDLE_BF16) s = launch_dtype<SPINDLE_BF16>(p, U, st);
-  else s = launch_dtype<SPINDLE_F32>(p, U, st);
+  if (desc->dtype == SPINDLE_F16) s = launch_dtype<SPINDLE_F16>(p, L.keys, U, st);
+  else if (desc->dtype == SPINDLE_BF16) s = launch_dtype<SPINDLE_BF16>(p, L.keys, U, st);
+  else s = launch_dtype<SPINDLE_F32>(p, L.keys, U, st);
   if (s != SPINDLE_OK) return s;
 
   SelectParams sp;
