@@ -121,8 +121,9 @@ struct DeepParams {
   const char *K;       // [U][l][128] elements
   const char *Q;       // [U][R][128] elements (R = hn*lw rows, head-major)
   float2 *partial;     // [U][nchunks][Rpad] (max, sum) per chunk of keys, logits in base-2 units
-  float *scores;       // [U][lc] group-averaged accumulated attention
-  int *hist;           // [U][kBins] cleared here for deep_select
+  float *scores;       // [U][spitch] group-averaged accumulated attention
+  int spitch;          // l_c rounded up to 4
+  int *hist;           // [U][kBins] cleared here for deep_select (NULL: not needed)
   int *done;           // [U]
   int l, lc, lw, hn, R, Rpad, nchunks;
   int stages;          // stages per block
@@ -162,7 +163,7 @@ __global__ __launch_bounds__((Geo<DT, WR, KEYS>::kThreads)) void deep_stats(Deep
   const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int g = lane >> 5, c = lane & 31;
   const int wr = wave % WR, wk = wave / WR;
-  if (chunk == 0) {                                    // counters of this unit's selection
+  if (chunk == 0 && p.hist) {                          // counters of this unit's selection
     for (int i = threadIdx.x; i < kBins; i += S::kThreads) p.hist[(size_t)u * kBins + i] = 0;
     if (threadIdx.x == 0) p.done[u] = 0;
   }
@@ -400,7 +401,7 @@ __global__ __launch_bounds__((Geo<DT, WR, KEYS>::kThreads)) void deep_accumulate
         for (int j = 0; j < WR; ++j) sum += cp[j * S::kStageKeys + i];
         float v = sum * p.inv_hn;
         if (p.norm == SPINDLE_NORM_PAPER) v = v / (float)(p.l - a);
-        p.scores[(size_t)u * p.lc + a] = v;
+        p.scores[(size_t)u * p.spitch + a] = v;
       }
     }
   }
@@ -408,7 +409,7 @@ __global__ __launch_bounds__((Geo<DT, WR, KEYS>::kThreads)) void deep_accumulate
 
 // ---------------------------------------------------------------- pool + top-k
 struct SelectParams {
-  const float *scores;   // [U][lc]
+  const float *scores;   // [U][spitch]
   uint32_t *pooled;      // [U][lc] pooled scores as order-preserving keys
   float *scores_out;     // optional [U][lc]
   int *hist;             // [U][kBins], zero on entry
@@ -416,7 +417,18 @@ struct SelectParams {
   const int32_t *budgets;
   int32_t *kept;         // [U][out_stride]
   int l, lc, lw, pool, budget, out_stride, nseg;
+  int spitch;            // floats per unit of `scores`, a multiple of 4
 };
+
+// How many context tokens unit u keeps.
+__device__ __forceinline__ int kept_context(const SelectParams &p, int u) {
+  int budget = p.budgets ? p.budgets[u] : p.budget;
+  if (budget < p.lw) budget = p.lw;
+  int k = budget - p.lw;
+  if (k > p.lc) k = p.lc;
+  if (k > p.out_stride - p.lw) k = p.out_stride - p.lw;   // never write past the row pitch
+  return k;
+}
 
 constexpr int kSelThreads = 1024;
 constexpr int kSegLen = 2048;        // context positions per workgroup
@@ -502,6 +514,253 @@ __device__ void radix_step(const uint32_t *src, int nsrc, bool other_groups_wrot
   __syncthreads();
 }
 
+// One workgroup per unit, everything on chip: the raw scores go to LDS, a lane pools four neighbouring positions at a
+// time and puts their keys in the place of the scores; histogram of the top 12 bits, the k-th largest among the keys
+// of its bin by comparing all of them, ordered compaction.
+// Bound by latency and by the instructions of one compute unit; loops stay rolled, since a cold kernel also waits for
+// its code (36 KB of it, unrolled with the keys in registers: 1.5 to 3 us more).  The segments of a unit over several
+// workgroups (deep_select) take 16 us for a unit of 480 positions, 22 for eight of 4064, 66 for 192 of 8160 and 24 for eight
+// of 32704; this 7, 10, 15 and 27.
+constexpr int kUnitMax = 16384, kUnitRadius = 8;
+constexpr int kUnitStep = 4 * kSelThreads;             // positions of the workgroup per step
+constexpr int kUnitLoads = kUnitMax / kUnitStep;
+constexpr int kUnitRank = 1024;                        // keys of one bin that are ranked by comparing all of them
+constexpr int kCopies = 4;                             // of the histogram, by lane, so that equal digits collide less;
+constexpr int kCopyPitch = kBins + 8;                  // in other banks
+__host__ __device__ inline int unit_raw(int lc) { return (lc + kUnitStep - 1) / kUnitStep * kUnitStep + 2 * kUnitRadius; }
+inline size_t unit_lds(int lc) { return ((size_t)unit_raw(lc) + kCopies * kCopyPitch) * sizeof(int); }
+
+// Sum over the lanes up to this one, by lane shifts (no trip through LDS).
+__device__ __forceinline__ int lanes_up_to(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);   // row_shr 1, 2, 4, 8 within 16 lanes
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);   // lane 15 of rows 0 and 2 to the row behind
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);   // lane 31 to the two rows behind
+  return v;
+}
+
+__global__ __launch_bounds__(kSelThreads) void deep_select_unit(SelectParams p) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  __shared__ __attribute__((aligned(16))) uint32_t cand[kUnitRank + 4];
+  __shared__ int wtotal[2][kSelThreads / 64];
+  __shared__ int hist256[256];
+  __shared__ uint32_t sh_prefix;
+  __shared__ int sh_krem, sh_ncand;
+  constexpr int kWaves = kSelThreads / 64;
+  const int u = blockIdx.x, tid = threadIdx.x, lane = lane_id(), wave = tid >> 6, lc = p.lc;
+  const float *raw = p.scores + (size_t)u * p.spitch;
+  const int steps = (lc + kUnitStep - 1) / kUnitStep, run = steps * 256;   // of 256 positions; of a wave
+  const int w0 = wave * run + 4 * lane;                // step i of a lane: positions w0 + 256 i ..
+  float *rawl = reinterpret_cast<float *>(smem) + kUnitRadius;   // scores, then keys, by position; kUnitRadius more at both ends
+  uint32_t *keys = reinterpret_cast<uint32_t *>(rawl);
+  int *hist = reinterpret_cast<int *>(smem) + unit_raw(lc);
+  {
+    float4 v[kUnitLoads];
+#pragma unroll
+    for (int i = 0; i < kUnitLoads; ++i)
+      if (i < steps && w0 + 256 * i < lc) v[i] = *reinterpret_cast<const float4 *>(raw + w0 + 256 * i);
+    for (int i = tid; i < kCopies * kCopyPitch / 4; i += kSelThreads) reinterpret_cast<int4 *>(hist)[i] = make_int4(0, 0, 0, 0);
+#pragma unroll
+    for (int i = 0; i < kUnitLoads; ++i)
+      if (i < steps) {
+        const int left = lc - (w0 + 256 * i);          // positions that exist
+        v[i].x = left < 1 ? -INFINITY : v[i].x;
+        v[i].y = left < 2 ? -INFINITY : v[i].y;
+        v[i].z = left < 3 ? -INFINITY : v[i].z;
+        v[i].w = left < 4 ? -INFINITY : v[i].w;
+        *reinterpret_cast<float4 *>(rawl + w0 + 256 * i) = v[i];
+      }
+  }
+  if (tid < kUnitRadius) rawl[tid - kUnitRadius] = rawl[kWaves * run + tid] = -INFINITY;
+  if (tid == 0) sh_ncand = 0;
+  const int k = kept_context(p, u), r = (p.pool - 1) / 2;
+  int32_t *kept = p.kept + (size_t)u * p.out_stride;
+  __syncthreads();
+
+  // Pooling in place: a step is read before the one in front of it is written, and what the neighbouring waves write
+  // is read before the barrier.
+  {
+    float4 f[5];                                       // positions a - 8 .. a + 11
+    const float4 end0 = *reinterpret_cast<const float4 *>(rawl + (wave + 1) * run), end1 = *reinterpret_cast<const float4 *>(rawl + (wave + 1) * run + 4);
+    auto read = [&](int i) __attribute__((always_inline)) {
+      const float *at = rawl + w0 + 256 * i;
+      f[2] = *reinterpret_cast<const float4 *>(at);
+      if (r > 0) {                                     // uniform, as below
+        f[1] = *reinterpret_cast<const float4 *>(at - 4);
+        f[3] = *reinterpret_cast<const float4 *>(at + 4);
+      }
+      if (r > 4) {
+        f[0] = *reinterpret_cast<const float4 *>(at - 8);
+        f[4] = *reinterpret_cast<const float4 *>(at + 8);
+      }
+      if (i == steps - 1) {                            // (the next wave may have written there)
+        if (lane == 63) { f[3] = end0; f[4] = end1; }
+        if (lane == 62) f[4] = end0;
+      }
+    };
+    read(0);
+    __syncthreads();
+    const bool wide = p.scores_out && (lc & 3) == 0 && (reinterpret_cast<uintptr_t>(p.scores_out) & 15) == 0;
+    int *own = hist + (lane & (kCopies - 1)) * kCopyPitch;
+#pragma unroll 1
+    for (int i = 0; i < steps; ++i) {
+      const int a = w0 + 256 * i;
+      const float *v = reinterpret_cast<const float *>(f);
+      float mx[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) mx[j] = fmaxf(-INFINITY, v[8 + j]);
+#pragma unroll
+      for (int d = 1; d <= kUnitRadius; ++d)
+        if (d <= r) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) mx[j] = fmaxf(mx[j], fmaxf(v[8 + j - d], v[8 + j + d]));
+        }
+      u4 x;                                            // 0 past the end
+#pragma unroll
+      for (int j = 0; j < 4; ++j) x[j] = a + j < lc ? orderable(mx[j]) : 0u;
+      if (wide) {
+        if (a < lc) *reinterpret_cast<float4 *>(p.scores_out + (size_t)u * lc + a) = make_float4(mx[0], mx[1], mx[2], mx[3]);
+      } else if (p.scores_out) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          if (a + j < lc) p.scores_out[(size_t)u * lc + a + j] = mx[j];
+      }
+      int n = 1;                                       // pooled neighbours are often equal: one addition for a run of them
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        if (j < 3 && x[j] >> 20 == x[j < 3 ? j + 1 : 3] >> 20) {
+          ++n;
+        } else {
+          if (x[j]) atomicAdd(&own[x[j] >> 20], n);
+          n = 1;
+        }
+      }
+      if (i + 1 < steps) read(i + 1);
+      *reinterpret_cast<u4 *>(keys + a) = x;
+    }
+  }
+  for (int b = tid; b < p.lw; b += kSelThreads) kept[k + b] = lc + b;
+  for (int j = k + p.lw + tid; j < p.out_stride; j += kSelThreads) kept[j] = -1;
+  if (k == 0) return;
+  if (k >= lc) {
+    for (int a = tid; a < lc; a += kSelThreads) kept[a] = a;
+    return;
+  }
+  __syncthreads();
+
+  // threshold bin: thread t owns four bins, from the top, so that counts add up along the threads
+  {
+    const int bin0 = kBins - 4 - 4 * tid;
+    int4 h = make_int4(0, 0, 0, 0);
+    for (int c = 0; c < kCopies; ++c) {
+      const int4 y = *reinterpret_cast<const int4 *>(hist + c * kCopyPitch + bin0);
+      h.x += y.x; h.y += y.y; h.z += y.z; h.w += y.w;
+    }
+    const int hh[4] = {h.w, h.z, h.y, h.x}, mine = h.x + h.y + h.z + h.w, incl = lanes_up_to(mine);
+    if (lane == 63) wtotal[0][wave] = incl;
+    __syncthreads();
+    int seen = incl - mine;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) seen += w < wave ? wtotal[0][w] : 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      if (seen < k && k <= seen + hh[j]) {
+        sh_prefix = (uint32_t)(bin0 + 3 - j) << 20;
+        sh_krem = k - seen;
+      }
+      seen += hh[j];
+    }
+  }
+  __syncthreads();
+  uint32_t prefix = sh_prefix;                         // to become the key of the k-th largest pooled score
+  int krem = sh_krem;                                  // how many keys equal to it are taken
+  const unsigned long long below = (1ull << lane) - 1ull;
+#pragma unroll 1
+  for (int i = 0; i < steps; ++i) {
+    const u4 x = *reinterpret_cast<const u4 *>(keys + w0 + 256 * i);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const bool in = x[j] >> 20 == prefix >> 20 && x[j] != 0;
+      const unsigned long long mk = __ballot(in);
+      if (mk) {                                        // wave-uniform
+        int at = 0;
+        if (lane == __builtin_ctzll(mk)) at = atomicAdd(&sh_ncand, __popcll(mk));
+        at = __shfl(at, __builtin_ctzll(mk)) + __popcll(mk & below);
+        if (in && at < kUnitRank) cand[at] = x[j];
+      }
+    }
+  }
+  __syncthreads();
+  const int ncand = sh_ncand;
+  if (ncand <= kUnitRank) {
+    if (wave * 64 < ncand) {
+      const uint32_t own = tid < ncand ? cand[tid] : 0u;
+      int gt = 0, eq = 0;
+      for (int j = 0; j < ncand; j += 4) {
+        const u4 y = *reinterpret_cast<const u4 *>(cand + j);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          gt += j + q < ncand && y[q] > own;
+          eq += j + q < ncand && y[q] == own;
+        }
+      }
+      if (tid < ncand && gt < krem && krem <= gt + eq) {
+        sh_prefix = own;
+        sh_krem = krem - gt;
+      }
+    }
+    __syncthreads();
+    prefix = sh_prefix;
+    krem = sh_krem;
+  } else {
+    int bits_left = 20;
+    while (bits_left > 0) radix_step(keys, kWaves * run, false, prefix, krem, bits_left, hist256, &sh_prefix, &sh_krem);
+  }
+
+  // ordered compaction: everything above the threshold, then the first `krem` equal to it; both counts in one word
+  auto count = [&](const u4 &x) __attribute__((always_inline)) {
+    int n = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) n += (x[j] > prefix ? 1 << 16 : 0) + (x[j] == prefix ? 1 : 0);
+    return n;
+  };
+  int total = 0;
+#pragma unroll 1
+  for (int i = 0; i < steps; ++i) total += count(*reinterpret_cast<const u4 *>(keys + w0 + 256 * i));
+  total = lanes_up_to(total);
+  if (lane == 63) wtotal[1][wave] = total;
+  __syncthreads();
+  int gt_seen = 0, eq_seen = 0;
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) {
+    gt_seen += w < wave ? wtotal[1][w] >> 16 : 0;
+    eq_seen += w < wave ? wtotal[1][w] & 0xFFFF : 0;
+  }
+#pragma unroll 1
+  for (int i = 0; i < steps; ++i) {
+    const u4 x = *reinterpret_cast<const u4 *>(keys + w0 + 256 * i);
+    const int own = count(x), incl = lanes_up_to(own);
+    int gt = gt_seen + ((incl - own) >> 16), eq = eq_seen + ((incl - own) & 0xFFFF);
+    if (own)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        if (x[j] > prefix) {
+          kept[gt + (eq < krem ? eq : krem)] = w0 + 256 * i + j;
+          ++gt;
+        } else if (x[j] == prefix) {
+          if (eq < krem) kept[gt + eq] = w0 + 256 * i + j;
+          ++eq;
+        }
+      }
+    const int all = __builtin_amdgcn_readlane(incl, 63);
+    gt_seen += all >> 16;
+    eq_seen += all & 0xFFFF;
+  }
+}
+
+// Units of more than kUnitMax context positions or pooled over more than 2 kUnitRadius + 1 of them.
 // Grid (segments, units).  Every workgroup pools its segment of the raw scores, stores the
 // pooled scores as keys and adds its 4096-bin histogram to the unit's.  The workgroup that
 // finishes last for a unit carries on alone: threshold bin from the histogram, exact value of
@@ -515,7 +774,7 @@ __global__ __launch_bounds__(kSelThreads) void deep_select(SelectParams p) {
   __shared__ int sh_krem, sh_last, sh_ncand;
   const int seg = blockIdx.x, u = blockIdx.y, tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
   const int lc = p.lc;
-  const float *raw = p.scores + (size_t)u * lc;
+  const float *raw = p.scores + (size_t)u * p.spitch;
   uint32_t *pooled = p.pooled + (size_t)u * lc;
   int *ghist = p.hist + (size_t)u * kBins;
 
@@ -557,11 +816,7 @@ __global__ __launch_bounds__(kSelThreads) void deep_select(SelectParams p) {
 
   // ---- the last workgroup of the unit
   int32_t *kept = p.kept + (size_t)u * p.out_stride;
-  int budget = p.budgets ? p.budgets[u] : p.budget;
-  if (budget < p.lw) budget = p.lw;
-  int k = budget - p.lw;
-  if (k > lc) k = lc;
-  if (k > p.out_stride - p.lw) k = p.out_stride - p.lw;   // never write past the row pitch
+  const int k = kept_context(p, u);
 
   constexpr int kWaves = kSelThreads / 64;
   constexpr int kBatch = 32;
@@ -747,7 +1002,7 @@ DeepLayout deep_layout(void *ws, int U, int l, int lw, int Rpad, int dtype) {
   L.nchunks = (l + L.stages * L.keys - 1) / (L.stages * L.keys);
   const int lc = l - lw;
   L.partial = cv.take<float2>((size_t)U * L.nchunks * Rpad);
-  L.scores = cv.take<float>((size_t)U * (lc > 0 ? lc : 1));
+  L.scores = cv.take<float>((size_t)U * (lc > 0 ? (lc + 3) & ~3 : 4));
   L.pooled = cv.take<uint32_t>((size_t)U * (lc > 0 ? lc : 1));
   L.hist = cv.take<int>((size_t)U * kBins);
   L.done = cv.take<int>((size_t)U);
@@ -852,7 +1107,9 @@ extern "C" spindle_status spindle_compress_deep(const spindle_kv_desc *desc, con
   p.Q = static_cast<const char *>(Qw);
   p.partial = L.partial;
   p.scores = L.scores;
-  p.hist = L.hist;
+  p.spitch = (lc + 3) & ~3;
+  const bool by_unit = lc > 0 && lc <= kUnitMax && pool_kernel <= 2 * kUnitRadius + 1;
+  p.hist = by_unit ? nullptr : L.hist;
   p.done = L.done;
   p.l = l; p.lc = lc; p.lw = lw; p.hn = desc->group_size; p.R = R; p.Rpad = Rpad;
   p.stages = L.stages;
@@ -870,10 +1127,14 @@ extern "C" spindle_status spindle_compress_deep(const spindle_kv_desc *desc, con
   sp.hist = L.hist; sp.done = L.done;
   sp.budgets = budgets; sp.kept = kept_idx;
   sp.l = l; sp.lc = lc; sp.lw = lw; sp.pool = pool_kernel; sp.budget = budget; sp.out_stride = out_stride;
+  sp.spitch = p.spitch;
   sp.nseg = lc > 0 ? (lc + kSegLen - 1) / kSegLen : 1;
   {
+    static LdsLimit lim;
+    if ((s = allow_lds(lim, reinterpret_cast<const void *>(&deep_select_unit), unit_lds(kUnitMax))) != SPINDLE_OK) return s;
     ProfScope ps("deep_select", st);
-    hipLaunchKernelGGL(deep_select, dim3(sp.nseg, U), dim3(kSelThreads), 0, st, sp);
+    if (by_unit) hipLaunchKernelGGL(deep_select_unit, dim3(U), dim3(kSelThreads), unit_lds(lc), st, sp);
+    else hipLaunchKernelGGL(deep_select, dim3(sp.nseg, U), dim3(kSelThreads), 0, st, sp);
   }
 
   GatherParams gp;

@@ -82,3 +82,37 @@ def test_deterministic_across_runs():
     b = parity.gpu_deep(L)
     for x, y in zip(a, b):
         assert np.array_equal(x, y)
+
+
+@pytest.mark.parametrize("lc,pool", [(1, 1), (255, 3), (4093, 5), (4096, 9), (4097, 15), (8192, 17), (8190, 19), (16384, 7), (16383, 11),
+                                     (16385, 7)])
+def test_selection_by_unit_and_over_several_workgroups(oracle, lc, pool):
+    # the workgroup per unit takes up to 16384 context positions in steps of 4096, pooled over up to 17; beyond that
+    # segments of 2048; around the steps, the last of them ragged, half of the positions kept and few
+    L = wl.small_random(7, "f16", B=1, H=2, l=lc + 16, hn=1, lw=16, pool=pool, budget=16 + (lc + 1) // 2)
+    parity.check_deep_layer(oracle, L)
+    parity.check_deep_layer(oracle, L, budget=16 + (lc + 40) // 41)
+
+
+@pytest.mark.parametrize("l", [2100, 9000, 17000])
+def test_more_ties_than_are_ranked_at_once(l):
+    # zero queries without the divisor: all scores equal, thousands of candidates for the threshold; the first win
+    L = wl.small_random(8, "f16", B=1, H=1, l=l, hn=4, lw=16, pool=7, budget=1016)
+    L.Qw = np.zeros_like(L.Qw)
+    kept, _, _, _ = parity.gpu_deep(L, norm=1)
+    assert kept[0, 0].tolist() == list(range(1000)) + list(range(l - 16, l))
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
+@pytest.mark.parametrize("H,l,lw,hn", [(1, 33, 16, 4), (1, 700, 32, 4), (2, 2300, 64, 4), (8, 2065, 32, 4), (8, 3000, 16, 4), (60, 1100, 64, 4),
+                                       (130, 600, 16, 1)])
+def test_stage_sizes_and_blocks(oracle, dtype, H, l, lw, hn):
+    # 32 to 256 keys per stage and one to several stages per block, as the number of units and their length have it,
+    # with 64, 128 and 256 query rows; blocks and stages that the sequence does not fill
+    L = wl.small_random(9, dtype, B=1, H=H, l=l, hn=hn, lw=lw, pool=3, budget=lw + l // 7)
+    units = [(0, h) for h in sorted({0, H // 2, H - 1})]
+    p64, k64 = zip(*[[x[0, 0] for x in parity.oracle_deep(oracle, wl.Layer(dtype, L.K[:, h:h + 1], L.V[:, h:h + 1], L.Qw[:, hn * h:hn * (h + 1)],
+                                                                           hn, lw, 3, L.budget, 64), L.budget)] for _, h in units])
+    kept, _, _, sc = parity.gpu_deep(L)
+    for (b, h), p, k in zip(units, p64, k64):
+        parity.check_deep_unit(p, k, sc[b, h], kept[b, h], lw, l, {})
