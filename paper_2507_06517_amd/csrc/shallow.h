@@ -100,7 +100,6 @@ struct ShallowParams {
   uint32_t *serr;          // [UT][n] distance of the sketch from what it stands for, sketch units squared
   uint16_t *bucket;        // [UT][n] pivot of a token
   uint32_t *mean;          // [UT][2] first eight coordinates of the pivots' mean
-  int *first;              // [UT][kPivots] tokens of lower pivots
   uint16_t *hist;          // [UT][order blocks][kPivots] tokens per bucket in each block of tokens
   int8_t *sk;              // [UT][Tp][kTileBytes] sketches by position
   uint32_t *etile;         // [UT][Tp] largest serr of a tile

@@ -46,7 +46,6 @@ size_t carve(ShallowParams &p, void *ws, int UT, int n) {
   p.serr = cv.take<uint32_t>(N);
   p.bucket = cv.take<uint16_t>(N);
   p.mean = cv.take<uint32_t>((size_t)UT * 2);
-  p.first = cv.take<int>((size_t)UT * kPivots);
   p.hist = cv.take<uint16_t>((size_t)UT * ((n + kOrderTokens - 1) / kOrderTokens) * kPivots);
   p.sk = cv.take<int8_t>((size_t)UT * p.Tp * kTileBytes);
   p.todo = cv.take<uint32_t>(scan_blocks(p));

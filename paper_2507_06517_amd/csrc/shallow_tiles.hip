@@ -28,7 +28,7 @@ constexpr float kStepEnd = 0.345f, kStep = 0.388f, kMeanSome = 0.15f, kMeanMost 
 constexpr int kMeanOf = 128;
 constexpr int kPivotThreads = 256;
 
-__global__ __launch_bounds__(kPivotThreads) void shallow_pivots(ShallowParams p, int npiv, int nblk) {
+__global__ __launch_bounds__(kPivotThreads, 2) void shallow_pivots(ShallowParams p, int npiv, int nblk) {
   __shared__ __attribute__((aligned(16))) char piv[kPivots * kSketchBytes];    // fragment order: tile, half, lane
   __shared__ uint32_t cnt[kPivots];
   __shared__ __attribute__((aligned(16))) int init[kPivots];                   // what is taken off a pivot's products
@@ -136,7 +136,9 @@ __global__ __launch_bounds__(kPivotThreads) void shallow_pivots(ShallowParams p,
     }
   }
   __syncthreads();
-  int best[4] = {INT32_MIN, INT32_MIN, INT32_MIN, INT32_MIN};
+  // Per tile of pivots the largest product's step and, in the four bits below it, the first result register that has it; a
+  // later tile only counts if its step is higher.
+  int best[4] = {INT32_MIN, INT32_MIN, INT32_MIN, INT32_MIN}, best_pt[4] = {0, 0, 0, 0};
   auto compare = [&](auto first) __attribute__((always_inline)) {   // first(pt): what the products of a pivot tile start at
     for (int pt = 0; pt < npiv / 32; ++pt) {
       const i4v a0 = *reinterpret_cast<const i4v *>(piv + pt * kTileBytes + lane * 16);
@@ -147,11 +149,12 @@ __global__ __launch_bounds__(kPivotThreads) void shallow_pivots(ShallowParams p,
         i16v acc = off4;
         acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(a0, bf[r][0], acc, 0, 0, 0);
         acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(a1, bf[r][1], acc, 0, 0, 0);
+        int m = (acc[0] & mask) | 15;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int x = (acc[v] & mask) | (kPivots - 1 - (pt * 32 + mma_row(v, g)));
-          best[r] = x > best[r] ? x : best[r];
-        }
+        for (int v = 1; v < 16; ++v) m = max(m, (acc[v] & mask) | (15 - v));
+        const bool higher = (m & mask) > best[r];
+        best[r] = higher ? m : best[r];
+        best_pt[r] = higher ? pt : best_pt[r];
       }
     }
   };
@@ -174,8 +177,9 @@ __global__ __launch_bounds__(kPivotThreads) void shallow_pivots(ShallowParams p,
   }
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
-    const int o = __shfl_xor(best[r], 32);
-    const int b = kPivots - 1 - ((o > best[r] ? o : best[r]) & (kPivots - 1));
+    const int own = (best[r] & mask) | (kPivots - 1 - (best_pt[r] * 32 + mma_row(15 - (best[r] & 15), g)));
+    const int o = __shfl_xor(own, 32);
+    const int b = kPivots - 1 - ((o > own ? o : own) & (kPivots - 1));
     if (g == 0 && tok[r] < n) {
       p.bucket[(size_t)ut * n + tok[r]] = (uint16_t)b;
       atomicAdd(&cnt[b], 1u);
@@ -214,56 +218,106 @@ __global__ __launch_bounds__(kPivots) void shallow_order(ShallowParams p, int nb
   __syncthreads();
   for (int w = 0; w < wave; ++w) incl += wsum[w];
   cursor[tid] = incl - total + before;
-  if (blk == 0) p.first[(size_t)ut * kPivots + tid] = incl - total;
   __syncthreads();
   const int tok = blk * kOrderTokens + tid;
   if (tid < kOrderTokens && tok < n) p.perm[base + atomicAdd(&cursor[p.bucket[base + tok]], 1)] = (uint16_t)tok;
 }
 
 // A window of 2048 places in that order: the tokens of each pivot sorted by eight signs of their
-// sketches less the mean (a token counts the ones of its pivot that go before it), which keeps together what has no
+// sketches less the mean, which keeps together what has no
 // pivot of its own.  Then everything later kernels read by position.  Sketches go to fragment order:
 // tile, half of the 64 bytes, lane.
+// Tokens of a pivot with fewer than kFew in the window count the ones that go before them; more are counted by signs
+// (256 bins per pivot, of which no more than kMany fit the window).  Where all of them were compared, isolated tokens, which
+// stand with the lowest pivots, cost 2048 comparisons each: WINDOW_US; a bitonic sort took longer than comparing clusters.
 constexpr int kWindow = 2048;
 constexpr int kWindowThreads = 1024;
+constexpr int kFew = 64, kMany = kWindow / kFew;
 
 __global__ __launch_bounds__(kWindowThreads) void shallow_window(ShallowParams p, int nwin) {
-  __shared__ __attribute__((aligned(16))) uint32_t order_by[kWindow];   // signs << 16 | place in the window
+  __shared__ uint16_t order_by[kWindow];               // pivots, then the tokens' signs by place
   __shared__ uint16_t at_place[kWindow];
+  __shared__ int first[kPivots], last[kPivots];        // places of a pivot's tokens
+  __shared__ __attribute__((aligned(16))) int count[kMany][256];
+  __shared__ uint8_t slot[kPivots];
+  __shared__ int nslots;
   const int item = xcd_item();
   if (item >= p.UT * nwin) return;
   const int ut = item / nwin, n = p.n, w0 = (item % nwin) * kWindow, w1 = min(n, w0 + kWindow);
   const size_t base = (size_t)ut * n;
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
   const uint2 mean = reinterpret_cast<const uint2 *>(p.mean)[ut];
-  int tok[2], lo[2], hi[2];
+  static_assert(kWindow == 2 * kWindowThreads && kPivots == kWindowThreads, "two places per thread");
+  int tok[2], b[2], signs[2];
 #pragma unroll
   for (int k = 0; k < 2; ++k) {
     const int i = tid + k * kWindowThreads;
-    tok[k] = -1;
-    if (w0 + i < w1) {
-      tok[k] = (int)p.perm[base + w0 + i];
-      const int b = (int)p.bucket[base + tok[k]];
-      const int *first = p.first + (size_t)ut * kPivots + b;
-      lo[k] = max(first[0], w0) - w0;
-      hi[k] = min(b + 1 < kPivots ? first[1] : n, w1) - w0;
-      const uint2 s = *reinterpret_cast<const uint2 *>(p.sk0 + (base + tok[k]) * kSketchBytes);
-      uint32_t signs = 0;
+    tok[k] = w0 + i < w1 ? (int)p.perm[base + w0 + i] : -1;
+  }
+  for (int i = tid; i < kMany * 256 / 4; i += kWindowThreads) reinterpret_cast<int4 *>(&count[0][0])[i] = make_int4(0, 0, 0, 0);
+  if (tid == 0) nslots = 0;
 #pragma unroll
-      for (int d = 0; d < 8; ++d)
-        signs |= (uint32_t)((int8_t)((d < 4 ? s.x : s.y) >> 8 * (d & 3)) < (int8_t)((d < 4 ? mean.x : mean.y) >> 8 * (d & 3))) << d;
-      order_by[i] = signs << 16 | (uint32_t)i;
+  for (int k = 0; k < 2; ++k) {
+    b[k] = signs[k] = 0;
+    if (tok[k] < 0) continue;
+    b[k] = (int)p.bucket[base + tok[k]];
+    const uint2 s = *reinterpret_cast<const uint2 *>(p.sk0 + (base + tok[k]) * kSketchBytes);
+#pragma unroll
+    for (int d = 0; d < 8; ++d)
+      signs[k] |= (int)((int8_t)((d < 4 ? s.x : s.y) >> 8 * (d & 3)) < (int8_t)((d < 4 ? mean.x : mean.y) >> 8 * (d & 3))) << d;
+    order_by[tid + k * kWindowThreads] = (uint16_t)b[k];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {                        // the tokens of a pivot stand together
+    const int i = tid + k * kWindowThreads;
+    if (tok[k] < 0) continue;
+    if (i == 0 || order_by[i - 1] != b[k]) first[b[k]] = i;
+    if (w0 + i == w1 - 1 || i == kWindow - 1 || order_by[i + 1] != b[k]) last[b[k]] = i;
+  }
+  __syncthreads();
+  int lo[2], hi[2];
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const int i = tid + k * kWindowThreads;
+    lo[k] = hi[k] = 0;
+    if (tok[k] < 0) continue;
+    lo[k] = first[b[k]];
+    hi[k] = last[b[k]] + 1;
+    order_by[i] = (uint16_t)signs[k];
+    if (i == lo[k] && hi[k] - lo[k] >= kFew) slot[b[k]] = (uint8_t)atomicAdd(&nslots, 1);
+  }
+  __syncthreads();
+  int before[2];
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const int i = tid + k * kWindowThreads;
+    before[k] = 0;
+    if (hi[k] - lo[k] >= kFew) {
+      before[k] = atomicAdd(&count[slot[b[k]]][signs[k]], 1);   // of those with the same signs
+    } else {
+      for (int j = lo[k]; j < hi[k]; ++j) before[k] += order_by[j] < signs[k] || (order_by[j] == signs[k] && j < i);
     }
+  }
+  __syncthreads();
+  for (int q = wave; q < nslots; q += kWindowThreads / kWave) {   // counts to those of lower signs
+    int4 c = *reinterpret_cast<int4 *>(&count[q][4 * lane]);
+    const int sum = c.x + c.y + c.z + c.w;
+    int incl = sum;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+      const int x = __shfl_up(incl, o);
+      if (lane >= o) incl += x;
+    }
+    incl -= sum;
+    *reinterpret_cast<int4 *>(&count[q][4 * lane]) = make_int4(incl, incl + c.x, incl + c.x + c.y, incl + c.x + c.y + c.z);
   }
   __syncthreads();
 #pragma unroll
   for (int k = 0; k < 2; ++k) {
     if (tok[k] < 0) continue;
-    const uint32_t own = order_by[tid + k * kWindowThreads];
-    int r = lo[k];
-#pragma unroll 8
-    for (int j = lo[k]; j < hi[k]; ++j) r += order_by[j] < own;
-    at_place[r] = (uint16_t)tok[k];
+    const int under = hi[k] - lo[k] >= kFew ? count[slot[b[k]]][signs[k]] : 0;
+    at_place[lo[k] + under + before[k]] = (uint16_t)tok[k];
   }
   __syncthreads();
   int8_t *sk = p.sk + (size_t)ut * p.Tp * kTileBytes;
