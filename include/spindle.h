@@ -399,10 +399,11 @@ int32_t spindle_profile_read(char *names, float *ms, int32_t max);
  *                                 values with the signs and magnitudes of fp16 unit vectors
  *                                 (x 2^10), which draw more power per instruction and so show the
  *                                 clock the part sustains on such data.
- *   spindle_calibrate_similarity  all cosine similarities by fp16 matrix instructions on the unit
- *                                 vectors an earlier spindle_compress_shallow call with the same desc
- *                                 and n_tensors left in `workspace`, each pair of 256-token panels once,
- *                                 nothing done with the results and nothing written: its duration in
+ *   spindle_calibrate_similarity  all cosine similarities by fp16 matrix instructions, for the shape of
+ *                                 desc and n_tensors, on vectors with the signs and magnitudes of unit
+ *                                 vectors that it writes to `workspace` first (the size is that of
+ *                                 spindle_shallow_workspace_bytes, what a call left there is lost), each
+ *                                 pair of 256-token panels once, nothing done with the results: its duration in
  *                                 milliseconds, the time a kernel that computes every pair cannot go
  *                                 below.  `mode` 0: as just said; 1: without the loads that stream the
  *                                 tokens into LDS after the first two stages (the matrix instructions

@@ -522,7 +522,7 @@ def spindle_calibrate_copy(src, dst, stream=None) -> float:
 
 def spindle_calibrate_similarity(plan: "ShallowPlan", mode: int = 0, stream=None) -> float:
     """Milliseconds of all cosine similarities by fp16 matrix instructions, nothing done with the
-    results, on the unit vectors the plan's last run left in its workspace (measurement aid); mode 1
+    results, on stand-ins for unit vectors written to the plan's workspace (measurement aid); mode 1
     without the streaming loads, mode 2 matrix instructions only."""
     out = C.c_double(0.0)
     n_t = sum(1 for k in plan.out if k.startswith("ref_"))

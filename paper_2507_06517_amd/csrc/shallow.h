@@ -1,14 +1,14 @@
 // Similarity codebook replacement (Sec. "Similarity Based Token Replacement", Alg. 1): what its
 // kernels share.  ut = tensor * units + unit indexes one independent (batch, kv-head, K|V)
 // problem of n tokens.  The kernels, in the order spindle_compress_shallow enqueues them:
-//   shallow_prep    what must start from a known value; magnitudes (Eq. 8) in double precision, unit
-//                   vectors rounded to fp16, and a 64-byte sketch of every token whose products bound
-//                   the cosines from above
+//   shallow_prep    what must start from a known value; magnitudes (Eq. 8) in double precision, of
+//                   fp32 inputs unit vectors rounded to fp16, and a 64-byte sketch of every token whose
+//                   products bound the cosines from above
 //   shallow_pivots, shallow_order, shallow_window
 //                   the tokens of a problem sorted so that similar ones stand together
 //   shallow_scan    sketch products of all pairs of 32-token tiles on the int8 matrix cores:
 //                   which tiles can hold a pair above theta at all
-//   shallow_refine  where the sketches exclude little, the same from the fp16 unit vectors
+//   shallow_refine  where the sketches exclude little, the same from the rows
 //   shallow_rows    for those tiles the cosines themselves (Eq. 4, 9), decided exactly; degrees
 //                   (Eq. 10) and neighbour lists
 //   merge_onehop, merge_twohop, merge_update
@@ -17,8 +17,7 @@
 //   shallow_merge   the remaining rounds (all of them for short problems) and the codebook order of
 //                   the picked tokens, one workgroup per problem
 //   shallow_emit    references in codebook order and the codebook vectors
-//   shallow_assign, shallow_assign_exact, shallow_overflow
-//                   tokens whose entry fell beyond the codebook cap go to the nearest
+//   shallow_assign  tokens whose entry fell beyond the codebook cap go to the nearest
 //                   stored entry
 //
 // shallow_prep.hip holds shallow_prep, shallow_tiles.hip the kernels from the order of the tokens to
@@ -44,6 +43,9 @@ constexpr float kGuard = 1.05e-3f;
 
 constexpr int kStageCols = 64;
 constexpr int kLdsRow = 272;      // fp16 row of 128 + 16 B pad (shallow_prep)
+// What the sums of 128 exact products in fp32, truncated or not, and the two factors may be off from a cosine is less than
+// 2e-5; a result within this of theta is decided in double precision.
+constexpr float kRowsGuard = 7e-5f;
 constexpr int kStageBytes = kStageCols * 256;   // staged tokens: unpadded rows, 16-byte pieces swizzled
 
 // Sketch of a token: 64 bytes, integers scaled by kSketchScale.  60 coordinates of the unit vector
@@ -90,19 +92,20 @@ struct ShallowParams {
   KvLayout lay;            // rows of the input tensors
   int cap;
   // workspace
-  _Float16 *Xh;            // [UT][n][128] unit vectors
+  _Float16 *Xh;            // [UT][n][128] fp32 inputs: unit vectors
+  _Float16 *Xe;            // [UT][n][128] unit vectors of the stored entries, where tokens were cut
   double *m64;             // [UT][n]
   int *slot, *alive, *cand, *dying, *rank, *rank_vert;   // [UT][n] (cand: candidate bits in the grid rounds)
   // Lists, keys and everything after them count tokens by position: place in the sorted order.
   uint16_t *perm, *iperm;  // [UT][n] token at a position, position of a token
-  float *inv, *invp;       // [UT][n] factor of a token's row in the cosine (see shallow_rows), by token and by position
+  float *invp;             // [UT][n] factor of a row in the cosine (see shallow_rows), by position
   uint8_t *sk0;            // [UT][n][64] sketches by token
-  uint32_t *serr;          // [UT][n] distance of the sketch from what it stands for, sketch units squared
+  uint2 *inv_err;          // [UT][n] by token (scan): the factor, and the distance of the sketch from what it stands for, sketch units squared
   uint16_t *bucket;        // [UT][n] pivot of a token
   uint32_t *mean;          // [UT][2] first eight coordinates of the pivots' mean
   uint16_t *hist;          // [UT][order blocks][kPivots] tokens per bucket in each block of tokens
   int8_t *sk;              // [UT][Tp][kTileBytes] sketches by position
-  uint32_t *etile;         // [UT][Tp] largest serr of a tile
+  uint32_t *etile;         // [UT][Tp] largest distance of a sketch of a tile
   uint32_t *tpairs;        // [UT][T][TW] bit t of row r: tiles r and t may hold a pair above theta
   int T, Tp, TW;           // tiles, rounded up to whole panels; words per row of tpairs
   int scan;                // 1: tokens are sorted and tpairs says which tiles count; 0: all tiles, positions = tokens
@@ -126,10 +129,7 @@ struct ShallowParams {
   unsigned *pairs_exact;   // [UT] pairs decided in double precision
   uint32_t *ovf;           // [UT][n] tokens whose codebook entry was cut, per problem
   unsigned *ovf_cnt;       // [UT] their number
-  float2 *cstat;           // [UT][n][2] per cut token and lane group: largest approximate cosine seen, entries collected
-  uint2 *ccand;            // [UT][n][2][kCandCap] (entry index, approximate cosine bits)
-  uint32_t *ovf_left;      // [UT*n] cut tokens left to the exhaustive search, packed ut << 16 | token
-  unsigned *ovf_count;     // [1] their number
+  uint2 *ccand;            // [UT][n][2][kCandCap] lists of shallow_assign: (entry index, approximate cosine bits)
   // outputs (index = tensor slot)
   char *C[2];
   int32_t *n_codes[2], *n_found[2], *ref[2];
@@ -181,6 +181,7 @@ constexpr int kCandCap = 8;
 spindle_status launch_prep(const ShallowParams &p, size_t nzero, size_t cpieces, hipStream_t st);   // words to clear, 16-byte pieces of a tensor's codebooks
 spindle_status launch_tiles(const ShallowParams &p, hipStream_t st);      // order, scan and lists
 spindle_status launch_adjacency(const ShallowParams &p, uint32_t *const out[2], hipStream_t st);   // exports G
+spindle_status launch_unit_like(const ShallowParams &p, hipStream_t st);   // operands of the next into Xe
 spindle_status launch_bare_similarity(const ShallowParams &p, hipStream_t st, int mode);   // measurement aid
 spindle_status launch_merge(const ShallowParams &p, hipStream_t st);
 spindle_status launch_codebook(const ShallowParams &p, hipStream_t st);

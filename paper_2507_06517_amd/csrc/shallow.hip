@@ -14,7 +14,7 @@ int padded_tiles_of(int n) { return (int)align_up((size_t)tiles_of(n), kScanPane
 // 32-bit words at the end of the workspace that every call clears before use (`scan`: also what
 // only the scan writes).
 size_t zero_words(int UT, int n, int scan) {
-  size_t w = (size_t)UT * kCounters + 4 + 2 * (size_t)UT;
+  size_t w = (size_t)UT * kCounters + 2 * (size_t)UT;
   if (scan) w += (size_t)UT * padded_tiles_of(n) + (size_t)UT * tiles_of(n) * ((tiles_of(n) + 31) / 32);
   return w;
 }
@@ -32,7 +32,8 @@ size_t carve(ShallowParams &p, void *ws, int UT, int n) {
   const long work = (long)UT * nI * (nI + 1) / 2048;
   p.stages_per_item = work < 1 ? 1 : (work > kScanRun ? kScanRun : (int)work);
   p.njg = (nS + p.stages_per_item - 1) / p.stages_per_item;
-  p.Xh = cv.take<_Float16>((N + 512) * kHeadDim);   // the similarity loop stages up to 5 tiles past the last token
+  p.Xe = cv.take<_Float16>((N + 512) * kHeadDim);   // the similarity loop stages up to 5 tiles past the last token
+  p.Xh = p.dtype == SPINDLE_F32 ? cv.take<_Float16>(N * kHeadDim) : nullptr;
   p.Xl = p.dtype == SPINDLE_F32 ? cv.take<_Float16>(N * kHeadDim) : nullptr;
   p.m64 = cv.take<double>(N);
   p.list_row = p.T;
@@ -40,10 +41,9 @@ size_t carve(ShallowParams &p, void *ws, int UT, int n) {
   p.rows = cv.take<uint2>(N);
   p.perm = cv.take<uint16_t>(N);
   p.iperm = cv.take<uint16_t>(N);
-  p.inv = cv.take<float>(N);
   p.invp = cv.take<float>(N);
   p.sk0 = cv.take<uint8_t>(N * kSketchBytes);
-  p.serr = cv.take<uint32_t>(N);
+  p.inv_err = cv.take<uint2>(N);
   p.bucket = cv.take<uint16_t>(N);
   p.mean = cv.take<uint32_t>((size_t)UT * 2);
   p.hist = cv.take<uint16_t>((size_t)UT * ((n + kOrderTokens - 1) / kOrderTokens) * kPivots);
@@ -62,18 +62,15 @@ size_t carve(ShallowParams &p, void *ws, int UT, int n) {
   p.m1 = cv.take<uint32_t>((size_t)UT * p.n16);
   p.pick_key = cv.take<uint32_t>(N);
   p.ovf = cv.take<uint32_t>(N);
-  p.ovf_left = cv.take<uint32_t>(N);
-  p.cstat = cv.take<float2>(N * 2);
   p.ccand = cv.take<uint2>(N * 2 * kCandCap);
   // everything that must start at zero sits together at the end:
-  // counters [UT][kCounters], ovf_count + 3 spare, pairs_exact [UT], ovf_cnt [UT], then (scan) etile [UT][Tp],
+  // counters [UT][kCounters], pairs_exact [UT], ovf_cnt [UT], then (scan) etile [UT][Tp],
   // tpairs [UT][T][TW]
   p.counters = cv.take<int>(zero_words(UT, n, 1));
   int *tail = p.counters ? p.counters + (size_t)UT * kCounters : nullptr;
-  p.ovf_count = reinterpret_cast<unsigned *>(tail);
-  p.pairs_exact = reinterpret_cast<unsigned *>(tail ? tail + 4 : nullptr);
-  p.ovf_cnt = reinterpret_cast<unsigned *>(tail ? tail + 4 + UT : nullptr);
-  p.etile = reinterpret_cast<uint32_t *>(tail ? tail + 4 + 2 * (size_t)UT : nullptr);
+  p.pairs_exact = reinterpret_cast<unsigned *>(tail);
+  p.ovf_cnt = reinterpret_cast<unsigned *>(tail ? tail + UT : nullptr);
+  p.etile = reinterpret_cast<uint32_t *>(tail ? tail + 2 * (size_t)UT : nullptr);
   p.tpairs = p.etile ? p.etile + (size_t)UT * p.Tp : nullptr;
   return cv.total();
 }
@@ -293,6 +290,7 @@ extern "C" spindle_status spindle_calibrate_similarity(const spindle_kv_desc *de
   if ((s = kv_layout(desc, &p.lay)) != SPINDLE_OK) return s;
   p.theta[0] = p.theta[1] = 0.98f;
   carve(p, workspace, p.UT, p.n);
+  if ((s = launch_unit_like(p, st)) != SPINDLE_OK) return s;
   hipEvent_t e0, e1;
   SPINDLE_HIP(hipEventCreate(&e0));
   SPINDLE_HIP(hipEventCreate(&e1));

@@ -14,6 +14,9 @@ namespace {
 // tokens with 128 entries 27 -> 7 us.
 constexpr int kEmitThreads = 256;
 
+// Factor that takes a row of magnitude m to its unit vector x 2^10 (0 for a zero row).
+__device__ __forceinline__ float unit_factor(double m) { return (float)(m > 0.0 ? (double)kUnitScale / m : 0.0); }
+
 constexpr int kEmitTokens = 4 * kEmitThreads;        // per block
 
 template <int DT>
@@ -68,6 +71,7 @@ __global__ __launch_bounds__(kEmitThreads) void shallow_emit(ShallowParams p, in
     }
   }
   const int piece = tid % kLanes;
+  const bool cut = p.counters[(size_t)ut * kCounters + C_PICKS] > p.cap;
   for (int e = (blk * kEmitThreads + tid) / kLanes; e < stored; e += nblk * (kEmitThreads / kLanes)) {
     const int vert = rank_vert[e];
     const double m = p.m64[base + vert];
@@ -78,6 +82,15 @@ __global__ __launch_bounds__(kEmitThreads) void shallow_emit(ShallowParams p, in
 #pragma unroll
     for (int k = 0; k < kPer; ++k)
       y[k] = Elem<DT>::from_float(m > 0.0 ? (float)((double)Elem<DT>::to_float(x[k]) / m) : 0.f);
+    if (cut) {                                   // for shallow_assign: x 2^10, in fp16
+      const float scale = unit_factor(m);
+      _Float16 z[kPer];
+#pragma unroll
+      for (int k = 0; k < kPer; ++k) z[k] = (_Float16)(Elem<DT>::to_float(x[k]) * scale);
+      _Float16 *to = p.Xe + (base + e) * kHeadDim + piece * kPer;
+      if constexpr (kPer == 8) *reinterpret_cast<u4 *>(to) = *reinterpret_cast<const u4 *>(z);
+      else *reinterpret_cast<uint2 *>(to) = *reinterpret_cast<const uint2 *>(z);
+    }
     reinterpret_cast<u4 *>(reinterpret_cast<T *>(p.C[t]) + ((size_t)u * p.cap + e) * kHeadDim)[piece] = out;
   }
 }
@@ -86,43 +99,73 @@ __global__ __launch_bounds__(kEmitThreads) void shallow_emit(ShallowParams p, in
 // A token whose entry was cut goes to the stored entry of highest cosine (Eq. 4), lowest
 // entry index on ties, decided as the double-precision evaluation decides it.
 //
-// shallow_assign finds, per cut token, the few entries that can be that maximum: fp16
-// matrix-core cosines (the unit vectors of shallow_prep) against all stored entries, off
+// A block takes 256 cut tokens against all stored entries: fp16 matrix-core cosines of the unit vectors (the
+// entries' as shallow_emit left them, streamed through LDS two stages ahead; the tokens' made on the spot), off
 // from the exact value by less than kGuard.  With F the largest approximate cosine of a
 // token, the exact maximum has an approximate value >= F - 2 kGuard, and so has every entry
 // that ties with it.  Each lane keeps, for its token and its half of the entries, the
 // running maximum and the entries seen within 2 kGuard of it (the list restarts whenever the
-// maximum jumps by more than that, so it stays short).  shallow_assign_exact evaluates the
-// surviving entries in double precision; a token whose list ran full is left to
-// shallow_overflow, the exhaustive search.
+// maximum jumps by more than that, so it stays short).  Then a thread per token looks at the entries that are
+// left: one as a rule, which is the answer; several are evaluated in double precision; where a list ran full or
+// no cosine is a number the block searches all entries that way.
+// Where few tokens were cut in all, a block takes 64 of them and its waves a quarter of the products each: four
+// times the blocks for four times the reads of the entries.
+// Lists in memory; in LDS 64 KiB per block, two blocks per CU: 1.81 ms where this took 1.58.
+// The exact comparison of every listed entry and the search of what was left as launches of their own, and the
+// entries gathered by token: 64 problems with half of 32768 tokens cut, 4096 entries, 1165 + 228 + 4 us, now 1235; 2 with 4000
+// cut, 2048 entries, 74 + 20 + 4, now 48.
 constexpr int kAssignThreads = 256;
+constexpr int kAssignStages = 3;
+constexpr int kAssignFew = 512;                        // blocks of 256 below which they take 64 tokens
 
+template <int DT>
 __global__ __launch_bounds__(kAssignThreads, 2) void shallow_assign(ShallowParams p) {
   typedef Mma<SPINDLE_F16> M;
-  __shared__ __attribute__((aligned(1024))) char stage[2 * kStageBytes];
+  typedef typename Elem<DT>::type T;
+  __shared__ __attribute__((aligned(1024))) char stage[kAssignStages * kStageBytes];
+  __shared__ int left[kAssignThreads], nleft;
   const int ut = blockIdx.y, n = p.n;
   const int nov = (int)p.ovf_cnt[ut];
-  const int slot0 = blockIdx.x * kAssignThreads;
+  const bool few = 4 * nov <= n && (long)nov * gridDim.y < (long)kAssignFew * kAssignThreads;   // (4 nov <= n: the blocks and the lists are there)
+  const int per = few ? kAssignThreads / 4 : kAssignThreads, slot0 = blockIdx.x * per;
   if (slot0 >= nov) return;
   const int kept = p.n_codes[ut / p.U][ut % p.U];     // = cap whenever tokens were cut
   if (kept <= 0) return;
   const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), g = lane >> 5, c = lane & 31;
-  const char *Xh = reinterpret_cast<const char *>(p.Xh) + (size_t)ut * n * 256;
+  const char *Xe = reinterpret_cast<const char *>(p.Xe) + (size_t)ut * n * 256;
   const uint32_t *ovf = p.ovf + (size_t)ut * n;
-  const int *rank_vert = p.rank_vert + (size_t)ut * n;
   const float band2 = 2.f * kGuard * kUnitScale * kUnitScale;
+  if (threadIdx.x == 0) nleft = 0;
 
-  // the wave's 64 cut tokens: MFMA B operand (matrix columns = lanes)
+  // the wave's cut tokens: 64 of them, or 32 and one of the two tiles of a stage; MFMA B operand (matrix columns = lanes)
+  const int own_tile = few ? wave >> 1 : -1, lists = few ? 4 : 2;
   int slot[2];
   bool valid[2];
   M::frag af[2][M::kSteps];
 #pragma unroll
   for (int cb = 0; cb < 2; ++cb) {
-    slot[cb] = slot0 + 64 * wave + 32 * cb + c;
-    valid[cb] = slot[cb] < nov;
-    const int tok = valid[cb] ? (int)ovf[slot[cb]] : 0;
+    slot[cb] = slot0 + (few ? 32 * (wave & 1) : 64 * wave + 32 * cb) + c;
+    valid[cb] = slot[cb] < nov && !(few && cb > 0);
 #pragma unroll
-    for (int ks = 0; ks < M::kSteps; ++ks) af[cb][ks] = valid[cb] ? M::load(Xh + (size_t)tok * 256, ks, g) : M::zero();
+    for (int ks = 0; ks < M::kSteps; ++ks) af[cb][ks] = M::zero();
+    if (valid[cb]) {
+      const int tok = (int)ovf[slot[cb]];
+      if constexpr (DT == SPINDLE_F32) {
+        const char *row = reinterpret_cast<const char *>(p.Xh) + ((size_t)ut * n + tok) * 256;
+#pragma unroll
+        for (int ks = 0; ks < M::kSteps; ++ks) af[cb][ks] = M::load(row, ks, g);
+      } else {
+        const char *row = x_row(p, ut, tok);
+        const float scale = unit_factor(p.m64[(size_t)ut * n + tok]);
+#pragma unroll
+        for (int ks = 0; ks < M::kSteps; ++ks) {
+          const u4 in = *reinterpret_cast<const u4 *>(row + ks * 32 + g * 16);
+          const T *x = reinterpret_cast<const T *>(&in);
+#pragma unroll
+          for (int k = 0; k < 8; ++k) af[cb][ks][k] = (_Float16)(Elem<DT>::to_float(x[k]) * scale);
+        }
+      }
+    }
   }
   // staged entry 16*g + v of a tile is fed to matrix row 8*(v/4) + 4*g + v%4 (as in shallow_rows)
   const int prow = 16 * ((c >> 2) & 1) + 4 * (c >> 3) + (c & 3);
@@ -130,33 +173,21 @@ __global__ __launch_bounds__(kAssignThreads, 2) void shallow_assign(ShallowParam
 #pragma unroll
   for (int ks = 0; ks < M::kSteps; ++ks)
     soff[ks] = prow * 256 + (((2 * ks + g) ^ ((prow & 7) | ((prow & 16) >> 1))) << 4);
-  // loads of a 64-entry stage: wave w, load q covers rows (4 w + q) * 4 + lane / 16
-  int srow[4];
-  uint32_t spiece[4];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    srow[q] = (wave * 4 + q) * 4 + (lane >> 4);
-    spiece[q] = (uint32_t)((((lane & 15) ^ ((srow[q] & 7) | ((srow[q] & 16) >> 1))) << 4));
-  }
   const uint32_t stage_lds = (uint32_t)(size_t)(__attribute__((address_space(3))) char *)stage;
   const int nstages = (kept + kStageCols - 1) / kStageCols;
-  int tokq[4];                                       // tokens of the entries the next load brings in
-  auto fetch_tokens = [&](int s) {
+  auto dma = [&](int s) __attribute__((always_inline)) {   // load q of wave w: rows (4 w + q) * 4 + lane / 16; rows past the last entry are masked below
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const int j = s * kStageCols + srow[q];
-      tokq[q] = j < kept ? rank_vert[j] : 0;         // rows past the last entry are masked below
+      const int r = (wave * 4 + q) * 4 + (lane >> 4);
+      lds_dma16_at(Xe, (uint32_t)min(s * kStageCols + r, kept - 1) * 256u + (((lane & 15) ^ ((r & 7) | ((r & 16) >> 1))) << 4),
+                   stage_lds + (s % kAssignStages) * kStageBytes + (wave * 4 + q) * 1024);
     }
-  };
-  auto dma = [&](int bufsel) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-      lds_dma16_at(Xh, (uint32_t)tokq[q] * 256u + spiece[q], stage_lds + bufsel * kStageBytes + (wave * 4 + q) * 1024);
   };
   float runmax[2] = {-INFINITY, -INFINITY};
   int cnt[2] = {0, 0};
   uint2 *cand = p.ccand + (size_t)ut * n * 2 * kCandCap;
-  auto collect = [&](f16v a, int cb, int j0) {
+  auto list_of = [&](int cb) { return (size_t)slot[cb] * lists + (few ? 2 * own_tile : 0) + g; };
+  auto collect = [&](f16v a, int cb, int j0) __attribute__((always_inline)) {
     if (j0 + 32 > kept) {
 #pragma unroll
       for (int v = 0; v < 16; ++v)
@@ -176,7 +207,7 @@ __global__ __launch_bounds__(kAssignThreads, 2) void shallow_assign(ShallowParam
     for (int v = 15; v >= 0; --v) miss = __builtin_amdgcn_alignbit(miss, __float_as_uint(a[v] - thr), 31);
     uint32_t hits = valid[cb] ? ~miss & 0xFFFFu : 0u;
     if (hits) {
-      uint2 *list = cand + ((size_t)slot[cb] * 2 + g) * kCandCap;
+      uint2 *list = cand + list_of(cb) * kCandCap;
       do {
         const int v = __builtin_ctz(hits);
         hits &= hits - 1;
@@ -189,107 +220,114 @@ __global__ __launch_bounds__(kAssignThreads, 2) void shallow_assign(ShallowParam
     }
   };
 
-  fetch_tokens(0);
   dma(0);
-  if (nstages > 1) fetch_tokens(1);
+  if (nstages > 1) dma(1);
   for (int s = 0; s < nstages; ++s) {
-    __builtin_amdgcn_s_waitcnt(0x0F70);               // vmcnt(0): stage s has landed
-    __syncthreads();                                  // ... for every wave; the other buffer is free
-    if (s + 1 < nstages) {
-      dma((s + 1) & 1);
-      if (s + 2 < nstages) fetch_tokens(s + 2);
-    }
+    // the wave's loads of stage s have landed (and everything else before them; those of stage s + 1 may be on their
+    // way, and a list entry behind them only makes the wait longer), behind the barrier every wave's; the buffer
+    // of stage s - 1 is free
+    if (s + 1 < nstages) __builtin_amdgcn_s_waitcnt(0x0F74);
+    else __builtin_amdgcn_s_waitcnt(0x0F70);
+    __syncthreads();
+    if (s + 2 < nstages) dma(s + 2);
 #pragma unroll
     for (int ct = 0; ct < 2; ++ct) {
       const int j0 = s * kStageCols + 32 * ct;
       if (j0 >= kept) break;
+      if (few && ct != own_tile) continue;            // wave-uniform, as below
+      const char *st = stage + (s % kAssignStages) * kStageBytes + ct * 32 * 256;
       f16v acc0, acc1;
 #pragma unroll
       for (int v = 0; v < 16; ++v) { acc0[v] = 0.f; acc1[v] = 0.f; }
+      if (few) {
 #pragma unroll
-      for (int ks = 0; ks < M::kSteps; ++ks) {
-        const M::frag f = *reinterpret_cast<const M::frag *>(stage + (s & 1) * kStageBytes + ct * 32 * 256 + soff[ks]);
-        acc0 = M::mma(f, af[0][ks], acc0);
-        acc1 = M::mma(f, af[1][ks], acc1);
+        for (int ks = 0; ks < M::kSteps; ++ks) acc0 = M::mma(*reinterpret_cast<const M::frag *>(st + soff[ks]), af[0][ks], acc0);
+        collect(acc0, 0, j0);
+      } else {
+#pragma unroll
+        for (int ks = 0; ks < M::kSteps; ++ks) {
+          const M::frag f = *reinterpret_cast<const M::frag *>(st + soff[ks]);
+          acc0 = M::mma(f, af[0][ks], acc0);
+          acc1 = M::mma(f, af[1][ks], acc1);
+        }
+        collect(acc0, 0, j0);
+        collect(acc1, 1, j0);
       }
-      collect(acc0, 0, j0);
-      collect(acc1, 1, j0);
     }
   }
-  float2 *cstat = p.cstat + (size_t)ut * n * 2;
+
+  // what the lanes found, by token of the block and list
+  __syncthreads();                                    // the stages have been read
+  float2 *stat = reinterpret_cast<float2 *>(stage);
 #pragma unroll
   for (int cb = 0; cb < 2; ++cb)
-    if (valid[cb]) cstat[(size_t)slot[cb] * 2 + g] = make_float2(runmax[cb], __int_as_float(cnt[cb]));
-}
-
-__global__ __launch_bounds__(256) void shallow_assign_exact(ShallowParams p) {
-  const int ut = blockIdx.y, n = p.n;
-  const int nov = (int)p.ovf_cnt[ut];
-  const uint32_t *ovf = p.ovf + (size_t)ut * n;
+    if (valid[cb]) stat[list_of(cb) - (size_t)slot0 * lists] = make_float2(runmax[cb], __int_as_float(cnt[cb]));
+  __syncthreads();                                    // (and the lists in memory are every wave's to read)
+  int32_t *ref = p.ref[ut / p.U] + (size_t)(ut % p.U) * n;
   const int *rank_vert = p.rank_vert + (size_t)ut * n;
-  const float2 *cstat = p.cstat + (size_t)ut * n * 2;
-  const uint2 *cand = p.ccand + (size_t)ut * n * 2 * kCandCap;
-  const float band2 = 2.f * kGuard * kUnitScale * kUnitScale;
-  for (int s = blockIdx.x * 256 + threadIdx.x; s < nov; s += gridDim.x * 256) {
-    const int a = (int)ovf[s];
-    const float2 st0 = cstat[(size_t)s * 2], st1 = cstat[(size_t)s * 2 + 1];
-    const int c0 = __float_as_int(st0.y), c1 = __float_as_int(st1.y);
-    if (c0 > kCandCap || c1 > kCandCap) {              // a list ran full: exhaustive search
-      p.ovf_left[atomicAdd(p.ovf_count, 1u)] = ((uint32_t)ut << 16) | (uint32_t)a;
-      continue;
+  const int tid = threadIdx.x;
+  if (tid < per && slot0 + tid < nov) {
+    const int a = (int)ovf[slot0 + tid];
+    const float2 *own = stat + tid * lists;
+    float top = -INFINITY;
+    bool full = false;
+    for (int h = 0; h < lists; ++h) {
+      top = fmaxf(top, own[h].x);
+      full |= __float_as_int(own[h].y) > kCandCap;
     }
-    const float thr = fmaxf(st0.x, st1.x) - band2;
-    double bv = -INFINITY;
-    int bj = 0x7FFFFFFF;
-    for (int h = 0; h < 2; ++h) {
-      const int ch = h ? c1 : c0;
-      for (int i = 0; i < ch; ++i) {
-        const uint2 e = cand[((size_t)s * 2 + h) * kCandCap + i];
+    const float thr = top - band2;
+    const uint2 *mine = cand + (size_t)(slot0 + tid) * lists * kCandCap;
+    int found = 0, bj = 0x7FFFFFFF;
+    for (int h = 0; h < lists && !full; ++h)
+      for (int i = 0; i < __float_as_int(own[h].y); ++i) {
+        const uint2 e = mine[h * kCandCap + i];
         if (__uint_as_float(e.y) >= thr) {
-          const int j = (int)e.x;
-          const double cv = cos64(p, ut, a, rank_vert[j]);
-          if (cv > bv || (cv == bv && j < bj)) { bv = cv; bj = j; }
+          ++found;
+          bj = (int)e.x;
         }
       }
+    if (found > 1) {
+      double bv = -INFINITY;
+      bj = 0x7FFFFFFF;
+      for (int h = 0; h < lists; ++h)
+        for (int i = 0; i < __float_as_int(own[h].y); ++i) {
+          const uint2 e = mine[h * kCandCap + i];
+          if (__uint_as_float(e.y) >= thr) {
+            const int j = (int)e.x;
+            const double cv = cos64<DT, 4>(p, ut, a, rank_vert[j]);
+            if (cv > bv || (cv == bv && j < bj)) { bv = cv; bj = j; }
+          }
+        }
     }
-    if (bj == 0x7FFFFFFF) {                            // no approximate cosine is a number: a NaN or an infinity in the token
-      p.ovf_left[atomicAdd(p.ovf_count, 1u)] = ((uint32_t)ut << 16) | (uint32_t)a;
-      continue;
-    }
-    p.ref[ut / p.U][(size_t)(ut % p.U) * n + a] = bj;
+    if (full || bj == 0x7FFFFFFF) left[atomicAdd(&nleft, 1)] = a;   // (no approximate cosine is a number: a NaN or an infinity in the token)
+    else ref[a] = bj;
   }
-}
-
-// One block per token left over: highest cosine among all stored entries.
-__global__ __launch_bounds__(256) void shallow_overflow(ShallowParams p) {
-  __shared__ double sh_v[256];
-  __shared__ int sh_j[256];
-  const unsigned count = *p.ovf_count;
-  for (unsigned i = blockIdx.x; i < count; i += gridDim.x) {
-    const uint32_t e = p.ovf_left[i];
-    const int ut = (int)(e >> 16), a = (int)(e & 0xFFFFu);
-    const int *rank_vert = p.rank_vert + (size_t)ut * p.n;
+  __syncthreads();
+  double *sh_v = reinterpret_cast<double *>(stage);
+  int *sh_j = reinterpret_cast<int *>(stage + kAssignThreads * sizeof(double));
+  for (int i = 0; i < nleft; ++i) {
+    const int a = left[i];
     double bv = -INFINITY;
     int bj = 0x7FFFFFFF;
-    for (int j = threadIdx.x; j < p.cap; j += 256) {
-      const double cv = cos64(p, ut, a, rank_vert[j]);
+    for (int j = tid; j < kept; j += kAssignThreads) {
+      const double cv = cos64<DT, 4>(p, ut, a, rank_vert[j]);
       if (cv > bv) { bv = cv; bj = j; }
     }
-    sh_v[threadIdx.x] = bv;
-    sh_j[threadIdx.x] = bj;
+    sh_v[tid] = bv;
+    sh_j[tid] = bj;
     __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-      if (threadIdx.x < o) {
-        const double ov = sh_v[threadIdx.x + o];
-        const int oj = sh_j[threadIdx.x + o];
-        if (ov > sh_v[threadIdx.x] || (ov == sh_v[threadIdx.x] && oj < sh_j[threadIdx.x])) {
-          sh_v[threadIdx.x] = ov;
-          sh_j[threadIdx.x] = oj;
+    for (int o = kAssignThreads / 2; o > 0; o >>= 1) {
+      if (tid < o) {
+        const double ov = sh_v[tid + o];
+        const int oj = sh_j[tid + o];
+        if (ov > sh_v[tid] || (ov == sh_v[tid] && oj < sh_j[tid])) {
+          sh_v[tid] = ov;
+          sh_j[tid] = oj;
         }
       }
       __syncthreads();
     }
-    if (threadIdx.x == 0) p.ref[ut / p.U][(size_t)(ut % p.U) * p.n + a] = sh_j[0] == 0x7FFFFFFF ? 0 : sh_j[0];
+    if (tid == 0) ref[a] = sh_j[0] == 0x7FFFFFFF ? 0 : sh_j[0];
     __syncthreads();
   }
 }
@@ -306,12 +344,13 @@ spindle_status launch_codebook(const ShallowParams &p, hipStream_t st) {
   if (p.dtype == SPINDLE_F16) hipLaunchKernelGGL(shallow_emit<SPINDLE_F16>, eg, dim3(kEmitThreads), 0, st, p, nblk);
   else if (p.dtype == SPINDLE_BF16) hipLaunchKernelGGL(shallow_emit<SPINDLE_BF16>, eg, dim3(kEmitThreads), 0, st, p, nblk);
   else hipLaunchKernelGGL(shallow_emit<SPINDLE_F32>, eg, dim3(kEmitThreads), 0, st, p, nblk); }
-  { ProfScope ps("shallow_assign", st);
-  hipLaunchKernelGGL(shallow_assign, dim3((n + kAssignThreads - 1) / kAssignThreads, p.UT), dim3(kAssignThreads), 0, st, p);
-  int ax = (n + 255) / 256;
-  hipLaunchKernelGGL(shallow_assign_exact, dim3(ax < 64 ? ax : 64, p.UT), dim3(256), 0, st, p); }
-  { ProfScope ps("shallow_overflow", st);
-  hipLaunchKernelGGL(shallow_overflow, dim3(2048), dim3(256), 0, st, p); }
+  if (p.cap < n) {                                    // (else no entry can be cut)
+    ProfScope ps("shallow_assign", st);
+    const dim3 ag((n + kAssignThreads - 1) / kAssignThreads, p.UT);
+    if (p.dtype == SPINDLE_F16) hipLaunchKernelGGL(shallow_assign<SPINDLE_F16>, ag, dim3(kAssignThreads), 0, st, p);
+    else if (p.dtype == SPINDLE_BF16) hipLaunchKernelGGL(shallow_assign<SPINDLE_BF16>, ag, dim3(kAssignThreads), 0, st, p);
+    else hipLaunchKernelGGL(shallow_assign<SPINDLE_F32>, ag, dim3(kAssignThreads), 0, st, p);
+  }
   SPINDLE_HIP(hipGetLastError());
   return SPINDLE_OK;
 }

@@ -31,8 +31,10 @@ __global__ __launch_bounds__(256) void shallow_prep(ShallowParams p, size_t nzer
   constexpr int lds_row = row_bytes + 16;
   constexpr int tpr = row_bytes / 16;
   __shared__ __attribute__((aligned(16))) char tile_in[kRows * lds_row];
-  __shared__ __attribute__((aligned(16))) char tile_out[kRows * kLdsRow];
+  constexpr bool kUnit = DT == SPINDLE_F32;            // unit vectors and their remainders
+  __shared__ __attribute__((aligned(16))) char tile_out[kUnit ? kRows * kLdsRow : 16];
   __shared__ double row_inv[kRows];
+  __shared__ float row_factor[kRows];
   const int ut = blockIdx.y, t = ut / p.U;
   const int row0 = blockIdx.x * kRows;
   begin_call(p, nzero, cpieces);
@@ -70,15 +72,16 @@ __global__ __launch_bounds__(256) void shallow_prep(ShallowParams p, size_t nzer
       const bool usual = DT == SPINDLE_F32 ? m > 0x1p-100 && m < 0x1p100 : m > 0x1p-40 && m < 0x1p55;
       inv = !usual ? NAN : DT == SPINDLE_F32 ? 1.f / kUnitScale : (float)(1.0 / m);
     }
-    p.inv[idx] = inv;
+    row_factor[r] = inv;
+    if (!kSketch) p.invp[idx] = inv;                 // (positions are tokens)
     p.perm[idx] = (uint16_t)(row0 + r);
     p.iperm[idx] = (uint16_t)(row0 + r);
   } else if (threadIdx.x < kRows) {
     row_inv[threadIdx.x] = 0.0;                      // rows past the end of the sequence
   }
   __syncthreads();
-  {
-    // four threads per row: fp16 unit vector (x 2^10)
+  if (kUnit || kSketch) {
+    // four threads per row: unit vector (x 2^10), of fp32 inputs rounded to fp16
     const int r = threadIdx.x >> 2, part = threadIdx.x & 3;
     constexpr int per = 16 / sizeof(T);
     const double inv64 = row_inv[r];
@@ -93,7 +96,7 @@ __global__ __launch_bounds__(256) void shallow_prep(ShallowParams p, size_t nzer
       for (int i = 0; i < per; ++i) {
         const float x = Elem<DT>::to_float(e[i]) * inv;
         u[c * per + i] = x;
-        reinterpret_cast<_Float16 *>(tile_out + r * kLdsRow)[ch * per + i] = (_Float16)x;
+        if (kUnit) reinterpret_cast<_Float16 *>(tile_out + r * kLdsRow)[ch * per + i] = (_Float16)x;
       }
     }
     if (DT == SPINDLE_F32 && row0 + r < p.n) {
@@ -152,10 +155,13 @@ __global__ __launch_bounds__(256) void shallow_prep(ShallowParams p, size_t nzer
         // most half of the two squares.  In sketch units squared, rounded up.
         const float e = sqrtf(q2) * (1.f / kSketchScale);
         if (part == 0)
-          p.serr[idx] = fine && e < 4.f ? (uint32_t)((e + 0.5f * e * e) * (kSketchScale * kSketchScale * (1.f + 1e-5f))) + 2u : kSketchUnknown;
+          p.inv_err[idx] = make_uint2(
+              __float_as_uint(row_factor[r]),
+              fine && e < 4.f ? (uint32_t)((e + 0.5f * e * e) * (kSketchScale * kSketchScale * (1.f + 1e-5f))) + 2u : kSketchUnknown);
       }
     }
   }
+  if (!kUnit) return;
   __syncthreads();
   for (int i = threadIdx.x; i < kRows * 16; i += 256) {
     const int r = i / 16, ch = i % 16;

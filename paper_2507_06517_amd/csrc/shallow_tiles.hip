@@ -229,7 +229,8 @@ __global__ __launch_bounds__(kPivots) void shallow_order(ShallowParams p, int nb
 // tile, half of the 64 bytes, lane.
 // Tokens of a pivot with fewer than kFew in the window count the ones that go before them; more are counted by signs
 // (256 bins per pivot, of which no more than kMany fit the window).  Where all of them were compared, isolated tokens, which
-// stand with the lowest pivots, cost 2048 comparisons each: WINDOW_US; a bitonic sort took longer than comparing clusters.
+// stand with the lowest pivots, cost 2048 comparisons each: 51 us for the kernel on two
+// problems of 32768 rows, 182 on 64, now 21 and 99; a bitonic sort took longer than comparing clusters.
 constexpr int kWindow = 2048;
 constexpr int kWindowThreads = 1024;
 constexpr int kFew = 64, kMany = kWindow / kFew;
@@ -320,27 +321,46 @@ __global__ __launch_bounds__(kWindowThreads) void shallow_window(ShallowParams p
     at_place[lo[k] + under + before[k]] = (uint16_t)tok[k];
   }
   __syncthreads();
+  // A wave takes 32 places at a time: their sketches are read four lanes to a row and turned to fragment order in LDS
+  // (which the counts no longer need).
   int8_t *sk = p.sk + (size_t)ut * p.Tp * kTileBytes;
+  char *turn = reinterpret_cast<char *>(&count[0][0]) + wave * kTileBytes;
+  static_assert(sizeof(count) >= kWindowThreads / kWave * kTileBytes, "a tile per wave");
   const int end = w1 < n ? w1 : p.Tp * kTile;         // the last window also fills the places past the last token
-  for (int pos = w0 + tid; pos < end; pos += kWindowThreads) {
-    u4 *d = reinterpret_cast<u4 *>(sk + (size_t)(pos >> 5) * kTileBytes);
+  for (int p0 = w0 + wave * kTile; p0 < end; p0 += kWindowThreads / kWave * kTile) {
+    u4 v[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int pos = p0 + 16 * j + (lane >> 2);
+      v[j] = u4{0, 0, 0, 0};
+      if (pos < n) v[j] = reinterpret_cast<const u4 *>(p.sk0 + (base + at_place[pos - w0]) * kSketchBytes)[lane & 3];
+    }
     uint32_t e = 0;
-    if (pos < n) {
-      const int t = (int)at_place[pos - w0];
+    if (lane < kTile && p0 + lane < n) {
+      const int pos = p0 + lane, t = (int)at_place[pos - w0];
+      const uint2 f = p.inv_err[base + t];
       p.perm[base + pos] = (uint16_t)t;
       p.iperm[base + t] = (uint16_t)pos;
-      p.invp[base + pos] = p.inv[base + t];
-      const u4 *s = reinterpret_cast<const u4 *>(p.sk0 + (base + t) * kSketchBytes);
-#pragma unroll
-      for (int k = 0; k < 4; ++k) d[(k >> 1) * 64 + (k & 1) * 32 + (pos & 31)] = s[k];
-      e = p.serr[base + t];
-    } else {
-#pragma unroll
-      for (int k = 0; k < 4; ++k) d[(k >> 1) * 64 + (k & 1) * 32 + (pos & 31)] = u4{0, 0, 0, 0};
+      p.invp[base + pos] = __uint_as_float(f.x);
+      e = f.y;
     }
 #pragma unroll
     for (int o = 16; o > 0; o >>= 1) e = max(e, (uint32_t)__shfl_xor((int)e, o));
-    if ((pos & 31) == 0) p.etile[(size_t)ut * p.Tp + (pos >> 5)] = e;
+    if (lane == 0) p.etile[(size_t)ut * p.Tp + (p0 >> 5)] = e;
+    // piece k of row r at place k ^ (r / 4) % 4: sixteen consecutive lanes of either access hit all banks
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // the tile before has been read
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int r = 16 * j + (lane >> 2);
+      *reinterpret_cast<u4 *>(turn + r * kSketchBytes + (((lane & 3) ^ ((r >> 2) & 3)) << 4)) = v[j];
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // LDS keeps the order of one wave's accesses
+    u4 *d = reinterpret_cast<u4 *>(sk + (size_t)(p0 >> 5) * kTileBytes);
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const int r = lane & 31, piece = 2 * k + (lane >> 5);
+      d[k * 64 + lane] = *reinterpret_cast<const u4 *>(turn + r * kSketchBytes + ((piece ^ ((r >> 2) & 3)) << 4));
+    }
   }
 }
 
@@ -485,21 +505,27 @@ __global__ __launch_bounds__(kScanThreads, 2) void shallow_scan(ShallowParams p)
   if (!refine) put_marks<4>(p, w.ut, r0, w.s0, w.s1, marks + wave * 4);
 }
 
-// What shallow_scan left over, from the fp16 unit vectors: a tile pair is marked if one of its cosines can be
-// above theta, kGuard allowed for.  Half of a scan block's panel at a time: two row tiles per wave in
+// What shallow_scan left over, from the rows themselves (fp32 inputs: from their fp16 unit vectors): a tile pair is marked
+// if one of its cosines can be above theta, kRowsGuard (kGuard) allowed for.  With f the factors of rows the test of a
+// product is dot * f_b > (theta - guard) / f_a.  Half of a scan block's panel at a time: two row tiles per wave in
 // registers, the columns gathered into LDS in their order, 64 at a time, two steps ahead of their use; the
 // maxima of a tile are taken while the matrix cores work on the next one.  The blocks stay and deal the work
 // out among them in the scan's order, so that an XCD's blocks share their columns in its L2.
-// 16 problems of 32768 tokens, all pairs: 1.8 ms = 1.2 PFLOP/s; three blocks per compute unit without the overlap 2.05 ms.
+// 16 problems of 32768 tokens, all pairs: 2.0 ms; 1.8 from fp16 unit vectors of 16-bit inputs, but these cost shallow_prep
+// 20 us per 16 problems of every call, and hardly a call comes here.
 constexpr int kRefineThreads = 256;
 constexpr int kRefineBlocks = 512;                     // two per compute unit
 constexpr int kRefineStages = 3;
 constexpr int kRefineList = 2048;                      // items looked at in one go
 
+template <int DT>
 __global__ __launch_bounds__(kRefineThreads, 2) void shallow_refine(ShallowParams p, int nitems) {
-  typedef Mma<SPINDLE_F16> M;
+  typedef Mma<DT == SPINDLE_BF16 ? SPINDLE_BF16 : SPINDLE_F16> M;
+  constexpr bool kRaw = DT != SPINDLE_F32;
   __shared__ __attribute__((aligned(1024))) char stage[kRefineStages][kStageBytes];
   __shared__ uint16_t cols[kScanRun * kScanStage * kTile];
+  __shared__ __attribute__((aligned(16))) float factor[kRaw ? kScanRun * kScanStage * kTile : 4];
+  __shared__ unsigned long long odd_s[2];              // column tiles with rows whose products say nothing
   __shared__ uint8_t marks[kScanPanel / 2][kScanRun];
   __shared__ uint16_t list[kRefineList];
   __shared__ int wave_n[kRefineList / kWave];
@@ -538,44 +564,73 @@ __global__ __launch_bounds__(kRefineThreads, 2) void shallow_refine(ShallowParam
     for (int at = slot; at < 2 * total; at += nslots) {
       const ScanItem w = scan_item(p, i0 + list[at >> 1], xcd);
       const size_t base = (size_t)w.ut * n;
-      const char *Xh = reinterpret_cast<const char *>(p.Xh) + base * 256;
+      const char *X = kRaw ? x_row(p, w.ut, 0) : reinterpret_cast<const char *>(p.Xh) + base * 256;
+      const size_t pitch = kRaw ? (size_t)p.lay.st : 256;
+      const float *inv = p.invp + base;
       const uint16_t *perm = p.perm + base;
       const uint32_t *et = p.etile + (size_t)w.ut * p.Tp;
       const int r0 = w.I * kScanPanel + (at & 1) * (kScanPanel / 2) + 2 * wave;
       const int tile0 = w.s0 * kScanStage, ntiles = (w.s1 - w.s0) * kScanStage, nsteps = ntiles * kTile / kStageCols;
-      const int thr = __float_as_int((p.theta[w.ut / p.U] - kGuard) * (kUnitScale * kUnitScale));
+      const float least = kRaw ? p.theta[w.ut / p.U] - kRowsGuard : (p.theta[w.ut / p.U] - kGuard) * (kUnitScale * kUnitScale);
       __syncthreads();                                 // the item before is done with these
-      for (int i = threadIdx.x; i < ntiles * kTile; i += kRefineThreads) cols[i] = perm[min(tile0 * kTile + i, n - 1)];
+      if (threadIdx.x < 2) odd_s[threadIdx.x] = 0;
+      __syncthreads();
+      for (int i = threadIdx.x; i < ntiles * kTile; i += kRefineThreads) {   // (a wave has two tiles)
+        const int pos = min(tile0 * kTile + i, n - 1);
+        cols[i] = perm[pos];
+        if (kRaw) {
+          const float f = inv[pos];
+          factor[i] = f == f ? f : 0.f;
+          const unsigned long long nan = __ballot(f != f);
+          const int t = i >> 5;
+          if (c == 0 && (uint32_t)(nan >> (32 * g))) atomicOr(&odd_s[t >> 6], 1ull << (t & 63));
+        }
+      }
       if (threadIdx.x < sizeof(marks)) reinterpret_cast<uint8_t *>(marks)[threadIdx.x] = 0;
-      M::frag af[2][M::kSteps];
-      bool odd[2];                                     // rows whose unit vectors say nothing,
+      typename M::frag af[2][M::kSteps];
+      bool odd[2];                                     // row tiles with rows whose products say nothing,
+      int thr[2];
 #pragma unroll
       for (int cb = 0; cb < 2; ++cb) {
-        const char *row = Xh + (size_t)perm[min((r0 + cb) * kTile + c, n - 1)] * 256;
+        const int pos = min((r0 + cb) * kTile + c, n - 1);
+        const char *row = X + (size_t)perm[pos] * pitch;
 #pragma unroll
         for (int ks = 0; ks < M::kSteps; ++ks) af[cb][ks] = M::load(row, ks, g);
-        odd[cb] = et[r0 + cb] >= kSketchUnknown;
+        const float f = kRaw ? inv[pos] : 1.f;
+        odd[cb] = et[r0 + cb] >= kSketchUnknown || __any(f != f);
+        thr[cb] = __float_as_int(f > 0.f ? least / f : INFINITY);
       }
       unsigned long long odd_cols[2];                  // ... and columns, a bit per tile
 #pragma unroll
       for (int k = 0; k < 2; ++k)
         odd_cols[k] = __ballot(k * kWave + lane < ntiles && et[tile0 + min(k * kWave + lane, ntiles - 1)] >= kSketchUnknown);
       __syncthreads();
+#pragma unroll
+      for (int k = 0; k < 2; ++k) odd_cols[k] |= odd_s[k];
       auto dma = [&](int s) __attribute__((always_inline)) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           const int r = (wave * 4 + q) * 4 + (lane >> 4);
-          lds_dma16_at(Xh, (uint32_t)cols[s * kStageCols + r] * 256u + (((lane & 15) ^ ((r & 7) | ((r & 16) >> 1))) << 4),
-                       stage_lds + (s % kRefineStages) * kStageBytes + (wave * 4 + q) * 1024);
+          lds_dma16(X + cols[s * kStageCols + r] * pitch + (((lane & 15) ^ ((r & 7) | ((r & 16) >> 1))) << 4),
+                    stage_lds + (s % kRefineStages) * kStageBytes + (wave * 4 + q) * 1024);
         }
       };
       // results of column tile t; thr is positive: floats order as integers as far as it matters
       auto look = [&](int t, const f16v &x0, const f16v &x1) __attribute__((always_inline)) {
-        int m0 = __float_as_int(x0[0]), m1 = __float_as_int(x1[0]);
+        int m0 = INT32_MIN, m1 = INT32_MIN;
 #pragma unroll
-        for (int v = 1; v < 16; ++v) { m0 = max(m0, __float_as_int(x0[v])); m1 = max(m1, __float_as_int(x1[v])); }
+        for (int v0 = 0; v0 < 16; v0 += 4) {
+          float4 f = make_float4(1.f, 1.f, 1.f, 1.f);
+          if (kRaw) f = *reinterpret_cast<const float4 *>(&factor[t * kTile + mma_row(v0, g)]);
+          const float fv[4] = {f.x, f.y, f.z, f.w};
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            m0 = max(m0, __float_as_int(kRaw ? x0[v0 + k] * fv[k] : x0[v0 + k]));
+            m1 = max(m1, __float_as_int(kRaw ? x1[v0 + k] * fv[k] : x1[v0 + k]));
+          }
+        }
         const bool oddc = odd_cols[t >> 6] >> (t & 63) & 1;
-        const bool hit0 = oddc | odd[0] | (__any(m0 > thr) != 0), hit1 = oddc | odd[1] | (__any(m1 > thr) != 0);
+        const bool hit0 = oddc | odd[0] | (__any(m0 > thr[0]) != 0), hit1 = oddc | odd[1] | (__any(m1 > thr[1]) != 0);
         if ((hit0 | hit1) && lane < 2 && (lane ? hit1 : hit0)) marks[2 * wave + lane][t >> 3] |= (uint8_t)(1u << (t & 7));
       };
       f16v y0, y1;
@@ -596,9 +651,9 @@ __global__ __launch_bounds__(kRefineThreads, 2) void shallow_refine(ShallowParam
           f16v x0, x1;
 #pragma unroll
           for (int v = 0; v < 16; ++v) { x0[v] = 0.f; x1[v] = 0.f; }
-          M::frag f[M::kSteps];
+          typename M::frag f[M::kSteps];
 #pragma unroll
-          for (int ks = 0; ks < M::kSteps; ++ks) f[ks] = *reinterpret_cast<const M::frag *>(st + ct * kTile * 256 + soff[ks]);
+          for (int ks = 0; ks < M::kSteps; ++ks) f[ks] = *reinterpret_cast<const typename M::frag *>(st + ct * kTile * 256 + soff[ks]);
           __builtin_amdgcn_sched_barrier(0);           // all reads on their way before the first instruction waits
 #pragma unroll
           for (int ks = 0; ks < M::kSteps; ++ks) {
@@ -632,7 +687,6 @@ __global__ __launch_bounds__(kRefineThreads, 2) void shallow_refine(ShallowParam
 // are too few row tiles to fill the chip.  Bound by the gathered rows (random 256-byte rows, mostly from
 // L2): 0.22 ms for 16 problems of 32768 tokens, 0.20 ms for 128 of 8192 in clusters of 128, three blocks per compute unit
 // (0.31 and 0.25 with two); one wave per row tile with its own gathers took 0.73 and 0.84 ms.
-constexpr float kRowsGuard = 7e-5f;
 constexpr int kRowsQueue = 192;                    // waiting pairs per wave
 constexpr int kRowsThreads = 256;
 constexpr int kRowsPitch = kWave + 2;              // result bits of a step, and a word so that one lane's bits of 32 steps are 32 banks
@@ -748,7 +802,7 @@ __global__ __launch_bounds__(kRowsThreads, 2) void shallow_rows(ShallowParams p,
   const size_t base = (size_t)ut * n;
   uint16_t *bits = l.bits[wave], *queue = l.queue[wave];
   const uint16_t *perm = p.perm + base;
-  const float *inv = (p.scan ? p.invp : p.inv) + base;
+  const float *inv = p.invp + base;
   const float theta = p.theta[ut / p.U];
 
   const char *X, *Xlo = nullptr;
@@ -1117,7 +1171,9 @@ spindle_status launch_tiles(const ShallowParams &p, hipStream_t st) {
     { ProfScope ps("shallow_scan", st, most_by(p) == kBySketch);
     hipLaunchKernelGGL(shallow_scan, dim3((unsigned)(8 * nitems)), dim3(kScanThreads), 0, st, p); }
     { ProfScope ps("shallow_refine", st, most_by(p) == kByVector);
-    hipLaunchKernelGGL(shallow_refine, dim3(kRefineBlocks), dim3(kRefineThreads), 0, st, p, nitems); }
+    if (p.dtype == SPINDLE_F16) hipLaunchKernelGGL(shallow_refine<SPINDLE_F16>, dim3(kRefineBlocks), dim3(kRefineThreads), 0, st, p, nitems);
+    else if (p.dtype == SPINDLE_BF16) hipLaunchKernelGGL(shallow_refine<SPINDLE_BF16>, dim3(kRefineBlocks), dim3(kRefineThreads), 0, st, p, nitems);
+    else hipLaunchKernelGGL(shallow_refine<SPINDLE_F32>, dim3(kRefineBlocks), dim3(kRefineThreads), 0, st, p, nitems); }
   }
   if (p.dtype == SPINDLE_F16) return launch_rows<SPINDLE_F16>(p, st);
   if (p.dtype == SPINDLE_BF16) return launch_rows<SPINDLE_BF16>(p, st);

@@ -11,7 +11,7 @@ constexpr int kChunkCols = 1024;  // tokens per chunk
 constexpr int kItemChunks = 4;    // chunks a block handles with the same rows in registers
 constexpr int kLoopThreads = 256;
 
-// Block = 4 waves; wave w keeps the unit vectors of tokens a in [I*256 + 64w, +64) as MFMA B fragments
+// Block = 4 waves; wave w keeps the vectors of tokens a in [I*256 + 64w, +64) as MFMA B fragments
 // and streams the tokens b of the chunks from its own first row on through LDS.
 //   kMode 0   staging, barriers, fragment reads and matrix instructions
 //   kMode 1   without the loads of a chunk's stages after the first two (the matrix instructions keep
@@ -36,7 +36,7 @@ __global__ __launch_bounds__(kLoopThreads, 2) void similarity_loop(ShallowParams
   const int Jfirst = (I * kPanelRows) / kChunkCols;
   if ((Jg + 1) * kItemChunks <= Jfirst) return;
   const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), g = lane >> 5, c = lane & 31;
-  const char *Xh = reinterpret_cast<const char *>(p.Xh) + (size_t)ut * n * 256;
+  const char *Xh = reinterpret_cast<const char *>(p.Xe) + (size_t)ut * n * 256;
   M::frag af[2][M::kSteps];
 #pragma unroll
   for (int cb = 0; cb < 2; ++cb) {
@@ -99,7 +99,25 @@ __global__ __launch_bounds__(kLoopThreads, 2) void similarity_loop(ShallowParams
   if (keep == 0x9E3779B9u) p.ovf[0] = keep;          // never in practice: keeps the results alive
 }
 
+// Values with the signs and magnitudes of unit vectors x 2^10.
+__global__ __launch_bounds__(256) void unit_like(ShallowParams p, size_t count) {
+  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < count; i += (size_t)gridDim.x * 256) {
+    uint32_t h = (uint32_t)i * 0x9E3779B1u;
+    h ^= h >> 15;
+    h *= 0x85EBCA77u;
+    h ^= h >> 13;
+    // the sum of two uniform numbers, of variance 1 / 128
+    p.Xe[i] = (_Float16)(((float)(h & 0xFFFFu) + (float)(h >> 16) - 65535.f) * (kUnitScale * 2.4495f / (65536.f * 11.3137f)));
+  }
+}
+
 }  // namespace
+
+spindle_status launch_unit_like(const ShallowParams &p, hipStream_t st) {
+  hipLaunchKernelGGL(unit_like, dim3(4096), dim3(256), 0, st, p, ((size_t)p.UT * p.n + 512) * kHeadDim);
+  SPINDLE_HIP(hipGetLastError());
+  return SPINDLE_OK;
+}
 
 spindle_status launch_bare_similarity(const ShallowParams &p, hipStream_t st, int mode) {
   const int nI = (p.n + kPanelRows - 1) / kPanelRows;

@@ -258,3 +258,45 @@ def test_measurement_aids_run_and_leave_results_alone():
     torch.cuda.synchronize()
     for k in a:
         assert torch.equal(a[k].view(torch.uint8), b[k].view(torch.uint8)), k
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
+@pytest.mark.parametrize("ncut", [1, 31, 64, 65, 129, 300, 700])
+def test_cut_tokens_with_one_several_and_too_many_candidates(oracle, dtype, ncut):
+    # 96 stored entries along axes, twice each so that they are picked first; the tokens whose entries are cut are near one
+    # of them, or between two (equal cosines, or a little off), or as near to 64 of them (more than a list of candidates
+    # holds), or zero, or hold a NaN; blocks of 64 cut tokens where they are few, of 256 where they are more than a
+    # quarter, ragged either way
+    rng = np.random.default_rng(ncut)
+    axes = np.repeat(np.eye(128)[:96], 2, axis=0) * rng.uniform(0.5, 2.0, (192, 1))
+    far = rng.standard_normal((ncut, 128))
+    far /= np.linalg.norm(far, axis=1, keepdims=True)
+    kind = np.arange(ncut) % 5
+    for i in range(ncut):
+        j, k = rng.choice(96, 2, replace=False)
+        if kind[i] == 1:
+            far[i] = 0.3 * far[i]
+            far[i, j] = 0.9
+        elif kind[i] == 2:
+            far[i, [j, k]] = 0.5 + (i % 2) * rng.uniform(0.0, 2e-3, 2)
+        elif kind[i] == 3:
+            far[i] = rng.choice([-1.0, 1.0], 128)
+    if ncut > 60:
+        far[50], far[55] = 0.0, 1.0
+    x = np.concatenate([axes, far])[rng.permutation(192 + ncut)]
+    K = wl.cast(x[None, None], dtype)
+    if ncut > 60:
+        spoilt = int(np.flatnonzero((x == 1.0).all(1))[0])
+        K[0, 0, spoilt, 3] = wl.cast(np.array([np.nan]), dtype)[0]
+    L = wl.Layer(dtype, K, K.copy(), np.zeros_like(K[:, :, :1]), 1, 1, 1, 192 + ncut, 96, theta_k=0.97, theta_v=0.97)
+    if ncut <= 60:
+        res, g = parity.check_shallow_layer(oracle, L, tensors=("k",), debug=False)
+        assert res[0]["n_codes_uncapped"] > 96
+        return
+    # (the oracle's cosine of a NaN is not the library's business: that token's own reference only has to exist)
+    g = parity.gpu_shallow(L, tensors=("k",), debug=False)
+    clean = np.array(L.K)
+    clean[0, 0, spoilt] = wl.cast(np.ones(128), dtype)
+    o = oracle.shallow_unit(wl.to_f64(clean[0, 0], dtype), float(np.float32(0.97)), 96)
+    keep = np.arange(192 + ncut) != spoilt
+    assert np.array_equal(g["ref_k"][0, 0][keep], o["ref"][keep]) and 0 <= g["ref_k"][0, 0, spoilt] < 96
