@@ -55,7 +55,13 @@ constexpr int kStageBytes = kStageCols * 256;   // staged tokens: unpadded rows,
 constexpr float kSketchScale = 300.f;
 constexpr int kSketchBytes = 64;
 constexpr int kTile = 32;                        // tokens per tile of the sorted order
-constexpr int kTileBytes = kTile * kSketchBytes;   // sketches of a tile, in matrix-core fragment order
+constexpr int kTileBytes = kTile * kSketchBytes;   // sketches of a tile as bytes
+// What shallow_scan multiplies are the sketches in six-bit floats (two exponent and three mantissa bits, up to 7.5),
+// kSixScale of the integers to the unit: twice the rate of bytes on the matrix cores.  They are off by 0.025 of a unit
+// vector where the bytes are by 0.008; a clustered layer has as many tile pairs marked all the same (2.3 % of them).
+// Products are multiples of 2^-6 below 2^12, so their sums are exact.
+constexpr float kSixScale = 16.f;
+constexpr int kSixBytes = kTile * 48;            // of a tile: 16 bytes of every lane's 24, then 8 of every lane
 constexpr int kScanPanel = 16;                   // row tiles of a block of shallow_scan
 constexpr int kScanStage = 8;                    // column tiles it stages at a time
 constexpr int kScanRun = 16;                     // stages of a block at most
@@ -100,12 +106,12 @@ struct ShallowParams {
   uint16_t *perm, *iperm;  // [UT][n] token at a position, position of a token
   float *invp;             // [UT][n] factor of a row in the cosine (see shallow_rows), by position
   uint8_t *sk0;            // [UT][n][64] sketches by token
-  uint2 *inv_err;          // [UT][n] by token (scan): the factor, and the distance of the sketch from what it stands for, sketch units squared
+  float2 *inv_err;         // [UT][n] by token (scan): the factor, and the distance of the sketch from what it stands for (< 0: says nothing)
   uint16_t *bucket;        // [UT][n] pivot of a token
   uint32_t *mean;          // [UT][2] first eight coordinates of the pivots' mean
   uint16_t *hist;          // [UT][order blocks][kPivots] tokens per bucket in each block of tokens
-  int8_t *sk;              // [UT][Tp][kTileBytes] sketches by position
-  uint32_t *etile;         // [UT][Tp] largest distance of a sketch of a tile
+  uint8_t *sk;             // [UT][Tp][kSixBytes] sketches by position, in six-bit floats
+  uint32_t *etile;         // [UT][Tp] what a tile's sketches may be off by in a product, sketch units squared
   uint32_t *tpairs;        // [UT][T][TW] bit t of row r: tiles r and t may hold a pair above theta
   int T, Tp, TW;           // tiles, rounded up to whole panels; words per row of tpairs
   int scan;                // 1: tokens are sorted and tpairs says which tiles count; 0: all tiles, positions = tokens

@@ -43,11 +43,11 @@ size_t carve(ShallowParams &p, void *ws, int UT, int n) {
   p.iperm = cv.take<uint16_t>(N);
   p.invp = cv.take<float>(N);
   p.sk0 = cv.take<uint8_t>(N * kSketchBytes);
-  p.inv_err = cv.take<uint2>(N);
+  p.inv_err = cv.take<float2>(N);
   p.bucket = cv.take<uint16_t>(N);
   p.mean = cv.take<uint32_t>((size_t)UT * 2);
   p.hist = cv.take<uint16_t>((size_t)UT * ((n + kOrderTokens - 1) / kOrderTokens) * kPivots);
-  p.sk = cv.take<int8_t>((size_t)UT * p.Tp * kTileBytes);
+  p.sk = cv.take<uint8_t>((size_t)UT * p.Tp * kSixBytes);
   p.todo = cv.take<uint32_t>(scan_blocks(p));
   p.alive = cv.take<int>(N);
   p.n16 = (n + 15) & ~15;

@@ -151,13 +151,7 @@ __global__ __launch_bounds__(256) void shallow_prep(ShallowParams p, size_t nzer
         u4 piece = {w[0], w[1], w[2], w[3]};
         if (!fine) piece = u4{0, 0, 0, 0};
         *reinterpret_cast<u4 *>(p.sk0 + idx * kSketchBytes + part * 16) = piece;
-        // |a.b - a'.b'| <= e_a + e_b + e_a e_b for sketches a', b' at distances e_a, e_b; the last term is at
-        // most half of the two squares.  In sketch units squared, rounded up.
-        const float e = sqrtf(q2) * (1.f / kSketchScale);
-        if (part == 0)
-          p.inv_err[idx] = make_uint2(
-              __float_as_uint(row_factor[r]),
-              fine && e < 4.f ? (uint32_t)((e + 0.5f * e * e) * (kSketchScale * kSketchScale * (1.f + 1e-5f))) + 2u : kSketchUnknown);
+        if (part == 0) p.inv_err[idx] = make_float2(row_factor[r], fine ? sqrtf(q2) * (1.f / kSketchScale) : -1.f);
       }
     }
   }

@@ -8,6 +8,7 @@ namespace spindle {
 namespace {
 
 typedef int i4v __attribute__((ext_vector_type(4)));
+typedef int i8v __attribute__((ext_vector_type(8)));
 typedef int i16v __attribute__((ext_vector_type(16)));
 
 // ---------------------------------------------------------------- order
@@ -231,6 +232,24 @@ __global__ __launch_bounds__(kPivots) void shallow_order(ShallowParams p, int nb
 // (256 bins per pivot, of which no more than kMany fit the window).  Where all of them were compared, isolated tokens, which
 // stand with the lowest pivots, cost 2048 comparisons each: 51 us for the kernel on two
 // problems of 32768 rows, 182 on 64, now 21 and 99; a bitonic sort took longer than comparing clusters.
+typedef uint32_t u6 __attribute__((ext_vector_type(6)));
+typedef float f32v __attribute__((ext_vector_type(32)));
+
+// 32 numbers / kSixScale to six-bit floats (a[0], b[0], a[1], b[1], ...) and back, the 192 bits as a lane's half of a row
+// in a 32x32x64 matrix instruction.  As assembly, since the result must not share registers with the operands
+// (which are read while it is written); the compiler's own form lets it.  The result may not be read by the
+// instruction right behind.
+__device__ __forceinline__ u6 to_six(const f16v &a, const f16v &b) {
+  u6 r;
+  asm("v_cvt_scalef32_2xpk16_fp6_f32 %0, %1, %2, %3\n\ts_nop 7" : "=&v"(r) : "v"(a), "v"(b), "v"(kSixScale));
+  return r;
+}
+__device__ __forceinline__ f32v from_six(const u6 &x) {
+  f32v r;
+  asm("v_cvt_scalef32_pk32_f32_fp6 %0, %1, %2\n\ts_nop 7" : "=&v"(r) : "v"(x), "v"(kSixScale));
+  return r;
+}
+
 constexpr int kWindow = 2048;
 constexpr int kWindowThreads = 1024;
 constexpr int kFew = 64, kMany = kWindow / kFew;
@@ -321,9 +340,9 @@ __global__ __launch_bounds__(kWindowThreads) void shallow_window(ShallowParams p
     at_place[lo[k] + under + before[k]] = (uint16_t)tok[k];
   }
   __syncthreads();
-  // A wave takes 32 places at a time: their sketches are read four lanes to a row and turned to fragment order in LDS
-  // (which the counts no longer need).
-  int8_t *sk = p.sk + (size_t)ut * p.Tp * kTileBytes;
+  // A wave takes 32 places at a time: their sketches are read four lanes to a row, turned to fragment order in LDS
+  // (which the counts no longer need) and rounded to six-bit floats.
+  uint8_t *sk = p.sk + (size_t)ut * p.Tp * kSixBytes;
   char *turn = reinterpret_cast<char *>(&count[0][0]) + wave * kTileBytes;
   static_assert(sizeof(count) >= kWindowThreads / kWave * kTileBytes, "a tile per wave");
   const int end = w1 < n ? w1 : p.Tp * kTile;         // the last window also fills the places past the last token
@@ -335,18 +354,18 @@ __global__ __launch_bounds__(kWindowThreads) void shallow_window(ShallowParams p
       v[j] = u4{0, 0, 0, 0};
       if (pos < n) v[j] = reinterpret_cast<const u4 *>(p.sk0 + (base + at_place[pos - w0]) * kSketchBytes)[lane & 3];
     }
-    uint32_t e = 0;
-    if (lane < kTile && p0 + lane < n) {
-      const int pos = p0 + lane, t = (int)at_place[pos - w0];
-      const uint2 f = p.inv_err[base + t];
-      p.perm[base + pos] = (uint16_t)t;
-      p.iperm[base + t] = (uint16_t)pos;
-      p.invp[base + pos] = __uint_as_float(f.x);
-      e = f.y;
+    float off = 0.f;                                   // of the bytes from what they stand for
+    const int pos = p0 + (lane & 31);
+    if (pos < n) {
+      const int t = (int)at_place[pos - w0];
+      const float2 f = p.inv_err[base + t];
+      off = f.y;
+      if (lane < kTile) {
+        p.perm[base + pos] = (uint16_t)t;
+        p.iperm[base + t] = (uint16_t)pos;
+        p.invp[base + pos] = f.x;
+      }
     }
-#pragma unroll
-    for (int o = 16; o > 0; o >>= 1) e = max(e, (uint32_t)__shfl_xor((int)e, o));
-    if (lane == 0) p.etile[(size_t)ut * p.Tp + (p0 >> 5)] = e;
     // piece k of row r at place k ^ (r / 4) % 4: sixteen consecutive lanes of either access hit all banks
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // the tile before has been read
 #pragma unroll
@@ -355,12 +374,34 @@ __global__ __launch_bounds__(kWindowThreads) void shallow_window(ShallowParams p
       *reinterpret_cast<u4 *>(turn + r * kSketchBytes + (((lane & 3) ^ ((r >> 2) & 3)) << 4)) = v[j];
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // LDS keeps the order of one wave's accesses
-    u4 *d = reinterpret_cast<u4 *>(sk + (size_t)(p0 >> 5) * kTileBytes);
+    f16v x[2];                                         // a row's pieces g and g + 2
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
       const int r = lane & 31, piece = 2 * k + (lane >> 5);
-      d[k * 64 + lane] = *reinterpret_cast<const u4 *>(turn + r * kSketchBytes + ((piece ^ ((r >> 2) & 3)) << 4));
+      const u4 y = *reinterpret_cast<const u4 *>(turn + r * kSketchBytes + ((piece ^ ((r >> 2) & 3)) << 4));
+#pragma unroll
+      for (int i = 0; i < 16; ++i) x[k][i] = (float)(int)__builtin_amdgcn_sbfe((int)y[i >> 2], 8 * (i & 3), 8);
     }
+    const u6 six = to_six(x[0], x[1]);
+    const f32v back = from_six(six);
+    float d2 = 0.f;                                    // squared distance of the six-bit floats from the bytes
+#pragma unroll
+    for (int i = 0; i < 32; ++i) {
+      const float d = back[i] - x[i & 1][i >> 1];
+      d2 = fmaf(d, d, d2);
+    }
+    d2 += __shfl_xor(d2, 32);
+    // |a.b - a'.b'| <= e_a + e_b + e_a e_b for sketches a', b' at distances e_a, e_b; the last term is at
+    // most half of the two squares.  In sketch units squared, rounded up.
+    const float dist = off + sqrtf(d2) * (1.0001f / kSketchScale);
+    uint32_t e = off >= 0.f && dist < 4.f ? (uint32_t)((dist + 0.5f * dist * dist) * (kSketchScale * kSketchScale * (1.f + 1e-5f))) + 2u : kSketchUnknown;
+    if (pos >= n) e = 0;
+#pragma unroll
+    for (int o = 16; o > 0; o >>= 1) e = max(e, (uint32_t)__shfl_xor((int)e, o));
+    if (lane == 0) p.etile[(size_t)ut * p.Tp + (p0 >> 5)] = e;
+    uint8_t *d = sk + (size_t)(p0 >> 5) * kSixBytes;
+    reinterpret_cast<u4 *>(d)[lane] = u4{six[0], six[1], six[2], six[3]};
+    reinterpret_cast<uint2 *>(d + 1024)[lane] = make_uint2(six[4], six[5]);
   }
 }
 
@@ -410,9 +451,10 @@ __device__ __forceinline__ void put_marks(const ShallowParams &p, int ut, int r0
 
 // The row tiles' sketches stay in registers as the matrix columns, four tiles per wave; the column tiles are
 // staged through LDS eight at a time (fragment order: loads and reads are both linear, no bank conflicts).  Per
-// 32 x 32 pairs two 32x32x32 int8 matrix instructions; all the results are needed for is their maximum, eight
-// v_max3 per lane, and one comparison for the wave's four tiles.  Tiles that pass are marked in both
-// directions.  16 problems of 32768 tokens: 0.38 ms = 2.9 POP/s; all cosines in fp16, with the bits packed
+// 32 x 32 pairs one 32x32x64 matrix instruction on six-bit floats; all the results are needed for is their maximum, eight
+// v_max3 per lane (which take as long as the matrix instruction), and one comparison for the wave's four tiles.  Tiles
+// that pass are marked in both directions.  16 problems of 32768 tokens: 0.27 ms; with bytes, two 32x32x32
+// instructions, 0.38 ms; all cosines in fp16, with the bits packed
 // and records written, took 1.80 ms.
 // A block that finds more than kRefineShare of its column tiles marked (keys with a common component, low
 // thresholds) stops and leaves all of its pairs to shallow_refine.  The panel's own columns don't count, and a
@@ -420,7 +462,7 @@ __device__ __forceinline__ void put_marks(const ShallowParams &p, int ut, int r0
 constexpr int kScanThreads = 256;
 
 __global__ __launch_bounds__(kScanThreads, 2) void shallow_scan(ShallowParams p) {
-  __shared__ __attribute__((aligned(1024))) char stage[2][kScanStage * kTileBytes];
+  __shared__ __attribute__((aligned(1024))) char stage[2][kScanStage * kSixBytes];
   __shared__ uint8_t marks[kScanPanel][kScanRun];
   __shared__ int found[kScanRun];                      // marks of a stage, once for the four row tiles of a wave
   const int xcd = blockIdx.x & 7;
@@ -430,36 +472,45 @@ __global__ __launch_bounds__(kScanThreads, 2) void shallow_scan(ShallowParams p)
     return;
   }
   const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const char *sk = reinterpret_cast<const char *>(p.sk) + (size_t)w.ut * p.Tp * kTileBytes;
+  const char *sk = reinterpret_cast<const char *>(p.sk) + (size_t)w.ut * p.Tp * kSixBytes;
   const uint32_t *et = p.etile + (size_t)w.ut * p.Tp;
   const int r0 = w.I * kScanPanel + wave * 4;
   const int thr0 = p.scan_thr[w.ut / p.U];
+  constexpr float kUnit = 1.f / (kSixScale * kSixScale);   // products are in units of kSixScale squared
   reinterpret_cast<uint8_t *>(marks)[threadIdx.x] = 0;
   if (threadIdx.x < kScanRun) found[threadIdx.x] = 0;
-  i4v bf[4][2];
-  int ethr[4];                                         // theta less the row tile's error
+  auto tile_at = [&](const char *t) __attribute__((always_inline)) {
+    const u4 a = *reinterpret_cast<const u4 *>(t + lane * 16);
+    const uint2 b = *reinterpret_cast<const uint2 *>(t + 1024 + lane * 8);
+    return i8v{(int)a[0], (int)a[1], (int)a[2], (int)a[3], (int)b.x, (int)b.y, 0, 0};
+  };
+  i8v bf[4];
+  float ethr[4];                                       // theta less the row tile's error
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
-    bf[r][0] = *reinterpret_cast<const i4v *>(sk + (size_t)(r0 + r) * kTileBytes + lane * 16);
-    bf[r][1] = *reinterpret_cast<const i4v *>(sk + (size_t)(r0 + r) * kTileBytes + 1024 + lane * 16);
-    ethr[r] = thr0 - (int)et[r0 + r];
+    bf[r] = tile_at(sk + (size_t)(r0 + r) * kSixBytes);
+    ethr[r] = (float)(thr0 - (int)et[r0 + r]) * kUnit;
   }
-  const int emin = min(min(ethr[0], ethr[1]), min(ethr[2], ethr[3]));
+  const float emin = fminf(fminf(ethr[0], ethr[1]), fminf(ethr[2], ethr[3]));
   const uint32_t stage_lds = (uint32_t)(size_t)(__attribute__((address_space(3))) char *)stage;
+  constexpr int kLoads = kScanStage * kSixBytes / 1024 / (kScanThreads / kWave);   // of 1 KiB per wave and stage
+  static_assert(kLoads * 1024 * (kScanThreads / kWave) == kScanStage * kSixBytes, "whole loads");
   auto dma = [&](int s) {
-    const char *src = sk + (size_t)s * (kScanStage * kTileBytes) + wave * 4096;
+    const char *src = sk + (size_t)s * (kScanStage * kSixBytes) + wave * (kLoads * 1024);
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
+    for (int q = 0; q < kLoads; ++q)
       lds_dma16_at(src, (uint32_t)(q * 1024 + lane * 16),
-                   stage_lds + (s & 1) * (kScanStage * kTileBytes) + wave * 4096 + q * 1024);
+                   stage_lds + (s & 1) * (kScanStage * kSixBytes) + wave * (kLoads * 1024) + q * 1024);
   };
+  // What the integers of results above a threshold exceed: all of them where it isn't positive (no result is -0).
+  auto above = [](float thr) __attribute__((always_inline)) { return thr > 0.f ? __float_as_int(thr) : INT32_MIN; };
   constexpr int kPerStage = kScanPanel / 4 * kScanStage;   // column tiles, once per wave
   const int own = (w.I + 1) * (kScanPanel / kScanStage);   // first stage behind the panel's own columns
   int all = 0;                                         // marks of the stages from there on
   bool refine = false;
   dma(w.s0);
   for (int s = w.s0;; ++s) {
-    const int ecol = s < w.s1 ? (int)et[s * kScanStage + (lane & 7)] : 0;
+    const float ecol = s < w.s1 ? (float)et[s * kScanStage + (lane & 7)] * kUnit : 0.f;
     __builtin_amdgcn_s_waitcnt(0x0F70);                // vmcnt(0): this wave's part of stage s has landed
     __syncthreads();                                   // ... and every wave's; the other buffer is free
     if (s > w.s0 && s > own) {
@@ -470,27 +521,29 @@ __global__ __launch_bounds__(kScanThreads, 2) void shallow_scan(ShallowParams p)
     if (s == w.s1) break;
     if (s + 1 < w.s1) dma(s + 1);
     const char *st = stage[s & 1];
+    const int least = above(emin - ecol);              // lane t: of column tile t
     uint32_t hit[4] = {0, 0, 0, 0};
 #pragma unroll
     for (int t = 0; t < kScanStage; ++t) {
-      const i4v a0 = *reinterpret_cast<const i4v *>(st + t * kTileBytes + lane * 16);
-      const i4v a1 = *reinterpret_cast<const i4v *>(st + t * kTileBytes + 1024 + lane * 16);
-      int m[4];
+      const i8v a = tile_at(st + t * kSixBytes);
+      int m[4];                                        // (as integers: floats order alike as far as it matters)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        i16v acc = {};
-        acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(a0, bf[r][0], acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(a1, bf[r][1], acc, 0, 0, 0);
-        int x = acc[0];
+        f16v acc;
 #pragma unroll
-        for (int v = 1; v < 16; ++v) x = max(x, acc[v]);
+        for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+        // (formats 2: six bits, two of them exponent; no block scales)
+        acc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, bf[r], acc, 2, 2, 0, 0, 0, 0);
+        int x = __float_as_int(acc[0]);
+#pragma unroll
+        for (int v = 1; v < 16; ++v) x = max(x, __float_as_int(acc[v]));
         m[r] = x;
       }
-      const int ec = __builtin_amdgcn_readlane(ecol, t);
-      if (__any(max(max(m[0], m[1]), max(m[2], m[3])) > emin - ec)) {
+      if (__any(max(max(m[0], m[1]), max(m[2], m[3])) > __builtin_amdgcn_readlane(least, t))) {
+        const float ec = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(ecol), t));
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-          if (__any(m[r] > ethr[r] - ec)) hit[r] |= 1u << t;
+          if (__any(m[r] > above(ethr[r] - ec))) hit[r] |= 1u << t;
       }
     }
     if (hit[0] | hit[1] | hit[2] | hit[3]) {
@@ -566,6 +619,7 @@ __global__ __launch_bounds__(kRefineThreads, 2) void shallow_refine(ShallowParam
       const size_t base = (size_t)w.ut * n;
       const char *X = kRaw ? x_row(p, w.ut, 0) : reinterpret_cast<const char *>(p.Xh) + base * 256;
       const size_t pitch = kRaw ? (size_t)p.lay.st : 256;
+      const bool narrow = pitch < 1u << 24 && pitch * n <= 0xFFFFFFFFull;   // (a product of 64 bits is sixteen times the cycles)
       const float *inv = p.invp + base;
       const uint16_t *perm = p.perm + base;
       const uint32_t *et = p.etile + (size_t)w.ut * p.Tp;
@@ -611,8 +665,10 @@ __global__ __launch_bounds__(kRefineThreads, 2) void shallow_refine(ShallowParam
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           const int r = (wave * 4 + q) * 4 + (lane >> 4);
-          lds_dma16(X + cols[s * kStageCols + r] * pitch + (((lane & 15) ^ ((r & 7) | ((r & 16) >> 1))) << 4),
-                    stage_lds + (s % kRefineStages) * kStageBytes + (wave * 4 + q) * 1024);
+          const uint32_t tok = cols[s * kStageCols + r], piece = (((lane & 15) ^ ((r & 7) | ((r & 16) >> 1))) << 4);
+          const uint32_t to = stage_lds + (s % kRefineStages) * kStageBytes + (wave * 4 + q) * 1024;
+          if (narrow) lds_dma16_at(X, __umul24(tok, (uint32_t)pitch) + piece, to);
+          else lds_dma16(X + tok * pitch + piece, to);
         }
       };
       // results of column tile t; thr is positive: floats order as integers as far as it matters
