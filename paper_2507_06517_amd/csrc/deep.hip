@@ -76,10 +76,17 @@ struct Geo {
     for (int j = 0; j < kLoadsPerWave; ++j) lds_dma16_at(base, off[j], lds + (wave * kLoadsPerWave + j) * 1024);
   }
   static constexpr int kFrags = DT == SPINDLE_F32 ? 16 : 8;        // 16-byte pieces of a row per lane group
-  // MFMA operand pieces j of staged row `row` for lane group g: piece 2 j + g (one step of a 16-bit type; four of
-  // fp32, whose lane groups may hold any dimensions as long as both operands agree)
+  // MFMA operand j of staged row `row` for lane group g: one step of a 16-bit type, which is piece 2 j + g; four steps
+  // of fp32, dimensions 8 j + 2 i + g, of which two pieces have every second one (a lane group could hold the pieces as
+  // they are, but the sums would take the dimensions in another order, and scores of fp32 calls would differ by 2e-6).
   static __device__ __forceinline__ u4 piece(const char *buf, int row, int j, int g) {
-    return *reinterpret_cast<const u4 *>(buf + row * kRowBytes + (((2 * j + g) ^ (row & (kPieces - 1))) << 4));
+    auto at = [&](int q) __attribute__((always_inline)) { return buf + row * kRowBytes + ((q ^ (row & (kPieces - 1))) << 4); };
+    if constexpr (DT == SPINDLE_F32) {
+      const uint32_t *x = reinterpret_cast<const uint32_t *>(at(2 * j)) + g, *y = reinterpret_cast<const uint32_t *>(at(2 * j + 1)) + g;
+      return u4{x[0], x[2], y[0], y[2]};
+    } else {
+      return *reinterpret_cast<const u4 *>(at(2 * j + g));
+    }
   }
   static __device__ __forceinline__ f16v mma(u4 a, u4 b, f16v c) {
     if constexpr (DT == SPINDLE_F32) {
