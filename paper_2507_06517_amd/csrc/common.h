@@ -64,7 +64,7 @@ spindle_status allow_lds(LdsLimit &state, const void *kernel, size_t bytes);
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
-inline int dtype_bytes(int dt) { return dt == SPINDLE_F32 ? 4 : 2; }
+constexpr int dtype_bytes(int dt) { return dt == SPINDLE_F32 ? 4 : 2; }
 
 // Bump allocator over the caller's workspace.
 struct Carver {

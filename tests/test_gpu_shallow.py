@@ -300,3 +300,23 @@ def test_cut_tokens_with_one_several_and_too_many_candidates(oracle, dtype, ncut
     o = oracle.shallow_unit(wl.to_f64(clean[0, 0], dtype), float(np.float32(0.97)), 96)
     keep = np.arange(192 + ncut) != spoilt
     assert np.array_equal(g["ref_k"][0, 0][keep], o["ref"][keep]) and 0 <= g["ref_k"][0, 0, spoilt] < 96
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
+@pytest.mark.parametrize("units,n,cap", [(1, 1, 1), (3, 63, 7), (2, 65, 300), (5, 129, 64), (1, 70001, 33), (40, 4100, 9)])
+def test_reconstruct_blocks_and_large_outputs(dtype, units, n, cap):
+    # around the rows a block takes, several units, and outputs above 32 MiB, which are streamed; references out of the
+    # table give zero rows.  The product of two floats rounded to the cache type: exact
+    import torch
+    from paper_2507_06517_amd import binding as sb
+    g = torch.Generator(device="cuda").manual_seed(n)
+    dt = sb.torch_dtype(dtype)
+    Cb = torch.randn((1, units, cap, 128), generator=g, device="cuda").to(dt)
+    ref = torch.randint(-1, cap + 1, (1, units, n), generator=g, device="cuda", dtype=torch.int32)
+    mag = torch.rand((1, units, n), generator=g, device="cuda") * 20
+    R = sb.reconstruct(Cb, ref, mag, dtype)
+    ok = (ref >= 0) & (ref < cap)
+    at = ref.clamp(0, cap - 1).long().unsqueeze(3).expand(1, units, n, 128)
+    want = (torch.gather(Cb.float(), 2, at) * mag.unsqueeze(3)).to(dt)
+    want = torch.where(ok.unsqueeze(3), want, torch.zeros_like(want))
+    assert torch.equal(R, want)
