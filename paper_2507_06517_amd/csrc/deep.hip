@@ -9,9 +9,10 @@
 //                     the last workgroup of a unit finds the k-th largest score from the
 //                     histogram and the few scores that share its bin, then writes the kept
 //                     positions in order (Eq. 7)
+//   deep_select_unit  the same by one workgroup per unit, scores and keys in LDS, for shorter contexts
 //   deep_gather       K_out = K[kept], V_out = V[kept]
 //
-// Both passes over K stream 64-KiB stages of keys through LDS with direct global->LDS loads
+// Both passes over K stream stages of up to 64 KiB of keys through LDS with direct global->LDS loads
 // (two stages, the next one in flight while the current one is multiplied); the 16-byte pieces
 // of a row are XOR-swizzled by the row number so that the fragment reads of sixteen
 // consecutive rows fall into different banks.

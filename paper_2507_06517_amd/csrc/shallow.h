@@ -6,7 +6,7 @@
 //                   products bound the cosines from above
 //   shallow_pivots, shallow_order, shallow_window
 //                   the tokens of a problem sorted so that similar ones stand together
-//   shallow_scan    sketch products of all pairs of 32-token tiles on the int8 matrix cores:
+//   shallow_scan    sketch products of all pairs of 32-token tiles, in six-bit floats:
 //                   which tiles can hold a pair above theta at all
 //   shallow_refine  where the sketches exclude little, the same from the rows
 //   shallow_rows    for those tiles the cosines themselves (Eq. 4, 9), decided exactly; degrees
@@ -77,14 +77,14 @@ inline int scan_pays(int UT, int n) {
   return n >= 2048 || (n >= 1024 && UT * T * (T - 24) >= 18000);
 }
 // Below kSketchMinTheta the sketches are not asked: a sketch product of unrelated tokens is about 0.53 with a
-// spread of 0.06, so the largest of a pair of tiles is above 0.7 nearly always.  Below kVectorMinTheta the unit
+// spread of 0.06, so the largest of a pair of tiles is above 0.7 nearly always.  Below kVectorMinTheta the full
 // vectors are not asked either: at 0.3 a third of the pairs of tiles of unrelated tokens hold a cosine above it, three
 // quarters for four row tiles together, and what is left out of shallow_rows is what finding it takes.
 constexpr float kSketchMinTheta = 0.7f, kVectorMinTheta = 0.3f;
 enum { kByNone, kByVector, kBySketch };
-// Column tiles a scan block may mark before the unit vectors decide instead, counted once for the four row tiles
-// that shallow_rows takes together: all pairs from the unit vectors cost a fifth of what shallow_rows takes
-// for all of them (16 problems of 32768 tokens: 1.8 and 9.9 ms).
+// Column tiles a scan block may mark before the full vectors decide instead, counted once for the four row tiles
+// that shallow_rows takes together: all pairs in shallow_refine cost a fifth of what shallow_rows takes
+// for all of them (16 problems of 32768 tokens: 2.0 and 9.9 ms).
 constexpr float kRefineShare = 0.22f;
 
 constexpr int kCounters = 32;     // ints per ut
@@ -99,7 +99,7 @@ struct ShallowParams {
   int cap;
   // workspace
   _Float16 *Xh;            // [UT][n][128] fp32 inputs: unit vectors
-  _Float16 *Xe;            // [UT][n][128] unit vectors of the stored entries, where tokens were cut
+  _Float16 *Xe;            // [UT][n][128] unit vectors of the stored entries, where tokens were cut; the room of Xl
   double *m64;             // [UT][n]
   int *slot, *alive, *cand, *dying, *rank, *rank_vert;   // [UT][n] (cand: candidate bits in the grid rounds)
   // Lists, keys and everything after them count tokens by position: place in the sorted order.

@@ -34,7 +34,7 @@ size_t carve(ShallowParams &p, void *ws, int UT, int n) {
   p.njg = (nS + p.stages_per_item - 1) / p.stages_per_item;
   p.Xe = cv.take<_Float16>((N + 512) * kHeadDim);   // the similarity loop stages up to 5 tiles past the last token
   p.Xh = p.dtype == SPINDLE_F32 ? cv.take<_Float16>(N * kHeadDim) : nullptr;
-  p.Xl = p.dtype == SPINDLE_F32 ? cv.take<_Float16>(N * kHeadDim) : nullptr;
+  p.Xl = p.Xe;                                      // (for shallow_rows only, which is done when entries are written)
   p.m64 = cv.take<double>(N);
   p.list_row = p.T;
   p.lists = cv.take<uint32_t>(N * p.list_row);
