@@ -22,10 +22,9 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 PEAK_MFMA_F16_TFLOPS = 2500.0      # MI355X dense fp16 matrix peak
-PEAK_MFMA_I8_TOPS = 5000.0         # MI355X dense int8 matrix peak
+PEAK_MFMA_F6_TFLOPS = 10000.0      # MI355X dense six-bit float matrix peak
 PEAK_HBM_GBS = 8000.0
-SKETCH_DIMS = 64                    # bytes of a token's sketch: multiply-adds per pair of tokens of the scan
-PEAK_VALU_F64_TFLOPS = 78.6         # 256 CUs x 64 lanes x 2 flop x 2.4 GHz
+SKETCH_DIMS = 64                    # values of a token's sketch: multiply-adds per pair of tokens of the scan
 
 
 # sets of buffers the pipelined steps rotate over (2.60 ms per step with two, 2.56 with three, 2.60 with four)
@@ -156,7 +155,7 @@ def config5_layer(torch, sb, wl, cap=4096, steps=8, warmup=3):
     out = {"workload": f"configs[4], one layer: batch 4 x {L.seq_len}, bf16, pool 15, budget = cap = {cap}; one stream",
            "steps": steps, "ms_per_step": ms, "tokens_per_s": L.batch * L.seq_len / (ms * 1e-3), "kernel_ms": per,
            "deep_call_ms": deep_ms, "deep_frac_of_hbm": nbytes / (deep_ms * 1e-3) / 1e9 / PEAK_HBM_GBS,
-           "shallow_scan_frac_of_mfma_i8": scan_ops / (per["shallow_scan"] * 1e-3) / 1e12 / PEAK_MFMA_I8_TOPS}
+           "shallow_scan_frac_of_mfma_f6": scan_ops / (per["shallow_scan"] * 1e-3) / 1e12 / PEAK_MFMA_F6_TFLOPS}
     del deep, shallow, K, V, Q
     torch.cuda.empty_cache()
     return out
@@ -194,8 +193,8 @@ def time_reconstruct(torch, sb, L, shallow, reps=20):
 def time_decode(torch, sb, L, K, shallow, m=256, novel=0.25, reps=10):
     """Decode-time merge on the step's own K codebooks, outside the timed step: m later tokens per
     head (tokens of the layer at random positions with 1 % noise; a quarter replaced by directions
-    the layer never saw) merged into the stored entries.  Dominant kernel: the double-precision
-    search of the stored entries, 2 x 128 flop per (token, entry) on the vector ALUs."""
+    the layer never saw) merged into the stored entries.  decode_match, the search of the stored entries, is 2 x 128
+    flop per (token, entry) on the fp16 matrix cores, a few microseconds at their rate: latency bounds it."""
     g = torch.Generator(device="cuda").manual_seed(5)
     pos = torch.randint(0, L.seq_len, (m,), generator=g, device="cuda")
     base = K[:, :, pos].float()
@@ -237,8 +236,8 @@ def time_decode(torch, sb, L, K, shallow, m=256, novel=0.25, reps=10):
             "entries_after": out["n_found"].cpu().numpy().ravel().tolist(),
             "kernel_ms": ms, "tokens_per_s": L.batch * L.n_kv_heads * m / (total * 1e-3),
             "one_token_per_head_call_us": float(np.mean(single)) * 1e3,
-            "roofline": {"kernel": "decode_match", "bound": "alu", "achieved": tf, "peak": PEAK_VALU_F64_TFLOPS,
-                         "unit": "TFLOP/s", "frac": tf / PEAK_VALU_F64_TFLOPS}}
+            "roofline": {"kernel": "decode_match", "bound": "mfma fp16", "achieved": tf, "peak": PEAK_MFMA_F16_TFLOPS,
+                         "unit": "TFLOP/s", "frac": tf / PEAK_MFMA_F16_TFLOPS}}
 
 
 def main():
@@ -373,11 +372,11 @@ def main():
     tokens = L.batch * L.seq_len
     units = L.batch * L.n_kv_heads
     # the kernel that goes over all pairs of tokens: each unordered pair once, one product of
-    # two 64-byte sketches (short prompts: of two tokens): n^2/2 pairs x 64 (128) multiply-adds x 2, per (unit, K|V).
+    # two sketches of 64 values (short prompts: of two tokens): n^2/2 pairs x 64 (128) multiply-adds x 2, per (unit, K|V).
     scanned = pair_kernel == "shallow_scan"
     pair_ops = 2 * units * (L.seq_len ** 2 / 2) * (SKETCH_DIMS if scanned else L.head_dim) * 2
     achieved = pair_ops / (pair_ms * 1e-3) / 1e12
-    pair_peak = PEAK_MFMA_I8_TOPS if scanned else PEAK_MFMA_F16_TFLOPS
+    pair_peak = PEAK_MFMA_F6_TFLOPS if scanned else PEAK_MFMA_F16_TFLOPS
     # what computing every cosine in fp16 would take (the calibration loop below does)
     gram_flop = 2 * units * (L.seq_len ** 2 / 2) * L.head_dim * 2
     out = {
@@ -413,8 +412,8 @@ def main():
         "codebook_entries_found": n_codes,
         "merge_rounds": st[:, 0].tolist(), "pairs_decided_in_f64": int(st[:, 2].sum()),
         "merge_phase_us_unit0": st[0, 4:14].tolist(),
-        "roofline": {"kernel": pair_kernel, "bound": "mfma int8" if scanned else "mfma fp16", "kernel_ms": pair_ms,
-                     "achieved": achieved, "peak": pair_peak, "unit": "TOP/s" if scanned else "TFLOP/s",
+        "roofline": {"kernel": pair_kernel, "bound": "mfma fp6" if scanned else "mfma fp16", "kernel_ms": pair_ms,
+                     "achieved": achieved, "peak": pair_peak, "unit": "TFLOP/s",
                      "frac": achieved / pair_peak},
     }
     # what the part sustains (measurement aids of the library): a register-resident fp16 MFMA loop, and
