@@ -134,6 +134,12 @@ __device__ double dot64(const char *ra, const char *rb) {
   return acc;
 }
 
+// Unsigned numbers in the order of the cosines (-0 as 0), never 0.
+__device__ __forceinline__ unsigned long long order_key(double cs) {
+  const unsigned long long b = (unsigned long long)__double_as_longlong(cs + 0.0);
+  return b >> 63 ? ~b : b | 1ull << 63;
+}
+
 __device__ __forceinline__ int lane_id() { return threadIdx.x & 63; }
 
 // 16 bytes per lane from global memory straight into LDS: lane i's piece lands at

@@ -180,12 +180,6 @@ __device__ __forceinline__ double exact_cosine(const char *x, const char *c) {
   return den > 0.0 ? acc / den : 0.0;
 }
 
-// Unsigned numbers in the order of the cosines (-0 as 0), never 0.
-__device__ __forceinline__ unsigned long long order_key(double cs) {
-  const unsigned long long b = (unsigned long long)__double_as_longlong(cs + 0.0);
-  return b >> 63 ? ~b : b | 1ull << 63;
-}
-
 // Products of 128 terms in fp32 (truncated sums included) and the norms: approximate cosines are off by less than 2.5e-5.
 constexpr float kDecodeGuard = 7e-5f;
 

@@ -95,6 +95,22 @@ def check_deep_layer(orc, L: wl.Layer, budget=None, norm=0, got=None):
     return report
 
 
+def least_us(call, reps=8, calls=5):
+    """Microseconds of `call`, the least of `reps` means over `calls` in a row: for tests that compare durations of one
+    process with a wide margin."""
+    import torch
+    times = []
+    for i in range(reps + 1):
+        begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        begin.record()
+        for _ in range(calls):
+            call()
+        end.record()
+        torch.cuda.synchronize()
+        times.append(begin.elapsed_time(end) / calls * 1e3)
+    return min(times[1:])                              # (the first run loads the kernels)
+
+
 # ------------------------------------------------------------------ codebook path
 
 def gpu_shallow(L: wl.Layer, cap=None, debug=True, tensors=("k", "v")):

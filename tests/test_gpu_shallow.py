@@ -302,6 +302,25 @@ def test_cut_tokens_with_one_several_and_too_many_candidates(oracle, dtype, ncut
     assert np.array_equal(g["ref_k"][0, 0][keep], o["ref"][keep]) and 0 <= g["ref_k"][0, 0, spoilt] < 96
 
 
+@pytest.mark.parametrize("dtype,n,cap", [("f16", 1024, 128), ("bf16", 1024, 128), ("f32", 512, 64), ("f16", 4096, 512)])
+def test_padding_by_the_hundred_is_cut(oracle, dtype, n, cap):
+    # half of a prompt is padding: its zero rows are entries of their own and hundreds of them are cut.  Their cosine is 0 with
+    # every entry, so none of them needs a search: the call takes about as long as one with as many tokens in clusters
+    # (four to five times as long where every such row was compared with all entries, one after the other)
+    from paper_2507_06517_amd import binding as sb
+    L = wl.small_random(n, dtype, B=1, H=1, l=n, lw=1, cap=cap, n_centroids=20, noise_frac=0.0)
+    plain_in = sb.to_device(L.K, dtype), sb.to_device(L.V, dtype)
+    plan = sb.plan_shallow(plain_in[0], dtype, L.theta_k, L.theta_v, cap)
+    plain = parity.least_us(lambda: plan.run(*plain_in))
+    L.K[:, :, ::2], L.V[:, :, ::2] = 0, 0
+    res, _ = parity.check_shallow_layer(oracle, L, debug=False)
+    assert all(o["n_codes_uncapped"] > cap + 200 for o in res)
+    padded = sb.to_device(L.K, dtype), sb.to_device(L.V, dtype)
+    took = parity.least_us(lambda: plan.run(*padded))
+    print("cut padding", dtype, n, cap, round(plain), round(took), flush=True)
+    assert took < 2.0 * plain
+
+
 @pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
 @pytest.mark.parametrize("units,n,cap", [(1, 1, 1), (3, 63, 7), (2, 65, 300), (5, 129, 64), (1, 70001, 33), (40, 4100, 9)])
 def test_reconstruct_blocks_and_large_outputs(dtype, units, n, cap):
