@@ -129,10 +129,20 @@ struct TileRows {
 
 // 1 / norm of a row from its squared norm in fp32: 0 for a zero row, NaN where that or the products may leave
 // the range of fp32 or are no numbers (such rows are decided in double precision).
-template <int DT>
-__device__ __forceinline__ float inverse_of(float ss) {
-  if (DT == SPINDLE_F16 && ss == 0.f) return 0.f;      // (squares of fp16 numbers don't vanish)
+__device__ __forceinline__ float inverse_of(float ss, bool zero) {
+  if (zero) return 0.f;
   return ss > 0x1p-80f && ss < 0x1p100f ? __builtin_amdgcn_rsqf(ss) : NAN;
+}
+
+// Whether a row is zero, where every wave-mate from `group` lanes on has a part of it.  Squares of fp16 numbers don't
+// vanish; for the other types the bits say whether a squared norm of 0 stands for zeros: the padding of a prompt is
+// no reason to decide all of a row's pairs in double precision.  bits(): all words of the lane's part or'ed.
+template <int DT, class F>
+__device__ __forceinline__ bool zero_row(float ss, bool asks, int group, F bits) {
+  if (DT == SPINDLE_F16 || !__any(asks && ss == 0.f)) return ss == 0.f;
+  uint32_t x = bits();
+  for (int o = group; o < kWave; o <<= 1) x |= (uint32_t)__shfl_xor((int)x, o);
+  return ss == 0.f && (x & (DT == SPINDLE_F32 ? 0x7FFFFFFFu : 0x7FFF7FFFu)) == 0u;
 }
 
 // The same where a lane pair (lane, lane + 32) holds the row's fragments.
@@ -151,7 +161,20 @@ __device__ __forceinline__ float inverse_norm(const typename Mma<DT>::frag (&f)[
       }
     }
   }
-  return inverse_of<DT>(ss + __shfl_xor(ss, 32));
+  ss += __shfl_xor(ss, 32);
+  return inverse_of(ss, zero_row<DT>(ss, true, 32, [&]() {
+    uint32_t x = 0;
+#pragma unroll
+    for (int ks = 0; ks < Mma<DT>::kSteps; ++ks) {
+      if constexpr (DT == SPINDLE_F32) {
+        x |= __float_as_uint(f[ks]);
+      } else {
+        const u4 w = __builtin_bit_cast(u4, f[ks]);
+        x |= w[0] | w[1] | w[2] | w[3];
+      }
+    }
+    return x;
+  }));
 }
 
 // cos(x, c) as the decision is defined: double precision, every sum over the dimensions in order, 0 for a zero row.
@@ -821,7 +844,16 @@ __global__ __launch_bounds__(kSmallThreads) void decode_small(DecodeParams p) {
 #pragma unroll
       for (int j = 0; j < 8; ++j) ss = fmaf((float)xf[s][j], (float)xf[s][j], ss);
     ss += __shfl_xor(ss, 16);
-    im = inverse_of<DT>(ss + __shfl_xor(ss, 32));
+    ss += __shfl_xor(ss, 32);
+    im = inverse_of(ss, zero_row<DT>(ss, true, 16, [&]() {
+      uint32_t x = 0;
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const u4 w = __builtin_bit_cast(u4, xf[s]);
+        x |= w[0] | w[1] | w[2] | w[3];
+      }
+      return x;
+    }));
   }
   nc = nc < 0 ? 0 : (nc > p.cap ? p.cap : nc);
   const int ntiles = (nc + 15) / 16;
@@ -849,7 +881,16 @@ __global__ __launch_bounds__(kSmallThreads) void decode_small(DecodeParams p) {
         own = product(f, f, own);
         dot = product(f, xf[s], dot);
       }
-      const float ie = inverse_of<DT>((r16 & 2) ? ((r16 & 1) ? own[3] : own[2]) : ((r16 & 1) ? own[1] : own[0]));
+      const float ss = (r16 & 2) ? ((r16 & 1) ? own[3] : own[2]) : ((r16 & 1) ? own[1] : own[0]);
+      const float ie = inverse_of(ss, zero_row<DT>(ss, quarter == r16 >> 2 && tile * 16 + r16 < nc, 16, [&]() {
+        uint32_t x = 0;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          const u4 w = *reinterpret_cast<const u4 *>(turn[wave] + r16 * row_bytes + (((4 * s + quarter) ^ r16) << 4));
+          x |= w[0] | w[1] | w[2] | w[3];
+        }
+        return x;
+      }));
       const float thr = fmaxf(near, mx - 2.f * kDecodeGuard);
       float x[4];                                    // NaN: a row out of range
       x[0] = dot[0] * quad_lane<0>(ie) * im;

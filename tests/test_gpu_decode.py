@@ -274,6 +274,43 @@ def test_equal_entries_and_rows_out_of_range(oracle, dtype, m):
                 assert res[0]["ref"][0] == 300
 
 
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
+@pytest.mark.parametrize("m", [1, 4, 37, 256])
+def test_zero_tokens_and_entries_take_no_longer_than_others(oracle, dtype, m):
+    # what padding leaves: half of the new tokens zero, half of the stored entries zero.  Their cosines are 0, so none of
+    # their pairs needs double precision: the call takes about as long as one without them (4 to 11 times as long in bf16
+    # and fp32 where a squared norm of 0 counted as out of range); minus zeros and rows of the smallest numbers besides
+    import torch
+    from paper_2507_06517_amd import binding as sb
+    rng = np.random.default_rng(m)
+    k, cap, theta = 1650, 2200, float(np.float32(0.95))
+    ent = rng.standard_normal((8, k, 128))
+    ent /= np.linalg.norm(ent, axis=2, keepdims=True)
+    new = 3.0 * ent[:, k // 2 - m // 2:k // 2 - m // 2 + m] + 0.02 * rng.standard_normal((8, m, 128))
+    took = []
+    for zeros in (False, True):
+        if zeros:
+            new[:, ::2], ent[:, 1::2] = 0.0, 0.0
+            ent[0, 7] = -0.0
+            ent[:, 5, :] = 0.0
+            ent[:, 5, 3] = 2.0 ** -24 if dtype == "f16" else 2.0 ** -130
+        Cb = wl.cast(np.concatenate([ent, np.zeros((8, cap - k, 128))], axis=1)[None], dtype)
+        X = wl.cast(new[None], dtype)
+        nc = np.full((1, 8), k, dtype=np.int32)
+        if zeros:
+            run_and_check(oracle, np.ascontiguousarray(X[:, :2]), np.ascontiguousarray(Cb[:, :2]), nc[:, :2], dtype, theta)
+        Xd, Cd, stored = sb.to_device(X, dtype), sb.to_device(Cb, dtype), torch.from_numpy(nc).cuda()
+        nd = stored.clone()
+
+        def call():
+            nd.copy_(stored)
+            sb.decode_merge(Xd, dtype, theta, Cd, nd)
+
+        took.append(parity.least_us(call, calls=20))
+    print("zero rows at decode", dtype, m, [round(t, 1) for t in took], flush=True)
+    assert took[1] < 2.5 * took[0]
+
+
 def test_rejects_bad_arguments():
     import torch
     from paper_2507_06517_amd import binding as sb
