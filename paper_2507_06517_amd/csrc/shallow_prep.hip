@@ -5,7 +5,11 @@ namespace spindle {
 namespace {
 
 // Counters, errors and marks zero, n_codes = -1 ("not finished"), codebooks zero: every thread of the launch writes
-// its share.  (As a launch of its own it took 3 to 6 us of every call, most of it the launch.)
+// its share.  (As a launch of its own it took 3 to 6 us of every call, most of it the launch.)  A short problem with a
+// large table has blocks behind its tokens that do nothing else, as many as leave a thread kClearPieces pieces, and no more
+// than the chip has compute units: the call for 64 fp16 tokens with tables of 16384 and 65536 rows 69 and 160 us by the
+// block of the tokens alone, 35 and 39 with them (1024 blocks: 8 problems of 512 tokens and 32768 rows 76 -> 80).
+constexpr int kClearPieces = 8, kClearBlocks = 256;
 __device__ __forceinline__ void begin_call(const ShallowParams &p, size_t nzero, size_t cpieces) {
   const size_t stride = (size_t)gridDim.x * gridDim.y * 256;
   const size_t i0 = ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * 256 + threadIdx.x;
@@ -38,6 +42,7 @@ __global__ __launch_bounds__(256) void shallow_prep(ShallowParams p, size_t nzer
   const int ut = blockIdx.y, t = ut / p.U;
   const int row0 = blockIdx.x * kRows;
   begin_call(p, nzero, cpieces);
+  if (row0 >= p.n) return;                             // a block that only clears
   for (int i = threadIdx.x; i < kRows * tpr; i += 256) {
     const int r = i / tpr, ch = i % tpr;
     u4 v = {0, 0, 0, 0};
@@ -168,7 +173,9 @@ __global__ __launch_bounds__(256) void shallow_prep(ShallowParams p, size_t nzer
 }  // namespace
 
 spindle_status launch_prep(const ShallowParams &p, size_t nzero, size_t cpieces, hipStream_t st) {
-  const dim3 pgrid((p.n + 63) / 64, p.UT);
+  const size_t clear = ((size_t)(p.UT / p.U) * cpieces / kClearPieces + 255) / 256;   // blocks, of the whole call
+  const int tokens = (p.n + 63) / 64, wide = (int)(((clear < kClearBlocks ? clear : kClearBlocks) + p.UT - 1) / p.UT);
+  const dim3 pgrid(tokens > wide ? tokens : wide, p.UT);
 #define SPINDLE_PREP(DT)                                                                                          \
   do {                                                                                                            \
     if (p.scan) hipLaunchKernelGGL((shallow_prep<DT, true>), pgrid, dim3(256), 0, st, p, nzero, cpieces);         \
