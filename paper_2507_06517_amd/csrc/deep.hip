@@ -984,16 +984,24 @@ struct DeepLayout {
 // merges): many blocks are as bad as a last round of few.  Statistics, weights and the rest of the call on fp16
 // keys, us: 24 layers of 8192 tokens with 4 stages per block 282, with 6 276, with 8 (three whole rounds) 253; 32 heads of 32768
 // tokens 251, 236 and 227.
+// Every block of the second pass merges the statistics of all chunks of its unit, 32 in flight: 0.3 of a stage for each
+// 32 of them (a stage of fp32 keys takes four times as long).  It keeps one or two units from being cut into 256 chunks:
+// one of 8192 tokens with 256 query rows 39 us by 256 chunks of 32 keys, 27 by 64 of 128; 32768 tokens 53 and 48, two units of
+// 8192 31 and 27; 32 query rows 32 and 21.  Over 1 to 192 units of 512 to 131072 tokens with 32, 128 and 256 query rows the
+// choice is 2.6 % off the best of all stage sizes and counts on average, 19 % at most; without this term 7.4 % and 51 %.  (More than
+// one block of small stages fits a compute unit; counting them so did not choose better.)
 constexpr int kBlocksAtOnce = 256;
 
 void choose_stages(int U, int l, int dtype, int *keys, int *stages) {
   const int full = dtype == SPINDLE_F32 ? 128 : 256;
+  const double merge = dtype == SPINDLE_F32 ? 0.08 : 0.3;
   double best = INFINITY;
   for (int k = full; k >= 32; k /= 2) {
     const int n = (l + k - 1) / k;
     for (int s = 1; s <= kMaxStagesPerBlock; ++s) {
-      const long blocks = (long)U * ((n + s - 1) / s), rounds = (blocks + kBlocksAtOnce - 1) / kBlocksAtOnce;
-      const double t = (double)rounds * (s * ((double)k / full + 0.1) + 1.2);
+      const int chunks = (n + s - 1) / s;
+      const long rounds = ((long)U * chunks + kBlocksAtOnce - 1) / kBlocksAtOnce;
+      const double t = (double)rounds * (s * ((double)k / full + 0.1) + 1.2) + merge * ((chunks + 31) / 32);
       if (t < best) {
         best = t;
         *keys = k;

@@ -116,3 +116,26 @@ def test_stage_sizes_and_blocks(oracle, dtype, H, l, lw, hn):
     kept, _, _, sc = parity.gpu_deep(L)
     for (b, h), p, k in zip(units, p64, k64):
         parity.check_deep_unit(p, k, sc[b, h], kept[b, h], lw, l, {})
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
+@pytest.mark.parametrize("B,H,l,lw,hn", [(1, 1, 2049, 8, 4), (1, 1, 8200, 64, 4), (1, 2, 8191, 32, 4), (1, 1, 33000, 32, 2)])
+def test_few_long_units(oracle, dtype, B, H, l, lw, hn):
+    # one or two units cut into up to a hundred chunks whose statistics every block merges
+    L = wl.small_random(l, dtype, B=B, H=H, l=l, hn=hn, lw=lw, pool=7, budget=lw + 100, n_centroids=24)
+    print("units", dtype, H, l, parity.check_deep_layer(oracle, L), flush=True)
+
+
+@pytest.mark.parametrize("l,lw,hn", [(8192, 64, 4), (8192, 32, 1)])
+def test_one_unit_takes_no_longer_than_eight(l, lw, hn):
+    # (one took 22 to 38 % longer where it was cut into as many chunks as the chip has compute units)
+    import torch
+    from paper_2507_06517_amd import binding as sb
+    took = []
+    for H in (1, 8):
+        g = torch.Generator(device="cuda").manual_seed(H)
+        K, Q = (torch.randn((1, h, n, 128), generator=g, device="cuda").half() for h, n in ((H, l), (H * hn, lw)))
+        plan = sb.plan_deep(K, hn, "f16", lw, 7, lw + 500, want_scores=False)
+        took.append(parity.least_us(lambda: plan.run(K, K, Q), calls=20))
+    print("units", l, lw * hn, [round(t, 1) for t in took], flush=True)
+    assert took[0] < 1.12 * took[1]
