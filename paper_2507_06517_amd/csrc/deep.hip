@@ -646,7 +646,11 @@ __global__ __launch_bounds__(kSelThreads) void deep_select_unit(SelectParams p) 
         }
       }
       if (i + 1 < steps) read(i + 1);
+      // every lane's reads in front of any lane's store, and the store in front of later reads: LDS keeps the order of one
+      // wave's accesses, the fences (no instruction) keep the compiler from changing it
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       *reinterpret_cast<u4 *>(keys + a) = x;
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     }
   }
   for (int b = tid; b < p.lw; b += kSelThreads) kept[k + b] = lc + b;
