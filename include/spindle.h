@@ -304,9 +304,11 @@ spindle_status spindle_decode_merge(const spindle_kv_desc *desc, const void *X_n
  * spindle_decode_merge for callers that cannot allocate device memory or carry a workspace
  * around: code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.
  * Same operation, arguments, results and errors as spindle_decode_merge, without `workspace`:
- * the scratch memory (one partial result per new token and 512 stored entries; its size also
- * counts 1 KiB and a magnitude per token) is an array of spindle_decode_static_capacity() bytes (6 MiB) inside the
+ * the scratch memory is an array of spindle_decode_static_capacity() bytes (6 MiB) inside the
  * library's code object, which every GPU the library runs on holds until the process ends.
+ * (Used of it: one partial result per new token and 512 stored entries, nothing for up to four
+ * tokens per problem.  spindle_decode_workspace_bytes, by which calls are accepted, also counts
+ * 1 KiB and a magnitude per token.)
  * The call allocates and frees nothing on host or device and only enqueues on `stream`, which
  * must belong to the current device.  (With per-kernel timing switched on, spindle_profile
  * creates HIP events; leave it off for such callers.)

@@ -1102,8 +1102,9 @@ spindle_status check_decode(const spindle_kv_desc *desc) {
   return SPINDLE_OK;
 }
 
-// Carves the workspace (or only sizes it when `ws` is null).  The size is that of a workspace which also holds the new
-// tokens as doubles and their magnitudes: what fits the built-in array is part of the interface.
+// Carves the workspace (or only sizes it when `ws` is null).  The kernels use the partial results alone, and none of it for
+// up to four tokens per problem; the size also counts the new tokens as doubles and their magnitudes, 16 KiB per 16
+// tokens and problem, which callers have been told and what fits the built-in array is measured by.
 size_t decode_carve(const spindle_kv_desc *desc, int cap, void *ws, DecodeParams *p) {
   const size_t U = (size_t)desc->batch * desc->n_kv_heads;
   const int tiles = (desc->seq_len + 15) / 16;
@@ -1138,7 +1139,7 @@ extern "C" spindle_status spindle_decode_workspace_bytes(const spindle_kv_desc *
 
 namespace {
 
-// Validation both entry points share; *need = bytes of scratch memory the call uses.
+// Validation both entry points share; *need = spindle_decode_workspace_bytes of the call.
 spindle_status decode_check_args(const spindle_kv_desc *desc, const void *X_new, float theta, int32_t max_codes,
                                  const void *C, const int32_t *n_codes, const int32_t *n_found, const int32_t *ref,
                                  const float *mag, size_t *need) {
@@ -1174,7 +1175,7 @@ spindle_status launch_small<SPINDLE_F32>(const DecodeParams &p, hipStream_t st) 
   return launch_small_f32<4>(p, st);
 }
 
-// Enqueues the kernels of one merge; `scratch_mem` holds decode_carve's arrays and needs no
+// Enqueues the kernels of one merge; `scratch_mem` has decode_carve's size and needs no
 // initial content: every element a kernel reads was written by an earlier kernel of the same call.
 spindle_status decode_enqueue(const spindle_kv_desc *desc, const void *X_new, float theta, int32_t max_codes,
                               void *C, int32_t *n_codes, int32_t *n_found, int32_t *n_matched, int32_t *ref,
@@ -1282,8 +1283,9 @@ extern "C" spindle_status spindle_decode_merge_static(const spindle_kv_desc *des
   if (s != SPINDLE_OK) return s;
   if (need > kStaticScratchBytes)
     SPINDLE_FAIL(SPINDLE_ERR_UNSUPPORTED,
-                 "this call needs %zu bytes of scratch memory, the built-in buffer holds %zu: fewer new tokens or "
-                 "problems per call, a smaller max_codes, or spindle_decode_merge with a workspace",
+                 "the scratch memory of this call counts %zu bytes (spindle_decode_workspace_bytes), the built-in buffer "
+                 "is for calls of up to %zu: fewer new tokens or problems per call, a smaller max_codes, or "
+                 "spindle_decode_merge with a workspace",
                  need, kStaticScratchBytes);
   void *mem = nullptr;
   s = static_scratch(&mem);
