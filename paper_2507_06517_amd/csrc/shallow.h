@@ -153,24 +153,12 @@ __device__ __forceinline__ const char *x_row(const ShallowParams &p, int ut, int
   return p.X[t] + kv_unit_offset(p.lay, u) + (size_t)a * (size_t)p.lay.st;
 }
 
-__device__ inline double dot64_any(int dtype, const char *ra, const char *rb) {
-  if (dtype == SPINDLE_F16) return dot64<SPINDLE_F16>(ra, rb);
-  if (dtype == SPINDLE_BF16) return dot64<SPINDLE_BF16>(ra, rb);
-  return dot64<SPINDLE_F32>(ra, rb);
-}
+constexpr uint32_t kDenseRow = 1u << 31;
 
 // Eq. 4 evaluated the way the adjacency decision is defined: double precision,
 // dimension-order dot product, 0 when either vector is zero.
-__device__ inline double cos64(const ShallowParams &p, int ut, int a, int b) {
-  const double den = p.m64[(size_t)ut * p.n + a] * p.m64[(size_t)ut * p.n + b];
-  if (!(den > 0.0)) return 0.0;
-  return dot64_any(p.dtype, x_row(p, ut, a), x_row(p, ut, b)) / den;
-}
-
-constexpr uint32_t kDenseRow = 1u << 31;
-
 template <int DT, int kBatch>
-__device__ inline double cos64(const ShallowParams &p, int ut, int a, int b) {   // the type known at compile time
+__device__ inline double cos64(const ShallowParams &p, int ut, int a, int b) {
   const double den = p.m64[(size_t)ut * p.n + a] * p.m64[(size_t)ut * p.n + b];
   if (!(den > 0.0)) return 0.0;
   return dot64<DT, kBatch>(x_row(p, ut, a), x_row(p, ut, b)) / den;
