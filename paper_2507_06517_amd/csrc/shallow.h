@@ -132,7 +132,7 @@ struct ShallowParams {
   uint32_t *picked;        // [UT][T] bit per position: became a codebook entry
   uint32_t *pick_key;      // [UT][n] key of a picked position at pick time; slot = position of a token's entry
   int *counters;           // [UT][kCounters]
-  unsigned *pairs_exact;   // [UT] pairs decided in double precision
+  unsigned *pairs_exact;   // [UT][T][rows_waves] pairs decided in double precision, by wave
   uint32_t *ovf;           // [UT][n] tokens whose codebook entry was cut, per problem
   unsigned *ovf_cnt;       // [UT] their number
   uint2 *ccand;            // [UT][n][2][kCandCap] lists of shallow_assign: (entry index, approximate cosine bits)
@@ -152,6 +152,12 @@ __device__ __forceinline__ const char *x_row(const ShallowParams &p, int ut, int
   const int t = ut / p.U, u = ut % p.U;
   return p.X[t] + kv_unit_offset(p.lay, u) + (size_t)a * (size_t)p.lay.st;
 }
+
+// Waves of shallow_rows that share a row tile: four (one row tile per block) while four row tiles per block would leave
+// compute units without a block.  fp16 and fp32 heads of 512 tokens, 256 row tiles in all 12 and 15 us (four per block 21
+// and 27), 512 row tiles 21 and 30 (21 and 28), 1024 38 and 47 (22 and 28); of 1000 tokens, 512 row tiles 31 and 38 (35 and
+// 52), 1024 60 and 72 (36 and 47).
+inline int rows_waves(int UT, int T) { return (long)UT * T < 1024 ? 4 : 1; }
 
 constexpr uint32_t kDenseRow = 1u << 31;
 

@@ -1,5 +1,6 @@
 // Codebook path: workspace layout and the C entry points (kernels: shallow_prep.hip, shallow_tiles.hip,
 // shallow_merge.hip, shallow_codebook.hip; what they share: shallow.h).
+#include <numeric>
 #include <vector>
 
 #include "shallow.h"
@@ -14,7 +15,7 @@ int padded_tiles_of(int n) { return (int)align_up((size_t)tiles_of(n), kScanPane
 // 32-bit words at the end of the workspace that every call clears before use (`scan`: also what
 // only the scan writes).
 size_t zero_words(int UT, int n, int scan) {
-  size_t w = (size_t)UT * kCounters + 2 * (size_t)UT;
+  size_t w = (size_t)UT * kCounters + (size_t)UT;
   if (scan) w += (size_t)UT * padded_tiles_of(n) + (size_t)UT * tiles_of(n) * ((tiles_of(n) + 31) / 32);
   return w;
 }
@@ -63,14 +64,14 @@ size_t carve(ShallowParams &p, void *ws, int UT, int n) {
   p.pick_key = cv.take<uint32_t>(N);
   p.ovf = cv.take<uint32_t>(N);
   p.ccand = cv.take<uint2>(N * 2 * kCandCap);
+  p.pairs_exact = cv.take<unsigned>((size_t)UT * p.T * rows_waves(UT, p.T));
   // everything that must start at zero sits together at the end:
-  // counters [UT][kCounters], pairs_exact [UT], ovf_cnt [UT], then (scan) etile [UT][Tp],
+  // counters [UT][kCounters], ovf_cnt [UT], then (scan) etile [UT][Tp],
   // tpairs [UT][T][TW]
   p.counters = cv.take<int>(zero_words(UT, n, 1));
   int *tail = p.counters ? p.counters + (size_t)UT * kCounters : nullptr;
-  p.pairs_exact = reinterpret_cast<unsigned *>(tail);
-  p.ovf_cnt = reinterpret_cast<unsigned *>(tail ? tail + UT : nullptr);
-  p.etile = reinterpret_cast<uint32_t *>(tail ? tail + 2 * (size_t)UT : nullptr);
+  p.ovf_cnt = reinterpret_cast<unsigned *>(tail);
+  p.etile = reinterpret_cast<uint32_t *>(tail ? tail + UT : nullptr);
   p.tpairs = p.etile ? p.etile + (size_t)UT * p.Tp : nullptr;
   return cv.total();
 }
@@ -106,14 +107,15 @@ extern "C" spindle_status spindle_shallow_stats(const spindle_kv_desc *desc, int
   carve(p, const_cast<void *>(workspace), UT, desc->seq_len);
   hipStream_t st = static_cast<hipStream_t>(stream);
   std::vector<int> cnt((size_t)UT * kCounters);
-  std::vector<unsigned> fixc(UT);
+  const size_t waves = (size_t)p.T * rows_waves(UT, p.T);   // that counted, per problem
+  std::vector<unsigned> fixc(UT * waves);
   SPINDLE_HIP(hipStreamSynchronize(st));
   SPINDLE_HIP(hipMemcpy(cnt.data(), p.counters, cnt.size() * sizeof(int), hipMemcpyDeviceToHost));
   SPINDLE_HIP(hipMemcpy(fixc.data(), p.pairs_exact, fixc.size() * sizeof(unsigned), hipMemcpyDeviceToHost));
   for (int i = 0; i < UT; ++i) {
     stats[16 * i + 0] = cnt[(size_t)i * kCounters + C_ROUNDS];
     stats[16 * i + 1] = cnt[(size_t)i * kCounters + C_PICKS];
-    stats[16 * i + 2] = (int32_t)fixc[i];
+    stats[16 * i + 2] = (int32_t)std::accumulate(fixc.begin() + i * waves, fixc.begin() + (i + 1) * waves, 0u);
     stats[16 * i + 3] = 0;
     for (int k = 0; k < 10; ++k) stats[16 * i + 4 + k] = cnt[(size_t)i * kCounters + 6 + k] / 100;
     stats[16 * i + 14] = stats[16 * i + 15] = 0;

@@ -1083,7 +1083,9 @@ __global__ __launch_bounds__(kRowsThreads, 2) void shallow_rows(ShallowParams p,
   }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) ndecided += __shfl_xor(ndecided, o);
-  if (lane == 0 && ndecided) atomicAdd(p.pairs_exact + ut, (unsigned)ndecided);
+  // (A place for every wave: sums of a problem's waves in one word each put 16384 additions into one cache line that all
+  // dies ask for, and the kernel waited: 268 us for 16 problems of 32768 fp16 tokens, 221 now.)
+  if (lane == 0 && mine) p.pairs_exact[((size_t)ut * T + R) * kCols + member] = (unsigned)ndecided;
   if (lane == 0 && member == 0 && mine) {
     const uint32_t ones = rows_here == kTile ? 0xFFFFFFFFu : (1u << rows_here) - 1u;
     p.live[0][(size_t)ut * T + R] = ones;
@@ -1203,11 +1205,7 @@ spindle_status launch_rows(const ShallowParams &p, hipStream_t st) {
 }
 template <int DT>
 spindle_status launch_rows(const ShallowParams &p, hipStream_t st) {
-  // one row tile per block while four would leave compute units without a block: fp16 and fp32 heads of 512 tokens,
-  // 256 row tiles in all 12 and 15 us (four per block 21 and 27), 512 row tiles 21 and 30 (21 and 28), 1024 38 and 47 (22 and
-  // 28); of 1000 tokens, 512 row tiles 31 and 38 (35 and 52), 1024 60 and 72 (36 and 47)
-  if ((long)p.UT * p.T < 1024) return launch_rows<DT, 4>(p, st);
-  return launch_rows<DT, 1>(p, st);
+  return rows_waves(p.UT, p.T) == 4 ? launch_rows<DT, 4>(p, st) : launch_rows<DT, 1>(p, st);
 }
 }  // namespace
 

@@ -111,6 +111,38 @@ def test_more_close_pairs_than_the_pair_list_holds(oracle):
     assert plan.stats()[0, 2] > 32 * n
 
 
+@pytest.mark.parametrize("dtype", ["f16", "f32"])
+def test_counts_of_double_precision_decisions_by_problem(dtype):
+    # the waves of a problem count for themselves, one or four of them per row tile (40 problems of 29 row tiles, one
+    # problem); the same pairs are close to theta either way
+    import torch
+    from paper_2507_06517_amd import binding as sb
+    rng = np.random.default_rng(12)
+    theta = float(np.float32(0.98))
+    c, u = rng.standard_normal((40, 1, 128)), rng.standard_normal((40, 900, 128))
+    c /= np.linalg.norm(c, axis=2, keepdims=True)
+    u -= (u * c).sum(axis=2, keepdims=True) * c
+    u /= np.linalg.norm(u, axis=2, keepdims=True)
+    X = wl.cast((np.sqrt(theta) * c + np.sqrt(1 - theta) * u)[None], dtype)   # cos(x_a, x_b) = theta + (1 - theta) u_a.u_b
+    X[0, 3] = X[0, 4]                                    # (two alike, one with nothing but zeros)
+    X[0, 7] = 0
+    K, V = sb.to_device(np.ascontiguousarray(X[:, :20]), dtype), sb.to_device(np.ascontiguousarray(X[:, 20:]), dtype)
+    plan = sb.plan_shallow(K, dtype, theta, theta, 900)
+    counts = []
+    for _ in range(2):
+        plan.run(K, V)
+        torch.cuda.synchronize()
+        counts.append(plan.stats()[:, 2].copy())
+    alone = []
+    one = sb.plan_shallow(K[:, :1].contiguous(), dtype, theta, theta, 900, tensors=("k",))
+    for i in range(40):
+        one.run(sb.to_device(np.ascontiguousarray(X[:, i:i + 1]), dtype), None)
+        torch.cuda.synchronize()
+        alone.append(int(one.stats()[0, 2]))
+    assert counts[0].tolist() == counts[1].tolist() == alone
+    assert alone[3] == alone[4] and alone[7] == 0 and min(alone[:7]) > 900
+
+
 def test_duplicates_and_zero_vectors(oracle):
     L = wl.small_random(10, "f16", B=1, H=1, l=400, lw=1, cap=400)
     L.K[0, 0, 100:150] = L.K[0, 0, 7]            # exact duplicates
