@@ -559,25 +559,32 @@ __global__ __launch_bounds__(kScanThreads, 2) void shallow_scan(ShallowParams p)
 }
 
 // What shallow_scan left over, from the rows themselves (fp32 inputs: from their fp16 unit vectors): a tile pair is marked
-// if one of its cosines can be above theta, kRowsGuard (kGuard) allowed for.  With f the factors of rows the test of a
-// product is dot * f_b > (theta - guard) / f_a.  Half of a scan block's panel at a time: two row tiles per wave in
-// registers, the columns gathered into LDS in their order, 64 at a time, two steps ahead of their use; the
-// maxima of a tile are taken while the matrix cores work on the next one.  The blocks stay and deal the work
-// out among them in the scan's order, so that an XCD's blocks share their columns in its L2.
-// 16 problems of 32768 tokens, all pairs: 2.0 ms; 1.8 from fp16 unit vectors of 16-bit inputs, but these cost shallow_prep
-// 20 us per 16 problems of every call, and hardly a call comes here.
+// if one of its cosines can be above theta, refine_guard allowed for.  Half of a scan block's panel at a time: two row
+// tiles per wave in registers as unit vectors (x 2^10, rounded to the type of the rows), the columns as they are, gathered
+// into LDS in their order, 64 at a time, two steps ahead of their use.  A lane has a column and sixteen rows of a tile's
+// products: their maximum, times the factor of the column, is tested once, while the matrix cores work on the next tile.
+// The blocks stay and deal the work out among them in the scan's order, so that an XCD's blocks share their columns in its L2.
+// 16 problems of 32768 fp16 tokens, all pairs: 1.95 ms; with raw rows on both sides, where every product has a factor
+// of its own, 2.1; 1.8 from unit vectors on both sides, but these cost shallow_prep 20 us per 16 problems of every
+// call, and hardly a call comes here.
 constexpr int kRefineThreads = 256;
 constexpr int kRefineBlocks = 512;                     // two per compute unit
 constexpr int kRefineStages = 3;
 constexpr int kRefineList = 2048;                      // items looked at in one go
 
+// Rounding one of the two unit vectors changes a cosine by at most the type's unit roundoff (2^-11, 2^-9); the sums and the
+// factors add less than 2e-5.
+template <int DT>
+__host__ __device__ constexpr float refine_guard() { return DT == SPINDLE_F32 ? kGuard : (DT == SPINDLE_F16 ? 0x1p-11f : 0x1p-9f) + kRowsGuard; }
+
 template <int DT>
 __global__ __launch_bounds__(kRefineThreads, 2) void shallow_refine(ShallowParams p, int nitems) {
   typedef Mma<DT == SPINDLE_BF16 ? SPINDLE_BF16 : SPINDLE_F16> M;
+  typedef typename Elem<DT>::type T;
   constexpr bool kRaw = DT != SPINDLE_F32;
   __shared__ __attribute__((aligned(1024))) char stage[kRefineStages][kStageBytes];
   __shared__ uint16_t cols[kScanRun * kScanStage * kTile];
-  __shared__ __attribute__((aligned(16))) float factor[kRaw ? kScanRun * kScanStage * kTile : 4];
+  __shared__ float factor[kRaw ? kScanRun * kScanStage * kTile : 1];
   __shared__ unsigned long long odd_s[2];              // column tiles with rows whose products say nothing
   __shared__ uint8_t marks[kScanPanel / 2][kScanRun];
   __shared__ uint16_t list[kRefineList];
@@ -625,7 +632,7 @@ __global__ __launch_bounds__(kRefineThreads, 2) void shallow_refine(ShallowParam
       const uint32_t *et = p.etile + (size_t)w.ut * p.Tp;
       const int r0 = w.I * kScanPanel + (at & 1) * (kScanPanel / 2) + 2 * wave;
       const int tile0 = w.s0 * kScanStage, ntiles = (w.s1 - w.s0) * kScanStage, nsteps = ntiles * kTile / kStageCols;
-      const float least = kRaw ? p.theta[w.ut / p.U] - kRowsGuard : (p.theta[w.ut / p.U] - kGuard) * (kUnitScale * kUnitScale);
+      const float least = (p.theta[w.ut / p.U] - refine_guard<DT>()) * (kRaw ? kUnitScale : kUnitScale * kUnitScale);
       __syncthreads();                                 // the item before is done with these
       if (threadIdx.x < 2) odd_s[threadIdx.x] = 0;
       __syncthreads();
@@ -643,16 +650,25 @@ __global__ __launch_bounds__(kRefineThreads, 2) void shallow_refine(ShallowParam
       if (threadIdx.x < sizeof(marks)) reinterpret_cast<uint8_t *>(marks)[threadIdx.x] = 0;
       typename M::frag af[2][M::kSteps];
       bool odd[2];                                     // row tiles with rows whose products say nothing,
-      int thr[2];
 #pragma unroll
       for (int cb = 0; cb < 2; ++cb) {
         const int pos = min((r0 + cb) * kTile + c, n - 1);
         const char *row = X + (size_t)perm[pos] * pitch;
 #pragma unroll
         for (int ks = 0; ks < M::kSteps; ++ks) af[cb][ks] = M::load(row, ks, g);
-        const float f = kRaw ? inv[pos] : 1.f;
-        odd[cb] = et[r0 + cb] >= kSketchUnknown || __any(f != f);
-        thr[cb] = __float_as_int(f > 0.f ? least / f : INFINITY);
+        odd[cb] = et[r0 + cb] >= kSketchUnknown;
+        if constexpr (kRaw) {
+          const float f = inv[pos], scale = f * kUnitScale;
+          odd[cb] |= __any(f != f) != 0;
+#pragma unroll
+          for (int ks = 0; ks < M::kSteps; ++ks) {
+            u4 x = __builtin_bit_cast(u4, af[cb][ks]);
+            T *e = reinterpret_cast<T *>(&x);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) e[j] = Elem<DT>::from_float(Elem<DT>::to_float(e[j]) * scale);
+            af[cb][ks] = __builtin_bit_cast(typename M::frag, x);
+          }
+        }
       }
       unsigned long long odd_cols[2];                  // ... and columns, a bit per tile
 #pragma unroll
@@ -671,27 +687,20 @@ __global__ __launch_bounds__(kRefineThreads, 2) void shallow_refine(ShallowParam
           else lds_dma16(X + tok * pitch + piece, to);
         }
       };
-      // results of column tile t; thr is positive: floats order as integers as far as it matters
+      // results of column tile t; `least` is positive: floats order as integers as far as it matters
       auto look = [&](int t, const f16v &x0, const f16v &x1) __attribute__((always_inline)) {
-        int m0 = INT32_MIN, m1 = INT32_MIN;
+        const float f = kRaw ? factor[t * kTile + c] : 1.f;
+        int m0 = __float_as_int(x0[0]), m1 = __float_as_int(x1[0]);
 #pragma unroll
-        for (int v0 = 0; v0 < 16; v0 += 4) {
-          float4 f = make_float4(1.f, 1.f, 1.f, 1.f);
-          if (kRaw) f = *reinterpret_cast<const float4 *>(&factor[t * kTile + mma_row(v0, g)]);
-          const float fv[4] = {f.x, f.y, f.z, f.w};
-#pragma unroll
-          for (int k = 0; k < 4; ++k) {
-            m0 = max(m0, __float_as_int(kRaw ? x0[v0 + k] * fv[k] : x0[v0 + k]));
-            m1 = max(m1, __float_as_int(kRaw ? x1[v0 + k] * fv[k] : x1[v0 + k]));
-          }
-        }
+        for (int v = 1; v < 16; ++v) { m0 = max(m0, __float_as_int(x0[v])); m1 = max(m1, __float_as_int(x1[v])); }
         const bool oddc = odd_cols[t >> 6] >> (t & 63) & 1;
-        const bool hit0 = oddc | odd[0] | (__any(m0 > thr[0]) != 0), hit1 = oddc | odd[1] | (__any(m1 > thr[1]) != 0);
+        const bool hit0 = oddc | odd[0] | (__any(__int_as_float(m0) * f > least) != 0);
+        const bool hit1 = oddc | odd[1] | (__any(__int_as_float(m1) * f > least) != 0);
         if ((hit0 | hit1) && lane < 2 && (lane ? hit1 : hit0)) marks[2 * wave + lane][t >> 3] |= (uint8_t)(1u << (t & 7));
       };
       f16v y0, y1;
 #pragma unroll
-      for (int v = 0; v < 16; ++v) { y0[v] = 0.f; y1[v] = 0.f; }   // (below thr)
+      for (int v = 0; v < 16; ++v) { y0[v] = 0.f; y1[v] = 0.f; }   // (below `least`)
       dma(0);
       dma(1);                                          // (a stage of the scan is four steps)
       for (int s = 0; s < nsteps; ++s) {
@@ -713,8 +722,8 @@ __global__ __launch_bounds__(kRefineThreads, 2) void shallow_refine(ShallowParam
           __builtin_amdgcn_sched_barrier(0);           // all reads on their way before the first instruction waits
 #pragma unroll
           for (int ks = 0; ks < M::kSteps; ++ks) {
-            x0 = M::mma(f[ks], af[0][ks], x0);
-            x1 = M::mma(f[ks], af[1][ks], x1);
+            x0 = M::mma(af[0][ks], f[ks], x0);
+            x1 = M::mma(af[1][ks], f[ks], x1);
           }
           if (ct > 0 || s > 0) look(2 * s + ct - 1, y0, y1);
           y0 = x0;

@@ -186,6 +186,38 @@ def test_tile_pairs_by_sketch_by_vector_and_all(oracle, dtype, H, l, common, the
     parity.check_shallow_layer(oracle, L, units=[(0, H // 2)], debug=False, cap=l // 50)
 
 
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
+def test_neighbours_that_rounding_takes_below_the_threshold(oracle, dtype):
+    # pairs a little above theta, one of them a row whose unit vector (x 2^10) the type rounds towards zero in every
+    # coordinate by nearly half a unit: what refines tile pairs must allow for the cosine it loses by that
+    rng = np.random.default_rng(9)
+    l, theta, npairs = 2400, 0.5, 120
+    bits = 8 if dtype == "bf16" else 11
+    coord = 1024 / np.sqrt(np.arange(1, 129))
+    ulp = 2.0 ** (np.floor(np.log2(coord)) - (bits - 1))
+    lost = (coord - np.round(coord / ulp) * ulp) / coord
+    m = int(np.argmax(lost)) + 1                             # coordinates of such a row
+    assert lost[m - 1] > 0.6 * 2.0 ** -bits
+    x = rng.standard_normal((l, 128))
+    places = rng.permutation(l)[:2 * npairs].reshape(npairs, 2)
+    for a, b in places:
+        u = np.where(rng.permutation(128) < m, rng.choice([-1.0, 1.0], 128), 0.0)
+        while True:
+            w = rng.standard_normal((500, 128))
+            w -= np.outer(w @ u, u) / m
+            w /= np.linalg.norm(w, axis=1, keepdims=True)
+            y = (theta + 5e-5) * u / np.sqrt(m) + np.sqrt(1 - theta ** 2) * w
+            y = wl.to_f64(wl.cast(y * rng.uniform(0.5, 2.0, (500, 1)), dtype), dtype)
+            cs = y @ u / np.sqrt(m) / np.linalg.norm(y, axis=1)
+            good = np.flatnonzero((cs > theta + 1e-6) & (cs < theta + 1e-4))
+            if len(good):
+                break
+        x[a], x[b] = 3.0 * u, y[good[0]]
+    X = wl.cast(x[None, None], dtype)
+    L = wl.Layer(dtype, X, X.copy(), np.zeros_like(X[:, :, :1]), 1, 1, 1, l, l, theta_k=theta, theta_v=theta)
+    parity.check_shallow_layer(oracle, L, tensors=("k",))
+
+
 @pytest.mark.parametrize("H,l,theta_k,theta_v,kernel", [(1, 700, 0.98, 0.95, "shallow_rows"), (1, 2100, 0.2, 0.98, "shallow_scan"),
                                                         (1, 2100, 0.6, 0.2, "shallow_refine"), (1, 2100, 0.2, 0.1, "shallow_rows"),
                                                         (64, 1500, 0.98, 0.95, "shallow_scan")])
