@@ -84,7 +84,7 @@ constexpr float kSketchMinTheta = 0.7f, kVectorMinTheta = 0.3f;
 enum { kByNone, kByVector, kBySketch };
 // Column tiles a scan block may mark before the full vectors decide instead, counted once for the four row tiles
 // that shallow_rows takes together: all pairs in shallow_refine cost a fifth of what shallow_rows takes
-// for all of them (16 problems of 32768 tokens: 2.0 and 9.9 ms).
+// for all of them (16 problems of 32768 tokens: 1.95 and 8 to 10 ms).
 constexpr float kRefineShare = 0.22f;
 
 constexpr int kCounters = 32;     // ints per ut

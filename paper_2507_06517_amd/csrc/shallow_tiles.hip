@@ -750,7 +750,7 @@ __global__ __launch_bounds__(kRefineThreads, 2) void shallow_refine(ShallowParam
 // use, and every wave multiplies one of them with one row tile (held in registers).  kCols = 1: what
 // similar rows have in common is read once for four row tiles; kCols = 4: short problems, where there
 // are too few row tiles to fill the chip.  Bound by the gathered rows (random 256-byte rows, mostly from
-// L2): 0.23 to 0.27 ms for 16 problems of 32768 tokens, 0.19 ms for 128 of 8192 in clusters of 128, three blocks per compute unit
+// L2): 0.21 ms for 16 problems of 32768 tokens, 0.19 ms for 128 of 8192 in clusters of 128, three blocks per compute unit
 // (0.31 and 0.25 with two); one wave per row tile with its own gathers took 0.73 and 0.84 ms.
 constexpr int kRowsQueue = 192;                    // waiting pairs per wave
 constexpr int kRowsThreads = 256;
