@@ -6,8 +6,8 @@
 //                   products bound the cosines from above
 //   shallow_pivots, shallow_order, shallow_window
 //                   the tokens of a problem sorted so that similar ones stand together
-//   shallow_scan    sketch products of all pairs of 32-token tiles, in six-bit floats:
-//                   which tiles can hold a pair above theta at all
+//   shallow_scan    which pairs of 32-token tiles can hold a pair above theta at all: balls around the
+//                   tiles' sketches first, then sketch products, in six-bit floats
 //   shallow_refine  where the sketches exclude little, the same from the rows
 //   shallow_rows    for those tiles the cosines themselves (Eq. 4, 9), decided exactly; degrees
 //                   (Eq. 10) and neighbour lists
@@ -66,8 +66,13 @@ constexpr int kScanPanel = 16;                   // row tiles of a block of shal
 constexpr int kScanStage = 8;                    // column tiles it stages at a time
 constexpr int kScanRun = 16;                     // stages of a block at most
 constexpr uint32_t kSketchUnknown = 1u << 20;    // error of a token whose sketch says nothing
-constexpr int kPivots = 1024;                    // at most, and one per 16 tokens
+// Tokens are sorted by bucket, two per pivot (at most kPivots, one per 16 tokens): what is near it, and what isn't but has
+// it nearest.
+constexpr int kPivots = 1024, kBuckets = 2 * kPivots;
 constexpr int kOrderTokens = 512;                // tokens per block of shallow_pivots and shallow_order
+constexpr int kWindow = 1024;                    // places of a block of shallow_window
+constexpr int kBallTiles = 64;                   // tiles whose balls stand together: one each, and 32 seconds
+constexpr int kBalls = 3 * kTile;
 // Problems of 2048 tokens and more are sorted and scanned, shorter ones only where there are many: what the launches
 // take, about 45 us, has to come back from shallow_rows, which then needn't take every tile.  Clusters and
 // isolated tokens, without and with: 16 problems of 1280 124, 142 and 107, 151 us, of 1536 135, 152 and 111, 152; 64 of
@@ -75,6 +80,14 @@ constexpr int kOrderTokens = 512;                // tokens per block of shallow_
 inline int scan_pays(int UT, int n) {
   const long T = (n + 31) / 32;
   return n >= 2048 || (n >= 1024 && UT * T * (T - 24) >= 18000);
+}
+// Tile pairs of all problems from which the scan pays for asking the balls around the tiles first, which takes shallow_window
+// and short blocks of shallow_scan some 10 us.  Calls on clusters, fp16, without and with, us: 16 problems of 4096 tokens (0.26
+// million) 118, 132, of 8192 (1.05) 162, 163 (with a third isolated 220, 226), of 12000 (2.25) 208, 194; 2 of 16384 (0.52) 144,
+// 152, of 32768 (2.1) 188, 171; 128 of 2048 (0.52) 197, 211, of 4096 (2.1) 330, 318.
+inline int balls_pay(int UT, int n) {
+  const long T = (n + 31) / 32;
+  return UT * T * T >= 1600000;
 }
 // Below kSketchMinTheta the sketches are not asked: a sketch product of unrelated tokens is about 0.53 with a
 // spread of 0.06, so the largest of a pair of tiles is above 0.7 nearly always.  Below kVectorMinTheta the full
@@ -107,11 +120,19 @@ struct ShallowParams {
   float *invp;             // [UT][n] factor of a row in the cosine (see shallow_rows), by position
   uint8_t *sk0;            // [UT][n][64] sketches by token
   float2 *inv_err;         // [UT][n] by token (scan): the factor, and the distance of the sketch from what it stands for (< 0: says nothing)
-  uint16_t *bucket;        // [UT][n] pivot of a token
+  uint16_t *bucket;        // [UT][n] bucket of a token
   uint32_t *mean;          // [UT][2] first eight coordinates of the pivots' mean
-  uint16_t *hist;          // [UT][order blocks][kPivots] tokens per bucket in each block of tokens
+uint32_t *total;         // [UT][kBuckets] tokens per bucket
+  uint16_t *before;        // [UT][order blocks][kBuckets] place within a bucket of a block's first token of it
   uint8_t *sk;             // [UT][Tp][kSixBytes] sketches by position, in six-bit floats
   uint32_t *etile;         // [UT][Tp] what a tile's sketches may be off by in a product, sketch units squared
+  int balls;               // 1: the scan asks the balls around tiles first
+  float *tnorm;            // [UT][Tp] longest six-bit sketch of a tile, in six-bit units (as the radii)
+  // Balls around the six-bit sketches of a tile, or of its two parts: centres as 3 tiles of 32 per kBallTiles, and per centre
+  // what the products of its tile may be off by, in six-bit units squared (no tile: a large negative number), and its radius.
+  uint8_t *skc;            // [UT][Tp / 64][3][kSixBytes]
+  float2 *ball;            // [UT][Tp / 64][kBalls]
+  uint8_t *second;         // [UT][Tp / 64][kTile] tile of the 64 that a second ball belongs to
   uint32_t *tpairs;        // [UT][T][TW] bit t of row r: tiles r and t may hold a pair above theta
   int T, Tp, TW;           // tiles, rounded up to whole panels; words per row of tpairs
   int scan;                // 1: tokens are sorted and tpairs says which tiles count; 0: all tiles, positions = tokens

@@ -16,7 +16,7 @@ int padded_tiles_of(int n) { return (int)align_up((size_t)tiles_of(n), kScanPane
 // only the scan writes).
 size_t zero_words(int UT, int n, int scan) {
   size_t w = (size_t)UT * kCounters + (size_t)UT;
-  if (scan) w += (size_t)UT * padded_tiles_of(n) + (size_t)UT * tiles_of(n) * ((tiles_of(n) + 31) / 32);
+  if (scan) w += (size_t)UT * (kBuckets + padded_tiles_of(n)) + (size_t)UT * tiles_of(n) * ((tiles_of(n) + 31) / 32);
   return w;
 }
 
@@ -27,10 +27,11 @@ size_t carve(ShallowParams &p, void *ws, int UT, int n) {
   p.Tp = padded_tiles_of(n);
   p.TW = (p.T + 31) / 32;
   p.UT = UT;
-  // stages per block of the scan: about 2048 blocks, so that short problems fill the chip too (the longest last
+  // stages per block of the scan: about 1024 blocks, so that short problems fill the chip too (the longest last
   // about 15 us)
   const int nI = p.Tp / kScanPanel, nS = p.Tp / kScanStage;
-  const long work = (long)UT * nI * (nI + 1) / 2048;
+  p.balls = balls_pay(UT, n);
+  const long work = (long)UT * nI * (nI + 1) / (p.balls ? 1024 : 2048);
   p.stages_per_item = work < 1 ? 1 : (work > kScanRun ? kScanRun : (int)work);
   p.njg = (nS + p.stages_per_item - 1) / p.stages_per_item;
   p.Xe = cv.take<_Float16>((N + 512) * kHeadDim);   // the similarity loop stages up to 5 tiles past the last token
@@ -47,8 +48,13 @@ size_t carve(ShallowParams &p, void *ws, int UT, int n) {
   p.inv_err = cv.take<float2>(N);
   p.bucket = cv.take<uint16_t>(N);
   p.mean = cv.take<uint32_t>((size_t)UT * 2);
-  p.hist = cv.take<uint16_t>((size_t)UT * ((n + kOrderTokens - 1) / kOrderTokens) * kPivots);
+  p.before = cv.take<uint16_t>((size_t)UT * ((n + kOrderTokens - 1) / kOrderTokens) * kBuckets);
   p.sk = cv.take<uint8_t>((size_t)UT * p.Tp * kSixBytes);
+  const size_t groups = (size_t)UT * ((p.Tp + kBallTiles - 1) / kBallTiles);
+  p.tnorm = cv.take<float>((size_t)UT * p.Tp);
+  p.skc = cv.take<uint8_t>(groups * 3 * kSixBytes);
+  p.ball = cv.take<float2>(groups * kBalls);
+  p.second = cv.take<uint8_t>(groups * kTile);
   p.todo = cv.take<uint32_t>(scan_blocks(p));
   p.alive = cv.take<int>(N);
   p.n16 = (n + 15) & ~15;
@@ -66,12 +72,13 @@ size_t carve(ShallowParams &p, void *ws, int UT, int n) {
   p.ccand = cv.take<uint2>(N * 2 * kCandCap);
   p.pairs_exact = cv.take<unsigned>((size_t)UT * p.T * rows_waves(UT, p.T));
   // everything that must start at zero sits together at the end:
-  // counters [UT][kCounters], ovf_cnt [UT], then (scan) etile [UT][Tp],
-  // tpairs [UT][T][TW]
+  // counters [UT][kCounters], ovf_cnt [UT], then (scan) total [UT][kBuckets],
+  // etile [UT][Tp], tpairs [UT][T][TW]
   p.counters = cv.take<int>(zero_words(UT, n, 1));
   int *tail = p.counters ? p.counters + (size_t)UT * kCounters : nullptr;
   p.ovf_cnt = reinterpret_cast<unsigned *>(tail);
-  p.etile = reinterpret_cast<uint32_t *>(tail ? tail + UT : nullptr);
+  p.total = reinterpret_cast<uint32_t *>(tail ? tail + UT : nullptr);
+  p.etile = p.total ? p.total + (size_t)UT * kBuckets : nullptr;
   p.tpairs = p.etile ? p.etile + (size_t)UT * p.Tp : nullptr;
   return cv.total();
 }

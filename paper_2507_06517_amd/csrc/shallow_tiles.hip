@@ -26,12 +26,15 @@ typedef int i16v __attribute__((ext_vector_type(16)));
 // the mean instead.
 constexpr int kStepOffset = 3000;
 constexpr float kStepEnd = 0.345f, kStep = 0.388f, kMeanSome = 0.15f, kMeanMost = 1.9f;
-constexpr int kMeanOf = 128;
+// Tokens that are near no pivot (a cosine of 0.73, the last step from 0.88 on) go ahead of the others, and so do the
+// few of a pivot that is alone (kAlone tokens): what is isolated stands together then and doesn't widen the tiles of what is
+// not.  Where sketches aren't asked (kByVector) all tokens keep to their pivots.
+constexpr int kMeanOf = 128, kNearStep = 5, kAlone = 8;
 constexpr int kPivotThreads = 256;
 
 __global__ __launch_bounds__(kPivotThreads, 2) void shallow_pivots(ShallowParams p, int npiv, int nblk) {
   __shared__ __attribute__((aligned(16))) char piv[kPivots * kSketchBytes];    // fragment order: tile, half, lane
-  __shared__ uint32_t cnt[kPivots];
+  __shared__ uint32_t cnt[kBuckets];
   __shared__ __attribute__((aligned(16))) int init[kPivots];                   // what is taken off a pivot's products
   __shared__ __attribute__((aligned(16))) int sum[kSketchBytes], mean4[kSketchBytes / 4];
   __shared__ int sum_sq;
@@ -46,7 +49,7 @@ __global__ __launch_bounds__(kPivotThreads, 2) void shallow_pivots(ShallowParams
     const int tok = (int)((long)j * n / npiv);
     *reinterpret_cast<u4 *>(piv + piv_at(j, piece)) = *reinterpret_cast<const u4 *>(sk + (size_t)tok * kSketchBytes + piece * 16);
   }
-  for (int i = tid; i < kPivots; i += kPivotThreads) cnt[i] = 0;
+  for (int i = tid; i < kBuckets; i += kPivotThreads) cnt[i] = 0;
   if (tid < kSketchBytes) sum[tid] = 0;
   if (tid == 0) sum_sq = 0;
   // the wave's 128 tokens: matrix columns = lanes
@@ -176,55 +179,79 @@ __global__ __launch_bounds__(kPivotThreads, 2) void shallow_pivots(ShallowParams
     for (int v = 0; v < 16; ++v) x16[v] = off;
     compare([&](int) { return x16; });
   }
+  const int near = p.by[ut / p.U] != kBySketch ? INT32_MIN : some ? 1 << bits : kNearStep << 14;
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
-    const int own = (best[r] & mask) | (kPivots - 1 - (best_pt[r] * 32 + mma_row(15 - (best[r] & 15), g)));
-    const int o = __shfl_xor(own, 32);
-    const int b = kPivots - 1 - ((o > own ? o : own) & (kPivots - 1));
+    const int own = (best[r] & mask) | (1023 - (best_pt[r] * 32 + mma_row(15 - (best[r] & 15), g)));
+    const int o = __shfl_xor(own, 32), top = o > own ? o : own, pivot = 1023 - (top & 1023);
+    const int b = top >= near ? kPivots + pivot : pivot;
     if (g == 0 && tok[r] < n) {
       p.bucket[(size_t)ut * n + tok[r]] = (uint16_t)b;
       atomicAdd(&cnt[b], 1u);
     }
   }
   __syncthreads();
-  uint16_t *h = p.hist + ((size_t)ut * nblk + blk) * kPivots;
-  for (int i = tid; i < kPivots; i += kPivotThreads) h[i] = (uint16_t)cnt[i];
+  // (all additions on their way before the first result is waited for)
+  constexpr int kOwn = kBuckets / kPivotThreads;
+  uint32_t *total = p.total + (size_t)ut * kBuckets;
+  uint16_t *before = p.before + ((size_t)ut * nblk + blk) * kBuckets;
+  uint32_t x[kOwn], was[kOwn];
+#pragma unroll
+  for (int k = 0; k < kOwn; ++k) x[k] = cnt[k * kPivotThreads + tid];
+#pragma unroll
+  for (int k = 0; k < kOwn; ++k) {
+    was[k] = 0;
+    if (x[k]) was[k] = atomicAdd(total + k * kPivotThreads + tid, x[k]);
+  }
+#pragma unroll
+  for (int k = 0; k < kOwn; ++k)
+    if (x[k]) before[k * kPivotThreads + tid] = (uint16_t)was[k];
 }
 
-// Tokens in the order of their pivots: a counting sort whose counts shallow_pivots left per block of
-// tokens (every block adds up the ones it needs, so no launch in between).
-__global__ __launch_bounds__(kPivots) void shallow_order(ShallowParams p, int nblk) {
-  __shared__ int cursor[kPivots];
-  __shared__ int wsum[kPivots / kWave];
+// Tokens in the order of their buckets: a counting sort.  shallow_pivots left how many tokens a bucket has and which
+// place within it a block's tokens start at (with counts per block that every block added up, twice the buckets would have
+// cost twice the 26 us that half of them took on 16 problems of 32768 tokens; now 9).
+constexpr int kOrderThreads = 1024;
+
+__global__ __launch_bounds__(kOrderThreads) void shallow_order(ShallowParams p, int nblk) {
+  __shared__ int cursor[kBuckets];
+  __shared__ uint32_t wsum[kOrderThreads / kWave];
+  static_assert(kBuckets == 2 * kOrderThreads, "two buckets per thread");
   const int item = xcd_item();
   if (item >= p.UT * nblk) return;
   const int ut = item / nblk, blk = item % nblk, n = p.n;
   const size_t base = (size_t)ut * n;
   const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
-  const uint16_t *h = p.hist + (size_t)ut * nblk * kPivots + tid;
-  int total = 0, before = 0;
-#pragma unroll 8
-  for (int k = 0; k < nblk; ++k) {
-    const int x = h[(size_t)k * kPivots];
-    total += x;
-    before += k < blk ? x : 0;
-  }
-  int incl = total;
+  const int tok = blk * kOrderTokens + tid;
+  const bool on = tid < kOrderTokens && tok < n;
+  const int b = on ? (int)p.bucket[base + tok] : 0;
+  const uint2 total = reinterpret_cast<const uint2 *>(p.total + (size_t)ut * kBuckets)[tid];
+  const ushort2 before = reinterpret_cast<const ushort2 *>(p.before + ((size_t)ut * nblk + blk) * kBuckets)[tid];
+  // both kinds of buckets at once: those that go first in the low half (at most 65535 tokens in all)
+  auto half = [](int bucket, uint32_t x) { return bucket < kPivots || x <= (uint32_t)kAlone ? 0 : 16; };
+  const int h0 = half(2 * tid, total.x), h1 = half(2 * tid + 1, total.y);
+  const uint32_t own = (total.x << h0) + (total.y << h1);
+  uint32_t incl = own, all = 0;
 #pragma unroll
   for (int o = 1; o < kWave; o <<= 1) {
-    const int x = __shfl_up(incl, o);
+    const uint32_t x = __shfl_up(incl, o);
     if (lane >= o) incl += x;
   }
   if (lane == kWave - 1) wsum[wave] = incl;
   __syncthreads();
-  for (int w = 0; w < wave; ++w) incl += wsum[w];
-  cursor[tid] = incl - total + before;
+  for (int w = 0; w < kOrderThreads / kWave; ++w) {
+    const uint32_t x = wsum[w];
+    incl += w < wave ? x : 0u;
+    all += x;
+  }
+  const uint32_t at0 = incl - own, at1 = at0 + (total.x << h0), nfirst = all & 0xFFFFu;
+  cursor[2 * tid] = (int)((h0 ? nfirst : 0u) + (at0 >> h0 & 0xFFFFu)) + before.x;
+  cursor[2 * tid + 1] = (int)((h1 ? nfirst : 0u) + (at1 >> h1 & 0xFFFFu)) + before.y;
   __syncthreads();
-  const int tok = blk * kOrderTokens + tid;
-  if (tid < kOrderTokens && tok < n) p.perm[base + atomicAdd(&cursor[p.bucket[base + tok]], 1)] = (uint16_t)tok;
+  if (on) p.perm[base + atomicAdd(&cursor[b], 1)] = (uint16_t)tok;
 }
 
-// A window of 2048 places in that order: the tokens of each pivot sorted by eight signs of their
+// A window of 1024 places in that order: the tokens of each pivot sorted by eight signs of their
 // sketches less the mean, which keeps together what has no
 // pivot of its own.  Then everything later kernels read by position.  Sketches go to fragment order:
 // tile, half of the 64 bytes, lane.
@@ -250,24 +277,39 @@ __device__ __forceinline__ f32v from_six(const u6 &x) {
   return r;
 }
 
-constexpr int kWindow = 2048;
-constexpr int kWindowThreads = 1024;
+// Over the two lane groups of 32; over the lanes of a group.
+__device__ __forceinline__ float groups_sum(float x) {
+  const auto y = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(y[0]) + __uint_as_float(y[1]);
+}
+__device__ __forceinline__ uint32_t max32(uint32_t x) {
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0xB1, 0xF, 0xF, true));    // quad_perm [1,0,3,2]
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x4E, 0xF, 0xF, true));    // quad_perm [2,3,0,1]
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x141, 0xF, 0xF, true));   // row_half_mirror
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x140, 0xF, 0xF, true));   // row_mirror
+  const auto y = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+  return max(y[0], y[1]);
+}
+
+constexpr int kWindowThreads = 512;
 constexpr int kFew = 64, kMany = kWindow / kFew;
 
 __global__ __launch_bounds__(kWindowThreads) void shallow_window(ShallowParams p, int nwin) {
   __shared__ uint16_t order_by[kWindow];               // pivots, then the tokens' signs by place
   __shared__ uint16_t at_place[kWindow];
-  __shared__ int first[kPivots], last[kPivots];        // places of a pivot's tokens
+  __shared__ int first[kBuckets], last[kBuckets];      // places of a bucket's tokens
   __shared__ __attribute__((aligned(16))) int count[kMany][256];
-  __shared__ uint8_t slot[kPivots];
+  __shared__ uint8_t slot[kBuckets];
   __shared__ int nslots;
+  __shared__ uint32_t starts[kWindow / kTile];         // per tile the places where a bucket starts
+  __shared__ __attribute__((aligned(16))) float centre[kWindowThreads / kWave][kSketchBytes];
   const int item = xcd_item();
   if (item >= p.UT * nwin) return;
   const int ut = item / nwin, n = p.n, w0 = (item % nwin) * kWindow, w1 = min(n, w0 + kWindow);
   const size_t base = (size_t)ut * n;
   const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
   const uint2 mean = reinterpret_cast<const uint2 *>(p.mean)[ut];
-  static_assert(kWindow == 2 * kWindowThreads && kPivots == kWindowThreads, "two places per thread");
+  static_assert(kWindow == 2 * kWindowThreads, "two places per thread");
   int tok[2], b[2], signs[2];
 #pragma unroll
   for (int k = 0; k < 2; ++k) {
@@ -307,6 +349,11 @@ __global__ __launch_bounds__(kWindowThreads) void shallow_window(ShallowParams p
     order_by[i] = (uint16_t)signs[k];
     if (i == lo[k] && hi[k] - lo[k] >= kFew) slot[b[k]] = (uint8_t)atomicAdd(&nslots, 1);
   }
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const unsigned long long at = __ballot(tok[k] >= 0 && lo[k] == tid + k * kWindowThreads);
+    if (lane < 2) starts[(k * kWindowThreads + wave * kWave) / kTile + lane] = (uint32_t)(at >> (32 * lane));
+  }
   __syncthreads();
   int before[2];
 #pragma unroll
@@ -341,10 +388,25 @@ __global__ __launch_bounds__(kWindowThreads) void shallow_window(ShallowParams p
   }
   __syncthreads();
   // A wave takes 32 places at a time: their sketches are read four lanes to a row, turned to fragment order in LDS
-  // (which the counts no longer need) and rounded to six-bit floats.
+  // (which the counts no longer need) and rounded to six-bit floats.  Then the ball around them: the rounded mean, and how far
+  // the farthest is from it.  Where a bucket starts inside the tile, the one that starts next to its middle parts it
+  // in two, each with a ball of its own, as far as a window has room for seconds (a tile of many buckets is of isolated
+  // tokens, and stays whole).
   uint8_t *sk = p.sk + (size_t)ut * p.Tp * kSixBytes;
   char *turn = reinterpret_cast<char *>(&count[0][0]) + wave * kTileBytes;
   static_assert(sizeof(count) >= kWindowThreads / kWave * kTileBytes, "a tile per wave");
+  // (a window has half of the tiles whose balls stand together, and half of the seconds)
+  static_assert(kBallTiles * kTile == 2 * kWindow && kWindow / kTile == kTile, "two windows, a lane per tile of one");
+  const int half_at = (item % nwin & 1) * kTile;       // its first tile among them
+  const size_t group = (size_t)ut * (nwin / 2) + item % nwin / 2;
+  uint8_t *centres = p.skc + group * (3 * kSixBytes);
+  float2 *balls = p.ball + group * kBalls;
+  const uint32_t inside = starts[lane & 31] >> 1;
+  const uint32_t parted = (uint32_t)__ballot(inside != 0 && __popc(inside) <= 2);
+  constexpr int kSeconds = kTile / 2;
+  const int second0 = half_at / 2;
+  if (p.balls && wave == 0 && lane >= __popc(parted) && lane < kSeconds) balls[2 * kTile + second0 + lane] = make_float2(-0x1p30f, 0.f);
+  constexpr float kUnit = 1.f / (kSixScale * kSixScale);   // products of six-bit floats are in units of kSixScale squared
   const int end = w1 < n ? w1 : p.Tp * kTile;         // the last window also fills the places past the last token
   for (int p0 = w0 + wave * kTile; p0 < end; p0 += kWindowThreads / kWave * kTile) {
     u4 v[2];
@@ -374,34 +436,114 @@ __global__ __launch_bounds__(kWindowThreads) void shallow_window(ShallowParams p
       *reinterpret_cast<u4 *>(turn + r * kSketchBytes + (((lane & 3) ^ ((r >> 2) & 3)) << 4)) = v[j];
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // LDS keeps the order of one wave's accesses
-    f16v x[2];                                         // a row's pieces g and g + 2
+    u6 six;
+    float d2 = 0.f, norm2 = 0.f;                       // squared distance of the six-bit floats from the bytes, their length
+    {
+      f16v x[2];                                       // a row's pieces g and g + 2
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {
-      const int r = lane & 31, piece = 2 * k + (lane >> 5);
-      const u4 y = *reinterpret_cast<const u4 *>(turn + r * kSketchBytes + ((piece ^ ((r >> 2) & 3)) << 4));
+      for (int k = 0; k < 2; ++k) {
+        const int r = lane & 31, piece = 2 * k + (lane >> 5);
+        const u4 y = *reinterpret_cast<const u4 *>(turn + r * kSketchBytes + ((piece ^ ((r >> 2) & 3)) << 4));
 #pragma unroll
-      for (int i = 0; i < 16; ++i) x[k][i] = (float)(int)__builtin_amdgcn_sbfe((int)y[i >> 2], 8 * (i & 3), 8);
+        for (int i = 0; i < 16; ++i) x[k][i] = (float)(int)__builtin_amdgcn_sbfe((int)y[i >> 2], 8 * (i & 3), 8);
+      }
+      six = to_six(x[0], x[1]);
+      const f32v back = from_six(six);
+#pragma unroll
+      for (int i = 0; i < 32; ++i) {
+        const float e = back[i] - x[i & 1][i >> 1];
+        d2 = fmaf(e, e, d2);
+        norm2 = fmaf(back[i], back[i], norm2);
+      }
+      uint8_t *d = sk + (size_t)(p0 >> 5) * kSixBytes;
+      reinterpret_cast<u4 *>(d)[lane] = u4{six[0], six[1], six[2], six[3]};
+      reinterpret_cast<uint2 *>(d + 1024)[lane] = make_uint2(six[4], six[5]);
     }
-    const u6 six = to_six(x[0], x[1]);
-    const f32v back = from_six(six);
-    float d2 = 0.f;                                    // squared distance of the six-bit floats from the bytes
-#pragma unroll
-    for (int i = 0; i < 32; ++i) {
-      const float d = back[i] - x[i & 1][i >> 1];
-      d2 = fmaf(d, d, d2);
-    }
-    d2 += __shfl_xor(d2, 32);
+    d2 = groups_sum(d2);
+    norm2 = groups_sum(norm2) * kUnit;                 // (exact, as all sums of products of six-bit floats)
     // |a.b - a'.b'| <= e_a + e_b + e_a e_b for sketches a', b' at distances e_a, e_b; the last term is at
     // most half of the two squares.  In sketch units squared, rounded up.
     const float dist = off + sqrtf(d2) * (1.0001f / kSketchScale);
     uint32_t e = off >= 0.f && dist < 4.f ? (uint32_t)((dist + 0.5f * dist * dist) * (kSketchScale * kSketchScale * (1.f + 1e-5f))) + 2u : kSketchUnknown;
     if (pos >= n) e = 0;
+    e = max32(e);
+    if (!p.balls) {                                    // uniform
+      if (lane == 0) p.etile[(size_t)ut * p.Tp + (p0 >> 5)] = e;
+      continue;
+    }
+    const int tw = (p0 - w0) >> 5;                     // tile of the window
+    const uint32_t inner = __builtin_amdgcn_readfirstlane(starts[tw]) & ~1u;
+    const int nth = __popc(parted & ((1u << tw) - 1u));
+    const bool two = (parted >> tw & 1) && nth < kSeconds;   // wave-uniform
+    int split = kTile;
+    if (two) {
+      const int up = inner >> 16 ? 16 + __builtin_ctz(inner >> 16) : 64, down = inner & 0xFFFFu ? 31 - __builtin_clz(inner & 0xFFFFu) : -64;
+      split = up - 16 <= 16 - down ? up : down;
+    }
+    // sums of the bytes over the rows of either part: a lane takes four coordinates of every fourth row
+    int part[4] = {0, 0, 0, 0}, rest[4] = {0, 0, 0, 0};
+    const int q = lane & 15, h = lane >> 4;
 #pragma unroll
-    for (int o = 16; o > 0; o >>= 1) e = max(e, (uint32_t)__shfl_xor((int)e, o));
-    if (lane == 0) p.etile[(size_t)ut * p.Tp + (p0 >> 5)] = e;
-    uint8_t *d = sk + (size_t)(p0 >> 5) * kSixBytes;
-    reinterpret_cast<u4 *>(d)[lane] = u4{six[0], six[1], six[2], six[3]};
-    reinterpret_cast<uint2 *>(d + 1024)[lane] = make_uint2(six[4], six[5]);
+    for (int j = 0; j < 8; ++j) {
+      const int r = 4 * j + h;
+      const int x = *reinterpret_cast<const int *>(turn + r * kSketchBytes + (((q >> 2) ^ (j & 3)) << 4) + (q & 3) * 4);
+      const int x0 = two && r >= split ? 0 : x;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) part[k] = __builtin_amdgcn_sdot4(x0, 1 << (8 * k), part[k], false);
+      if (two) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) rest[k] = __builtin_amdgcn_sdot4(x ^ x0, 1 << (8 * k), rest[k], false);
+      }
+    }
+    const int rows = min(kTile, max(n - p0, 0)), rows0 = min(split, rows), row = lane & 31;
+    for (int half = 0; half < (two ? 2 : 1); ++half) {
+      const int count_of = half ? rows - rows0 : rows0;
+      const float each = count_of > 0 ? 1.f / (float)count_of : 0.f;
+      float4 m;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        int x = half ? rest[k] : part[k];
+        const auto y = __builtin_amdgcn_permlane16_swap((uint32_t)x, (uint32_t)x, false, false);
+        x = (int)(y[0] + y[1]);
+        const auto z = __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)x, false, false);
+        reinterpret_cast<float *>(&m)[k] = (float)(int)(z[0] + z[1]) * each;
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // the centre before has been read
+      if (lane < 16) *reinterpret_cast<float4 *>(&centre[wave][4 * q]) = m;
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      f16v x[2];
+#pragma unroll
+      for (int k = 0; k < 2; ++k)
+#pragma unroll
+        for (int i = 0; i < 16; i += 4) {
+          const float4 y = *reinterpret_cast<const float4 *>(&centre[wave][(2 * k + (lane >> 5)) * 16 + i]);
+          x[k][i] = y.x; x[k][i + 1] = y.y; x[k][i + 2] = y.z; x[k][i + 3] = y.w;
+        }
+      const u6 c = to_six(x[0], x[1]);
+      // squared distances from the products with the centre, which is all rows of one operand
+      const i8v ca = {(int)c[0], (int)c[1], (int)c[2], (int)c[3], (int)c[4], (int)c[5], 0, 0};
+      const i8v sa = {(int)six[0], (int)six[1], (int)six[2], (int)six[3], (int)six[4], (int)six[5], 0, 0};
+      const f16v zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+      const float with = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(ca, sa, zero, 2, 2, 0, 0, 0, 0)[0];
+      const float own = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(ca, ca, zero, 2, 2, 0, 0, 0, 0)[0];
+      const float r2 = row < rows && (row < split) == (half == 0) ? fmaxf(norm2 - 2.f * with + own, 0.f) : 0.f;
+      const float far2 = __uint_as_float(max32(__float_as_uint(r2)));
+      const int at = half ? 2 * kTile + second0 + nth : half_at + tw, cl = (lane & 32) + (at & 31);
+      uint8_t *to = centres + (at >> 5) * kSixBytes;
+      if (row == 0) {
+        *reinterpret_cast<u4 *>(to + cl * 16) = u4{c[0], c[1], c[2], c[3]};
+        *reinterpret_cast<uint2 *>(to + 1024 + cl * 8) = make_uint2(c[4], c[5]);
+      }
+      if (lane == 0) {
+        balls[at] = make_float2((float)e * kUnit + 0x1p-9f, sqrtf(far2) * (1.f + 1e-5f));   // (the power: rounding of thresholds)
+        if (half) p.second[group * kTile + second0 + nth] = (uint8_t)(half_at + tw);
+      }
+    }
+    const float longest2 = __uint_as_float(max32(__float_as_uint(norm2)));
+    if (lane == 0) {
+      p.etile[(size_t)ut * p.Tp + (p0 >> 5)] = e;
+      p.tnorm[(size_t)ut * p.Tp + (p0 >> 5)] = sqrtf(longest2) * (1.f + 1e-5f);
+    }
   }
 }
 
@@ -449,108 +591,286 @@ __device__ __forceinline__ void put_marks(const ShallowParams &p, int ut, int r0
   }
 }
 
-// The row tiles' sketches stay in registers as the matrix columns, four tiles per wave; the column tiles are
-// staged through LDS eight at a time (fragment order: loads and reads are both linear, no bank conflicts).  Per
-// 32 x 32 pairs one 32x32x64 matrix instruction on six-bit floats; all the results are needed for is their maximum, eight
-// v_max3 per lane (which take as long as the matrix instruction), and one comparison for the wave's four tiles.  Tiles
-// that pass are marked in both directions.  16 problems of 32768 tokens: 0.27 ms; with bytes, two 32x32x32
-// instructions, 0.38 ms; all cosines in fp16, with the bits packed
-// and records written, took 1.80 ms.
+// A block first asks the balls (shallow_window): a pair of a tile A and a ball with centre c and radius R can hold a sketch
+// product above a threshold only if the largest product of A's sketches with c, plus R times the length of the longest
+// of them, is above it.  One matrix instruction answers that for a tile and 32 balls (the ballot of the lanes is the answer as bits),
+// where the sketches of 32 tiles take 32.  The panel's tiles are asked against the columns' balls, and what is
+// left of the columns against the panel's balls: a tight tile excludes what it doesn't reach whatever stands on the other side.
+// Then the sketches of what is left: per 32 x 32 pairs one 32x32x64 matrix instruction on six-bit floats; all the results are
+// needed for is their maximum, eight v_max3 per lane (which take as long as the matrix instruction), and one comparison.
+// As a rule a wave takes every fourth column tile that is left, in registers, and the panel's tiles that it is left for from LDS.
+// Where most is left (isolated tokens) the row tiles' sketches stay in registers, four tiles per wave, and the column tiles
+// are staged through LDS, eight at a time (fragment order: loads and reads are both linear, no bank conflicts).
+// Tiles that pass are marked in both directions.
+// 16 problems of 32768 tokens in drifting clusters: 280 us with all sketch products, 125 now; 64 of which half of the tokens are
+// isolated 1035 and 575; 128 of 8192 in clusters 210 and 58 (and 12 to 27 more in shallow_window for the balls).  A pair of tiles
+// among all takes 39 cycles of a SIMD, one of its own about 150, mostly latency.
 // A block that finds more than kRefineShare of its column tiles marked (keys with a common component, low
-// thresholds) stops and leaves all of its pairs to shallow_refine.  The panel's own columns don't count, and a
+// thresholds) leaves all of its pairs to shallow_refine.  The panel's own columns don't count, and a
 // run of similar tokens behind them is allowed for: those are true neighbours.
 constexpr int kScanThreads = 256;
+constexpr int kScanCols = kScanRun * kScanStage;
+constexpr int kScanWords = (kScanCols + 2 * kWave - 2) / kWave * 2;   // of 32 tiles, whole windows around a run
+constexpr float kBallLoose = 8.f;                      // radius that excludes nothing (0.43 of a sketch)
 
-__global__ __launch_bounds__(kScanThreads, 2) void shallow_scan(ShallowParams p) {
-  __shared__ __attribute__((aligned(1024))) char stage[2][kScanStage * kSixBytes];
-  __shared__ uint8_t marks[kScanPanel][kScanRun];
-  __shared__ int found[kScanRun];                      // marks of a stage, once for the four row tiles of a wave
+template <bool kWithBalls>
+__global__ __launch_bounds__(kScanThreads, 4) void shallow_scan(ShallowParams p) {
+  __shared__ __attribute__((aligned(1024))) char stage[2 * kScanStage * kSixBytes];   // the panel's tiles, or two stages
+  static_assert(2 * kScanStage == kScanPanel, "the panel's tiles fit");
+  __shared__ __attribute__((aligned(16))) uint8_t marks[kScanPanel][kScanRun];
+  __shared__ int found[kScanRun];                      // marks of a stage, once for four row tiles
+  __shared__ uint32_t need[kScanPanel][kScanWords];    // bit per column tile that a row tile is left with
+  __shared__ float col_thr[kScanCols], col_norm[kScanCols];   // theta less a column tile's error; longest sketch
+  __shared__ float row_thr[kScanPanel];                // theta less a row tile's error
+  __shared__ uint32_t list[kScanThreads / kWave][kScanCols];
   const int xcd = blockIdx.x & 7;
   const ScanItem w = scan_item(p, blockIdx.x >> 3, xcd);
   if (w.s0 >= w.s1 || p.by[w.ut / p.U] != kBySketch) {
     if (threadIdx.x == 0) p.todo[blockIdx.x] = w.s0 < w.s1 && p.by[w.ut / p.U] == kByVector;
     return;
   }
-  const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), c = lane & 31, g = lane >> 5;
   const char *sk = reinterpret_cast<const char *>(p.sk) + (size_t)w.ut * p.Tp * kSixBytes;
   const uint32_t *et = p.etile + (size_t)w.ut * p.Tp;
-  const int r0 = w.I * kScanPanel + wave * 4;
+  const float *norm = p.tnorm + (size_t)w.ut * p.Tp;
+  const int r0 = w.I * kScanPanel + wave * 4, c0 = w.s0 * kScanStage, c1 = w.s1 * kScanStage;
+  const int win0 = c0 / kBallTiles, win1 = (c1 - 1) / kBallTiles;   // groups of balls of the columns
+  static_assert(kBallTiles == kWave, "places of tiles in a group");
+  const size_t windows = (size_t)w.ut * ((p.Tp + kBallTiles - 1) / kBallTiles);
   const int thr0 = p.scan_thr[w.ut / p.U];
   constexpr float kUnit = 1.f / (kSixScale * kSixScale);   // products are in units of kSixScale squared
+  const uint32_t stage_lds = (uint32_t)(size_t)(__attribute__((address_space(3))) char *)stage;
+  constexpr int kLoads = kScanStage * kSixBytes / 1024 / (kScanThreads / kWave);   // of 1 KiB per wave and stage
+  static_assert(kLoads * 1024 * (kScanThreads / kWave) == kScanStage * kSixBytes, "whole loads");
+  auto dma = [&](int s, int buffer) __attribute__((always_inline)) {
+    const char *src = sk + (size_t)s * (kScanStage * kSixBytes) + wave * (kLoads * 1024);
+#pragma unroll
+    for (int q = 0; q < kLoads; ++q)
+      lds_dma16_at(src, (uint32_t)(q * 1024 + lane * 16),
+                   stage_lds + buffer * (kScanStage * kSixBytes) + wave * (kLoads * 1024) + q * 1024);
+  };
+  if (kWithBalls) {
+    dma(w.I * 2, 0);
+    dma(w.I * 2 + 1, 1);
+  }
   reinterpret_cast<uint8_t *>(marks)[threadIdx.x] = 0;
   if (threadIdx.x < kScanRun) found[threadIdx.x] = 0;
+  if (lane < 4 * kScanWords) need[wave * 4 + lane / kScanWords][lane % kScanWords] = 0;
+  static_assert(4 * kScanWords <= kWave, "a lane per word");
   auto tile_at = [&](const char *t) __attribute__((always_inline)) {
     const u4 a = *reinterpret_cast<const u4 *>(t + lane * 16);
     const uint2 b = *reinterpret_cast<const uint2 *>(t + 1024 + lane * 8);
     return i8v{(int)a[0], (int)a[1], (int)a[2], (int)a[3], (int)b.x, (int)b.y, 0, 0};
   };
+  auto products = [&](const i8v &a, const i8v &b) __attribute__((always_inline)) {
+    f16v acc;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+    // (formats 2: six bits, two of them exponent; no block scales)
+    return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, acc, 2, 2, 0, 0, 0, 0);
+  };
+  // largest of a lane's products (as integers: floats order alike as far as it matters)
+  auto most = [&](const f16v &acc) __attribute__((always_inline)) {
+    int x = __float_as_int(acc[0]);
+#pragma unroll
+    for (int v = 1; v < 16; ++v) x = max(x, __float_as_int(acc[v]));
+    return x;
+  };
+  // What the integers of results above a threshold exceed: all of them where it isn't positive (no result is -0).
+  auto above = [](float thr) __attribute__((always_inline)) { return thr > 0.f ? __float_as_int(thr) : INT32_MIN; };
+  auto both_groups = [](unsigned long long m) __attribute__((always_inline)) { return (uint32_t)m | (uint32_t)(m >> 32); };
   i8v bf[4];
-  float ethr[4];                                       // theta less the row tile's error
+  float ethr[4], rnorm[4];                             // theta less the row tile's error; longest sketch
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     bf[r] = tile_at(sk + (size_t)(r0 + r) * kSixBytes);
     ethr[r] = (float)(thr0 - (int)et[r0 + r]) * kUnit;
+    rnorm[r] = kWithBalls ? norm[r0 + r] : 0.f;
   }
-  const float emin = fminf(fminf(ethr[0], ethr[1]), fminf(ethr[2], ethr[3]));
-  const uint32_t stage_lds = (uint32_t)(size_t)(__attribute__((address_space(3))) char *)stage;
-  constexpr int kLoads = kScanStage * kSixBytes / 1024 / (kScanThreads / kWave);   // of 1 KiB per wave and stage
-  static_assert(kLoads * 1024 * (kScanThreads / kWave) == kScanStage * kSixBytes, "whole loads");
-  auto dma = [&](int s) {
-    const char *src = sk + (size_t)s * (kScanStage * kSixBytes) + wave * (kLoads * 1024);
-#pragma unroll
-    for (int q = 0; q < kLoads; ++q)
-      lds_dma16_at(src, (uint32_t)(q * 1024 + lane * 16),
-                   stage_lds + (s & 1) * (kScanStage * kSixBytes) + wave * (kLoads * 1024) + q * 1024);
-  };
-  // What the integers of results above a threshold exceed: all of them where it isn't positive (no result is -0).
-  auto above = [](float thr) __attribute__((always_inline)) { return thr > 0.f ? __float_as_int(thr) : INT32_MIN; };
   constexpr int kPerStage = kScanPanel / 4 * kScanStage;   // column tiles, once per wave
   const int own = (w.I + 1) * (kScanPanel / kScanStage);   // first stage behind the panel's own columns
-  int all = 0;                                         // marks of the stages from there on
-  bool refine = false;
-  dma(w.s0);
-  for (int s = w.s0;; ++s) {
-    const float ecol = s < w.s1 ? (float)et[s * kScanStage + (lane & 7)] * kUnit : 0.f;
-    __builtin_amdgcn_s_waitcnt(0x0F70);                // vmcnt(0): this wave's part of stage s has landed
-    __syncthreads();                                   // ... and every wave's; the other buffer is free
-    if (s > w.s0 && s > own) {
-      all += found[s - 1 - w.s0];
-      refine = all > (s - max(own, w.s0)) * (int)(kRefineShare * kPerStage) + kPerStage / 3;
-      if (refine) break;
+  bool dense = true, refine = false;
+  if constexpr (kWithBalls) {
+  for (int i = threadIdx.x; i < c1 - c0; i += kScanThreads) {
+    col_thr[i] = (float)(thr0 - (int)et[c0 + i]) * kUnit;
+    col_norm[i] = norm[c0 + i];
+  }
+  if (threadIdx.x < kScanPanel) row_thr[threadIdx.x] = (float)(thr0 - (int)et[w.I * kScanPanel + threadIdx.x]) * kUnit;
+
+  // ---- the panel's balls: the first of row tile i in column i, seconds from column 16 on
+  const int pwin = w.I * kScanPanel / kWave, prow = w.I * kScanPanel % kWave;   // window of the panel, its first tile there
+  const float2 *pinfo = p.ball + (windows + pwin) * kBalls;
+  int prow_of;                                         // a lane's row tile of the panel, -1: no ball
+  float2 pball;
+  i8v pc;
+  {
+    const float e2 = pinfo[2 * kTile + c].x;
+    const int row2 = ((int)p.second[(windows + pwin) * kTile + c] & (kWave - 1)) - prow;
+    const uint32_t mine = (uint32_t)__ballot(e2 > -0x1p29f && row2 >= 0 && row2 < kScanPanel);   // slots, ascending tiles: a run
+    const int slot = mine ? __builtin_ctz(mine) + (c & 15) : 0;
+    const bool second = c >= kScanPanel;
+    const int at = second ? 2 * kTile + min(slot, kTile - 1) : prow + c;
+    pball = pinfo[at];
+    const char *t = reinterpret_cast<const char *>(p.skc) + (windows + pwin) * (3 * kSixBytes) + (at >> 5) * kSixBytes;
+    const u4 x = *reinterpret_cast<const u4 *>(t + (g * 32 + (at & 31)) * 16);
+    const uint2 y = *reinterpret_cast<const uint2 *>(t + 1024 + (g * 32 + (at & 31)) * 8);
+    pc = i8v{(int)x[0], (int)x[1], (int)x[2], (int)x[3], (int)y.x, (int)y.y, 0, 0};
+    const int of2 = __shfl(row2, min(slot, kTile - 1));
+    prow_of = !second ? c : slot < kTile && (mine >> slot & 1) ? of2 : -1;
+  }
+  const uint32_t loose = (uint32_t)__ballot(lane < kScanPanel && !(pball.y < kBallLoose));   // row tiles (the same in all waves)
+
+  // ---- the panel's tiles against the columns' balls
+  for (int win = win0; win <= win1; ++win) {
+    const char *ct = reinterpret_cast<const char *>(p.skc) + (windows + win) * (3 * kSixBytes);
+    const float2 *info = p.ball + (windows + win) * kBalls;
+    const int tw = (int)p.second[(windows + win) * kTile + c] & (kWave - 1);
+    i8v b[3];
+    float2 f[3];
+#pragma unroll
+    for (int part = 0; part < 3; ++part) {
+      b[part] = tile_at(ct + part * kSixBytes);
+      f[part] = info[part * kTile + c];
     }
-    if (s == w.s1) break;
-    if (s + 1 < w.s1) dma(s + 1);
-    const char *st = stage[s & 1];
-    const int least = above(emin - ecol);              // lane t: of column tile t
-    uint32_t hit[4] = {0, 0, 0, 0};
+    if (!__any(f[0].y < kBallLoose || f[1].y < kBallLoose || (f[2].y < kBallLoose && f[2].x > -0x1p29f))) {   // isolated tokens
+      if (lane < 8) need[wave * 4 + (lane >> 1)][(win - win0) * 2 + (lane & 1)] = 0xFFFFFFFFu;
+      continue;
+    }
 #pragma unroll
-    for (int t = 0; t < kScanStage; ++t) {
-      const i8v a = tile_at(st + t * kSixBytes);
-      int m[4];                                        // (as integers: floats order alike as far as it matters)
+    for (int part = 0; part < 3; ++part) {
+      const int first = win * kWave + part * kTile, word = (win - win0) * 2 + part;
+      if (part < 2 && (first >= c1 || first + kTile <= c0)) continue;   // block-uniform
+      uint32_t hits[4];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        f16v acc;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-        // (formats 2: six bits, two of them exponent; no block scales)
-        acc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, bf[r], acc, 2, 2, 0, 0, 0, 0);
-        int x = __float_as_int(acc[0]);
-#pragma unroll
-        for (int v = 1; v < 16; ++v) x = max(x, __float_as_int(acc[v]));
-        m[r] = x;
+      for (int r = 0; r < 4; r += 2) {
+        const f16v x = products(bf[r], b[part]), y = products(bf[r + 1], b[part]);
+        hits[r] = both_groups(__ballot(most(x) > above(ethr[r] - f[part].x - rnorm[r] * f[part].y)));
+        hits[r + 1] = both_groups(__ballot(most(y) > above(ethr[r + 1] - f[part].x - rnorm[r + 1] * f[part].y)));
       }
-      if (__any(max(max(m[0], m[1]), max(m[2], m[3])) > __builtin_amdgcn_readlane(least, t))) {
-        const float ec = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(ecol), t));
+      if (part < 2) {
+        if (lane < 4) need[wave * 4 + lane][part < 2 ? word : 0] = lane == 0 ? hits[0] : lane == 1 ? hits[1] : lane == 2 ? hits[2] : hits[3];
+      } else if (lane < kTile) {
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-          if (__any(m[r] > above(ethr[r] - ec))) hit[r] |= 1u << t;
+          if (hits[r] >> c & 1) atomicOr(&need[wave * 4 + r][(win - win0) * 2 + (tw >> 5)], 1u << (tw & 31));
       }
     }
-    if (hit[0] | hit[1] | hit[2] | hit[3]) {
-      if (lane == 0) {
+  }
+  __builtin_amdgcn_s_waitcnt(0x0F70);                  // vmcnt(0): this wave's part of the panel has landed
+  __syncthreads();
+  // Column tiles that any row tile is left with, in order: tile of the run | a bit per row tile << 16 (every wave the same).
+  int nlist = 0, npairs = 0, nloose = 0;               // pairs of tiles; of loose row tiles
 #pragma unroll
-        for (int r = 0; r < 4; ++r) marks[wave * 4 + r][s - w.s0] = (uint8_t)hit[r];
-        atomicAdd(&found[s - w.s0], __popc(hit[0] | hit[1] | hit[2] | hit[3]));
+  for (int half = 0; half < kScanCols; half += kWave) {
+    const int t = half + lane, at = c0 + t - win0 * kWave;
+    uint32_t rows = 0;
+#pragma unroll
+    for (int r = 0; r < kScanPanel; ++r) rows |= (need[r][at >> 5] >> (at & 31) & 1u) << r;
+    if (t >= c1 - c0) rows = 0;
+    const unsigned long long m = __ballot(rows != 0);
+    if (rows) list[wave][nlist + __popcll(m & ((1ull << lane) - 1ull))] = (uint32_t)t | rows << 16;
+    nlist += __popcll(m);
+    npairs += __popc(rows) + (__popc(rows & loose) << 16);
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) npairs += __shfl_xor(npairs, o);
+  nloose = npairs >> 16;
+  npairs &= 0xFFFF;
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  // What tight row tiles are left with their balls will mostly exclude, unless nothing is excluded at all.  A pair of its
+  // own takes three to four times what it does among all.
+  dense = __builtin_amdgcn_readfirstlane(2 * nloose > (c1 - c0) * kScanPanel || 5 * npairs > 4 * (c1 - c0) * kScanPanel);
+
+  if (!dense) {
+    // Every fourth column tile that is left is the wave's, one per lane: what a step needs of it comes from the lane that
+    // has it, and what it finds goes there (as scalars: lists and flags in LDS were a dozen waits per step).
+    constexpr int kStep = kScanThreads / kWave;
+    const int ncols = nlist > wave ? (nlist - wave + kStep - 1) / kStep : 0;   // at most 32
+    const uint32_t e = lane < ncols ? list[wave][wave + kStep * lane] : 0u;
+    const float ethr_l = col_thr[e & 127], norm_l = col_norm[e & 127], row_thr_l = row_thr[lane & 15];
+    uint32_t hit_l = 0;                                // row tiles that pass with the lane's tile
+    i8v a{}, a1{};
+    auto fetch = [&](int i) __attribute__((always_inline)) { return tile_at(sk + (size_t)(c0 + (__builtin_amdgcn_readlane(e, min(i, ncols - 1)) & 127)) * kSixBytes); };
+    if (ncols > 0) {
+      a = fetch(0);
+      a1 = fetch(1);
+    }
+    for (int i = 0; i < ncols; ++i) {
+      const i8v a2 = fetch(i + 2);
+      const float tthr = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(ethr_l), i)), tn = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(norm_l), i));
+      const float off = tthr - (float)thr0 * kUnit;    // less the column tile's error
+      const uint32_t balls = both_groups(__ballot(prow_of >= 0 && most(products(a, pc)) > above(tthr - pball.x - tn * pball.y)));
+      uint32_t rows = balls & 0xFFFFu, hit = 0;
+      for (uint32_t m = balls >> 16; m; m &= m - 1) rows |= 1u << __builtin_amdgcn_readlane(prow_of, 16 + __builtin_ctz(m));
+      rows &= (uint32_t)__builtin_amdgcn_readlane(e, i) >> 16;
+      while (rows) {                                   // two row tiles at a time
+        const int ra = __builtin_ctz(rows);
+        rows &= rows - 1;
+        const int rb = rows ? __builtin_ctz(rows) : ra;
+        rows &= rows - 1;
+        const i8v xa = tile_at(stage + ra * kSixBytes), xb = tile_at(stage + rb * kSixBytes);
+        const f16v pa = products(xa, a), pb = products(xb, a);
+        const float ta = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(row_thr_l), ra)), tb = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(row_thr_l), rb));
+        hit |= (uint32_t)(__ballot(most(pa) > above(ta + off)) != 0) << ra | (uint32_t)(__ballot(most(pb) > above(tb + off)) != 0) << rb;
+      }
+      hit_l = lane == i ? hit : hit_l;
+      a = a1;
+      a1 = a2;
+    }
+    for (; hit_l; hit_l &= hit_l - 1) {
+      const int t = (int)(e & 127);
+      atomicOr(reinterpret_cast<uint32_t *>(&marks[__builtin_ctz(hit_l)][0]) + (t >> 5), 1u << (t & 31));
+    }
+    __syncthreads();
+    // column tiles marked behind the panel's own, once for four row tiles: lane 16 q + s
+    int all = 0;
+    {
+      const int q = lane >> 4, s = lane & 15;
+      if (w.s0 + s >= own && w.s0 + s < w.s1)
+        all = __popc((uint32_t)marks[4 * q][s] | marks[4 * q + 1][s] | marks[4 * q + 2][s] | marks[4 * q + 3][s]);
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) all += __shfl_xor(all, o);
+    }
+    refine = w.s1 > own && all > (w.s1 - max(own, w.s0)) * (int)(kRefineShare * kPerStage) + kPerStage / 3;
+  }
+  }
+  if (dense) {
+    const float emin = fminf(fminf(ethr[0], ethr[1]), fminf(ethr[2], ethr[3]));
+    int all = 0;                                       // marks of the stages behind the panel's own
+    dma(w.s0, 0);                                      // (no wave reads the panel's tiles)
+    for (int s = w.s0;; ++s) {
+      const float ecol = s < w.s1 ? (float)et[s * kScanStage + (lane & 7)] * kUnit : 0.f;
+      __builtin_amdgcn_s_waitcnt(0x0F70);              // vmcnt(0): this wave's part of stage s has landed
+      __syncthreads();                                 // ... and every wave's; the other buffer is free
+      if (s > w.s0 && s > own) {
+        all += found[s - 1 - w.s0];
+        refine = all > (s - max(own, w.s0)) * (int)(kRefineShare * kPerStage) + kPerStage / 3;
+        if (refine) break;
+      }
+      if (s == w.s1) break;
+      if (s + 1 < w.s1) dma(s + 1, (s + 1 - w.s0) & 1);
+      const char *st = stage + ((s - w.s0) & 1) * (kScanStage * kSixBytes);
+      const int least = above(emin - ecol);            // lane t: of column tile t
+      uint32_t hit[4] = {0, 0, 0, 0};
+#pragma unroll
+      for (int t = 0; t < kScanStage; ++t) {
+        const i8v a = tile_at(st + t * kSixBytes);
+        int m[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) m[r] = most(products(a, bf[r]));
+        if (__any(max(max(m[0], m[1]), max(m[2], m[3])) > __builtin_amdgcn_readlane(least, t))) {
+          const float ec = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(ecol), t));
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            if (__any(m[r] > above(ethr[r] - ec))) hit[r] |= 1u << t;
+        }
+      }
+      if (hit[0] | hit[1] | hit[2] | hit[3]) {
+        if (lane == 0) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) marks[wave * 4 + r][s - w.s0] = (uint8_t)hit[r];
+          atomicAdd(&found[s - w.s0], __popc(hit[0] | hit[1] | hit[2] | hit[3]));
+        }
       }
     }
   }
@@ -621,8 +941,15 @@ __global__ __launch_bounds__(kRefineThreads, 2) void shallow_refine(ShallowParam
       total += x;
     }
     __syncthreads();
-    for (int at = slot; at < 2 * total; at += nslots) {
-      const ScanItem w = scan_item(p, i0 + list[at >> 1], xcd);
+    // few items are cut along their columns too, as long as there are blocks without any (one item by two blocks: 30 us)
+    int cuts = 1;
+    while (cuts < kScanRun / 2 && 4 * cuts * total <= nslots) cuts *= 2;
+    for (int at = slot; at < 2 * cuts * total; at += nslots) {
+      ScanItem w = scan_item(p, i0 + list[at / (2 * cuts)], xcd);
+      const int some = (w.s1 - w.s0 + cuts - 1) / cuts;   // stages
+      w.s0 += (at >> 1) % cuts * some;
+      w.s1 = min(w.s1, w.s0 + some);
+      if (w.s0 >= w.s1) continue;                      // (the same for the block)
       const size_t base = (size_t)w.ut * n;
       const char *X = kRaw ? x_row(p, w.ut, 0) : reinterpret_cast<const char *>(p.Xh) + base * 256;
       const size_t pitch = kRaw ? (size_t)p.lay.st : 256;
@@ -1221,18 +1548,19 @@ spindle_status launch_rows(const ShallowParams &p, hipStream_t st) {
 spindle_status launch_tiles(const ShallowParams &p, hipStream_t st) {
   const int n = p.n;
   if (p.scan) {
-    const int nblk = (n + kOrderTokens - 1) / kOrderTokens, nwin = (n + kWindow - 1) / kWindow;
+    const int nblk = (n + kOrderTokens - 1) / kOrderTokens, nwin = 2 * ((n + 2 * kWindow - 1) / (2 * kWindow));
     int npiv = (n / 16) & ~31;
     if (npiv > kPivots) npiv = kPivots;
     { ProfScope ps("shallow_pivots", st);
     hipLaunchKernelGGL(shallow_pivots, dim3(xcd_grid((size_t)p.UT * nblk)), dim3(kPivotThreads), 0, st, p, npiv, nblk); }
     { ProfScope ps("shallow_order", st);
-    hipLaunchKernelGGL(shallow_order, dim3(xcd_grid((size_t)p.UT * nblk)), dim3(kPivots), 0, st, p, nblk); }
+    hipLaunchKernelGGL(shallow_order, dim3(xcd_grid((size_t)p.UT * nblk)), dim3(kOrderThreads), 0, st, p, nblk); }
     { ProfScope ps("shallow_window", st);
     hipLaunchKernelGGL(shallow_window, dim3(xcd_grid((size_t)p.UT * nwin)), dim3(kWindowThreads), 0, st, p, nwin); }
     const int nitems = scan_blocks(p) / 8;
     { ProfScope ps("shallow_scan", st, most_by(p) == kBySketch);
-    hipLaunchKernelGGL(shallow_scan, dim3((unsigned)(8 * nitems)), dim3(kScanThreads), 0, st, p); }
+    if (p.balls) hipLaunchKernelGGL(shallow_scan<true>, dim3((unsigned)(8 * nitems)), dim3(kScanThreads), 0, st, p);
+    else hipLaunchKernelGGL(shallow_scan<false>, dim3((unsigned)(8 * nitems)), dim3(kScanThreads), 0, st, p); }
     { ProfScope ps("shallow_refine", st, most_by(p) == kByVector);
     if (p.dtype == SPINDLE_F16) hipLaunchKernelGGL(shallow_refine<SPINDLE_F16>, dim3(kRefineBlocks), dim3(kRefineThreads), 0, st, p, nitems);
     else if (p.dtype == SPINDLE_BF16) hipLaunchKernelGGL(shallow_refine<SPINDLE_BF16>, dim3(kRefineBlocks), dim3(kRefineThreads), 0, st, p, nitems);

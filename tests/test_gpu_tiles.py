@@ -15,11 +15,23 @@ pytestmark = [pytest.mark.gpu, pytest.mark.timeout(300)]
 @pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
 @pytest.mark.parametrize("l", [2047, 2048, 2049, 2560, 4095, 4097])
 def test_lengths_around_the_scan_and_its_windows(oracle, dtype, l):
-    # sorted from 2048 tokens on, windows of 2048 places, panels of 512: ragged and whole ends
+    # sorted from 2048 tokens on, windows of 1024 places, panels of 512: ragged and whole ends
     L = wl.small_random(61, dtype, B=1, H=1, l=l, lw=1, cap=max(1, l // 9), n_centroids=l // 40, noise_frac=0.3,
                         drift_sigma=0.003)
     parity.check_shallow_layer(oracle, L, debug=False)
     parity.check_shallow_layer(oracle, L, cap=l, tensors=("k",))            # with G and the degrees
+
+
+@pytest.mark.parametrize("dtype,H,l,centroids,noise,drift,theta", [
+    ("f16", 128, 2593, 20, 0.3, 0.003, 0.98),             # 82 tiles: a second group of balls that is mostly not there
+    ("bf16", 100, 3000, 3, 0.1, 0.0, 0.9), ("f32", 64, 3650, 40, 0.5, 0.0, 0.95),
+    ("f16", 52, 4097, 200, 0.05, 0.002, 0.95),            # few tokens per cluster, many second balls
+    ("bf16", 64, 3649, 1, 0.97, 0.0, 0.75)])              # isolated tokens: blocks that take all pairs
+def test_tile_pairs_excluded_by_balls(oracle, dtype, H, l, centroids, noise, drift, theta):
+    # enough problems for the scan to ask the balls around the tiles first
+    L = wl.small_random(64, dtype, B=1, H=H, l=l, lw=1, cap=l // 7, n_centroids=centroids, noise_frac=noise, drift_sigma=drift)
+    L.theta_k = L.theta_v = theta
+    parity.check_shallow_layer(oracle, L, units=[(0, 0), (0, H // 2), (0, H - 1)], debug=False)
 
 
 @pytest.mark.parametrize("H,l", [(1, 2304), (8, 2016), (8, 2048), (16, 1000), (17, 960)])
