@@ -127,6 +127,34 @@ __device__ __forceinline__ int seg_sum(int v) {             // over a segment, r
   return v;
 }
 
+// Largest of the values in memory that the words of a row select (and m), for a segment whose lanes have a word each: a
+// quad takes its four words one after the other, each lane 16 of the 64 bytes, so that a load of the wave touches 16 lines
+// and not 64 (what bounded the one-hop maxima of 128 problems of 8192 tokens in clusters of 128: 76 us with a word per lane, 33 now).
+__device__ __forceinline__ uint32_t quad_max(const uint32_t *a, uint32_t word, uint32_t m) {
+  const int piece = lane_id() & 3;
+  uint32_t w[4];
+  u4 q[4];
+  w[0] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)word, 0x00, 0xF, 0xF, true);   // quad_perm [i,i,i,i]
+  w[1] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)word, 0x55, 0xF, 0xF, true);
+  w[2] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)word, 0xAA, 0xF, 0xF, true);
+  w[3] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)word, 0xFF, 0xF, 0xF, true);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    q[i] = u4{0, 0, 0, 0};
+    if (w[i] & 0xFFFFu) q[i] = reinterpret_cast<const u4 *>(a + (w[i] >> 16) * 16)[piece];
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int bits = (int)(w[i] >> (4 * piece));
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const uint32_t y = q[i][j] & (uint32_t)__builtin_amdgcn_sbfe(bits, j, 1);
+      m = y > m ? y : m;
+    }
+  }
+  return m;
+}
+
 // Bit s of the result: `on` of segment s (0..7), given in the segment's first lane.
 __device__ __forceinline__ uint32_t seg_bits(bool on) {
   const unsigned long long m = __ballot(on && (lane_id() & (kSegW - 1)) == 0);
@@ -161,14 +189,17 @@ __global__ __launch_bounds__(kPhaseThreads) void merge_onehop(ShallowParams p, i
     r[k] = row_at(p, base, lists, v);
     own[k] = key[v];
   }
+  // (a token without neighbours needs none of its words)
 #pragma unroll
-  for (int k = 0; k < 4; ++k) w0[k] = on[k] && sl < r[k].n ? word_at(r[k], sl) : 0;
+  for (int k = 0; k < 4; ++k) {
+    if (!on[k] || own[k] >> 16 == 1) r[k].n = 0;
+    w0[k] = sl < r[k].n ? word_at(r[k], sl) : 0;
+  }
   uint32_t bits = 0;
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
-    uint32_t m = own[k];                              // a token is its own neighbour
-    if (w0[k] & 0xFFFFu) m = masked_max(key, w0[k], m);
-    if (on[k]) for_words(r[k], sl + kSegW, [&](uint32_t w) { m = masked_max(key, w, m); });
+    uint32_t m = quad_max(key, w0[k], own[k]);        // a token is its own neighbour
+    for (int i = sl + kSegW; __any(i < r[k].n); i += kSegW) m = quad_max(key, i < r[k].n ? word_at(r[k], i) : 0, m);
     m = seg_max(m);
     if (on[k] && sl == 0) m1[W * kTile + 8 * k + seg] = m;
     bits |= seg_bits(on[k] && m == own[k]) << (8 * k);
@@ -191,19 +222,33 @@ __global__ __launch_bounds__(kPhaseThreads) void merge_twohop(ShallowParams p, i
   const uint32_t *lists = p.lists + base * p.list_row, *live = p.live[round] + (size_t)ut * p.T;
   uint32_t *next[2] = {p.live[1] + (size_t)ut * p.T, p.live[2] + (size_t)ut * p.T};
   int *slot = p.slot + base;
-  uint32_t bits = 0;
+  // tokens without neighbours are picked as they are, a lane each
+  const int v = W * kTile + (lane & 31);
+  const uint32_t kv = cand >> (lane & 31) & 1 ? key[v] : 0u;
+  const bool alone = lane < kTile && kv >> 16 == 1;
+  if (alone) {
+    p.pick_key[base + v] = kv;
+    slot[v] = v;
+  }
+  uint32_t bits = (uint32_t)__ballot(alone);
+  if (bits && lane == 0) {
+    if (round == 0) atomicAnd(next[0] + W, ~bits);
+    atomicAnd(next[1] + W, ~bits);
+  }
+  const uint32_t rest = cand & ~bits;
   for (int k = 0; k < 4; ++k) {
-    if (((cand >> (8 * k)) & 0xFFu) == 0) continue;   // wave-uniform
-    const bool on = (cand >> (8 * k + seg)) & 1;
+    if (((rest >> (8 * k)) & 0xFFu) == 0) continue;   // wave-uniform
+    const bool on = (rest >> (8 * k + seg)) & 1;
     const int u = on ? W * kTile + 8 * k + seg : W * kTile;
-    const Row r = row_at(p, base, lists, u);
+    Row r = row_at(p, base, lists, u);
+    if (!on) r.n = 0;
     const uint32_t ku = key[u];
     uint32_t m = 0;
-    if (on)
-      for_words(r, sl, [&](uint32_t w) {
-        const uint32_t rem = still(live, w);          // neighbours still there at the start of the round
-        if (rem) m = masked_max(m1, (w & 0xFFFF0000u) | rem, m);
-      });
+    for (int i = sl; __any(i < r.n); i += kSegW) {
+      uint32_t w = i < r.n ? word_at(r, i) : 0;
+      w = (w & 0xFFFF0000u) | still(live, w);         // neighbours still there at the start of the round
+      m = quad_max(m1, w, m);
+    }
     const bool pick = on && seg_max(m) == ku;
     bits |= seg_bits(pick) << (8 * k);
     if (pick) {
