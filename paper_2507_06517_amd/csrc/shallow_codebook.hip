@@ -114,6 +114,10 @@ __global__ __launch_bounds__(kEmitThreads) void shallow_emit(ShallowParams p, in
 // zero, 128 entries: the call 426 us with a search for every such token, one token at a time per block, 79 now.
 // Where few tokens were cut in all, a block takes 64 of them and its waves a quarter of the products each: four
 // times the blocks for four times the reads of the entries.
+// What a tile of products costs besides the matrix instructions: its maximum (eight v_max3), the test whether any lane
+// is within reach of its token's maximum, and in the tiles where one is, the sixteen tests.  64 problems with half of 32768
+// tokens cut, 4096 entries: 1110 us with the tests in every tile and a maximum per lane, 968 now, 1.14 PFLOP/s, where the
+// matrix cores alone sustain 1.6 on such operands.
 // Lists in memory; in LDS 64 KiB per block, two blocks per CU: 1.81 ms where this took 1.58.
 // The exact comparison of every listed entry and the search of what was left as launches of their own, and the
 // entries gathered by token: 64 problems with half of 32768 tokens cut, 4096 entries, 1165 + 228 + 4 us, now 1235; 2 with 4000
@@ -208,25 +212,25 @@ __global__ __launch_bounds__(kAssignThreads, 2) void shallow_assign(ShallowParam
     float t = a[0];
 #pragma unroll
     for (int v = 1; v < 16; ++v) t = fmaxf(t, a[v]);
-    const float nm = fmaxf(runmax[cb], t);
+    // (the two lanes of a token know of each other's maximum)
+    const auto both = __builtin_amdgcn_permlane32_swap(__float_as_uint(t), __float_as_uint(t), false, false);
+    const float nm = fmaxf(fmaxf(runmax[cb], __uint_as_float(both[0])), __uint_as_float(both[1]));
     if (nm > runmax[cb] + band2) cnt[cb] = 0;         // everything collected so far is out of reach
     runmax[cb] = nm;
-    const float thr = nm - band2;
+    const float thr = fmaxf(nm - band2, -0x1p126f);   // (nothing but -INFINITY seen: nothing to collect)
+    if (!__any(t >= thr)) return;                      // most tiles once the maxima are known
     // bit v of `hits`: a[v] >= thr, from the sign of a[v] - thr (sixteen tests and branches, one per
     // value, cost several times the matrix instructions of the tile; hits are rare)
     uint32_t miss = 0;
 #pragma unroll
     for (int v = 15; v >= 0; --v) miss = __builtin_amdgcn_alignbit(miss, __float_as_uint(a[v] - thr), 31);
-    uint32_t hits = seeks[cb] ? ~miss & 0xFFFFu : 0u;
+    uint32_t hits = t >= thr && seeks[cb] ? ~miss & 0xFFFFu : 0u;
     if (hits) {
-      uint2 *list = cand + list_of(cb) * kCandCap;
+      uint2 *list = cand + list_of(cb) * kCandCap;     // (with the tile's maximum, which is the value of all but a few)
       do {
         const int v = __builtin_ctz(hits);
         hits &= hits - 1;
-        float val = a[0];
-#pragma unroll
-        for (int u = 1; u < 16; ++u) val = v == u ? a[u] : val;
-        if (cnt[cb] < kCandCap) list[cnt[cb]] = make_uint2((uint32_t)(j0 + 16 * g + v), __float_as_uint(val));
+        if (cnt[cb] < kCandCap) list[cnt[cb]] = make_uint2((uint32_t)(j0 + 16 * g + v), __float_as_uint(t));
         ++cnt[cb];
       } while (hits);
     }
