@@ -69,7 +69,7 @@ constexpr uint32_t kSketchUnknown = 1u << 20;    // error of a token whose sketc
 // Tokens are sorted by bucket, two per pivot (at most kPivots, one per 16 tokens): what is near it, and what isn't but has
 // it nearest.
 constexpr int kPivots = 1024, kBuckets = 2 * kPivots;
-constexpr int kOrderTokens = 512;                // tokens per block of shallow_pivots and shallow_order
+constexpr int kOrderTokens = 512;                // tokens per block of shallow_pivots and shallow_order, or twice as many
 constexpr int kWindow = 1024;                    // places of a block of shallow_window
 constexpr int kBallTiles = 64;                   // tiles whose balls stand together: one each, and 32 seconds
 constexpr int kBalls = 3 * kTile;

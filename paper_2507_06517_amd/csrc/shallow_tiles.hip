@@ -24,7 +24,12 @@ typedef int i16v __attribute__((ext_vector_type(16)));
 // are about three times that wide, and one ends 2.7 times it above.  Where the mean is most of the length, more than
 // kMeanMost, the norms vary more than what is left: their four bytes then carry the token's own product with
 // the mean instead.
-constexpr int kStepOffset = 3000;
+// The pivots' bytes are rounded to multiples of 16 (0.015 of a cosine), so that products are multiples of 16 and start at
+// the number of their result register: the maximum of a tile of pivots, which is all that is taken of it, says which one it
+// was; a lower pivot of a tile starts 1/16 of a step ahead of the next, so that tokens near several agree on one (taking
+// the nearest parts every fifth cluster of 8192 tokens: 5 % more for shallow_rows).  With the register put into each product
+// behind a mask the vector work was twice the matrix instructions.
+constexpr int kStepOffset = 3008;
 constexpr float kStepEnd = 0.345f, kStep = 0.388f, kMeanSome = 0.15f, kMeanMost = 1.9f;
 // Tokens that are near no pivot (a cosine of 0.73, the last step from 0.88 on) go ahead of the others, and so do the
 // few of a pivot that is alone (kAlone tokens): what is isolated stands together then and doesn't widen the tiles of what is
@@ -32,6 +37,7 @@ constexpr float kStepEnd = 0.345f, kStep = 0.388f, kMeanSome = 0.15f, kMeanMost 
 constexpr int kMeanOf = 128, kNearStep = 5, kAlone = 8;
 constexpr int kPivotThreads = 256;
 
+template <int kTiles>                                  // of 32 tokens per wave
 __global__ __launch_bounds__(kPivotThreads, 2) void shallow_pivots(ShallowParams p, int npiv, int nblk) {
   __shared__ __attribute__((aligned(16))) char piv[kPivots * kSketchBytes];    // fragment order: tile, half, lane
   __shared__ uint32_t cnt[kBuckets];
@@ -44,20 +50,37 @@ __global__ __launch_bounds__(kPivotThreads, 2) void shallow_pivots(ShallowParams
   const uint8_t *sk = p.sk0 + (size_t)ut * n * kSketchBytes;
   const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6, g = lane >> 5, c = lane & 31;
   auto piv_at = [](int j, int piece) { return (j >> 5) * kTileBytes + (piece >> 1) * 1024 + ((piece & 1) * 32 + (j & 31)) * 16; };
-  for (int i = tid; i < npiv * 4; i += kPivotThreads) {
-    const int j = i >> 2, piece = i & 3;               // piece = 2 * half + lane group
-    const int tok = (int)((long)j * n / npiv);
-    *reinterpret_cast<u4 *>(piv + piv_at(j, piece)) = *reinterpret_cast<const u4 *>(sk + (size_t)tok * kSketchBytes + piece * 16);
+  constexpr int kAtOnce = 8;                           // loads of a thread in flight
+  for (int i0 = tid; i0 < npiv * 4; i0 += kAtOnce * kPivotThreads) {
+    u4 v[kAtOnce];
+#pragma unroll
+    for (int q = 0; q < kAtOnce; ++q) {
+      const int i = min(i0 + q * kPivotThreads, npiv * 4 - 1), j = i >> 2, piece = i & 3;   // piece = 2 * half + lane group
+      const int tok = (int)((uint32_t)j * (uint32_t)n / (uint32_t)npiv);   // (below 2^26)
+      v[q] = *reinterpret_cast<const u4 *>(sk + (size_t)tok * kSketchBytes + piece * 16);
+    }
+#pragma unroll
+    for (int q = 0; q < kAtOnce; ++q) {
+      const int i = i0 + q * kPivotThreads;
+      if (i >= npiv * 4) break;
+      // every byte + 8 without carries into the next, 127 + 8 back into the range, then the multiple of 16 below
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const uint32_t sign = v[q][k] & 0x80808080u, up = (v[q][k] & 0x7F7F7F7Fu) + 0x08080808u;
+        v[q][k] = ((up ^ sign) - ((up & ~sign & 0x80808080u) >> 3)) & 0xF0F0F0F0u;
+      }
+      *reinterpret_cast<u4 *>(piv + piv_at(i >> 2, i & 3)) = v[q];
+    }
   }
   for (int i = tid; i < kBuckets; i += kPivotThreads) cnt[i] = 0;
   if (tid < kSketchBytes) sum[tid] = 0;
   if (tid == 0) sum_sq = 0;
-  // the wave's 128 tokens: matrix columns = lanes
-  i4v bf[4][2];
-  int tok[4];
+  // the wave's tokens: matrix columns = lanes
+  i4v bf[kTiles][2];
+  int tok[kTiles];
 #pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    tok[r] = blk * kOrderTokens + wave * 128 + r * 32 + c;
+  for (int r = 0; r < kTiles; ++r) {
+    tok[r] = (blk * (kPivotThreads / kWave) + wave) * (kTiles * kTile) + r * kTile + c;
     const uint8_t *s = sk + (size_t)(tok[r] < n ? tok[r] : n - 1) * kSketchBytes + g * 16;
     bf[r][0] = *reinterpret_cast<const i4v *>(s);
     bf[r][1] = *reinterpret_cast<const i4v *>(s + 32);
@@ -106,7 +129,7 @@ __global__ __launch_bounds__(kPivotThreads, 2) void shallow_pivots(ShallowParams
   // (every block of a problem comes to the same figures)
   const float left = fmaxf((float)sum_sq / (float)nmean - (float)mm, 1.f);
   const bool some = (float)mm > kMeanSome * left, most = (float)mm > kMeanMost * left;
-  const int bits = some ? min(14, max(10, (int)rintf(log2f(kStep * left)))) : 14, mask = -(1 << bits);
+  const int bits = some ? min(14, max(10, (int)rintf(log2f(kStep * left)))) : 14, mask = -(1 << bits), ahead = bits - 4;
   const int off = some ? -(int)((most ? 0.f : norms) + kStepEnd * left) : kStepOffset;
   for (int j = tid; some && j < npiv; j += kPivotThreads) {
     int x = off;
@@ -117,15 +140,16 @@ __global__ __launch_bounds__(kPivotThreads, 2) void shallow_pivots(ShallowParams
 #pragma unroll
       for (int k = 0; k < 4; ++k) x -= __builtin_amdgcn_sdot4(v[k], m[k], 0, false);
     }
-    init[j] = x;
+    const int last = 15 - (((j >> 3) & 3) * 4 + (j & 3));   // 15 less the result register of row j of a tile
+    init[j] = ((x & ~15) | last) + (last << ahead);
     if (most)
 #pragma unroll
-      for (int piece = 0; piece < 4; ++piece) piv[piv_at(j, piece) + 15] = 127;
+      for (int piece = 0; piece < 4; ++piece) piv[piv_at(j, piece) + 15] = 112;
   }
   if (blk == 0 && tid < 2) p.mean[2 * ut + tid] = some ? (uint32_t)mean4[tid] : 0u;
   if (most) {
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
+    for (int r = 0; r < kTiles; ++r) {
       int x = 0;                                       // (a lane has pieces g and g + 2 of the four)
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
@@ -134,30 +158,36 @@ __global__ __launch_bounds__(kPivotThreads, 2) void shallow_pivots(ShallowParams
         for (int k = 0; k < 4; ++k) x = __builtin_amdgcn_sdot4(bf[r][h][k], m[k], x, false);
       }
       x += __shfl_xor(x, 32);
-      const int q = min(508, max(-508, (int)rintf((float)(mm - x) * (1.f / 127.f))));   // dealt out to the four
+      const int q = min(508, max(-508, (int)rintf((float)(mm - x) * (1.f / 112.f))));   // dealt out to the four
       bf[r][0][3] = (bf[r][0][3] & 0x00FFFFFF) | ((q + g) >> 2) << 24;
       bf[r][1][3] = (bf[r][1][3] & 0x00FFFFFF) | ((q + 2 + g) >> 2) << 24;
     }
   }
   __syncthreads();
-  // Per tile of pivots the largest product's step and, in the four bits below it, the first result register that has it; a
-  // later tile only counts if its step is higher.
-  int best[4] = {INT32_MIN, INT32_MIN, INT32_MIN, INT32_MIN}, best_pt[4] = {0, 0, 0, 0};
+  // The largest product and, in the four bits below it, its result register; a later tile of pivots only counts if its step is
+  // higher.
+  int best[kTiles], best_pt[kTiles];
+#pragma unroll
+  for (int r = 0; r < kTiles; ++r) {
+    best[r] = INT32_MIN;
+    best_pt[r] = 0;
+  }
   auto compare = [&](auto first) __attribute__((always_inline)) {   // first(pt): what the products of a pivot tile start at
     for (int pt = 0; pt < npiv / 32; ++pt) {
       const i4v a0 = *reinterpret_cast<const i4v *>(piv + pt * kTileBytes + lane * 16);
       const i4v a1 = *reinterpret_cast<const i4v *>(piv + pt * kTileBytes + 1024 + lane * 16);
       const i16v off4 = first(pt);
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
+      for (int r = 0; r < kTiles; ++r) {
         i16v acc = off4;
         acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(a0, bf[r][0], acc, 0, 0, 0);
         acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(a1, bf[r][1], acc, 0, 0, 0);
-        int m = (acc[0] & mask) | 15;
+        int m = acc[0];
 #pragma unroll
-        for (int v = 1; v < 16; ++v) m = max(m, (acc[v] & mask) | (15 - v));
+        for (int v = 1; v < 16; ++v) m = max(m, acc[v]);
+        m -= (m & 15) << ahead;
         const bool higher = (m & mask) > best[r];
-        best[r] = higher ? m : best[r];
+        best[r] = higher ? m : best[r];                // (no product's step is above the product)
         best_pt[r] = higher ? pt : best_pt[r];
       }
     }
@@ -176,12 +206,12 @@ __global__ __launch_bounds__(kPivotThreads, 2) void shallow_pivots(ShallowParams
   } else {
     i16v x16;
 #pragma unroll
-    for (int v = 0; v < 16; ++v) x16[v] = off;
+    for (int v = 0; v < 16; ++v) x16[v] = off + 15 - v + ((15 - v) << ahead);
     compare([&](int) { return x16; });
   }
   const int near = p.by[ut / p.U] != kBySketch ? INT32_MIN : some ? 1 << bits : kNearStep << 14;
 #pragma unroll
-  for (int r = 0; r < 4; ++r) {
+  for (int r = 0; r < kTiles; ++r) {
     const int own = (best[r] & mask) | (1023 - (best_pt[r] * 32 + mma_row(15 - (best[r] & 15), g)));
     const int o = __shfl_xor(own, 32), top = o > own ? o : own, pivot = 1023 - (top & 1023);
     const int b = top >= near ? kPivots + pivot : pivot;
@@ -213,7 +243,7 @@ __global__ __launch_bounds__(kPivotThreads, 2) void shallow_pivots(ShallowParams
 // cost twice the 26 us that half of them took on 16 problems of 32768 tokens; now 9).
 constexpr int kOrderThreads = 1024;
 
-__global__ __launch_bounds__(kOrderThreads) void shallow_order(ShallowParams p, int nblk) {
+__global__ __launch_bounds__(kOrderThreads) void shallow_order(ShallowParams p, int nblk, int per) {
   __shared__ int cursor[kBuckets];
   __shared__ uint32_t wsum[kOrderThreads / kWave];
   static_assert(kBuckets == 2 * kOrderThreads, "two buckets per thread");
@@ -222,8 +252,8 @@ __global__ __launch_bounds__(kOrderThreads) void shallow_order(ShallowParams p, 
   const int ut = item / nblk, blk = item % nblk, n = p.n;
   const size_t base = (size_t)ut * n;
   const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
-  const int tok = blk * kOrderTokens + tid;
-  const bool on = tid < kOrderTokens && tok < n;
+  const int tok = blk * per + tid;                     // (per: tokens of a block, no more than threads)
+  const bool on = tid < per && tok < n;
   const int b = on ? (int)p.bucket[base + tok] : 0;
   const uint2 total = reinterpret_cast<const uint2 *>(p.total + (size_t)ut * kBuckets)[tid];
   const ushort2 before = reinterpret_cast<const ushort2 *>(p.before + ((size_t)ut * nblk + blk) * kBuckets)[tid];
@@ -1548,13 +1578,18 @@ spindle_status launch_rows(const ShallowParams &p, hipStream_t st) {
 spindle_status launch_tiles(const ShallowParams &p, hipStream_t st) {
   const int n = p.n;
   if (p.scan) {
-    const int nblk = (n + kOrderTokens - 1) / kOrderTokens, nwin = 2 * ((n + 2 * kWindow - 1) / (2 * kWindow));
+    // 1024 tokens per block where that leaves a block for every place on the chip (two per compute unit): what a block does
+    // before and after its products takes 14 of 30 us with 512 tokens.
+    const int per = (long)p.UT * ((n + 2 * kOrderTokens - 1) / (2 * kOrderTokens)) >= 512 ? 2 * kOrderTokens : kOrderTokens;
+    const int nblk = (n + per - 1) / per, nwin = 2 * ((n + 2 * kWindow - 1) / (2 * kWindow));
     int npiv = (n / 16) & ~31;
     if (npiv > kPivots) npiv = kPivots;
     { ProfScope ps("shallow_pivots", st);
-    hipLaunchKernelGGL(shallow_pivots, dim3(xcd_grid((size_t)p.UT * nblk)), dim3(kPivotThreads), 0, st, p, npiv, nblk); }
+    const dim3 pg(xcd_grid((size_t)p.UT * nblk));
+    if (per == kOrderTokens) hipLaunchKernelGGL(shallow_pivots<4>, pg, dim3(kPivotThreads), 0, st, p, npiv, nblk);
+    else hipLaunchKernelGGL(shallow_pivots<8>, pg, dim3(kPivotThreads), 0, st, p, npiv, nblk); }
     { ProfScope ps("shallow_order", st);
-    hipLaunchKernelGGL(shallow_order, dim3(xcd_grid((size_t)p.UT * nblk)), dim3(kOrderThreads), 0, st, p, nblk); }
+    hipLaunchKernelGGL(shallow_order, dim3(xcd_grid((size_t)p.UT * nblk)), dim3(kOrderThreads), 0, st, p, nblk, per); }
     { ProfScope ps("shallow_window", st);
     hipLaunchKernelGGL(shallow_window, dim3(xcd_grid((size_t)p.UT * nwin)), dim3(kWindowThreads), 0, st, p, nwin); }
     const int nitems = scan_blocks(p) / 8;
