@@ -1103,12 +1103,13 @@ __global__ __launch_bounds__(kRefineThreads, 2) void shallow_refine(ShallowParam
 // double precision as the definition says (the pairs wait in LDS for a wave's worth of them).
 //
 // A block takes 4 / kCols neighbouring row tiles and walks over the column tiles that any of them is
-// marked for, kCols at a time: their rows are gathered straight into LDS, two steps ahead of their
+// marked for, kCols at a time: their rows are gathered straight into LDS, ahead of their
 // use, and every wave multiplies one of them with one row tile (held in registers).  kCols = 1: what
 // similar rows have in common is read once for four row tiles; kCols = 4: short problems, where there
-// are too few row tiles to fill the chip.  Bound by the gathered rows (random 256-byte rows, mostly from
-// L2): 0.21 ms for 16 problems of 32768 tokens, 0.19 ms for 128 of 8192 in clusters of 128, three blocks per compute unit
-// (0.31 and 0.25 with two); one wave per row tile with its own gathers took 0.73 and 0.84 ms.
+// are too few row tiles to fill the chip.  Bound by latency (half of a block's 18 us is its lists and first rows, the rest
+// gathered rows, mostly from L2, products and tests), so what counts is blocks per compute unit: LDS and registers
+// allow four with two stages and 28 steps' bits, where three stages and 32 steps allowed three.  16 problems of 32768 tokens
+// 173 -> 146 us, 128 of 8192 in clusters of 128 200 -> 168, 64 of 32768 with half isolated 379 -> 315.
 constexpr int kRowsQueue = 192;                    // waiting pairs per wave
 constexpr int kRowsThreads = 256;
 constexpr int kRowsPitch = kWave + 2;              // result bits of a step, and a word so that one lane's bits of 32 steps are 32 banks
@@ -1117,15 +1118,16 @@ template <int DT, int kCols>
 struct RowsLds {
   static constexpr int kPart = kTile * 256;                              // 32 rows of 128 two-byte elements
   static constexpr int kStage = kCols * kPart * (DT == SPINDLE_F32 ? 2 : 1);
-  static constexpr int kStages = kCols == 1 ? 3 : 2;
-  static constexpr int kBatch = kCols == 1 ? 32 : 16;                    // steps whose result bits a wave keeps
+  static constexpr int kStages = kCols == 1 && DT == SPINDLE_F32 ? 3 : 2;
+  static constexpr int kBatch = kCols > 1 ? 16 : DT == SPINDLE_F32 ? 32 : 28;   // steps whose result bits a wave keeps
   char stage[kStages][kStage];
   float inv[kBatch * kCols][kTile];
   uint16_t tok[kBatch * kCols][kTile];
   uint16_t bits[4][kBatch * kRowsPitch];
   __attribute__((aligned(4))) uint16_t queue[4][kRowsQueue];                                         // at the end: degree << 16 | words of every lane
-  uint16_t tiles[2048];                                                  // column tile | 1 << (11 + row tile of the block)
   int ntiles;
+  __device__ uint16_t *tiles() { return reinterpret_cast<uint16_t *>(this + 1); }  // [T] column tile | 1 << (11 + row tile of the block)
+  static size_t bytes(int T) { return sizeof(RowsLds) + align_up((size_t)T * sizeof(uint16_t), 16); }
 };
 
 // A wave's rows r0 .. r0 + nr - 1 of row tile R from the bits in memory (word t of a row's room: column tile t, written for the
@@ -1208,7 +1210,7 @@ __device__ __forceinline__ void rows_from_memory(const ShallowParams &p, int ut,
 }
 
 template <int DT, int kCols>
-__global__ __launch_bounds__(kRowsThreads, 2) void shallow_rows(ShallowParams p, int nblk) {
+__global__ __launch_bounds__(kRowsThreads, kCols == 1 && DT != SPINDLE_F32 ? 4 : 2) void shallow_rows(ShallowParams p, int nblk) {
   typedef Mma<DT == SPINDLE_BF16 ? SPINDLE_BF16 : SPINDLE_F16> M;
   typedef RowsLds<DT, kCols> L;
   constexpr bool kSplit = DT == SPINDLE_F32;
@@ -1222,7 +1224,7 @@ __global__ __launch_bounds__(kRowsThreads, 2) void shallow_rows(ShallowParams p,
   const int ut = item / nblk, n = p.n, T = p.T, R0 = (item % nblk) * kRT, R = R0 + rt;
   const bool mine = R < T;                             // (the last block's last row tiles may not exist)
   const size_t base = (size_t)ut * n;
-  uint16_t *bits = l.bits[wave], *queue = l.queue[wave];
+  uint16_t *bits = l.bits[wave], *queue = l.queue[wave], *tiles = l.tiles();
   const uint16_t *perm = p.perm + base;
   const float *inv = p.invp + base;
   const float theta = p.theta[ut / p.U];
@@ -1261,10 +1263,10 @@ __global__ __launch_bounds__(kRowsThreads, 2) void shallow_rows(ShallowParams p,
         uint32_t e = (uint32_t)(lane * 32 + t);
 #pragma unroll
         for (int k = 0; k < kRT; ++k) e |= (word[k] >> t & 1u) << (11 + k);
-        l.tiles[at++] = (uint16_t)e;
+        tiles[at++] = (uint16_t)e;
       }
     } else {
-      for (int t = lane; t < T; t += kWave) l.tiles[t] = (uint16_t)(t | ((1 << kRT) - 1) << 11);
+      for (int t = lane; t < T; t += kWave) tiles[t] = (uint16_t)(t | ((1 << kRT) - 1) << 11);
       if (lane == 0) l.ntiles = T;
     }
   }
@@ -1313,7 +1315,7 @@ __global__ __launch_bounds__(kRowsThreads, 2) void shallow_rows(ShallowParams p,
     const int t0 = s0 * kCols, nt = min(L::kBatch * kCols, ntiles - t0);
     if (batch > 0) __syncthreads();                    // the batch before is done with these
     for (int i = tid; i < nt * kTile; i += kRowsThreads) {
-      const int col = (int)(l.tiles[t0 + (i >> 5)] & 2047u) * kTile + (i & 31);
+      const int col = (int)(tiles[t0 + (i >> 5)] & 2047u) * kTile + (i & 31);
       l.tok[i >> 5][i & 31] = perm[col < n ? col : n - 1];
       l.inv[i >> 5][i & 31] = col < n ? inv[col] : 0.f;
     }
@@ -1343,7 +1345,7 @@ __global__ __launch_bounds__(kRowsThreads, 2) void shallow_rows(ShallowParams p,
       __syncthreads();
       if (s + L::kStages - 1 < ns) fetch(s + L::kStages - 1);
       const int i = s * kCols + member;                // this wave's tile of the batch
-      const uint32_t entry = i < nt ? (uint32_t)__builtin_amdgcn_readfirstlane((int)l.tiles[t0 + i]) : 0u;
+      const uint32_t entry = i < nt ? (uint32_t)__builtin_amdgcn_readfirstlane((int)tiles[t0 + i]) : 0u;
       if (!(entry >> (11 + rt) & 1u)) {                // wave-uniform
         bits[s * kRowsPitch + lane] = 0;
         continue;
@@ -1429,7 +1431,7 @@ __global__ __launch_bounds__(kRowsThreads, 2) void shallow_rows(ShallowParams p,
         const int slot = (int)(e >> 10), ln = (int)((e >> 4) & 63), v = (int)(e & 15);
         const int a = (int)perm[R * kTile + (ln & 31)], b = (int)l.tok[slot * kCols + member][16 * (ln >> 5) + v];
         ++ndecided;
-        if (cos64<DT, 4>(p, ut, a, b) > (double)theta) {
+        if (cos64<DT, 8>(p, ut, a, b) > (double)theta) {
           const int at = slot * kRowsPitch + ln;
           atomicOr(reinterpret_cast<uint32_t *>(bits) + (at >> 1), 1u << (v + 16 * (at & 1)));
         }
@@ -1440,8 +1442,8 @@ __global__ __launch_bounds__(kRowsThreads, 2) void shallow_rows(ShallowParams p,
     if (nbatch == 1) break;
     constexpr int kRowsAtOnce = kWave / L::kBatch;     // lanes along the steps: runs of neighbouring tiles are runs of memory
     const int ls = lane % L::kBatch, li = ls * kCols + member;
-    if (ls < ns && li < nt) {
-      const int t = (int)(l.tiles[t0 + li] & 2047u);
+    if (ls < ns && li < nt && lane < kRowsAtOnce * L::kBatch) {
+      const int t = (int)(tiles[t0 + li] & 2047u);
       for (int r = lane / L::kBatch; r < rows_here; r += kRowsAtOnce)
         lists[(size_t)(R * kTile + r) * p.list_row + t] =
             (uint32_t)bits[ls * kRowsPitch + r] | (uint32_t)bits[ls * kRowsPitch + 32 + r] << 16;
@@ -1460,8 +1462,8 @@ __global__ __launch_bounds__(kRowsThreads, 2) void shallow_rows(ShallowParams p,
   }
   if (nbatch > 1) {
     __syncthreads();                                   // (and the words in memory are every wave's to read)
-    if (ntiles <= 8 * kWave) rows_from_memory<4, 8>(p, ut, R, member * (kTile / kCols), kTile / kCols, rows_here, l.tiles, ntiles);
-    else rows_from_memory<1, 32>(p, ut, R, member * (kTile / kCols), kTile / kCols, rows_here, l.tiles, ntiles);
+    if (ntiles <= 8 * kWave) rows_from_memory<4, 8>(p, ut, R, member * (kTile / kCols), kTile / kCols, rows_here, tiles, ntiles);
+    else rows_from_memory<1, 32>(p, ut, R, member * (kTile / kCols), kTile / kCols, rows_here, tiles, ntiles);
     return;
   }
   int deg = 0, words = 0;
@@ -1508,7 +1510,7 @@ __global__ __launch_bounds__(kRowsThreads, 2) void shallow_rows(ShallowParams p,
   for (int s = 0; s < nall; ++s) {
     const int i = s * kCols + member;
     if (i >= ntiles) break;
-    const uint32_t m = bits[s * kRowsPitch + lane], half = 2u * (l.tiles[i] & 2047u) + g;
+    const uint32_t m = bits[s * kRowsPitch + lane], half = 2u * (tiles[i] & 2047u) + g;
     if (dense) {
       if (row_on) reinterpret_cast<uint16_t *>(out)[half] = (uint16_t)m;
     } else if (m) {
@@ -1562,10 +1564,11 @@ template <int DT, int kCols>
 spindle_status launch_rows(const ShallowParams &p, hipStream_t st) {
   constexpr int kRT = 4 / kCols;
   static LdsLimit lim;
-  if (spindle_status e = allow_lds(lim, reinterpret_cast<const void *>(&shallow_rows<DT, kCols>), sizeof(RowsLds<DT, kCols>))) return e;
+  if (spindle_status e = allow_lds(lim, reinterpret_cast<const void *>(&shallow_rows<DT, kCols>), RowsLds<DT, kCols>::bytes(2048))) return e;
   const int nblk = (p.T + kRT - 1) / kRT;
+  const size_t lds = RowsLds<DT, kCols>::bytes(p.T);
   ProfScope ps("shallow_rows", st, most_by(p) == kByNone);
-  hipLaunchKernelGGL((shallow_rows<DT, kCols>), dim3(xcd_grid((size_t)p.UT * nblk)), dim3(kRowsThreads), sizeof(RowsLds<DT, kCols>),
+  hipLaunchKernelGGL((shallow_rows<DT, kCols>), dim3(xcd_grid((size_t)p.UT * nblk)), dim3(kRowsThreads), lds,
                      st, p, nblk);
   return SPINDLE_OK;
 }

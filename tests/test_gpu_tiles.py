@@ -34,9 +34,10 @@ def test_tile_pairs_excluded_by_balls(oracle, dtype, H, l, centroids, noise, dri
     parity.check_shallow_layer(oracle, L, units=[(0, 0), (0, H // 2), (0, H - 1)], debug=False)
 
 
-@pytest.mark.parametrize("H,l", [(1, 2304), (8, 2016), (8, 2048), (16, 1000), (17, 960)])
+@pytest.mark.parametrize("H,l", [(1, 2304), (8, 2016), (8, 2048), (16, 1000), (17, 960), (19, 896), (18, 928)])
 def test_block_shapes_of_the_list_kernel(oracle, H, l):
-    # 1024 row tiles over all problems of the call is where a block starts to take four of them
+    # 1024 row tiles over all problems of the call is where a block starts to take four of them; 28 column tiles are what
+    # it then keeps the bits of
     L = wl.small_random(62, "f16", B=1, H=H, l=l, lw=1, cap=l, n_centroids=20, noise_frac=0.2)
     units = [(0, h) for h in sorted({0, H // 2, H - 1})]
     parity.check_shallow_layer(oracle, L, units=units, debug=False)
