@@ -5,12 +5,12 @@
 //   deep_accumulate   merges the per-chunk statistics into max + log2(sum) per query row,
 //                     recomputes the logits, forms softmax weights, sums them over the window
 //                     queries and the GQA group (Eq. 2, 3)
-//   deep_select       max-pool, 4096-bin histogram of the pooled scores over many workgroups;
-//                     the last workgroup of a unit finds the k-th largest score from the
-//                     histogram and the few scores that share its bin, then writes the kept
-//                     positions in order (Eq. 7)
-//   deep_select_unit  the same by one workgroup per unit, scores and keys in LDS, for shorter contexts
-//   deep_gather       K_out = K[kept], V_out = V[kept]
+//   deep_select       max-pool, 4096-bin histogram of the pooled scores over many workgroups
+//   deep_finish       the k-th largest score from the histogram and the few scores that share its bin,
+//                     the kept positions in order (Eq. 7), K_out = K[kept], V_out = V[kept]
+//   deep_select_unit, deep_gather
+//                     the same for shorter contexts: one workgroup per unit, scores and keys in LDS, and
+//                     the copies of the rows
 //
 // Both passes over K stream stages of up to 64 KiB of keys through LDS with direct global->LDS loads
 // (two stages, the next one in flight while the current one is multiplied); the 16-byte pieces
@@ -132,7 +132,6 @@ struct DeepParams {
   float *scores;       // [U][spitch] group-averaged accumulated attention
   int spitch;          // l_c rounded up to 4
   int *hist;           // [U][kBins] cleared here for deep_select (NULL: not needed)
-  int *done;           // [U]
   int l, lc, lw, hn, R, Rpad, nchunks;
   int stages;          // stages per block
   KvLayout lay;        // rows of K
@@ -173,7 +172,6 @@ __global__ __launch_bounds__((Geo<DT, WR, KEYS>::kThreads)) void deep_stats(Deep
   const int wr = wave % WR, wk = wave / WR;
   if (chunk == 0 && p.hist) {                          // counters of this unit's selection
     for (int i = threadIdx.x; i < kBins; i += S::kThreads) p.hist[(size_t)u * kBins + i] = 0;
-    if (threadIdx.x == 0) p.done[u] = 0;
   }
   const int key_begin = chunk * p.stages * S::kStageKeys;
   int nst = (p.l - key_begin + S::kStageKeys - 1) / S::kStageKeys;
@@ -421,11 +419,18 @@ struct SelectParams {
   uint32_t *pooled;      // [U][lc] pooled scores as order-preserving keys
   float *scores_out;     // optional [U][lc]
   int *hist;             // [U][kBins], zero on entry
-  int *done;             // [U], zero on entry
   const int32_t *budgets;
   int32_t *kept;         // [U][out_stride]
   int l, lc, lw, pool, budget, out_stride, nseg;
   int spitch;            // floats per unit of `scores`, a multiple of 4
+};
+
+struct GatherParams {
+  const char *K, *V;
+  char *Ko, *Vo;
+  const int32_t *kept;
+  int l, out_stride, row_bytes;
+  KvLayout lay;        // rows of K and V
 };
 
 // How many context tokens unit u keeps.
@@ -448,21 +453,10 @@ __device__ __forceinline__ uint32_t orderable(float f) {
   return b ^ ((b >> 31) ? 0xFFFFFFFFu : 0x80000000u);
 }
 
-// Stores and loads that workgroups of one launch use to hand data to each other: performed at
-// device scope (they go through to, and come from, memory that every compute unit sees), so
-// that no cache has to be written back or invalidated as a fence would do; the writer waits for
-// its stores (s_waitcnt vmcnt(0)) before it takes its ticket.
-__device__ __forceinline__ void store_shared(uint32_t *ptr, uint32_t v) {
-  __hip_atomic_store(ptr, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ uint32_t load_shared(const uint32_t *ptr) {
-  return __hip_atomic_load(ptr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
 // Counts, from the top, the digits of the keys `src[0 .. nsrc)` that match `prefix` above
 // `bits_left`, and narrows (prefix, krem) by one digit of width w: afterwards the krem-th
 // largest matching key still matches.  All threads of the block call it with the same arguments.
-__device__ void radix_step(const uint32_t *src, int nsrc, bool other_groups_wrote, uint32_t &prefix, int &krem, int &bits_left, int *hist,
+__device__ void radix_step(const uint32_t *src, int nsrc, uint32_t &prefix, int &krem, int &bits_left, int *hist,
                            uint32_t *sh_prefix, int *sh_krem) {
   const int tid = threadIdx.x, lane = lane_id();
   const int w = bits_left < 8 ? bits_left : 8, shift = bits_left - w;
@@ -475,7 +469,7 @@ __device__ void radix_step(const uint32_t *src, int nsrc, bool other_groups_wrot
 #pragma unroll
     for (int q = 0; q < kAtOnce; ++q) {
       const int a = a0 + q * kSelThreads + tid;
-      x[q] = a < nsrc ? (other_groups_wrote ? load_shared(src + a) : src[a]) : 0u;
+      x[q] = a < nsrc ? src[a] : 0u;
     }
 #pragma unroll
     for (int q = 0; q < kAtOnce; ++q) {
@@ -527,8 +521,8 @@ __device__ void radix_step(const uint32_t *src, int nsrc, bool other_groups_wrot
 // of its bin by comparing all of them, ordered compaction.
 // Bound by latency and by the instructions of one compute unit; loops stay rolled, since a cold kernel also waits for
 // its code (36 KB of it, unrolled with the keys in registers: 1.5 to 3 us more).  The segments of a unit over several
-// workgroups (deep_select) take 16 us for a unit of 480 positions, 22 for eight of 4064, 66 for 192 of 8160 and 24 for eight
-// of 32704; this 7, 10, 15 and 27.
+// workgroups (deep_select and deep_finish, which copies the rows as well) against this and deep_gather, the eviction call, us:
+// one unit of 480 positions 23 and 19, eight of 4064 32 and 25, of 8160 38 and 32, of 16352 44 and 43, 192 of 8160 269 and 241.
 constexpr int kUnitMax = 16384, kUnitRadius = 8;
 constexpr int kUnitStep = 4 * kSelThreads;             // positions of the workgroup per step
 constexpr int kUnitLoads = kUnitMax / kUnitStep;
@@ -728,7 +722,7 @@ __global__ __launch_bounds__(kSelThreads) void deep_select_unit(SelectParams p) 
     krem = sh_krem;
   } else {
     int bits_left = 20;
-    while (bits_left > 0) radix_step(keys, kWaves * run, false, prefix, krem, bits_left, hist256, &sh_prefix, &sh_krem);
+    while (bits_left > 0) radix_step(keys, kWaves * run, prefix, krem, bits_left, hist256, &sh_prefix, &sh_krem);
   }
 
   // ordered compaction: everything above the threshold, then the first `krem` equal to it; both counts in one word
@@ -772,25 +766,18 @@ __global__ __launch_bounds__(kSelThreads) void deep_select_unit(SelectParams p) 
   }
 }
 
-// Units of more than kUnitMax context positions or pooled over more than 2 kUnitRadius + 1 of them.
-// Grid (segments, units).  Every workgroup pools its segment of the raw scores, stores the
-// pooled scores as keys and adds its 4096-bin histogram to the unit's.  The workgroup that
-// finishes last for a unit carries on alone: threshold bin from the histogram, exact value of
-// the k-th largest key among the keys of that bin, ordered compaction of the unit.
+// Units of more than kUnitMax context positions or pooled over more than 2 kUnitRadius + 1 of them, grid (segments, units)
+// of two launches.  In the first every workgroup pools its segment of the raw scores, stores the pooled scores as keys and
+// adds its 4096-bin histogram to the unit's.
 __global__ __launch_bounds__(kSelThreads) void deep_select(SelectParams p) {
   __shared__ float rawl[kSegLen + 2 * kHaloMax];
   __shared__ int hist[kBins];
-  __shared__ uint32_t cand[kCandMax];
-  __shared__ int wsum[kSelThreads / 64][2];
-  __shared__ uint32_t sh_prefix;
-  __shared__ int sh_krem, sh_last, sh_ncand;
-  const int seg = blockIdx.x, u = blockIdx.y, tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
+  const int seg = blockIdx.x, u = blockIdx.y, tid = threadIdx.x, lane = lane_id();
   const int lc = p.lc;
   const float *raw = p.scores + (size_t)u * p.spitch;
   uint32_t *pooled = p.pooled + (size_t)u * lc;
   int *ghist = p.hist + (size_t)u * kBins;
 
-  // ---- every workgroup: pooling and histogram of its segment
   for (int i = tid; i < kBins; i += kSelThreads) hist[i] = 0;
   const int a_begin = seg * kSegLen;
   const int a_end = a_begin + kSegLen < lc ? a_begin + kSegLen : lc;
@@ -807,7 +794,7 @@ __global__ __launch_bounds__(kSelThreads) void deep_select(SelectParams p) {
     if (in_lds) for (int j = lo; j <= hi; ++j) mx = fmaxf(mx, rawl[j - h_begin]);
     else for (int j = lo; j <= hi; ++j) mx = fmaxf(mx, raw[j]);
     const uint32_t x = orderable(mx);
-    store_shared(pooled + a, x);
+    pooled[a] = x;
     if (p.scores_out) p.scores_out[(size_t)u * lc + a] = mx;
     const int d = (int)(x >> 20);
     const int d0 = __builtin_amdgcn_readfirstlane(d);
@@ -820,140 +807,195 @@ __global__ __launch_bounds__(kSelThreads) void deep_select(SelectParams p) {
     const int v = hist[i];
     if (v) __hip_atomic_fetch_add(&ghist[i], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  __builtin_amdgcn_s_waitcnt(0x0F70);                  // vmcnt(0): this thread's keys and counts have arrived
-  __syncthreads();
-  if (tid == 0) sh_last = __hip_atomic_fetch_add(&p.done[u], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == p.nseg - 1;
-  __syncthreads();
-  if (!sh_last) return;
+}
 
-  // ---- the last workgroup of the unit
+// Every workgroup works out what the whole unit's selection comes to, threshold bin from the histogram, exact value of the
+// k-th largest key among the keys of that bin, what is kept in front of its segment, then writes the kept positions of its own
+// segment and copies their rows of K and V.  Bound by latency, and doing the same in all workgroups of a unit takes no longer
+// than in one: eight units of 32704 positions 24 us where the workgroup that was last to pool did the rest of its unit
+// alone, and 5 for a launch that copied the rows; now 5 and 17.
+__global__ __launch_bounds__(kSelThreads) void deep_finish(SelectParams p, GatherParams q) {
+  __shared__ int hist[256];
+  __shared__ __attribute__((aligned(16))) uint32_t cand[kCandMax];
+  __shared__ int wsum[kSelThreads / 64];
+  __shared__ int front[2], here[kSelThreads / 64];
+  __shared__ uint32_t sh_prefix;
+  __shared__ int sh_krem, sh_ncand;
+  const int seg = blockIdx.x, u = blockIdx.y, tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
+  const int lc = p.lc;
+  const uint32_t *pooled = p.pooled + (size_t)u * lc;
+  const int *ghist = p.hist + (size_t)u * kBins;
   int32_t *kept = p.kept + (size_t)u * p.out_stride;
   const int k = kept_context(p, u);
+  const int a_begin = seg * kSegLen, a_end = min(lc, a_begin + kSegLen);
 
   constexpr int kWaves = kSelThreads / 64;
   constexpr int kBatch = 32;
   const int run = (((lc + kWaves - 1) / kWaves) + 63) & ~63;      // positions per wave
   const int w0 = wave * run, w1 = w0 + run < lc ? w0 + run : lc;
   const bool one_trip = run <= 64 * kBatch;
-  const unsigned long long below = (1ull << lane) - 1ull;
   uint32_t x[kBatch];
   auto load_keys = [&](int b0) {
 #pragma unroll
     for (int i = 0; i < kBatch; ++i) {
       const int a = b0 + 64 * i + lane;
-      x[i] = a < w1 ? load_shared(pooled + a) : 0u;
+      x[i] = a < w1 ? pooled[a] : 0u;
     }
   };
   uint32_t prefix = 0;                                 // key of the k-th largest pooled score
   int krem = k;                                        // how many keys equal to it are taken
+  int nkept = 0;                                       // positions of the segment that are kept, their places in `mine`
+  int first = 0;                                       // kept positions in front of the segment
+  uint16_t *mine = reinterpret_cast<uint16_t *>(cand); // [kSegLen], less a_begin
   if (k > 0 && k < lc) {
     if (one_trip) load_keys(w0);
-    // threshold bin: thread t owns bins 4t .. 4t+3, counts from the top
+    // threshold bin: thread t owns four bins, from the top, so that counts add up along the threads
     {
-      int h[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) h[j] = (int)load_shared(reinterpret_cast<const uint32_t *>(ghist) + 4 * tid + j);
-      const int mine = h[0] + h[1] + h[2] + h[3];
-      int above = mine;                                // inclusive sum over the higher lanes of the wave
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const int up = __shfl_down(above, o);
-        if (lane + o < 64) above += up;
-      }
-      if (lane == 0) wsum[wave][0] = above;            // total of the wave
+      const int bin0 = kBins - 4 - 4 * tid;
+      const int4 h = *reinterpret_cast<const int4 *>(ghist + bin0);
+      const int hh[4] = {h.w, h.z, h.y, h.x}, own = h.x + h.y + h.z + h.w, incl = lanes_up_to(own);
+      if (lane == 63) wsum[wave] = incl;
       __syncthreads();
-      above -= mine;
-      for (int w2 = wave + 1; w2 < kSelThreads / 64; ++w2) above += wsum[w2][0];
-      int seen = above;
+      int seen = incl - own;
 #pragma unroll
-      for (int j = 3; j >= 0; --j) {
-        if (seen < k && k <= seen + h[j]) {
-          sh_prefix = (uint32_t)(4 * tid + j) << 20;
+      for (int w = 0; w < kWaves; ++w) seen += w < wave ? wsum[w] : 0;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        if (seen < k && k <= seen + hh[j]) {
+          sh_prefix = (uint32_t)(bin0 + 3 - j) << 20;
           sh_krem = k - seen;
         }
-        seen += h[j];
+        seen += hh[j];
       }
-      if (tid == 0) sh_ncand = 0;
+      if (tid == 0) sh_ncand = front[0] = front[1] = 0;
       __syncthreads();
       prefix = sh_prefix;
       krem = sh_krem;
     }
-    // The unit's keys, dealt to the waves in contiguous runs (the order of the compaction below),
+    // The unit's keys, dealt to the waves in contiguous runs,
     // thirty-two 64-position steps per lane and trip, all loads of a trip in flight together.  A
-    // unit of up to 32768 positions is one trip: its keys stay in registers for all three uses.
+    // unit of up to 32768 positions is one trip: its keys stay in registers for both uses.
     // First use: the keys of the threshold's bin, ranked in LDS when they fit (a few hundred as a
     // rule), else where they are.
     for (int b0 = w0; b0 < w1; b0 += 64 * kBatch) {
       if (!one_trip) load_keys(b0);
+      int own = 0;                                     // (keys past the end are 0, in the lowest bin, which no score has)
 #pragma unroll
-      for (int i = 0; i < kBatch; ++i) {
-        const int a = b0 + 64 * i + lane;
-        const bool in = a < w1 && (x[i] >> 20) == (prefix >> 20);
-        const unsigned long long mk = __ballot(in);
-        if (mk) {                                      // wave-uniform
-          int at = 0;
-          if (lane == __builtin_ctzll(mk)) at = atomicAdd(&sh_ncand, __popcll(mk));
-          at = __shfl(at, __builtin_ctzll(mk)) + __popcll(mk & below);
-          if (in && at < kCandMax) cand[at] = x[i];
-        }
-      }
+      for (int i = 0; i < kBatch; ++i) own += x[i] >> 20 == prefix >> 20;
+      const int incl = lanes_up_to(own);
+      int at = 0;
+      if (lane == 63 && incl) at = atomicAdd(&sh_ncand, incl);
+      at = __builtin_amdgcn_readlane(at, 63) + incl - own;
+      if (own)
+#pragma unroll
+        for (int i = 0; i < kBatch; ++i)
+          if (x[i] >> 20 == prefix >> 20) {
+            if (at < kCandMax) cand[at] = x[i];
+            ++at;
+          }
     }
     __syncthreads();
     const int ncand = sh_ncand;
     const uint32_t *src = ncand <= kCandMax ? cand : pooled;
     const int nsrc = ncand <= kCandMax ? ncand : lc;
     int bits_left = 20;
-    while (bits_left > 0) radix_step(src, nsrc, ncand > kCandMax, prefix, krem, bits_left, hist, &sh_prefix, &sh_krem);
-  }
-  // ordered compaction: everything above the threshold, then the first `krem` equal to it.
-  // Ranks within a 64-position step come from ballots, the offset of the wave from a count pass
-  // and a scan over the waves.
-  if (k >= lc) {
-    for (int a = tid; a < lc; a += kSelThreads) kept[a] = a;
-  } else if (k > 0) {
-    int ngt = 0, neq = 0;                              // wave-uniform
-    for (int b0 = w0; b0 < w1; b0 += 64 * kBatch) {
-      if (!one_trip) load_keys(b0);
+    while (bits_left > 0) radix_step(src, nsrc, prefix, krem, bits_left, hist, &sh_prefix, &sh_krem);
+    // what is kept in front of the segment: everything above the threshold, the first `krem` equal to it
+    if (w0 < a_begin) {
+      int ngt = 0, neq = 0;
+      for (int b0 = w0; b0 < min(w1, a_begin); b0 += 64 * kBatch) {
+        if (!one_trip) load_keys(b0);
 #pragma unroll
-      for (int i = 0; i < kBatch; ++i) {
-        const int a = b0 + 64 * i + lane;
-        ngt += __popcll(__ballot(a < w1 && x[i] > prefix));
-        neq += __popcll(__ballot(a < w1 && x[i] == prefix));
+        for (int i = 0; i < kBatch; ++i) {
+          const int a = b0 + 64 * i + lane;
+          ngt += a < min(w1, a_begin) && x[i] > prefix;
+          neq += a < min(w1, a_begin) && x[i] == prefix;
+        }
+      }
+      ngt = lanes_up_to(ngt);
+      neq = lanes_up_to(neq);
+      if (lane == 63) {
+        atomicAdd(&front[0], ngt);
+        atomicAdd(&front[1], neq);
       }
     }
-    __syncthreads();                                   // wsum was read above
-    if (lane == 0) { wsum[wave][0] = ngt; wsum[wave][1] = neq; }
+    // ordered compaction of the segment, two neighbouring positions per thread
+    static_assert(kSegLen == 2 * kSelThreads, "two positions per thread");
+    const int a = a_begin + 2 * tid;
+    const uint32_t x0 = a < a_end ? pooled[a] : 0u, x1 = a + 1 < a_end ? pooled[a + 1] : 0u;
+    // (counts of both kinds in one word; an absent position counts as neither)
+    const int c0 = a < a_end ? (x0 > prefix ? 1 << 16 : 0) + (x0 == prefix) : 0;
+    const int c1 = a + 1 < a_end ? (x1 > prefix ? 1 << 16 : 0) + (x1 == prefix) : 0;
+    const int incl = lanes_up_to(c0 + c1);
+    if (lane == 63) here[wave] = incl;
     __syncthreads();
-    int gt_seen = 0, eq_seen = 0;
-    for (int w = 0; w < wave; ++w) { gt_seen += wsum[w][0]; eq_seen += wsum[w][1]; }
-    for (int b0 = w0; b0 < w1; b0 += 64 * kBatch) {
-      if (!one_trip) load_keys(b0);
+    int at = incl - c0 - c1;
 #pragma unroll
-      for (int i = 0; i < kBatch; ++i) {
-        const int a = b0 + 64 * i + lane;
-        const bool gt = a < w1 && x[i] > prefix, eq = a < w1 && x[i] == prefix;
-        const unsigned long long mgt = __ballot(gt), meq = __ballot(eq);
-        const int gt_before = gt_seen + __popcll(mgt & below), eq_before = eq_seen + __popcll(meq & below);
-        if (gt) kept[gt_before + (eq_before < krem ? eq_before : krem)] = a;
-        else if (eq && eq_before < krem) kept[gt_before + eq_before] = a;
-        gt_seen += __popcll(mgt);
-        eq_seen += __popcll(meq);
+    for (int w = 0; w < kWaves; ++w) {
+      at += w < wave ? here[w] : 0;
+      nkept += here[w];
+    }
+    const int gt_front = front[0], eq_front = front[1], left = max(0, krem - eq_front);   // equal ones still taken
+    first = gt_front + min(eq_front, krem);
+    nkept = (nkept >> 16) + min(nkept & 0xFFFF, left);
+    auto place = [&](int before, int own, int pos) __attribute__((always_inline)) {
+      const int gt = before >> 16, eq = before & 0xFFFF;
+      if (own >> 16 || (own && eq < left)) {
+        const int to = gt + min(eq, left);
+        mine[to] = (uint16_t)(pos - a_begin);
+        kept[first + to] = pos;
       }
+    };
+    place(at, c0, a);
+    place(at + c0, c1, a + 1);
+  } else if (k > 0) {
+    first = a_begin;
+    nkept = max(0, a_end - a_begin);
+    for (int i = tid; i < nkept; i += kSelThreads) {
+      mine[i] = (uint16_t)i;
+      kept[a_begin + i] = a_begin + i;
     }
   }
-  for (int b = tid; b < p.lw; b += kSelThreads) kept[k + b] = lc + b;
-  for (int j = k + p.lw + tid; j < p.out_stride; j += kSelThreads) kept[j] = -1;
+  __syncthreads();
+  // their rows, and of the window and the padding behind the kept positions the segment's share
+  const int tpr = q.row_bytes / 16, per = kSelThreads / tpr, t = tid % tpr;
+  const size_t in = kv_unit_offset(q.lay, u) + t * 16, out = (size_t)u * p.out_stride * q.row_bytes + t * 16;
+  const int behind = p.out_stride - k, share = (behind + p.nseg - 1) / p.nseg;
+  const int nbehind = max(0, min(behind - seg * share, share));
+  for (int i0 = tid / tpr; i0 < nkept + nbehind; i0 += 2 * per) {
+    u4 kv[2], vv[2];
+    int to[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int i = i0 + j * per;
+      to[j] = -1;
+      kv[j] = vv[j] = u4{0, 0, 0, 0};
+      if (i >= nkept + nbehind) continue;
+      int idx;
+      if (i < nkept) {
+        to[j] = first + i;
+        idx = a_begin + (int)mine[i];
+      } else {
+        const int b = seg * share + i - nkept;         // of the window, then of the padding
+        to[j] = k + b;
+        idx = b < p.lw ? lc + b : -1;
+        if (t == 0) kept[to[j]] = idx;
+      }
+      if (idx >= 0) {
+        kv[j] = *reinterpret_cast<const u4 *>(q.K + in + (size_t)idx * (size_t)q.lay.st);
+        if (q.V) vv[j] = *reinterpret_cast<const u4 *>(q.V + in + (size_t)idx * (size_t)q.lay.st);
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+      if (to[j] >= 0) {
+        *reinterpret_cast<u4 *>(q.Ko + out + (size_t)to[j] * q.row_bytes) = kv[j];
+        if (q.Vo) *reinterpret_cast<u4 *>(q.Vo + out + (size_t)to[j] * q.row_bytes) = vv[j];
+      }
+  }
 }
 
 // ---------------------------------------------------------------- gather
-struct GatherParams {
-  const char *K, *V;
-  char *Ko, *Vo;
-  const int32_t *kept;
-  int l, out_stride, row_bytes;
-  KvLayout lay;        // rows of K and V
-};
-
 __global__ __launch_bounds__(256) void deep_gather(GatherParams p) {
   const int tpr = p.row_bytes / 16;
   const int rows_per_block = 256 / tpr;
@@ -978,7 +1020,7 @@ struct DeepLayout {
   float2 *partial;
   float *scores;
   uint32_t *pooled;
-  int *hist, *done;
+  int *hist;
   int keys, stages, nchunks;   // keys per stage, stages per block
   size_t bytes;
 };
@@ -1025,7 +1067,6 @@ DeepLayout deep_layout(void *ws, int U, int l, int lw, int Rpad, int dtype) {
   L.scores = cv.take<float>((size_t)U * (lc > 0 ? (lc + 3) & ~3 : 4));
   L.pooled = cv.take<uint32_t>((size_t)U * (lc > 0 ? lc : 1));
   L.hist = cv.take<int>((size_t)U * kBins);
-  L.done = cv.take<int>((size_t)U);
   L.bytes = cv.total();
   return L;
 }
@@ -1130,7 +1171,6 @@ extern "C" spindle_status spindle_compress_deep(const spindle_kv_desc *desc, con
   p.spitch = (lc + 3) & ~3;
   const bool by_unit = lc > 0 && lc <= kUnitMax && pool_kernel <= 2 * kUnitRadius + 1;
   p.hist = by_unit ? nullptr : L.hist;
-  p.done = L.done;
   p.l = l; p.lc = lc; p.lw = lw; p.hn = desc->group_size; p.R = R; p.Rpad = Rpad;
   p.stages = L.stages;
   p.nchunks = L.nchunks;
@@ -1144,28 +1184,31 @@ extern "C" spindle_status spindle_compress_deep(const spindle_kv_desc *desc, con
 
   SelectParams sp;
   sp.scores = L.scores; sp.pooled = L.pooled; sp.scores_out = scores_out;
-  sp.hist = L.hist; sp.done = L.done;
+  sp.hist = L.hist;
   sp.budgets = budgets; sp.kept = kept_idx;
   sp.l = l; sp.lc = lc; sp.lw = lw; sp.pool = pool_kernel; sp.budget = budget; sp.out_stride = out_stride;
   sp.spitch = p.spitch;
   sp.nseg = lc > 0 ? (lc + kSegLen - 1) / kSegLen : 1;
-  {
-    static LdsLimit lim;
-    if ((s = allow_lds(lim, reinterpret_cast<const void *>(&deep_select_unit), unit_lds(kUnitMax))) != SPINDLE_OK) return s;
-    ProfScope ps("deep_select", st);
-    if (by_unit) hipLaunchKernelGGL(deep_select_unit, dim3(U), dim3(kSelThreads), unit_lds(lc), st, sp);
-    else hipLaunchKernelGGL(deep_select, dim3(sp.nseg, U), dim3(kSelThreads), 0, st, sp);
-  }
-
   GatherParams gp;
   gp.K = static_cast<const char *>(K); gp.V = static_cast<const char *>(V);
   gp.Ko = static_cast<char *>(K_out); gp.Vo = static_cast<char *>(V_out);
   gp.kept = kept_idx; gp.l = l; gp.out_stride = out_stride;
   gp.row_bytes = kHeadDim * dtype_bytes(desc->dtype);
   gp.lay = lay;
-  const int rows_per_block = 256 / (gp.row_bytes / 16);
-  { ProfScope ps("deep_gather", st);
-  hipLaunchKernelGGL(deep_gather, dim3((out_stride + rows_per_block - 1) / rows_per_block, U), dim3(256), 0, st, gp); }
+  if (by_unit) {
+    static LdsLimit lim;
+    if ((s = allow_lds(lim, reinterpret_cast<const void *>(&deep_select_unit), unit_lds(kUnitMax))) != SPINDLE_OK) return s;
+    { ProfScope ps("deep_select", st);
+    hipLaunchKernelGGL(deep_select_unit, dim3(U), dim3(kSelThreads), unit_lds(lc), st, sp); }
+    const int rows_per_block = 256 / (gp.row_bytes / 16);
+    ProfScope ps("deep_gather", st);
+    hipLaunchKernelGGL(deep_gather, dim3((out_stride + rows_per_block - 1) / rows_per_block, U), dim3(256), 0, st, gp);
+  } else {
+    { ProfScope ps("deep_select", st);
+    hipLaunchKernelGGL(deep_select, dim3(sp.nseg, U), dim3(kSelThreads), 0, st, sp); }
+    ProfScope ps("deep_finish", st);
+    hipLaunchKernelGGL(deep_finish, dim3(sp.nseg, U), dim3(kSelThreads), 0, st, sp, gp);
+  }
   SPINDLE_HIP(hipGetLastError());
   return SPINDLE_OK;
 }
