@@ -373,7 +373,7 @@ spindle_status spindle_reserve_ratio(int64_t kept_tokens, int64_t total_tokens, 
 /*
  * enable = 1: every kernel the library launches from now on is bracketed by a pair of HIP
  * events recorded on the stream it is launched on; enable = 2: only the kernel of
- * spindle_compress_shallow that goes over all pairs of tokens is, one record per call: "shallow_scan";
+ * spindle_compress_shallow that finds the pairs of tokens to look at is, one record per call: "shallow_scan";
  * for thresholds below 0.7 on K and V "shallow_refine"; for short problems and thresholds below 0.3
  * "shallow_rows"; enable = 0 stops recording.  An event between two kernels of a stream costs about 10 us of idle time on the GPU, so mode 1 lengthens a
  * step by some 5 % and is meant for breakdowns, mode 2 (two events per call) for measuring the

@@ -129,7 +129,8 @@ __device__ __forceinline__ int seg_sum(int v) {             // over a segment, r
 
 // Largest of the values in memory that the words of a row select (and m), for a segment whose lanes have a word each: a
 // quad takes its four words one after the other, each lane 16 of the 64 bytes, so that a load of the wave touches 16 lines
-// and not 64 (what bounded the one-hop maxima of 128 problems of 8192 tokens in clusters of 128: 76 us with a word per lane, 33 now).
+// and not 64 (one-hop maxima of 128 problems of 8192 tokens in clusters of 128, both rounds: 90 us with a word per lane, 60 now;
+// the largest key of every half tile and whose it is, asked first, takes 50 there and half as long again in small calls).
 __device__ __forceinline__ uint32_t quad_max(const uint32_t *a, uint32_t word, uint32_t m) {
   const int piece = lane_id() & 3;
   uint32_t w[4];

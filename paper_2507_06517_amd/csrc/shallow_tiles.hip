@@ -239,8 +239,8 @@ __global__ __launch_bounds__(kPivotThreads, 2) void shallow_pivots(ShallowParams
 }
 
 // Tokens in the order of their buckets: a counting sort.  shallow_pivots left how many tokens a bucket has and which
-// place within it a block's tokens start at (with counts per block that every block added up, twice the buckets would have
-// cost twice the 26 us that half of them took on 16 problems of 32768 tokens; now 9).
+// place within it a block's tokens start at.  (With counts per block that every block added up, half as many buckets took 15 us
+// on 16 problems of 32768 tokens and 54 on 64; now 6 and 18.)
 constexpr int kOrderThreads = 1024;
 
 __global__ __launch_bounds__(kOrderThreads) void shallow_order(ShallowParams p, int nblk, int per) {

@@ -104,10 +104,11 @@ def test_rows_of_more_than_512_column_tiles(dtype, theta, sizes):
 
 
 @pytest.mark.parametrize("sizes", [(300,) + (2,) * 400 + (1,) * 7600, (300,) + (2,) * 400 + (1,) * 3000, (257,) + (3,) * 100 + (1,) * 467,
-                                   (1,) * 1025, (512, 512), (513, 512)])
+                                   (1,) * 1025, (512, 512), (513, 512), (17,) * 140, (40, 15, 16) * 35])
 def test_codebook_order_in_lds_and_in_memory(sizes):
     # picks that fit twice into the free LDS of the merge kernel (7000 of them at 8000 tokens) and more than that,
-    # degrees of one and of two digits, with and without the grid rounds (from 1025 tokens on); the order is that of
+    # degrees of one and of two digits, with and without the grid rounds (from 1025 tokens on), words of half tiles that
+    # several clusters share; the order is that of
     # the clusters' sizes, then of their first tokens
     rng = np.random.default_rng(73)
     which = rng.permutation(np.repeat(np.arange(len(sizes)), sizes))
