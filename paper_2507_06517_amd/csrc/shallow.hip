@@ -12,10 +12,12 @@ namespace {
 int tiles_of(int n) { return (n + kTile - 1) / kTile; }
 int padded_tiles_of(int n) { return (int)align_up((size_t)tiles_of(n), kScanPanel); }
 
+size_t cut_words(int UT) { return align_up((size_t)UT, 64); }   // (what follows starts at a whole cache line: it is read in pairs of words)
+
 // 32-bit words at the end of the workspace that every call clears before use (`scan`: also what
 // only the scan writes).
 size_t zero_words(int UT, int n, int scan) {
-  size_t w = (size_t)UT * kCounters + (size_t)UT;
+  size_t w = (size_t)UT * kCounters + cut_words(UT);
   if (scan) w += (size_t)UT * (kBuckets + padded_tiles_of(n)) + (size_t)UT * tiles_of(n) * ((tiles_of(n) + 31) / 32);
   return w;
 }
@@ -77,7 +79,7 @@ size_t carve(ShallowParams &p, void *ws, int UT, int n) {
   p.counters = cv.take<int>(zero_words(UT, n, 1));
   int *tail = p.counters ? p.counters + (size_t)UT * kCounters : nullptr;
   p.ovf_cnt = reinterpret_cast<unsigned *>(tail);
-  p.total = reinterpret_cast<uint32_t *>(tail ? tail + UT : nullptr);
+  p.total = reinterpret_cast<uint32_t *>(tail ? tail + cut_words(UT) : nullptr);
   p.etile = p.total ? p.total + (size_t)UT * kBuckets : nullptr;
   p.tpairs = p.etile ? p.etile + (size_t)UT * p.Tp : nullptr;
   return cv.total();
