@@ -82,12 +82,13 @@ inline int scan_pays(int UT, int n) {
   return n >= 2048 || (n >= 1024 && UT * T * (T - 24) >= 18000);
 }
 // Tile pairs of all problems from which the scan pays for asking the balls around the tiles first, which takes shallow_window
-// and short blocks of shallow_scan some 10 us.  Calls on clusters, fp16, without and with, us: 16 problems of 4096 tokens (0.26
-// million) 118, 132, of 8192 (1.05) 162, 163 (with a third isolated 220, 226), of 12000 (2.25) 208, 194; 2 of 16384 (0.52) 144,
-// 152, of 32768 (2.1) 188, 171; 128 of 2048 (0.52) 197, 211, of 4096 (2.1) 330, 318.
+// and short blocks of shallow_scan some 10 us.  Calls, fp16, without and with, us: clusters, 16 problems of 4096 tokens (0.26
+// million) 118, 132, of 8192 (1.05) 162, 163, of 11000 (1.9) 192, 181 (with a third isolated 241, 243), of 12000 (2.25)
+// 208, 194; 128 of 4096 (2.1) 305, 299 (394, 409); 2 of 32768 (2.1) 188, 170 (with a fifth isolated 246, 237; kept rows of
+// repeated heads 270, 281).
 inline int balls_pay(int UT, int n) {
   const long T = (n + 31) / 32;
-  return UT * T * T >= 1600000;
+  return UT * T * T >= 2200000;
 }
 // Below kSketchMinTheta the sketches are not asked: a sketch product of unrelated tokens is about 0.53 with a
 // spread of 0.06, so the largest of a pair of tiles is above 0.7 nearly always.  Below kVectorMinTheta the full

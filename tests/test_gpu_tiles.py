@@ -23,10 +23,10 @@ def test_lengths_around_the_scan_and_its_windows(oracle, dtype, l):
 
 
 @pytest.mark.parametrize("dtype,H,l,centroids,noise,drift,theta", [
-    ("f16", 128, 2593, 20, 0.3, 0.003, 0.98),             # 82 tiles: a second group of balls that is mostly not there
-    ("bf16", 100, 3000, 3, 0.1, 0.0, 0.9), ("f32", 64, 3650, 40, 0.5, 0.0, 0.95),
-    ("f16", 52, 4097, 200, 0.05, 0.002, 0.95),            # few tokens per cluster, many second balls
-    ("bf16", 64, 3649, 1, 0.97, 0.0, 0.75)])              # isolated tokens: blocks that take all pairs
+    ("f16", 128, 3009, 20, 0.3, 0.003, 0.98),             # 95 tiles: a second group of balls that is half there
+    ("bf16", 100, 3400, 3, 0.1, 0.0, 0.9), ("f32", 64, 4300, 40, 0.5, 0.0, 0.95),
+    ("f16", 68, 4097, 200, 0.05, 0.002, 0.95),            # few tokens per cluster, many second balls; a third group of one tile
+    ("bf16", 64, 4225, 1, 0.97, 0.0, 0.75)])              # isolated tokens: blocks that take all pairs
 def test_tile_pairs_excluded_by_balls(oracle, dtype, H, l, centroids, noise, drift, theta):
     # enough problems for the scan to ask the balls around the tiles first
     L = wl.small_random(64, dtype, B=1, H=H, l=l, lw=1, cap=l // 7, n_centroids=centroids, noise_frac=noise, drift_sigma=drift)
