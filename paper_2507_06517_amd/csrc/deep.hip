@@ -810,24 +810,24 @@ __global__ __launch_bounds__(kSelThreads) void deep_select(SelectParams p) {
 }
 
 // Every workgroup works out what the whole unit's selection comes to, threshold bin from the histogram, exact value of the
-// k-th largest key among the keys of that bin, what is kept in front of its segment, then writes the kept positions of its own
-// segment and copies their rows of K and V.  Bound by latency, and doing the same in all workgroups of a unit takes no longer
-// than in one: eight units of 32704 positions 24 us where the workgroup that was last to pool did the rest of its unit
-// alone, and 5 for a launch that copied the rows; now 5 and 17.
+// k-th largest key among the keys of that bin, then writes its share of the kept positions, as many as every other, and copies
+// their rows of K and V.  (By segments of the context, the one that holds most of what is kept copies it alone: the divisor of
+// Eq. 3 has similar keys keep the end of the context.  Calls that keep 2048 random keys, 8 units of 32736 positions 64 us by segments and 51
+// now, 32 units 157 and 133.)  Bound by latency.
 __global__ __launch_bounds__(kSelThreads) void deep_finish(SelectParams p, GatherParams q) {
   __shared__ int hist[256];
   __shared__ __attribute__((aligned(16))) uint32_t cand[kCandMax];
-  __shared__ int wsum[kSelThreads / 64];
-  __shared__ int front[2], here[kSelThreads / 64];
+  __shared__ int wsum[kSelThreads / 64], wcount[kSelThreads / 64][2];
   __shared__ uint32_t sh_prefix;
   __shared__ int sh_krem, sh_ncand;
-  const int seg = blockIdx.x, u = blockIdx.y, tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
+  const int blk = blockIdx.x, u = blockIdx.y, tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
   const int lc = p.lc;
   const uint32_t *pooled = p.pooled + (size_t)u * lc;
   const int *ghist = p.hist + (size_t)u * kBins;
   int32_t *kept = p.kept + (size_t)u * p.out_stride;
   const int k = kept_context(p, u);
-  const int a_begin = seg * kSegLen, a_end = min(lc, a_begin + kSegLen);
+  const int share = (k + p.nseg - 1) / p.nseg;         // (a segment's length at most)
+  const int r0 = min(k, blk * share), r1 = min(k, r0 + share);   // the workgroup's kept positions
 
   constexpr int kWaves = kSelThreads / 64;
   constexpr int kBatch = 32;
@@ -844,9 +844,8 @@ __global__ __launch_bounds__(kSelThreads) void deep_finish(SelectParams p, Gathe
   };
   uint32_t prefix = 0;                                 // key of the k-th largest pooled score
   int krem = k;                                        // how many keys equal to it are taken
-  int nkept = 0;                                       // positions of the segment that are kept, their places in `mine`
-  int first = 0;                                       // kept positions in front of the segment
-  uint16_t *mine = reinterpret_cast<uint16_t *>(cand); // [kSegLen], less a_begin
+  uint32_t *mine = cand;                               // [share] positions r0 .. r1 - 1, behind the candidates' last use
+  static_assert(kCandMax >= kSegLen, "a share fits");
   if (k > 0 && k < lc) {
     if (one_trip) load_keys(w0);
     // threshold bin: thread t owns four bins, from the top, so that counts add up along the threads
@@ -867,14 +866,14 @@ __global__ __launch_bounds__(kSelThreads) void deep_finish(SelectParams p, Gathe
         }
         seen += hh[j];
       }
-      if (tid == 0) sh_ncand = front[0] = front[1] = 0;
+      if (tid == 0) sh_ncand = 0;
       __syncthreads();
       prefix = sh_prefix;
       krem = sh_krem;
     }
-    // The unit's keys, dealt to the waves in contiguous runs,
+    // The unit's keys, dealt to the waves in contiguous runs (the order of the compaction below),
     // thirty-two 64-position steps per lane and trip, all loads of a trip in flight together.  A
-    // unit of up to 32768 positions is one trip: its keys stay in registers for both uses.
+    // unit of up to 32768 positions is one trip: its keys stay in registers for all three uses.
     // First use: the keys of the threshold's bin, ranked in LDS when they fit (a few hundred as a
     // rule), else where they are.
     for (int b0 = w0; b0 < w1; b0 += 64 * kBatch) {
@@ -900,68 +899,63 @@ __global__ __launch_bounds__(kSelThreads) void deep_finish(SelectParams p, Gathe
     const int nsrc = ncand <= kCandMax ? ncand : lc;
     int bits_left = 20;
     while (bits_left > 0) radix_step(src, nsrc, prefix, krem, bits_left, hist, &sh_prefix, &sh_krem);
-    // what is kept in front of the segment: everything above the threshold, the first `krem` equal to it
-    if (w0 < a_begin) {
-      int ngt = 0, neq = 0;
-      for (int b0 = w0; b0 < min(w1, a_begin); b0 += 64 * kBatch) {
+    // ordered compaction: everything above the threshold, the first `krem` equal to it.  Counts of the waves first; those
+    // that have some of the workgroup's own then place them by ballots over 64 positions.
+    int ngt = 0, neq = 0;
+    for (int b0 = w0; b0 < w1; b0 += 64 * kBatch) {
+      if (!one_trip) load_keys(b0);
+#pragma unroll
+      for (int i = 0; i < kBatch; ++i) {
+        const bool in = b0 + 64 * i + lane < w1;
+        ngt += in && x[i] > prefix;
+        neq += in && x[i] == prefix;
+      }
+    }
+    ngt = __builtin_amdgcn_readlane(lanes_up_to(ngt), 63);
+    neq = __builtin_amdgcn_readlane(lanes_up_to(neq), 63);
+    if (lane == 0) {
+      wcount[wave][0] = ngt;
+      wcount[wave][1] = neq;
+    }
+    __syncthreads();
+    int gt_seen = 0, eq_seen = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+      gt_seen += w < wave ? wcount[w][0] : 0;
+      eq_seen += w < wave ? wcount[w][1] : 0;
+    }
+    const int from = gt_seen + min(eq_seen, krem), to = gt_seen + ngt + min(eq_seen + neq, krem);   // of the wave
+    const unsigned long long below = (1ull << lane) - 1ull;
+    if (from < r1 && to > r0)
+      for (int b0 = w0; b0 < w1; b0 += 64 * kBatch) {
         if (!one_trip) load_keys(b0);
 #pragma unroll
         for (int i = 0; i < kBatch; ++i) {
           const int a = b0 + 64 * i + lane;
-          ngt += a < min(w1, a_begin) && x[i] > prefix;
-          neq += a < min(w1, a_begin) && x[i] == prefix;
+          const bool gt = a < w1 && x[i] > prefix, eq = a < w1 && x[i] == prefix;
+          const unsigned long long mgt = __ballot(gt), meq = __ballot(eq);
+          const int eq_before = eq_seen + __popcll(meq & below);
+          const int at = gt_seen + __popcll(mgt & below) + min(eq_before, krem);
+          if ((gt || (eq && eq_before < krem)) && at >= r0 && at < r1) {
+            mine[at - r0] = (uint32_t)a;
+            kept[at] = a;
+          }
+          gt_seen += __popcll(mgt);
+          eq_seen += __popcll(meq);
         }
       }
-      ngt = lanes_up_to(ngt);
-      neq = lanes_up_to(neq);
-      if (lane == 63) {
-        atomicAdd(&front[0], ngt);
-        atomicAdd(&front[1], neq);
-      }
-    }
-    // ordered compaction of the segment, two neighbouring positions per thread
-    static_assert(kSegLen == 2 * kSelThreads, "two positions per thread");
-    const int a = a_begin + 2 * tid;
-    const uint32_t x0 = a < a_end ? pooled[a] : 0u, x1 = a + 1 < a_end ? pooled[a + 1] : 0u;
-    // (counts of both kinds in one word; an absent position counts as neither)
-    const int c0 = a < a_end ? (x0 > prefix ? 1 << 16 : 0) + (x0 == prefix) : 0;
-    const int c1 = a + 1 < a_end ? (x1 > prefix ? 1 << 16 : 0) + (x1 == prefix) : 0;
-    const int incl = lanes_up_to(c0 + c1);
-    if (lane == 63) here[wave] = incl;
-    __syncthreads();
-    int at = incl - c0 - c1;
-#pragma unroll
-    for (int w = 0; w < kWaves; ++w) {
-      at += w < wave ? here[w] : 0;
-      nkept += here[w];
-    }
-    const int gt_front = front[0], eq_front = front[1], left = max(0, krem - eq_front);   // equal ones still taken
-    first = gt_front + min(eq_front, krem);
-    nkept = (nkept >> 16) + min(nkept & 0xFFFF, left);
-    auto place = [&](int before, int own, int pos) __attribute__((always_inline)) {
-      const int gt = before >> 16, eq = before & 0xFFFF;
-      if (own >> 16 || (own && eq < left)) {
-        const int to = gt + min(eq, left);
-        mine[to] = (uint16_t)(pos - a_begin);
-        kept[first + to] = pos;
-      }
-    };
-    place(at, c0, a);
-    place(at + c0, c1, a + 1);
-  } else if (k > 0) {
-    first = a_begin;
-    nkept = max(0, a_end - a_begin);
-    for (int i = tid; i < nkept; i += kSelThreads) {
-      mine[i] = (uint16_t)i;
-      kept[a_begin + i] = a_begin + i;
+  } else {
+    for (int i = tid; i < r1 - r0; i += kSelThreads) {
+      mine[i] = (uint32_t)(r0 + i);
+      kept[r0 + i] = r0 + i;
     }
   }
   __syncthreads();
-  // their rows, and of the window and the padding behind the kept positions the segment's share
+  // their rows, and of the window and the padding behind the kept positions the workgroup's share
   const int tpr = q.row_bytes / 16, per = kSelThreads / tpr, t = tid % tpr;
   const size_t in = kv_unit_offset(q.lay, u) + t * 16, out = (size_t)u * p.out_stride * q.row_bytes + t * 16;
-  const int behind = p.out_stride - k, share = (behind + p.nseg - 1) / p.nseg;
-  const int nbehind = max(0, min(behind - seg * share, share));
+  const int nkept = r1 - r0, behind = p.out_stride - k, share_behind = (behind + p.nseg - 1) / p.nseg;
+  const int nbehind = max(0, min(behind - blk * share_behind, share_behind));
   for (int i0 = tid / tpr; i0 < nkept + nbehind; i0 += 2 * per) {
     u4 kv[2], vv[2];
     int to[2];
@@ -973,10 +967,10 @@ __global__ __launch_bounds__(kSelThreads) void deep_finish(SelectParams p, Gathe
       if (i >= nkept + nbehind) continue;
       int idx;
       if (i < nkept) {
-        to[j] = first + i;
-        idx = a_begin + (int)mine[i];
+        to[j] = r0 + i;
+        idx = (int)mine[i];
       } else {
-        const int b = seg * share + i - nkept;         // of the window, then of the padding
+        const int b = blk * share_behind + i - nkept;  // of the window, then of the padding
         to[j] = k + b;
         idx = b < p.lw ? lc + b : -1;
         if (t == 0) kept[to[j]] = idx;

@@ -139,3 +139,20 @@ def test_one_unit_takes_no_longer_than_eight(l, lw, hn):
         took.append(parity.least_us(lambda: plan.run(K, K, Q), calls=20))
     print("units", l, lw * hn, [round(t, 1) for t in took], flush=True)
     assert took[0] < 1.12 * took[1]
+
+
+def test_kept_tokens_that_stand_together_take_no_longer():
+    # zero queries: the paper's divisor keeps the last 2000 context tokens, which one workgroup copied where the copies
+    # went by segments of the context (half as long again); without the divisor random queries keep tokens from everywhere
+    import torch
+    from paper_2507_06517_amd import binding as sb
+    g = torch.Generator(device="cuda").manual_seed(3)
+    K, Q = (torch.randn((1, 4, n, 128), generator=g, device="cuda") for n in (20000, 16))
+    took = []
+    for q, norm in ((torch.zeros_like(Q), 0), (Q, 1)):
+        plan = sb.plan_deep(K, 1, "f32", 16, 7, 2016, norm=norm, want_scores=False)
+        took.append(parity.least_us(lambda: plan.run(K, K, q), calls=20))
+        kept = plan.kept[0, 0].cpu().numpy()
+        assert (np.diff(kept) == 1).all() == (norm == 0)
+    print("kept together, spread", [round(t, 1) for t in took], flush=True)
+    assert took[0] < 1.15 * took[1]
