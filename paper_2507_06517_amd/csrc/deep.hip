@@ -7,7 +7,8 @@
 //                     queries and the GQA group (Eq. 2, 3)
 //   deep_select       max-pool, 4096-bin histogram of the pooled scores over many workgroups
 //   deep_finish       the k-th largest score from the histogram and the few scores that share its bin,
-//                     the kept positions in order (Eq. 7), K_out = K[kept], V_out = V[kept]
+//                     the kept positions in order (Eq. 7), K_out = K[kept], V_out = V[kept] (of many or
+//                     very long units without the copies)
 //   deep_select_unit, deep_gather
 //                     the same for shorter contexts: one workgroup per unit, scores and keys in LDS, and
 //                     the copies of the rows
@@ -421,7 +422,8 @@ struct SelectParams {
   int *hist;             // [U][kBins], zero on entry
   const int32_t *budgets;
   int32_t *kept;         // [U][out_stride]
-  int l, lc, lw, pool, budget, out_stride, nseg;
+  int l, lc, lw, pool, budget, out_stride;
+  int nfinish;           // workgroups per unit of deep_finish
   int spitch;            // floats per unit of `scores`, a multiple of 4
 };
 
@@ -813,7 +815,9 @@ __global__ __launch_bounds__(kSelThreads) void deep_select(SelectParams p) {
 // k-th largest key among the keys of that bin, then writes its share of the kept positions, as many as every other, and copies
 // their rows of K and V.  (By segments of the context, the one that holds most of what is kept copies it alone: the divisor of
 // Eq. 3 has similar keys keep the end of the context.  Calls that keep 2048 random keys, 8 units of 32736 positions 64 us by segments and 51
-// now, 32 units 157 and 133.)  Bound by latency.
+// by shares, 32 units 157 and 133.)  Bound by latency.
+// Where the workgroups of all units would not run at once (finish_blocks), one per unit selects and deep_gather copies (kCopies = false).
+template <bool kCopies>
 __global__ __launch_bounds__(kSelThreads) void deep_finish(SelectParams p, GatherParams q) {
   __shared__ int hist[256];
   __shared__ __attribute__((aligned(16))) uint32_t cand[kCandMax];
@@ -826,7 +830,7 @@ __global__ __launch_bounds__(kSelThreads) void deep_finish(SelectParams p, Gathe
   const int *ghist = p.hist + (size_t)u * kBins;
   int32_t *kept = p.kept + (size_t)u * p.out_stride;
   const int k = kept_context(p, u);
-  const int share = (k + p.nseg - 1) / p.nseg;         // (a segment's length at most)
+  const int share = (k + p.nfinish - 1) / p.nfinish;   // (kCopies: a segment's length at most)
   const int r0 = min(k, blk * share), r1 = min(k, r0 + share);   // the workgroup's kept positions
 
   constexpr int kWaves = kSelThreads / 64;
@@ -937,7 +941,7 @@ __global__ __launch_bounds__(kSelThreads) void deep_finish(SelectParams p, Gathe
           const int eq_before = eq_seen + __popcll(meq & below);
           const int at = gt_seen + __popcll(mgt & below) + min(eq_before, krem);
           if ((gt || (eq && eq_before < krem)) && at >= r0 && at < r1) {
-            mine[at - r0] = (uint32_t)a;
+            if (kCopies) mine[at - r0] = (uint32_t)a;
             kept[at] = a;
           }
           gt_seen += __popcll(mgt);
@@ -946,15 +950,19 @@ __global__ __launch_bounds__(kSelThreads) void deep_finish(SelectParams p, Gathe
       }
   } else {
     for (int i = tid; i < r1 - r0; i += kSelThreads) {
-      mine[i] = (uint32_t)(r0 + i);
+      if (kCopies) mine[i] = (uint32_t)(r0 + i);
       kept[r0 + i] = r0 + i;
     }
+  }
+  if constexpr (!kCopies) {
+    for (int b = tid; b < p.out_stride - k; b += kSelThreads) kept[k + b] = b < p.lw ? lc + b : -1;
+    return;
   }
   __syncthreads();
   // their rows, and of the window and the padding behind the kept positions the workgroup's share
   const int tpr = q.row_bytes / 16, per = kSelThreads / tpr, t = tid % tpr;
   const size_t in = kv_unit_offset(q.lay, u) + t * 16, out = (size_t)u * p.out_stride * q.row_bytes + t * 16;
-  const int nkept = r1 - r0, behind = p.out_stride - k, share_behind = (behind + p.nseg - 1) / p.nseg;
+  const int nkept = r1 - r0, behind = p.out_stride - k, share_behind = (behind + p.nfinish - 1) / p.nfinish;
   const int nbehind = max(0, min(behind - blk * share_behind, share_behind));
   for (int i0 = tid / tpr; i0 < nkept + nbehind; i0 += 2 * per) {
     u4 kv[2], vv[2];
@@ -1065,6 +1073,17 @@ DeepLayout deep_layout(void *ws, int U, int l, int lw, int Rpad, int dtype) {
   return L;
 }
 
+// Workgroups per unit of deep_finish.  Each reads all keys of its unit, so there are no more of them than run at once: then the
+// copies come along for nothing (one per unit and a launch for the copies, and as chosen here, us: 8 units of 32736 positions 51.5,
+// 50.1, 1 of which 16384 are kept 43.5, 41.5, 8 of 65504 83, 81, 2 of 262112 142, 141).  More wait for each other, and what they
+// read grows with the square of the context: 192 units of 32736 positions 672 and, 16 workgroups each, 823, 8 of 131040 144 and 186, of
+// 524256 569 and 1683.  More than four per segment gain nothing.  (A single unit of 524256 positions takes 225 either way: three reads of
+// its keys by one workgroup are most of it.)
+int finish_blocks(int U, int nseg) {
+  const int each = kBlocksAtOnce / U;
+  return each < nseg ? 1 : (each < 4 * nseg ? each : 4 * nseg);
+}
+
 int padded_rows(int R) { return R <= 64 ? 64 : (R <= 128 ? 128 : 256); }
 
 template <int DT, int WR, int KEYS>
@@ -1095,6 +1114,12 @@ spindle_status launch_rows(const DeepParams &p, int keys, int U, hipStream_t st)
   if (keys == 128) return launch_passes<DT, WR, 128>(p, U, st);
   if constexpr (DT != SPINDLE_F32) return launch_passes<DT, WR, 256>(p, U, st);
   SPINDLE_FAIL(SPINDLE_ERR_UNSUPPORTED, "%d keys per stage", keys);
+}
+
+void launch_gather(const GatherParams &p, int U, hipStream_t st) {
+  const int rows_per_block = 256 / (p.row_bytes / 16);
+  ProfScope ps("deep_gather", st);
+  hipLaunchKernelGGL(deep_gather, dim3((p.out_stride + rows_per_block - 1) / rows_per_block, U), dim3(256), 0, st, p);
 }
 
 template <int DT>
@@ -1182,7 +1207,6 @@ extern "C" spindle_status spindle_compress_deep(const spindle_kv_desc *desc, con
   sp.budgets = budgets; sp.kept = kept_idx;
   sp.l = l; sp.lc = lc; sp.lw = lw; sp.pool = pool_kernel; sp.budget = budget; sp.out_stride = out_stride;
   sp.spitch = p.spitch;
-  sp.nseg = lc > 0 ? (lc + kSegLen - 1) / kSegLen : 1;
   GatherParams gp;
   gp.K = static_cast<const char *>(K); gp.V = static_cast<const char *>(V);
   gp.Ko = static_cast<char *>(K_out); gp.Vo = static_cast<char *>(V_out);
@@ -1194,14 +1218,16 @@ extern "C" spindle_status spindle_compress_deep(const spindle_kv_desc *desc, con
     if ((s = allow_lds(lim, reinterpret_cast<const void *>(&deep_select_unit), unit_lds(kUnitMax))) != SPINDLE_OK) return s;
     { ProfScope ps("deep_select", st);
     hipLaunchKernelGGL(deep_select_unit, dim3(U), dim3(kSelThreads), unit_lds(lc), st, sp); }
-    const int rows_per_block = 256 / (gp.row_bytes / 16);
-    ProfScope ps("deep_gather", st);
-    hipLaunchKernelGGL(deep_gather, dim3((out_stride + rows_per_block - 1) / rows_per_block, U), dim3(256), 0, st, gp);
+    launch_gather(gp, U, st);
   } else {
+    const int nseg = lc > 0 ? (lc + kSegLen - 1) / kSegLen : 1;
+    sp.nfinish = finish_blocks(U, nseg);
     { ProfScope ps("deep_select", st);
-    hipLaunchKernelGGL(deep_select, dim3(sp.nseg, U), dim3(kSelThreads), 0, st, sp); }
-    ProfScope ps("deep_finish", st);
-    hipLaunchKernelGGL(deep_finish, dim3(sp.nseg, U), dim3(kSelThreads), 0, st, sp, gp);
+    hipLaunchKernelGGL(deep_select, dim3(nseg, U), dim3(kSelThreads), 0, st, sp); }
+    { ProfScope ps("deep_finish", st);
+    if (sp.nfinish > 1) hipLaunchKernelGGL(deep_finish<true>, dim3(sp.nfinish, U), dim3(kSelThreads), 0, st, sp, gp);
+    else hipLaunchKernelGGL(deep_finish<false>, dim3(1, U), dim3(kSelThreads), 0, st, sp, gp); }
+    if (sp.nfinish == 1) launch_gather(gp, U, st);
   }
   SPINDLE_HIP(hipGetLastError());
   return SPINDLE_OK;

@@ -156,3 +156,18 @@ def test_kept_tokens_that_stand_together_take_no_longer():
         assert (np.diff(kept) == 1).all() == (norm == 0)
     print("kept together, spread", [round(t, 1) for t in took], flush=True)
     assert took[0] < 1.15 * took[1]
+
+
+@pytest.mark.parametrize("H", [8, 1])
+def test_selection_takes_time_in_proportion_to_the_context(H):
+    # eight times the context: 12 times the time where every workgroup of a unit read all of its keys, however many there were
+    import torch
+    from paper_2507_06517_amd import binding as sb
+    took = []
+    for l in (65536, 524288):
+        g = torch.Generator(device="cuda").manual_seed(l)
+        K, Q = (torch.randn((1, H, n, 128), generator=g, device="cuda", dtype=torch.float16) for n in (l, 16))
+        plan = sb.plan_deep(K, 1, "f16", 16, 7, 2016, want_scores=False)
+        took.append(parity.least_us(lambda: plan.run(K, K, Q)))
+    print("units", H, "contexts of 65536, 524288", [round(t, 1) for t in took], flush=True)
+    assert took[1] < 9 * took[0]
