@@ -90,6 +90,11 @@ inline int balls_pay(int UT, int n) {
   const long T = (n + 31) / 32;
   return UT * T * T >= 2200000;
 }
+// Below kBallMinTheta balls exclude too little: products of unrelated tokens end at about 0.65 for a tile, and the radius
+// and the errors add 0.2.  Calls, fp16, without and with, us, by theta: 16 problems of 32768 drifting tokens 0.9 659, 649, 0.88 763, 799, 0.86
+// 1038, 1100, of which a third isolated 0.9 826, 705, 0.86 1202, 1137, 0.83 1703, 1682; 64 of 8192 in clusters 0.88 356, 319, 0.83 386, 365,
+// 0.77 697, 765, half isolated 0.9 578, 569, 0.88 641, 656, 0.86 783, 899, 0.74 1067, 1231.
+constexpr float kBallMinTheta = 0.87f;
 // Below kSketchMinTheta the sketches are not asked: a sketch product of unrelated tokens is about 0.53 with a
 // spread of 0.06, so the largest of a pair of tiles is above 0.7 nearly always.  Below kVectorMinTheta the full
 // vectors are not asked either: at 0.3 a third of the pairs of tiles of unrelated tokens hold a cosine above it, three
@@ -127,7 +132,7 @@ uint32_t *total;         // [UT][kBuckets] tokens per bucket
   uint16_t *before;        // [UT][order blocks][kBuckets] place within a bucket of a block's first token of it
   uint8_t *sk;             // [UT][Tp][kSixBytes] sketches by position, in six-bit floats
   uint32_t *etile;         // [UT][Tp] what a tile's sketches may be off by in a product, sketch units squared
-  int balls;               // 1: the scan asks the balls around tiles first
+  int balls, asks[2];      // 1: the scan asks the balls around tiles first, in any of the tensors, in each
   float *tnorm;            // [UT][Tp] longest six-bit sketch of a tile, in six-bit units (as the radii)
   // Balls around the six-bit sketches of a tile, or of its two parts: centres as 3 tiles of 32 per kBallTiles, and per centre
   // what the products of its tile may be off by, in six-bit units squared (no tile: a large negative number), and its radius.
@@ -138,6 +143,7 @@ uint32_t *total;         // [UT][kBuckets] tokens per bucket
   int T, Tp, TW;           // tiles, rounded up to whole panels; words per row of tpairs
   int scan;                // 1: tokens are sorted and tpairs says which tiles count; 0: all tiles, positions = tokens
   int stages_per_item, njg;   // column stages of a block of the scan, runs of them in a problem
+  int stages_to_refine;    // of a block of shallow_refine
   uint32_t *todo;          // [scan_blocks] 1: left to shallow_refine
   int by[2];               // which tile pairs count: kBySketch, kByVector or, all of them, kByNone
   int scan_thr[2];         // theta in sketch units squared

@@ -22,6 +22,15 @@ size_t zero_words(int UT, int n, int scan) {
   return w;
 }
 
+// Stages per block of the scan and of shallow_refine: about so many blocks, that short problems fill the chip too (the longest
+// last about 15 us).
+void cut_stages(ShallowParams &p, int blocks) {
+  const int nI = p.Tp / kScanPanel, nS = p.Tp / kScanStage;
+  const long work = (long)p.UT * nI * (nI + 1) / blocks;
+  p.stages_per_item = work < 1 ? 1 : (work > kScanRun ? kScanRun : (int)work);
+  p.njg = (nS + p.stages_per_item - 1) / p.stages_per_item;
+}
+
 size_t carve(ShallowParams &p, void *ws, int UT, int n) {
   Carver cv(ws);
   const size_t N = (size_t)UT * n;
@@ -29,13 +38,8 @@ size_t carve(ShallowParams &p, void *ws, int UT, int n) {
   p.Tp = padded_tiles_of(n);
   p.TW = (p.T + 31) / 32;
   p.UT = UT;
-  // stages per block of the scan: about 1024 blocks, so that short problems fill the chip too (the longest last
-  // about 15 us)
-  const int nI = p.Tp / kScanPanel, nS = p.Tp / kScanStage;
-  p.balls = balls_pay(UT, n);
-  const long work = (long)UT * nI * (nI + 1) / (p.balls ? 1024 : 2048);
-  p.stages_per_item = work < 1 ? 1 : (work > kScanRun ? kScanRun : (int)work);
-  p.njg = (nS + p.stages_per_item - 1) / p.stages_per_item;
+  cut_stages(p, 2048);
+  p.stages_to_refine = p.stages_per_item;
   p.Xe = cv.take<_Float16>((N + 512) * kHeadDim);   // the similarity loop stages up to 5 tiles past the last token
   p.Xh = p.dtype == SPINDLE_F32 ? cv.take<_Float16>(N * kHeadDim) : nullptr;
   p.Xl = p.Xe;                                      // (for shallow_rows only, which is done when entries are written)
@@ -185,7 +189,11 @@ spindle_status run_shallow(int phases,
     p.by[i] = !p.scan || p.theta[i] < kVectorMinTheta ? kByNone : p.theta[i] < kSketchMinTheta ? kByVector : kBySketch;
     const double thr = p.by[i] == kBySketch ? ((double)p.theta[i] - 1e-4) * kSketchScale * kSketchScale : 0.0;
     p.scan_thr[i] = thr < (double)(1 << 28) ? (int)floor(thr) : 1 << 28;
+    p.asks[i] = p.by[i] == kBySketch && p.theta[i] >= kBallMinTheta && balls_pay(p.UT, n);
+    p.balls |= p.asks[i];
   }
+  // (where balls are asked, what a block does before its first products is more; never more blocks than `todo` has room for)
+  if (p.balls) cut_stages(p, 1024);
   if (phases & kPhaseGraph) {
     // zero: counters, and where there is a scan its errors and marks; codebooks
     const size_t nzero = zero_words(p.UT, n, p.scan);

@@ -339,6 +339,7 @@ __global__ __launch_bounds__(kWindowThreads) void shallow_window(ShallowParams p
   const size_t base = (size_t)ut * n;
   const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
   const uint2 mean = reinterpret_cast<const uint2 *>(p.mean)[ut];
+  const bool asks = p.asks[ut / p.U];
   static_assert(kWindow == 2 * kWindowThreads, "two places per thread");
   int tok[2], b[2], signs[2];
 #pragma unroll
@@ -435,7 +436,7 @@ __global__ __launch_bounds__(kWindowThreads) void shallow_window(ShallowParams p
   const uint32_t parted = (uint32_t)__ballot(inside != 0 && __popc(inside) <= 2);
   constexpr int kSeconds = kTile / 2;
   const int second0 = half_at / 2;
-  if (p.balls && wave == 0 && lane >= __popc(parted) && lane < kSeconds) balls[2 * kTile + second0 + lane] = make_float2(-0x1p30f, 0.f);
+  if (asks && wave == 0 && lane >= __popc(parted) && lane < kSeconds) balls[2 * kTile + second0 + lane] = make_float2(-0x1p30f, 0.f);
   constexpr float kUnit = 1.f / (kSixScale * kSixScale);   // products of six-bit floats are in units of kSixScale squared
   const int end = w1 < n ? w1 : p.Tp * kTile;         // the last window also fills the places past the last token
   for (int p0 = w0 + wave * kTile; p0 < end; p0 += kWindowThreads / kWave * kTile) {
@@ -497,7 +498,7 @@ __global__ __launch_bounds__(kWindowThreads) void shallow_window(ShallowParams p
     uint32_t e = off >= 0.f && dist < 4.f ? (uint32_t)((dist + 0.5f * dist * dist) * (kSketchScale * kSketchScale * (1.f + 1e-5f))) + 2u : kSketchUnknown;
     if (pos >= n) e = 0;
     e = max32(e);
-    if (!p.balls) {                                    // uniform
+    if (!asks) {                                       // uniform
       if (lane == 0) p.etile[(size_t)ut * p.Tp + (p0 >> 5)] = e;
       continue;
     }
@@ -679,7 +680,8 @@ __global__ __launch_bounds__(kScanThreads, 4) void shallow_scan(ShallowParams p)
       lds_dma16_at(src, (uint32_t)(q * 1024 + lane * 16),
                    stage_lds + buffer * (kScanStage * kSixBytes) + wave * (kLoads * 1024) + q * 1024);
   };
-  if (kWithBalls) {
+  const bool asks = kWithBalls && p.asks[w.ut / p.U];
+  if (asks) {
     dma(w.I * 2, 0);
     dma(w.I * 2 + 1, 1);
   }
@@ -715,12 +717,12 @@ __global__ __launch_bounds__(kScanThreads, 4) void shallow_scan(ShallowParams p)
   for (int r = 0; r < 4; ++r) {
     bf[r] = tile_at(sk + (size_t)(r0 + r) * kSixBytes);
     ethr[r] = (float)(thr0 - (int)et[r0 + r]) * kUnit;
-    rnorm[r] = kWithBalls ? norm[r0 + r] : 0.f;
+    rnorm[r] = asks ? norm[r0 + r] : 0.f;
   }
   constexpr int kPerStage = kScanPanel / 4 * kScanStage;   // column tiles, once per wave
   const int own = (w.I + 1) * (kScanPanel / kScanStage);   // first stage behind the panel's own columns
   bool dense = true, refine = false;
-  if constexpr (kWithBalls) {
+  if constexpr (kWithBalls) if (asks) {
   for (int i = threadIdx.x; i < c1 - c0; i += kScanThreads) {
     col_thr[i] = (float)(thr0 - (int)et[c0 + i]) * kUnit;
     col_norm[i] = norm[c0 + i];
@@ -971,8 +973,9 @@ __global__ __launch_bounds__(kRefineThreads, 2) void shallow_refine(ShallowParam
       total += x;
     }
     __syncthreads();
-    // few items are cut along their columns too, as long as there are blocks without any (one item by two blocks: 30 us)
-    int cuts = 1;
+    // items are cut along their columns too: to what they are where no balls are asked (64 problems of 8192 tokens by blocks twice that
+    // long 747 us, not 612), and, few ones, as long as there are blocks without any (one item by two blocks: 30 us)
+    int cuts = (p.stages_per_item + p.stages_to_refine - 1) / p.stages_to_refine;
     while (cuts < kScanRun / 2 && 4 * cuts * total <= nslots) cuts *= 2;
     for (int at = slot; at < 2 * cuts * total; at += nslots) {
       ScanItem w = scan_item(p, i0 + list[at / (2 * cuts)], xcd);

@@ -295,3 +295,29 @@ def test_codebook_order(oracle, dtype, sizes):
     L = wl.Layer(dtype, K, K.copy(), np.zeros_like(K[:, :, :1]), 1, 1, 1, l, l)
     parity.check_shallow_layer(oracle, L, tensors=("k",), debug=False)
     parity.check_shallow_layer(oracle, L, tensors=("v",), debug=False, cap=max(1, len(sizes) // 3))
+
+
+@pytest.mark.parametrize("dtype,theta_k,theta_v", [("f16", 0.95, 0.6), ("bf16", 0.75, 0.9), ("f32", 0.88, 0.86)])
+def test_balls_for_one_of_the_tensors(oracle, dtype, theta_k, theta_v):
+    # K and V differ in whether the scan asks the balls, or the sketches at all
+    L = wl.small_random(75, dtype, B=1, H=64, l=4300, lw=1, cap=600, n_centroids=40, noise_frac=0.3)
+    L.theta_k, L.theta_v = theta_k, theta_v
+    parity.check_shallow_layer(oracle, L, units=[(0, 0), (0, 63)], debug=False)
+
+
+def test_low_thresholds_pay_nothing_for_balls():
+    # 64 problems against 16, which are too few to ask the balls: 3.12 times the time, 3.53 where balls were made that no
+    # one asks and the work left to the full vectors came in longer blocks
+    import torch
+    from paper_2507_06517_amd import binding as sb
+    took = []
+    for H in (8, 32):
+        g = torch.Generator(device="cuda").manual_seed(H)
+        centres = torch.randn((H, 64, 128), generator=g, device="cuda")
+        at = torch.randint(0, 64, (H, 8192), generator=g, device="cuda")
+        K, V = ((centres.gather(1, at[:, :, None].expand(H, 8192, 128)) + 0.1 * torch.randn((H, 8192, 128), generator=g, device="cuda"))
+                .half().unsqueeze(0) for _ in range(2))
+        plan = sb.plan_shallow(K, "f16", 0.6, 0.6, 1024)
+        took.append(parity.least_us(lambda: plan.run(K, V)))
+    print("8 and 32 heads", [round(t, 1) for t in took], flush=True)
+    assert took[1] < 3.35 * took[0]
