@@ -140,10 +140,7 @@ __device__ __forceinline__ uint32_t quad_max(const uint32_t *a, uint32_t word, u
   w[2] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)word, 0xAA, 0xF, 0xF, true);
   w[3] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)word, 0xFF, 0xF, 0xF, true);
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    q[i] = u4{0, 0, 0, 0};
-    if (w[i] & 0xFFFFu) q[i] = reinterpret_cast<const u4 *>(a + (w[i] >> 16) * 16)[piece];
-  }
+  for (int i = 0; i < 4; ++i) q[i] = *reinterpret_cast<const u4 *>(reinterpret_cast<const char *>(a) + ((w[i] >> 16) * 64u + piece * 16u));
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int bits = (int)(w[i] >> (4 * piece));
@@ -153,6 +150,18 @@ __device__ __forceinline__ uint32_t quad_max(const uint32_t *a, uint32_t word, u
       m = y > m ? y : m;
     }
   }
+  return m;
+}
+
+// Where a row is dense, a lane takes a half tile (or word) of its own, four in flight: the lanes' half tiles follow each
+// other, and instructions count, of which quad_max has half as many again.  Two grid rounds of 4 problems of 8192 tokens
+// in two clusters 208 us by quads and 143 so, of 2 of 40515 tokens with a common mean 1823 and 1486.
+template <typename L>
+__device__ __forceinline__ uint32_t dense_max(const uint32_t *a, const Row &r, int sl, L look, uint32_t m) {
+  for_words(r, sl, [&](uint32_t w) {
+    w = look(w);
+    if (w & 0xFFFFu) m = masked_max(a, w, m);
+  });
   return m;
 }
 
@@ -190,6 +199,22 @@ __global__ __launch_bounds__(kPhaseThreads) void merge_onehop(ShallowParams p, i
     r[k] = row_at(p, base, lists, v);
     own[k] = key[v];
   }
+  if (__any(r[0].dense | r[1].dense | r[2].dense | r[3].dense)) {
+    uint32_t bits = 0;
+#pragma unroll 1
+    for (int k = 0; k < 4; ++k) {                      // (anew: what a rolled loop counts over cannot stay in registers)
+      const int v = W * kTile + 8 * k + seg;
+      const bool here = live >> (8 * k + seg) & 1;
+      const uint32_t key_v = here ? key[v] : 0u;
+      uint32_t m = key_v;
+      if (here) m = dense_max(key, row_at(p, base, lists, v), sl, [](uint32_t w) { return w; }, m);
+      m = seg_max(m);
+      if (here && sl == 0) m1[v] = m;
+      bits |= seg_bits(here && m == key_v) << (8 * k);
+    }
+    if (lane == 0) cand[W] = bits;
+    return;
+  }
   // (a token without neighbours needs none of its words)
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
@@ -200,7 +225,14 @@ __global__ __launch_bounds__(kPhaseThreads) void merge_onehop(ShallowParams p, i
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
     uint32_t m = quad_max(key, w0[k], own[k]);        // a token is its own neighbour
-    for (int i = sl + kSegW; __any(i < r[k].n); i += kSegW) m = quad_max(key, i < r[k].n ? word_at(r[k], i) : 0, m);
+    if (__any(sl + kSegW < r[k].n)) {                 // (the next word on its way)
+      uint32_t w = sl + kSegW < r[k].n ? word_at(r[k], sl + kSegW) : 0;
+      for (int i = sl + kSegW; __any(i < r[k].n); i += kSegW) {
+        const uint32_t next = i + kSegW < r[k].n ? word_at(r[k], i + kSegW) : 0;
+        m = quad_max(key, w, m);
+        w = next;
+      }
+    }
     m = seg_max(m);
     if (on[k] && sl == 0) m1[W * kTile + 8 * k + seg] = m;
     bits |= seg_bits(on[k] && m == own[k]) << (8 * k);
@@ -245,10 +277,17 @@ __global__ __launch_bounds__(kPhaseThreads) void merge_twohop(ShallowParams p, i
     if (!on) r.n = 0;
     const uint32_t ku = key[u];
     uint32_t m = 0;
-    for (int i = sl; __any(i < r.n); i += kSegW) {
-      uint32_t w = i < r.n ? word_at(r, i) : 0;
-      w = (w & 0xFFFF0000u) | still(live, w);         // neighbours still there at the start of the round
-      m = quad_max(m1, w, m);
+    auto here = [&](uint32_t w) { return (w & 0xFFFF0000u) | still(live, w); };   // neighbours still there at the start of the round
+    auto left = [&](int i) { return here(i < r.n ? word_at(r, i) : 0); };
+    if (__any(r.dense)) {
+      m = dense_max(m1, r, sl, here, m);
+    } else {
+      uint32_t w = left(sl);
+      for (int i = sl; __any(i < r.n); i += kSegW) {
+        const uint32_t next = left(i + kSegW);
+        m = quad_max(m1, w, m);
+        w = next;
+      }
     }
     const bool pick = on && seg_max(m) == ku;
     bits |= seg_bits(pick) << (8 * k);

@@ -321,3 +321,32 @@ def test_low_thresholds_pay_nothing_for_balls():
         took.append(parity.least_us(lambda: plan.run(K, V)))
     print("8 and 32 heads", [round(t, 1) for t in took], flush=True)
     assert took[1] < 3.35 * took[0]
+
+
+def test_merge_rounds_on_dense_graphs():
+    # two clusters: rows of bits.  The grid rounds of the merge take 0.56 to 0.63 of what finding the pairs takes, 0.85 to 1.0
+    # where a quad took the half tiles of such rows together
+    import torch
+    from paper_2507_06517_amd import binding as sb
+    for H, n in ((2, 8192), (2, 12000)):
+        g = torch.Generator(device="cuda").manual_seed(1)
+        centres = torch.randn((H, 2, 128), generator=g, device="cuda")
+        at = torch.randint(0, 2, (H, n), generator=g, device="cuda")
+        K = (centres.gather(1, at[:, :, None].expand(H, n, 128)) + 0.1 * torch.randn((H, n, 128), generator=g, device="cuda")).half().unsqueeze(0)
+        plan = sb.plan_shallow(K, "f16", 0.9, 0.9, 64)
+        plan.run(K, K)
+        took = []
+        sb.spindle_profile(1)
+        try:
+            for _ in range(6):
+                plan.run(K, K)
+                torch.cuda.synchronize()
+                by = {}
+                for name, ms in sb.spindle_profile_read():
+                    by[name] = by.get(name, 0.0) + ms * 1e3
+                took.append((by["shallow_merge_grid"], by["shallow_rows"]))
+        finally:
+            sb.spindle_profile(0)
+        grid, rows = (min(x) for x in zip(*took))
+        print("tokens", n, "grid rounds, rows", round(grid, 1), round(rows, 1), flush=True)
+        assert grid < 0.74 * rows
