@@ -143,7 +143,7 @@ uint32_t *total;         // [UT][kBuckets] tokens per bucket
   int T, Tp, TW;           // tiles, rounded up to whole panels; words per row of tpairs
   int scan;                // 1: tokens are sorted and tpairs says which tiles count; 0: all tiles, positions = tokens
   int stages_per_item, njg;   // column stages of a block of the scan, runs of them in a problem
-  int stages_to_refine;    // of a block of shallow_refine
+  int refine_cuts;         // parts of such a block for shallow_refine
   uint32_t *todo;          // [scan_blocks] 1: left to shallow_refine
   int by[2];               // which tile pairs count: kBySketch, kByVector or, all of them, kByNone
   int scan_thr[2];         // theta in sketch units squared

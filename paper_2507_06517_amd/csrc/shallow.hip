@@ -39,7 +39,7 @@ size_t carve(ShallowParams &p, void *ws, int UT, int n) {
   p.TW = (p.T + 31) / 32;
   p.UT = UT;
   cut_stages(p, 2048);
-  p.stages_to_refine = p.stages_per_item;
+  p.refine_cuts = 1;
   p.Xe = cv.take<_Float16>((N + 512) * kHeadDim);   // the similarity loop stages up to 5 tiles past the last token
   p.Xh = p.dtype == SPINDLE_F32 ? cv.take<_Float16>(N * kHeadDim) : nullptr;
   p.Xl = p.Xe;                                      // (for shallow_rows only, which is done when entries are written)
@@ -193,7 +193,11 @@ spindle_status run_shallow(int phases,
     p.balls |= p.asks[i];
   }
   // (where balls are asked, what a block does before its first products is more; never more blocks than `todo` has room for)
-  if (p.balls) cut_stages(p, 1024);
+  if (p.balls) {
+    const int to_refine = p.stages_per_item;
+    cut_stages(p, 1024);
+    p.refine_cuts = (p.stages_per_item + to_refine - 1) / to_refine;
+  }
   if (phases & kPhaseGraph) {
     // zero: counters, and where there is a scan its errors and marks; codebooks
     const size_t nzero = zero_words(p.UT, n, p.scan);
