@@ -1113,21 +1113,24 @@ __global__ __launch_bounds__(kRefineThreads, 2) void shallow_refine(ShallowParam
 // gathered rows, mostly from L2, products and tests), so what counts is blocks per compute unit: LDS and registers
 // allow four with two stages and 28 steps' bits, where three stages and 32 steps allowed three.  16 problems of 32768 tokens
 // 173 -> 146 us, 128 of 8192 in clusters of 128 200 -> 168, 64 of 32768 with half isolated 379 -> 315.
-constexpr int kRowsQueue = 192;                    // waiting pairs per wave
 constexpr int kRowsThreads = 256;
 constexpr int kRowsPitch = kWave + 2;              // result bits of a step, and a word so that one lane's bits of 32 steps are 32 banks
 
-template <int DT, int kCols>
+// kAll: problems that are not sorted, of 29 to 32 tiles.  Every block takes all tiles, so one batch has to hold them; that four
+// blocks still fit, fewer pairs wait.  The kernel on 32 problems of 1000 tokens 49 us with 28
+// steps, 38 so, on 128 74 and 66.
+template <int DT, int kCols, bool kAll>
 struct RowsLds {
+  static constexpr int kQueue = kAll ? 176 : 192;                        // waiting pairs per wave
   static constexpr int kPart = kTile * 256;                              // 32 rows of 128 two-byte elements
   static constexpr int kStage = kCols * kPart * (DT == SPINDLE_F32 ? 2 : 1);
   static constexpr int kStages = kCols == 1 && DT == SPINDLE_F32 ? 3 : 2;
-  static constexpr int kBatch = kCols > 1 ? 16 : DT == SPINDLE_F32 ? 32 : 28;   // steps whose result bits a wave keeps
+  static constexpr int kBatch = kCols > 1 ? 16 : DT == SPINDLE_F32 || kAll ? 32 : 28;   // steps whose result bits a wave keeps
   char stage[kStages][kStage];
   float inv[kBatch * kCols][kTile];
   uint16_t tok[kBatch * kCols][kTile];
   uint16_t bits[4][kBatch * kRowsPitch];
-  __attribute__((aligned(4))) uint16_t queue[4][kRowsQueue];                                         // at the end: degree << 16 | words of every lane
+  __attribute__((aligned(4))) uint16_t queue[4][kQueue];                                         // at the end: degree << 16 | words of every lane
   int ntiles;
   __device__ uint16_t *tiles() { return reinterpret_cast<uint16_t *>(this + 1); }  // [T] column tile | 1 << (11 + row tile of the block)
   static size_t bytes(int T) { return sizeof(RowsLds) + align_up((size_t)T * sizeof(uint16_t), 16); }
@@ -1135,8 +1138,9 @@ struct RowsLds {
 
 // A wave's rows r0 .. r0 + nr - 1 of row tile R from the bits in memory (word t of a row's room: column tile t, written for the
 // tiles of the list): counted, and turned into words in place.  A row is in registers before any of
-// it is overwritten, kRows rows at a time for the latency of the reads.  16 problems of 32768 similar tokens: 9.9 ms for
-// the kernel, 19.6 where cosines were taken again to write words whose number was known by then.
+// it is overwritten, kRows rows at a time for the latency of the reads: a block that has one tile more than a batch holds is the last
+// to end, 20 us with four at a time, 12 with sixteen (the call on 4 problems of 23000 tokens 203 us and 196).  16 problems of
+// 32768 similar tokens: 9.9 ms for the kernel, 19.6 where cosines were taken again to write words whose number was known by then.
 template <int kRows, int kWords>
 __device__ __forceinline__ void rows_from_memory(const ShallowParams &p, int ut, int R, int r0, int nr, int rows_here,
                                                  const uint16_t *tiles, int ntiles) {
@@ -1212,10 +1216,10 @@ __device__ __forceinline__ void rows_from_memory(const ShallowParams &p, int ut,
   }
 }
 
-template <int DT, int kCols>
+template <int DT, int kCols, bool kAll>
 __global__ __launch_bounds__(kRowsThreads, kCols == 1 && DT != SPINDLE_F32 ? 4 : 2) void shallow_rows(ShallowParams p, int nblk) {
   typedef Mma<DT == SPINDLE_BF16 ? SPINDLE_BF16 : SPINDLE_F16> M;
-  typedef RowsLds<DT, kCols> L;
+  typedef RowsLds<DT, kCols, kAll> L;
   constexpr bool kSplit = DT == SPINDLE_F32;
   constexpr int kRT = 4 / kCols;                       // row tiles of the block
   extern __shared__ __attribute__((aligned(1024))) char lds_raw[];
@@ -1401,7 +1405,7 @@ __global__ __launch_bounds__(kRowsThreads, kCols == 1 && DT != SPINDLE_F32 ? 4 :
       bits[s * kRowsPitch + lane] = (uint16_t)yes;
       for (;;) {                                       // one close pair per lane at a time into the queue
         const unsigned long long m = __ballot(close != 0);
-        if (nq > kRowsQueue - kWave || (m == 0 && nq > 0 && s + 1 == ns)) {
+        if (nq > L::kQueue - kWave || (m == 0 && nq > 0 && s + 1 == ns)) {
           // (the bits are written as halves elsewhere and as words here: keep the compiler from reordering them)
           asm volatile("" ::: "memory");
           for (int j = lane; j < nq; j += kWave) {
@@ -1465,7 +1469,8 @@ __global__ __launch_bounds__(kRowsThreads, kCols == 1 && DT != SPINDLE_F32 ? 4 :
   }
   if (nbatch > 1) {
     __syncthreads();                                   // (and the words in memory are every wave's to read)
-    if (ntiles <= 8 * kWave) rows_from_memory<4, 8>(p, ut, R, member * (kTile / kCols), kTile / kCols, rows_here, tiles, ntiles);
+    if (kCols == 1 && ntiles <= kWave) rows_from_memory<16, 1>(p, ut, R, member * (kTile / kCols), kTile / kCols, rows_here, tiles, ntiles);
+    else if (ntiles <= 8 * kWave) rows_from_memory<4, 8>(p, ut, R, member * (kTile / kCols), kTile / kCols, rows_here, tiles, ntiles);
     else rows_from_memory<1, 32>(p, ut, R, member * (kTile / kCols), kTile / kCols, rows_here, tiles, ntiles);
     return;
   }
@@ -1475,7 +1480,7 @@ __global__ __launch_bounds__(kRowsThreads, kCols == 1 && DT != SPINDLE_F32 ? 4 :
     deg += __popc(m);
     words += m != 0;
   }
-  static_assert(kRowsQueue * sizeof(uint16_t) >= kWave * sizeof(uint32_t), "the counts take the queue's place");
+  static_assert(L::kQueue * sizeof(uint16_t) >= kWave * sizeof(uint32_t), "the counts take the queue's place");
   auto counts = [&](int w) { return reinterpret_cast<uint32_t *>(l.queue[w]); };
   asm volatile("" ::: "memory");                       // (read as halves before)
   counts(wave)[lane] = (uint32_t)deg << 16 | (uint32_t)words;
@@ -1563,21 +1568,25 @@ namespace {
 // How the tile pairs that count are found; of K and V the one that is looked at first.
 int most_by(const ShallowParams &p) { return p.UT > p.U && p.by[1] > p.by[0] ? p.by[1] : p.by[0]; }
 
-template <int DT, int kCols>
+template <int DT, int kCols, bool kAll>
 spindle_status launch_rows(const ShallowParams &p, hipStream_t st) {
+  typedef RowsLds<DT, kCols, kAll> L;
   constexpr int kRT = 4 / kCols;
   static LdsLimit lim;
-  if (spindle_status e = allow_lds(lim, reinterpret_cast<const void *>(&shallow_rows<DT, kCols>), RowsLds<DT, kCols>::bytes(2048))) return e;
+  if (spindle_status e = allow_lds(lim, reinterpret_cast<const void *>(&shallow_rows<DT, kCols, kAll>), L::bytes(2048))) return e;
   const int nblk = (p.T + kRT - 1) / kRT;
-  const size_t lds = RowsLds<DT, kCols>::bytes(p.T);
+  const size_t lds = L::bytes(p.T);
   ProfScope ps("shallow_rows", st, most_by(p) == kByNone);
-  hipLaunchKernelGGL((shallow_rows<DT, kCols>), dim3(xcd_grid((size_t)p.UT * nblk)), dim3(kRowsThreads), lds,
+  hipLaunchKernelGGL((shallow_rows<DT, kCols, kAll>), dim3(xcd_grid((size_t)p.UT * nblk)), dim3(kRowsThreads), lds,
                      st, p, nblk);
   return SPINDLE_OK;
 }
 template <int DT>
 spindle_status launch_rows(const ShallowParams &p, hipStream_t st) {
-  return rows_waves(p.UT, p.T) == 4 ? launch_rows<DT, 4>(p, st) : launch_rows<DT, 1>(p, st);
+  if (rows_waves(p.UT, p.T) == 4) return launch_rows<DT, 4, false>(p, st);
+  if constexpr (DT != SPINDLE_F32)
+    if (p.T > RowsLds<DT, 1, false>::kBatch && p.T <= RowsLds<DT, 1, true>::kBatch && most_by(p) == kByNone) return launch_rows<DT, 1, true>(p, st);
+  return launch_rows<DT, 1, false>(p, st);
 }
 }  // namespace
 

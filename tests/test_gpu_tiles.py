@@ -350,3 +350,21 @@ def test_merge_rounds_on_dense_graphs():
         grid, rows = (min(x) for x in zip(*took))
         print("tokens", n, "grid rounds, rows", round(grid, 1), round(rows, 1), flush=True)
         assert grid < 0.74 * rows
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_one_more_tile_than_a_batch_held(dtype):
+    # problems that are not sorted: every block of the list kernel takes all tiles, and 29 of them are no more than one batch
+    import torch
+    from paper_2507_06517_amd import binding as sb
+    took = []
+    for H, n in ((19, 896), (18, 928)):
+        g = torch.Generator(device="cuda").manual_seed(2)
+        centres = torch.randn((H, 20, 128), generator=g, device="cuda")
+        at = torch.randint(0, 20, (H, n), generator=g, device="cuda")
+        K = (centres.gather(1, at[:, :, None].expand(H, n, 128)) + 0.1 * torch.randn((H, n, 128), generator=g, device="cuda"))
+        K = K.to(sb.torch_dtype(dtype)).unsqueeze(0)
+        plan = sb.plan_shallow(K, dtype, 0.95, 0.95, 64)
+        took.append(parity.least_us(lambda: plan.run(K, K), calls=20))
+    print("28 and 29 tiles", [round(t, 1) for t in took], flush=True)
+    assert took[1] < 1.1 * took[0]
