@@ -297,7 +297,7 @@ def test_codebook_order(oracle, dtype, sizes):
     parity.check_shallow_layer(oracle, L, tensors=("v",), debug=False, cap=max(1, len(sizes) // 3))
 
 
-@pytest.mark.parametrize("dtype,theta_k,theta_v", [("f16", 0.95, 0.6), ("bf16", 0.75, 0.9), ("f32", 0.88, 0.86)])
+@pytest.mark.parametrize("dtype,theta_k,theta_v", [("f16", 0.95, 0.6), ("bf16", 0.75, 0.9), ("f32", 0.81, 0.79)])
 def test_balls_for_one_of_the_tensors(oracle, dtype, theta_k, theta_v):
     # K and V differ in whether the scan asks the balls, or the sketches at all
     L = wl.small_random(75, dtype, B=1, H=64, l=4300, lw=1, cap=600, n_centroids=40, noise_frac=0.3)
