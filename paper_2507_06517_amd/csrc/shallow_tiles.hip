@@ -1116,16 +1116,19 @@ __global__ __launch_bounds__(kRefineThreads, 2) void shallow_refine(ShallowParam
 constexpr int kRowsThreads = 256;
 constexpr int kRowsPitch = kWave + 2;              // result bits of a step, and a word so that one lane's bits of 32 steps are 32 banks
 
-// kAll: problems that are not sorted, of 29 to 32 tiles.  Every block takes all tiles, so one batch has to hold them; that four
-// blocks still fit, fewer pairs wait.  The kernel on 32 problems of 1000 tokens 49 us with 28
-// steps, 38 so, on 128 74 and 66.
-template <int DT, int kCols, bool kAll>
+// kShort: problems whose list of tiles is short enough (kShortTiles) that four blocks fit with 32 steps and fewer waiting pairs,
+// too.  Where tokens are not sorted every block takes all tiles; where they are, the few blocks that take the most end last.  The
+// kernel on 32 problems of 1000 tokens 49 us with 28 steps, 38 so, on 128 74 and 66, on 16 of 2060 in seven clusters 45 and 31.
+constexpr int kShortTiles = 120;
+constexpr size_t kLdsBytes = 160 * 1024;           // of a compute unit
+
+template <int DT, int kCols, bool kShort>
 struct RowsLds {
-  static constexpr int kQueue = kAll ? 176 : 192;                        // waiting pairs per wave
+  static constexpr int kQueue = kShort ? 160 : 192;                      // waiting pairs per wave
   static constexpr int kPart = kTile * 256;                              // 32 rows of 128 two-byte elements
   static constexpr int kStage = kCols * kPart * (DT == SPINDLE_F32 ? 2 : 1);
   static constexpr int kStages = kCols == 1 && DT == SPINDLE_F32 ? 3 : 2;
-  static constexpr int kBatch = kCols > 1 ? 16 : DT == SPINDLE_F32 || kAll ? 32 : 28;   // steps whose result bits a wave keeps
+  static constexpr int kBatch = kCols > 1 ? 16 : DT == SPINDLE_F32 || kShort ? 32 : 28;   // steps whose result bits a wave keeps
   char stage[kStages][kStage];
   float inv[kBatch * kCols][kTile];
   uint16_t tok[kBatch * kCols][kTile];
@@ -1133,7 +1136,7 @@ struct RowsLds {
   __attribute__((aligned(4))) uint16_t queue[4][kQueue];                                         // at the end: degree << 16 | words of every lane
   int ntiles;
   __device__ uint16_t *tiles() { return reinterpret_cast<uint16_t *>(this + 1); }  // [T] column tile | 1 << (11 + row tile of the block)
-  static size_t bytes(int T) { return sizeof(RowsLds) + align_up((size_t)T * sizeof(uint16_t), 16); }
+  static constexpr size_t bytes(int T) { return sizeof(RowsLds) + ((size_t)T * sizeof(uint16_t) + 15) / 16 * 16; }
 };
 
 // A wave's rows r0 .. r0 + nr - 1 of row tile R from the bits in memory (word t of a row's room: column tile t, written for the
@@ -1216,10 +1219,10 @@ __device__ __forceinline__ void rows_from_memory(const ShallowParams &p, int ut,
   }
 }
 
-template <int DT, int kCols, bool kAll>
+template <int DT, int kCols, bool kShort>
 __global__ __launch_bounds__(kRowsThreads, kCols == 1 && DT != SPINDLE_F32 ? 4 : 2) void shallow_rows(ShallowParams p, int nblk) {
   typedef Mma<DT == SPINDLE_BF16 ? SPINDLE_BF16 : SPINDLE_F16> M;
-  typedef RowsLds<DT, kCols, kAll> L;
+  typedef RowsLds<DT, kCols, kShort> L;
   constexpr bool kSplit = DT == SPINDLE_F32;
   constexpr int kRT = 4 / kCols;                       // row tiles of the block
   extern __shared__ __attribute__((aligned(1024))) char lds_raw[];
@@ -1568,24 +1571,26 @@ namespace {
 // How the tile pairs that count are found; of K and V the one that is looked at first.
 int most_by(const ShallowParams &p) { return p.UT > p.U && p.by[1] > p.by[0] ? p.by[1] : p.by[0]; }
 
-template <int DT, int kCols, bool kAll>
+template <int DT, int kCols, bool kShort>
 spindle_status launch_rows(const ShallowParams &p, hipStream_t st) {
-  typedef RowsLds<DT, kCols, kAll> L;
+  typedef RowsLds<DT, kCols, kShort> L;
   constexpr int kRT = 4 / kCols;
   static LdsLimit lim;
-  if (spindle_status e = allow_lds(lim, reinterpret_cast<const void *>(&shallow_rows<DT, kCols, kAll>), L::bytes(2048))) return e;
+  if (spindle_status e = allow_lds(lim, reinterpret_cast<const void *>(&shallow_rows<DT, kCols, kShort>), L::bytes(2048))) return e;
   const int nblk = (p.T + kRT - 1) / kRT;
   const size_t lds = L::bytes(p.T);
   ProfScope ps("shallow_rows", st, most_by(p) == kByNone);
-  hipLaunchKernelGGL((shallow_rows<DT, kCols, kAll>), dim3(xcd_grid((size_t)p.UT * nblk)), dim3(kRowsThreads), lds,
+  hipLaunchKernelGGL((shallow_rows<DT, kCols, kShort>), dim3(xcd_grid((size_t)p.UT * nblk)), dim3(kRowsThreads), lds,
                      st, p, nblk);
   return SPINDLE_OK;
 }
 template <int DT>
 spindle_status launch_rows(const ShallowParams &p, hipStream_t st) {
   if (rows_waves(p.UT, p.T) == 4) return launch_rows<DT, 4, false>(p, st);
-  if constexpr (DT != SPINDLE_F32)
-    if (p.T > RowsLds<DT, 1, false>::kBatch && p.T <= RowsLds<DT, 1, true>::kBatch && most_by(p) == kByNone) return launch_rows<DT, 1, true>(p, st);
+  if constexpr (DT != SPINDLE_F32) {
+    static_assert(RowsLds<DT, 1, true>::bytes(kShortTiles) <= kLdsBytes / 4, "four blocks");
+    if (p.T > RowsLds<DT, 1, false>::kBatch && p.T <= kShortTiles) return launch_rows<DT, 1, true>(p, st);
+  }
   return launch_rows<DT, 1, false>(p, st);
 }
 }  // namespace

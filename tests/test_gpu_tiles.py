@@ -368,3 +368,12 @@ def test_one_more_tile_than_a_batch_held(dtype):
         took.append(parity.least_us(lambda: plan.run(K, K), calls=20))
     print("28 and 29 tiles", [round(t, 1) for t in took], flush=True)
     assert took[1] < 1.1 * took[0]
+
+
+@pytest.mark.parametrize("l", [3840, 3841])
+def test_batches_of_short_problems(oracle, l):
+    # 120 tiles are the most that a list of 32 steps is kept for; blocks of few and of more than 28 of them, close pairs waiting
+    L = wl.small_random(76, "f16", B=1, H=9, l=l, lw=1, cap=l // 8, n_centroids=7, noise_frac=0.1, drift_sigma=0.002)
+    for theta in (0.9, 0.97):
+        L.theta_k = L.theta_v = theta
+        parity.check_shallow_layer(oracle, L, units=[(0, 0), (0, 8)], debug=False)
