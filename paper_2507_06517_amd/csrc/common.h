@@ -142,6 +142,17 @@ __device__ __forceinline__ unsigned long long order_key(double cs) {
 
 __device__ __forceinline__ int lane_id() { return threadIdx.x & 63; }
 
+// Sum over the lanes up to this one, by lane shifts (no trip through LDS).
+__device__ __forceinline__ int lanes_up_to(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);   // row_shr 1, 2, 4, 8 within 16 lanes
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);   // lane 15 of rows 0 and 2 to the row behind
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);   // lane 31 to the two rows behind
+  return v;
+}
+
 // 16 bytes per lane from global memory straight into LDS: lane i's piece lands at
 // lds_addr + 16 i (lds_addr wave-uniform).  Issued as assembly on purpose: the compiler
 // would put a wait for the load in front of every later LDS read of the kernel, since it

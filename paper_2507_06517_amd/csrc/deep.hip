@@ -534,17 +534,6 @@ constexpr int kCopyPitch = kBins + 8;                  // in other banks
 __host__ __device__ inline int unit_raw(int lc) { return (lc + kUnitStep - 1) / kUnitStep * kUnitStep + 2 * kUnitRadius; }
 inline size_t unit_lds(int lc) { return ((size_t)unit_raw(lc) + kCopies * kCopyPitch) * sizeof(int); }
 
-// Sum over the lanes up to this one, by lane shifts (no trip through LDS).
-__device__ __forceinline__ int lanes_up_to(int v) {
-  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);   // row_shr 1, 2, 4, 8 within 16 lanes
-  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);
-  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);
-  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);
-  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);   // lane 15 of rows 0 and 2 to the row behind
-  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);   // lane 31 to the two rows behind
-  return v;
-}
-
 __global__ __launch_bounds__(kSelThreads) void deep_select_unit(SelectParams p) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   __shared__ __attribute__((aligned(16))) uint32_t cand[kUnitRank + 4];

@@ -31,10 +31,17 @@ typedef int i16v __attribute__((ext_vector_type(16)));
 // behind a mask the vector work was twice the matrix instructions.
 constexpr int kStepOffset = 3008;
 constexpr float kStepEnd = 0.345f, kStep = 0.388f, kMeanSome = 0.15f, kMeanMost = 1.9f;
-// Tokens that are near no pivot (a cosine of 0.73, the last step from 0.88 on) go ahead of the others, and so do the
-// few of a pivot that is alone (kAlone tokens): what is isolated stands together then and doesn't widen the tiles of what is
-// not.  Where sketches aren't asked (kByVector) all tokens keep to their pivots.
-constexpr int kMeanOf = 128, kNearStep = 5, kAlone = 8;
+// Tokens that are near no pivot (a cosine of 0.73, the last step from 0.88 on; without the mean, a product of kMeanNear of the
+// length left, between the largest of 1024 unrelated ones and nearly all of a cluster's own) go ahead of the others: what is isolated
+// stands together then and doesn't widen the tiles of what is not.  So do pivots that have no other token, where more than one token in
+// kFarShare is near none, and what a second pivot took of a cluster: a kRemnant-th of what buckets have as a rule, at most kFewest
+// tokens.  More than that is something else, the heavy tokens of clusters in keys with a common mean, and a tile of them is marked for
+// ten clusters.  16 problems of 8192 tokens in 128 clusters, a twentieth of them heavy, with a mean of half their length, 4 of 23000 in 200, 2 of
+// 18445 in 26, us per call: with the step above instead of kMeanNear and up to eight tokens to a pivot 220, 203, 243, now 166, 178, 235.
+// Where sketches aren't asked (kByVector) all tokens keep to their pivots but for the remnants.
+constexpr int kMeanOf = 128, kNearStep = 5, kFarShare = 16, kRemnant = 128;
+constexpr uint32_t kFewest = 8;
+constexpr float kMeanNear = 0.58f;
 constexpr int kPivotThreads = 256;
 
 template <int kTiles>                                  // of 32 tokens per wave
@@ -209,12 +216,12 @@ __global__ __launch_bounds__(kPivotThreads, 2) void shallow_pivots(ShallowParams
     for (int v = 0; v < 16; ++v) x16[v] = off + 15 - v + ((15 - v) << ahead);
     compare([&](int) { return x16; });
   }
-  const int near = p.by[ut / p.U] != kBySketch ? INT32_MIN : some ? 1 << bits : kNearStep << 14;
+  const int near = p.by[ut / p.U] != kBySketch ? INT32_MIN : some ? (int)((kMeanNear - kStepEnd) * left) : kNearStep << 14;
 #pragma unroll
   for (int r = 0; r < kTiles; ++r) {
     const int own = (best[r] & mask) | (1023 - (best_pt[r] * 32 + mma_row(15 - (best[r] & 15), g)));
     const int o = __shfl_xor(own, 32), top = o > own ? o : own, pivot = 1023 - (top & 1023);
-    const int b = top >= near ? kPivots + pivot : pivot;
+    const int b = max(best[r], __shfl_xor(best[r], 32)) >= near ? kPivots + pivot : pivot;
     if (g == 0 && tok[r] < n) {
       p.bucket[(size_t)ut * n + tok[r]] = (uint16_t)b;
       atomicAdd(&cnt[b], 1u);
@@ -246,6 +253,7 @@ constexpr int kOrderThreads = 1024;
 __global__ __launch_bounds__(kOrderThreads) void shallow_order(ShallowParams p, int nblk, int per) {
   __shared__ int cursor[kBuckets];
   __shared__ uint32_t wsum[kOrderThreads / kWave];
+  __shared__ uint2 sums[kOrderThreads / kWave];
   static_assert(kBuckets == 2 * kOrderThreads, "two buckets per thread");
   const int item = xcd_item();
   if (item >= p.UT * nblk) return;
@@ -257,18 +265,30 @@ __global__ __launch_bounds__(kOrderThreads) void shallow_order(ShallowParams p, 
   const int b = on ? (int)p.bucket[base + tok] : 0;
   const uint2 total = reinterpret_cast<const uint2 *>(p.total + (size_t)ut * kBuckets)[tid];
   const ushort2 before = reinterpret_cast<const ushort2 *>(p.before + ((size_t)ut * nblk + blk) * kBuckets)[tid];
-  // both kinds of buckets at once: those that go first in the low half (at most 65535 tokens in all)
-  auto half = [](int bucket, uint32_t x) { return bucket < kPivots || x <= (uint32_t)kAlone ? 0 : 16; };
+  // tokens near no pivot, near one, and how many of the latter share a bucket with one of them on average
+  uint32_t count = 2 * tid < kPivots ? total.x + total.y : (total.x + total.y) << 16;   // (at most 65535 in all)
+  uint32_t square = 2 * tid < kPivots ? 0u : (total.x * total.x >> 7) + (total.y * total.y >> 7);
+  count = (uint32_t)lanes_up_to((int)count);
+  square = (uint32_t)lanes_up_to((int)square);
+  if (lane == kWave - 1) sums[wave] = make_uint2(count, square);
+  __syncthreads();
+  count = square = 0;
+#pragma unroll
+  for (int w = 0; w < kOrderThreads / kWave; ++w) {
+    count += sums[w].x;
+    square += sums[w].y;
+  }
+  const uint32_t nfar = count & 0xFFFFu, shared = square / max(1u, count >> 16);   // (shared: 128 of them and more)
+  static_assert(kRemnant == 128, "what the squares are shifted by");
+  const uint32_t few = max(nfar * (uint32_t)kFarShare >= (uint32_t)n ? 1u : 0u, min(shared, kFewest));
+  // both kinds of buckets at once: those that go first in the low half
+  auto half = [&](int bucket, uint32_t x) { return bucket < kPivots || x <= few ? 0 : 16; };
   const int h0 = half(2 * tid, total.x), h1 = half(2 * tid + 1, total.y);
   const uint32_t own = (total.x << h0) + (total.y << h1);
-  uint32_t incl = own, all = 0;
-#pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) {
-    const uint32_t x = __shfl_up(incl, o);
-    if (lane >= o) incl += x;
-  }
+  uint32_t incl = (uint32_t)lanes_up_to((int)own), all = 0;
   if (lane == kWave - 1) wsum[wave] = incl;
   __syncthreads();
+#pragma unroll
   for (int w = 0; w < kOrderThreads / kWave; ++w) {
     const uint32_t x = wsum[w];
     incl += w < wave ? x : 0u;

@@ -377,3 +377,24 @@ def test_batches_of_short_problems(oracle, l):
     for theta in (0.9, 0.97):
         L.theta_k = L.theta_v = theta
         parity.check_shallow_layer(oracle, L, units=[(0, 0), (0, 8)], debug=False)
+
+
+def test_order_of_keys_with_a_mean():
+    # 128 clusters, some of their tokens heavy: a mean of half the clusters' length leaves the order nearly what it is without
+    # one (1.08 times the time; 1.43 where clusters whose products end low, and heavy tokens, were taken for isolated ones)
+    import torch
+    from paper_2507_06517_amd import binding as sb
+    g = torch.Generator(device="cuda").manual_seed(5)
+    H, n = 8, 8192
+    centres = torch.randn((H, 128, 128), generator=g, device="cuda")
+    at = torch.randint(0, 128, (H, n), generator=g, device="cuda")
+    x = centres.gather(1, at[:, :, None].expand(H, n, 128)) + 0.1 * torch.randn((H, n, 128), generator=g, device="cuda")
+    x = torch.where(torch.rand((H, n, 1), generator=g, device="cuda") < 0.05, 4.0 * x, x)
+    mean = torch.randn((H, 1, 128), generator=g, device="cuda")
+    took = []
+    for share in (0.0, 0.5):
+        K = (x + share * mean).half().unsqueeze(0)
+        plan = sb.plan_shallow(K, "f16", 0.98, 0.95, 1024)
+        took.append(parity.least_us(lambda: plan.run(K, K), calls=20))
+    print("without a mean, with", [round(t, 1) for t in took], flush=True)
+    assert took[1] < 1.25 * took[0]
