@@ -155,7 +155,7 @@ __device__ __forceinline__ uint32_t quad_max(const uint32_t *a, uint32_t word, u
 
 // Where a row is dense, a lane takes a half tile (or word) of its own, four in flight: the lanes' half tiles follow each
 // other, and instructions count, of which quad_max has half as many again.  Two grid rounds of 4 problems of 8192 tokens
-// in two clusters 208 us by quads and 143 so, of 2 of 40515 tokens with a common mean 1823 and 1486.
+// in two clusters 208 us by quads and 143 so, of 2 of 40515 tokens with a common mean 1823 and 1420.
 template <typename L>
 __device__ __forceinline__ uint32_t dense_max(const uint32_t *a, const Row &r, int sl, L look, uint32_t m) {
   for_words(r, sl, [&](uint32_t w) {
@@ -176,7 +176,9 @@ __device__ __forceinline__ uint32_t seg_bits(bool on) {
 // ---------------------------------------------------------------- grid rounds
 // Wave index within a problem = word of the bit arrays = 32 positions; pass k of 4 takes positions
 // 8 k .. 8 k + 7 of it, one per segment.
-__global__ __launch_bounds__(kPhaseThreads) void merge_onehop(ShallowParams p, int round) {
+// (Eight waves per SIMD: 128 problems of 8192 tokens in clusters, both rounds 90 us, with the registers for six, the next word on
+// its way, 97.)
+__global__ __launch_bounds__(kPhaseThreads, 8) void merge_onehop(ShallowParams p, int round) {
   const int ut = blockIdx.y, W = (int)blockIdx.x * (kPhaseThreads / kWave) + (int)(threadIdx.x >> 6);
   if (W >= p.T) return;
   const int lane = lane_id(), seg = lane / kSegW, sl = lane & (kSegW - 1);
@@ -225,14 +227,7 @@ __global__ __launch_bounds__(kPhaseThreads) void merge_onehop(ShallowParams p, i
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
     uint32_t m = quad_max(key, w0[k], own[k]);        // a token is its own neighbour
-    if (__any(sl + kSegW < r[k].n)) {                 // (the next word on its way)
-      uint32_t w = sl + kSegW < r[k].n ? word_at(r[k], sl + kSegW) : 0;
-      for (int i = sl + kSegW; __any(i < r[k].n); i += kSegW) {
-        const uint32_t next = i + kSegW < r[k].n ? word_at(r[k], i + kSegW) : 0;
-        m = quad_max(key, w, m);
-        w = next;
-      }
-    }
+    for (int i = sl + kSegW; __any(i < r[k].n); i += kSegW) m = quad_max(key, i < r[k].n ? word_at(r[k], i) : 0, m);
     m = seg_max(m);
     if (on[k] && sl == 0) m1[W * kTile + 8 * k + seg] = m;
     bits |= seg_bits(on[k] && m == own[k]) << (8 * k);
@@ -240,7 +235,7 @@ __global__ __launch_bounds__(kPhaseThreads) void merge_onehop(ShallowParams p, i
   if (lane == 0) cand[W] = bits;
 }
 
-__global__ __launch_bounds__(kPhaseThreads) void merge_twohop(ShallowParams p, int round) {
+__global__ __launch_bounds__(kPhaseThreads, 8) void merge_twohop(ShallowParams p, int round) {
   const int ut = blockIdx.y, W = (int)blockIdx.x * (kPhaseThreads / kWave) + (int)(threadIdx.x >> 6);
   if (W >= p.T) return;
   const int lane = lane_id(), seg = lane / kSegW, sl = lane & (kSegW - 1);
@@ -278,17 +273,8 @@ __global__ __launch_bounds__(kPhaseThreads) void merge_twohop(ShallowParams p, i
     const uint32_t ku = key[u];
     uint32_t m = 0;
     auto here = [&](uint32_t w) { return (w & 0xFFFF0000u) | still(live, w); };   // neighbours still there at the start of the round
-    auto left = [&](int i) { return here(i < r.n ? word_at(r, i) : 0); };
-    if (__any(r.dense)) {
-      m = dense_max(m1, r, sl, here, m);
-    } else {
-      uint32_t w = left(sl);
-      for (int i = sl; __any(i < r.n); i += kSegW) {
-        const uint32_t next = left(i + kSegW);
-        m = quad_max(m1, w, m);
-        w = next;
-      }
-    }
+    if (__any(r.dense)) m = dense_max(m1, r, sl, here, m);
+    else for (int i = sl; __any(i < r.n); i += kSegW) m = quad_max(m1, here(i < r.n ? word_at(r, i) : 0), m);
     const bool pick = on && seg_max(m) == ku;
     bits |= seg_bits(pick) << (8 * k);
     if (pick) {
