@@ -1062,14 +1062,17 @@ DeepLayout deep_layout(void *ws, int U, int l, int lw, int Rpad, int dtype) {
   return L;
 }
 
-// Workgroups per unit of deep_finish.  Each reads all keys of its unit, so there are no more of them than run at once: then the
-// copies come along for nothing (one per unit and a launch for the copies, and as chosen here, us: 8 units of 32736 positions 51.5,
-// 50.1, 1 of which 16384 are kept 43.5, 41.5, 8 of 65504 83, 81, 2 of 262112 142, 141).  More wait for each other, and what they
-// read grows with the square of the context: 192 units of 32736 positions 672 and, 16 workgroups each, 823, 8 of 131040 144 and 186, of
-// 524256 569 and 1683.  More than four per segment gain nothing.  (A single unit of 524256 positions takes 225 either way: three reads of
-// its keys by one workgroup are most of it.)
+// Workgroups per unit of deep_finish.  Each reads all keys of its unit, so there are no more of them than run at once on half
+// of the chip (the call may run beside others': three layers of 32768 tokens in a pipeline 2030 us with all of it, 2019 with half).  Then the
+// copies come along for nothing: one per unit and a launch for the copies, and as chosen here, us: 8 units of 32736 positions 51.5, 50.8,
+// 1 of which 16384 are kept 43.5, 41.5, 2 of 131040 86.9, 85.3.  More wait for each other, and what they read grows with the
+// square of the context: 192 units of 32736 positions 672 and, 16 workgroups each, 823, 8 of 131040 144 and 186, of 524256 569 and
+// 1683.  More than four per segment gain nothing.  (A single unit of 524256 positions takes 225 either way: three reads of its keys by one
+// workgroup are most of it.)
+constexpr int kFinishBlocks = 128;
+
 int finish_blocks(int U, int nseg) {
-  const int each = kBlocksAtOnce / U;
+  const int each = kFinishBlocks / U;
   return each < nseg ? 1 : (each < 4 * nseg ? each : 4 * nseg);
 }
 
