@@ -82,13 +82,15 @@ inline int scan_pays(int UT, int n) {
   return n >= 2048 || (n >= 1024 && UT * T * (T - 24) >= 18000);
 }
 // Tile pairs of all problems from which the scan pays for asking the balls around the tiles first, which takes shallow_window
-// and short blocks of shallow_scan some 10 us.  Calls, fp16, without and with, us: clusters, 16 problems of 4096 tokens (0.26
-// million) 118, 132, of 8192 (1.05) 162, 163, of 11000 (1.9) 192, 181 (with a third isolated 241, 243), of 12000 (2.25)
-// 208, 194; 128 of 4096 (2.1) 305, 299 (394, 409); 2 of 32768 (2.1) 188, 170 (with a fifth isolated 246, 237; kept rows of
-// repeated heads 270, 281).
+// and short blocks of shallow_scan some 10 us.  What they exclude depends on the rows (most in clusters, least where
+// many are isolated) and grows with the length, so the line is where calls on the whole cost the same: 108 calls of 0.3 to 2.2
+// million, clusters, drifting ones, a twentieth to half of the tokens isolated, common means, with balls against without: 0.3 to 0.6 1.07, to
+// 0.9 1.06, to 1.2 1.02, to 1.5 1.02, to 1.8 1.00, to 2.2 0.98.  Without and with, us: clusters, 16 problems of 8192 tokens (1.05) 153, 153, of
+// 11000 (1.9) 188, 180 (a third isolated 239, 241), 4 of 23000 (2.1) 178, 164 (half 320, 319), 2 of 28000 (1.5) 160, 155, of 32768 (2.1) 183, 165
+// (a fifth 272, 260), 128 of 4096 (2.1) 304, 291 (a third 394, 414); kept rows of repeated heads, 2 of 32768, 275, 285.
 inline int balls_pay(int UT, int n) {
   const long T = (n + 31) / 32;
-  return UT * T * T >= 2200000;
+  return UT * T * T >= 1600000;
 }
 // Below kBallMinTheta balls exclude too little: products of unrelated tokens end at about 0.65 for a tile, and the radius
 // and the errors add 0.2.  Calls, fp16, without and with, us, by theta: 64 problems of 8192 tokens in clusters 0.88 356, 319, 0.83 386, 365, 0.8

@@ -398,3 +398,19 @@ def test_order_of_keys_with_a_mean():
         took.append(parity.least_us(lambda: plan.run(K, K), calls=20))
     print("without a mean, with", [round(t, 1) for t in took], flush=True)
     assert took[1] < 1.25 * took[0]
+
+
+def test_fewer_tokens_take_less():
+    # two problems of 32768 clustered tokens took longer than two of 34816 where only the latter asked the balls
+    import torch
+    from paper_2507_06517_amd import binding as sb
+    took = []
+    for n in (32768, 34816):
+        g = torch.Generator(device="cuda").manual_seed(6)
+        centres = torch.randn((256, 128), generator=g, device="cuda")
+        at = torch.randint(0, 256, (n,), generator=g, device="cuda")
+        K = (centres[at] + 0.1 * torch.randn((n, 128), generator=g, device="cuda")).half().view(1, 1, n, 128)
+        plan = sb.plan_shallow(K, "f16", 0.98, 0.95, 1024)
+        took.append(parity.least_us(lambda: plan.run(K, K), calls=20))
+    print("32768 and 34816 tokens", [round(t, 1) for t in took], flush=True)
+    assert took[0] < 0.97 * took[1]
