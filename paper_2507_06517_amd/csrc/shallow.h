@@ -131,7 +131,7 @@ struct ShallowParams {
   float2 *inv_err;         // [UT][n] by token (scan): the factor, and the distance of the sketch from what it stands for (< 0: says nothing)
   uint16_t *bucket;        // [UT][n] bucket of a token
   uint32_t *mean;          // [UT][2] first eight coordinates of the pivots' mean
-uint32_t *total;         // [UT][kBuckets] tokens per bucket
+  uint32_t *total;         // [UT][kBuckets] tokens per bucket
   uint16_t *before;        // [UT][order blocks][kBuckets] place within a bucket of a block's first token of it
   uint8_t *sk;             // [UT][Tp][kSixBytes] sketches by position, in six-bit floats
   uint32_t *etile;         // [UT][Tp] what a tile's sketches may be off by in a product, sketch units squared

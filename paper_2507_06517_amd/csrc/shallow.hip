@@ -18,7 +18,7 @@ size_t cut_words(int UT) { return align_up((size_t)UT, 64); }   // (what follows
 // only the scan writes).
 size_t zero_words(int UT, int n, int scan) {
   size_t w = (size_t)UT * kCounters + cut_words(UT);
-  if (scan) w += (size_t)UT * (kBuckets + padded_tiles_of(n)) + (size_t)UT * tiles_of(n) * ((tiles_of(n) + 31) / 32);
+  if (scan) w += (size_t)UT * kBuckets + (size_t)UT * tiles_of(n) * ((tiles_of(n) + 31) / 32);
   return w;
 }
 
@@ -57,6 +57,7 @@ size_t carve(ShallowParams &p, void *ws, int UT, int n) {
   p.before = cv.take<uint16_t>((size_t)UT * ((n + kOrderTokens - 1) / kOrderTokens) * kBuckets);
   p.sk = cv.take<uint8_t>((size_t)UT * p.Tp * kSixBytes);
   const size_t groups = (size_t)UT * ((p.Tp + kBallTiles - 1) / kBallTiles);
+  p.etile = cv.take<uint32_t>((size_t)UT * p.Tp);
   p.tnorm = cv.take<float>((size_t)UT * p.Tp);
   p.skc = cv.take<uint8_t>(groups * 3 * kSixBytes);
   p.ball = cv.take<float2>(groups * kBalls);
@@ -78,14 +79,12 @@ size_t carve(ShallowParams &p, void *ws, int UT, int n) {
   p.ccand = cv.take<uint2>(N * 2 * kCandCap);
   p.pairs_exact = cv.take<unsigned>((size_t)UT * p.T * rows_waves(UT, p.T));
   // everything that must start at zero sits together at the end:
-  // counters [UT][kCounters], ovf_cnt [UT], then (scan) total [UT][kBuckets],
-  // etile [UT][Tp], tpairs [UT][T][TW]
+  // counters [UT][kCounters], ovf_cnt [UT], then (scan) total [UT][kBuckets], tpairs [UT][T][TW]
   p.counters = cv.take<int>(zero_words(UT, n, 1));
   int *tail = p.counters ? p.counters + (size_t)UT * kCounters : nullptr;
   p.ovf_cnt = reinterpret_cast<unsigned *>(tail);
   p.total = reinterpret_cast<uint32_t *>(tail ? tail + cut_words(UT) : nullptr);
-  p.etile = p.total ? p.total + (size_t)UT * kBuckets : nullptr;
-  p.tpairs = p.etile ? p.etile + (size_t)UT * p.Tp : nullptr;
+  p.tpairs = p.total ? p.total + (size_t)UT * kBuckets : nullptr;
   return cv.total();
 }
 
@@ -199,7 +198,7 @@ spindle_status run_shallow(int phases,
     p.refine_cuts = (p.stages_per_item + to_refine - 1) / to_refine;
   }
   if (phases & kPhaseGraph) {
-    // zero: counters, and where there is a scan its errors and marks; codebooks
+    // zero: counters, and where there is a scan its counts and marks; codebooks
     const size_t nzero = zero_words(p.UT, n, p.scan);
     const size_t cpieces = (size_t)U * max_codes * kHeadDim * dtype_bytes(p.dtype) / 16;
     if ((s = launch_prep(p, nzero, cpieces, st)) != SPINDLE_OK) return s;

@@ -4,7 +4,7 @@
 namespace spindle {
 namespace {
 
-// Counters, errors and marks zero, n_codes = -1 ("not finished"), codebooks zero: every thread of the launch writes
+// Counters, counts and marks zero, n_codes = -1 ("not finished"), codebooks zero: every thread of the launch writes
 // its share.  (As a launch of its own it took 3 to 6 us of every call, most of it the launch.)  A short problem with a
 // large table has blocks behind its tokens that do nothing else, as many as leave a thread kClearPieces pieces, and no more
 // than the chip has compute units: the call for 64 fp16 tokens with tables of 16384 and 65536 rows 69 and 160 us by the
