@@ -171,3 +171,53 @@ def test_selection_takes_time_in_proportion_to_the_context(H):
         took.append(parity.least_us(lambda: plan.run(K, K, Q)))
     print("units", H, "contexts of 65536, 524288", [round(t, 1) for t in took], flush=True)
     assert took[1] < 9 * took[0]
+
+
+@pytest.mark.parametrize("dtype,H", [("f16", 5), ("f32", 5), ("bf16", 20)])
+def test_budgets_and_padding_of_long_contexts(oracle, dtype, H):
+    # more than 16384 positions, a ragged last segment; five units are selected by several workgroups each, twenty by one.
+    # Only the window, one more, a few, half, all but one, all and more than all; rows behind what is kept
+    # are -1 and zeros; with and without V
+    l, lw = 20011, 16
+    L = wl.small_random(10, dtype, B=1, H=H, l=l, hn=1, lw=lw, pool=7, budget=lw)
+    some = [lw, lw + 1, 300, l // 2, l - 1, l, l + 5]
+    budgets = [some[u % len(some)] for u in range(H)]
+    if H == 5:
+        budgets = [lw, 300, l // 2, l - 1, l + 5]
+    kept, Ko, Vo, sc = parity.gpu_deep(L, budget=lw, budgets=budgets, out_stride=l + 3)
+    for u, bud in enumerate(budgets[:len(some)]):
+        one = wl.Layer(dtype, L.K[:, u:u + 1], L.V[:, u:u + 1], L.Qw[:, u:u + 1], 1, lw, 7, min(bud, l), 64)
+        p64, k64 = parity.oracle_deep(oracle, one, min(bud, l))
+        parity.check_deep_unit(p64[0, 0], k64[0, 0], sc[0, u], kept[0, u], lw, l, {})
+        n = min(bud, l)
+        assert np.array_equal(Ko[0, u, :n], L.K[0, u][kept[0, u, :n]]) and not Ko[0, u, n:].any()
+        assert np.array_equal(Vo[0, u, :n], L.V[0, u][kept[0, u, :n]]) and not Vo[0, u, n:].any()
+    import torch
+    from paper_2507_06517_amd import binding as sb
+    K, Q = (sb.to_device(x, dtype) for x in (L.K, L.Qw))
+    alone = sb.compress_deep(K, None, Q, 1, dtype, lw, 7, lw, scale=parity.scale_of(128), out_stride=l + 3,
+                             budgets=torch.tensor(budgets, dtype=torch.int32, device="cuda"))
+    assert np.array_equal(alone[0].cpu().numpy(), kept) and np.array_equal(sb.to_host_bits(alone[1], dtype), Ko) and alone[2] is None
+
+
+@pytest.mark.parametrize("H,l", [(30, 17000), (2, 70000), (8, 70000)])
+def test_ties_and_no_ties_over_several_trips(H, l):
+    # one workgroup per unit and several, keys of one trip and of more.  Zero queries: without the divisor all scores tie and the
+    # first win, with it the last ones; units of different budgets
+    import torch
+    from paper_2507_06517_amd import binding as sb
+    lw = 16
+    K = torch.randn((1, H, l, 128), device="cuda", dtype=torch.float16)
+    Q = torch.zeros((1, H, lw, 128), device="cuda", dtype=torch.float16)
+    k = [1 + (u * 9973) % (l - lw) for u in range(H)]
+    budgets = torch.tensor([lw + x for x in k], dtype=torch.int32, device="cuda")
+    for norm in (0, 1):
+        kept, Ko, _, _ = sb.compress_deep(K, None, Q, 1, "f16", lw, 7, lw, norm=norm, budgets=budgets, out_stride=l, want_scores=False)
+        for u in range(H):
+            # (a score is the largest of the seven around it: with the divisor the last four tie, the first of them wins)
+            first = 0 if norm else l - lw - k[u]
+            got = kept[0, u]
+            assert (got[k[u]:k[u] + lw] == torch.arange(l - lw, l, device="cuda")).all() and (got[k[u] + lw:] == -1).all()
+            if norm or k[u] > 3:
+                assert (got[:k[u]] == torch.arange(first, first + k[u], device="cuda")).all()
+            assert torch.equal(Ko[0, u, :k[u] + lw], K[0, u][got[:k[u] + lw].long()]) and not Ko[0, u, k[u] + lw:].any()

@@ -414,3 +414,31 @@ def test_fewer_tokens_take_less():
         took.append(parity.least_us(lambda: plan.run(K, K), calls=20))
     print("32768 and 34816 tokens", [round(t, 1) for t in took], flush=True)
     assert took[0] < 0.97 * took[1]
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
+def test_odd_rows_where_balls_are_asked(oracle, dtype):
+    # rows of NaN, infinity and zeros, subnormal and huge ones in a call large enough for the balls: their sketches say nothing,
+    # so nothing may be excluded for their tiles, whatever centre and radius such a tile gets
+    H, l = 64, 4000
+    L = wl.small_random(77, dtype, B=1, H=H, l=l, lw=1, cap=l, n_centroids=30, noise_frac=0.2)
+    small, big = {"f16": (2.0 ** -20, 512.0), "bf16": (2.0 ** -60, 2.0 ** 58), "f32": (2.0 ** -105, 2.0 ** 104)}[dtype]
+    odd = np.array([0, 1, 2, 3, 900, 901, 2333, l - 2, l - 1])
+    for name in ("K", "V"):
+        x = wl.to_f64(getattr(L, name), dtype)
+        x[0, :, 100:110] *= small
+        x[0, :, 1200:1210] *= big
+        x[0, :, 3000:3040] = 0.0
+        for i, t in enumerate(odd):
+            x[0, :, t, i::17] = (np.nan, -np.nan, np.inf, -np.inf)[i % 4]
+        with np.errstate(over="ignore", invalid="ignore"):
+            setattr(L, name, wl.cast(x, dtype))
+    g = parity.gpu_shallow(L)
+    for t, X, theta in (("k", L.K, L.theta_k), ("v", L.V, L.theta_v)):
+        for h in (0, H - 1):
+            adj = np.unpackbits(g[f"adj_{t}"][0, h].view(np.uint8), axis=1, bitorder="little")[:, :l]
+            assert np.array_equal(adj, adj.T)
+            assert np.array_equal(adj[odd], np.eye(l, dtype=np.uint8)[odd])
+            o = oracle.shallow_unit(wl.to_f64(X[0, h], dtype), float(np.float32(theta)), l)
+            assert np.array_equal(g[f"deg_{t}"][0, h], o["deg"]) and np.array_equal(g[f"ref_{t}"][0, h], o["ref"])
+            assert g[f"n_codes_{t}"][0, h] == o["n_codes"]
