@@ -131,6 +131,8 @@ __device__ __forceinline__ int seg_sum(int v) {             // over a segment, r
 // quad takes its four words one after the other, each lane 16 of the 64 bytes, so that a load of the wave touches 16 lines
 // and not 64 (one-hop maxima of 128 problems of 8192 tokens in clusters of 128, both rounds: 90 us with a word per lane, 60 now;
 // the largest key of every half tile and whose it is, asked first, takes 50 there and half as long again in small calls).
+// Steps without a bit in any lane's word are left out by the callers: rows that hold the bits of all half tiles are mostly empty where
+// a graph has several clusters (4 problems of 8192 tokens in two, both rounds, 208 us with such steps, 167 now; in one, 295, 255).
 __device__ __forceinline__ uint32_t quad_max(const uint32_t *a, uint32_t word, uint32_t m) {
   const int piece = lane_id() & 3;
   uint32_t w[4];
@@ -153,18 +155,6 @@ __device__ __forceinline__ uint32_t quad_max(const uint32_t *a, uint32_t word, u
   return m;
 }
 
-// Where a row is dense, a lane takes a half tile (or word) of its own, four in flight: the lanes' half tiles follow each
-// other, and instructions count, of which quad_max has half as many again.  Two grid rounds of 4 problems of 8192 tokens
-// in two clusters 208 us by quads and 143 so, of 2 of 40515 tokens with a common mean 1823 and 1420.
-template <typename L>
-__device__ __forceinline__ uint32_t dense_max(const uint32_t *a, const Row &r, int sl, L look, uint32_t m) {
-  for_words(r, sl, [&](uint32_t w) {
-    w = look(w);
-    if (w & 0xFFFFu) m = masked_max(a, w, m);
-  });
-  return m;
-}
-
 // Bit s of the result: `on` of segment s (0..7), given in the segment's first lane.
 __device__ __forceinline__ uint32_t seg_bits(bool on) {
   const unsigned long long m = __ballot(on && (lane_id() & (kSegW - 1)) == 0);
@@ -176,8 +166,8 @@ __device__ __forceinline__ uint32_t seg_bits(bool on) {
 // ---------------------------------------------------------------- grid rounds
 // Wave index within a problem = word of the bit arrays = 32 positions; pass k of 4 takes positions
 // 8 k .. 8 k + 7 of it, one per segment.
-// (Eight waves per SIMD: 128 problems of 8192 tokens in clusters, both rounds 90 us, with the registers for six, the next word on
-// its way, 97.)
+// (Eight waves per SIMD: 128 problems of 8192 tokens in clusters, both rounds 90 us; with the registers for six, the next word
+// on its way and dense rows by a half tile per lane 97, and 16 problems of 32768 similar tokens 4.5 ms, not 3.35.)
 __global__ __launch_bounds__(kPhaseThreads, 8) void merge_onehop(ShallowParams p, int round) {
   const int ut = blockIdx.y, W = (int)blockIdx.x * (kPhaseThreads / kWave) + (int)(threadIdx.x >> 6);
   if (W >= p.T) return;
@@ -201,22 +191,6 @@ __global__ __launch_bounds__(kPhaseThreads, 8) void merge_onehop(ShallowParams p
     r[k] = row_at(p, base, lists, v);
     own[k] = key[v];
   }
-  if (__any(r[0].dense | r[1].dense | r[2].dense | r[3].dense)) {
-    uint32_t bits = 0;
-#pragma unroll 1
-    for (int k = 0; k < 4; ++k) {                      // (anew: what a rolled loop counts over cannot stay in registers)
-      const int v = W * kTile + 8 * k + seg;
-      const bool here = live >> (8 * k + seg) & 1;
-      const uint32_t key_v = here ? key[v] : 0u;
-      uint32_t m = key_v;
-      if (here) m = dense_max(key, row_at(p, base, lists, v), sl, [](uint32_t w) { return w; }, m);
-      m = seg_max(m);
-      if (here && sl == 0) m1[v] = m;
-      bits |= seg_bits(here && m == key_v) << (8 * k);
-    }
-    if (lane == 0) cand[W] = bits;
-    return;
-  }
   // (a token without neighbours needs none of its words)
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
@@ -227,7 +201,10 @@ __global__ __launch_bounds__(kPhaseThreads, 8) void merge_onehop(ShallowParams p
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
     uint32_t m = quad_max(key, w0[k], own[k]);        // a token is its own neighbour
-    for (int i = sl + kSegW; __any(i < r[k].n); i += kSegW) m = quad_max(key, i < r[k].n ? word_at(r[k], i) : 0, m);
+    for (int i = sl + kSegW; __any(i < r[k].n); i += kSegW) {
+      const uint32_t w = i < r[k].n ? word_at(r[k], i) : 0;
+      if (__any(w & 0xFFFFu)) m = quad_max(key, w, m);
+    }
     m = seg_max(m);
     if (on[k] && sl == 0) m1[W * kTile + 8 * k + seg] = m;
     bits |= seg_bits(on[k] && m == own[k]) << (8 * k);
@@ -273,8 +250,10 @@ __global__ __launch_bounds__(kPhaseThreads, 8) void merge_twohop(ShallowParams p
     const uint32_t ku = key[u];
     uint32_t m = 0;
     auto here = [&](uint32_t w) { return (w & 0xFFFF0000u) | still(live, w); };   // neighbours still there at the start of the round
-    if (__any(r.dense)) m = dense_max(m1, r, sl, here, m);
-    else for (int i = sl; __any(i < r.n); i += kSegW) m = quad_max(m1, here(i < r.n ? word_at(r, i) : 0), m);
+    for (int i = sl; __any(i < r.n); i += kSegW) {
+      const uint32_t w = here(i < r.n ? word_at(r, i) : 0);
+      if (__any(w & 0xFFFFu)) m = quad_max(m1, w, m);
+    }
     const bool pick = on && seg_max(m) == ku;
     bits |= seg_bits(pick) << (8 * k);
     if (pick) {
