@@ -524,7 +524,8 @@ __device__ void radix_step(const uint32_t *src, int nsrc, uint32_t &prefix, int 
 // Bound by latency and by the instructions of one compute unit; loops stay rolled, since a cold kernel also waits for
 // its code (36 KB of it, unrolled with the keys in registers: 1.5 to 3 us more).  The segments of a unit over several
 // workgroups (deep_select and deep_finish, which copies the rows as well) against this and deep_gather, the eviction call, us:
-// one unit of 480 positions 23 and 19, eight of 4064 32 and 25, of 8160 38 and 32, of 16352 44 and 43, 192 of 8160 269 and 241.
+// one unit of 480 positions 27 and 18, eight of 4080 31 and 20, of 8176 34 and 27, of 12272 36 and 30, of 16368 39 and 38, one of
+// 16368 33 and 30, 32 of 16368 79 and 74, 192 of 8176 220 and 200.
 constexpr int kUnitMax = 16384, kUnitRadius = 8;
 constexpr int kUnitStep = 4 * kSelThreads;             // positions of the workgroup per step
 constexpr int kUnitLoads = kUnitMax / kUnitStep;

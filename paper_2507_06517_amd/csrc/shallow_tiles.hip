@@ -654,8 +654,9 @@ __device__ __forceinline__ void put_marks(const ShallowParams &p, int ut, int r0
 // are staged through LDS, eight at a time (fragment order: loads and reads are both linear, no bank conflicts).
 // Tiles that pass are marked in both directions.
 // 16 problems of 32768 tokens in drifting clusters: 280 us with all sketch products, 125 now; 64 of which half of the tokens are
-// isolated 1035 and 575; 128 of 8192 in clusters 210 and 58 (and 12 to 27 more in shallow_window for the balls).  A pair of tiles
-// among all takes 39 cycles of a SIMD, one of its own about 150, mostly latency.
+// isolated 1035 and 567; 128 of 8192 in clusters 210 and 58 (and 12 to 27 more in shallow_window for the balls).  Of those 567 us the
+// questions to the balls are a quarter (17400 cycles per block, by counts and clocks), the dense blocks, where a pair of tiles takes
+// 43 cycles of a SIMD, four tenths, and the pairs by themselves, 165 cycles each, mostly latency, a sixth.
 // A block that finds more than kRefineShare of its column tiles marked (keys with a common component, low
 // thresholds) leaves all of its pairs to shallow_refine.  The panel's own columns don't count, and a
 // run of similar tokens behind them is allowed for: those are true neighbours.
@@ -829,8 +830,10 @@ __global__ __launch_bounds__(kScanThreads, 4) void shallow_scan(ShallowParams p)
   nloose = npairs >> 16;
   npairs &= 0xFFFF;
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  // What tight row tiles are left with their balls will mostly exclude, unless nothing is excluded at all.  A pair of its
-  // own takes three to four times what it does among all.
+  // What tight row tiles are left with their balls will mostly exclude, unless nothing is excluded at all; so a block is
+  // dense by what its loose row tiles are left with.  A pair of its own takes four times what it does among all, yet half
+  // of all such pairs is the better line than a quarter of them, since balls of the panel take some of the rest: 64 problems of
+  // 32768 tokens, half isolated, 542 us (a third 557, a quarter 558); 16 in drifting clusters with noise 0.3 204 (206, 216).
   dense = __builtin_amdgcn_readfirstlane(2 * nloose > (c1 - c0) * kScanPanel || 5 * npairs > 4 * (c1 - c0) * kScanPanel);
 
   if (!dense) {
