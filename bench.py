@@ -2,7 +2,7 @@
 """Throughput of the prefill-time KV reduction pass on one MI355X.
 
 One step = one pass of the whole hot path over one layer of the 32k-context
-workload (the benchmark configuration configs[3]: Mistral-7B-shaped, 8 KV heads x 4 query heads,
+workload (the benchmark configuration: Mistral-7B-shaped, 8 KV heads x 4 query heads,
 head_dim 128, seq_len 32768, fp16, clustered keys/values with drift):
   spindle_compress_deep    (window 64, pool 7, budget 2048)  and
   spindle_compress_shallow (K and V, theta 0.98 / 0.95, codebook cap 2048).
@@ -98,7 +98,7 @@ def time_deep_call(torch, plan, K, V, Q, reps=30):
 
 
 def deep_folded(torch, sb, wl):
-    """The 24 eviction layers of the 8192-token stack (configs[2]) folded into the batch dimension of
+    """The 24 eviction layers of the 8192-token stack folded into the batch dimension of
     ONE call, with the stack's per-layer budgets as per-unit budgets: 192 units."""
     layers = list(range(8, 32))
     Ls = [wl.config3_layer(i) for i in layers]
@@ -114,13 +114,13 @@ def deep_folded(torch, sb, wl):
     l, d = Ls[0].seq_len, Ls[0].head_dim
     nbytes = deep_bytes(len(per_unit), l, d, 2, float(np.mean(per_unit)))
     gbs = nbytes / (ms * 1e-3) / 1e9
-    return {"workload": "configs[2] layers 8-31 as one call: 192 units of 8192 tokens, fp16, budgets 2048 .. 256",
+    return {"workload": "layers 8-31 of a 32-layer stack as one call: 192 units of 8192 tokens, fp16, budgets 2048 .. 256",
             "ms_per_call": ms, "tokens_per_s": len(layers) * l / (ms * 1e-3), "bound": "hbm", "achieved": gbs,
             "peak": PEAK_HBM_GBS, "unit": "GB/s", "frac": gbs / PEAK_HBM_GBS}
 
 
 def config5_layer(torch, sb, wl, cap=4096, steps=8, warmup=3):
-    """One layer of configs[4] (batch 4, bf16, half of the tokens isolated noise, budget = cap), the
+    """One layer of the batched workload (batch 4, bf16, half of the tokens isolated noise, budget = cap), the
     two calls one after the other on one stream: a secondary figure of the same run."""
     L = wl.config5_layer(0, cap)
     K, V, Q = (sb.to_device(x, L.dtype) for x in (L.K, L.V, L.Qw))
@@ -149,7 +149,7 @@ def config5_layer(torch, sb, wl, cap=4096, steps=8, warmup=3):
     units = L.batch * L.n_kv_heads
     nbytes = deep_bytes(units, L.seq_len, L.head_dim, 2, min(L.budget, L.seq_len))
     assert min(shallow.out["n_codes_k"].min().item(), shallow.out["n_codes_v"].min().item()) >= 1
-    out = {"workload": f"configs[4], one layer: batch 4 x {L.seq_len}, bf16, pool 15, budget = cap = {cap}; one stream",
+    out = {"workload": f"one layer, batch 4 x {L.seq_len}, bf16, pool 15, budget = cap = {cap}; one stream",
            "steps": steps, "ms_per_step": ms, "tokens_per_s": L.batch * L.seq_len / (ms * 1e-3), "kernel_ms": per,
            "deep_call_ms": deep_ms, "deep_frac_of_hbm": nbytes / (deep_ms * 1e-3) / 1e9 / PEAK_HBM_GBS}
     del deep, shallow, K, V, Q
@@ -391,11 +391,11 @@ def main():
         "n_gpus": 1, "steps": args.steps, "warmup": args.warmup, "ms_per_step": ms_step,
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
         "dtype": L.dtype, "data": "synthetic",
-        "config": {"workload": (f"configs[3]: Mistral-7B-shaped layer, 8 KV heads x 4 Q heads, head_dim 128, "
+        "config": {"workload": (f"Mistral-7B-shaped layer, 8 KV heads x 4 Q heads, head_dim 128, "
                                 f"seq_len {L.seq_len}, fp16, 256 drifting clusters; deep: window 64, pool 7, "
                                 f"budget 2048; shallow: K and V, theta 0.98/0.95, cap 2048; batch 1")
                    if args.workload == "config4" else
-                   (f"configs[4], one layer: batch 4, 8 KV heads x 4 Q heads, head_dim 128, seq_len {L.seq_len}, "
+                   (f"one layer, batch 4, 8 KV heads x 4 Q heads, head_dim 128, seq_len {L.seq_len}, "
                     f"bf16, half clustered / half noise; deep: window 64, pool 15, budget {L.budget}; "
                     f"shallow: K and V, theta 0.98/0.95, cap {L.max_codes}")},
         "streams": {"one-stream": "one: the eviction call, then the codebook call",
