@@ -157,8 +157,8 @@ struct ShallowParams {
   uint2 *rows;             // [UT][n] first word and number of words of a row; dense rows: kDenseRow | half tiles
   uint32_t *lists;         // [UT][n][list_row]
   int list_row;            // words per row on average
-  int n16;                 // n rounded up to whole half tiles: pitch of key and m1
-  uint32_t *key, *m1;      // [UT][n16] (remaining degree << 16) | (0xFFFF - token), 0 once removed; largest in the neighbourhood
+  int n32;                 // n rounded up to whole tiles: pitch of key and m1 (a dense row has a word for both half tiles of the last)
+  uint32_t *key, *m1;      // [UT][n32] (remaining degree << 16) | (0xFFFF - token), 0 once removed; largest in the neighbourhood
   uint32_t *live[3];       // [UT][T] bit per position: still there at the start of round 0, 1, 2
   uint32_t *picked;        // [UT][T] bit per position: became a codebook entry
   uint32_t *pick_key;      // [UT][n] key of a picked position at pick time; slot = position of a token's entry

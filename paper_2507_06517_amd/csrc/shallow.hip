@@ -64,7 +64,7 @@ size_t carve(ShallowParams &p, void *ws, int UT, int n) {
   p.second = cv.take<uint8_t>(groups * kTile);
   p.todo = cv.take<uint32_t>(scan_blocks(p));
   p.alive = cv.take<int>(N);
-  p.n16 = (n + 15) & ~15;
+  p.n32 = p.T * kTile;
   for (int r = 0; r < 3; ++r) p.live[r] = cv.take<uint32_t>((size_t)UT * p.T);
   p.slot = cv.take<int>(N);
   p.cand = cv.take<int>(N);
@@ -72,8 +72,8 @@ size_t carve(ShallowParams &p, void *ws, int UT, int n) {
   p.picked = cv.take<uint32_t>((size_t)UT * p.T);
   p.rank = cv.take<int>(N);
   p.rank_vert = cv.take<int>(N);
-  p.key = cv.take<uint32_t>((size_t)UT * p.n16);
-  p.m1 = cv.take<uint32_t>((size_t)UT * p.n16);
+  p.key = cv.take<uint32_t>((size_t)UT * p.n32);
+  p.m1 = cv.take<uint32_t>((size_t)UT * p.n32);
   p.pick_key = cv.take<uint32_t>(N);
   p.ovf = cv.take<uint32_t>(N);
   p.ccand = cv.take<uint2>(N * 2 * kCandCap);

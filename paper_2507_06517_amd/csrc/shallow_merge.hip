@@ -179,8 +179,8 @@ __global__ __launch_bounds__(kPhaseThreads, 8) void merge_onehop(ShallowParams p
     return;
   }
   const size_t base = (size_t)ut * p.n;
-  const uint32_t *key = p.key + (size_t)ut * p.n16, *lists = p.lists + base * p.list_row;
-  uint32_t *m1 = p.m1 + (size_t)ut * p.n16;
+  const uint32_t *key = p.key + (size_t)ut * p.n32, *lists = p.lists + base * p.list_row;
+  uint32_t *m1 = p.m1 + (size_t)ut * p.n32;
   Row r[4];
   uint32_t w0[4], own[4];
   bool on[4];
@@ -223,7 +223,7 @@ __global__ __launch_bounds__(kPhaseThreads, 8) void merge_twohop(ShallowParams p
     if (round == 0 && lane == 0) *picked = 0;
     return;
   }
-  const uint32_t *key = p.key + (size_t)ut * p.n16, *m1 = p.m1 + (size_t)ut * p.n16;
+  const uint32_t *key = p.key + (size_t)ut * p.n32, *m1 = p.m1 + (size_t)ut * p.n32;
   const uint32_t *lists = p.lists + base * p.list_row, *live = p.live[round] + (size_t)ut * p.T;
   uint32_t *next[2] = {p.live[1] + (size_t)ut * p.T, p.live[2] + (size_t)ut * p.T};
   int *slot = p.slot + base;
@@ -284,7 +284,7 @@ __global__ __launch_bounds__(kPhaseThreads) void merge_update(ShallowParams p, i
   const uint32_t now = __builtin_amdgcn_readfirstlane(next[W]);
   if (was == 0) return;
   const size_t base = (size_t)ut * p.n;
-  uint32_t *key = p.key + (size_t)ut * p.n16 + W * kTile;
+  uint32_t *key = p.key + (size_t)ut * p.n32 + W * kTile;
   const uint32_t *lists = p.lists + base * p.list_row;
   if (lane < kTile && ((was & ~now) >> lane & 1)) key[lane] = 0;
   if (now == 0) return;
@@ -464,8 +464,8 @@ __device__ __forceinline__ void rank_picks(const ShallowParams &p, int ut, const
   }
   __syncthreads();
   const bool in_lds = 2 * P <= room;
-  uint32_t *src = in_lds ? reinterpret_cast<uint32_t *>(&l + 1) : p.m1 + (size_t)ut * p.n16;
-  uint32_t *dst = in_lds ? src + P : p.key + (size_t)ut * p.n16;
+  uint32_t *src = in_lds ? reinterpret_cast<uint32_t *>(&l + 1) : p.m1 + (size_t)ut * p.n32;
+  uint32_t *dst = in_lds ? src + P : p.key + (size_t)ut * p.n32;
 #pragma unroll 1
   for (int t0 = tid; t0 - tid < n; t0 += kLoads * kMergeThreads) {
     int v[kLoads];
@@ -598,7 +598,7 @@ __global__ __launch_bounds__(kMergeThreads) void shallow_merge(ShallowParams p, 
   const size_t base = (size_t)ut * n;
   const bool keys_in_lds = n <= kKeysInLds;
   int *cnt = p.counters + (size_t)ut * kCounters;
-  uint32_t *gkey = p.key + (size_t)ut * p.n16, *m1 = p.m1 + (size_t)ut * p.n16;
+  uint32_t *gkey = p.key + (size_t)ut * p.n32, *m1 = p.m1 + (size_t)ut * p.n32;
   const int T4 = (T + 3) & ~3;
   Tail w;
   w.lists = p.lists + base * p.list_row;
@@ -640,7 +640,7 @@ __global__ __launch_bounds__(kMergeThreads) void shallow_merge(ShallowParams p, 
   __syncthreads();
   if (sh_n[0] > 0 && keys_in_lds) {
     const u4 *src = reinterpret_cast<const u4 *>(gkey);
-    for (int i = tid; i < p.n16 / 4; i += kMergeThreads) reinterpret_cast<u4 *>(w.key)[i] = src[i];
+    for (int i = tid; i < p.n32 / 4; i += kMergeThreads) reinterpret_cast<u4 *>(w.key)[i] = src[i];
   }
   __syncthreads();
   MERGE_TICK(0)
@@ -724,7 +724,7 @@ spindle_status launch_merge(const ShallowParams &p, hipStream_t st) {
   // LDS: bits picked, live and next, keys; afterwards, in the place of all but the first, the codebook order's arrays
   // and the picks twice, as far as two blocks per compute unit allow or the keys took that much anyway
   const size_t T4 = (size_t)((p.T + 3) & ~3), rank = T4 + sizeof(RankLds) / sizeof(uint32_t);
-  size_t words = 3 * T4 + (n <= kKeysInLds ? (size_t)p.n16 : 0);
+  size_t words = 3 * T4 + (n <= kKeysInLds ? (size_t)p.n32 : 0);
   const size_t want = rank + 2 * (size_t)n, half = 78 * 1024 / sizeof(uint32_t);
   if (words < want) words = want <= half ? want : (words < half ? half : words);
   static LdsLimit lim_merge;                              // raised once per device to the largest size in use

@@ -1236,7 +1236,7 @@ __device__ __forceinline__ void rows_from_memory(const ShallowParams &p, int ut,
   }
   if (lane < r1 - r0) {
     const int row = R * kTile + r0 + lane, tok = (int)p.perm[base + row];
-    p.key[(size_t)ut * p.n16 + row] = ((uint32_t)deg << 16) | (uint32_t)(0xFFFF - tok);
+    p.key[(size_t)ut * p.n32 + row] = ((uint32_t)deg << 16) | (uint32_t)(0xFFFF - tok);
     p.rows[base + row] = make_uint2((uint32_t)row * pitch, words);
     if (p.deg_out[ut / p.U]) p.deg_out[ut / p.U][(size_t)(ut % p.U) * n + tok] = deg;
   }
@@ -1531,7 +1531,7 @@ __global__ __launch_bounds__(kRowsThreads, kCols == 1 && DT != SPINDLE_F32 ? 4 :
   const bool dense = __builtin_amdgcn_readlane(incl, 31) > rows_here * p.list_row;
   const uint32_t first = dense ? (uint32_t)row * p.list_row : (uint32_t)(R * kTile * p.list_row + incl - total);
   if (g == 0 && row_on && member == 0) {
-    p.key[(size_t)ut * p.n16 + row] = ((uint32_t)d << 16) | (uint32_t)(0xFFFF - row_tok);
+    p.key[(size_t)ut * p.n32 + row] = ((uint32_t)d << 16) | (uint32_t)(0xFFFF - row_tok);
     p.rows[base + row] = make_uint2(first, dense ? kDenseRow | (uint32_t)(2 * T) : (uint32_t)total);
     if (p.deg_out[ut / p.U]) p.deg_out[ut / p.U][(size_t)(ut % p.U) * n + row_tok] = d;
   }
