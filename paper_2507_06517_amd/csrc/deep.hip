@@ -449,6 +449,14 @@ constexpr int kSelThreads = 1024;
 constexpr int kSegLen = 2048;        // context positions per workgroup
 constexpr int kHaloMax = 256;        // pooling radius up to which the raw scores of a segment sit in LDS
 constexpr int kCandMax = 8192;       // scores sharing the threshold's bin that are ranked in LDS
+constexpr int kRunsMax = 1024;       // runs that deep_finish counts apart
+constexpr int kWaves = kSelThreads / 64, kBatch = 32;   // of deep_finish, steps of 64 keys that a wave has in flight
+constexpr int kOneTripMax = kWaves * 64 * kBatch;
+
+// base + how many of the bits are those of lanes below this one.
+__device__ __forceinline__ int lanes_below(unsigned long long bits, int base) {
+  return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(bits >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bits, (uint32_t)base));
+}
 
 __device__ __forceinline__ uint32_t orderable(float f) {
   const uint32_t b = __float_as_uint(f);
@@ -804,14 +812,18 @@ __global__ __launch_bounds__(kSelThreads) void deep_select(SelectParams p) {
 // Every workgroup works out what the whole unit's selection comes to, threshold bin from the histogram, exact value of the
 // k-th largest key among the keys of that bin, then writes its share of the kept positions, as many as every other, and copies
 // their rows of K and V.  (By segments of the context, the one that holds most of what is kept copies it alone: the divisor of
-// Eq. 3 has similar keys keep the end of the context.  Calls that keep 2048 random keys, 8 units of 32736 positions 64 us by segments and 51
-// by shares, 32 units 157 and 133.)  Bound by latency.
+// Eq. 3 has similar keys keep the end of the context.  Calls that keep 2048 random keys, 8 units of 32736 positions 64 us by segments and 48
+// by shares, 32 units 156 and 118; without the divisor, positions all over, 48 and 50, 126 and 118.)
+// Bound by latency.  The keys are read once: where a run's kept positions start follows from how many of it are above the bin
+// and from those in the bin, which are in LDS by run, and only the runs that hold some of the share are looked at again (three
+// reads: 8 units of 131040 positions 143 us, now 119, one of 524256 231, now 128).
+// Ranking the keys of the bin by comparing all of them, as deep_select_unit does, takes 40 us where there are a thousand.
 // Where the workgroups of all units would not run at once (finish_blocks), one per unit selects and deep_gather copies (kCopies = false).
-template <bool kCopies>
+template <bool kCopies, bool kOneTrip>
 __global__ __launch_bounds__(kSelThreads) void deep_finish(SelectParams p, GatherParams q) {
   __shared__ int hist[256];
   __shared__ __attribute__((aligned(16))) uint32_t cand[kCandMax];
-  __shared__ int wsum[kSelThreads / 64], wcount[kSelThreads / 64][2];
+  __shared__ int wsum[kWaves], run_gt[kRunsMax], run_eq[kRunsMax];
   __shared__ uint32_t sh_prefix;
   __shared__ int sh_krem, sh_ncand;
   const int blk = blockIdx.x, u = blockIdx.y, tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
@@ -820,28 +832,26 @@ __global__ __launch_bounds__(kSelThreads) void deep_finish(SelectParams p, Gathe
   const int *ghist = p.hist + (size_t)u * kBins;
   int32_t *kept = p.kept + (size_t)u * p.out_stride;
   const int k = kept_context(p, u);
-  const int share = (k + p.nfinish - 1) / p.nfinish;   // (kCopies: a segment's length at most)
+  const int share = (k + p.nfinish - 1) / p.nfinish;   // (kCopies: kCandMax at most)
   const int r0 = min(k, blk * share), r1 = min(k, r0 + share);   // the workgroup's kept positions
 
-  constexpr int kWaves = kSelThreads / 64;
-  constexpr int kBatch = 32;
-  const int run = (((lc + kWaves - 1) / kWaves) + 63) & ~63;      // positions per wave
-  const int w0 = wave * run, w1 = w0 + run < lc ? w0 + run : lc;
-  const bool one_trip = run <= 64 * kBatch;
+  // The unit's keys in runs, dealt to the waves in turn: of thirty-two steps of 64 positions, all loads of which are in flight
+  // together, or a few times that, and shorter ones where every wave has one: then its keys stay in registers for all uses.
+  const int run = kOneTrip ? (((lc + kWaves - 1) / kWaves) + 63) & ~63 : 64 * kBatch * ((lc - 1) / (64 * kBatch * kRunsMax) + 1);
+  const int nruns = (lc + run - 1) / max(run, 1);
   uint32_t x[kBatch];
-  auto load_keys = [&](int b0) {
+  auto load_keys = [&](int b0, int end) __attribute__((always_inline)) {
 #pragma unroll
     for (int i = 0; i < kBatch; ++i) {
       const int a = b0 + 64 * i + lane;
-      x[i] = a < w1 ? pooled[a] : 0u;
+      x[i] = a < end ? pooled[a] : 0u;
     }
   };
   uint32_t prefix = 0;                                 // key of the k-th largest pooled score
   int krem = k;                                        // how many keys equal to it are taken
   uint32_t *mine = cand;                               // [share] positions r0 .. r1 - 1, behind the candidates' last use
-  static_assert(kCandMax >= kSegLen, "a share fits");
   if (k > 0 && k < lc) {
-    if (one_trip) load_keys(w0);
+    if (kOneTrip) load_keys(wave * run, min(lc, (wave + 1) * run));
     // threshold bin: thread t owns four bins, from the top, so that counts add up along the threads
     {
       const int bin0 = kBins - 4 - 4 * tid;
@@ -865,27 +875,43 @@ __global__ __launch_bounds__(kSelThreads) void deep_finish(SelectParams p, Gathe
       prefix = sh_prefix;
       krem = sh_krem;
     }
-    // The unit's keys, dealt to the waves in contiguous runs (the order of the compaction below),
-    // thirty-two 64-position steps per lane and trip, all loads of a trip in flight together.  A
-    // unit of up to 32768 positions is one trip: its keys stay in registers for all three uses.
-    // First use: the keys of the threshold's bin, ranked in LDS when they fit (a few hundred as a
-    // rule), else where they are.
-    for (int b0 = w0; b0 < w1; b0 += 64 * kBatch) {
-      if (!one_trip) load_keys(b0);
-      int own = 0;                                     // (keys past the end are 0, in the lowest bin, which no score has)
+    // First use: the keys of the threshold's bin, ranked in LDS when they fit (a few hundred as a rule), else where they are,
+    // those of a run together; and how many of a run are in higher bins.
+    const uint32_t last = prefix | 0xFFFFFu;           // of the bin
+    for (int r = wave; r < nruns; r += kWaves) {
+      const int end = min(lc, (r + 1) * run);
+      int above = 0, at = 0, n = 0;
+      for (int b0 = r * run; b0 < end; b0 += 64 * kBatch) {
+        if (!kOneTrip) load_keys(b0, end);
+        int own = 0, higher = 0;                       // (keys past the end are 0, in the lowest bin, which no score has)
 #pragma unroll
-      for (int i = 0; i < kBatch; ++i) own += x[i] >> 20 == prefix >> 20;
-      const int incl = lanes_up_to(own);
-      int at = 0;
-      if (lane == 63 && incl) at = atomicAdd(&sh_ncand, incl);
-      at = __builtin_amdgcn_readlane(at, 63) + incl - own;
-      if (own)
+        for (int i = 0; i < kBatch; ++i) {
+          higher += x[i] > last;
+          own += x[i] >= prefix;
+        }
+        own -= higher;
+        const int incl = lanes_up_to(higher << 16 | own), all = __builtin_amdgcn_readlane(incl, 63);
+        n = all & 0xFFFF;
+        above += all >> 16;
+        if (n) {
+          if (lane == 0) at = atomicAdd(&sh_ncand, n);
+          at = __builtin_amdgcn_readfirstlane(at);
+          int to = at + (incl & 0xFFFF) - own;
+          if (own)
 #pragma unroll
-        for (int i = 0; i < kBatch; ++i)
-          if (x[i] >> 20 == prefix >> 20) {
-            if (at < kCandMax) cand[at] = x[i];
-            ++at;
-          }
+            for (int i = 0; i < kBatch; ++i)
+              if (x[i] - prefix <= 0xFFFFFu) {
+                if (to < kCandMax) cand[to] = x[i];
+                ++to;
+              }
+        }
+        if (kOneTrip) break;
+      }
+      if (lane == 0) {
+        run_gt[r] = above;
+        run_eq[r] = (int)((uint32_t)at << 12 | (uint32_t)n);   // where they are, if all fit and the run is one trip
+      }
+      if (kOneTrip) break;
     }
     __syncthreads();
     const int ncand = sh_ncand;
@@ -893,55 +919,97 @@ __global__ __launch_bounds__(kSelThreads) void deep_finish(SelectParams p, Gathe
     const int nsrc = ncand <= kCandMax ? ncand : lc;
     int bits_left = 20;
     while (bits_left > 0) radix_step(src, nsrc, prefix, krem, bits_left, hist, &sh_prefix, &sh_krem);
-    // ordered compaction: everything above the threshold, the first `krem` equal to it.  Counts of the waves first; those
-    // that have some of the workgroup's own then place them by ballots over 64 positions.
-    int ngt = 0, neq = 0;
-    for (int b0 = w0; b0 < w1; b0 += 64 * kBatch) {
-      if (!one_trip) load_keys(b0);
-#pragma unroll
-      for (int i = 0; i < kBatch; ++i) {
-        const bool in = b0 + 64 * i + lane < w1;
-        ngt += in && x[i] > prefix;
-        neq += in && x[i] == prefix;
-      }
-    }
-    ngt = __builtin_amdgcn_readlane(lanes_up_to(ngt), 63);
-    neq = __builtin_amdgcn_readlane(lanes_up_to(neq), 63);
-    if (lane == 0) {
-      wcount[wave][0] = ngt;
-      wcount[wave][1] = neq;
-    }
-    __syncthreads();
-    int gt_seen = 0, eq_seen = 0;
-#pragma unroll
-    for (int w = 0; w < kWaves; ++w) {
-      gt_seen += w < wave ? wcount[w][0] : 0;
-      eq_seen += w < wave ? wcount[w][1] : 0;
-    }
-    const int from = gt_seen + min(eq_seen, krem), to = gt_seen + ngt + min(eq_seen + neq, krem);   // of the wave
-    const unsigned long long below = (1ull << lane) - 1ull;
-    if (from < r1 && to > r0)
-      for (int b0 = w0; b0 < w1; b0 += 64 * kBatch) {
-        if (!one_trip) load_keys(b0);
-#pragma unroll
-        for (int i = 0; i < kBatch; ++i) {
-          const int a = b0 + 64 * i + lane;
-          const bool gt = a < w1 && x[i] > prefix, eq = a < w1 && x[i] == prefix;
-          const unsigned long long mgt = __ballot(gt), meq = __ballot(eq);
-          const int eq_before = eq_seen + __popcll(meq & below);
-          const int at = gt_seen + __popcll(mgt & below) + min(eq_before, krem);
-          if ((gt || (eq && eq_before < krem)) && at >= r0 && at < r1) {
-            if (kCopies) mine[at - r0] = (uint32_t)a;
-            kept[at] = a;
+    // ordered compaction: everything above the threshold, the first `krem` equal to it.  Counts of the runs first, of all of them
+    // from their candidates where these are in LDS, else of 64 at a time up to the last that the workgroup needs;
+    const bool listed = ncand <= kCandMax && run <= 64 * kBatch && prefix != 0;
+    int gt_before = 0, eq_before = 0;
+    for (int s0 = 0; s0 < nruns; ) {
+      const int s1 = listed ? nruns : min(nruns, s0 + 64);
+      for (int r = s0 + wave; r < s1; r += kWaves) {
+        int ngt = 0, neq = 0;
+        if (listed) {
+          const uint32_t rec = (uint32_t)run_eq[r];
+          const int at = (int)(rec >> 12), n = (int)(rec & 0xFFFu);
+          for (int i = lane; i < n; i += 64) {
+            ngt += cand[at + i] > prefix;
+            neq += cand[at + i] == prefix;
           }
-          gt_seen += __popcll(mgt);
-          eq_seen += __popcll(meq);
+        } else {
+          const int end = min(lc, (r + 1) * run);
+          for (int b0 = r * run; b0 < end; b0 += 64 * kBatch) {
+            if (!kOneTrip) load_keys(b0, end);
+            int here = b0 + lane;
+            asm("" : "+v"(here));                      // (the comparisons of the loads are not kept in 64 scalar registers)
+#pragma unroll
+            for (int i = 0; i < kBatch; ++i) {
+              const bool in = here + 64 * i < end;
+              ngt += in && x[i] > prefix;
+              neq += in && x[i] == prefix;
+            }
+            if (kOneTrip) break;
+          }
         }
+        ngt = lanes_up_to(ngt);
+        neq = lanes_up_to(neq);
+        if (lane == 63) {
+          run_gt[r] = (listed ? run_gt[r] : 0) + ngt;
+          run_eq[r] = neq;
+        }
+        if (kOneTrip) break;
       }
+      __syncthreads();
+      // then the places of those runs that hold some of the workgroup's own, by ballots over 64 positions.
+      for (int c0 = s0; c0 < s1; c0 += 64) {
+        const int g = c0 + lane < s1 ? run_gt[c0 + lane] : 0, e = c0 + lane < s1 ? run_eq[c0 + lane] : 0;
+        const int ig = lanes_up_to(g) + gt_before, ie = lanes_up_to(e) + eq_before;   // with the run itself
+        const int from = ig - g + min(ie - e, krem), to = ig + min(ie, krem);
+        unsigned long long todo = __ballot(from < to && from < r1 && to > r0) & (0x0001000100010001ull << wave);
+        static_assert(kWaves == 16, "every sixteenth run is the wave's");
+        for (; todo; todo &= todo - 1) {
+          const int nth = __builtin_ctzll(todo), r = c0 + nth, end = min(lc, (r + 1) * run);
+          const int gt0 = __builtin_amdgcn_readlane(ig - g, nth), eq0 = __builtin_amdgcn_readlane(ie - e, nth);
+          const int eq1 = __builtin_amdgcn_readlane(ie, nth);
+          // (of the keys equal to the threshold a run has all taken, or none, but for one run)
+          const bool some = prefix + 1u <= 1u || (eq0 < krem && eq1 > krem);
+          const uint32_t least = prefix + (eq0 >= krem);
+          int seen = gt0 + min(eq0, krem) - r0, eq_seen = eq0;
+          for (int b0 = r * run; b0 < end; b0 += 64 * kBatch) {
+            if (!kOneTrip) load_keys(b0, end);
+            int here = b0 + lane;
+            asm("" : "+v"(here));
+#pragma unroll
+            for (int i = 0; i < kBatch; ++i) {
+              const int a = here + 64 * i;
+              bool take = x[i] >= least;
+              if (some) {
+                const bool eq = a < end && x[i] == prefix;
+                const unsigned long long meq = __ballot(eq);
+                take = x[i] > prefix || (eq && lanes_below(meq, eq_seen) < krem);
+                eq_seen += __popcll(meq);
+              }
+              const unsigned long long taken = __ballot(take);
+              const int at = lanes_below(taken, seen);
+              if (take && (unsigned)at < (unsigned)(r1 - r0)) {
+                if (kCopies) mine[at] = (uint32_t)a;
+                else kept[r0 + at] = a;
+              }
+              seen += __popcll(taken);
+            }
+            if (kOneTrip) break;
+          }
+          if (kOneTrip) break;
+        }
+        if (kOneTrip) break;
+        gt_before = __builtin_amdgcn_readlane(ig, 63);
+        eq_before = __builtin_amdgcn_readlane(ie, 63);
+      }
+      s0 = s1;
+      if (kOneTrip || gt_before + min(eq_before, krem) >= r1) break;
+    }
   } else {
     for (int i = tid; i < r1 - r0; i += kSelThreads) {
       if (kCopies) mine[i] = (uint32_t)(r0 + i);
-      kept[r0 + i] = r0 + i;
+      else kept[r0 + i] = r0 + i;
     }
   }
   if constexpr (!kCopies) {
@@ -971,8 +1039,8 @@ __global__ __launch_bounds__(kSelThreads) void deep_finish(SelectParams p, Gathe
         const int b = blk * share_behind + i - nkept;  // of the window, then of the padding
         to[j] = k + b;
         idx = b < p.lw ? lc + b : -1;
-        if (t == 0) kept[to[j]] = idx;
       }
+      if (t == 0) kept[to[j]] = idx;
       if (idx >= 0) {
         kv[j] = *reinterpret_cast<const u4 *>(q.K + in + (size_t)idx * (size_t)q.lay.st);
         if (q.V) vv[j] = *reinterpret_cast<const u4 *>(q.V + in + (size_t)idx * (size_t)q.lay.st);
@@ -1064,17 +1132,17 @@ DeepLayout deep_layout(void *ws, int U, int l, int lw, int Rpad, int dtype) {
 }
 
 // Workgroups per unit of deep_finish.  Each reads all keys of its unit, so there are no more of them than run at once on half
-// of the chip (the call may run beside others': three layers of 32768 tokens in a pipeline 2030 us with all of it, 2019 with half).  Then the
-// copies come along for nothing: one per unit and a launch for the copies, and as chosen here, us: 8 units of 32736 positions 51.5, 50.8,
-// 1 of which 16384 are kept 43.5, 41.5, 2 of 131040 86.9, 85.3.  More wait for each other, and what they read grows with the
-// square of the context: 192 units of 32736 positions 672 and, 16 workgroups each, 823, 8 of 131040 144 and 186, of 524256 569 and
-// 1683.  More than four per segment gain nothing.  (A single unit of 524256 positions takes 225 either way: three reads of its keys by one
-// workgroup are most of it.)
+// of the chip (the call may run beside others': three layers of 32768 tokens in a pipeline, all of it against half, 2057 and 2059, on
+// another day 2030 and 2019 us; alone, 16 units of 32736 positions 68 and 69), and as many as have LDS for their places.  Then the copies
+// come along for nothing: 16 units of 32736 positions 69 us (74 by one workgroup each and a launch for the copies), 3 of 99987 62
+// (101), one of 524256 128 (280).  More wait for each other, and what they read grows with the
+// square of the context: 8 of 524256 519 us, as many as segments 1040.  More than four per segment gain nothing.
 constexpr int kFinishBlocks = 128;
 
 int finish_blocks(int U, int nseg) {
   const int each = kFinishBlocks / U;
-  return each < nseg ? 1 : (each < 4 * nseg ? each : 4 * nseg);
+  static_assert(kCandMax >= 4 * kSegLen, "a share of what is kept fits");
+  return each < (nseg + 3) / 4 ? 1 : (each < 4 * nseg ? each : 4 * nseg);
 }
 
 int padded_rows(int R) { return R <= 64 ? 64 : (R <= 128 ? 128 : 256); }
@@ -1218,8 +1286,9 @@ extern "C" spindle_status spindle_compress_deep(const spindle_kv_desc *desc, con
     { ProfScope ps("deep_select", st);
     hipLaunchKernelGGL(deep_select, dim3(nseg, U), dim3(kSelThreads), 0, st, sp); }
     { ProfScope ps("deep_finish", st);
-    if (sp.nfinish > 1) hipLaunchKernelGGL(deep_finish<true>, dim3(sp.nfinish, U), dim3(kSelThreads), 0, st, sp, gp);
-    else hipLaunchKernelGGL(deep_finish<false>, dim3(1, U), dim3(kSelThreads), 0, st, sp, gp); }
+    auto *finish = sp.nfinish > 1 ? (lc <= kOneTripMax ? deep_finish<true, true> : deep_finish<true, false>)
+                                  : (lc <= kOneTripMax ? deep_finish<false, true> : deep_finish<false, false>);
+    hipLaunchKernelGGL(finish, dim3(sp.nfinish, U), dim3(kSelThreads), 0, st, sp, gp); }
     if (sp.nfinish == 1) launch_gather(gp, U, st);
   }
   SPINDLE_HIP(hipGetLastError());

@@ -221,3 +221,26 @@ def test_ties_and_no_ties_over_several_trips(H, l):
             if norm or k[u] > 3:
                 assert (got[:k[u]] == torch.arange(first, first + k[u], device="cuda")).all()
             assert torch.equal(Ko[0, u, :k[u] + lw], K[0, u][got[:k[u] + lw].long()]) and not Ko[0, u, k[u] + lw:].any()
+
+
+@pytest.mark.parametrize("few_rows", [False, True])
+@pytest.mark.parametrize("H,lc", [(2, 32768), (2, 32769), (60, 20000), (3, 70000), (1, 2200000)])
+def test_selection_in_runs(H, lc, few_rows):
+    # keys that stay in registers and one more, one workgroup per unit, runs of several trips (above 2097152 positions); few distinct rows:
+    # more scores share the threshold's bin than fit in LDS, and many of all runs tie with the threshold
+    import torch
+    from paper_2507_06517_amd import binding as sb
+    lw, l = 16, lc + 16
+    g = torch.Generator(device="cuda").manual_seed(lc + few_rows)
+    Q = torch.randn((1, H, lw, 128), generator=g, device="cuda", dtype=torch.float16)
+    K = torch.randn((1, H, 8 if few_rows else l, 128), generator=g, device="cuda", dtype=torch.float16)
+    if few_rows:
+        K = K[:, :, torch.randint(0, 8, (l,), generator=g, device="cuda")].contiguous()
+    k = [1 + (u * 9973 + lc // 3) % (lc - 1) for u in range(H)]
+    budgets = torch.tensor([lw + x for x in k], dtype=torch.int32, device="cuda")
+    kept, Ko, _, sc = sb.compress_deep(K, None, Q, 1, "f16", lw, 1 if few_rows else 7, lw, norm=1, budgets=budgets, out_stride=max(k) + lw)
+    for u in range(H):
+        own = kept[0, u, :k[u]].cpu().numpy()
+        assert np.array_equal(own, parity.lowest_index_topk(sc[0, u, :lc].cpu().numpy(), k[u]))
+        assert (kept[0, u, k[u]:k[u] + lw] == torch.arange(lc, l, device="cuda")).all() and (kept[0, u, k[u] + lw:] == -1).all()
+        assert torch.equal(Ko[0, u, :k[u] + lw], K[0, u][kept[0, u, :k[u] + lw].long()]) and not Ko[0, u, k[u] + lw:].any()
