@@ -532,12 +532,16 @@ __device__ void radix_step(const uint32_t *src, int nsrc, uint32_t &prefix, int 
 // Bound by latency and by the instructions of one compute unit; loops stay rolled, since a cold kernel also waits for
 // its code (36 KB of it, unrolled with the keys in registers: 1.5 to 3 us more).  The segments of a unit over several
 // workgroups (deep_select and deep_finish, which copies the rows as well) against this and deep_gather, the eviction call, us:
-// one unit of 480 positions 27 and 18, eight of 4080 31 and 20, of 8176 34 and 27, of 12272 36 and 30, of 16368 39 and 38, one of
-// 16368 33 and 30, 32 of 16368 79 and 74, 192 of 8176 220 and 200.
+// one unit of 480 positions 24 and 18, eight of 4080 30 and 23, of 8176 32 and 28, of 12272 33 and 32, of 16368 36 and 35, one of
+// 16368 31 and 30, 32 of 16368 67 and 67, 192 of 8176 201 and 187 (random keys; with scores that all tie 26 and 20, 31 and 23, 36 and
+// 30, 40 and 35, 46 and 41, 42 and 38, 77 and 73, 204 and 188).
 constexpr int kUnitMax = 16384, kUnitRadius = 8;
 constexpr int kUnitStep = 4 * kSelThreads;             // positions of the workgroup per step
 constexpr int kUnitLoads = kUnitMax / kUnitStep;
-constexpr int kUnitRank = 1024;                        // keys of one bin that are ranked by comparing all of them
+// Keys of one bin that are ranked by comparing all of them; more by radix passes over the unit's keys, 2 us or so.  Comparing a
+// thousand takes 30: 8 units of 12272 positions with random scores 66 us up to 1024 and 33 up to 128, 32 of 16368 114 and 70, one
+// of 2032 (a few more than 128) 23.7 up to 256 and 20.6.
+constexpr int kUnitRank = 128;
 constexpr int kCopies = 4;                             // of the histogram, by lane, so that equal digits collide less;
 constexpr int kCopyPitch = kBins + 8;                  // in other banks
 __host__ __device__ inline int unit_raw(int lc) { return (lc + kUnitStep - 1) / kUnitStep * kUnitStep + 2 * kUnitRadius; }

@@ -244,3 +244,22 @@ def test_selection_in_runs(H, lc, few_rows):
         assert np.array_equal(own, parity.lowest_index_topk(sc[0, u, :lc].cpu().numpy(), k[u]))
         assert (kept[0, u, k[u]:k[u] + lw] == torch.arange(lc, l, device="cuda")).all() and (kept[0, u, k[u] + lw:] == -1).all()
         assert torch.equal(Ko[0, u, :k[u] + lw], K[0, u][kept[0, u, :k[u] + lw].long()]) and not Ko[0, u, k[u] + lw:].any()
+
+
+@pytest.mark.parametrize("l", [2000, 9000])
+def test_ranking_of_few_and_of_many_keys_of_a_bin(l):
+    # scores that tie by the hundred: from a few to thousands of keys share the bin in which the selection ends, whichever it is
+    import torch
+    from paper_2507_06517_amd import binding as sb
+    lw = 16
+    lc = l - lw
+    rows = [1, 2, 3, 5, 8, 16, 60, 120, 125, 126, 127, 128, 129, 130, 140, 260]
+    g = torch.Generator(device="cuda").manual_seed(l)
+    Q = torch.randn((1, len(rows), lw, 128), generator=g, device="cuda", dtype=torch.float16)
+    K = torch.randn((1, len(rows), l, 128), generator=g, device="cuda", dtype=torch.float16)
+    for u, n in enumerate(rows):                       # every n-th token is one and the same
+        K[0, u, ::n] = K[0, u, :1]
+    for k in (1, lc // 130, lc // 16, lc // 2, lc - 1):
+        kept, _, _, sc = sb.compress_deep(K, None, Q, 1, "f16", lw, 1, lw + k, norm=1)
+        for u in range(len(rows)):
+            assert np.array_equal(kept[0, u, :k].cpu().numpy(), parity.lowest_index_topk(sc[0, u, :lc].cpu().numpy(), k))
