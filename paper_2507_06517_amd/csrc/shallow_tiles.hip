@@ -33,11 +33,13 @@ constexpr int kStepOffset = 3008;
 constexpr float kStepEnd = 0.345f, kStep = 0.388f, kMeanSome = 0.15f, kMeanMost = 1.9f;
 // Tokens that are near no pivot (a cosine of 0.73, the last step from 0.88 on; without the mean, a product of kMeanNear of the
 // length left, between the largest of 1024 unrelated ones and nearly all of a cluster's own) go ahead of the others: what is isolated
-// stands together then and doesn't widen the tiles of what is not.  So do pivots that have no other token, where more than one token in
-// kFarShare is near none, and what a second pivot took of a cluster: a kRemnant-th of what buckets have as a rule, at most kFewest
-// tokens.  More than that is something else, the heavy tokens of clusters in keys with a common mean, and a tile of them is marked for
+// stands together then and doesn't widen the tiles of what is not.  So do small buckets: up to kFewest tokens where more than one token in
+// kFarShare is near no pivot, and otherwise what a second pivot took of a cluster: a kRemnant-th of what buckets have as a rule, at most
+// kFewest.  More than that is something else, the heavy tokens of clusters in keys with a common mean, and a tile of them is marked for
 // ten clusters.  16 problems of 8192 tokens in 128 clusters, a twentieth of them heavy, with a mean of half their length, 4 of 23000 in 200, 2 of
 // 18445 in 26, us per call: with the step above instead of kMeanNear and up to eight tokens to a pivot 220, 203, 243, now 166, 178, 235.
+// (With isolated tokens, single ones only go first: 2 problems of 32768 kept rows of repeated heads, a fifth isolated, 316 us, not 303, of 48000
+// 435 and 424; the 16 problems with a mean, a tenth isolated, 241 and 260.)
 // Where sketches aren't asked (kByVector) all tokens keep to their pivots but for the remnants.
 constexpr int kMeanOf = 128, kNearStep = 5, kFarShare = 16, kRemnant = 128;
 constexpr uint32_t kFewest = 8;
@@ -280,7 +282,7 @@ __global__ __launch_bounds__(kOrderThreads) void shallow_order(ShallowParams p, 
   }
   const uint32_t nfar = count & 0xFFFFu, shared = square / max(1u, count >> 16);   // (shared: 128 of them and more)
   static_assert(kRemnant == 128, "what the squares are shifted by");
-  const uint32_t few = max(nfar * (uint32_t)kFarShare >= (uint32_t)n ? 1u : 0u, min(shared, kFewest));
+  const uint32_t few = nfar * (uint32_t)kFarShare >= (uint32_t)n ? kFewest : min(shared, kFewest);
   // both kinds of buckets at once: those that go first in the low half
   auto half = [&](int bucket, uint32_t x) { return bucket < kPivots || x <= few ? 0 : 16; };
   const int h0 = half(2 * tid, total.x), h1 = half(2 * tid + 1, total.y);

@@ -442,3 +442,39 @@ def test_odd_rows_where_balls_are_asked(oracle, dtype):
             o = oracle.shallow_unit(wl.to_f64(X[0, h], dtype), float(np.float32(theta)), l)
             assert np.array_equal(g[f"deg_{t}"][0, h], o["deg"]) and np.array_equal(g[f"ref_{t}"][0, h], o["ref"])
             assert g[f"n_codes_{t}"][0, h] == o["n_codes"]
+
+
+def test_order_of_repeated_rows_with_isolated_ones():
+    # kept rows of repeated heads, a fifth of them isolated: more clusters than pivots, and small buckets of what second pivots took.
+    # The scan takes 1.26 of what it takes on as many rows of which half are isolated, 1.40 where such buckets stood between the clusters
+    import torch
+    from paper_2507_06517_amd import binding as sb
+    took = []
+    for repeated in (True, False):
+        g = torch.Generator(device="cuda").manual_seed(8)
+        H, kept, C = (32, 1024, 96) if repeated else (1, 32768, 256)
+        G = H // 4 if repeated else 1
+        pool = 2 * kept if repeated else kept
+        centres = torch.randn((G, C, 128), generator=g, device="cuda")
+        at = torch.randint(0, C, (G, pool), generator=g, device="cuda")
+        x = centres.gather(1, at[:, :, None].expand(G, pool, 128)) + 0.1 * torch.randn((G, pool, 128), generator=g, device="cuda")
+        far = torch.rand((G, pool, 1), generator=g, device="cuda") < (0.2 if repeated else 0.5)
+        x = torch.where(far, torch.randn((G, pool, 128), generator=g, device="cuda"), x)
+        if repeated:
+            which = torch.rand((H, pool), generator=g, device="cuda").argsort(1)[:, :kept].sort(1).values
+            x = x.repeat_interleave(4, 0).gather(1, which[:, :, None].expand(H, kept, 128))
+        K = x.half().reshape(1, 1, 32768, 128).contiguous()
+        plan = sb.plan_shallow(K, "f16", 0.98, 0.95, 2048)
+        plan.run(K, K)
+        best = 1e9
+        sb.spindle_profile(1)
+        try:
+            for _ in range(8):
+                plan.run(K, K)
+                torch.cuda.synchronize()
+                best = min(best, sum(ms for name, ms in sb.spindle_profile_read() if name == "shallow_scan") * 1e3)
+        finally:
+            sb.spindle_profile(0)
+        took.append(best)
+    print("scan of repeated rows, of half isolated ones", [round(t, 1) for t in took], flush=True)
+    assert took[0] < 1.33 * took[1]
