@@ -82,15 +82,14 @@ inline int scan_pays(int UT, int n) {
   return n >= 2048 || (n >= 1024 && UT * T * (T - 24) >= 18000);
 }
 // Tile pairs of all problems from which the scan pays for asking the balls around the tiles first, which takes shallow_window
-// and short blocks of shallow_scan some 10 us.  What they exclude depends on the rows (most in clusters, least where
-// many are isolated) and grows with the length, so the line is where calls on the whole cost the same: 108 calls of 0.3 to 2.2
-// million, clusters, drifting ones, a twentieth to half of the tokens isolated, common means, with balls against without: 0.3 to 0.6 1.07, to
-// 0.9 1.06, to 1.2 1.02, to 1.5 1.02, to 1.8 1.00, to 2.2 0.98.  Without and with, us: clusters, 16 problems of 8192 tokens (1.05) 153, 153, of
-// 11000 (1.9) 188, 180 (a third isolated 239, 241), 4 of 23000 (2.1) 178, 164 (half 320, 319), 2 of 28000 (1.5) 160, 155, of 32768 (2.1) 183, 165
-// (a fifth 272, 260), 128 of 4096 (2.1) 304, 291 (a third 394, 414); kept rows of repeated heads, 2 of 32768, 275, 285.
+// and shallow_scan some 10 us.  What they exclude depends on the rows (most in clusters, least where
+// many are isolated) and grows with the length, so the line is where calls on the whole cost the same.  fp16, without balls and with, us: 16 problems
+// of 8192 tokens (1.05 million) in clusters 158, 165, a third isolated 186, 195; 2 of 28000 (1.53) 160, 160 and 254, 257, drifting 273, 277; 16 of
+// 11000 (1.9) 190, 191 and 240, 245, drifting 252, 257; 4 of 23000 (2.1) 174, 169, half isolated 261, 265; 2 of 32768 (2.1) 176, 170, a fifth
+// 223, 217, half 300, 302, kept rows of repeated heads 230, 221; 128 of 4096 (2.1) 301, 299, a third isolated 413, 426, drifting 372, 374.
 inline int balls_pay(int UT, int n) {
   const long T = (n + 31) / 32;
-  return UT * T * T >= 1600000;
+  return UT * T * T >= 2000000;
 }
 // Below kBallMinTheta balls exclude too little: products of unrelated tokens end at about 0.65 for a tile, and the radius
 // and the errors add 0.2.  Calls, fp16, without and with, us, by theta: 64 problems of 8192 tokens in clusters 0.88 356, 319, 0.83 386, 365, 0.8
@@ -146,7 +145,6 @@ struct ShallowParams {
   int T, Tp, TW;           // tiles, rounded up to whole panels; words per row of tpairs
   int scan;                // 1: tokens are sorted and tpairs says which tiles count; 0: all tiles, positions = tokens
   int stages_per_item, njg;   // column stages of a block of the scan, runs of them in a problem
-  int refine_cuts;         // parts of such a block for shallow_refine
   uint32_t *todo;          // [scan_blocks] 1: left to shallow_refine
   int by[2];               // which tile pairs count: kBySketch, kByVector or, all of them, kByNone
   int scan_thr[2];         // theta in sketch units squared

@@ -22,15 +22,6 @@ size_t zero_words(int UT, int n, int scan) {
   return w;
 }
 
-// Stages per block of the scan and of shallow_refine: about so many blocks, that short problems fill the chip too (the longest
-// last about 15 us).
-void cut_stages(ShallowParams &p, int blocks) {
-  const int nI = p.Tp / kScanPanel, nS = p.Tp / kScanStage;
-  const long work = (long)p.UT * nI * (nI + 1) / blocks;
-  p.stages_per_item = work < 1 ? 1 : (work > kScanRun ? kScanRun : (int)work);
-  p.njg = (nS + p.stages_per_item - 1) / p.stages_per_item;
-}
-
 size_t carve(ShallowParams &p, void *ws, int UT, int n) {
   Carver cv(ws);
   const size_t N = (size_t)UT * n;
@@ -38,8 +29,16 @@ size_t carve(ShallowParams &p, void *ws, int UT, int n) {
   p.Tp = padded_tiles_of(n);
   p.TW = (p.T + 31) / 32;
   p.UT = UT;
-  cut_stages(p, 2048);
-  p.refine_cuts = 1;
+  // stages per block of the scan and of shallow_refine: about 2048 blocks, so that short problems fill the chip too (the longest
+  // last about 15 us), and the runs of a panel alike.  With half as many where balls are asked, shallow_scan takes, now and so, us: 128
+  // problems of 4096 tokens in clusters 49 and 37, but a third isolated 78 and 100, 4 of 32768 drifting ones, some isolated, 74 and 87,
+  // 2 of 32768 and of 48000 kept rows of repeated heads 48 and 50, 91 and 90, of 44800 99 and 106, 16 of 14000 with a third
+  // isolated 44 and 47.
+  const int nI = p.Tp / kScanPanel, nS = p.Tp / kScanStage;
+  const long work = (long)UT * nI * (nI + 1) / 2048;
+  p.stages_per_item = work < 1 ? 1 : (work > kScanRun ? kScanRun : (int)work);
+  p.njg = (nS + p.stages_per_item - 1) / p.stages_per_item;
+  p.stages_per_item = (nS + p.njg - 1) / p.njg;
   p.Xe = cv.take<_Float16>((N + 512) * kHeadDim);   // the similarity loop stages up to 5 tiles past the last token
   p.Xh = p.dtype == SPINDLE_F32 ? cv.take<_Float16>(N * kHeadDim) : nullptr;
   p.Xl = p.Xe;                                      // (for shallow_rows only, which is done when entries are written)
@@ -190,12 +189,6 @@ spindle_status run_shallow(int phases,
     p.scan_thr[i] = thr < (double)(1 << 28) ? (int)floor(thr) : 1 << 28;
     p.asks[i] = p.by[i] == kBySketch && p.theta[i] >= kBallMinTheta && balls_pay(p.UT, n);
     p.balls |= p.asks[i];
-  }
-  // (where balls are asked, what a block does before its first products is more; never more blocks than `todo` has room for)
-  if (p.balls) {
-    const int to_refine = p.stages_per_item;
-    cut_stages(p, 1024);
-    p.refine_cuts = (p.stages_per_item + to_refine - 1) / to_refine;
   }
   if (phases & kPhaseGraph) {
     // zero: counters, and where there is a scan its counts and marks; codebooks

@@ -998,9 +998,8 @@ __global__ __launch_bounds__(kRefineThreads, 2) void shallow_refine(ShallowParam
       total += x;
     }
     __syncthreads();
-    // items are cut along their columns too: to what they are where no balls are asked (64 problems of 8192 tokens by blocks twice that
-    // long 747 us, not 612), and, few ones, as long as there are blocks without any (one item by two blocks: 30 us)
-    int cuts = p.refine_cuts;
+    // few items are cut along their columns too, as long as there are blocks without any (one item by two blocks: 30 us)
+    int cuts = 1;
     while (cuts < kScanRun / 2 && 4 * cuts * total <= nslots) cuts *= 2;
     for (int at = slot; at < 2 * cuts * total; at += nslots) {
       ScanItem w = scan_item(p, i0 + list[at / (2 * cuts)], xcd);
