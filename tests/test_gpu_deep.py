@@ -173,9 +173,9 @@ def test_selection_takes_time_in_proportion_to_the_context(H):
     assert took[1] < 9 * took[0]
 
 
-@pytest.mark.parametrize("dtype,H", [("f16", 5), ("f32", 5), ("bf16", 20)])
+@pytest.mark.parametrize("dtype,H", [("f16", 5), ("f32", 5), ("bf16", 20), ("f16", 50)])
 def test_budgets_and_padding_of_long_contexts(oracle, dtype, H):
-    # more than 16384 positions, a ragged last segment; five units are selected by several workgroups each, twenty by one.
+    # more than 16384 positions, a ragged last segment; five units are selected by many workgroups each, twenty by six, fifty by one.
     # Only the window, one more, a few, half, all but one, all and more than all; rows behind what is kept
     # are -1 and zeros; with and without V
     l, lw = 20011, 16
@@ -200,7 +200,7 @@ def test_budgets_and_padding_of_long_contexts(oracle, dtype, H):
     assert np.array_equal(alone[0].cpu().numpy(), kept) and np.array_equal(sb.to_host_bits(alone[1], dtype), Ko) and alone[2] is None
 
 
-@pytest.mark.parametrize("H,l", [(30, 17000), (2, 70000), (8, 70000)])
+@pytest.mark.parametrize("H,l", [(30, 17000), (60, 17000), (2, 70000), (8, 70000), (20, 70000)])
 def test_ties_and_no_ties_over_several_trips(H, l):
     # one workgroup per unit and several, keys of one trip and of more.  Zero queries: without the divisor all scores tie and the
     # first win, with it the last ones; units of different budgets
