@@ -466,12 +466,16 @@ __device__ __forceinline__ uint32_t orderable(float f) {
 // Counts, from the top, the digits of the keys `src[0 .. nsrc)` that match `prefix` above
 // `bits_left`, and narrows (prefix, krem) by one digit of width w: afterwards the krem-th
 // largest matching key still matches.  All threads of the block call it with the same arguments.
+// Digits of ten bits where the keys may be in memory: two passes over them for 20 bits, not three (one unit of 524256 positions of which 100000
+// are kept 349 us with digits of eight, 306 now, with scores that all tie 431 and 339); over those in LDS it is the same.
+template <int kDigitBits>
 __device__ void radix_step(const uint32_t *src, int nsrc, uint32_t &prefix, int &krem, int &bits_left, int *hist,
                            uint32_t *sh_prefix, int *sh_krem) {
   const int tid = threadIdx.x, lane = lane_id();
-  const int w = bits_left < 8 ? bits_left : 8, shift = bits_left - w;
+  const int w = bits_left < kDigitBits ? bits_left : kDigitBits, shift = bits_left - w;
   const uint32_t dmask = (1u << w) - 1u;
-  if (tid < 256) hist[tid] = 0;
+  static_assert(1 << kDigitBits <= kSelThreads, "a counter per thread");
+  if (tid < 1 << kDigitBits) hist[tid] = 0;
   __syncthreads();
   constexpr int kAtOnce = 4;                           // independent keys per thread and trip
   for (int a0 = 0; a0 < nsrc; a0 += kAtOnce * kSelThreads) {
@@ -498,9 +502,15 @@ __device__ void radix_step(const uint32_t *src, int nsrc, uint32_t &prefix, int 
   }
   __syncthreads();
   if (tid < 64) {
-    // lane t owns counters 4t .. 4t+3; find the digit at which the count from the top reaches krem
-    const int h0 = hist[4 * tid], h1 = hist[4 * tid + 1], h2 = hist[4 * tid + 2], h3 = hist[4 * tid + 3];
-    const int mine = h0 + h1 + h2 + h3;
+    // lane t owns kPer counters; find the digit at which the count from the top reaches krem
+    constexpr int kPer = (1 << kDigitBits) / 64;
+    int hh[kPer], mine = 0;
+#pragma unroll
+    for (int j = 0; j < kPer; j += 4) {
+      const int4 h = *reinterpret_cast<const int4 *>(hist + kPer * tid + j);
+      hh[j] = h.x; hh[j + 1] = h.y; hh[j + 2] = h.z; hh[j + 3] = h.w;
+      mine += h.x + h.y + h.z + h.w;
+    }
     int above = mine;                                  // inclusive sum over lanes >= t
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
@@ -508,12 +518,11 @@ __device__ void radix_step(const uint32_t *src, int nsrc, uint32_t &prefix, int 
       if (tid + o < 64) above += x;
     }
     above -= mine;                                     // keys in counters of higher lanes
-    const int hh[4] = {h0, h1, h2, h3};
     int run = above;
 #pragma unroll
-    for (int j = 3; j >= 0; --j) {
+    for (int j = kPer - 1; j >= 0; --j) {
       if (run < krem && krem <= run + hh[j]) {
-        *sh_prefix = prefix | ((uint32_t)(4 * tid + j) << shift);
+        *sh_prefix = prefix | ((uint32_t)(kPer * tid + j) << shift);
         *sh_krem = krem - run;
       }
       run += hh[j];
@@ -551,7 +560,7 @@ __global__ __launch_bounds__(kSelThreads) void deep_select_unit(SelectParams p) 
   extern __shared__ __attribute__((aligned(16))) char smem[];
   __shared__ __attribute__((aligned(16))) uint32_t cand[kUnitRank + 4];
   __shared__ int wtotal[2][kSelThreads / 64];
-  __shared__ int hist256[256];
+  __shared__ __attribute__((aligned(16))) int hist256[256];
   __shared__ uint32_t sh_prefix;
   __shared__ int sh_krem, sh_ncand;
   constexpr int kWaves = kSelThreads / 64;
@@ -726,7 +735,7 @@ __global__ __launch_bounds__(kSelThreads) void deep_select_unit(SelectParams p) 
     krem = sh_krem;
   } else {
     int bits_left = 20;
-    while (bits_left > 0) radix_step(keys, kWaves * run, prefix, krem, bits_left, hist256, &sh_prefix, &sh_krem);
+    while (bits_left > 0) radix_step<8>(keys, kWaves * run, prefix, krem, bits_left, hist256, &sh_prefix, &sh_krem);
   }
 
   // ordered compaction: everything above the threshold, then the first `krem` equal to it; both counts in one word
@@ -825,7 +834,7 @@ __global__ __launch_bounds__(kSelThreads) void deep_select(SelectParams p) {
 // Where the workgroups of all units would not run at once (finish_blocks), one per unit selects and deep_gather copies (kCopies = false).
 template <bool kCopies, bool kOneTrip>
 __global__ __launch_bounds__(kSelThreads) void deep_finish(SelectParams p, GatherParams q) {
-  __shared__ int hist[256];
+  __shared__ __attribute__((aligned(16))) int hist[1024];
   __shared__ __attribute__((aligned(16))) uint32_t cand[kCandMax];
   __shared__ int wsum[kWaves], run_gt[kRunsMax], run_eq[kRunsMax];
   __shared__ uint32_t sh_prefix;
@@ -922,7 +931,7 @@ __global__ __launch_bounds__(kSelThreads) void deep_finish(SelectParams p, Gathe
     const uint32_t *src = ncand <= kCandMax ? cand : pooled;
     const int nsrc = ncand <= kCandMax ? ncand : lc;
     int bits_left = 20;
-    while (bits_left > 0) radix_step(src, nsrc, prefix, krem, bits_left, hist, &sh_prefix, &sh_krem);
+    while (bits_left > 0) radix_step<10>(src, nsrc, prefix, krem, bits_left, hist, &sh_prefix, &sh_krem);
     // ordered compaction: everything above the threshold, the first `krem` equal to it.  Counts of the runs first, of all of them
     // from their candidates where these are in LDS, else of 64 at a time up to the last that the workgroup needs;
     const bool listed = ncand <= kCandMax && run <= 64 * kBatch && prefix != 0;
